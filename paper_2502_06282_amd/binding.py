@@ -1,8 +1,11 @@
-"""ctypes binding of libjakiro_verify (argument marshalling only).
+"""Python binding of libjakiro_verify (argument marshalling only).
 
 Function names and argument meaning follow include/jakiro_verify.h.  Tensors
 are torch tensors on the ROCm device; torch is used for device memory and the
-current stream, nothing else.
+current stream, nothing else.  The calls that a decoding loop makes are marshalled
+by the extension module `_native` (csrc/native.cpp): this file gives them their
+names, defaults and documentation.  Size queries, plans and the other host-only
+entry points go through ctypes.
 """
 from __future__ import annotations
 
@@ -152,6 +155,31 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+class _NotBuilt:
+    """Stands in for `_native` until the extension has been built (no fallback path exists)."""
+
+    def __getattr__(self, name):
+        global _n
+        import importlib
+        import torch  # noqa: F401  (the extension links against torch's libraries)
+        try:
+            _n = importlib.import_module("._native", __package__)
+        except ImportError as e:
+            raise RuntimeError(f"{os.path.join(_HERE, '_native.so')} cannot be loaded ({e}): build it with "
+                               "`python -m paper_2502_06282_amd.build` (needs hipcc)") from e
+        _n.set_error_class(JakiroError)
+        return getattr(_n, name)
+
+
+_n = _NotBuilt()
+
+
+def __getattr__(name):
+    if name == "PreparedCall":  # a call with its arguments marshalled once (returned by the prepare_* functions)
+        return _n.PreparedCall
+    raise AttributeError(name)
+
+
 def version() -> str:
     return lib().jk_version().decode()
 
@@ -166,22 +194,10 @@ def _ptr(t) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
-_initialised_devices = set()
-
-
 def _stream_handle(stream) -> Optional[int]:
     """The hipStream_t of `stream` (default: torch's current stream).  The first use on a device also runs
     jk_init there (a short synchronous probe), unless that stream is being captured into a graph."""
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    handle = s.cuda_stream or None
-    dev = torch.cuda.current_device()
-    if dev not in _initialised_devices and not torch.cuda.is_current_stream_capturing():
-        st = lib().jk_init(handle)
-        if st != 0:
-            raise JakiroError(st, "jk_init")
-        _initialised_devices.add(dev)
-    return handle
+    return _n.stream_handle(stream) or None
 
 
 def _new_workspace(nbytes: int, device, stream):
@@ -249,34 +265,15 @@ def tree_verify_attention(q, k_cache, v_cache, k_tree, v_tree, parent, prefix_le
     k_tree, v_tree [B,T,Hkv,D] (same strides); parent int32 [B,T]; prefix_len int32 [B], all on
     the device.  Returns out [B,T,Hq,D] (allocated unless given).  Asynchronous on `stream`
     (default: torch's current stream)."""
-    import torch
-    if k_cache is not None and k_cache.shape[1] == 0:  # an empty cache has no meaningful strides
-        k_cache = v_cache = None
-    if max_prefix_len is None:
-        max_prefix_len = 0 if k_cache is None else int(k_cache.shape[1])
-    if out is None:
-        out = torch.empty_like(q, memory_format=torch.contiguous_format)
-    if k_cache is not None and (k_cache.stride() != v_cache.stride() or k_cache.shape != v_cache.shape):
-        raise ValueError("k_cache and v_cache must share shape and strides")
-    if k_tree.stride() != v_tree.stride() or k_tree.shape != v_tree.shape:
-        raise ValueError("k_tree and v_tree must share shape and strides")
-    if parent.dtype != torch.int32 or prefix_len.dtype != torch.int32:
-        raise TypeError("parent and prefix_len must be int32")
-    if not (parent.is_contiguous() and prefix_len.is_contiguous()):
-        raise ValueError("parent and prefix_len must be contiguous")
-    d = _make_desc(q, k_cache, k_tree, out, scale)
-    need = int(lib().jk_tree_verify_attention_workspace(ctypes.byref(d), int(max_prefix_len)))
-    if need == 0:
-        raise JakiroError(3, "jk_tree_verify_attention_workspace")
     if workspace is None:
+        kc = None if k_cache is None or k_cache.shape[1] == 0 else k_cache
+        bound = max_prefix_len if max_prefix_len is not None else 0 if kc is None else int(kc.shape[1])
+        need = int(lib().jk_tree_verify_attention_workspace(ctypes.byref(_make_desc(q, kc, k_tree, q if out is None else out, scale)),
+                                                            int(bound)))
+        if need == 0:
+            raise JakiroError(3, "jk_tree_verify_attention_workspace")
         workspace = _new_workspace(need, q.device, stream)
-    st = lib().jk_tree_verify_attention(ctypes.byref(d), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(k_tree),
-                                        _ptr(v_tree), _ptr(parent), _ptr(prefix_len), int(max_prefix_len),
-                                        _ptr(out), _ptr(workspace), workspace.numel() * workspace.element_size(),
-                                        _stream_handle(stream))
-    if st != 0:
-        raise JakiroError(st, "jk_tree_verify_attention")
-    return out
+    return _n.attention(q, k_cache, v_cache, None, k_tree, v_tree, parent, prefix_len, max_prefix_len, scale, out, workspace, stream)
 
 
 def accept_path_workspace(batch: int, n_tree: int, vocab: int, mode: int) -> int:
@@ -304,35 +301,13 @@ def accept_path(tree_tokens, parent, target_logits, mode: int = JK_GREEDY, tempe
     """jk_accept_path.  tree_tokens, parent int32 [B,N]; target_logits fp32 [B,N+1,V] contiguous;
     sampling also needs draft_probs fp32 [B,N,V] and uniforms fp32 [B,N+1].
     Returns (path [B,max_depth], accept_len [B], bonus_token [B]) int32 device tensors."""
-    import torch
-    B, N = tree_tokens.shape
-    V = target_logits.shape[-1]
-    if max_depth is None:
-        max_depth = N
-    for t in (tree_tokens, parent):
-        if t.dtype != torch.int32 or not t.is_contiguous():
-            raise TypeError("tree_tokens and parent must be contiguous int32")
-    for t in (target_logits, draft_probs, uniforms):
-        if t is not None and (t.dtype != torch.float32 or not t.is_contiguous()):
-            raise TypeError("logits, draft_probs and uniforms must be contiguous float32")
-    if target_logits.shape != (B, N + 1, V):
-        raise ValueError("target_logits must be [B, N+1, V]")
-    dev = tree_tokens.device
-    path = torch.empty((B, max_depth), dtype=torch.int32, device=dev)
-    alen = torch.empty((B,), dtype=torch.int32, device=dev)
-    bonus = torch.empty((B,), dtype=torch.int32, device=dev)
-    need = accept_path_workspace(B, N, V, mode)
-    if need == 0:
-        raise JakiroError(3, "jk_accept_path_workspace")
     if workspace is None:
-        workspace = _new_workspace(need, dev, stream)
-    st = lib().jk_accept_path(B, N, V, int(max_depth), _ptr(tree_tokens), _ptr(parent), _ptr(target_logits),
-                              int(mode), float(temperature), _ptr(draft_probs), _ptr(uniforms), _ptr(path),
-                              _ptr(alen), _ptr(bonus), _ptr(workspace),
-                              workspace.numel() * workspace.element_size(), _stream_handle(stream))
-    if st != 0:
-        raise JakiroError(st, "jk_accept_path")
-    return path, alen, bonus
+        B, N = tree_tokens.shape
+        need = accept_path_workspace(B, N, target_logits.shape[-1], mode)
+        if need == 0:
+            raise JakiroError(3, "jk_accept_path_workspace")
+        workspace = _new_workspace(need, tree_tokens.device, stream)
+    return _n.accept(tree_tokens, parent, target_logits, mode, temperature, draft_probs, None, uniforms, max_depth, workspace, stream)
 
 
 def accept_path_greedy_static(tree_tokens, parent, target_logits, out_path, out_accept_len, out_bonus_token,
@@ -359,72 +334,25 @@ def accept_path_greedy_static(tree_tokens, parent, target_logits, out_path, out_
         raise JakiroError(st, "jk_accept_path_greedy_static")
 
 
-class PreparedCall:
-    """A C-ABI call with its arguments marshalled once.  `launch()` issues exactly that one
-    library call on the given (default: torch's current) stream: what a decoding loop, or a
-    HIP-graph capture of it, calls per step.  Holds references to every tensor it points to."""
-
-    def __init__(self, fn, where, args, stream_index, keep):
-        self._fn, self._where, self._args, self._si, self._keep = fn, where, list(args), stream_index, keep
-
-    def launch(self, stream=None) -> None:
-        self._args[self._si] = _stream_handle(stream)
-        st = self._fn(*self._args)
-        if st != 0:
-            raise JakiroError(st, self._where)
-
-
 def prepare_tree_verify_attention(q, k_cache, v_cache, k_tree, v_tree, parent, prefix_len, out, workspace,
-                                  max_prefix_len: Optional[int] = None, scale: float = 0.0) -> PreparedCall:
-    """Same arguments as tree_verify_attention with out and workspace given; nothing is launched."""
-    if k_cache is not None and k_cache.shape[1] == 0:
-        k_cache = v_cache = None
-    if max_prefix_len is None:
-        max_prefix_len = 0 if k_cache is None else int(k_cache.shape[1])
-    d = _make_desc(q, k_cache, k_tree, out, scale)
-    args = [ctypes.byref(d), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(k_tree), _ptr(v_tree), _ptr(parent),
-            _ptr(prefix_len), int(max_prefix_len), _ptr(out), _ptr(workspace),
-            workspace.numel() * workspace.element_size(), None]
-    return PreparedCall(lib().jk_tree_verify_attention, "jk_tree_verify_attention", args, 12,
-                        (d, q, k_cache, v_cache, k_tree, v_tree, parent, prefix_len, out, workspace))
-
-
-def _commit_args(k_tree, v_tree, k_cache, v_cache, path, accept_len, prefix_len, advance):
-    import torch
-    B, T, Hkv, D = k_tree.shape
-    if k_tree.dtype == torch.bfloat16:
-        dt = JK_BF16
-    elif k_tree.dtype == torch.float32:
-        dt = JK_F32
-    else:
-        raise TypeError("k_tree must be bfloat16 or float32")
-    if v_tree.stride() != k_tree.stride() or v_cache.stride() != k_cache.stride():
-        raise ValueError("K and V must share strides")
-    for t in (k_tree, k_cache):
-        if t.stride(-1) != 1 and t.shape[-1] > 1:
-            raise ValueError("head_dim must be the contiguous innermost axis")
-    d = AttnDesc(B, T, Hkv, Hkv, D, 0, 0, 0, k_cache.stride(0), k_cache.stride(1), k_cache.stride(2),
-                 k_tree.stride(0), k_tree.stride(1), k_tree.stride(2), 0, 0, 0, 0.0, dt)
-    return d, [_ptr(k_tree), _ptr(v_tree), _ptr(k_cache), _ptr(v_cache), _ptr(path), _ptr(accept_len),
-               int(path.shape[1]), int(k_cache.shape[1]), _ptr(prefix_len), 1 if advance else 0]
+                                  max_prefix_len: Optional[int] = None, scale: float = 0.0) -> "PreparedCall":
+    """Same arguments as tree_verify_attention with out and workspace given; nothing is launched.  Returns a call whose
+    `launch(stream=None)` issues exactly that one library call: what a decoding loop, or a HIP-graph capture of it, calls
+    per step.  It holds references to every tensor it points to."""
+    return _n.prepare_attention(q, k_cache, v_cache, None, k_tree, v_tree, parent, prefix_len, max_prefix_len, scale, out, workspace)
 
 
 def commit_path(k_tree, v_tree, k_cache, v_cache, path, accept_len, prefix_len, advance: bool = True,
                 stream=None) -> None:
     """jk_commit_path: copies the K/V rows of the accepted nodes path[b][:accept_len[b]] to the cache
     positions prefix_len[b]..., in place; advances prefix_len (device int32 [B]) when `advance`."""
-    d, args = _commit_args(k_tree, v_tree, k_cache, v_cache, path, accept_len, prefix_len, advance)
-    st = lib().jk_commit_path(ctypes.byref(d), *args, _stream_handle(stream))
-    if st != 0:
-        raise JakiroError(st, "jk_commit_path")
+    _n.commit(k_tree, v_tree, k_cache, v_cache, None, path, accept_len, prefix_len, advance, 0, stream)
 
 
 def prepare_commit_path(k_tree, v_tree, k_cache, v_cache, path, accept_len, prefix_len,
                         advance: bool = True) -> "PreparedCall":
     """Same arguments as commit_path; nothing is launched."""
-    d, args = _commit_args(k_tree, v_tree, k_cache, v_cache, path, accept_len, prefix_len, advance)
-    return PreparedCall(lib().jk_commit_path, "jk_commit_path", [ctypes.byref(d)] + args + [None], 11,
-                        (d, k_tree, v_tree, k_cache, v_cache, path, accept_len, prefix_len))
+    return _n.prepare_commit(k_tree, v_tree, k_cache, v_cache, None, path, accept_len, prefix_len, advance, 0)
 
 
 def prepare_commit_path_layers(k_trees, v_trees, k_caches, v_caches, path, accept_len, prefix_len,
@@ -436,19 +364,10 @@ def prepare_commit_path_layers(k_trees, v_trees, k_caches, v_caches, path, accep
     for ts in (k_trees, v_trees, k_caches, v_caches):
         if len(ts) != n or any(t.stride() != ts[0].stride() or t.shape != ts[0].shape for t in ts):
             raise ValueError("per-layer tensors must share shape and strides")
-    d, args = _commit_args(k_trees[0], v_trees[0], k_caches[0], v_caches[0], path, accept_len, prefix_len, advance)
     tables = [torch.tensor([t.data_ptr() for t in ts], dtype=torch.int64, device=path.device)
               for ts in (k_trees, v_trees, k_caches, v_caches)]
-    call_args = [ctypes.byref(d), n] + [_ptr(t) for t in tables] + args[4:] + [None]
-    return PreparedCall(lib().jk_commit_path_layers, "jk_commit_path_layers", call_args, 12,
-                        (d, tables, list(k_trees), list(v_trees), list(k_caches), list(v_caches), path, accept_len,
-                         prefix_len))
-
-
-def _paged(k_pool, block_table) -> PagedKV:
-    """k_pool [n_pages, page_size, Hkv, D]; block_table int32 [B, max_blocks] on the device."""
-    return PagedKV(block_table.data_ptr(), int(block_table.shape[1]), int(k_pool.shape[1]), int(k_pool.shape[0]),
-                   int(k_pool.stride(0)))
+    return _n.prepare_commit(k_trees[0], v_trees[0], k_caches[0], v_caches[0], None, path, accept_len, prefix_len, advance, n,
+                             *tables, list(k_trees), list(v_trees), list(k_caches), list(v_caches))
 
 
 def _paged_desc(q, k_pool, k_tree, out, scale):
@@ -461,32 +380,21 @@ def prepare_tree_verify_attention_paged(q, k_pool, v_pool, block_table, k_tree, 
                                         workspace, max_prefix_len: int, scale: float = 0.0) -> "PreparedCall":
     """jk_tree_verify_attention_paged with out and workspace given; nothing is launched.  k_pool, v_pool
     [n_pages, page_size, Hkv, D] (same strides), block_table int32 [B, max_blocks]."""
-    if v_pool.stride() != k_pool.stride():
-        raise ValueError("K and V pools must share strides")
-    d = _paged_desc(q, k_pool, k_tree, out, scale)
-    pg = _paged(k_pool, block_table)
-    args = [ctypes.byref(d), ctypes.byref(pg), _ptr(q), _ptr(k_pool), _ptr(v_pool), _ptr(k_tree), _ptr(v_tree),
-            _ptr(parent), _ptr(prefix_len), int(max_prefix_len), _ptr(out), _ptr(workspace),
-            workspace.numel() * workspace.element_size(), None]
-    return PreparedCall(lib().jk_tree_verify_attention_paged, "jk_tree_verify_attention_paged", args, 13,
-                        (d, pg, q, k_pool, v_pool, block_table, k_tree, v_tree, parent, prefix_len, out, workspace))
+    return _n.prepare_attention(q, k_pool, v_pool, block_table, k_tree, v_tree, parent, prefix_len, int(max_prefix_len), scale, out,
+                                workspace)
 
 
 def tree_verify_attention_paged(q, k_pool, v_pool, block_table, k_tree, v_tree, parent, prefix_len,
                                 max_prefix_len: int, scale: float = 0.0, out=None, workspace=None, stream=None):
     """jk_tree_verify_attention_paged; returns out [B,T,Hq,D] (allocated unless given)."""
-    import torch
-    if out is None:
-        out = torch.empty_like(q)
     if workspace is None:
-        d = _paged_desc(q, k_pool, k_tree, out, scale)
+        d = _paged_desc(q, k_pool, k_tree, q if out is None else out, scale)
         need = int(lib().jk_tree_verify_attention_workspace(ctypes.byref(d), int(max_prefix_len)))
         if need == 0:
             raise JakiroError(3, "jk_tree_verify_attention_workspace")
         workspace = _new_workspace(need, q.device, stream)
-    prepare_tree_verify_attention_paged(q, k_pool, v_pool, block_table, k_tree, v_tree, parent, prefix_len, out,
-                                        workspace, max_prefix_len, scale).launch(stream)
-    return out
+    return _n.attention(q, k_pool, v_pool, block_table, k_tree, v_tree, parent, prefix_len, int(max_prefix_len), scale, out, workspace,
+                        stream)
 
 
 def prepare_commit_path_layers_paged(k_trees, v_trees, k_pools, v_pools, block_table, path, accept_len, prefix_len,
@@ -497,53 +405,17 @@ def prepare_commit_path_layers_paged(k_trees, v_trees, k_pools, v_pools, block_t
     for ts in (k_trees, v_trees, k_pools, v_pools):
         if len(ts) != n or any(t.stride() != ts[0].stride() or t.shape != ts[0].shape for t in ts):
             raise ValueError("per-layer tensors must share shape and strides")
-    kt, kp = k_trees[0], k_pools[0]
-    B, T, Hkv, D = kt.shape
-    dt = JK_BF16 if kt.dtype == torch.bfloat16 else JK_F32
-    d = AttnDesc(B, T, Hkv, Hkv, D, 0, 0, 0, 0, kp.stride(1), kp.stride(2), kt.stride(0), kt.stride(1), kt.stride(2),
-                 0, 0, 0, 0.0, dt)
-    pg = _paged(kp, block_table)
     tables = [torch.tensor([t.data_ptr() for t in ts], dtype=torch.int64, device=path.device)
               for ts in (k_trees, v_trees, k_pools, v_pools)]
-    args = [ctypes.byref(d), ctypes.byref(pg), n] + [_ptr(t) for t in tables] + \
-           [_ptr(path), _ptr(accept_len), int(path.shape[1]), _ptr(prefix_len), 1 if advance else 0, None]
-    return PreparedCall(lib().jk_commit_path_layers_paged, "jk_commit_path_layers_paged", args, 12,
-                        (d, pg, tables, list(k_trees), list(v_trees), list(k_pools), list(v_pools), block_table, path,
-                         accept_len, prefix_len))
+    return _n.prepare_commit(k_trees[0], v_trees[0], k_pools[0], v_pools[0], block_table, path, accept_len, prefix_len, advance, n,
+                             *tables, list(k_trees), list(v_trees), list(k_pools), list(v_pools))
 
 
 def prepare_accept_path(tree_tokens, parent, target_logits, mode, temperature, draft_probs, uniforms, out_path,
-                        out_accept_len, out_bonus_token, workspace) -> PreparedCall:
+                        out_accept_len, out_bonus_token, workspace) -> "PreparedCall":
     """Same arguments as accept_path with outputs and workspace given; nothing is launched."""
-    B, N = tree_tokens.shape
-    V = target_logits.shape[-1]
-    args = [B, N, V, int(out_path.shape[1]), _ptr(tree_tokens), _ptr(parent), _ptr(target_logits), int(mode),
-            float(temperature), _ptr(draft_probs), _ptr(uniforms), _ptr(out_path), _ptr(out_accept_len),
-            _ptr(out_bonus_token), _ptr(workspace), workspace.numel() * workspace.element_size(), None]
-    return PreparedCall(lib().jk_accept_path, "jk_accept_path", args, 16,
-                        (tree_tokens, parent, target_logits, draft_probs, uniforms, out_path, out_accept_len,
-                         out_bonus_token, workspace))
-
-
-def _draft_heads_args(f_top, s_top, w_head, mode, temperature, top_k, alpha, beta, logits, draft_probs,
-                      topk_tokens, topk_probs, workspace):
-    import torch
-    R, two, d = f_top.shape
-    V = w_head.shape[0]
-    if two != 2 or tuple(s_top.shape) != (R, 2) or w_head.shape[1] != d:
-        raise ValueError("f_top [R,2,d], s_top [R,2], w_head [V,d]")
-    for t in (f_top, w_head):
-        if t.dtype != torch.bfloat16 or not t.is_contiguous():
-            raise TypeError("f_top and w_head must be contiguous bfloat16")
-    for t in (s_top, logits, draft_probs, topk_probs):
-        if t is not None and (t.dtype != torch.float32 or not t.is_contiguous()):
-            raise TypeError("s_top, logits, draft_probs and topk_probs must be contiguous float32")
-    if topk_tokens.dtype != torch.int32 or not topk_tokens.is_contiguous():
-        raise TypeError("topk_tokens must be contiguous int32")
-    desc = DraftHeadsDesc(R, d, V, int(top_k), int(mode), float(temperature), float(alpha), float(beta))
-    args = [ctypes.byref(desc), _ptr(f_top), _ptr(s_top), _ptr(w_head), _ptr(logits), _ptr(draft_probs),
-            _ptr(topk_tokens), _ptr(topk_probs), _ptr(workspace), workspace.numel() * workspace.element_size(), None]
-    return desc, args
+    return _n.prepare_accept(tree_tokens, parent, target_logits, mode, temperature, draft_probs, None, uniforms, out_path,
+                             out_accept_len, out_bonus_token, workspace)
 
 
 def draft_heads_workspace(rows: int, d_model: int, vocab: int) -> int:
@@ -556,62 +428,14 @@ def draft_heads(f_top, s_top, w_head, mode: int = JK_HEADS_DECOUPLED, temperatur
     Returns (logits [R,2,V], draft_probs [R,2,V] or None, topk_tokens [R,2,k] int32, topk_probs [R,2,k]).
     `out_probs` (contiguous fp32 [R,2,V], for instance rows of a round's table of draft distributions)
     receives the distributions instead of a new tensor."""
-    import torch
-    R, _, d = f_top.shape
-    V = w_head.shape[0]
-    dev = f_top.device
-    logits = torch.empty((R, 2, V), dtype=torch.float32, device=dev)
-    if out_probs is not None:
-        if tuple(out_probs.shape) != (R, 2, V):
-            raise ValueError("out_probs must be [R, 2, V]")
-        probs = out_probs
-    else:
-        probs = torch.empty((R, 2, V), dtype=torch.float32, device=dev) if want_probs else None
-    tk = torch.empty((R, 2, int(top_k)), dtype=torch.int32, device=dev)
-    tp = torch.empty((R, 2, int(top_k)), dtype=torch.float32, device=dev)
-    need = draft_heads_workspace(R, d, V)
-    if need == 0:
-        raise JakiroError(3, "jk_draft_heads_workspace")
-    ws = torch.empty(need, dtype=torch.uint8, device=dev)
-    desc, args = _draft_heads_args(f_top, s_top, w_head, mode, temperature, top_k, alpha, beta, logits, probs,
-                                   tk, tp, ws)
-    args[-1] = _stream_handle(stream)
-    st = lib().jk_draft_heads(*args)
-    if st != 0:
-        raise JakiroError(st, "jk_draft_heads")
-    return logits, probs, tk, tp
+    return _n.draft_heads(f_top, s_top, w_head, mode, temperature, top_k, alpha, beta, want_probs, out_probs, stream)
 
 
 def prepare_draft_heads(f_top, s_top, w_head, mode, temperature, top_k, alpha, beta, logits, draft_probs,
-                        topk_tokens, topk_probs, workspace) -> PreparedCall:
+                        topk_tokens, topk_probs, workspace) -> "PreparedCall":
     """jk_draft_heads with outputs and workspace given; nothing is launched."""
-    desc, args = _draft_heads_args(f_top, s_top, w_head, mode, temperature, top_k, alpha, beta, logits, draft_probs,
-                                   topk_tokens, topk_probs, workspace)
-    return PreparedCall(lib().jk_draft_heads, "jk_draft_heads", args, 10,
-                        (desc, f_top, s_top, w_head, logits, draft_probs, topk_tokens, topk_probs, workspace))
-
-
-def _moe_args(u, centroids, w_gate, w_up, w_down, f_top, s_top, expert_idx, f_mix, workspace):
-    import torch
-    R, d = u.shape
-    N, F, d2 = w_gate.shape
-    if d2 != d or tuple(centroids.shape) != (N, d) or tuple(w_up.shape) != (N, F, d) or tuple(w_down.shape) != (N, d, F):
-        raise ValueError("u [R,d], centroids [N,d], w_gate/w_up [N,F,d], w_down [N,d,F]")
-    for t in (u, centroids, w_gate, w_up, w_down, f_top, f_mix):
-        if t is not None and (t.dtype != torch.bfloat16 or not t.is_contiguous()):
-            raise TypeError("features and weights must be contiguous bfloat16")
-    if s_top.dtype != torch.float32 or expert_idx.dtype != torch.int32:
-        raise TypeError("s_top float32, expert_idx int32")
-    desc = MoeDesc(R, d, F, N)
-    need = int(lib().jk_moe_experts_workspace(ctypes.byref(desc)))
-    if workspace is None:
-        if need == 0:
-            raise JakiroError(3, "jk_moe_experts_workspace")
-        workspace = torch.empty(need, dtype=torch.uint8, device=u.device)
-    args = [ctypes.byref(desc), _ptr(u), _ptr(centroids), _ptr(w_gate), _ptr(w_up), _ptr(w_down), _ptr(f_top),
-            _ptr(s_top), _ptr(expert_idx), _ptr(f_mix), _ptr(workspace), workspace.numel() * workspace.element_size(),
-            None]
-    return desc, args, workspace
+    return _n.prepare_draft_heads(f_top, s_top, w_head, mode, temperature, top_k, alpha, beta, logits, draft_probs, topk_tokens,
+                                  topk_probs, workspace)
 
 
 def moe_experts_workspace(rows: int, d_model: int, d_ff: int, n_experts: int) -> int:
@@ -620,26 +444,12 @@ def moe_experts_workspace(rows: int, d_model: int, d_ff: int, n_experts: int) ->
 
 def moe_experts(u, centroids, w_gate, w_up, w_down, want_mix: bool = True, stream=None):
     """jk_moe_experts.  Returns (f_top [R,2,d] bf16, s_top [R,2], expert_idx [R,2] int32, f_mix [R,d] bf16 or None)."""
-    import torch
-    R, d = u.shape
-    dev = u.device
-    f_top = torch.empty((R, 2, d), dtype=torch.bfloat16, device=dev)
-    s_top = torch.empty((R, 2), dtype=torch.float32, device=dev)
-    idx = torch.empty((R, 2), dtype=torch.int32, device=dev)
-    f_mix = torch.empty((R, d), dtype=torch.bfloat16, device=dev) if want_mix else None
-    desc, args, ws = _moe_args(u, centroids, w_gate, w_up, w_down, f_top, s_top, idx, f_mix, None)
-    args[-1] = _stream_handle(stream)
-    st = lib().jk_moe_experts(*args)
-    if st != 0:
-        raise JakiroError(st, "jk_moe_experts")
-    return f_top, s_top, idx, f_mix
+    return _n.moe_experts(u, centroids, w_gate, w_up, w_down, want_mix, stream)
 
 
-def prepare_moe_experts(u, centroids, w_gate, w_up, w_down, f_top, s_top, expert_idx, f_mix, workspace) -> PreparedCall:
+def prepare_moe_experts(u, centroids, w_gate, w_up, w_down, f_top, s_top, expert_idx, f_mix, workspace) -> "PreparedCall":
     """jk_moe_experts with outputs and workspace given; nothing is launched."""
-    desc, args, ws = _moe_args(u, centroids, w_gate, w_up, w_down, f_top, s_top, expert_idx, f_mix, workspace)
-    return PreparedCall(lib().jk_moe_experts, "jk_moe_experts", args, 12,
-                        (desc, u, centroids, w_gate, w_up, w_down, f_top, s_top, expert_idx, f_mix, ws))
+    return _n.prepare_moe_experts(u, centroids, w_gate, w_up, w_down, f_top, s_top, expert_idx, f_mix, workspace)
 
 
 class TreeState:
@@ -665,149 +475,50 @@ class TreeState:
 def tree_grow(state: TreeState, frontier_in, cand_tokens, cand_probs, width: int, q_row_base: int, stream=None):
     """jk_tree_grow.  frontier_in int32 [B,n_front] or None (root); cand_tokens int32 / cand_probs fp32
     [B*n_front,2,k].  Returns the next frontier, int32 [B,width]."""
-    import torch
-    B = state.batch
-    n_front = 1 if frontier_in is None else int(frontier_in.shape[1])
-    rows, two, k = cand_tokens.shape
-    if rows != B * n_front or two != 2 or tuple(cand_probs.shape) != (rows, 2, k):
-        raise ValueError("cand_tokens / cand_probs must be [B*n_front, 2, k]")
-    if cand_tokens.dtype != torch.int32 or cand_probs.dtype != torch.float32 or \
-            not cand_tokens.is_contiguous() or not cand_probs.is_contiguous():
-        raise TypeError("cand_tokens contiguous int32, cand_probs contiguous float32")
-    if frontier_in is not None and (frontier_in.dtype != torch.int32 or not frontier_in.is_contiguous()):
-        raise TypeError("frontier_in contiguous int32")
-    out = torch.empty((B, int(width)), dtype=torch.int32, device=cand_tokens.device)
-    d = state.desc()
-    st = lib().jk_tree_grow(ctypes.byref(d), B, n_front, int(k), int(width), int(q_row_base), _ptr(frontier_in),
-                            _ptr(cand_tokens), _ptr(cand_probs), _ptr(out), _stream_handle(stream))
-    if st != 0:
-        raise JakiroError(st, "jk_tree_grow")
-    return out
+    return _n.tree_grow(state.tokens, state.parent, state.score, state.q_row, state.n_nodes, frontier_in, cand_tokens, cand_probs,
+                        width, q_row_base, stream)
 
 
 def tree_grow_tail(state: TreeState, frontier_in, cand_tokens, cand_probs, k1: int, k2: int, width: int,
                    q_row_base: int, stream=None) -> None:
     """jk_tree_grow_tail: children from head 0's lists, grandchildren from head 1's (contrastive mode)."""
-    B = state.batch
-    n_front = 1 if frontier_in is None else int(frontier_in.shape[1])
-    rows, two, k = cand_tokens.shape
-    if rows != B * n_front or two != 2 or tuple(cand_probs.shape) != (rows, 2, k):
-        raise ValueError("cand_tokens / cand_probs must be [B*n_front, 2, k]")
-    d = state.desc()
-    st = lib().jk_tree_grow_tail(ctypes.byref(d), B, n_front, int(k), int(k1), int(k2), int(width), int(q_row_base),
-                                 _ptr(frontier_in), _ptr(cand_tokens), _ptr(cand_probs), _stream_handle(stream))
-    if st != 0:
-        raise JakiroError(st, "jk_tree_grow_tail")
+    _n.tree_grow_tail(state.tokens, state.parent, state.score, state.q_row, state.n_nodes, frontier_in, cand_tokens, cand_probs, k1, k2,
+                      width, q_row_base, stream)
 
 
 def tree_fill_static(state: TreeState, frontier_in, cand_tokens, cand_probs, shape_slot, shape_expert, shape_rank,
                      next_index, q_row_base: int, stream=None):
     """jk_tree_fill_static.  shape_* int32 [n_new] device tensors; next_index int32 [n_next] or None.
     Returns (frontier_out int32 [B,n_next] or None, new_ids int32 [B,n_new])."""
-    import torch
-    B = state.batch
-    n_front = 1 if frontier_in is None else int(frontier_in.shape[1])
-    rows, two, k = cand_tokens.shape
-    if rows != B * n_front or two != 2 or tuple(cand_probs.shape) != (rows, 2, k):
-        raise ValueError("cand_tokens / cand_probs must be [B*n_front, 2, k]")
-    n_new = int(shape_slot.numel())
-    n_next = 0 if next_index is None else int(next_index.numel())
-    dev = cand_tokens.device
-    new_ids = torch.empty((B, n_new), dtype=torch.int32, device=dev)
-    out = torch.empty((B, n_next), dtype=torch.int32, device=dev) if n_next else None
-    d = state.desc()
-    st = lib().jk_tree_fill_static(ctypes.byref(d), B, n_front, int(k), int(q_row_base), _ptr(frontier_in),
-                                   _ptr(cand_tokens), _ptr(cand_probs), _ptr(shape_slot), _ptr(shape_expert),
-                                   _ptr(shape_rank), n_new, _ptr(next_index), n_next, _ptr(out), _ptr(new_ids),
-                                   _stream_handle(stream))
-    if st != 0:
-        raise JakiroError(st, "jk_tree_fill_static")
-    return out, new_ids
+    return _n.tree_fill_static(state.tokens, state.parent, state.score, state.q_row, state.n_nodes, frontier_in, cand_tokens,
+                               cand_probs, shape_slot, shape_expert, shape_rank, next_index, q_row_base, stream)
 
 
 def tree_finalize(state: TreeState, n_keep: int, stream=None):
     """jk_tree_finalize.  Returns (tree_tokens, parent, q_row, old_index) int32 [B,n_keep] and n_valid int32 [B]."""
-    import torch
-    B = state.batch
-    dev = state.tokens.device
-    outs = [torch.empty((B, int(n_keep)), dtype=torch.int32, device=dev) for _ in range(4)]
-    n_valid = torch.empty((B,), dtype=torch.int32, device=dev)
-    d = state.desc()
-    st = lib().jk_tree_finalize(ctypes.byref(d), B, int(n_keep), _ptr(outs[0]), _ptr(outs[1]), _ptr(outs[2]),
-                                _ptr(outs[3]), _ptr(n_valid), _stream_handle(stream))
-    if st != 0:
-        raise JakiroError(st, "jk_tree_finalize")
-    return outs[0], outs[1], outs[2], outs[3], n_valid
+    return _n.tree_finalize(state.tokens, state.parent, state.score, state.q_row, state.n_nodes, n_keep, stream)
 
 
 def gather_draft_probs(q_all, q_row, stream=None):
     """jk_gather_draft_probs.  q_all fp32 [n_rows, V] (contiguous), q_row int32 [B, N] -> fp32 [B, N, V]."""
-    import torch
-    if q_all.dtype != torch.float32 or not q_all.is_contiguous() or q_row.dtype != torch.int32 or \
-            not q_row.is_contiguous():
-        raise TypeError("q_all contiguous float32, q_row contiguous int32")
-    V = q_all.shape[-1]
-    n_rows = q_all.numel() // V
-    B, N = q_row.shape
-    out = torch.empty((B, N, V), dtype=torch.float32, device=q_all.device)
-    st = lib().jk_gather_draft_probs(B, N, V, _ptr(q_all), n_rows, _ptr(q_row), _ptr(out), _stream_handle(stream))
-    if st != 0:
-        raise JakiroError(st, "jk_gather_draft_probs")
-    return out
+    return _n.gather_draft_probs(q_all, q_row, stream)
 
 
 def linear(x, w, residual=None, out_dtype=None, stream=None):
     """jk_linear: x bf16 [m,k], w bf16 [n,k], residual bf16 [m,n] or None -> x @ w.T (+ residual) as bf16
     (default) or float32 (out_dtype=torch.float32)."""
-    import torch
-    m, k = x.shape
-    n = w.shape[0]
-    for t in (x, w, residual):
-        if t is not None and (t.dtype != torch.bfloat16 or not t.is_contiguous()):
-            raise TypeError("x, w and residual must be contiguous bfloat16")
-    if w.shape[1] != k or (residual is not None and tuple(residual.shape) != (m, n)):
-        raise ValueError("x [m,k], w [n,k], residual [m,n]")
-    f32 = out_dtype == torch.float32
-    out = torch.empty((m, n), dtype=torch.float32 if f32 else torch.bfloat16, device=x.device)
-    need = int(lib().jk_linear_workspace(m, n, k))
-    if need == 0:
-        raise JakiroError(3, "jk_linear_workspace")
-    ws = torch.empty(need, dtype=torch.uint8, device=x.device)
-    st = lib().jk_linear(m, n, k, _ptr(x), _ptr(w), _ptr(residual), None if f32 else _ptr(out),
-                         _ptr(out) if f32 else None, _ptr(ws), need, _stream_handle(stream))
-    if st != 0:
-        raise JakiroError(st, "jk_linear")
-    return out
+    f32 = False
+    if out_dtype is not None:
+        import torch
+        f32 = out_dtype == torch.float32
+    return _n.linear(x, w, residual, f32, stream)
 
 
 def accept_path_rows(tree_tokens, parent, target_logits, q_all, q_row, uniforms, temperature: float = 1.0,
                      max_depth: Optional[int] = None, workspace=None, stream=None):
     """jk_accept_path_rows (speculative sampling): like accept_path, with node k of sequence b tested against
     q_all[q_row[b, k]] (q_all fp32 [n_rows, V] contiguous, q_row int32 [B, N]) instead of a dense draft_probs."""
-    import torch
-    B, N = tree_tokens.shape
-    V = target_logits.shape[-1]
-    if max_depth is None:
-        max_depth = N
-    for t in (tree_tokens, parent, q_row):
-        if t.dtype != torch.int32 or not t.is_contiguous():
-            raise TypeError("tree_tokens, parent and q_row must be contiguous int32")
-    for t in (target_logits, q_all, uniforms):
-        if t.dtype != torch.float32 or not t.is_contiguous():
-            raise TypeError("logits, q_all and uniforms must be contiguous float32")
-    if q_all.shape[-1] != V or tuple(q_row.shape) != (B, N):
-        raise ValueError("q_all [n_rows, V], q_row [B, N]")
-    dev = tree_tokens.device
-    path = torch.empty((B, max_depth), dtype=torch.int32, device=dev)
-    alen = torch.empty((B,), dtype=torch.int32, device=dev)
-    bonus = torch.empty((B,), dtype=torch.int32, device=dev)
-    need = accept_path_workspace(B, N, V, JK_SAMPLE)
     if workspace is None:
-        workspace = _new_workspace(need, dev, stream)
-    st = lib().jk_accept_path_rows(B, N, V, int(max_depth), _ptr(tree_tokens), _ptr(parent), _ptr(target_logits),
-                                   JK_SAMPLE, float(temperature), _ptr(q_all), q_all.numel() // V, _ptr(q_row),
-                                   _ptr(uniforms), _ptr(path), _ptr(alen), _ptr(bonus), _ptr(workspace),
-                                   workspace.numel() * workspace.element_size(), _stream_handle(stream))
-    if st != 0:
-        raise JakiroError(st, "jk_accept_path_rows")
-    return path, alen, bonus
+        B, N = tree_tokens.shape
+        workspace = _new_workspace(accept_path_workspace(B, N, target_logits.shape[-1], JK_SAMPLE), tree_tokens.device, stream)
+    return _n.accept(tree_tokens, parent, target_logits, JK_SAMPLE, temperature, q_all, q_row, uniforms, max_depth, workspace, stream)

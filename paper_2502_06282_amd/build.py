@@ -1,38 +1,63 @@
-"""Builds libjakiro_verify.so for gfx950 with hipcc (in-tree, next to this file)."""
+"""Builds libjakiro_verify.so for gfx950 with hipcc and the Python extension _native.so that marshals its calls
+(both in-tree, next to this file)."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
+OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libjakiro_verify.so")
+NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["api.cpp", "tva_bf16.hip", "tva_f32.hip", "tva_combine.hip", "accept.hip", "accept_coop.hip", "commit.hip",
            "draft_head.hip", "draft_tree.hip"]
 # packed-fp32 code generation is switched off for all device code
-FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-inline-asm",  # the LDS-transfer helper names m0 as clobbered on purpose
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
 
-def build(verbose: bool = False) -> str:
-    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc] + FLAGS
-    for s in SOURCES:
-        cmd += ["-x", "hip", os.path.join(CSRC, s)]
-    cmd += ["-o", LIB]
+def _run(cmd, verbose: bool) -> None:
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)
     noise = "is not a recognized feature for this target"
     err = "\n".join(l for l in r.stderr.splitlines() if noise not in l)
     if r.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + err)
+        raise RuntimeError(f"{cmd[0]} failed:\n" + err)
     if verbose and err.strip():
         print(err, file=sys.stderr)
+
+
+def _native_command(output: str):
+    """Host code only: the extension sees torch's C++ headers and the library's C header."""
+    import torch
+    tdir = os.path.dirname(os.path.abspath(torch.__file__))
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(tdir, "include"),
+            "-isystem", os.path.join(tdir, "include", "torch", "csrc", "api", "include"), "-isystem", os.path.join(rocm, "include"),
+            "-isystem", sysconfig.get_paths()["include"], "-c", os.path.join(CSRC, "native.cpp"), "-o", output], os.path.join(tdir, "lib")
+
+
+def build(verbose: bool = False) -> str:
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    os.makedirs(OBJ, exist_ok=True)
+    objects = [os.path.join(OBJ, os.path.splitext(s)[0] + ".o") for s in SOURCES]
+    native_obj = os.path.join(OBJ, "native.o")
+    native_cmd, torch_lib = _native_command(native_obj)
+    jobs = [[hipcc] + FLAGS + ["-x", "hip", "-c", os.path.join(CSRC, s), "-o", o] for s, o in zip(SOURCES, objects)] + [native_cmd]
+    with ThreadPoolExecutor(min(8, int(os.environ.get("MAX_JOBS", "8")))) as pool:
+        list(pool.map(lambda c: _run(c, verbose), jobs))
+    _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objects + ["-o", LIB], verbose)
+    _run(["g++", "-shared", native_obj, "-o", NATIVE, "-L", HERE, "-ljakiro_verify", "-L", torch_lib, "-lc10", "-lc10_hip",
+          "-ltorch_hip", "-ltorch_cpu", "-ltorch", "-ltorch_python", "-lamdhip64", "-Wl,-rpath,$ORIGIN"], verbose)
     return LIB
 
 

@@ -86,7 +86,8 @@ struct PlanModel {
   double merge_kernel_fixed = 3.0, merge_kernel_per_mb = 0.28, merge_kernel_per_mb_busy = 0.4;  // second launch: c3/c2/c5 traces
 };
 
-bool make_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_allowed, AttnPlan* pl) {
+namespace {
+bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_allowed, AttnPlan* pl) {
   static const PlanModel km;
   if (!desc_ok(d) || !shape_supported(d) || max_prefix_len < 0 || max_prefix_len > (1 << 24)) return false;
   const int G = d.n_q_heads / d.n_kv_heads;
@@ -233,6 +234,33 @@ bool make_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_allowe
   pl->part_o_bytes = need_parts ? up(rows * d.head_dim * (d.dtype == JK_BF16 ? 2 : sizeof(float))) : 0;
   pl->part_ml_bytes = need_parts ? up(rows * sizeof(float2)) : 0;
   pl->total_bytes = kAttnHeaderBytes + pl->part_o_bytes + pl->part_ml_bytes;
+  return true;
+}
+}  // namespace
+
+// Pricing up to 128 ways to cut a call costs the host 3 - 10 us, as much as a small call runs on the GPU: a thread
+// keeps the plans of its last shapes (a model's layers all ask for the same one; a draft round for a handful).
+bool make_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_allowed, AttnPlan* pl) {
+  constexpr int kKey = 13, kSlots = 32;
+  struct Entry {
+    int key[kKey];
+    AttnPlan plan;
+  };
+  static thread_local Entry kept[kSlots];  // (a key of zeros names no valid shape: batch >= 1)
+  if (!desc_ok(d)) return false;
+  const Tuning& t = tuning();
+  const int key[kKey] = {d.batch, d.n_tree, d.n_q_heads, d.n_kv_heads, d.head_dim, d.dtype, max_prefix_len, fused_allowed ? 1 : 0,
+                         t.attn_wm, t.attn_wn, t.attn_splits, t.attn_fused, t.attn_deep};
+  unsigned h = 0;
+  for (int v : key) h = (h ^ (unsigned)v) * 0x9E3779B1u;
+  Entry& e = kept[h >> 27];
+  if (std::memcmp(e.key, key, sizeof(key)) != 0) {
+    AttnPlan fresh;
+    if (!compute_attn_plan(d, max_prefix_len, fused_allowed, &fresh)) return false;
+    e.plan = fresh;
+    std::memcpy(e.key, key, sizeof(key));
+  }
+  *pl = e.plan;
   return true;
 }
 
