@@ -15,7 +15,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libjakiro_verify.so")
 NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["api.cpp", "tva_bf16.hip", "tva_f32.hip", "tva_combine.hip", "accept.hip", "accept_coop.hip", "commit.hip",
-           "draft_head.hip", "draft_tree.hip"]
+           "draft_head.hip", "draft_tree.hip", "stream_gemm.hip"]
 # packed-fp32 code generation is switched off for all device code
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

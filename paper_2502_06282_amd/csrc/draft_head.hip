@@ -6,11 +6,10 @@
 //
 // Kernels:
 //   head_inputs_kernel     X[2R (padded to 32), d] bf16 from f_top, s_top (elementwise, tiny)
-//   skinny_gemm_kernel     Y[M, N] fp32 = X[M, K] . W[N, K]^T with M <= 256: the weight matrix
-//                          (gigabytes for an output embedding) is streamed from HBM exactly once;
-//                          both operands are staged HBM/L2 -> LDS in swizzled 64-byte row segments
-//                          and read from there in MFMA layout.  Batched over experts and split
-//                          along k where a projection alone would not fill the chip.
+//   skinny_gemm_kernel     Y[M, N] fp32 = X[M, K] . W[N, K]^T with M <= 192 and very many weight rows: the weight
+//                          matrix (a gigabyte for an output embedding) is streamed from HBM exactly once; both
+//                          operands are staged HBM/L2 -> LDS in swizzled 64-byte row segments and read from there
+//                          in MFMA layout.  All other products run in stream_gemm.hip.
 //   row_parts_kernel, row_finish_kernel   per logits row: maximum, normaliser,
 //                          top-k by value (ties to the lower token id), probabilities.
 //   router_kernel, gated_act_kernel, select_kernel   the draft layer's router (Eq. 2, 5) and what
@@ -89,22 +88,6 @@ struct GemmParams {
   float* y;           // [m][ldy]
   int m, n, k;
   long long ldw, ldy;
-  // batch (blockIdx.y): element offsets between consecutive problems; `sel` (device, may be null):
-  // n_sel problem numbers, a problem that none of them names is switched off (the experts no
-  // row selected; every workgroup scans the list itself: at most 256 entries, and no flag array
-  // that a launch of its own would have to clear first)
-  int batch;
-  long long x_batch, w_batch, y_batch;
-  const int* sel;
-  int n_sel;
-  // a second weight tensor over the same X (the experts' gate and up projections in one launch):
-  // blockIdx.y in [batch, 2 batch) takes w2 / y2
-  const uint16_t* w2;
-  float* y2;
-  // split of the k range (blockIdx.z): every part writes its own partial output, y_split elements
-  // apart; whoever reads y adds them up in a fixed order
-  int ksplit;
-  long long y_split;
 };
 
 typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8_t;
@@ -120,10 +103,10 @@ using dev::wait_vm;
 // and a ring of DX steps of X slabs (shared by the workgroup).
 template <int MB>
 struct GemmCfg {
-  static constexpr int NBW = MB <= 6 ? 2 : 1;
+  static constexpr int NBW = 2;
   static constexpr int STRIP = 8 * 32 * NBW;       // weight rows (output columns) per workgroup
-  static constexpr int DW = NBW == 1 ? 6 : 4;
-  static constexpr int DX = MB <= 3 ? 4 : (MB <= 5 ? 3 : (MB == 6 ? 2 : 3));
+  static constexpr int DW = 4;
+  static constexpr int DX = MB <= 3 ? 4 : (MB <= 5 ? 3 : 2);
   static constexpr int W_STEP = NBW * 2048;        // bytes per wave and step: NBW*32 rows of 64 bytes
   static constexpr int W_WAVE = DW * W_STEP;
   static constexpr int X_STEP = MB * 2048;         // MB*32 rows of 64 bytes
@@ -161,26 +144,11 @@ __global__ __launch_bounds__(kGemmThreads, 1) void skinny_gemm_kernel(GemmParams
   using C = GemmCfg<MB>;
   constexpr int NBW = C::NBW;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];  // the kernel's only LDS: offset 0
-  int e = blockIdx.y;
-  if (e >= p.batch) {
-    e -= p.batch;
-    p.w = p.w2;
-    p.y = p.y2;
-  }
-  if (p.sel) {  // every wave scans the whole list itself: the same answer in all of them, no LDS, no barrier
-    int mine = 0;
-    for (int i = threadIdx.x & 63; i < p.n_sel; i += 64) mine |= (int)(p.sel[i] == e);
-    if (!__any(mine)) return;  // (the whole workgroup: nobody waits at a later barrier)
-  }
-  p.x += (long long)e * p.x_batch;
-  p.w += (long long)e * p.w_batch;
-  p.y += (long long)e * p.y_batch + (long long)blockIdx.z * p.y_split;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 31, h = lane >> 5;
   const long long strip0 = (long long)blockIdx.x * C::STRIP;
   const int n_base = (int)strip0 + wave * 32 * NBW;
-  const int nkb = p.k / kKB / p.ksplit;  // k blocks of this part
-  const int k_first = (int)blockIdx.z * nkb * kKB;
+  const int nkb = p.k / kKB;  // k blocks
   // Workgroups start at different k blocks and wrap around, so that at any moment they ask for
   // different columns of the weight matrix and of X.
   const int kb0 = (int)((blockIdx.x * 5u) % (unsigned)nkb);
@@ -208,13 +176,13 @@ __global__ __launch_bounds__(kGemmThreads, 1) void skinny_gemm_kernel(GemmParams
   const unsigned w_ring = (unsigned)(wave * C::W_WAVE);
 
   auto issue_x = [&](int kb) {
-    const uint16_t* xb = uniform_ptr(p.x + k_first + rot(kb) * kKB);
+    const uint16_t* xb = uniform_ptr(p.x + rot(kb) * kKB);
     const unsigned xs = (unsigned)(C::X_BASE + (kb % C::DX) * C::X_STEP);
     if (cx > 0) dma16(xb, voff_x[0], xs + (unsigned)(wave * 1024));
     if (cx > 1) dma16(xb, voff_x[1], xs + (unsigned)((wave + 8) * 1024));
   };
   auto issue_w = [&](int kb) {
-    const uint16_t* wb = uniform_ptr(w_strip + k_first + rot(kb) * kKB);
+    const uint16_t* wb = uniform_ptr(w_strip + rot(kb) * kKB);
     const unsigned ws = w_ring + (unsigned)((kb % C::DW) * C::W_STEP);
 #pragma unroll
     for (int i = 0; i < C::NWI; ++i) dma16(wb, voff_w[i], ws + (unsigned)(i * 1024));
@@ -301,8 +269,7 @@ hipError_t launch_gemm_mb(const GemmParams& p, hipStream_t stream) {
       e != hipSuccess)
     return e;
   const unsigned grid = (unsigned)((p.n + GemmCfg<MB>::STRIP - 1) / GemmCfg<MB>::STRIP);
-  hipLaunchKernelGGL(skinny_gemm_kernel<MB>, dim3(grid, (unsigned)(p.batch * (p.w2 ? 2 : 1)), (unsigned)p.ksplit), dim3(kGemmThreads),
-                     GemmCfg<MB>::SMEM, stream, p);
+  hipLaunchKernelGGL(skinny_gemm_kernel<MB>, dim3(grid), dim3(kGemmThreads), GemmCfg<MB>::SMEM, stream, p);
   return hipGetLastError();
 }
 
@@ -314,10 +281,15 @@ hipError_t launch_gemm(const GemmParams& p, hipStream_t stream) {
     case 4: return launch_gemm_mb<4>(p, stream);
     case 5: return launch_gemm_mb<5>(p, stream);
     case 6: return launch_gemm_mb<6>(p, stream);
-    case 7: return launch_gemm_mb<7>(p, stream);
-    case 8: return launch_gemm_mb<8>(p, stream);
     default: return hipErrorInvalidValue;
   }
+}
+
+// Where strips of 512 weight rows alone give most CUs a workgroup this kernel is the better one: 128256 x 4096 with 20
+// rows 177 us against 180, with 160 rows 234 against 252; 100000 x 4096 143 against 154.  80000 x 4096 (157 strips) is
+// not: 130 against 125.
+bool gemm_fits(int m, int n) {
+  return m <= 192 && (long long)(n + GemmCfg<1>::STRIP - 1) / GemmCfg<1>::STRIP * 4 >= 3LL * device_cu_count();
 }
 
 // ------------------------------------------------------------------ softmax + top-k per logits row
@@ -333,7 +305,9 @@ constexpr int kPartMax = kPartThreads * kPartPerThread;        // 8 192
 constexpr int kMaxTopK = 16;
 
 struct SoftParams {
-  const float* logits;  // [n_rows][vocab]
+  float* logits;        // [n_rows][vocab]
+  const float* sums;    // or null: [ksplit][n_rows][vocab] partial logits, summed up here
+  int ksplit;
   float* probs;         // [n_rows][vocab] or nullptr
   int* tk_ids;          // [n_rows][k]
   float* tk_probs;      // [n_rows][k]
@@ -407,8 +381,29 @@ __global__ __launch_bounds__(kPartThreads) void row_parts_kernel(SoftParams p) {
   const int tid = threadIdx.x, V = p.vocab, K = p.k;
   const int row = blockIdx.x / p.parts, part = blockIdx.x % p.parts;
   const int lo = part * p.part_len, hi = min(V, lo + p.part_len);
-  const float* x = p.logits + (long long)row * V;
+  float* x = p.logits + (long long)row * V;
   const bool vec = (V & 3) == 0 && (reinterpret_cast<size_t>(p.logits) & 15) == 0;
+  if (p.sums) {  // the k parts' partial products come together here (in a fixed order); each thread reads back its own
+    const float* part_x = p.sums + (long long)row * V;
+    const long long step = (long long)p.n_rows * V;
+#pragma unroll 2
+    for (int u = 0; u < kPartPerThread / 4; ++u) {
+      const int e = lo + 4 * (tid + kPartThreads * u);
+      if (vec && e + 3 < hi) {
+        floatx4 v = *reinterpret_cast<const floatx4*>(part_x + e);
+#pragma unroll 4
+        for (int z = 1; z < p.ksplit; ++z) v += *reinterpret_cast<const floatx4*>(part_x + z * step + e);
+        *reinterpret_cast<floatx4*>(x + e) = v;
+      } else {
+        for (int c = 0; c < 4; ++c)
+          if (e + c < hi) {
+            float v = part_x[e + c];
+            for (int z = 1; z < p.ksplit; ++z) v += part_x[z * step + e + c];
+            x[e + c] = v;
+          }
+      }
+    }
+  }
   if (tid == 0) {
     n_cand = 0;
     s_tau = -INFINITY;
@@ -652,31 +647,24 @@ constexpr int kMaxExperts = 64;
 struct RouterParams {
   const uint16_t* u;          // [rows][d] bf16
   const uint16_t* centroids;  // [n_experts][d] bf16
-  uint16_t* x;                // [rows padded to 32][d] bf16: copy of u, zero rows behind it
   float* s_top;               // [rows][2]
   int* idx;                   // [rows][2]
   int rows, d, n_experts;
 };
 
-// One workgroup per (padded) row: copies the row into the GEMM's padded input, and for real rows
-// computes the router scores s_j = softmax_j(u . e_j) (Eq. 2; fp32), picks the two largest (Eq. 5,
-// K = 2, ties to the lower expert).
+// One workgroup per row: the router scores s_j = softmax_j(u . e_j) (Eq. 2; fp32), of which it picks the two largest
+// (Eq. 5, K = 2, ties to the lower expert).  Bound by one trip to memory: a wave has the row and two centroids in
+// flight at once, and the softmax and both maxima are taken across the lanes of a wave.
 __global__ __launch_bounds__(256) void router_kernel(RouterParams p) {
   __shared__ float score[kMaxExperts];
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  u32x4* dst = reinterpret_cast<u32x4*>(p.x + (long long)row * p.d);
-  if (row >= p.rows) {
-    for (int c = tid; c < p.d / 8; c += 256) dst[c] = u32x4{0u, 0u, 0u, 0u};
-    return;
-  }
   const u32x4* src = reinterpret_cast<const u32x4*>(p.u + (long long)row * p.d);
-  for (int c = tid; c < p.d / 8; c += 256) dst[c] = src[c];
   for (int j0 = wave; j0 < p.n_experts; j0 += 8) {  // two experts per pass: their loads share the trip to memory
     const bool two = j0 + 4 < p.n_experts;
     const u32x4* e0 = reinterpret_cast<const u32x4*>(p.centroids + (long long)j0 * p.d);
     const u32x4* e1 = reinterpret_cast<const u32x4*>(p.centroids + (long long)(two ? j0 + 4 : j0) * p.d);
     float acc0 = 0.f, acc1 = 0.f;
-#pragma unroll 4
+#pragma unroll 8
     for (int c = lane; c < p.d / 8; c += 64) {
       const u32x4 a = src[c], b0 = e0[c], b1 = e1[c];
 #pragma unroll
@@ -696,67 +684,76 @@ __global__ __launch_bounds__(256) void router_kernel(RouterParams p) {
     }
   }
   __syncthreads();
-  if (tid == 0) {
-    float m = -INFINITY;
-    for (int j = 0; j < p.n_experts; ++j) m = fmaxf(m, score[j]);
-    float z = 0.f;
-    for (int j = 0; j < p.n_experts; ++j) z += expf(score[j] - m);
-    int i1 = 0;
-    for (int j = 1; j < p.n_experts; ++j)
-      if (score[j] > score[i1]) i1 = j;
-    int i2 = i1 == 0 ? 1 : 0;
-    for (int j = 0; j < p.n_experts; ++j)
-      if (j != i1 && score[j] > score[i2]) i2 = j;
-    p.s_top[2 * row] = expf(score[i1] - m) / z;
-    p.s_top[2 * row + 1] = expf(score[i2] - m) / z;
-    p.idx[2 * row] = i1;
-    p.idx[2 * row + 1] = i2;
+  if (wave != 0) return;
+  const float mine = lane < p.n_experts ? score[lane] : -INFINITY;  // (at most 64 experts)
+  const Best b1 = wave_best(mine, lane);
+  const Best b2 = wave_best(lane == b1.id ? -INFINITY : mine, lane == b1.id ? INT_MAX : lane);
+  float z = lane < p.n_experts ? expf(mine - b1.v) : 0.f;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) z += __shfl_xor(z, o);
+  if (lane == 0) {
+    p.s_top[2 * row] = 1.f / z;
+    p.s_top[2 * row + 1] = expf(b2.v - b1.v) / z;
+    p.idx[2 * row] = b1.id;
+    p.idx[2 * row + 1] = b2.id;
   }
+}
+
+// How many of the first n_rows rows chose expert e (the same in every lane of a wave): with n_rows = a row's number its
+// place among the expert's rows, which is how the experts' products number them.
+__device__ __forceinline__ int rows_with(const int* sel, int n_rows, int e) {
+  int n = 0;
+  for (int i0 = 0; i0 < n_rows; i0 += 64) {
+    const int row = i0 + (int)(threadIdx.x & 63);
+    n += __popcll(__ballot(row < n_rows && (sel[2 * row] == e || sel[2 * row + 1] == e)));
+  }
+  return n;
+}
+// The k parts' partial results of four consecutive outputs, up to eight of them in flight, added in a fixed order
+__device__ __forceinline__ floatx4 sum_parts(const float* part, int ksplit, long long step) {
+  floatx4 v = {0.f, 0.f, 0.f, 0.f};
+  for (int z0 = 0; z0 < ksplit; z0 += 8) {
+    floatx4 t[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (z0 + i < ksplit) t[i] = *reinterpret_cast<const floatx4*>(part + (z0 + i) * step);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (z0 + i < ksplit) v += t[i];
+  }
+  return v;
 }
 
 struct ActParams {
   const float *g, *up;  // [ksplit][n_experts][rows][f] fp32: partial gate and up projections
-  uint16_t* h;          // [n_experts][rows padded to 32][f] bf16
+  uint16_t* h;          // [n_experts][rows][f] bf16
   const int* sel;  // [2 rows]: the experts the rows selected
-  int rows, rows_pad, f, ksplit;
+  int rows, f, ksplit;
   long long split_stride;
 };
 
-// h = silu(gate) * up, rounded to bf16 once; padding rows are zero-filled
+// h = silu(gate) * up, rounded to bf16 once, where the k range of the two projections was divided (an undivided one
+// has this in its epilogue)
 __global__ __launch_bounds__(256) void gated_act_kernel(ActParams p) {
   const int e = blockIdx.y, row = blockIdx.x;
-  {
-    int mine = 0;
-    for (int i = threadIdx.x & 63; i < 2 * p.rows; i += 64) mine |= (int)(p.sel[i] == e);
-    if (!__any(mine)) return;  // nobody selected this expert (every wave finds the same)
-  }
-  uint16_t* h = p.h + ((long long)e * p.rows_pad + row) * p.f;
-  if (row >= p.rows) {
-    for (int c = threadIdx.x; c < p.f / 8; c += 256) reinterpret_cast<u32x4*>(h)[c] = u32x4{0u, 0u, 0u, 0u};
-    return;
-  }
-  const float* g = p.g + ((long long)e * p.rows + row) * p.f;
-  const float* up = p.up + ((long long)e * p.rows + row) * p.f;
-  for (int c = threadIdx.x; c < p.f / 4; c += 256) {
-    floatx4 a = reinterpret_cast<const floatx4*>(g)[c], b = reinterpret_cast<const floatx4*>(up)[c];
-    for (int z = 1; z < p.ksplit; ++z) {
-      a += reinterpret_cast<const floatx4*>(g + z * p.split_stride)[c];
-      b += reinterpret_cast<const floatx4*>(up + z * p.split_stride)[c];
-    }
+  if (row >= rows_with(p.sel, p.rows, e)) return;
+  const long long at = ((long long)e * p.rows + row) * p.f;
+  for (int c = blockIdx.z * 256 + threadIdx.x; c < p.f / 4; c += 256 * gridDim.z) {
+    const floatx4 a = sum_parts(p.g + at + 4 * c, p.ksplit, p.split_stride), b = sum_parts(p.up + at + 4 * c, p.ksplit, p.split_stride);
     float o[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) o[i] = a[i] / (1.f + expf(-a[i])) * b[i];
     uint2 w;
     w.x = bf16_bits_rne(o[0]) | (bf16_bits_rne(o[1]) << 16);
     w.y = bf16_bits_rne(o[2]) | (bf16_bits_rne(o[3]) << 16);
-    reinterpret_cast<uint2*>(h)[c] = w;
+    reinterpret_cast<uint2*>(p.h + at)[c] = w;
   }
 }
 
 struct SelectParams {
   int ksplit;
   long long split_stride;
-  const float* y;     // [ksplit][n_experts][rows][d] fp32: the experts' (partial) outputs
+  const float* y;     // [ksplit][n_experts][rows][d] fp32: the experts' (partial) outputs for their own rows
   const uint16_t* u;  // [rows][d] bf16
   const float* s_top;
   const int* idx;
@@ -770,58 +767,43 @@ __global__ __launch_bounds__(256) void select_kernel(SelectParams p) {
   const int row = blockIdx.x;
   const int i1 = p.idx[2 * row], i2 = p.idx[2 * row + 1];
   const float s1 = p.s_top[2 * row], s2 = p.s_top[2 * row + 1];
-  const float* y1 = p.y + ((long long)i1 * p.rows + row) * p.d;
-  const float* y2 = p.y + ((long long)i2 * p.rows + row) * p.d;
-  const uint16_t* u = p.u + (long long)row * p.d;
-  for (int c = blockIdx.y * 256 + threadIdx.x; c < p.d / 2; c += 256 * gridDim.y) {
-    const unsigned uu = reinterpret_cast<const unsigned*>(u)[c];
-    const float u0 = bf16_lo(uu), u1 = bf16_hi(uu);
-    float2 a = reinterpret_cast<const float2*>(y1)[c], b = reinterpret_cast<const float2*>(y2)[c];
-    for (int z = 1; z < p.ksplit; ++z) {
-      const float2 az = reinterpret_cast<const float2*>(y1 + z * p.split_stride)[c];
-      const float2 bz = reinterpret_cast<const float2*>(y2 + z * p.split_stride)[c];
-      a.x += az.x; a.y += az.y;
-      b.x += bz.x; b.y += bz.y;
-    }
-    reinterpret_cast<unsigned*>(p.f_top + ((long long)row * 2 + 0) * p.d)[c] =
-        bf16_bits_rne(a.x + u0) | (bf16_bits_rne(a.y + u1) << 16);
-    reinterpret_cast<unsigned*>(p.f_top + ((long long)row * 2 + 1) * p.d)[c] =
-        bf16_bits_rne(b.x + u0) | (bf16_bits_rne(b.y + u1) << 16);
-    if (p.f_mix)
-      reinterpret_cast<unsigned*>(p.f_mix + (long long)row * p.d)[c] =
-          bf16_bits_rne(s1 * a.x + s2 * b.x + u0) | (bf16_bits_rne(s1 * a.y + s2 * b.y + u1) << 16);
-  }
+  const float* y1 = p.y + ((long long)i1 * p.rows + rows_with(p.idx, row, i1)) * p.d;
+  const float* y2 = p.y + ((long long)i2 * p.rows + rows_with(p.idx, row, i2)) * p.d;
+  const int c = blockIdx.y * 256 + threadIdx.x;
+  if (c >= p.d / 4) return;
+  const floatx4 a = sum_parts(y1 + 4 * c, p.ksplit, p.split_stride), b = sum_parts(y2 + 4 * c, p.ksplit, p.split_stride);
+  const uint2 uu = reinterpret_cast<const uint2*>(p.u + (long long)row * p.d)[c];
+  const floatx4 u = {bf16_lo(uu.x), bf16_hi(uu.x), bf16_lo(uu.y), bf16_hi(uu.y)};
+  auto store = [&](uint16_t* dst, const floatx4& v) {
+    uint2 w;
+    w.x = bf16_bits_rne(v[0]) | (bf16_bits_rne(v[1]) << 16);
+    w.y = bf16_bits_rne(v[2]) | (bf16_bits_rne(v[3]) << 16);
+    reinterpret_cast<uint2*>(dst)[c] = w;
+  };
+  store(p.f_top + ((long long)row * 2 + 0) * p.d, a + u);
+  store(p.f_top + ((long long)row * 2 + 1) * p.d, b + u);
+  if (p.f_mix) store(p.f_mix + (long long)row * p.d, s1 * a + s2 * b + u);
 }
 
 struct MoePlan {
-  int rows_pad, split1, split2;
-  size_t x_off, g_off, up_off, h_off, y_off, total;
+  int split1, split2;
+  size_t g_off, up_off, h_off, y_off, total;
 };
-// k parts so that a projection with few output columns still fills the chip: a workgroup can
-// pull only a fixed share of the memory bandwidth, so the weight stream needs about one
-// workgroup per CU.  A part keeps at least 512 of k and a multiple of 128.
-int pick_ksplit(int n_out, int k, int mb, int batch, int cus) {
-  const int strip = mb <= 6 ? 512 : 256;
-  const long long wgs = (long long)((n_out + strip - 1) / strip) * batch;
-  int best = 1;
-  for (int s = 2; s <= 8; ++s) {
-    if (k % (128 * s) != 0 || k / s < 512) continue;
-    if (wgs * s <= (long long)cus + cus / 8) best = s;
-  }
-  return best;
-}
 MoePlan moe_plan(int rows, int d, int f, int n) {
   MoePlan m;
   auto up = [](size_t v) { return (v + 255) / 256 * 256; };
-  m.rows_pad = (rows + 31) / 32 * 32;
-  const int cus = device_cu_count();
-  m.split1 = pick_ksplit(f, d, m.rows_pad / 32, 2 * n, cus);  // gate and up in one launch
-  m.split2 = pick_ksplit(d, f, m.rows_pad / 32, n, cus);
-  m.x_off = 0;
-  m.g_off = up((size_t)m.rows_pad * d * 2);
-  m.up_off = m.g_off + up((size_t)m.split1 * n * rows * f * 4);
-  m.h_off = m.up_off + up((size_t)m.split1 * n * rows * f * 4);
-  m.y_off = m.h_off + up((size_t)n * m.rows_pad * f * 2);
+  // the experts that rows choosing two of n each are likely to reach, and how many rows each of those has
+  double missed = 1.0;
+  for (int r = 0; r < rows; ++r) missed *= 1.0 - 2.0 / n;
+  const int used = n * (1.0 - missed) < 2.0 ? 2 : (int)(n * (1.0 - missed) + 0.5);
+  const int each = (2 * rows + used - 1) / used;
+  m.split1 = stream_gemm_ksplit(each, f, d, used, true);  // gate and up in one launch
+  m.split2 = stream_gemm_ksplit(each, d, f, used, false);
+  const size_t pre = m.split1 > 1 ? up((size_t)m.split1 * n * rows * f * 4) : 0;
+  m.g_off = 0;
+  m.up_off = pre;
+  m.h_off = 2 * pre;
+  m.y_off = m.h_off + up((size_t)n * rows * f * 2);
   m.total = m.y_off + up((size_t)m.split2 * n * rows * d * 4);
   return m;
 }
@@ -837,19 +819,37 @@ struct LinFinishParams {
   int ksplit;
 };
 __global__ __launch_bounds__(256) void linear_finish_kernel(LinFinishParams p) {
-  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < p.n_out; i += (long long)gridDim.x * 256) {
-    float v = p.part[i];
-    for (int z = 1; z < p.ksplit; ++z) v += p.part[i + z * p.n_out];
-    if (p.residual) v += __uint_as_float((unsigned)p.residual[i] << 16);
-    if (p.out_f32) p.out_f32[i] = v;
-    if (p.out_bf16) p.out_bf16[i] = (uint16_t)bf16_bits_rne(v);
+  const long long i = ((long long)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (i >= p.n_out) return;
+  const bool vec = (p.n_out & 3) == 0 && (reinterpret_cast<size_t>(p.residual) & 7) == 0 && (reinterpret_cast<size_t>(p.out_bf16) & 7) == 0 &&
+                   (reinterpret_cast<size_t>(p.out_f32) & 15) == 0;
+  if (vec) {
+    uint2 q = {0u, 0u};
+    if (p.residual) q = *reinterpret_cast<const uint2*>(p.residual + i);
+    floatx4 v = sum_parts(p.part + i, p.ksplit, p.n_out);
+    if (p.residual) v += floatx4{bf16_lo(q.x), bf16_hi(q.x), bf16_lo(q.y), bf16_hi(q.y)};
+    if (p.out_f32) *reinterpret_cast<floatx4*>(p.out_f32 + i) = v;
+    if (p.out_bf16) {
+      uint2 w;
+      w.x = bf16_bits_rne(v[0]) | (bf16_bits_rne(v[1]) << 16);
+      w.y = bf16_bits_rne(v[2]) | (bf16_bits_rne(v[3]) << 16);
+      *reinterpret_cast<uint2*>(p.out_bf16 + i) = w;
+    }
+    return;
+  }
+  for (long long j = i; j < i + 4 && j < p.n_out; ++j) {
+    float v = p.part[j];
+    for (int z = 1; z < p.ksplit; ++z) v += p.part[j + z * p.n_out];
+    if (p.residual) v += bf16_lo(p.residual[j]);
+    if (p.out_f32) p.out_f32[j] = v;
+    if (p.out_bf16) p.out_bf16[j] = (uint16_t)bf16_bits_rne(v);
   }
 }
 
-int linear_ksplit(int m, int n, int k) {
-  int s = pick_ksplit(n, k, (m + 31) / 32, 1, device_cu_count());
+// parts of a product with few output columns, at most 64 MB of partial results
+int capped_ksplit(int m, int n, int k) {
+  int s = stream_gemm_ksplit(m, n, k, 1, false);
   while (s > 1 && (size_t)s * m * n * 4 > ((size_t)64 << 20)) --s;
-  while (s > 1 && (k % (128 * s) != 0 || k / s < 512)) --s;
   return s;
 }
 
@@ -858,15 +858,6 @@ struct RowPlan {
   size_t x_bytes, ms_off, cv_off, ci_off, part_off, total;
 };
 
-// logits = sum of the k parts' partial products (fixed order)
-__global__ __launch_bounds__(256) void sum_parts_kernel(const float* __restrict__ part, float* __restrict__ out,
-                                                        long long n, int ksplit) {
-  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long long)gridDim.x * 256) {
-    float v = part[i];
-    for (int z = 1; z < ksplit; ++z) v += part[i + z * n];
-    out[i] = v;
-  }
-}
 RowPlan row_plan(int rows, int d_model, int vocab) {
   RowPlan r;
   const size_t m = 2 * (size_t)rows, m_pad = (m + 31) / 32 * 32;
@@ -878,10 +869,7 @@ RowPlan row_plan(int rows, int d_model, int vocab) {
   r.cv_off = r.ms_off + up(m * r.parts * 2 * 4);
   r.ci_off = r.cv_off + up(m * r.parts * kMaxTopK * 4);
   r.part_off = r.ci_off + up(m * r.parts * kMaxTopK * 4);
-  // a small vocabulary gives few 512-row strips: split k until the chip is full (partials of at most 64 MB)
-  r.ksplit = pick_ksplit(vocab, d_model, (int)(m_pad / 32), 1, device_cu_count());
-  while (r.ksplit > 1 && (size_t)r.ksplit * m * vocab * 4 > ((size_t)64 << 20)) --r.ksplit;
-  while (r.ksplit > 1 && (d_model % (128 * r.ksplit) != 0 || d_model / r.ksplit < 512)) --r.ksplit;
+  r.ksplit = gemm_fits((int)m, vocab) ? 1 : capped_ksplit((int)m, vocab, d_model);
   r.total = r.part_off + (r.ksplit > 1 ? up((size_t)r.ksplit * m * vocab * 4) : 0);
   return r;
 }
@@ -903,26 +891,25 @@ hipError_t launch_draft_heads(const DraftHeadsArgs& a, hipStream_t stream) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
 
-  GemmParams gp;
-  gp.x = reinterpret_cast<const uint16_t*>(ws);
-  gp.w = static_cast<const uint16_t*>(a.w_head);
-  gp.y = a.logits;
-  gp.m = m; gp.n = a.vocab; gp.k = a.d_model;
-  gp.ldw = a.d_model; gp.ldy = a.vocab;
-  gp.batch = 1; gp.x_batch = gp.w_batch = gp.y_batch = 0; gp.sel = nullptr; gp.n_sel = 0; gp.w2 = nullptr; gp.y2 = nullptr;
-  gp.ksplit = rp.ksplit; gp.y_split = (long long)m * a.vocab;
-  if (rp.ksplit > 1) gp.y = reinterpret_cast<float*>(ws + rp.part_off);
-  e = launch_gemm(gp, stream);
-  if (e != hipSuccess) return e;
-  if (rp.ksplit > 1) {
-    const long long n_out = (long long)m * a.vocab;
-    const unsigned grid = (unsigned)((n_out + 1023) / 1024 < 2048 ? (n_out + 1023) / 1024 : 2048);
-    hipLaunchKernelGGL(sum_parts_kernel, dim3(grid), dim3(256), 0, stream, gp.y, a.logits, n_out, rp.ksplit);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+  const uint16_t *x = reinterpret_cast<const uint16_t*>(ws), *w = static_cast<const uint16_t*>(a.w_head);
+  float* parts = rp.ksplit > 1 ? reinterpret_cast<float*>(ws + rp.part_off) : nullptr;
+  if (gemm_fits(m, a.vocab)) {
+    GemmParams gp;
+    gp.x = x; gp.w = w; gp.y = a.logits;
+    gp.m = m; gp.n = a.vocab; gp.k = a.d_model;
+    gp.ldw = a.d_model; gp.ldy = a.vocab;
+    e = launch_gemm(gp, stream);
+  } else {
+    StreamGemmArgs g{};
+    g.x = x; g.w = w; g.y = parts ? parts : a.logits;
+    g.m = m; g.n = a.vocab; g.k = a.d_model;
+    g.ksplit = rp.ksplit; g.y_split = (long long)m * a.vocab; g.batch = 1;
+    e = launch_stream_gemm(g, stream);
   }
+  if (e != hipSuccess) return e;
 
   SoftParams sp;
-  sp.logits = a.logits; sp.probs = a.draft_probs; sp.tk_ids = a.topk_tokens; sp.tk_probs = a.topk_probs;
+  sp.logits = a.logits; sp.sums = parts; sp.ksplit = rp.ksplit; sp.probs = a.draft_probs; sp.tk_ids = a.topk_tokens; sp.tk_probs = a.topk_probs;
   sp.part_ms = reinterpret_cast<float*>(ws + rp.ms_off);
   sp.part_cv = reinterpret_cast<float*>(ws + rp.cv_off);
   sp.part_ci = reinterpret_cast<int*>(ws + rp.ci_off);
@@ -944,67 +931,71 @@ hipError_t launch_moe_experts(const MoeArgs& a, hipStream_t stream) {
   hipError_t e;
   RouterParams rp;
   rp.u = static_cast<const uint16_t*>(a.u); rp.centroids = static_cast<const uint16_t*>(a.centroids);
-  rp.x = reinterpret_cast<uint16_t*>(ws + mp.x_off);
   rp.s_top = a.s_top; rp.idx = a.expert_idx;
   rp.rows = a.rows; rp.d = a.d_model; rp.n_experts = a.n_experts;
-  hipLaunchKernelGGL(router_kernel, dim3(mp.rows_pad), dim3(256), 0, stream, rp);
+  hipLaunchKernelGGL(router_kernel, dim3(a.rows), dim3(256), 0, stream, rp);
   if ((e = hipGetLastError()) != hipSuccess) return e;
 
-  GemmParams gp;
-  gp.x = rp.x; gp.m = a.rows; gp.n = a.d_ff; gp.k = a.d_model; gp.ldw = a.d_model; gp.ldy = a.d_ff;
-  gp.batch = a.n_experts; gp.x_batch = 0; gp.w_batch = (long long)a.d_ff * a.d_model;
-  gp.y_batch = (long long)a.rows * a.d_ff; gp.sel = a.expert_idx; gp.n_sel = 2 * a.rows;
-  gp.ksplit = mp.split1; gp.y_split = (long long)a.n_experts * a.rows * a.d_ff;
-  gp.w = static_cast<const uint16_t*>(a.w_gate); gp.y = reinterpret_cast<float*>(ws + mp.g_off);
-  gp.w2 = static_cast<const uint16_t*>(a.w_up); gp.y2 = reinterpret_cast<float*>(ws + mp.up_off);
-  if ((e = launch_gemm(gp, stream)) != hipSuccess) return e;  // gate and up projections of all experts
-  gp.w2 = nullptr; gp.y2 = nullptr;
-
-  ActParams ap;
-  ap.g = reinterpret_cast<const float*>(ws + mp.g_off); ap.up = reinterpret_cast<const float*>(ws + mp.up_off);
-  ap.h = reinterpret_cast<uint16_t*>(ws + mp.h_off); ap.sel = a.expert_idx;
-  ap.rows = a.rows; ap.rows_pad = mp.rows_pad; ap.f = a.d_ff;
-  ap.ksplit = mp.split1; ap.split_stride = gp.y_split;
-  hipLaunchKernelGGL(gated_act_kernel, dim3(mp.rows_pad, a.n_experts), dim3(256), 0, stream, ap);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-
-  gp.x = ap.h; gp.m = a.rows; gp.n = a.d_model; gp.k = a.d_ff; gp.ldw = a.d_ff; gp.ldy = a.d_model;
-  gp.x_batch = (long long)mp.rows_pad * a.d_ff; gp.w_batch = (long long)a.d_model * a.d_ff;
-  gp.y_batch = (long long)a.rows * a.d_model;
-  gp.ksplit = mp.split2; gp.y_split = (long long)a.n_experts * a.rows * a.d_model;
-  gp.w = static_cast<const uint16_t*>(a.w_down); gp.y = reinterpret_cast<float*>(ws + mp.y_off);
-  if ((e = launch_gemm(gp, stream)) != hipSuccess) return e;
+  // Each expert runs for the rows that chose it only, numbered in order: row r's place among them is how many rows
+  // before it chose the same expert, which every kernel finds out for itself.
+  uint16_t* h = reinterpret_cast<uint16_t*>(ws + mp.h_off);
+  StreamGemmArgs g{};
+  g.x = rp.u; g.m = a.rows; g.n = a.d_ff; g.k = a.d_model;
+  g.batch = a.n_experts; g.x_batch = 0; g.w_batch = (long long)a.d_ff * a.d_model; g.y_batch = (long long)a.rows * a.d_ff;
+  g.sel = a.expert_idx;
+  g.ksplit = mp.split1; g.y_split = (long long)a.n_experts * a.rows * a.d_ff;
+  g.w = static_cast<const uint16_t*>(a.w_gate); g.w2 = static_cast<const uint16_t*>(a.w_up);
+  if (mp.split1 > 1) {
+    g.y = reinterpret_cast<float*>(ws + mp.g_off); g.y2 = reinterpret_cast<float*>(ws + mp.up_off);
+  } else {
+    g.act = h; g.act_batch = (long long)a.rows * a.d_ff;
+  }
+  if ((e = launch_stream_gemm_pair(g, stream)) != hipSuccess) return e;  // gate and up projections of all experts
+  if (mp.split1 > 1) {
+    ActParams ap;
+    ap.g = g.y; ap.up = g.y2; ap.h = h; ap.sel = a.expert_idx;
+    ap.rows = a.rows; ap.f = a.d_ff; ap.ksplit = mp.split1; ap.split_stride = g.y_split;
+    hipLaunchKernelGGL(gated_act_kernel, dim3(a.rows, a.n_experts, (unsigned)((a.d_ff + 4095) / 4096)), dim3(256), 0, stream, ap);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  StreamGemmArgs o{};
+  o.x = h; o.m = a.rows; o.n = a.d_model; o.k = a.d_ff;
+  o.batch = a.n_experts; o.x_batch = (long long)a.rows * a.d_ff; o.w_batch = (long long)a.d_model * a.d_ff;
+  o.y_batch = (long long)a.rows * a.d_model; o.sel = a.expert_idx;
+  o.ksplit = mp.split2; o.y_split = (long long)a.n_experts * a.rows * a.d_model;
+  o.w = static_cast<const uint16_t*>(a.w_down); o.y = reinterpret_cast<float*>(ws + mp.y_off);
+  if ((e = launch_stream_gemm_down(o, stream)) != hipSuccess) return e;
 
   SelectParams sp;
-  sp.y = reinterpret_cast<const float*>(ws + mp.y_off); sp.u = rp.u; sp.s_top = a.s_top; sp.idx = a.expert_idx;
+  sp.y = o.y; sp.u = rp.u; sp.s_top = a.s_top; sp.idx = a.expert_idx;
   sp.f_top = static_cast<uint16_t*>(a.f_top); sp.f_mix = static_cast<uint16_t*>(a.f_mix);
   sp.rows = a.rows; sp.d = a.d_model;
-  sp.ksplit = mp.split2; sp.split_stride = gp.y_split;
-  const unsigned chunks = (unsigned)(a.d_model / 512 < 8 ? (a.d_model / 512 > 0 ? a.d_model / 512 : 1) : 8);
-  hipLaunchKernelGGL(select_kernel, dim3(a.rows, chunks), dim3(256), 0, stream, sp);
+  sp.ksplit = mp.split2; sp.split_stride = o.y_split;
+  hipLaunchKernelGGL(select_kernel, dim3(a.rows, (unsigned)((a.d_model / 4 + 255) / 256)), dim3(256), 0, stream, sp);
   return hipGetLastError();
 }
 
 size_t linear_workspace_bytes(int m, int n, int k) {
-  return ((size_t)linear_ksplit(m, n, k) * m * n * 4 + 255) / 256 * 256;
+  return ((size_t)capped_ksplit(m, n, k) * m * n * 4 + 255) / 256 * 256;
 }
 
 hipError_t launch_linear(const LinearArgs& a, hipStream_t stream) {
-  const int ks = linear_ksplit(a.m, a.n, a.k);
-  const bool direct = ks == 1 && !a.residual && !a.out_bf16 && a.out_f32;
-  GemmParams gp;
-  gp.x = static_cast<const uint16_t*>(a.x); gp.w = static_cast<const uint16_t*>(a.w);
-  gp.y = direct ? a.out_f32 : static_cast<float*>(a.workspace);
-  gp.m = a.m; gp.n = a.n; gp.k = a.k; gp.ldw = a.k; gp.ldy = a.n;
-  gp.batch = 1; gp.x_batch = gp.w_batch = gp.y_batch = 0; gp.sel = nullptr; gp.n_sel = 0; gp.w2 = nullptr; gp.y2 = nullptr;
-  gp.ksplit = ks; gp.y_split = (long long)a.m * a.n;
-  hipError_t e = launch_gemm(gp, stream);
-  if (e != hipSuccess || direct) return e;
+  const int ks = capped_ksplit(a.m, a.n, a.k);
+  StreamGemmArgs g{};
+  g.x = static_cast<const uint16_t*>(a.x); g.w = static_cast<const uint16_t*>(a.w);
+  g.m = a.m; g.n = a.n; g.k = a.k; g.ksplit = ks; g.y_split = (long long)a.m * a.n; g.batch = 1;
+  if (ks == 1) {
+    g.finish = true;
+    g.y = a.out_f32; g.residual = static_cast<const uint16_t*>(a.residual); g.out_bf16 = static_cast<uint16_t*>(a.out_bf16);
+    return launch_stream_gemm(g, stream);
+  }
+  g.y = static_cast<float*>(a.workspace);
+  hipError_t e = launch_stream_gemm(g, stream);
+  if (e != hipSuccess) return e;
   LinFinishParams fp;
-  fp.part = gp.y; fp.residual = static_cast<const uint16_t*>(a.residual); fp.out_f32 = a.out_f32;
+  fp.part = g.y; fp.residual = static_cast<const uint16_t*>(a.residual); fp.out_f32 = a.out_f32;
   fp.out_bf16 = static_cast<uint16_t*>(a.out_bf16); fp.n_out = (long long)a.m * a.n; fp.ksplit = ks;
-  const unsigned grid = (unsigned)((fp.n_out + 1023) / 1024 < 2048 ? (fp.n_out + 1023) / 1024 : 2048);
-  hipLaunchKernelGGL(linear_finish_kernel, dim3(grid), dim3(256), 0, stream, fp);
+  hipLaunchKernelGGL(linear_finish_kernel, dim3((unsigned)((fp.n_out + 1023) / 1024)), dim3(256), 0, stream, fp);
   return hipGetLastError();
 }
 

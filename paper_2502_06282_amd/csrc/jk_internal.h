@@ -141,6 +141,32 @@ hipError_t launch_accept_coop(const AcceptArgs& a, void* coop_ws, int W, int sli
 hipError_t launch_zero_fill(void* p, size_t bytes, hipStream_t stream);
 hipError_t launch_stream_read(const void* src, size_t bytes, void* sink, hipStream_t stream);
 
+// few rows times a large weight matrix (stream_gemm.hip): y[m][n] = x[m][k] . w[n][k]^T, fp32, k a multiple of 128
+struct StreamGemmArgs {
+  const uint16_t *x, *w;  // bf16
+  float* y;
+  int m, n, k;
+  int ksplit;           // parts of the k range; part z writes its partial result y_split elements behind the first one's
+  long long y_split;
+  // plain products, undivided k range: with `finish` y (or null) and out_bf16 (or null) receive x . w^T + residual (or null)
+  bool finish;
+  const uint16_t* residual;
+  uint16_t* out_bf16;
+  // experts: `batch` problems, element offsets between them; problem e runs for the rows r of [0, m) with sel[2 r] or
+  // sel[2 r + 1] == e, numbered in order (its rows of y, of act and of the down projection's x), or not at all
+  int batch;
+  long long x_batch, w_batch, y_batch;
+  const int* sel;
+  const uint16_t* w2;   // gate and up projections in one launch: w, y and w2, y2; or, with `act` (undivided k range),
+  float* y2;            // act[e][row][n] = silu(x . w^T) * (x . w2^T) in bf16, act_batch elements between experts
+  uint16_t* act;
+  long long act_batch;
+};
+int stream_gemm_ksplit(int m, int n, int k, int batch, bool pair);
+hipError_t launch_stream_gemm(const StreamGemmArgs& p, hipStream_t stream);       // m <= 256
+hipError_t launch_stream_gemm_pair(const StreamGemmArgs& p, hipStream_t stream);  // m <= 128
+hipError_t launch_stream_gemm_down(const StreamGemmArgs& p, hipStream_t stream);  // m <= 128
+
 // draft head step (two heads over the shared output embedding)
 struct DraftHeadsArgs {
   int rows, d_model, vocab, top_k, mode;

@@ -75,3 +75,27 @@ def test_argument_errors():
         jk.linear(torch.zeros((257, 256), dtype=torch.bfloat16, device="cuda"), w)
     assert e.value.status == 3
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("m,n,k", [(1, 1, 128), (16, 127, 384), (17, 129, 640), (48, 4100, 1152), (65, 128, 8192), (97, 33, 896),
+                                   (129, 255, 256), (160, 257, 1920), (176, 513, 128), (241, 300, 2176), (3, 40000, 128)])
+def test_row_blocks_strips_and_k_parts_at_their_edges(m, n, k):
+    """Every row-block count of the streaming product with strips that end early, half chunks of k, one and many k parts,
+    and an output that is not aligned for vector stores: bit-exact on exact-arithmetic inputs."""
+    rng = np.random.default_rng(m + n + k)
+    x = rng.integers(-2, 3, size=(m, k)).astype(np.float32)
+    w = (rng.integers(-1, 2, size=(n, k)) * 0.125).astype(np.float32)
+    r = rng.integers(-4, 5, size=(m, n)).astype(np.float32)
+    want = dh.linear(x, w, r)
+    got = jk.linear(_bf(x), _bf(w), _bf(r), out_dtype=torch.float32).cpu().numpy()
+    np.testing.assert_array_equal(got.astype(np.float64), want)
+    both = torch.full((2, m * n + 1), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.empty(jk.lib().jk_linear_workspace(m, n, k), dtype=torch.uint8, device="cuda")
+    xd, wd, rd, out16 = _bf(x), _bf(w), _bf(r), torch.empty(m * n, dtype=torch.bfloat16, device="cuda")
+    st = jk.lib().jk_linear(m, n, k, xd.data_ptr(), wd.data_ptr(), rd.data_ptr(), out16.data_ptr(), both[1].data_ptr() + 4,
+                            ws.data_ptr(), ws.numel(), None)
+    torch.cuda.synchronize()
+    assert st == 0
+    np.testing.assert_array_equal(both[1, 1:].cpu().numpy().reshape(m, n).astype(np.float64), want)
+    np.testing.assert_array_equal(out16.float().cpu().numpy().reshape(m, n), round_to_bf16(want.astype(np.float32)))
+    assert torch.isnan(both[0]).all() and torch.isnan(both[1, 0])

@@ -212,3 +212,11 @@ def test_draft_step_captured_in_a_hip_graph_replays_bit_for_bit():
         for o, e in zip(outs, eager):
             assert torch.equal(o, e), f"replay {rep} differs from the eager result"
         assert torch.isfinite(junk)
+
+
+@pytest.mark.parametrize("rows,d,f,n", [(1, 1152, 4096, 2), (20, 384, 8192, 2), (48, 128, 4096, 4), (70, 640, 384, 2),
+                                        (96, 256, 2048, 3), (128, 128, 2048, 2)])
+def test_rows_gathered_per_expert(rows, d, f, n):
+    """Every row-block count an expert can have (all rows may choose the same two), with divided and undivided k ranges
+    and half chunks of k."""
+    _check(moe_inputs(rows, d, f, n, seed=rows + 1), min_gap=1e-6)
