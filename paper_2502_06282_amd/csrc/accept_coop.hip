@@ -3,66 +3,80 @@
 // Same rule as the single-workgroup walk (Section 2.1 steps 2-3 of the paper:
 // accept with probability min(1, p/q), continue with norm(max(0, p - q)) after
 // a rejection; siblings tried left to right, Section 3.1.2), spread over W
-// workgroups per tree.  Workgroup w owns the vocabulary slice
-// [w*SL, (w+1)*SL) and keeps the current distribution of that slice in LDS as
-// fp64, so that a rejection only streams the rejected node's draft
-// distribution from HBM.  Logits rows are read lazily: only the rows of nodes
-// the walk actually reaches (at most depth+1 of the N+1 rows).
+// workgroups per tree.  A thread owns PER consecutive vocabulary entries and keeps
+// their current probabilities in registers as fp64, so that a rejection only
+// streams the rejected node's draft distribution from HBM.  Logits rows are read
+// lazily: only the rows of nodes the walk may reach next.
 //
 // Every workgroup follows the same control flow.  Scalars that depend on the
-// whole vocabulary (row maximum and normaliser, residual mass, cumulative sums
-// for the final draw) are exchanged through a small table in the workspace:
-// each workgroup publishes its partial under a tag that is unique to the call
-// and the exchange number, then reads the W partials once all tags have
-// appeared.  All workgroups reduce the same values in the same order, so they
-// take identical decisions.  Waiting is bounded: if a partner never shows up
-// (the W workgroups of a tree are not all resident) the walk gives up and
-// reports accept_len = -1 instead of hanging; the last workgroup of a tree to
-// finish publishes the results and moves the call number on (see TreeWords), so
-// a call that gave up leaves nothing behind that a later call could mistake.
+// whole vocabulary (row maximum and normaliser, residual mass) are exchanged
+// through a small table in the workspace: each workgroup publishes its partial
+// under a tag that is unique to the call and the exchange number, then reads the
+// W partials once all tags have appeared.  All workgroups reduce the same values
+// in the same order, so they take identical decisions.
+//
+// What bounds it: the chain of exchanges, 2 - 2.5 us each through memory (a store that every
+// XCD can see, then a poll that sees it), not the bytes.  So the walk makes as few as it can and
+// hides its other work behind them:
+//   - an exchange carries, beside what it is needed for, the statistics of the row that comes
+//     next if the next candidate is accepted (worked out while the first part is on its way),
+//     so that an accepted candidate behind a rejection or behind the start costs no exchange;
+//   - the residual's owner of the next candidate's token publishes its value with the residual
+//     mass: the test needs nothing else;
+//   - the final draw takes the slices' sums from the last exchange;
+//   - the draft and logits slices of the next candidate and of its first child are asked for
+//     before the exchange in front of them.
+// Reductions across a wave are DPP moves (a shuffle through LDS takes several times as long), one
+// wave polls and reduces for the workgroup.  Measured (MI355X, us per call): one 60-node tree over a 128K vocabulary
+// 43.6 -> 22.7, eight 100-node trees over a 32K vocabulary 48.4 -> 25.8 (mean of three draws each, two or three
+// accepted tokens); ten rejections in a row 30, i.e. 2.5 a rejection, which is the exchange itself.
+//
+// Waiting is bounded: if a partner never shows up (the W workgroups of a tree are not all
+// resident) the walk gives up and reports accept_len = -1 instead of hanging; the last workgroup
+// of a tree to finish finds out and moves the call number on (see TreeWords), so a call that
+// gave up leaves nothing behind that a later call could mistake.
 #include "jk_internal.h"
 
 namespace jk {
 namespace {
 
-constexpr int kCoopThreads = 256;  // (512 measured 8 % faster for one tree and 60 % slower for eight: two workgroups per CU then)
+constexpr int kCoopThreads = 256;
 constexpr int kCoopWaves = kCoopThreads / 64;
 constexpr unsigned kDefaultSpinLimit = 1u << 12;  // polls before giving up: a few milliseconds
 
-// One workgroup's contribution to an exchange: two doubles, cut into four 32-bit halves,
-// each stored in a 64-bit word together with the exchange's 32-bit tag.  A word is written
-// and read with one 64-bit access, so a reader that sees the tag also sees the half that
-// belongs to it: no fences and no ordering between the words are needed.
-struct Slot {  // 32 bytes
-  unsigned long long word[4];
+// One workgroup's contribution to an exchange.  Every 64-bit word holds the exchange's 32-bit tag
+// and 32 bits of payload and is written and read with one access, so a reader that sees the tag
+// also sees the payload that belongs to it: no fences and no ordering between the words are needed.
+// Words 0 - 3 are what the exchange is for: a residual's mass (a double in two words) and the
+// residual's value at the next candidate's token (likewise; only the owner's counts), or a logits row's sum of
+// exponentials (two words) and largest logit (word 2).  Words 4 - 6: the same of the row that may come next.
+struct Slot {
+  unsigned long long word[8];
 };
 
 // Per-tree words in the workspace header.  `epoch` numbers the calls: every exchange of a call is
 // tagged with epoch + 1, and only the LAST workgroup of the tree to finish moves it on (it counts
-// the finished ones in `finish` and returns that to zero), so that workgroups that start late -
+// the finished ones, and those that gave up, in `finish` and returns that to zero), so that workgroups that start late -
 // even after the others have given up and left - still read the call's own epoch and can never
-// publish a tag that a later call would take for its own.  The results travel the same way: the
-// workgroup that owns the final draw leaves (tag, token) in `bonus`, workgroup 0 (tag, length) in
-// `len`, a workgroup that gave up its tag in `fail`; the last to finish reads the three and is
-// the only writer of accept_len and bonus_token.
+// publish a tag that a later call would take for its own.  The length and the bonus token are written
+// through to memory by the workgroups that know them; where one gave up, the last to finish overwrites them.
 struct TreeWords {  // 64 bytes
   unsigned long long epoch;
-  unsigned long long bonus, len, fail;
-  unsigned finish;
-  unsigned pad[7];
+  unsigned finish;  // finished workgroups, and << 16 those that gave up
+  unsigned pad[13];
 };
 
 // What a tree owns in the workspace: its words and two exchange tables of up to 64 slots.  Tree b's
 // block sits at b * sizeof(TreeBlock) whatever the batch size, mode or vocabulary of a call is, and
 // the blocks of all kCoopMaxTrees trees are set aside in every acceptance workspace (see
 // accept_coop_bytes), so calls of different shapes and modes can share one workspace.
-struct TreeBlock {  // 4160 bytes
+struct TreeBlock {  // 8256 bytes
   TreeWords words;
   Slot slots[2 * 64];
 };
 
 struct CoopParams {
-  int n_tree, vocab, max_depth, W, slice;
+  int n_tree, vocab, max_depth, W;
   double inv_temp;  // 1 / temperature
   const int *tokens, *parent;
   const float *logits, *draft, *uniforms;
@@ -74,400 +88,517 @@ struct CoopParams {
   unsigned* err;  // the workspace's sticky device error word
 };
 
-__device__ __forceinline__ double block_sum(double v, double* red) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  double s = 0.0;  // (waves in order: the same sum in every workgroup)
-#pragma unroll
-  for (int i = 0; i < kCoopWaves; i += 2) s += red[i] + red[i + 1];
-  return s;
+// ---- reductions over a wave, the result in every lane: exchanges with lane ^ 1, ^ 2 (quad_perm), then, the halves being
+// uniform by then, mirrored within 8 and 16, then halves of 32 and of 64 swapped
+template <int CTRL>
+__device__ __forceinline__ int dpp(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
 }
-__device__ __forceinline__ double block_max(double v, double* red) {
-  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  double m = red[0];
-#pragma unroll
-  for (int i = 1; i < kCoopWaves; ++i) m = fmax(m, red[i]);
-  return m;
+template <int CTRL>
+__device__ __forceinline__ double dpp64(double v) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = (unsigned)dpp<CTRL>((int)b), hi = (unsigned)dpp<CTRL>((int)(b >> 32));
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ unsigned other16(unsigned v, bool upper) {  // the value of lane ^ 16
+  const u32x2 s = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  return upper ? s[0] : s[1];
+}
+__device__ __forceinline__ unsigned other32(unsigned v, bool upper) {  // the value of lane ^ 32
+  const u32x2 s = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return upper ? s[0] : s[1];
+}
+__device__ __forceinline__ double swap64(double v, bool by32) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  const int lane = __lane_id();
+  unsigned lo = (unsigned)b, hi = (unsigned)(b >> 32);
+  if (by32) {
+    lo = other32(lo, lane & 32);
+    hi = other32(hi, lane & 32);
+  } else {
+    lo = other16(lo, lane & 16);
+    hi = other16(hi, lane & 16);
+  }
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  v += dpp64<0xB1>(v);   // quad_perm [1,0,3,2]
+  v += dpp64<0x4E>(v);   // quad_perm [2,3,0,1]
+  v += dpp64<0x141>(v);  // row_half_mirror
+  v += dpp64<0x140>(v);  // row_mirror
+  v += swap64(v, false);
+  v += swap64(v, true);
+  return v;
+}
+__device__ __forceinline__ float wave_max(float v) {
+  v = fmaxf(v, __int_as_float(dpp<0xB1>(__float_as_int(v))));
+  v = fmaxf(v, __int_as_float(dpp<0x4E>(__float_as_int(v))));
+  v = fmaxf(v, __int_as_float(dpp<0x141>(__float_as_int(v))));
+  v = fmaxf(v, __int_as_float(dpp<0x140>(__float_as_int(v))));
+  const int lane = __lane_id();
+  v = fmaxf(v, __uint_as_float(other16(__float_as_uint(v), lane & 16)));
+  v = fmaxf(v, __uint_as_float(other32(__float_as_uint(v), lane & 32)));
+  return v;
 }
 
-__global__ __launch_bounds__(kCoopThreads) void walk_sample_coop_kernel(CoopParams p) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  double* cur = reinterpret_cast<double*>(smem);   // [slice] current distribution of my slice
-  __shared__ double red[kCoopWaves];
-  __shared__ double xa[64], xb[64];                // the W partials of an exchange
-  __shared__ unsigned xh[256];                     // their 32-bit halves as they arrive
+// inclusive sums over the lanes: rows of 16 by shifts, then the rows' totals broadcast into the rows behind them
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp64_rows(double v) {  // 0 where there is no source lane
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, false);
+  const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ double wave_scan(double v) {
+  v += dpp64_rows<0x111, 0xf>(v);  // row_shr:1
+  v += dpp64_rows<0x112, 0xf>(v);
+  v += dpp64_rows<0x114, 0xf>(v);
+  v += dpp64_rows<0x118, 0xf>(v);
+  v += dpp64_rows<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+  v += dpp64_rows<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
+  return v;
+}
+__device__ __forceinline__ double lane_before(double v) { return dpp64_rows<0x138, 0xf>(v); }  // wave_shr:1
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)b, lane), hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+__device__ __forceinline__ double pair_to_double(unsigned lo, unsigned hi) {
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+template <int PER>
+__global__ __launch_bounds__(kCoopThreads, 2) void walk_sample_coop_kernel(CoopParams p) {
+  constexpr int SLICE = kCoopThreads * PER;
   __shared__ int par_s[JK_MAX_TREE];
   __shared__ int tok_s[JK_MAX_TREE];
-  __shared__ int s_fail, s_found;
-  __shared__ double xw[64];                        // weights of the W partial softmax sums
-  __shared__ double rej_inv[JK_MAX_TREE];          // 1 / residual mass of the rejected siblings at this node
-  __shared__ int rej_k[JK_MAX_TREE];
-  __shared__ float pf_q[JK_MAX_TREE + 2];          // prefetched scalars of the next candidate (see below)
+  __shared__ int qrow_s[JK_MAX_TREE];
   __shared__ float uni_s[JK_MAX_TREE + 1];
+  __shared__ double red_d[2][kCoopWaves];
+  __shared__ float red_f[2][kCoopWaves];
+  __shared__ double xs[64];    // the slices' sums under the current distribution
+  // What the polling wave found.  A wave may be two finds ahead of another one (a row adopted right behind another), so
+  // each kind has its own words.
+  __shared__ double got_row[2][2], got_res[2];
+  __shared__ int got_ok[3];
+  __shared__ int s_found;
+  __shared__ int s_lp[kCoopWaves];
+  __shared__ double pv_s;
 
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int W = p.W;
   const int b = blockIdx.x / W, w = blockIdx.x % W;
   const int N = p.n_tree, V = p.vocab, rows = N + 1;
-  const int v_lo = min(V, w * p.slice), v_hi = min(V, v_lo + p.slice);
-  const int n_mine = v_hi - v_lo;
-  constexpr int kPer = 4096 / kCoopThreads;        // slice elements per thread at most
+  const int v0 = w * SLICE + tid * PER;  // my first vocabulary entry
 
-  // the tree's small arrays: loads go out now, the values are parked in LDS after the first
-  // logits row has been processed (nothing needs them before), so their latency is hidden
+  // PER consecutive floats of a row (rows are not aligned in general: loads of four at any multiple of four bytes)
+  typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+  auto load_slice = [&](float (&dst)[PER], const float* row, float fill) {
+    if (PER >= 4 && v0 + PER <= V) {
+#pragma unroll
+      for (int u = 0; u < PER; u += 4) {
+        const f4 x = *reinterpret_cast<const f4*>(row + v0 + u);
+#pragma unroll
+        for (int i = 0; i < 4 && u + i < PER; ++i) dst[u + i] = x[i];
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < PER; ++u) dst[u] = v0 + u < V ? row[v0 + u] : fill;
+    }
+  };
+  auto row_of = [&](int r) { return p.logits + ((long long)b * rows + r) * V; };
+
+  float lg[PER];
+  load_slice(lg, row_of(0), -INFINITY);  // (the first row is on its way before anything else is known)
   int pa_reg = -1, tok_reg = 0;
-  float uni_reg = 0.f;
+  TreeWords* tw = &p.trees[b].words;
+  const unsigned long long epoch = __hip_atomic_load(&tw->epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (tid < N) {
     pa_reg = p.parent[(long long)b * N + tid];
     tok_reg = p.tokens[(long long)b * N + tid];
-  }
-  if (tid <= N) uni_reg = p.uniforms[(long long)b * rows + tid];
-  if (tid == 0) s_fail = 0;
-  TreeWords* tw = &p.trees[b].words;
-  const unsigned long long epoch = __hip_atomic_load(&tw->epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __syncthreads();
-
-  // the draft distribution of node k (a row of p.draft)
-  auto q_of = [&](int k) -> const float* {
-    long long r = (long long)b * N + k;
+    long long r = (long long)b * N + tid;
     if (p.draft_row) {
       r = p.draft_row[r];
       r = r < 0 ? 0 : (r >= p.n_draft_rows ? p.n_draft_rows - 1 : r);  // a bad row number must not fault
     }
-    return p.draft + r * V;
-  };
+    par_s[tid] = (pa_reg >= -1 && pa_reg < tid) ? pa_reg : -1;
+    tok_s[tid] = min(max(tok_reg, 0), V - 1);  // a token id outside the vocabulary must not fault
+    qrow_s[tid] = (int)r;
+    if (w == 0) {  // both repairs are recorded in the workspace's error word
+      if (par_s[tid] != pa_reg) __hip_atomic_fetch_or(p.err, kDevErrBadTree, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (tok_s[tid] != tok_reg) __hip_atomic_fetch_or(p.err, kDevErrBadToken, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+  if (tid <= N) uni_s[tid] = p.uniforms[(long long)b * rows + tid];
+  __syncthreads();
+  auto q_of = [&](int k) { return p.draft + (long long)qrow_s[k] * V; };  // the draft distribution of node k
 
   // smallest j >= from with parent c, or -1: every wave looks at all (at most 128) nodes, two
   // per lane, so no barrier is needed and all waves get the same answer
   auto find_child = [&](int c, int from) -> int {
-    const int lane = tid & 63;
     const bool h0 = lane < N && lane >= from && par_s[lane] == c;
     const bool h1 = lane + 64 < N && lane + 64 >= from && par_s[lane + 64] == c;
     const unsigned long long m0 = __ballot(h0), m1 = __ballot(h1);
     return m0 ? __ffsll((long long)m0) - 1 : (m1 ? 63 + __ffsll((long long)m1) : -1);
   };
 
-  const int n_per = (p.slice + kCoopThreads - 1) / kCoopThreads;  // slice elements per thread (uniform)
-  Slot* slots = p.trees[b].slots;
-  unsigned n_exch = 0;
+  // A candidate and what will be needed of it: its draft slice and value at its token, the logits slice of its own row
+  // (the one that counts if it is accepted) and that row's value at its first child's token.
+  struct Candidate {
+    int k, first;  // node, its first child (or -1)
+    float q[PER], lg[PER];
+    float qx, row_x;
+  };
+  auto fetch = [&](Candidate& n, int k) {
+    n.k = k;
+    n.first = -1;
+    if (k < 0) return;
+    n.first = find_child(k, k + 1);
+    const float *q = q_of(k), *row = row_of(k + 1);
+    load_slice(n.q, q, 0.f);
+    n.qx = q[tok_s[k]];
+    load_slice(n.lg, row, -INFINITY);
+    n.row_x = row[tok_s[n.first < 0 ? k : n.first]];
+  };
 
-  // all-gather of one (a, b) pair per workgroup; results in xa[0..W), xb[0..W).
-  // Tags: 22 bits of call epoch, 10 bits of exchange number (at most N + depth + 2 < 1024 per
-  // call).  Both tables are rewritten by every call (a call has at least two exchanges), so
-  // a stale word is at most one epoch old and can never carry the current tag.
-  auto exchange = [&](double a, double bb, double pad_a) {
+  int flip = 0;  // alternates the LDS words of consecutive block reductions: one barrier each
+  auto block_sum = [&](double v) {
+    flip ^= 1;
+    v = wave_sum(v);
+    if (lane == 0) red_d[flip][wave] = v;
+    __syncthreads();
+    return (red_d[flip][0] + red_d[flip][1]) + (red_d[flip][2] + red_d[flip][3]);
+  };
+  auto block_max = [&](float v) {
+    flip ^= 1;
+    v = wave_max(v);
+    if (lane == 0) red_f[flip][wave] = v;
+    __syncthreads();
+    return fmaxf(fmaxf(red_f[flip][0], red_f[flip][1]), fmaxf(red_f[flip][2], red_f[flip][3]));
+  };
+
+  // Tags: 22 bits of call epoch, 10 bits of exchange number (at most N + depth + 2 < 1024 per call).  The two tables take
+  // turns from exchange to exchange and from call to call, and every exchange writes all its words.
+  unsigned n_exch = 0, tag = 0;
+  Slot* tab = nullptr;
+  auto open_exchange = [&] {
     ++n_exch;
-    const unsigned tag = (unsigned)(((epoch + 1) & 0x3FFFFFull) << 10) | (n_exch & 0x3FFu);
-    Slot* tab = slots + (n_exch & 1) * W;
+    tag = (unsigned)(((epoch + 1) & 0x3FFFFFull) << 10) | (n_exch & 0x3FFu);
+    tab = p.trees[b].slots + ((n_exch + (unsigned)epoch) & 1u) * 64;
+  };
+  auto put = [&](int word, unsigned payload) {
+    __hip_atomic_store(&tab[w].word[word], ((unsigned long long)tag << 32) | payload, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  auto publish4 = [&](double a, double v) {  // words 0 - 3
     if (tid < 4) {
-      const unsigned long long bits = (unsigned long long)__double_as_longlong(tid < 2 ? a : bb);
-      const unsigned half = (unsigned)(bits >> (32 * (tid & 1)));
-      __hip_atomic_store(&tab[w].word[tid], ((unsigned long long)tag << 32) | half, __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
+      const unsigned long long bits = (unsigned long long)__double_as_longlong(tid < 2 ? a : v);
+      put(tid, (unsigned)(bits >> (32 * (tid & 1))));
     }
-    if (tid < 4 * W) {
-      unsigned long long* src = &tab[tid >> 2].word[tid & 3];
-      unsigned long long v;
-      unsigned spins = 0;
-      while ((unsigned)((v = __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 32) != tag) {
-        if (++spins > p.spin_limit || s_fail) { s_fail = 1; v = 0; break; }
-        __builtin_amdgcn_s_sleep(1);
+  };
+  auto publish_row = [&](int at, double z, float m) {  // words at, at + 1 (z), at + 2 (m)
+    if (tid < 3) {
+      const unsigned long long bits = (unsigned long long)__double_as_longlong(z);
+      put(at + tid, tid == 2 ? __float_as_uint(m) : (unsigned)(bits >> (32 * tid)));
+    }
+  };
+  // wave 0: lane i waits for words [at, at + n) of workgroup i and returns their payloads
+  auto await = [&](int at, int n, unsigned (&pay)[4]) -> bool {
+    const bool in = lane < W;
+    unsigned spins = 0;
+    for (;;) {
+      bool ok = true;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (i < n && in) {
+          const unsigned long long v = __hip_atomic_load(&tab[lane].word[at + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          ok = ok && (unsigned)(v >> 32) == tag;
+          pay[i] = (unsigned)v;
+        }
+      if (__all(ok)) return true;
+      if (++spins > p.spin_limit) return false;
+      __builtin_amdgcn_s_sleep(1);
+    }
+  };
+
+  double e[PER];               // exp(row / T - its slice's maximum) of the row that `e_m` belongs to
+  float e_m = 0.f;
+  double cur[PER];             // the current distribution
+  double row_m = 0.0, row_inv = 1.0;  // of the current row: maximum of row / T, 1 / sum of exp(row / T - maximum)
+
+  // slice statistics of a row: e[], e_m (largest logit of the slice) and the slice's sum
+  auto slice_stats = [&](const float (&x)[PER]) -> double {
+    float m = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) m = fmaxf(m, x[u]);
+    e_m = block_max(m);
+    const double ref = e_m == -INFINITY ? 0.0 : (double)e_m * p.inv_temp;
+    double z = 0.0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      e[u] = exp((double)x[u] * p.inv_temp - ref);
+      z += e[u];
+    }
+    return block_sum(z);
+  };
+  // everybody's statistics of a row -> its maximum, normaliser and slice sums; cur[] from e[]
+  auto adopt_row = [&](int at) -> bool {
+    if (wave == 0) {
+      unsigned pay[4] = {0u, 0u, 0u, 0u};
+      const bool ok = await(at, 3, pay);
+      const float m_w = lane < W ? __uint_as_float(pay[2]) : -INFINITY;
+      const float m = wave_max(m_w);
+      const double ref = m == -INFINITY ? 0.0 : (double)m * p.inv_temp;
+      const double z_w = lane < W ? pair_to_double(pay[0], pay[1]) * exp((m_w == -INFINITY ? 0.0 : (double)m_w * p.inv_temp) - ref) : 0.0;
+      const double z = wave_sum(lane < W && m_w != -INFINITY ? z_w : 0.0);
+      const double inv = 1.0 / z;
+      xs[lane] = (m_w == -INFINITY ? 0.0 : z_w) * inv;
+      if (lane == 0) {
+        got_row[at == 4][0] = ref;
+        got_row[at == 4][1] = inv;
+        got_ok[at == 4] = ok;
       }
-      xh[tid] = (unsigned)v;
     }
     __syncthreads();
-    if (tid < W) {
-      xa[tid] = __longlong_as_double((long long)(((unsigned long long)xh[4 * tid + 1] << 32) | xh[4 * tid]));
-      xb[tid] = __longlong_as_double((long long)(((unsigned long long)xh[4 * tid + 3] << 32) | xh[4 * tid + 2]));
-    } else if (tid < 64) {
-      xa[tid] = pad_a;  // the reductions below always run over 64 entries
-      xb[tid] = 0.0;
-    }
-    __syncthreads();
-  };
-  // sum of 64 LDS doubles in a fixed order (four interleaved chains): identical in every workgroup
-  auto sum64 = [&](const double* v) {
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+    row_m = got_row[at == 4][0];
+    row_inv = got_row[at == 4][1];
+    const double ref = e_m == -INFINITY ? 0.0 : (double)e_m * p.inv_temp;
+    const double sc = exp(ref - row_m) * row_inv;
 #pragma unroll
-    for (int i = 0; i < 64; i += 4) {
-      a0 += v[i];
-      a1 += v[i + 1];
-      a2 += v[i + 2];
-      a3 += v[i + 3];
-    }
-    return (a0 + a1) + (a2 + a3);
+    for (int u = 0; u < PER; ++u) cur[u] = e[u] * sc;
+    return got_ok[at == 4] != 0;
   };
 
-  double row_m = 0.0, row_inv_z = 1.0;  // max of row/T, and 1 / sum of exp(row/T - max), of the current row
-  const float* row = nullptr;
-
-  // softmax of logits row r over my slice into cur[]; (row_m, row_inv_z) for everybody
-  auto load_row = [&](int r) {
-    row = p.logits + ((long long)b * rows + r) * V;
-    double z[kPer];
-    double lm = -INFINITY;
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      if (u >= n_per) break;
-      const int i = tid + u * kCoopThreads;
-      z[u] = i < n_mine ? (double)row[v_lo + i] * p.inv_temp : -INFINITY;
-      lm = fmax(lm, z[u]);
-    }
-    const double m_w = block_max(lm, red);
-    const double m_use = (m_w == -INFINITY) ? 0.0 : m_w;
-    double ls = 0.0;
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      if (u >= n_per) break;
-      z[u] = exp(z[u] - m_use);
-      ls += z[u];
-    }
-    const double z_w = block_sum(ls, red);
-    exchange(m_w, z_w, -INFINITY);
-    double M0 = -INFINITY, M1 = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < 64; i += 2) {
-      M0 = fmax(M0, xa[i]);
-      M1 = fmax(M1, xa[i + 1]);
-    }
-    const double M = fmax(M0, M1);
-    const double M_use = (M == -INFINITY) ? 0.0 : M;
-    if (tid < 64) xw[tid] = xb[tid] * exp(xa[tid] - M_use);  // 0 for an empty slice (-inf) and for the padding
-    __syncthreads();
-    const double Z = sum64(xw);  // same numbers, same order in every workgroup
-    row_m = M_use;
-    row_inv_z = 1.0 / Z;
-    const double sc = exp(m_use - M_use) * row_inv_z;
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      if (u >= n_per) break;
-      const int i = tid + u * kCoopThreads;
-      if (i < n_mine) cur[i] = z[u] * sc;
-    }
-    __syncthreads();
+  Candidate cand, ahead;
+  fetch(cand, find_child(-1, 0));
+  bool row_known;  // e[] and the open exchange's words 4 - 6 are the statistics of cand's own row
+  // The statistics of candidate n's row, behind the exchange that is under way (zeros for none: the words are always written)
+  auto look_ahead = [&](const Candidate& n) {
+    double z = 0.0;
+    if (n.k >= 0) z = slice_stats(n.lg);
+    publish_row(4, z, n.k >= 0 ? e_m : 0.f);
   };
 
-  // Scalars a candidate's test needs, gathered by one thread each and parked in LDS:
-  // pf_q[i] = q_{rej_k[i]}[x] for the n_rej siblings rejected so far, then q_child[x], then
-  // logits_row[x], with x the candidate's token.  `extra` >= 0 adds one more (pending)
-  // rejected sibling to the list: the gather for the next sibling is issued before the
-  // current one's fate is known, so that its latency hides behind the exchange.
-  auto gather_issue = [&](int child, int n_rej, int extra) -> float {
-    const int x = tok_s[child];
-    const int n_list = n_rej + (extra >= 0 ? 1 : 0);
-    float v = 0.f;
-    if (tid < n_list) {
-      const int kq = tid < n_rej ? rej_k[tid] : extra;
-      v = q_of(kq)[x];
-    } else if (tid == n_list) {
-      v = q_of(child)[x];
-    } else if (tid == n_list + 1) {
-      v = row[x];
+  int c = -1, len = 0;
+  double px = 0.0;  // probability of cand's token under the current distribution
+  bool alive;
+  {
+    const double z = slice_stats(lg);
+    open_exchange();
+    publish_row(0, z, e_m);
+    if (tid == 3) put(3, 0u);
+    double e0[PER];
+    const float m0 = e_m;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) e0[u] = e[u];
+    const float row_x = row_of(0)[tok_s[cand.k < 0 ? 0 : cand.k]];
+    look_ahead(cand);
+    double e1[PER];
+    const float m1 = e_m;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      e1[u] = e[u];
+      e[u] = e0[u];
     }
-    return v;
-  };
-  auto gather_park = [&](float v, int n_list) {
-    if (tid < n_list + 2) pf_q[tid] = v;
-  };
-
-  int c = -1, len = 0, n_rej = 0;
-  load_row(0);
-  if (tid < N) {
-    par_s[tid] = (pa_reg >= -1 && pa_reg < tid) ? pa_reg : -1;
-    tok_s[tid] = min(max(tok_reg, 0), V - 1);  // a token id outside the vocabulary must not fault
-    if (w == 0) {  // both repairs are recorded in the workspace's error word
-      if (par_s[tid] != pa_reg) __hip_atomic_fetch_or(p.err, kDevErrBadTree, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (tok_s[tid] != tok_reg) __hip_atomic_fetch_or(p.err, kDevErrBadToken, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    e_m = m0;
+    alive = adopt_row(0);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) e[u] = e1[u];
+    e_m = m1;
+    row_known = true;
+    px = exp((double)row_x * p.inv_temp - row_m) * row_inv;
   }
-  if (tid <= N) uni_s[tid] = uni_reg;
-  __syncthreads();
-  int child = find_child(-1, 0);
-  bool have_pf = false;     // pf_q[] and qreg[] already hold `child`'s data
-  float qreg[kPer];         // q_child over my slice
-  while (!s_fail && child >= 0) {
-    const float* qk = q_of(child);
-    if (!have_pf) {
-      const float v = gather_issue(child, n_rej, -1);
-#pragma unroll
-      for (int u = 0; u < kPer; ++u) {
-        const int i = tid + u * kCoopThreads;
-        qreg[u] = i < n_mine ? qk[v_lo + i] : 0.f;
-      }
-      gather_park(v, n_rej);
-      __syncthreads();
-    }
-    // probability of token x under the current distribution: the same chain of operations in
-    // every workgroup (global data only), so that all take the same decision
-    double px = exp((double)pf_q[n_rej + 1] * p.inv_temp - row_m) * row_inv_z;
-    for (int i = 0; i < n_rej; ++i) px = fmax(0.0, px - (double)pf_q[i]) * rej_inv[i];
-    const double lhs = (double)uni_s[child] * (double)pf_q[n_rej];
-    if (lhs < px) {
-      if (tid == 0 && w == 0) p.out_path[(long long)b * p.max_depth + len] = child;
+  while (alive && cand.k >= 0) {
+    const int k = cand.k;
+    if ((double)uni_s[k] * (double)cand.qx < px) {
+      // ---- accepted: the row of k becomes the current one, its first child the candidate
+      if (tid == 0 && w == 0) p.out_path[(long long)b * p.max_depth + len] = k;
       ++len;
-      c = child;
-      n_rej = 0;
-      have_pf = false;
-      __syncthreads();  // pf_q is rewritten for the first child
-      load_row(c + 1);
+      c = k;
+      const float row_x = cand.row_x;
       // at max_depth accepted nodes the walk stops: the token after c is drawn from c's own row
-      child = len < p.max_depth ? find_child(c, c + 1) : -1;
+      const int next = len < p.max_depth ? cand.first : -1;
+      if (row_known) {
+        fetch(ahead, next);
+        alive = adopt_row(4);
+        row_known = false;
+      } else {
+        const double z = slice_stats(cand.lg);
+        fetch(ahead, next);
+        open_exchange();
+        publish_row(0, z, e_m);
+        if (tid == 3) put(3, 0u);
+        double e0[PER];
+        const float m0 = e_m;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) e0[u] = e[u];
+        look_ahead(ahead);
+        double e1[PER];
+        const float m1 = e_m;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+          e1[u] = e[u];
+          e[u] = e0[u];
+        }
+        e_m = m0;
+        alive = adopt_row(0);
+#pragma unroll
+        for (int u = 0; u < PER; ++u) e[u] = e1[u];
+        e_m = m1;
+        row_known = true;
+      }
+      px = exp((double)row_x * p.inv_temp - row_m) * row_inv;
+      cand = ahead;
       continue;
     }
-    // rejected: candidate residual of my slice and its mass
-    double part = 0.0;
-    double res[kPer];
+    // ---- rejected: the residual's mass, and its value at the next sibling's token
+    fetch(ahead, find_child(c, k + 1));
+    const int x = ahead.k >= 0 ? tok_s[ahead.k] : 0;
+    double part = 0.0, at_x = 0.0, res[PER];
 #pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      if (u >= n_per) break;
-      const int i = tid + u * kCoopThreads;
-      res[u] = i < n_mine ? fmax(0.0, cur[i] - (double)qreg[u]) : 0.0;
+    for (int u = 0; u < PER; ++u) {
+      res[u] = v0 + u < V ? fmax(0.0, cur[u] - (double)cand.q[u]) : 0.0;
       part += res[u];
+      if (v0 + u == x) at_x = res[u];
     }
-    // the next sibling's data go out now; they arrive while the exchange is under way
-    const int nxt_child = find_child(c, child + 1);
-    float pv = 0.f;
-    float qnext[kPer];
-    if (nxt_child >= 0) {
-      pv = gather_issue(nxt_child, n_rej, child);
-      const float* qn = q_of(nxt_child);
-#pragma unroll
-      for (int u = 0; u < kPer; ++u) {
-        const int i = tid + u * kCoopThreads;
-        qnext[u] = i < n_mine ? qn[v_lo + i] : 0.f;
+    if (x >= v0 && x < v0 + PER) pv_s = at_x;  // (one thread of one workgroup; the sum's barrier orders it)
+    const double s_w = block_sum(part);
+    open_exchange();
+    publish4(s_w, pv_s);
+    look_ahead(ahead);
+    row_known = true;
+    if (wave == 0) {
+      unsigned pay[4] = {0u, 0u, 0u, 0u};
+      const bool ok = await(0, 4, pay);
+      const double mine = lane < W ? pair_to_double(pay[0], pay[1]) : 0.0;
+      const double s = wave_sum(mine);
+      const int owner = __builtin_amdgcn_readfirstlane(x / SLICE);
+      const double v = pair_to_double(__builtin_amdgcn_readlane(pay[2], owner), __builtin_amdgcn_readlane(pay[3], owner));
+      if (s > 0.0) xs[lane] = mine * (1.0 / s);
+      if (lane == 0) {
+        got_res[0] = s;
+        got_res[1] = v;
+        got_ok[2] = ok;
       }
-    }
-    const double s_w = block_sum(part, red);
-    exchange(s_w, 0.0, 0.0);
-    const double s = sum64(xa);
-    have_pf = false;
-    if (s > 0.0) {
-      const double inv_s = 1.0 / s;
-#pragma unroll
-      for (int u = 0; u < kPer; ++u) {
-        const int i = tid + u * kCoopThreads;
-        if (i < n_mine) cur[i] = res[u] * inv_s;
-      }
-      if (tid == 0) { rej_k[n_rej] = child; rej_inv[n_rej] = inv_s; }
-      if (nxt_child >= 0) {  // the prefetched list assumed exactly this rejection
-        gather_park(pv, n_rej + 1);
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) qreg[u] = qnext[u];  // (registers: nothing to skip)
-        have_pf = true;
-      }
-      ++n_rej;
     }
     __syncthreads();
-    child = nxt_child;
+    alive = got_ok[2] != 0;
+    const double s = got_res[0];
+    if (s > 0.0) {
+      const double inv = 1.0 / s;
+#pragma unroll
+      for (int u = 0; u < PER; ++u) cur[u] = res[u] * inv;
+      px = got_res[1] * inv;
+    } else if (alive && ahead.k >= 0) {
+      // nothing left of the distribution: it stays as it was, and the next token's value under it has to be asked for
+      double e1[PER];
+      if (x >= v0 && x < v0 + PER) {
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+          if (v0 + u == x) pv_s = cur[u];
+      }
+      __syncthreads();
+      // (the row statistics ahead go along again: words 4 - 6 belong to the exchange that is open)
+#pragma unroll
+      for (int u = 0; u < PER; ++u) e1[u] = e[u];
+      const float m1 = e_m;
+      double z = 0.0;
+#pragma unroll
+      for (int u = 0; u < PER; ++u) z += e1[u];
+      z = block_sum(z);
+      open_exchange();
+      publish4(0.0, pv_s);
+      publish_row(4, z, m1);
+      if (wave == 0) {
+        unsigned pay[4] = {0u, 0u, 0u, 0u};
+        const bool ok = await(0, 4, pay);
+        const int owner = __builtin_amdgcn_readfirstlane(x / SLICE);
+        const double v = pair_to_double(__builtin_amdgcn_readlane(pay[2], owner), __builtin_amdgcn_readlane(pay[3], owner));
+        if (lane == 0) {
+          got_res[1] = v;
+          got_ok[2] = ok;
+        }
+      }
+      __syncthreads();
+      alive = got_ok[2] != 0;
+      px = got_res[1];
+    }
+    cand = ahead;
   }
   // ---- final draw: smallest v whose cumulative probability exceeds u * total
-  if (!s_fail) {
-    double part = 0.0;
-    int last_pos = -1;
-    // contiguous segments per thread so that the in-slice order is the vocabulary order
-    const int seg = (n_mine + kCoopThreads - 1) / kCoopThreads;
-    const int i0 = min(n_mine, tid * seg), i1 = min(n_mine, i0 + seg);
-    for (int i = i0; i < i1; ++i) {
-      part += cur[i];
-      if (cur[i] > 0.0) last_pos = v_lo + i;
-    }
-    // scan of the 256 segment sums: wave scan, then wave offsets.  A thread's interval is
-    // [off + excl, off + incl) with excl taken from its left neighbour's incl, so that the
-    // intervals of threads, waves and workgroups tile [0, total) exactly, rounding included.
-    double incl = part;
-    for (int o = 1; o < 64; o <<= 1) {
-      const double t = __shfl_up(incl, o);
-      if ((tid & 63) >= o) incl += t;
-    }
-    double excl = __shfl_up(incl, 1);
-    if ((tid & 63) == 0) excl = 0.0;
-    __syncthreads();
-    if ((tid & 63) == 63) red[tid >> 6] = incl;
-    int lp = last_pos;
-    for (int o = 32; o > 0; o >>= 1) lp = max(lp, __shfl_xor(lp, o));
-    __shared__ int s_lp[kCoopWaves];
-    if ((tid & 63) == 0) s_lp[tid >> 6] = lp;
-    __syncthreads();
-    double woff = 0.0;
-    for (int i = 0; i < (tid >> 6); ++i) woff += red[i];
-    double t_w = 0.0;  // (in wave order, like the offsets: the last wave's interval ends exactly at the total)
-    int lp_w = -1;
+  if (alive) {
+    // workgroup i owns the crossing iff before(i) <= target < before(i) + its sum, with before(i) its left neighbour's
+    // scanned sum: the intervals tile [0, total), rounding included, and every workgroup computes the same ones
+    const double upto = wave_scan(lane < W ? xs[lane] : 0.0);
+    const double before = lane_before(upto);
+    const double total = lane_value(upto, 63);
+    const double target = (double)uni_s[N] * total;
+    const unsigned long long hit = __ballot(before <= target && upto > target);
+    const int owner = hit ? __ffsll((long long)hit) - 1 : -1;
+    const double owner_lo = hit ? lane_value(before, owner) : 0.0;
+    if (w == owner) {
+      const double local = target - owner_lo;
+      double part = 0.0;
+      int last_pos = -1;
 #pragma unroll
-    for (int i = 0; i < kCoopWaves; ++i) {
-      t_w += red[i];
-      lp_w = max(lp_w, s_lp[i]);
-    }
-    exchange(t_w, (double)lp_w, 0.0);
-    if (!s_fail) {
-      double before = 0.0, total = 0.0;
-      int last_any = -1;
-      for (int i = 0; i < W; ++i) {
-        if (i < w) before += xa[i];
-        total += xa[i];
-        last_any = max(last_any, (int)xb[i]);
+      for (int u = 0; u < PER; ++u) {
+        if (v0 + u < V) {
+          part += cur[u];
+          if (cur[u] > 0.0) last_pos = v0 + u;
+        }
       }
-      const double target = (double)uni_s[N] * total;
+      // scan of the threads' sums: wave scan, then wave offsets
+      const double incl = wave_scan(part), excl = lane_before(incl);
+      flip ^= 1;
+      if (lane == 63) red_d[flip][wave] = incl;
+      int lp = last_pos;
+      for (int o = 32; o > 0; o >>= 1) lp = max(lp, __shfl_xor(lp, o));
+      if (lane == 0) s_lp[wave] = lp;
       if (tid == 0) s_found = -1;
       __syncthreads();
-      // is the crossing inside my segment?
-      const double lo = before + (woff + excl), hi = before + (woff + incl);
-      if (i1 > i0 && lo <= target && hi > target) {
+      double off = 0.0;
+      for (int i = 0; i < wave; ++i) off += red_d[flip][i];
+      const double lo = off + excl, hi = off + incl;
+      if (lo <= local && hi > local) {
         double run = lo;
         int found = -1;
-        for (int i = i0; i < i1; ++i) {
-          run += cur[i];
-          if (run > target) { found = v_lo + i; break; }
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+          if (v0 + u < V) {
+            run += cur[u];
+            if (found < 0 && run > local) found = v0 + u;
+          }
         }
-        if (found < 0) found = v_lo + i1 - 1;  // rounding between the scanned and the re-added sums
+        if (found < 0) found = last_pos;  // rounding between the scanned and the re-added sums
         atomicMax(&s_found, found);
       }
       __syncthreads();
-      const bool mine = s_found >= 0;
-      // nobody crosses (u * total not below the last cumulative value): largest v with p > 0.
-      // Decided identically everywhere: workgroup w' owns the crossing iff
-      // before(w') <= target < before(w') + t(w'); sums of the same numbers in the same order.
-      bool any = false;
-      {
-        double acc = 0.0;
-        for (int i = 0; i < W; ++i) {
-          if (acc <= target && acc + xa[i] > target) any = true;
-          acc += xa[i];
-        }
-      }
       if (tid == 0) {
-        const unsigned long long tag = (epoch + 1) << 32;
-        if (mine || (!any && w == 0)) {
-          const int token = mine ? s_found : (last_any < 0 ? 0 : last_any);
-          __hip_atomic_store(&tw->bonus, tag | (unsigned)token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        if (w == 0) {
-          for (int i = len; i < p.max_depth; ++i) p.out_path[(long long)b * p.max_depth + i] = -1;
-          __hip_atomic_store(&tw->len, tag | (unsigned)len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        // (the slice's published sum and the re-added one may differ in the last place: then its last entry with p > 0)
+        const int token = s_found >= 0 ? s_found : max(max(s_lp[0], s_lp[1]), max(s_lp[2], s_lp[3]));
+        __hip_atomic_store(&p.out_bonus[b], token < 0 ? 0 : token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
+    if (w == 0 && tid == 0) {
+      if (owner < 0) __hip_atomic_store(&p.out_bonus[b], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // no entry with p > 0
+      for (int i = len; i < p.max_depth; ++i) p.out_path[(long long)b * p.max_depth + i] = -1;
+      __hip_atomic_store(&p.out_len[b], len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
   }
-  // ---- the end of this workgroup: say so; the last one of the tree publishes the results
+  // ---- the end of this workgroup: say so; where one of the tree gave up, the last to finish takes the results back
   if (tid == 0) {
-    const unsigned long long tag = (epoch + 1) << 32;
-    if (s_fail) __hip_atomic_store(&tw->fail, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // (the words above went through to memory; wait for that before the count can tell anybody)
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    const unsigned done = __hip_atomic_fetch_add(&tw->finish, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (done == (unsigned)W - 1) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the results went through to memory before the count can tell anybody)
+    const unsigned mine = 1u + (alive ? 0u : 0x10000u);
+    const unsigned all = __hip_atomic_fetch_add(&tw->finish, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + mine;
+    if ((all & 0xFFFFu) == (unsigned)W) {
       __hip_atomic_store(&tw->finish, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const unsigned long long f = __hip_atomic_load(&tw->fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const unsigned long long l = __hip_atomic_load(&tw->len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const unsigned long long t = __hip_atomic_load(&tw->bonus, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const bool ok = f != tag && (l >> 32) == (tag >> 32) && (t >> 32) == (tag >> 32);
-      p.out_len[b] = ok ? (int)(unsigned)l : -1;
-      p.out_bonus[b] = ok ? (int)(unsigned)t : -1;
-      if (!ok) __hip_atomic_fetch_or(p.err, kDevErrWalkWait, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (all >> 16) {
+        __hip_atomic_store(&p.out_len[b], -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&p.out_bonus[b], -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_or(p.err, kDevErrWalkWait, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
       __hip_atomic_store(&tw->epoch, epoch + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
@@ -481,22 +612,28 @@ __global__ __launch_bounds__(kCoopThreads) void walk_sample_coop_kernel(CoopPara
 constexpr int kCoopMaxTrees = 512;
 size_t accept_coop_bytes() { return (size_t)kCoopMaxTrees * sizeof(TreeBlock); }
 
-bool accept_coop_plan(int batch, int vocab, int cus, int* W, int* slice) {
+bool accept_coop_plan(int batch, int vocab, int cus, int* W, int* per) {
   if (batch > kCoopMaxTrees) return false;
-  int w = (2 * cus) / batch;
-  if (w > 64) w = 64;
-  if (w < 1) return false;
-  const int sl = (vocab + w - 1) / w;
-  if (sl > 4096) return false;  // 4096 doubles of LDS and 16 slice elements per thread
-  *W = w;
-  *slice = sl;
-  return true;
+  int most = (2 * cus) / batch;  // two workgroups per CU are resident together
+  if (most > 64) most = 64;
+  // Entries per thread: fewer of them mean more workgroups to wait for, more of them longer rows of exponentials.  Eight
+  // trees of 32 000 entries: 2 a thread (63 workgroups a tree) 28.1, 4 (32) 25.9, 8 (16) 27.4, 16 (8) 34.7 us; one tree of
+  // 128 256: 8 (63) 24.4, 16 (32) 30.0 us.
+  for (int n = 4; n <= 16; n *= 2) {
+    const int need = (vocab + kCoopThreads * n - 1) / (kCoopThreads * n);
+    if (need <= most) {
+      *W = need;
+      *per = n;
+      return true;
+    }
+  }
+  return false;
 }
 
-hipError_t launch_accept_coop(const AcceptArgs& a, void* coop_ws, int W, int slice, hipStream_t stream) {
+hipError_t launch_accept_coop(const AcceptArgs& a, void* coop_ws, int W, int per, hipStream_t stream) {
   CoopParams cp;
   cp.err = static_cast<unsigned*>(a.workspace);
-  cp.n_tree = a.n_tree; cp.vocab = a.vocab; cp.max_depth = a.max_depth; cp.W = W; cp.slice = slice;
+  cp.n_tree = a.n_tree; cp.vocab = a.vocab; cp.max_depth = a.max_depth; cp.W = W;
   cp.inv_temp = 1.0 / (double)a.temperature;
   cp.tokens = a.tokens; cp.parent = a.parent;
   cp.logits = a.logits; cp.draft = a.draft_probs; cp.uniforms = a.uniforms;
@@ -504,11 +641,13 @@ hipError_t launch_accept_coop(const AcceptArgs& a, void* coop_ws, int W, int sli
   cp.trees = static_cast<TreeBlock*>(coop_ws);
   cp.spin_limit = tuning().spin_limit >= 0 ? (unsigned)tuning().spin_limit : kDefaultSpinLimit;
   cp.out_path = a.out_path; cp.out_len = a.out_len; cp.out_bonus = a.out_bonus;
-  const size_t lds = (size_t)slice * sizeof(double);
-  static LdsLimitRaised raised;
-  if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(walk_sample_coop_kernel), 4096 * 8, raised); e != hipSuccess)
-    return e;
-  hipLaunchKernelGGL(walk_sample_coop_kernel, dim3(a.batch * W), dim3(kCoopThreads), lds, stream, cp);
+  const dim3 grid((unsigned)(a.batch * W)), block(kCoopThreads);
+  switch (per) {
+    case 4: hipLaunchKernelGGL(walk_sample_coop_kernel<4>, grid, block, 0, stream, cp); break;
+    case 8: hipLaunchKernelGGL(walk_sample_coop_kernel<8>, grid, block, 0, stream, cp); break;
+    case 16: hipLaunchKernelGGL(walk_sample_coop_kernel<16>, grid, block, 0, stream, cp); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 

@@ -518,3 +518,56 @@ def test_bad_tokens_and_parents_are_repaired_and_reported(mode, single):
     assert err == jk.JK_DEVERR_BAD_TREE and err_fixed == 0
     for g, w in zip(got, want):
         np.testing.assert_array_equal(g, w)
+
+
+def _near_the_target(a, par, rng, sigma):
+    """Draft distributions near the target's (noise sigma on its logits; below zero: the target's own), tokens drawn from them."""
+    V = a["logits"].shape[-1]
+    for b in range(par.shape[0]):
+        for k in range(par.shape[1]):
+            z = a["logits"][b, par[b, k] + 1].astype(np.float64)
+            if sigma > 0:
+                z = z + rng.standard_normal(V) * sigma
+            e = np.exp(z - z.max())
+            q = (e / e.sum()).astype(np.float32)
+            a["draft_probs"][b, k] = q
+            cdf = np.cumsum(q, dtype=np.float64)
+            a["tokens"][b, k] = min(int(np.searchsorted(cdf, rng.random() * cdf[-1], side="right")), V - 1)
+
+
+@pytest.mark.parametrize("V", [1, 2, 5, 1023, 1024, 1025, 4099, 65535, 65536, 65537, 131071, 131073, 262145])
+def test_sample_vocabularies_at_the_edges_of_a_threads_share(V):
+    """4, 8 and 16 entries a thread, the last workgroup with one entry or a full slice, one workgroup per tree, and more
+    than 64 workgroups' worth (the one-workgroup walk); walks that accept several tokens with and without a rejection in
+    front of them, at an odd depth limit too."""
+    rng = np.random.default_rng(V)
+    B = 2
+    cfg = CONFIGS["c3_llama3_8b"].with_(vocab=V, batch=B, n_tree=14)
+    par = tree_for_config(cfg, seed=V)
+    par[1] = np.arange(-1, 13)  # a chain
+    a = accept_inputs(cfg, par, seed=V)
+    _near_the_target(a, par, rng, 0.3)
+    skipped = 0
+    for depth in (None, 1, 3):
+        skipped += _compare(a, par, "sample", max_depth=depth)
+    assert skipped <= (3 if V <= 5 else 0)
+
+
+def test_sample_residual_that_vanishes_in_the_middle_of_the_siblings():
+    """Draft probabilities that cover the target's everywhere (twice its distribution): after the rejection nothing is left,
+    the distribution stays as it was, and the next siblings are tested against it."""
+    rng = np.random.default_rng(3)
+    V, N = 3000, 6
+    a = {"logits": rng.standard_normal((1, N + 1, V)).astype(np.float32) * 2, "draft_probs": np.empty((1, N, V), np.float32)}
+    z = a["logits"][0, 0].astype(np.float64)
+    p = np.exp(z - z.max())
+    p /= p.sum()
+    par = np.array([[-1, -1, -1, -1, 2, 2]], dtype=np.int32)
+    for k in range(N):
+        a["draft_probs"][0, k] = (2 * p if k in (0, 1) else p[::-1]).astype(np.float32)
+    a["tokens"] = rng.integers(0, V, size=(1, N)).astype(np.int32)
+    for u2 in (0.0, 0.999):
+        a["uniforms"] = np.array([[0.99, 0.98, u2, 0.5, 0.2, 0.7, 0.41]], dtype=np.float32)
+        for single in (0, 1):
+            tune("accept_single", single)
+            assert _compare(a, par, "sample") == 0
