@@ -759,38 +759,44 @@ __device__ __forceinline__ MergeThread merge_prepare(const MergeArgs& p, int uni
   return t;
 }
 
-template <int D, int THREADS, int QROWS>
-__device__ __forceinline__ void merge_run(const MergeArgs& p, const MergeThread& t, int sh, int b, int kv, int tile_row0,
-                                          int tid, float* wbuf) {
-  constexpr int CPR = D / 4, RPP = THREADS / CPR;
-  if (t.row_lo >= t.row_hi) return;  // (uniform)
+// (B) for up to 2^SH splits at a time, of as many rows as a thread's sixteen 8-byte slots hold: all of a slice's rows
+// go out together (a 128-row tile in 2^k splits leaves a thread exactly 16 / 2^k of them).  One row after the other,
+// each a round trip to L2, two splits of a 4x1 workgroup took 5.7 us longer to merge than sixteen.
+template <int D, int THREADS, int QROWS, int SH>
+__device__ __forceinline__ void merge_rows(const MergeArgs& p, const MergeThread& t, int sh, int b, int kv, int tile_row0,
+                                           int tid, float* wbuf) {
+  constexpr int CPR = D / 4, RPP = THREADS / CPR, SP = 1 << SH, ROWS = 16 >> SH;
   const int S = p.splits;
   const unsigned char* part = reinterpret_cast<const unsigned char*>(p.part_o);
   const unsigned po_step = (unsigned)p.m_pad * D * 2;  // bytes from one split's partial to the next
-  // ---- the (max, sum) pair of this thread's (row, split) first, then (B), first half: this thread's
-  // bytes of up to 16 splits go out (32-bit offsets from one base: an add per load)
+  const int rows_end = min(t.row_hi, p.M - tile_row0);
+  u32x2 raw[16];
+  auto fetch = [&](int r0, int s0) {  // (32-bit offsets from one base)
+#pragma unroll
+    for (int k = 0; k < ROWS; ++k) {
+      unsigned off = t.raw_off + (unsigned)s0 * po_step + (unsigned)((r0 - t.r_b + k * RPP) * (D * 2));
+      const bool live = r0 + k * RPP < rows_end;
+#pragma unroll
+      for (int u = 0; u < SP; ++u) {
+        raw[k * SP + u] = u32x2{0u, 0u};
+        if (live && s0 + u < S) raw[k * SP + u] = *reinterpret_cast<const u32x2*>(part + off);
+        off += po_step;
+      }
+    }
+  };
+  // ---- the (max, sum) pair of this thread's (row, split) first, then (B), first half
   float2 ml = make_float2(-INFINITY, 0.f);
   if (t.live_a) ml = *reinterpret_cast<const float2*>(reinterpret_cast<const unsigned char*>(p.part_ml) + t.ml_off);
-  u32x2 raw[16];
-  {
-    unsigned off = t.raw_off;
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      raw[u] = u32x2{0u, 0u};
-      if (t.live_b && u < S) raw[u] = *reinterpret_cast<const u32x2*>(part + off);
-      off += po_step;
-    }
-  }
+  fetch(t.r_b, 0);
   JK_TS(11);
   // ---- (A): pair (row, split) of this thread
+  const int wsh = sh < 2 ? 2 : sh;  // (a row's weights start at a multiple of four floats, for the 16-byte reads below)
   {
     if (!(ml.y > 0.f)) ml = make_float2(-INFINITY, 0.f);  // an empty split carries no weight
     const float mx = group_max(ml.x, sh);
     const float w = fast_exp2(ml.x - ((mx == -INFINITY) ? 0.f : mx));  // exp2(-inf) = 0
     const float l = group_sum(ml.y * w, sh);
-    // (l > 0 for a live row: it sees at least its own tree key; dead rows are not stored.  A row's
-    // weights start at a multiple of four floats, for the 16-byte reads below)
-    const int wsh = sh < 2 ? 2 : sh;
+    // (l > 0 for a live row: it sees at least its own tree key; dead rows are not stored)
     wbuf[((tid >> sh) << wsh) | (tid & ((1 << sh) - 1))] = w / l;
   }
   JK_TS(12);
@@ -800,52 +806,66 @@ __device__ __forceinline__ void merge_run(const MergeArgs& p, const MergeThread&
   JK_TS(13);
 #endif
   // ---- (B), second half
-  for (int r = t.r_b, pass = 0; r < t.row_hi; r += RPP, ++pass) {
-    const bool live = tile_row0 + r < p.M;
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    const float* wrow = wbuf + ((r - t.row_lo) << (sh < 2 ? 2 : sh));
-    for (int s0 = 0; s0 < S; s0 += 16) {
-      if (pass > 0 || s0 > 0) {  // (beyond the first 16 splits of the first row: fetched here)
+  for (int r0 = t.r_b; r0 < t.row_hi; r0 += ROWS * RPP) {
+    float acc[ROWS][4];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
-          raw[u] = u32x2{0u, 0u};
-          if (live && s0 + u < S)
-            raw[u] = *reinterpret_cast<const u32x2*>(part + ((unsigned)(s0 + u) * po_step + t.raw_off + (unsigned)(pass * RPP * D * 2)));
+    for (int k = 0; k < ROWS; ++k) acc[k][0] = acc[k][1] = acc[k][2] = acc[k][3] = 0.f;
+    for (int s0 = 0; s0 < S; s0 += SP) {
+      if (r0 != t.r_b || s0 > 0) fetch(r0, s0);  // (beyond what went out above)
+#pragma unroll
+      for (int k = 0; k < ROWS; ++k) {
+        // (a row past the slice reads another row's weights or none: its data are zeros and it is not stored)
+        const float* wrow = wbuf + ((min(r0 + k * RPP, t.row_hi - 1) - t.row_lo) << wsh) + s0;
+#pragma unroll
+        for (int u = 0; u < SP; u += 4) {
+          const float4 w4 = *reinterpret_cast<const float4*>(wrow + u);
+          const float w[4] = {w4.x, w4.y, w4.z, w4.w};
+#pragma unroll
+          for (int v = 0; v < 4 && u + v < SP; ++v) {
+            const u32x2 x = raw[k * SP + u + v];
+            const float wu = s0 + u + v < S ? w[v] : 0.f;
+            acc[k][0] = fmaf(__uint_as_float(x[0] << 16), wu, acc[k][0]);
+            acc[k][1] = fmaf(__uint_as_float(x[0] & 0xffff0000u), wu, acc[k][1]);
+            acc[k][2] = fmaf(__uint_as_float(x[1] << 16), wu, acc[k][2]);
+            acc[k][3] = fmaf(__uint_as_float(x[1] & 0xffff0000u), wu, acc[k][3]);
+          }
         }
       }
-      float w[16];
+    }
 #pragma unroll
-      for (int u = 0; u < 16; u += 4) {  // (slots beyond S hold zeros or other rows' weights; their data are zeros)
-        const float4 w4 = *reinterpret_cast<const float4*>(wrow + s0 + u);
-        w[u] = w4.x; w[u + 1] = w4.y; w[u + 2] = w4.z; w[u + 3] = w4.w;
+    for (int k = 0; k < ROWS; ++k) {
+      const int r = r0 + k * RPP;
+      if (r >= rows_end) continue;
+      u32x2 pk;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        bf16x2 o;
+        o[0] = (__bf16)acc[k][2 * h];
+        o[1] = (__bf16)acc[k][2 * h + 1];
+        pk[h] = __builtin_bit_cast(unsigned, o);
       }
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const float wu = s0 + u < S ? w[u] : 0.f;
-        acc[0] = fmaf(__uint_as_float(raw[u][0] << 16), wu, acc[0]);
-        acc[1] = fmaf(__uint_as_float(raw[u][0] & 0xffff0000u), wu, acc[1]);
-        acc[2] = fmaf(__uint_as_float(raw[u][1] << 16), wu, acc[2]);
-        acc[3] = fmaf(__uint_as_float(raw[u][1] & 0xffff0000u), wu, acc[3]);
+      uint16_t* dst;
+      if (k == 0 && r0 == t.r_b) {
+        dst = p.out + t.dst_off;
+      } else {
+        const int m = tile_row0 + r;
+        const int node = div_mg(m, p.mg_g);
+        dst = p.out + b * p.o_sb + node * p.o_st + (long long)(kv * p.G + (m - node * p.G)) * p.o_sh + (tid % CPR) * 4;
       }
+      *reinterpret_cast<u32x2*>(dst) = pk;  // (an ordinary store measured no slower than one through to memory here)
     }
-    if (!live) continue;
-    u32x2 pk;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      bf16x2 o;
-      o[0] = (__bf16)acc[2 * h];
-      o[1] = (__bf16)acc[2 * h + 1];
-      pk[h] = __builtin_bit_cast(unsigned, o);
-    }
-    uint16_t* dst;
-    if (pass == 0) {
-      dst = p.out + t.dst_off;
-    } else {
-      const int m = tile_row0 + r;
-      const int node = div_mg(m, p.mg_g);
-      dst = p.out + b * p.o_sb + node * p.o_st + (long long)(kv * p.G + (m - node * p.G)) * p.o_sh + (tid % CPR) * 4;
-    }
-    *reinterpret_cast<u32x2*>(dst) = pk;  // (an ordinary store measured no slower than one through to memory here)
+  }
+}
+
+template <int D, int THREADS, int QROWS>
+__device__ __forceinline__ void merge_run(const MergeArgs& p, const MergeThread& t, int sh, int b, int kv, int tile_row0,
+                                          int tid, float* wbuf) {
+  if (t.row_lo >= t.row_hi) return;  // (uniform)
+  switch (sh) {
+    case 1: merge_rows<D, THREADS, QROWS, 1>(p, t, sh, b, kv, tile_row0, tid, wbuf); break;
+    case 2: merge_rows<D, THREADS, QROWS, 2>(p, t, sh, b, kv, tile_row0, tid, wbuf); break;
+    case 3: merge_rows<D, THREADS, QROWS, 3>(p, t, sh, b, kv, tile_row0, tid, wbuf); break;
+    default: merge_rows<D, THREADS, QROWS, 4>(p, t, sh, b, kv, tile_row0, tid, wbuf); break;
   }
   __syncthreads();  // wbuf is free again (another slice may follow)
 }
