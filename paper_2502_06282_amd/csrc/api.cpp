@@ -71,19 +71,26 @@ bool shape_supported(const jk_attn_desc& d) {
 }
 }  // namespace
 
-// Constants of the attention plan's time estimate, each measured on an MI355X at head_dim 128 with
-// bench.py (forced plans through jk_set_tuning; the kernel's own time stamps in a -DJK_TIMING build):
+// Constants of the attention plan's time estimate. All were fitted together to 2100 shapes drawn over batch 1 - 32,
+// 1 - 128 tree nodes, 2 - 40 KV heads, head_dim 64/128 and prefixes up to 32k, contiguous and paged, the K/V warm in
+// the caches or cold, each timed on an MI355X with every plan that could be the best one. The plan the estimate takes
+// is 2 % (geometric mean; 6 % at the 90th percentile) slower than the best of each shape's plans, runs of one plan
+// differing by about as much; the estimate before it, from sweeps of five shapes, was 10 % (28 %) off.
 struct PlanModel {
-  double round_4x1 = 1.31;      // us per round (a pair of 32-key tiles) of a 4x1 workgroup alone on its CU: c3, 4 pairs in 5.26 us
-  double round_2x2 = 0.95;      // us per round (one tile per key column) of a 2x2 workgroup: c2 sweep of split counts
-  double share2_4x1 = 1.58;     // two 4x1 workgroups on one CU take this many times one's time: c5, 1 against 2 per CU
-  double share_2x2_slope = 0.75;  // 2x2 workgroups sharing a CU: time x (0.75 per workgroup + 0.25): c7 and c4 sweeps
-  double cu_pull = 22.0e3;      // bytes per us one CU draws from HBM with one round in flight (32 KB / 1.3 us round trip)
-  double stream = 4.0e6;        // bytes per us all CUs together: c4, 178 MB per call
-  double startup = 2.7;         // us before a workgroup's first K/V data are there (c3 time stamps: 2.6 - 2.8); with two
-                                // workgroups on a CU one's start hides under the other's loop (c7: 4 splits beat 2)
-  double merge_fused_fixed = 2.0, merge_fused_per_mb = 0.1;   // merge inside the kernel: c3 time stamps, xchg probe
-  double merge_kernel_fixed = 3.0, merge_kernel_per_mb = 0.28, merge_kernel_per_mb_busy = 0.4;  // second launch: c3/c2/c5 traces
+  double round_4x1 = 1.13, round_4x1_d64 = 0.84;  // us per round (a pair of 32-key tiles) of a 4x1 workgroup alone on its CU
+  double round_2x2 = 0.90, round_2x2_d64 = 0.58;  // us per round (one tile per key column) of a 2x2 workgroup
+  double tail_2x2 = 1.03;       // a ragged or tree tile costs this much of a round on top, shared by the splits
+  double share_4x1 = 1.45, share_2x2 = 1.37;      // two workgroups on a CU take this many times one's time
+  double far_bytes = 9.0e7;     // K/V beyond this come from HBM, not from a cache: the longer latency shows with
+  double far_2x2 = 1.24, far_2x2_shared = 1.11, far_deep = 1.02;  // the 2x2 arrangement's one round in flight
+  double stream = 7.0e6;        // bytes per us all CUs together
+  double startup = 5.7;         // us before a workgroup's first K/V data are there, and after its last
+  double startup_4x1 = 1.03;    // (more for twice the rows)
+  double turn_0 = 0.35, turn_step = 0.14, turn_min = 0.02;  // how much of a last, partly filled turn of two workgroups per CU
+                                // shows: a third after one full turn, less with each further one (they drift apart)
+  double merge_fused_fixed = 1.63, merge_fused_per_mb = 0.30;  // merge inside the kernel
+  double merge_kernel_fixed = 2.1, merge_kernel_per_mb = 0.36; // second launch
+  double merge_16 = 1.4;        // either way, for each 16 splits beyond the first (their loads go out in turns)
 };
 
 namespace {
@@ -126,14 +133,6 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
         const long long s_min = (n_tiles + kMaxTilesPerSplit - 1) / kMaxTilesPerSplit;
         if (s < s_min) s = s_min;
         if (s > kMaxSplits) continue;
-        // Estimated time of a call, in microseconds, from what was measured on an MI355X at
-        // head_dim 128: a workgroup runs a round (2 tiles per key column) in about 0.95 us as
-        // 2x2 waves and 1.33 us as 4x1 waves (which cover twice the rows, hand-pipelined);
-        // workgroups beyond one per CU share its throughput; the K/V stream (re-read from L2
-        // by the row tiles at a quarter of the price) moves at about 4 TB/s while every CU
-        // pulls, so CUs with one workgroup more than the average stretch it; partial outputs
-        // (bf16, written, flushed at the kernel boundary and read back) cost about 0.28 us per MB.
-        const double t_round = (wn == 1 ? km.round_4x1 : km.round_2x2) * d.head_dim / 128.0;
         // rounds of the longest split: the 4x1 arrangement deals tiles (an odd last tile costs about
         // half a round), the 2x2 arrangement whole rounds
         double rounds;
@@ -153,21 +152,39 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
             rounds = pairs_of(most) > last ? pairs_of(most) : last;
           }
         } else {
-          rounds = (double)(((n_tiles + wn * kt - 1) / (wn * kt) + s - 1) / s);
+          rounds = (double)(((n_tiles + wn * kt - 1) / (wn * kt) + s - 1) / s) +
+                   km.tail_2x2 * (double)(n_tiles - max_prefix_len / kTileKeys) / (double)(1 + s);
         }
-        const double per_cu = (double)(wgs * s) / slots;
-        // 4x1 workgroups that share a CU overlap each other's matrix and vector phases: two of
-        // them take 1.58 times one's time (measured on c5), plus a part of a workgroup of tail
-        const double share =
-            per_cu > 1.0 ? (wn == 1 ? 0.5 * km.share2_4x1 * (per_cu + 0.3 > 2.0 ? per_cu + 0.3 : 2.0)
-                                    : km.share_2x2_slope * per_cu + (1.0 - km.share_2x2_slope))
-                         : 1.0;
-        const double imbalance = per_cu > 1.0 ? std::ceil(per_cu) / per_cu : 1.0;
-        const double loop_us = rounds * t_round * share;
-        // (a CU pulls about 22 GB/s on its own: fewer workgroups than CUs stream slower than 4 TB/s)
-        const double active = (double)(wgs * s < slots ? wgs * s : slots);
-        const double rate = active * km.cu_pull < km.stream ? active * km.cu_pull : km.stream;  // bytes per microsecond
-        const double stream_us = imbalance * (double)units * kv_bytes * (1.0 + 0.25 * (n_qtiles - 1)) / rate;
+        const long long all_wgs = wgs * s;
+        // The six-tile ring of the 2x2 arrangement: two rounds in flight for a workgroup that has its CU to itself
+        // and a long way to stream (at least eight rounds): 0.75 - 0.86 of the time where K/V come from HBM, 1.02 where
+        // they sit in a cache (900 drawn shapes); never where two workgroups may share a CU, since only one with
+        // the deeper ring fits.
+        const bool deep_ok = wn == 2 && all_wgs <= slots;
+        const bool deep = deep_ok && (tn.attn_deep == 1 || (tn.attn_deep < 0 && ((n_tiles + 1) / 2 + s - 1) / s >= 8));
+        // One turn of at most two workgroups per CU: its rounds, or its share of the K/V stream, whichever is
+        // longer (they overlap badly where they are close, hence the 4-norm).
+        const double t_round = d.head_dim == 64 ? (wn == 1 ? km.round_4x1_d64 : km.round_2x2_d64)
+                                                : (wn == 1 ? km.round_4x1 : km.round_2x2);
+        const double stream_us = (double)units * kv_bytes / (double)all_wgs / km.stream;  // per workgroup of a turn
+        const bool far = wn == 2 && (double)units * kv_bytes > km.far_bytes;
+        const double lone = far ? (deep ? km.far_deep : km.far_2x2) : 1.0;
+        const double shared = wn == 1 ? km.share_4x1 : km.share_2x2 * (far ? km.far_2x2_shared : 1.0);
+        auto turn_us = [&](long long n) {
+          if (n <= 0) return 0.0;
+          const double loop = rounds * t_round * (n <= slots ? lone : shared);
+          const double l2 = loop * loop, m2 = stream_us * (double)n * (stream_us * (double)n);
+          return std::sqrt(std::sqrt(l2 * l2 + m2 * m2));
+        };
+        const long long full = all_wgs / (2 * slots);
+        const double body_full = (double)full * turn_us(2 * slots), body_last = turn_us(all_wgs - full * 2 * slots);
+        double body = body_full + body_last;
+        if (full >= 1) {
+          const double even = (double)all_wgs / (2.0 * slots) * turn_us(2 * slots);
+          const double part = km.turn_0 - km.turn_step * (double)(full - 1);
+          const double shows = part > km.turn_min ? part : km.turn_min;
+          body = shows * body + (1.0 - shows) * even;
+        }
         // Merge inside the kernel: possible when every workgroup is resident at once (here: at most
         // one per CU, or two when forced) and the workgroup numbering puts all splits of a (unit, row
         // tile) group on one XCD: logical ids are dealt to the 8 XCDs in contiguous ranges of
@@ -178,46 +195,37 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
         bool can_fuse = fused_mode != 0 && s > 1 && wgs <= kMaxFusedGroups &&
                         ((q_rows + s - 1) / s) * s_pow2 <= 64 * wm * wn &&
                         (double)units * s * n_qtiles * q_rows * d.head_dim * 2.0 < 2.0e9 &&
-                        wgs * s <= (long long)slots * 2;  // (two of these workgroups fit a CU: all resident)
+                        all_wgs <= (long long)slots * 2;  // (two of these workgroups fit a CU: all resident)
         if (can_fuse) {
-          const long long per_unit = s * n_qtiles, per_xcd = (wgs * s + 7) / 8;
+          const long long per_unit = s * n_qtiles, per_xcd = (all_wgs + 7) / 8;
           for (long long u = 0; u < units && can_fuse; ++u)
             can_fuse = (u * per_unit) / per_xcd == ((u + 1) * per_unit - 1) / per_xcd;
         }
-        // Partials (bf16): merged inside the kernel they are written once and read once through the XCD's L2
-        // (about 2 us of exchange latency whatever their size plus 0.1 us per MB); with the stand-alone merge
-        // kernel they cost a second launch (about 3 us) and 0.28 us per MB when the grid is one turn
-        // of workgroups and they are stored through to memory, 0.4 when they take the ordinary route
+        // Partials (bf16) are merged inside the kernel where that is possible (an exchange through the XCD's L2 instead
+        // of a second launch: 0.2 - 1.8 us less at every number of splits).
         const double part_mb = 1.0e-6 * (double)units * s * pl->m_rows * d.head_dim * 2.0;
-        const double partial_us =
-            s <= 1 ? 0.0
-            : can_fuse ? km.merge_fused_fixed + km.merge_fused_per_mb * part_mb
-                       : km.merge_kernel_fixed + (per_cu > 1.0 && wn == 1 ? km.merge_kernel_per_mb_busy : km.merge_kernel_per_mb) * part_mb;
-        // (near ties go to the count that gives every CU a workgroup: 2 % for an idle CU)
-        // (measured for the 2x2 arrangement only; two 4x1 workgroups on a CU get in each other's way from the start: c3, 20 - 32 splits)
-        const double start_us = km.startup * (wn == 2 && per_cu >= 1.5 ? 0.5 : 1.0);
-        const double cost = ((loop_us > stream_us ? loop_us : stream_us) + partial_us + start_us) * (active < slots ? 1.02 : 1.0);
+        const double fused_us = km.merge_fused_fixed + km.merge_fused_per_mb * part_mb;
+        const double kernel_us = km.merge_kernel_fixed + km.merge_kernel_per_mb * part_mb;
+        const double merge_us = s <= 1 ? 0.0 : (can_fuse ? fused_us : kernel_us) + km.merge_16 * (double)((s - 1) / 16);
+        const double start_us = km.startup * (wn == 1 ? km.startup_4x1 : 1.0);
+        // (near ties go to the count that gives every CU a workgroup: 2 % for idle CUs)
+        const double cost = (body + merge_us + start_us) * (all_wgs < slots ? 1.02 : 1.0);
         if (!have || cost < best_cost) {
           have = true;
           best_cost = cost;
           pl->wm = wm; pl->wn = wn; pl->kt = kt; pl->q_rows = q_rows; pl->n_qtiles = n_qtiles; pl->splits = (int)s;
           pl->fused = can_fuse ? 1 : 0;
+          pl->deep = deep ? 1 : 0;
         }
       }
     }
     if (!have) return false;
     pl->m_pad = pl->n_qtiles * pl->q_rows;
-    // The six-tile ring of the 2x2 arrangement: two rounds in flight for a workgroup that has its CU to itself
-    // and a long way to stream (at least eight rounds: c6 59.3 -> 56.1 us); never where two workgroups may share
-    // a CU, since only one with the deeper ring fits.
-    {
-      const long long all_wgs = units * pl->n_qtiles * pl->splits;
-      const long long rounds_per_split = ((n_tiles + 1) / 2 + pl->splits - 1) / pl->splits;
-      const bool fits = pl->wn == 2 && all_wgs <= slots;
-      pl->deep = fits && (tn.attn_deep == 1 || (tn.attn_deep < 0 && rounds_per_split >= 8)) ? 1 : 0;
-    }
+    // (the kernel ranks a batch with a lane per sequence, and the XCDs get whole units)
+    pl->ranked = d.batch >= 2 && d.batch <= 64 && units % 8 == 0 ? 1 : 0;
   } else {
     pl->fused = 0;
+    pl->ranked = 0;
     pl->deep = 0;
     pl->wm = pl->wn = pl->kt = 1;
     pl->q_rows = 1;

@@ -44,6 +44,7 @@ struct AttnPlan {
   int m_pad;       // n_qtiles * q_rows
   int splits;      // KV splits
   int fused;       // bf16 path: the splits are merged inside the attention kernel (no second launch)
+  int ranked;      // bf16 path: sequences taken by falling length, dealt to the XCDs in turn
   int deep;        // bf16 path, 2x2 waves: the six-tile K/V ring (one workgroup per CU, two rounds in flight)
   size_t part_o_bytes, part_ml_bytes, total_bytes;  // total = header + partials
 };

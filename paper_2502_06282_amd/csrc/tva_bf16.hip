@@ -94,6 +94,9 @@ struct KParams {
   int fused;
   unsigned spin_limit;
   int merge_rows, merge_shift;  // rows per slice = ceil(tile rows / splits); splits padded to 2^merge_shift
+  // batches: the sequences by falling length, dealt to the XCDs in turn (units_per_xcd > 0; see the kernel's start)
+  int units_per_xcd, second_turn;
+  unsigned long long mg_upx;
 };
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -947,19 +950,33 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
   // ---- which piece of work: consecutive hardware workgroup ids alternate between the 8
   // XCDs, so give each XCD a contiguous range of logical ids; q-tiles of one (b, kv, split)
   // are adjacent logical ids and therefore share that XCD's L2 for their common K/V.
+  // In a batch the (sequence, KV head) units are put in order of falling length, which only the device knows, and dealt
+  // to the XCDs in turn (every other time backwards): each XCD gets its share of long and short sequences, starts with
+  // the long ones, and where the grid is two workgroups a CU the second 32 of an XCD come the other way round, so that
+  // the longest shares its CU with the shortest.  16 sequences of 512 to 4096 tokens (8B shapes) took 88 us in the
+  // order of the batch (an XCD had two sequences of its own), 67 like this.
+  const bool ranked = p.units_per_xcd > 0;
   int wid;
   {
     const int n = blockIdx.x;
     const int per = p.total_wgs >> 3;  // total_wgs is padded to a multiple of 8
-    wid = (n & 7) * per + (n >> 3);
+    int local = n >> 3;
+    if (ranked && local >= p.second_turn) local = p.second_turn + per - 1 - local;
+    wid = (n & 7) * per + local;
   }
   int rest = div_mg(wid, p.mg_qtiles);
   const int qtile = wid - rest * p.n_qtiles;
-  const int unit_id = div_mg(rest, p.mg_splits);  // b * Hkv + kv
-  if (unit_id >= p.B * p.Hkv) return;             // padding workgroup
-  const int split = rest - unit_id * splits;
-  const int b = div_mg(unit_id, p.mg_hkv);
-  const int kv = unit_id - b * p.Hkv;
+  const int unit = div_mg(rest, p.mg_splits);  // b * Hkv + kv in the order of the batch
+  if (unit >= p.B * p.Hkv) return;             // padding workgroup
+  const int split = rest - unit * splits;
+  int place = unit;  // rank * Hkv + kv
+  if (ranked) {
+    const int x = div_mg(unit, p.mg_upx), i = unit - x * p.units_per_xcd;
+    place = i * 8 + ((i & 1) ? 7 - x : x);
+  }
+  const int rank = div_mg(place, p.mg_hkv);
+  const int kv = place - rank * p.Hkv;
+  int b = rank;  // (if all lengths are equal, the order of the batch: assumed until they have arrived)
 
   // ---- the prefix length first, as a per-lane vector load (an atomic load is never turned
   // into a scalar one, and the compiler must not see that the address is uniform, or it
@@ -970,25 +987,27 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
   // transfers: the compiler's waits for them then never include a transfer.
   int lane_zero = 0;
   asm volatile("" : "+v"(lane_zero));  // hides from the compiler that the address is uniform
-  const int L_raw = __hip_atomic_load(p.prefix_len + b + lane_zero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int L_raw = __hip_atomic_load(p.prefix_len + (ranked ? min(lane, p.B - 1) : b) + lane_zero, __ATOMIC_RELAXED,
+                                      __HIP_MEMORY_SCOPE_AGENT);  // (of a batch: lane i has sequence i's)
   WaveState<D> st;
   const int m_row = qtile * QROWS + wm * kWaveRows + c32;  // this lane's query row
   const bool row_ok = m_row < M;
   const int mm = row_ok ? m_row : M - 1;
   const int my_node = div_mg(mm, p.mg_g);
   u32x4 q_raw[DK];
-  {
+  // (the first wave builds the ancestor sets, nodes lane and lane + 64)
+  int parent_lo = -1, parent_hi = -1;
+  auto load_rows = [&]() {
     const uint16_t* src =
         p.q + b * p.q_sb + my_node * p.q_st + (long long)(kv * G + (mm - my_node * G)) * p.q_sh + 8 * g;
 #pragma unroll
     for (int ks = 0; ks < DK; ++ks) q_raw[ks] = *reinterpret_cast<const u32x4*>(src + ks * 16);  // clamped row: in bounds
-  }
-  // (the first wave builds the ancestor sets, nodes lane and lane + 64)
-  int parent_lo = -1, parent_hi = -1;
-  if (wave == 0) {
-    if (lane < T) parent_lo = p.parent[(long long)b * T + lane];
-    if (lane + 64 < T) parent_hi = p.parent[(long long)b * T + lane + 64];
-  }
+    if (wave == 0) {
+      if (lane < T) parent_lo = p.parent[(long long)b * T + lane];
+      if (lane + 64 < T) parent_hi = p.parent[(long long)b * T + lane + 64];
+    }
+  };
+  load_rows();
 
   // ---- tile range of this split.  The prefix length is still on its way: start the K/V
   // stream on the assumption that it equals the host's upper bound (the usual case); if it
@@ -1058,9 +1077,12 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
   const unsigned ring_addr = (unsigned)(size_t)LDS_PTR(unsigned char, ring);  // a multiple of 1024
   const unsigned k_lane = G_::k_lane(lane), v_lane = G_::v_lane(lane);
   LaneChunks<D, NW> lc;
-  lane_chunks<D, NW>(lc, wave, lane, ts, p.kc + (PAGED ? 0 : b * p.kc_sb) + (long long)kv * p.kc_sh,
-                     p.vc + (PAGED ? 0 : b * p.kc_sb) + (long long)kv * p.kc_sh, p.kt + b * p.kt_sb + (long long)kv * p.kt_sh,
-                     p.vt + b * p.kt_sb + (long long)kv * p.kt_sh);
+  auto set_streams = [&]() {
+    lane_chunks<D, NW>(lc, wave, lane, ts, p.kc + (PAGED ? 0 : b * p.kc_sb) + (long long)kv * p.kc_sh,
+                       p.vc + (PAGED ? 0 : b * p.kc_sb) + (long long)kv * p.kc_sh, p.kt + b * p.kt_sb + (long long)kv * p.kt_sh,
+                       p.vt + b * p.kt_sb + (long long)kv * p.kt_sh);
+  };
+  set_streams();
 
   set_range(p.max_prefix);
   int n_rounds = (ts.t_end - ts.t_begin + TPR - 1) / TPR;
@@ -1095,19 +1117,42 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
     }
   JK_TS(1);
 
-  int L = __builtin_amdgcn_readfirstlane(L_raw);
-  L = L < 0 ? 0 : (L > p.max_prefix ? p.max_prefix : L);
+  int L;
+  bool moved = false;  // another sequence than the assumed one
+  if (ranked) {
+    const int len = L_raw < 0 ? 0 : (L_raw > p.max_prefix ? p.max_prefix : L_raw);
+    L = p.max_prefix;
+    if (!__all(len == p.max_prefix)) {
+      int my_rank = 0;  // of sequence `lane`: longer ones, and equal ones in front of it
+      for (int i = 0; i < p.B; ++i) {
+        const int other = __builtin_amdgcn_readlane(len, i);
+        my_rank += (int)(other > len) | ((int)(other == len) & (int)(i < lane));
+      }
+      const int mine = __ffsll((long long)__ballot(lane < p.B && my_rank == rank)) - 1;
+      moved = mine != b;
+      b = mine;
+      L = __builtin_amdgcn_readlane(len, mine);
+    }
+  } else {
+    L = __builtin_amdgcn_readfirstlane(L_raw);
+    L = L < 0 ? 0 : (L > p.max_prefix ? p.max_prefix : L);
+  }
   JK_TS(2);
-  if (L != p.max_prefix) {  // uniform over the workgroup
+  if (L != p.max_prefix || moved) {  // uniform over the workgroup
     if (spec_any) {
       wait_dma<DMA_PER_ROUND>(0);  // the ring must be quiet before the same slots are filled again
       __syncthreads();
+    }
+    if (moved) {
+      set_streams();
+      load_rows();
     }
     n_spec = 0;
     set_range(L);
     n_rounds = (ts.t_end - ts.t_begin + TPR - 1) / TPR;
     if (PAGED) fill_pages();
   }
+  const int unit_id = b * p.Hkv + kv;
   const bool has_tree = ts.t_end > ts.n_ptiles;
   if (PAGED && bad_page) __hip_atomic_fetch_or(p.err, kDevErrBadPage, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
@@ -1566,6 +1611,13 @@ hipError_t launch_tva_bf16(const AttnArgs& a, const AttnPlan& pl, hipStream_t st
   kp.fused = pl.fused;
   if (pl.fused && pl.splits > 1) kp.through = 0;
   kp.sync = a.sync;
+  // (a lane per sequence in the ranking; the XCDs get whole units)
+  const long long units = (long long)d.batch * d.n_kv_heads;
+  const bool ranked = pl.ranked != 0;
+  kp.units_per_xcd = ranked ? (int)(units / 8) : 0;
+  kp.mg_upx = magic(ranked ? (int)(units / 8) : 1);
+  const int xcd_cus = device_cu_count() / 8, per_xcd = kp.total_wgs / 8;
+  kp.second_turn = ranked && per_xcd > xcd_cus && per_xcd <= 2 * xcd_cus ? xcd_cus : kp.total_wgs;
   kp.err = a.err;
   kp.spin_limit = tuning().spin_limit >= 0 ? (unsigned)tuning().spin_limit : 4096u;  // about 2 ms of polling
   kp.merge_rows = (pl.q_rows + pl.splits - 1) / pl.splits;

@@ -205,3 +205,52 @@ def test_paged_page_id_outside_the_pool_is_clamped_and_reported():
         assert errs == [jk.JK_DEVERR_BAD_PAGE, 0, 0], (arr, s, errs)
         assert torch.equal(outs[0], outs[1])
         assert not torch.equal(outs[0], outs[2])
+
+
+@pytest.mark.parametrize("hkv,lens", [
+    (8, [700, 0, 33, 512, 1, 640, 31, 257]),
+    (4, [0, 900]),
+    (8, [65, 64]),
+    (16, [300, 300, 300]),
+    (2, [600, 10, 10, 600, 599, 601, 0, 32, 33, 96, 128, 1]),
+    (1, [(37 * i) % 400 for i in range(64)]),
+    (1, [(53 * i) % 300 for i in range(72)]),
+], ids=["eight", "two", "one-key-apart", "equal", "ties", "sixty-four", "more-than-lanes"])
+def test_sequences_of_a_batch_give_what_each_gives_alone(hkv, lens):
+    """The workgroups of a batch take its sequences by falling length (up to 64 of them, where the KV heads of the
+    batch divide by eight).  Whatever the order: bit for bit the result of the sequence in a call of its own, paged
+    or not, with the splits merged in the kernel and by the second one, in a workspace used again with other
+    lengths."""
+    B, L, G, T = len(lens), max(lens), 2, 20
+    cfg = CONFIGS["c3_llama3_8b"].with_(batch=B, prefix_len=L, n_q_heads=hkv * G, n_kv_heads=hkv, n_tree=T)
+    par, x, kp, vp, table = _paged_case(cfg, 32, L, seed=B)
+    d = {k: _dev(v) for k, v in x.items()}
+    kp, vp, table, parent = _dev(kp), _dev(vp), torch.from_numpy(table).cuda(), torch.from_numpy(par).cuda()
+    ref = oracle_attention(**x, parent=par, prefix_len=lens)
+    bound = L + 5  # (no sequence is as long as the bound)
+    for wm, splits, fused in ((2, 1, -1), (4, 1, -1), (2, 3, 0), (4, 3, 1)):
+        tune("attn_wm", wm); tune("attn_wn", 4 // wm); tune("attn_splits", splits); tune("attn_fused", fused)
+        n = max(jk.tree_verify_attention_workspace(d["q"], d["k_cache"], d["k_tree"], m) for m in (L, bound))
+        ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+        jk.workspace_init(ws)
+        for most, order in ((L, list(range(B))), (L, list(range(B))[::-1]), (bound, list(range(B)))):
+            pl = torch.tensor([lens[i] for i in order], dtype=torch.int32).cuda()
+            pick = torch.tensor(order).cuda()
+            a = [d[k][pick].contiguous() for k in ("q", "k_cache", "v_cache", "k_tree", "v_tree")]
+            if most > L:
+                a[1], a[2] = (torch.nn.functional.pad(t, (0, 0, 0, 0, 0, most - L)) for t in (a[1], a[2]))
+            got = jk.tree_verify_attention(*a, parent[pick].contiguous(), pl, max_prefix_len=most, workspace=ws)
+            if most == L:
+                paged = jk.tree_verify_attention_paged(a[0], kp, vp, table[pick].contiguous(), a[3], a[4], parent[pick].contiguous(), pl,
+                                                       max_prefix_len=most, workspace=ws)
+                assert torch.equal(got, paged)
+            g = got.float().cpu().numpy()
+            assert np.isfinite(g).all() and np.abs(g - ref[order]).max() <= 2e-2
+            tune("attn_fused", 0)
+            for i in (0, B // 2, B - 1):
+                alone = jk.tree_verify_attention(*(t[i:i + 1].contiguous() for t in a), parent[pick][i:i + 1].contiguous(), pl[i:i + 1],
+                                                 max_prefix_len=most)
+                same = torch.equal(got[i:i + 1], alone) if fused != 1 else (got[i:i + 1].float() - alone.float()).abs().max() <= 2e-2
+                assert same, (wm, splits, fused, most, i)
+            tune("attn_fused", fused)
+        assert jk.last_device_error(ws) == 0
