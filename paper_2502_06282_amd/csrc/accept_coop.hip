@@ -36,6 +36,7 @@
 // of a tree to finish finds out and moves the call number on (see TreeWords), so a call that
 // gave up leaves nothing behind that a later call could mistake.
 #include "jk_internal.h"
+#include "jk_wave.h"
 
 namespace jk {
 namespace {
@@ -88,59 +89,8 @@ struct CoopParams {
   unsigned* err;  // the workspace's sticky device error word
 };
 
-// ---- reductions over a wave, the result in every lane: exchanges with lane ^ 1, ^ 2 (quad_perm), then, the halves being
-// uniform by then, mirrored within 8 and 16, then halves of 32 and of 64 swapped
-template <int CTRL>
-__device__ __forceinline__ int dpp(int v) {
-  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp64(double v) {
-  const long long b = __double_as_longlong(v);
-  const unsigned lo = (unsigned)dpp<CTRL>((int)b), hi = (unsigned)dpp<CTRL>((int)(b >> 32));
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ unsigned other16(unsigned v, bool upper) {  // the value of lane ^ 16
-  const u32x2 s = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-  return upper ? s[0] : s[1];
-}
-__device__ __forceinline__ unsigned other32(unsigned v, bool upper) {  // the value of lane ^ 32
-  const u32x2 s = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  return upper ? s[0] : s[1];
-}
-__device__ __forceinline__ double swap64(double v, bool by32) {
-  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-  const int lane = __lane_id();
-  unsigned lo = (unsigned)b, hi = (unsigned)(b >> 32);
-  if (by32) {
-    lo = other32(lo, lane & 32);
-    hi = other32(hi, lane & 32);
-  } else {
-    lo = other16(lo, lane & 16);
-    hi = other16(hi, lane & 16);
-  }
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-__device__ __forceinline__ double wave_sum(double v) {
-  v += dpp64<0xB1>(v);   // quad_perm [1,0,3,2]
-  v += dpp64<0x4E>(v);   // quad_perm [2,3,0,1]
-  v += dpp64<0x141>(v);  // row_half_mirror
-  v += dpp64<0x140>(v);  // row_mirror
-  v += swap64(v, false);
-  v += swap64(v, true);
-  return v;
-}
-__device__ __forceinline__ float wave_max(float v) {
-  v = fmaxf(v, __int_as_float(dpp<0xB1>(__float_as_int(v))));
-  v = fmaxf(v, __int_as_float(dpp<0x4E>(__float_as_int(v))));
-  v = fmaxf(v, __int_as_float(dpp<0x141>(__float_as_int(v))));
-  v = fmaxf(v, __int_as_float(dpp<0x140>(__float_as_int(v))));
-  const int lane = __lane_id();
-  v = fmaxf(v, __uint_as_float(other16(__float_as_uint(v), lane & 16)));
-  v = fmaxf(v, __uint_as_float(other32(__float_as_uint(v), lane & 32)));
-  return v;
-}
+using dev::wave_max;
+using dev::wave_sum;
 
 // inclusive sums over the lanes: rows of 16 by shifts, then the rows' totals broadcast into the rows behind them
 template <int CTRL, int ROWS>

@@ -5,7 +5,7 @@
 // divides by, and each head's top-k candidates.
 //
 // Kernels:
-//   head_inputs_kernel     X[2R (padded to 32), d] bf16 from f_top, s_top (elementwise, tiny)
+//   head_inputs_kernel     X[2R, d] bf16 from f_top, s_top (elementwise, tiny)
 //   skinny_gemm_kernel     Y[M, N] fp32 = X[M, K] . W[N, K]^T with M <= 192 and very many weight rows: the weight
 //                          matrix (a gigabyte for an output embedding) is streamed from HBM exactly once; both
 //                          operands are staged HBM/L2 -> LDS in swizzled 64-byte row segments and read from there
@@ -18,6 +18,7 @@
 
 #include "jk_device.h"
 #include "jk_internal.h"
+#include "jk_wave.h"
 
 namespace jk {
 namespace {
@@ -39,42 +40,41 @@ __device__ __forceinline__ float bf16_hi(unsigned w) { return __uint_as_float(w 
 struct MixParams {
   const unsigned short* f_top;  // [rows][2][d] bf16
   const float* s_top;           // [rows][2]
-  unsigned short* x;            // [m_pad][d] bf16, row 2r + h
+  unsigned short* x;            // [2 rows][d] bf16, row 2r + h
   int rows, d, mode;
   float alpha, beta;
 };
 
-__global__ __launch_bounds__(256) void head_inputs_kernel(MixParams p) {
-  const int row = blockIdx.x, r = row >> 1, h = row & 1;
-  u32x4* dst = reinterpret_cast<u32x4*>(p.x + (long long)row * p.d);
-  if (r >= p.rows) {  // padding rows of the last 32-row block
-    for (int c = threadIdx.x; c < p.d / 8; c += 256) dst[c] = u32x4{0u, 0u, 0u, 0u};
-    return;
-  }
-  const u32x4* f1 = reinterpret_cast<const u32x4*>(p.f_top + ((long long)r * 2 + 0) * p.d);
-  const u32x4* f2 = reinterpret_cast<const u32x4*>(p.f_top + ((long long)r * 2 + 1) * p.d);
+// One thread per 8 columns of a token: both heads' rows from one trip to its two features.
+__global__ __launch_bounds__(64) void head_inputs_kernel(MixParams p) {
+  const int d8 = p.d / 8;
+  const long long i = (long long)blockIdx.x * 64 + threadIdx.x;
+  if (i >= (long long)p.rows * d8) return;
+  const int r = (int)(i / d8), c = (int)(i % d8);
+  const u32x4 a = reinterpret_cast<const u32x4*>(p.f_top + ((long long)r * 2 + 0) * p.d)[c];
+  const u32x4 b = reinterpret_cast<const u32x4*>(p.f_top + ((long long)r * 2 + 1) * p.d)[c];
   const float s1 = p.s_top[2 * r], s2 = p.s_top[2 * r + 1];
-  // x = c1 f1 + c2 f2
-  float c1, c2;
-  if (p.mode == JK_HEADS_DECOUPLED) {
-    c1 = h == 0 ? s1 : 0.f;
-    c2 = h == 0 ? 0.f : s2;
-  } else {
-    c1 = h == 0 ? s1 : p.beta;
-    c2 = h == 0 ? s2 : -p.alpha;
-  }
-  for (int c = threadIdx.x; c < p.d / 8; c += 256) {
-    const u32x4 a = f1[c], b = f2[c];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    // x = c1 f1 + c2 f2
+    float c1, c2;
+    if (p.mode == JK_HEADS_DECOUPLED) {
+      c1 = h == 0 ? s1 : 0.f;
+      c2 = h == 0 ? 0.f : s2;
+    } else {
+      c1 = h == 0 ? s1 : p.beta;
+      c2 = h == 0 ? s2 : -p.alpha;
+    }
     u32x4 o;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int j = 0; j < 4; ++j) {
       // a term whose coefficient is zero is left out, so that a NaN in the other expert's
       // feature cannot leak into a decoupled head
-      const float lo = (c1 != 0.f ? c1 * bf16_lo(a[i]) : 0.f) + (c2 != 0.f ? c2 * bf16_lo(b[i]) : 0.f);
-      const float hi = (c1 != 0.f ? c1 * bf16_hi(a[i]) : 0.f) + (c2 != 0.f ? c2 * bf16_hi(b[i]) : 0.f);
-      o[i] = bf16_bits_rne(lo) | (bf16_bits_rne(hi) << 16);
+      const float lo = (c1 != 0.f ? c1 * bf16_lo(a[j]) : 0.f) + (c2 != 0.f ? c2 * bf16_lo(b[j]) : 0.f);
+      const float hi = (c1 != 0.f ? c1 * bf16_hi(a[j]) : 0.f) + (c2 != 0.f ? c2 * bf16_hi(b[j]) : 0.f);
+      o[j] = bf16_bits_rne(lo) | (bf16_bits_rne(hi) << 16);
     }
-    dst[c] = o;
+    reinterpret_cast<u32x4*>(p.x + (long long)(2 * r + h) * p.d)[c] = o;
   }
 }
 
@@ -293,15 +293,14 @@ bool gemm_fits(int m, int n) {
 }
 
 // ------------------------------------------------------------------ softmax + top-k per logits row
-// A row (a vocabulary of 10^5 entries) is cut into parts of at most 8 192 entries so that the
-// work spreads over all CUs:
+// A row (a vocabulary of 10^5 entries) is cut into parts of 256 threads x PT entries so that the work spreads over all
+// CUs; everything a thread needs is in its registers after one trip to memory:
 //   row_parts_kernel   per (row, part): maximum, sum of exp((x - max) / T), the part's k best
-//   row_finish_kernel  per (row, part): the row's maximum and normaliser from the parts' pairs (every
-//                      workgroup for itself), q = exp((x - max) / T) / Z of the part (if asked for);
-//                      a row's first workgroup: the k best of the parts' candidates, their probabilities
+//   row_finish_kernel  a workgroup per row first: the k best of the parts' candidates, their probabilities; then one per
+//                      (row, part): q = exp((x - max) / T) / Z (if asked for).  Each takes the row's maximum and
+//                      normaliser from the parts' pairs for itself.
 constexpr int kPartThreads = 256;
-constexpr int kPartPerThread = 32;                             // entries a thread holds in registers
-constexpr int kPartMax = kPartThreads * kPartPerThread;        // 8 192
+constexpr int kPartPerThreadMax = 16;
 constexpr int kMaxTopK = 16;
 
 struct SoftParams {
@@ -312,8 +311,7 @@ struct SoftParams {
   int* tk_ids;          // [n_rows][k]
   float* tk_probs;      // [n_rows][k]
   float* part_ms;       // [n_rows][parts][2]   max, sum
-  float* part_cv;       // [n_rows][parts][k]   candidate values
-  int* part_ci;         // [n_rows][parts][k]   candidate ids (INT_MAX: none)
+  unsigned long long* keys;  // [n_rows][parts][k]   candidates, best first (0: none)
   int n_rows, vocab, k, parts, part_len;  // part_len: entries per part, a multiple of 4
   float inv_temp;
 };
@@ -327,11 +325,6 @@ struct Best {
   float v;
   int id;
 };
-// the same order without short-circuit evaluation: both operands are always read, so that a
-// counting loop over LDS stays free of branches and its reads can be batched
-__device__ __forceinline__ int beats(float av, int ai, float bv, int bi) {
-  return (int)(av > bv) | ((int)(av == bv) & (int)(ai < bi));
-}
 
 __device__ __forceinline__ Best wave_best(float v, int id) {
 #pragma unroll
@@ -346,299 +339,290 @@ __device__ __forceinline__ Best wave_best(float v, int id) {
   return Best{v, id};
 }
 
+// The same order as one unsigned comparison: the value's bits made monotonic (+ 0: the two zeros are equal) above the
+// complement of the id.  No candidate has key 0.
+__device__ __forceinline__ unsigned ordered_bits(float v) {
+  const unsigned u = __float_as_uint(v + 0.f);
+  return u ^ ((u >> 31) ? 0xFFFFFFFFu : 0x80000000u);
+}
+__device__ __forceinline__ unsigned long long key_of(float v, int id) {
+  return ((unsigned long long)ordered_bits(v) << 32) | (unsigned)~id;
+}
+__device__ __forceinline__ int key_id(unsigned long long k) { return (int)~(unsigned)k; }
+__device__ __forceinline__ float key_value(unsigned long long k) {
+  const unsigned u = (unsigned)(k >> 32);
+  return __uint_as_float(u ^ ((u >> 31) ? 0x80000000u : 0xFFFFFFFFu));
+}
+__device__ __forceinline__ unsigned long long wave_max_key(unsigned long long k) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const unsigned long long other = __shfl_xor(k, o);
+    k = other > k ? other : k;
+  }
+  return k;
+}
+
 constexpr int kCandCap = 512;
 
-// best (value, id) pair of a 4-wave workgroup, for every thread.  `buf` alternates between
-// consecutive calls, so that one barrier per call is enough.
-__device__ __forceinline__ Best block_best4(float v, int id, float (*sv)[4], int (*si)[4], int buf) {
-  const Best w = wave_best(v, id);
-  if ((threadIdx.x & 63) == 0) {
-    sv[buf][threadIdx.x >> 6] = w.v;
-    si[buf][threadIdx.x >> 6] = w.id;
+// Place of each of the n listed keys (all different) by counting the larger ones: `put(rank, key)` for ranks below k.
+template <class F>
+__device__ __forceinline__ void rank_list(const unsigned long long* list, int n, int k, F put) {
+  for (int j = threadIdx.x; j < n; j += kPartThreads) {
+    const unsigned long long mine = list[j];
+    int rank = 0;
+#pragma unroll 8
+    for (int i = 0; i < n; ++i) rank += (int)(list[i] > mine);
+    if (rank < k) put(rank, mine);
   }
-  __syncthreads();
-  Best b{sv[buf][0], si[buf][0]};
-#pragma unroll
-  for (int i = 1; i < 4; ++i)
-    if (better(sv[buf][i], si[buf][i], b.v, b.id)) b = Best{sv[buf][i], si[buf][i]};
-  return b;
 }
+
+// The k-th largest of a wave's 64 values (k at most 64): the least of the values that fewer than k others exceed.  Ranking
+// by reading every lane in turn needs no memory and no rounds.
+__device__ __forceinline__ float wave_kth_largest(float v, int k) {
+  int above = 0;
+#pragma unroll
+  for (int j = 0; j < 64; ++j) above += (int)(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), j)) > v);
+  return -dev::wave_max(above < k ? -v : -INFINITY);
+}
+
+// A part as its workgroup holds it: PT entries a thread, ids increasing with the index.  Four consecutive entries per
+// load where rows start at multiples of 16 bytes, single ones otherwise; past the end: -inf.
+template <int PT>
+struct PartView {
+  int lo, hi, tid;
+  bool vec;
+  __device__ __forceinline__ PartView(const SoftParams& p, int part, bool aligned)
+      : lo(part * p.part_len), hi(min(p.vocab, part * p.part_len + p.part_len)), tid(threadIdx.x), vec(aligned && (p.vocab & 3) == 0) {}
+  __device__ __forceinline__ int id(int i) const {
+    return lo + (vec ? 4 * (tid + kPartThreads * (i >> 2)) + (i & 3) : tid + kPartThreads * i);
+  }
+  __device__ __forceinline__ void load(const float* x, float (&val)[PT]) const {
+    if (vec) {
+#pragma unroll
+      for (int u = 0; u < PT / 4; ++u) {
+        const int e = lo + 4 * (tid + kPartThreads * u);
+        floatx4 q = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+        if (e < hi) q = *reinterpret_cast<const floatx4*>(x + e);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) val[4 * u + c] = q[c];
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < PT; ++i) {
+        const int e = lo + tid + kPartThreads * i;
+        val[i] = e < hi ? x[e] : -INFINITY;
+      }
+    }
+  }
+  __device__ __forceinline__ void store(float* x, const float (&val)[PT]) const {
+    if (vec) {
+#pragma unroll
+      for (int u = 0; u < PT / 4; ++u) {
+        const int e = lo + 4 * (tid + kPartThreads * u);
+        if (e < hi) *reinterpret_cast<floatx4*>(x + e) = floatx4{val[4 * u], val[4 * u + 1], val[4 * u + 2], val[4 * u + 3]};
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < PT; ++i) {
+        const int e = lo + tid + kPartThreads * i;
+        if (e < hi) x[e] = val[i];
+      }
+    }
+  }
+};
+__device__ __forceinline__ bool on16(const void* p) { return (reinterpret_cast<size_t>(p) & 15) == 0; }
 
 // Top-k of a part: the k-th largest of 64 disjoint groups' maxima is a lower bound of the part's
 // k-th largest value, so only entries at or above it can be among the k best; they are put on a
 // short list in LDS (few, unless the part is full of ties) and each listed entry finds its place
 // by counting the entries that beat it.  A part with more such entries than the list holds
 // takes k passes over the registers instead.
+template <int PT>
 __global__ __launch_bounds__(kPartThreads) void row_parts_kernel(SoftParams p) {
-  __shared__ float sv[2][4];
-  __shared__ int si[2][4];
-  __shared__ float sf[4];
-  __shared__ float cand_v[kCandCap];
-  __shared__ int cand_i[kCandCap];
-  __shared__ int n_cand;
+  __shared__ unsigned long long cand[kCandCap];
+  __shared__ unsigned long long sk[2][4];
   __shared__ float lane_max[kPartThreads];
+  __shared__ float sf[4], ss[4];
   __shared__ float s_tau;
-  const int tid = threadIdx.x, V = p.vocab, K = p.k;
+  __shared__ int n_cand;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, V = p.vocab, K = p.k;
   const int row = blockIdx.x / p.parts, part = blockIdx.x % p.parts;
-  const int lo = part * p.part_len, hi = min(V, lo + p.part_len);
-  float* x = p.logits + (long long)row * V;
-  const bool vec = (V & 3) == 0 && (reinterpret_cast<size_t>(p.logits) & 15) == 0;
-  if (p.sums) {  // the k parts' partial products come together here (in a fixed order); each thread reads back its own
-    const float* part_x = p.sums + (long long)row * V;
+  const PartView<PT> view(p, part, on16(p.logits) && on16(p.sums));
+  float val[PT];
+  if (p.sums) {  // the k parts' partial products come together here, in a fixed order
+    const float* x = p.sums + (long long)row * V;
     const long long step = (long long)p.n_rows * V;
-#pragma unroll 2
-    for (int u = 0; u < kPartPerThread / 4; ++u) {
-      const int e = lo + 4 * (tid + kPartThreads * u);
-      if (vec && e + 3 < hi) {
-        floatx4 v = *reinterpret_cast<const floatx4*>(part_x + e);
-#pragma unroll 4
-        for (int z = 1; z < p.ksplit; ++z) v += *reinterpret_cast<const floatx4*>(part_x + z * step + e);
-        *reinterpret_cast<floatx4*>(x + e) = v;
-      } else {
-        for (int c = 0; c < 4; ++c)
-          if (e + c < hi) {
-            float v = part_x[e + c];
-            for (int z = 1; z < p.ksplit; ++z) v += part_x[z * step + e + c];
-            x[e + c] = v;
-          }
-      }
+    view.load(x, val);
+    constexpr int kAhead = PT <= 4 ? 4 : (PT <= 8 ? 2 : 1);
+#pragma unroll kAhead
+    for (int z = 1; z < p.ksplit; ++z) {
+      float more[PT];
+      view.load(x + z * step, more);
+#pragma unroll
+      for (int i = 0; i < PT; ++i) val[i] += more[i];
     }
+    view.store(p.logits + (long long)row * V, val);
+  } else {
+    view.load(p.logits + (long long)row * V, val);
   }
-  if (tid == 0) {
-    n_cand = 0;
-    s_tau = -INFINITY;
-  }
-
-  // entry (u, c) of this thread is vocabulary id lo + 4 (tid + 256 u) + c: ids increase with (u, c)
-  auto id_of = [&](int i) { return lo + 4 * (tid + kPartThreads * (i >> 2)) + (i & 3); };
-  float val[kPartPerThread];
-#pragma unroll
-  for (int u = 0; u < kPartPerThread / 4; ++u) {
-    const int e = lo + 4 * (tid + kPartThreads * u);
-    if (vec && e + 3 < hi) {
-      const floatx4 q = *reinterpret_cast<const floatx4*>(x + e);
-#pragma unroll
-      for (int c = 0; c < 4; ++c) val[4 * u + c] = q[c];
-    } else {
-#pragma unroll
-      for (int c = 0; c < 4; ++c) val[4 * u + c] = e + c < hi ? x[e + c] : -INFINITY;
-    }
-  }
-  // the thread's own maximum
   float tv = -INFINITY;
 #pragma unroll
-  for (int i = 0; i < kPartPerThread; ++i) tv = fmaxf(tv, val[i]);
-  float m = tv;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-  if ((tid & 63) == 0) sf[tid >> 6] = m;
+  for (int i = 0; i < PT; ++i) tv = fmaxf(tv, val[i]);
+  lane_max[tid] = tv;
+  {
+    const float m = dev::wave_max(tv);
+    if (lane == 0) sf[wave] = m;
+  }
+  if (tid == 0) n_cand = 0;
   __syncthreads();
-  m = fmaxf(fmaxf(sf[0], sf[1]), fmaxf(sf[2], sf[3]));
+  const float m = fmaxf(fmaxf(sf[0], sf[1]), fmaxf(sf[2], sf[3]));
   const float m_use = m > -INFINITY ? m : 0.f;  // a part of -inf only: nothing sensible to subtract
+  if (wave == 0) {  // the threshold: group g is threads g, g + 64, ...
+    const float t = wave_kth_largest(fmaxf(fmaxf(tv, lane_max[lane + 64]), fmaxf(lane_max[lane + 128], lane_max[lane + 192])), K);
+    if (lane == 0) s_tau = t;
+  }
   float s = 0.f;
 #pragma unroll
-  for (int i = 0; i < kPartPerThread; ++i) s += expf((val[i] - m_use) * p.inv_temp);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-  __syncthreads();
-  if ((tid & 63) == 0) sf[tid >> 6] = s;
+  for (int i = 0; i < PT; ++i) s += expf((val[i] - m_use) * p.inv_temp);
+  s = dev::wave_sum(s);
+  if (lane == 0) ss[wave] = s;
   __syncthreads();
   const long long slot = (long long)row * p.parts + part;
   if (tid == 0) {
     p.part_ms[2 * slot] = m;
-    p.part_ms[2 * slot + 1] = (sf[0] + sf[1]) + (sf[2] + sf[3]);
+    p.part_ms[2 * slot + 1] = (ss[0] + ss[1]) + (ss[2] + ss[3]);
   }
-
-  // threshold: the k-th largest of the 64 per-lane maxima (maximum over the four waves of the
-  // threads' own maxima), found by ranking: no rounds, no reductions
-  lane_max[tid] = tv;
-  __syncthreads();
-  if (tid < 64) {
-    const float v = fmaxf(fmaxf(lane_max[tid], lane_max[tid + 64]), fmaxf(lane_max[tid + 128], lane_max[tid + 192]));
-    lane_max[tid] = v;  // (wave 0 only reads and writes its own column here)
-  }
-  __syncthreads();
-  if (tid < 64) {
-    const float mine = lane_max[tid];
-    int rank = 0;
-#pragma unroll 8
-    for (int j = 0; j < 64; ++j) {
-      rank += beats(lane_max[j], j, mine, tid);
-    }
-    if (rank == K - 1) s_tau = mine;
-  }
-  __syncthreads();
   const float tau = s_tau;
 #pragma unroll
-  for (int i = 0; i < kPartPerThread; ++i)
-    if (val[i] >= tau && id_of(i) < hi) {
+  for (int i = 0; i < PT; ++i)
+    if (val[i] >= tau && val[i] > -INFINITY) {  // (-inf: past the end, or impossible)
       const int at = atomicAdd(&n_cand, 1);
-      if (at < kCandCap) {
-        cand_v[at] = val[i];
-        cand_i[at] = id_of(i);
-      }
+      if (at < kCandCap) cand[at] = key_of(val[i], view.id(i));
     }
   __syncthreads();
   const int nc = n_cand;
-  int round_no = 0;
+  unsigned long long* out = p.keys + slot * K;
   if (nc <= kCandCap) {
-    // rank every listed entry among the list; ranks below k are the winners' places
-    if (tid < K && tid >= nc) {  // (a part with fewer than k entries)
-      p.part_cv[slot * K + tid] = -INFINITY;
-      p.part_ci[slot * K + tid] = INT_MAX;
-    }
-    for (int j = tid; j < nc; j += kPartThreads) {
-      const float v = cand_v[j];
-      const int id = cand_i[j];
-      int rank = 0;
-#pragma unroll 8
-      for (int i = 0; i < nc; ++i) rank += beats(cand_v[i], cand_i[i], v, id);
-      if (rank < K) {
-        p.part_cv[slot * K + rank] = v;
-        p.part_ci[slot * K + rank] = id;
-      }
-    }
+    if (tid < K && tid >= nc) out[tid] = 0ull;  // (a part with fewer than k entries)
+    rank_list(cand, nc, K, [&](int rank, unsigned long long key) { out[rank] = key; });
   } else {
-    // one winner per pass: every thread offers its best entry that comes after the previous
-    // winner in the candidate order
-    float pv = INFINITY;
-    int pi = -1;
+    // one winner per pass: the largest key below the previous winner's
+    unsigned long long prev = ~0ull;
     for (int round = 0; round < K; ++round) {
-      float bv = -INFINITY;
-      int bi = INT_MAX;
+      unsigned long long best = 0ull;
 #pragma unroll
-      for (int i = 0; i < kPartPerThread; ++i) {
-        const int id = id_of(i);
-        const float v = val[i];
-        const bool after = v < pv || (v == pv && id > pi);
-        // ids increase with i, so among equal values the first one seen is the one to keep
-        if (after && id < hi && v > bv) {
-          bv = v;
-          bi = id;
-        }
+      for (int i = 0; i < PT; ++i) {
+        const unsigned long long key = key_of(val[i], view.id(i));
+        if (val[i] >= tau && val[i] > -INFINITY && key < prev && key > best) best = key;
       }
-      const Best b = block_best4(bv, bi, sv, si, (round_no++) & 1);
-      if (tid == 0) {
-        p.part_cv[slot * K + round] = b.v;
-        p.part_ci[slot * K + round] = b.id;
-      }
-      pv = b.v;
-      pi = b.id;  // INT_MAX once the part is exhausted: nothing comes after it
+      best = wave_max_key(best);
+      if (lane == 0) sk[round & 1][wave] = best;
+      __syncthreads();  // (one is enough: the buffers alternate)
+#pragma unroll
+      for (int w = 0; w < 4; ++w) best = sk[round & 1][w] > best ? sk[round & 1][w] : best;
+      if (tid == 0) out[round] = best;  // 0 once the part is exhausted: nothing comes after it
+      prev = best;
     }
   }
 }
 
-// The row's maximum and 1 / normaliser from the parts' (max, sum) pairs: every wave of every workgroup that
-// needs them reduces the pairs for itself, the same operations in the same order everywhere.
-__device__ __forceinline__ void row_max_and_norm(const SoftParams& p, int row, float& m_use, float& inv_z) {
+// The row's maximum and 1 / normaliser from the parts' (max, sum) pairs, and (for the top-k) the k-th largest of 64
+// groups of parts' maxima: every wave of every workgroup that needs them reduces the pairs for itself, the same operations
+// in the same order everywhere.
+__device__ __forceinline__ void row_max_and_norm(const SoftParams& p, int row, float& m_use, float& inv_z, float& group_max) {
   const int lane = threadIdx.x & 63, P = p.parts;
-  const float* ms = p.part_ms + (long long)row * P * 2;
-  float m = -INFINITY;
-  for (int i = lane; i < P; i += 64) m = fmaxf(m, ms[2 * i]);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+  const float2* ms = reinterpret_cast<const float2*>(p.part_ms) + (long long)row * P;
+  float2 own = make_float2(-INFINITY, 0.f);  // (rarely more than one part per lane)
+  if (lane < P) own = ms[lane];
+  float m = own.x;
+  for (int i = lane + 64; i < P; i += 64) m = fmaxf(m, ms[i].x);
+  group_max = m;
+  m = dev::wave_max(m);
   m_use = m > -INFINITY ? m : 0.f;
-  double z = 0.0;
-  for (int i = lane; i < P; i += 64) {
-    const float mp = ms[2 * i];
-    if (mp > -INFINITY) z += (double)ms[2 * i + 1] * (double)expf((mp - m_use) * p.inv_temp);
+  double z = own.x > -INFINITY ? (double)own.y * (double)expf((own.x - m_use) * p.inv_temp) : 0.0;
+  for (int i = lane + 64; i < P; i += 64) {
+    const float2 q = ms[i];
+    if (q.x > -INFINITY) z += (double)q.y * (double)expf((q.x - m_use) * p.inv_temp);
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) z += __shfl_xor(z, o);
-  inv_z = (float)(1.0 / z);
+  inv_z = (float)(1.0 / dev::wave_sum(z));
 }
 
-// the k best of the parts' candidates and their probabilities (one workgroup of four waves per row)
-__device__ __forceinline__ void row_top_k(const SoftParams& p, int row, float m_use, float inv_z) {
-  const int tid = threadIdx.x, lane = tid & 63, K = p.k, P = p.parts;
-  const float* cv = p.part_cv + (long long)row * P * K;
-  const int* ci = p.part_ci + (long long)row * P * K;
-  const int n = P * K;
-  if (n <= 1024) {  // the usual case: every candidate finds its place by counting those that beat it
-    __shared__ float mv[1024];
-    __shared__ int mi[1024];
-    for (int i = tid; i < n; i += 256) {
-      mv[i] = cv[i];
-      mi[i] = ci[i];
+// The k best of the parts' candidates and their probabilities (one workgroup of four waves per row).  As in a part: the
+// k-th largest of 64 groups' maxima bounds the row's k-th best from below, and few candidates reach it.
+__device__ __forceinline__ void row_top_k(const SoftParams& p, int row) {
+  __shared__ unsigned long long cand[kCandCap];
+  __shared__ int n_cand;
+  const int tid = threadIdx.x, lane = tid & 63, K = p.k, n = p.parts * K;
+  const unsigned long long* keys = p.keys + (long long)row * n;
+  if (tid == 0) n_cand = 0;
+  __syncthreads();
+  float m, inv_z, groups;
+  row_max_and_norm(p, row, m, inv_z, groups);
+  const unsigned tau = ordered_bits(wave_kth_largest(groups, K));
+#pragma unroll 4
+  for (int i = tid; i < n; i += kPartThreads) {
+    const unsigned long long key = keys[i];
+    if (key != 0ull && (unsigned)(key >> 32) >= tau) {
+      const int at = atomicAdd(&n_cand, 1);
+      if (at < kCandCap) cand[at] = key;
     }
-    // places that no candidate claims (fewer than k candidates in the whole row) read "none";
-    // the barrier orders these stores before the winners'
-    if (tid < K) {
-      p.tk_ids[(long long)row * K + tid] = 0;
-      p.tk_probs[(long long)row * K + tid] = 0.f;
-    }
-    __syncthreads();
-    for (int j = tid; j < n; j += 256) {
-      const float v = mv[j];
-      const int id = mi[j];
-      if (id < 0 || id >= p.vocab) continue;  // an exhausted part's filler
-      int rank = 0;
-#pragma unroll 8
-      for (int i = 0; i < n; ++i) rank += beats(mv[i], mi[i], v, id);
-      if (rank < K) {
-        p.tk_ids[(long long)row * K + rank] = id;
-        p.tk_probs[(long long)row * K + rank] = expf((v - m_use) * p.inv_temp) * inv_z;
-      }
-    }
+  }
+  __syncthreads();
+  const int nc = n_cand;
+  auto put = [&](int rank, unsigned long long key) {
+    p.tk_ids[(long long)row * K + rank] = key_id(key);
+    p.tk_probs[(long long)row * K + rank] = expf((key_value(key) - m) * p.inv_temp) * inv_z;
+  };
+  auto put_none = [&](int rank) {  // fewer than k candidates in the whole row
+    p.tk_ids[(long long)row * K + rank] = 0;
+    p.tk_probs[(long long)row * K + rank] = 0.f;
+  };
+  if (nc <= kCandCap) {
+    if (tid < K && tid >= nc) put_none(tid);
+    rank_list(cand, nc, K, put);
     return;
   }
-  if (tid >= 64) return;  // very many parts: one wave, k selection passes over the candidates in memory
-  float pv = INFINITY;
-  int pi = -1;
+  if (tid >= 64) return;  // very many ties: one wave, k selection passes over the candidates in memory
+  unsigned long long prev = ~0ull;
   for (int round = 0; round < K; ++round) {
-    float bv = -INFINITY;
-    int bi = INT_MAX;
+    unsigned long long best = 0ull;
     for (int i = lane; i < n; i += 64) {
-      const float v = cv[i];
-      const int id = ci[i];
-      const bool after = v < pv || (v == pv && id > pi);
-      if (after && better(v, id, bv, bi)) {
-        bv = v;
-        bi = id;
-      }
+      const unsigned long long key = keys[i];
+      if (key < prev && key > best) best = key;
     }
-    const Best b = wave_best(bv, bi);
+    best = wave_max_key(best);
     if (lane == 0) {
-      const bool ok = b.id >= 0 && b.id < p.vocab;
-      p.tk_ids[(long long)row * K + round] = ok ? b.id : 0;
-      p.tk_probs[(long long)row * K + round] = ok ? expf((b.v - m_use) * p.inv_temp) * inv_z : 0.f;
+      if (best != 0ull) put(round, best);
+      else put_none(round);
     }
-    pv = b.v;
-    pi = b.id;
+    prev = best;
   }
 }
 
-// One workgroup per (row, part): q = exp((x - max) / T) / Z for the part (if the distributions are asked for:
-// otherwise one workgroup per row); the workgroup of a row's first part also merges the parts' candidates
-// into the row's k best.  One launch where a merge kernel and a probabilities kernel used to follow each other.
+template <int PT>
 __global__ __launch_bounds__(kPartThreads) void row_finish_kernel(SoftParams p) {
-  const int tid = threadIdx.x, V = p.vocab;
-  const bool with_probs = p.probs != nullptr;
-  const int row = with_probs ? blockIdx.x / p.parts : blockIdx.x, part = with_probs ? blockIdx.x % p.parts : 0;
-  float m, inv_z;
-  row_max_and_norm(p, row, m, inv_z);
-  if (with_probs) {
-    const int lo = part * p.part_len, hi = min(V, lo + p.part_len);
-    const float* x = p.logits + (long long)row * V;
-    float* q = p.probs + (long long)row * V;
-    const bool vec = (V & 3) == 0 && (reinterpret_cast<size_t>(p.logits) & 15) == 0 &&
-                     (reinterpret_cast<size_t>(p.probs) & 15) == 0;
-#pragma unroll 4
-    for (int u = 0; u < kPartPerThread / 4; ++u) {
-      const int e = lo + 4 * (tid + kPartThreads * u);
-      if (vec && e + 3 < hi) {
-        const floatx4 s = *reinterpret_cast<const floatx4*>(x + e);
-        floatx4 o;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) o[c] = expf((s[c] - m) * p.inv_temp) * inv_z;
-        *reinterpret_cast<floatx4*>(q + e) = o;
-      } else {
-        for (int c = 0; c < 4; ++c)
-          if (e + c < hi) q[e + c] = expf((x[e + c] - m) * p.inv_temp) * inv_z;
-      }
-    }
+  const int V = p.vocab;
+  if ((int)blockIdx.x < p.n_rows) {  // (the longer chain: started first)
+    row_top_k(p, blockIdx.x);
+    return;
   }
-  if (part == 0) row_top_k(p, row, m, inv_z);
+  const int at = (int)blockIdx.x - p.n_rows, row = at / p.parts, part = at % p.parts;
+  const PartView<PT> view(p, part, on16(p.logits) && on16(p.probs));
+  float val[PT], m, inv_z, groups;
+  view.load(p.logits + (long long)row * V, val);  // on its way while the row's pairs are reduced
+  row_max_and_norm(p, row, m, inv_z, groups);
+#pragma unroll
+  for (int i = 0; i < PT; ++i) val[i] = expf((val[i] - m) * p.inv_temp) * inv_z;
+  view.store(p.probs + (long long)row * V, val);
+}
+
+template <int PT>
+hipError_t launch_rows(const SoftParams& p, hipStream_t stream) {
+  const unsigned parts = (unsigned)(p.n_rows * p.parts);
+  hipLaunchKernelGGL(row_parts_kernel<PT>, dim3(parts), dim3(kPartThreads), 0, stream, p);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  hipLaunchKernelGGL(row_finish_kernel<PT>, dim3(p.n_rows + (p.probs ? parts : 0u)), dim3(kPartThreads), 0, stream, p);
+  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ router and experts (Eq. 2, 3, 5)
@@ -854,21 +838,26 @@ int capped_ksplit(int m, int n, int k) {
 }
 
 struct RowPlan {
-  int parts, part_len, ksplit;
-  size_t x_bytes, ms_off, cv_off, ci_off, part_off, total;
+  int per_thread, parts, part_len, ksplit;
+  size_t x_bytes, ms_off, key_off, part_off, total;
 };
 
 RowPlan row_plan(int rows, int d_model, int vocab) {
   RowPlan r;
-  const size_t m = 2 * (size_t)rows, m_pad = (m + 31) / 32 * 32;
-  r.parts = (vocab + kPartMax - 1) / kPartMax;
+  const size_t m = 2 * (size_t)rows;
+  // Short parts spread a few rows over the CUs; with many rows long ones keep the grid at one turn of eight workgroups
+  // per CU (20 rows of 128256, all kernels: 199 us in parts of 2048, 202 in parts of 1024, 200 in parts of 4096, and 209
+  // in parts of 8192 with the top-k of a row in its first part's workgroup).
+  r.per_thread = 4;
+  while (r.per_thread < kPartPerThreadMax && (vocab + kPartThreads * r.per_thread - 1) / (kPartThreads * r.per_thread) * (long long)m > 8LL * device_cu_count())
+    r.per_thread *= 2;
+  r.parts = (vocab + kPartThreads * r.per_thread - 1) / (kPartThreads * r.per_thread);
   r.part_len = ((vocab + r.parts - 1) / r.parts + 3) / 4 * 4;
   auto up = [](size_t v) { return (v + 255) / 256 * 256; };
-  r.x_bytes = up(m_pad * (size_t)d_model * 2);
+  r.x_bytes = up(m * (size_t)d_model * 2);
   r.ms_off = r.x_bytes;
-  r.cv_off = r.ms_off + up(m * r.parts * 2 * 4);
-  r.ci_off = r.cv_off + up(m * r.parts * kMaxTopK * 4);
-  r.part_off = r.ci_off + up(m * r.parts * kMaxTopK * 4);
+  r.key_off = r.ms_off + up(m * r.parts * 2 * 4);
+  r.part_off = r.key_off + up(m * r.parts * kMaxTopK * 8);
   r.ksplit = gemm_fits((int)m, vocab) ? 1 : capped_ksplit((int)m, vocab, d_model);
   r.total = r.part_off + (r.ksplit > 1 ? up((size_t)r.ksplit * m * vocab * 4) : 0);
   return r;
@@ -879,7 +868,7 @@ RowPlan row_plan(int rows, int d_model, int vocab) {
 size_t draft_heads_workspace_bytes(int rows, int d_model, int vocab) { return row_plan(rows, d_model, vocab).total; }
 
 hipError_t launch_draft_heads(const DraftHeadsArgs& a, hipStream_t stream) {
-  const int m = 2 * a.rows, m_pad = (m + 31) / 32 * 32;
+  const int m = 2 * a.rows;
   const RowPlan rp = row_plan(a.rows, a.d_model, a.vocab);
   char* ws = static_cast<char*>(a.workspace);
   MixParams mp;
@@ -887,7 +876,7 @@ hipError_t launch_draft_heads(const DraftHeadsArgs& a, hipStream_t stream) {
   mp.s_top = a.s_top;
   mp.x = reinterpret_cast<unsigned short*>(ws);
   mp.rows = a.rows; mp.d = a.d_model; mp.mode = a.mode; mp.alpha = a.alpha; mp.beta = a.beta;
-  hipLaunchKernelGGL(head_inputs_kernel, dim3(m_pad), dim3(256), 0, stream, mp);
+  hipLaunchKernelGGL(head_inputs_kernel, dim3((unsigned)(((long long)a.rows * (a.d_model / 8) + 63) / 64)), dim3(64), 0, stream, mp);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
 
@@ -911,14 +900,14 @@ hipError_t launch_draft_heads(const DraftHeadsArgs& a, hipStream_t stream) {
   SoftParams sp;
   sp.logits = a.logits; sp.sums = parts; sp.ksplit = rp.ksplit; sp.probs = a.draft_probs; sp.tk_ids = a.topk_tokens; sp.tk_probs = a.topk_probs;
   sp.part_ms = reinterpret_cast<float*>(ws + rp.ms_off);
-  sp.part_cv = reinterpret_cast<float*>(ws + rp.cv_off);
-  sp.part_ci = reinterpret_cast<int*>(ws + rp.ci_off);
+  sp.keys = reinterpret_cast<unsigned long long*>(ws + rp.key_off);
   sp.n_rows = m; sp.vocab = a.vocab; sp.k = a.top_k; sp.parts = rp.parts; sp.part_len = rp.part_len;
   sp.inv_temp = 1.0f / a.temperature;
-  hipLaunchKernelGGL(row_parts_kernel, dim3(m * rp.parts), dim3(kPartThreads), 0, stream, sp);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(row_finish_kernel, dim3(a.draft_probs ? m * rp.parts : m), dim3(kPartThreads), 0, stream, sp);
-  return hipGetLastError();
+  switch (rp.per_thread) {
+    case 4: return launch_rows<4>(sp, stream);
+    case 8: return launch_rows<8>(sp, stream);
+    default: return launch_rows<16>(sp, stream);
+  }
 }
 
 size_t moe_experts_workspace_bytes(int rows, int d_model, int d_ff, int n_experts) {

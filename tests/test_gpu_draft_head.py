@@ -73,6 +73,15 @@ def test_random_inputs_every_row_block_count(rows):
     _check(draft_head_inputs(rows, 512, 4096 + 37 * (rows % 4), seed=rows), top_k=10)
 
 
+@pytest.mark.parametrize("rows,vocab,top_k", [(1, 1024, 16), (1, 1025, 2), (2, 5, 4), (1, 70003, 12), (66, 16388, 10),
+                                              (66, 16385, 10), (70, 33001, 5), (70, 40000, 16)])
+def test_rows_cut_into_parts_of_every_length(rows, vocab, top_k):
+    """4, 8 and 16 entries a thread (by the number of rows and the vocabulary), whole and ragged last parts, rows that
+    start at multiples of 16 bytes and not, equal logits in several parts."""
+    _check(draft_head_inputs(rows, 128, vocab, seed=vocab), top_k=top_k)
+    _check(_exact_inputs(rows, 128, vocab, vocab), top_k=top_k, exact=True)
+
+
 def test_widest_model_and_longest_candidate_lists():
     """d_model 16 384 and top-16, the largest the call takes (a small vocabulary keeps the oracle quick)."""
     _check(draft_head_inputs(3, 16384, 300, seed=5), top_k=16)
