@@ -6,25 +6,19 @@
 //
 // Kernels:
 //   head_inputs_kernel     X[2R, d] bf16 from f_top, s_top (elementwise, tiny)
-//   skinny_gemm_kernel     Y[M, N] fp32 = X[M, K] . W[N, K]^T with M <= 192 and very many weight rows: the weight
-//                          matrix (a gigabyte for an output embedding) is streamed from HBM exactly once; both
-//                          operands are staged HBM/L2 -> LDS in swizzled 64-byte row segments and read from there
-//                          in MFMA layout.  All other products run in stream_gemm.hip.
 //   row_parts_kernel, row_finish_kernel   per logits row: maximum, normaliser,
 //                          top-k by value (ties to the lower token id), probabilities.
 //   router_kernel, gated_act_kernel, select_kernel   the draft layer's router (Eq. 2, 5) and what
 //                          surrounds the experts' three projections (Eq. 3).
+// The products with weight matrices run in stream_gemm.hip.
 #include <climits>
 
-#include "jk_device.h"
 #include "jk_internal.h"
 #include "jk_wave.h"
 
 namespace jk {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
@@ -76,220 +70,6 @@ __global__ __launch_bounds__(64) void head_inputs_kernel(MixParams p) {
     }
     reinterpret_cast<u32x4*>(p.x + (long long)(2 * r + h) * p.d)[c] = o;
   }
-}
-
-// ------------------------------------------------------------------ skinny GEMM
-constexpr int kGemmThreads = 512;  // 8 waves
-constexpr int kKB = 32;            // k extent of one main-loop step (two MFMA k steps): 64 bytes per row
-
-struct GemmParams {
-  const uint16_t* x;  // [m][k] bf16
-  const uint16_t* w;  // [n][ldw] bf16
-  float* y;           // [m][ldy]
-  int m, n, k;
-  long long ldw, ldy;
-};
-
-typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8_t;
-__device__ __forceinline__ bf16x8 lds_read16(unsigned addr) { return *(lds_bf16x8_t*)(size_t)addr; }
-
-using dev::dma16;
-using dev::uniform_ptr;
-using dev::wait_vm;
-
-// Plan of one workgroup (one per CU, 8 waves).  Every wave owns NBW 32-row blocks of the weight
-// strip and all MB 32-row blocks of X: NBW * MB accumulator tiles of 16 registers.  LDS holds a
-// ring of DW steps of weight fragments per wave (private to the wave that loads and reads them)
-// and a ring of DX steps of X slabs (shared by the workgroup).
-template <int MB>
-struct GemmCfg {
-  static constexpr int NBW = 2;
-  static constexpr int STRIP = 8 * 32 * NBW;       // weight rows (output columns) per workgroup
-  static constexpr int DW = 4;
-  static constexpr int DX = MB <= 3 ? 4 : (MB <= 5 ? 3 : 2);
-  static constexpr int W_STEP = NBW * 2048;        // bytes per wave and step: NBW*32 rows of 64 bytes
-  static constexpr int W_WAVE = DW * W_STEP;
-  static constexpr int X_STEP = MB * 2048;         // MB*32 rows of 64 bytes
-  static constexpr int X_BASE = 8 * W_WAVE;
-  static constexpr int SMEM = X_BASE + DX * X_STEP;
-  static constexpr int NXI = 2 * MB;               // X transfers per step (1 KB = 16 rows each), dealt out to the waves
-  static constexpr int NWI = 2 * NBW;              // weight transfers per wave and step
-  static_assert(SMEM <= 160 * 1024, "LDS plan");
-  // Transfers complete in issue order; a wave issues, per step, its cx X transfers, then NWI of
-  // weights.  At the top of step kb the data of step kb must have landed: X(kb) was asked for
-  // DX - 1 steps ago, W(kb) DW - 1 steps ago.
-  static constexpr int wait_count(int cx) {
-    const int per = cx + NWI;
-    const int wx = NWI + (DX - 2) * per, ww = (DW - 2) * per;
-    return cx == 0 ? ww : (wx < ww ? wx : ww);
-  }
-};
-
-// v_mfma_f32_32x32x16_bf16 computes D[i][j] += sum_k A[i][k] B[k][j] with lane l holding
-// A[l % 32][8 (l / 32) .. + 8], B[.. same k ..][l % 32], and D[8 (v / 4) + 4 (l / 32) + v % 4][l % 32]
-// in accumulator register v.  Here i runs over weight rows (output columns n) and j over X rows
-// (output rows m): a lane's four consecutive accumulator registers are four consecutive n of
-// one output row, i.e. one 16-byte store.
-//
-// Both operands go HBM/L2 -> LDS in 64-byte row segments, four lanes per row (an MFMA operand
-// read straight from global memory would touch 32 cache lines per instruction and use 32 bytes
-// of each).  The strip is wide (up to 512 weight rows) because every workgroup has to pull all
-// of X through the same path as its weights: X traffic is (m / strip) of the weight traffic.
-// A row's four 16-byte pieces are stored XOR-swizzled with key(row) = (row >> 2) & 3 (the transfer
-// fetches piece s ^ key into slot s).  Measured with SQ_LDS_BANK_CONFLICT: this key (like bits 3-4 of
-// the row) gives no conflict cycles at all for an operand read (32 rows, one piece of each), bits
-// 0-1 or 1-2 cost four cycles per read.
-template <int MB>
-__global__ __launch_bounds__(kGemmThreads, 1) void skinny_gemm_kernel(GemmParams p) {
-  using C = GemmCfg<MB>;
-  constexpr int NBW = C::NBW;
-  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];  // the kernel's only LDS: offset 0
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int r = lane & 31, h = lane >> 5;
-  const long long strip0 = (long long)blockIdx.x * C::STRIP;
-  const int n_base = (int)strip0 + wave * 32 * NBW;
-  const int nkb = p.k / kKB;  // k blocks
-  // Workgroups start at different k blocks and wrap around, so that at any moment they ask for
-  // different columns of the weight matrix and of X.
-  const int kb0 = (int)((blockIdx.x * 5u) % (unsigned)nkb);
-  auto rot = [&](int kb) {
-    const int t = (kb < nkb ? kb : nkb - 1) + kb0;  // past the end: the last block again (unused, keeps the counts exact)
-    return t >= nkb ? t - nkb : t;
-  };
-
-  // transfer geometry: one instruction covers 16 rows, lane l -> row l / 4 of them, slot l % 4
-  const int sub = lane >> 2, slot = lane & 3;
-  // slot `slot` of a row holds piece slot ^ key(row), key(row) = (row >> 2) & 3 (the same for every 16-row transfer)
-  const unsigned piece = (unsigned)((slot ^ ((sub >> 2) & 3)) << 4);
-  unsigned voff_w[C::NWI], voff_x[2];
-#pragma unroll
-  for (int i = 0; i < C::NWI; ++i) {
-    const int row = min(n_base + 16 * i + sub, p.n - 1);  // rows past the end repeat the last one; never stored
-    voff_w[i] = (unsigned)((row - strip0) * p.ldw * 2) + piece;
-  }
-  // X transfer q (16 rows) belongs to wave q % 8: at most two per wave (MB <= 8)
-  const int cx = (wave < C::NXI ? 1 : 0) + (wave + 8 < C::NXI ? 1 : 0);
-#pragma unroll
-  for (int t = 0; t < 2; ++t)  // rows past the end repeat the last one (their results are never stored)
-    voff_x[t] = (unsigned)((long long)min(16 * (wave + 8 * t) + sub, p.m - 1) * p.k * 2) + piece;
-  const uint16_t* w_strip = uniform_ptr(p.w + strip0 * p.ldw);
-  const unsigned w_ring = (unsigned)(wave * C::W_WAVE);
-
-  auto issue_x = [&](int kb) {
-    const uint16_t* xb = uniform_ptr(p.x + rot(kb) * kKB);
-    const unsigned xs = (unsigned)(C::X_BASE + (kb % C::DX) * C::X_STEP);
-    if (cx > 0) dma16(xb, voff_x[0], xs + (unsigned)(wave * 1024));
-    if (cx > 1) dma16(xb, voff_x[1], xs + (unsigned)((wave + 8) * 1024));
-  };
-  auto issue_w = [&](int kb) {
-    const uint16_t* wb = uniform_ptr(w_strip + rot(kb) * kKB);
-    const unsigned ws = w_ring + (unsigned)((kb % C::DW) * C::W_STEP);
-#pragma unroll
-    for (int i = 0; i < C::NWI; ++i) dma16(wb, voff_w[i], ws + (unsigned)(i * 1024));
-  };
-
-  floatx16 acc[NBW][MB];
-#pragma unroll
-  for (int nb = 0; nb < NBW; ++nb)
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[nb][mb][v] = 0.f;
-
-  // operand read addresses within a slab: row r of a 32-row block (64 bytes per row), piece
-  // 2 j + h of MFMA k step j, swizzled
-  const unsigned rd = (unsigned)(r * 64);
-  const unsigned key = (unsigned)((r >> 2) & 3);
-
-#pragma unroll
-  for (int s = 0; s < C::DX - 1; ++s) issue_x(s);
-#pragma unroll
-  for (int s = 0; s < C::DW - 1; ++s) issue_w(s);
-
-  for (int kb = 0; kb < nkb; ++kb) {
-    if (kb < (C::DW > C::DX ? C::DW : C::DX)) {
-      wait_vm<0>();  // (the prologue's order differs from the steady state's)
-    } else if (cx == 2) {
-      wait_vm<C::wait_count(2)>();
-    } else if (cx == 1) {
-      wait_vm<C::wait_count(1)>();
-    } else {
-      wait_vm<C::wait_count(0)>();
-    }
-    __syncthreads();  // every wave's part of X(kb) has landed; everybody is done with step kb - 1
-    issue_x(kb + C::DX - 1);
-    issue_w(kb + C::DW - 1);
-    const unsigned xa = (unsigned)(C::X_BASE + (kb % C::DX) * C::X_STEP) + rd;
-    const unsigned wa = w_ring + (unsigned)((kb % C::DW) * C::W_STEP) + rd;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const unsigned pc = ((unsigned)(2 * j + h) ^ key) << 4;
-      bf16x8 a[NBW];
-#pragma unroll
-      for (int nb = 0; nb < NBW; ++nb) a[nb] = lds_read16(wa + (unsigned)(nb * 2048) + pc);
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        const bf16x8 b = lds_read16(xa + (unsigned)(mb * 2048) + pc);
-#pragma unroll
-        for (int nb = 0; nb < NBW; ++nb)
-          acc[nb][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[nb], b, acc[nb][mb], 0, 0, 0);
-      }
-    }
-  }
-  wait_vm<0>();  // the redundant transfers of the last steps must not outlive the workgroup's LDS
-
-  // epilogue: lane (r, h) holds, for output row mb*32 + r, columns block + 8 q + 4 h + (0..3)
-  const bool vec_ok = (p.ldy & 3) == 0 && (reinterpret_cast<size_t>(p.y) & 15) == 0;
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-    const int m = mb * 32 + r;
-    if (m >= p.m) continue;
-    float* yrow = p.y + (long long)m * p.ldy;
-#pragma unroll
-    for (int nb = 0; nb < NBW; ++nb)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int n = n_base + 32 * nb + 8 * q + 4 * h;
-        if (vec_ok && n + 3 < p.n) {
-          *reinterpret_cast<floatx4*>(yrow + n) = floatx4{acc[nb][mb][4 * q], acc[nb][mb][4 * q + 1],
-                                                          acc[nb][mb][4 * q + 2], acc[nb][mb][4 * q + 3]};
-        } else {
-#pragma unroll
-          for (int t = 0; t < 4; ++t)
-            if (n + t < p.n) yrow[n + t] = acc[nb][mb][4 * q + t];
-        }
-      }
-  }
-}
-
-template <int MB>
-hipError_t launch_gemm_mb(const GemmParams& p, hipStream_t stream) {
-  static LdsLimitRaised raised;
-  if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(skinny_gemm_kernel<MB>), GemmCfg<MB>::SMEM, raised);
-      e != hipSuccess)
-    return e;
-  const unsigned grid = (unsigned)((p.n + GemmCfg<MB>::STRIP - 1) / GemmCfg<MB>::STRIP);
-  hipLaunchKernelGGL(skinny_gemm_kernel<MB>, dim3(grid), dim3(kGemmThreads), GemmCfg<MB>::SMEM, stream, p);
-  return hipGetLastError();
-}
-
-hipError_t launch_gemm(const GemmParams& p, hipStream_t stream) {
-  switch ((p.m + 31) / 32) {
-    case 1: return launch_gemm_mb<1>(p, stream);
-    case 2: return launch_gemm_mb<2>(p, stream);
-    case 3: return launch_gemm_mb<3>(p, stream);
-    case 4: return launch_gemm_mb<4>(p, stream);
-    case 5: return launch_gemm_mb<5>(p, stream);
-    case 6: return launch_gemm_mb<6>(p, stream);
-    default: return hipErrorInvalidValue;
-  }
-}
-
-// Where strips of 512 weight rows alone give most CUs a workgroup this kernel is the better one: 128256 x 4096 with 20
-// rows 177 us against 180, with 160 rows 234 against 252; 100000 x 4096 143 against 154.  80000 x 4096 (157 strips) is
-// not: 130 against 125.
-bool gemm_fits(int m, int n) {
-  return m <= 192 && (long long)(n + GemmCfg<1>::STRIP - 1) / GemmCfg<1>::STRIP * 4 >= 3LL * device_cu_count();
 }
 
 // ------------------------------------------------------------------ softmax + top-k per logits row
@@ -781,8 +561,8 @@ MoePlan moe_plan(int rows, int d, int f, int n) {
   for (int r = 0; r < rows; ++r) missed *= 1.0 - 2.0 / n;
   const int used = n * (1.0 - missed) < 2.0 ? 2 : (int)(n * (1.0 - missed) + 0.5);
   const int each = (2 * rows + used - 1) / used;
-  m.split1 = stream_gemm_ksplit(each, f, d, used, true);  // gate and up in one launch
-  m.split2 = stream_gemm_ksplit(each, d, f, used, false);
+  m.split1 = stream_gemm_ksplit(each, f, d, used, true, 7000);  // gate and up in one launch
+  m.split2 = stream_gemm_ksplit(each, d, f, used, false, 0);
   const size_t pre = m.split1 > 1 ? up((size_t)m.split1 * n * rows * f * 4) : 0;
   m.g_off = 0;
   m.up_off = pre;
@@ -831,8 +611,8 @@ __global__ __launch_bounds__(256) void linear_finish_kernel(LinFinishParams p) {
 }
 
 // parts of a product with few output columns, at most 64 MB of partial results
-int capped_ksplit(int m, int n, int k) {
-  int s = stream_gemm_ksplit(m, n, k, 1, false);
+int capped_ksplit(int m, int n, int k, int split_ns) {
+  int s = stream_gemm_ksplit(m, n, k, 1, false, split_ns);
   while (s > 1 && (size_t)s * m * n * 4 > ((size_t)64 << 20)) --s;
   return s;
 }
@@ -858,7 +638,7 @@ RowPlan row_plan(int rows, int d_model, int vocab) {
   r.ms_off = r.x_bytes;
   r.key_off = r.ms_off + up(m * r.parts * 2 * 4);
   r.part_off = r.key_off + up(m * r.parts * kMaxTopK * 8);
-  r.ksplit = gemm_fits((int)m, vocab) ? 1 : capped_ksplit((int)m, vocab, d_model);
+  r.ksplit = capped_ksplit((int)m, vocab, d_model, 0);
   r.total = r.part_off + (r.ksplit > 1 ? up((size_t)r.ksplit * m * vocab * 4) : 0);
   return r;
 }
@@ -882,19 +662,11 @@ hipError_t launch_draft_heads(const DraftHeadsArgs& a, hipStream_t stream) {
 
   const uint16_t *x = reinterpret_cast<const uint16_t*>(ws), *w = static_cast<const uint16_t*>(a.w_head);
   float* parts = rp.ksplit > 1 ? reinterpret_cast<float*>(ws + rp.part_off) : nullptr;
-  if (gemm_fits(m, a.vocab)) {
-    GemmParams gp;
-    gp.x = x; gp.w = w; gp.y = a.logits;
-    gp.m = m; gp.n = a.vocab; gp.k = a.d_model;
-    gp.ldw = a.d_model; gp.ldy = a.vocab;
-    e = launch_gemm(gp, stream);
-  } else {
-    StreamGemmArgs g{};
-    g.x = x; g.w = w; g.y = parts ? parts : a.logits;
-    g.m = m; g.n = a.vocab; g.k = a.d_model;
-    g.ksplit = rp.ksplit; g.y_split = (long long)m * a.vocab; g.batch = 1;
-    e = launch_stream_gemm(g, stream);
-  }
+  StreamGemmArgs g{};
+  g.x = x; g.w = w; g.y = parts ? parts : a.logits;
+  g.m = m; g.n = a.vocab; g.k = a.d_model;
+  g.ksplit = rp.ksplit; g.y_split = (long long)m * a.vocab; g.batch = 1;
+  e = launch_stream_gemm(g, stream);
   if (e != hipSuccess) return e;
 
   SoftParams sp;
@@ -964,12 +736,16 @@ hipError_t launch_moe_experts(const MoeArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+namespace {
+constexpr int kLinearSplitNs = 3500;  // linear_finish_kernel
+}
+
 size_t linear_workspace_bytes(int m, int n, int k) {
-  return ((size_t)capped_ksplit(m, n, k) * m * n * 4 + 255) / 256 * 256;
+  return ((size_t)capped_ksplit(m, n, k, kLinearSplitNs) * m * n * 4 + 255) / 256 * 256;
 }
 
 hipError_t launch_linear(const LinearArgs& a, hipStream_t stream) {
-  const int ks = capped_ksplit(a.m, a.n, a.k);
+  const int ks = capped_ksplit(a.m, a.n, a.k, kLinearSplitNs);
   StreamGemmArgs g{};
   g.x = static_cast<const uint16_t*>(a.x); g.w = static_cast<const uint16_t*>(a.w);
   g.m = a.m; g.n = a.n; g.k = a.k; g.ksplit = ks; g.y_split = (long long)a.m * a.n; g.batch = 1;

@@ -163,7 +163,7 @@ struct StreamGemmArgs {
   uint16_t* act;
   long long act_batch;
 };
-int stream_gemm_ksplit(int m, int n, int k, int batch, bool pair);
+int stream_gemm_ksplit(int m, int n, int k, int batch, bool pair, int split_ns);
 hipError_t launch_stream_gemm(const StreamGemmArgs& p, hipStream_t stream);       // m <= 256
 hipError_t launch_stream_gemm_pair(const StreamGemmArgs& p, hipStream_t stream);  // m <= 128
 hipError_t launch_stream_gemm_down(const StreamGemmArgs& p, hipStream_t stream);  // m <= 128
@@ -218,7 +218,7 @@ hipError_t launch_tree_finalize(const TreeFinalArgs& a, hipStream_t stream);
 hipError_t launch_gather_rows(const float* q_all, const int* q_row, float* out, long long n_nodes, int vocab,
                               long long n_q_rows, hipStream_t stream);
 
-// plain linear layer on the skinny GEMM
+// plain linear layer
 struct LinearArgs {
   int m, n, k;
   const void *x, *w, *residual;

@@ -1,19 +1,20 @@
-// Products of few rows with weight matrices of tens to hundreds of megabytes (gfx950): the draft layer's linear layers,
-// its experts' projections, and output heads over a small vocabulary.  Y[M, N] = X[M, K] . W[N, K]^T, M <= 256, bf16
-// operands, fp32 accumulation.
+// Products of few rows with weight matrices (gfx950): the draft layer's linear layers, its experts' projections, and the
+// output heads.  Y[M, N] = X[M, K] . W[N, K]^T, M <= 256, bf16 operands, fp32 accumulation.
 //
 // What bounds it: the weight stream, and for a few tens of megabytes the round trip to memory in front of it.  So a wave
 // fetches its weights straight into registers in MFMA layout (v_mfma_f32_16x16x32_bf16: 16 rows of 64 bytes per
 // instruction, the other half of each 128-byte line with the next k step), 8 KB of them in flight from the first
-// cycle on, each register asked for again as soon as its product is issued; only X goes through LDS, one chunk of k
+// cycle on, each register asked for again as soon as its last product is issued; only X goes through LDS, one chunk of k
 // ahead of its use, shared by the workgroup's eight waves; one barrier per chunk.  Narrow strips (128 weight rows) and
 // whole k ranges where that gives every CU a workgroup, k split into as many parts as it takes otherwise.
-// Measured on an MI355X (weights cold, 40 rows, us): 4096 x 8192 15.2, 6144 x 4096 13.5, 4096 x 4096 9.4, 1024 x 2048
-// 4.9; 16 x 4096 x 4096 98, 8 x 4096 x 4096 49 (5.5 TB/s; a plain read of a gigabyte runs at 5.75).  The kernel that
-// these calls used before (skinny_gemm_kernel: weights through LDS rings, strips of 512 rows, at most eight k parts)
-// took 35.3, 22.9, 21.3, 15.2, 114 and 61 us.  It is still the better one for very many weight rows (128256 x 4096,
-// 20 rows: 177 us against 180), where a workgroup per CU has a strip of 512 to itself.  Non-temporal loads (-10 %) and
-// chunks of 512 (no difference) were tried.
+// Measured on an MI355X (weights cold, us): 40 rows, 4096 x 8192 15.2, 6144 x 4096 13.5, 4096 x 4096 9.4; 16 x 4096 x 4096
+// 98; 20 rows, 128256 x 4096 175 (6.0 TB/s), 80 rows 204; 32768 x 4096, 4 rows 47 (5.7 TB/s), 128 rows 63: with many
+// rows a CU draws as many bytes of X from L2 as of weights.  With weights through LDS rings and strips of 512 rows the
+// same products took 35.3, 22.9, 21.3, 114 and 177 us.  Non-temporal weight loads (-10 %), chunks of 512 and more
+// weights in flight (no difference) were tried.
+#include <cmath>
+#include <type_traits>
+
 #include "jk_internal.h"
 
 namespace jk {
@@ -24,6 +25,7 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 512;  // 8 waves
+constexpr int kListBytes = 512;  // the rows that chose an expert (at most 128)
 
 __device__ __forceinline__ unsigned bf16_bits_rne(float f) {
   const unsigned u = __float_as_uint(f);
@@ -40,89 +42,81 @@ __device__ __forceinline__ float bf16_hi(unsigned w) { return __uint_as_float(w 
 //   DOWN   a strip of an expert's output projection, for the rows it has
 enum Kind { PLAIN, PAIR, DOWN };
 
-template <int MT, int KC, Kind KIND>
+// NF: 16-row weight fragments of a wave, side by side; a workgroup has a strip of 128 NF weight rows
+constexpr int strip_rows(int nf) { return 128 * nf; }
+// k steps of 32 whose weights are in flight: 64 KB per workgroup (what a CU turns over in a round trip)
+constexpr int steps_ahead(int nf) { return nf == 1 ? 8 : (nf <= 3 ? 4 : 2); }
+
+// One strip for up to 16 MT rows
+template <int MT, int NF>
 struct Cfg {
-  static constexpr int NF = KIND == PAIR || MT > 8 ? 2 : 1;  // 16-row weight fragments per wave
-  static constexpr int COLS = KIND == PAIR ? 128 : 128 * NF;  // output columns per workgroup
-  static constexpr int KS = KC / 32;                          // MFMA k steps per chunk
+  static constexpr int AHEAD = steps_ahead(NF);
+  static constexpr int KC = MT > 8 && AHEAD < 8 ? 128 : 256;  // k per chunk of X
+  static constexpr int KS = KC / 32;  // MFMA k steps per chunk
   static constexpr int LDX = KC + 8;  // bf16 per LDS row: 16 bytes of padding spread the rows over the banks
   static constexpr int PIECES = MT * 16 * (KC / 8);           // 16-byte pieces of an X chunk
   static constexpr int XP = (PIECES + kThreads - 1) / kThreads;
   static constexpr int X_BYTES = MT * 16 * LDX * 2;
-  static constexpr int LIST = KIND == PLAIN ? 0 : 512;        // the rows that chose this expert (at most 128)
-  static constexpr int SMEM = LIST + 2 * X_BYTES;
-  static_assert(SMEM <= 160 * 1024, "LDS plan");
-  // operand reads of X run one k step ahead of the products; with many rows there are no registers for that, and
-  // the two waves of a SIMD cover each other's reads instead
-  static constexpr int NB = MT <= 8 ? 2 : 1;
+  static constexpr int SMEM = 2 * X_BYTES;
+  static_assert(SMEM + kListBytes <= 160 * 1024, "LDS plan");
+  static constexpr int LOOK = 7;      // products between an X operand's read from LDS and its use
 };
 
-template <int MT, int KC, Kind KIND>
-__global__ __launch_bounds__(kThreads, 2) void stream_gemm_kernel(StreamGemmArgs p) {
-  using C = Cfg<MT, KC, KIND>;
-  constexpr int NF = C::NF, KS = C::KS, NB = C::NB;
-  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int r = lane & 15, g = lane >> 4;
-  const int e = blockIdx.y;
-  int* list = reinterpret_cast<int*>(smem);
-  int m = p.m;
-  if (KIND != PLAIN) {
-    // The rows that chose expert e, in order.  Every wave makes the whole list (the same one) for itself: its LDS
-    // operations complete in order, so no barrier is needed before it reads its own entries.
-    m = 0;
-    for (int i0 = 0; i0 < p.m; i0 += 64) {
-      const int row = i0 + lane;
-      const bool mine = row < p.m && (p.sel[2 * row] == e || p.sel[2 * row + 1] == e);
-      const unsigned long long v = __ballot(mine);
-      if (mine) list[m + __popcll(v & ((1ull << lane) - 1ull))] = row;
-      m += __popcll(v);
+// A wave's weights: its rows' addresses, and the fragments of the next AHEAD k steps in registers
+template <int NF, Kind KIND>
+struct Weights {
+  static constexpr int AHEAD = steps_ahead(NF);
+  const uint16_t* row[NF];
+  bf16x8 a[NF][AHEAD];
+  int k0, k1;        // this part's k range, in units of 128
+  unsigned wg;
+
+  __device__ __forceinline__ void start(const StreamGemmArgs& p, int n_base, int e, int wave, int r, int g) {
+    const int units = p.k / 128;
+    k0 = (int)((long long)blockIdx.z * units / p.ksplit) * 128;
+    k1 = (int)((long long)(blockIdx.z + 1) * units / p.ksplit) * 128;
+    wg = blockIdx.x + gridDim.x * blockIdx.y;
+    const uint16_t* base = (KIND == PAIR && wave >= 4 ? p.w2 : p.w) + (long long)e * p.w_batch;
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      const int n = min(n_base + 16 * f + r, p.n - 1);  // rows past the end repeat the last one; never stored
+      row[f] = base + (long long)n * p.k + 8 * g;
     }
-    if (m == 0) return;  // nobody chose it (the whole workgroup: nobody waits at a later barrier)
   }
-  const int nt = KIND == PLAIN ? MT : (m + 15) / 16;  // 16-row blocks of X in use
-  const uint16_t* px = p.x + (long long)e * p.x_batch;
-  const uint16_t* pw = p.w + (long long)e * p.w_batch;
-  const int n_base = (int)blockIdx.x * C::COLS + wave * (C::COLS / 8);
-  // this part's k range, in units of 128 (whole chunks but perhaps for the last one of the range)
-  const int units = p.k / 128;
-  const int k0 = (int)((long long)blockIdx.z * units / p.ksplit) * 128, k1 = (int)((long long)(blockIdx.z + 1) * units / p.ksplit) * 128;
-  const int nc = (k1 - k0 + KC - 1) / KC;
+  // (what lies past a half chunk at the end of the range is fetched from inside it and not used)
+  __device__ __forceinline__ void load(int k, int slot) {
+    k = min(k, k1 - 32);
+#pragma unroll
+    for (int f = 0; f < NF; ++f) a[f][slot] = *reinterpret_cast<const bf16x8*>(row[f] + k);
+  }
   // Workgroups start at different chunks and wrap around: rows often lie a power of two apart, so that workgroups in
   // step would all ask the same few memory channels (16 x 4096 x 4096: 115 us in step, 98 us like this; 32000 x 4096:
   // 58 and 46).  Workgroups run on the eight XCDs in turn, so the start has to vary within every eighth of them too.
   // (A half chunk at the end stays last.)
-  const int whole = (k1 - k0) / KC;
-  const unsigned wg = blockIdx.x + gridDim.x * blockIdx.y;
-  const int rot = whole > 0 ? (int)((5u * wg + (wg >> 3)) % (unsigned)whole) : 0;
-  auto chunk_k = [&](int c) {
+  template <int KC>
+  __device__ __forceinline__ int chunk(int c) const {
+    const int whole = (k1 - k0) / KC;
+    const int rot = whole > 0 ? (int)((5u * wg + (wg >> 3)) % (unsigned)whole) : 0;
     const int t = c + rot;
     return k0 + (c < whole ? (t < whole ? t : t - whole) : c) * KC;
-  };
-
-  const uint16_t* wp[NF];
-#pragma unroll
-  for (int f = 0; f < NF; ++f) {
-    const int row = min(n_base + (KIND == PAIR ? 0 : 16 * f) + r, p.n - 1);  // rows past the end repeat the last one; never stored
-    const uint16_t* base = KIND == PAIR && f == 1 ? p.w2 + (long long)e * p.w_batch : pw;
-    wp[f] = base + (long long)row * p.k + 8 * g;
   }
-  bf16x8 a[NF][KS];
-  // (what lies past a half chunk at the end of the range is fetched from inside it and not used)
-  auto load_w = [&](int kc, int j) {
-    const int k = min(kc + 32 * j, k1 - 32);
-#pragma unroll
-    for (int f = 0; f < NF; ++f) a[f][j] = *reinterpret_cast<const bf16x8*>(wp[f] + k);
-  };
-#pragma unroll
-  for (int j = 0; j < KS; ++j) load_w(chunk_k(0), j);
+};
 
+template <int MT, int NF, Kind KIND>
+__device__ __forceinline__ void strip_products(const StreamGemmArgs& p, Weights<NF, KIND>& w, int m, const int* list, unsigned char* xbuf,
+                                               int e) {
+  using C = Cfg<MT, NF>;
+  constexpr int KS = C::KS, KC = C::KC, AHEAD = C::AHEAD;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r = lane & 15, g = lane >> 4;
+  const int k0 = w.k0, k1 = w.k1, nc = (k1 - k0 + KC - 1) / KC;
+  const uint16_t* px = p.x + (long long)e * p.x_batch;
   const uint16_t* xp[C::XP];
   u32x4 xr[C::XP];
   auto x_row = [&](int q) { return (tid + q * kThreads) / (KC / 8); };
   auto x_col = [&](int q) { return ((tid + q * kThreads) % (KC / 8)) * 8; };
   auto x_used = [&](int q) {
-    return KIND == PLAIN ? (C::PIECES % kThreads == 0 || tid + q * kThreads < C::PIECES) : x_row(q) < 16 * nt;
+    return C::PIECES % kThreads == 0 || tid + q * kThreads < C::PIECES;
   };
 #pragma unroll
   for (int q = 0; q < C::XP; ++q) {  // rows past the end repeat the last one; never stored
@@ -138,156 +132,243 @@ __global__ __launch_bounds__(kThreads, 2) void stream_gemm_kernel(StreamGemmArgs
   auto park_x = [&](int buf) {
 #pragma unroll
     for (int q = 0; q < C::XP; ++q)
-      if (x_used(q)) *reinterpret_cast<u32x4*>(smem + C::LIST + buf * C::X_BYTES + x_row(q) * (C::LDX * 2) + x_col(q) * 2) = xr[q];
+      if (x_used(q)) *reinterpret_cast<u32x4*>(xbuf + buf * C::X_BYTES + x_row(q) * (C::LDX * 2) + x_col(q) * 2) = xr[q];
   };
   floatx4 acc[NF][MT];
 #pragma unroll
   for (int f = 0; f < NF; ++f)
 #pragma unroll
     for (int t = 0; t < MT; ++t) acc[f][t] = floatx4{0.f, 0.f, 0.f, 0.f};
-  bf16x8 b[NB][MT];
-  const unsigned char* x_lane = smem + C::LIST + r * (C::LDX * 2) + 16 * g;
-  auto read_x = [&](int c, int j) {
+  const unsigned char* x_lane = xbuf + r * (C::LDX * 2) + 16 * g;
+  // k steps j0 .. j1 - 1 of chunk c, whose first k is kc; the following chunk, if there is one, starts at `next`.  X operands
+  // are read LOOK products ahead of their use, and each weight register is asked for again once its last product is
+  // issued.  The order is fixed step by step: left alone, the compiler puts each read right in front of its product
+  // (90 rows of a draft layer's three products: 133 us, and 124 like this) and gathers the loads at the chunk's end.
+  auto steps = [&](int c, int kc, int next, auto j0c, auto j1c, auto morec) {
+    constexpr int J0 = decltype(j0c)::value, N = (decltype(j1c)::value - J0) * MT, LOOK = C::LOOK < N ? C::LOOK : N;
+    const unsigned char* x = x_lane + (c & 1) * C::X_BYTES;
+    bf16x8 b[LOOK + 1];
+    auto read = [&](int i) { b[i % (LOOK + 1)] = *reinterpret_cast<const bf16x8*>(x + (i % MT) * 16 * (C::LDX * 2) + 64 * (J0 + i / MT)); };
 #pragma unroll
-    for (int t = 0; t < MT; ++t)
-      if (KIND == PLAIN || t < nt)
-        b[j % NB][t] = *reinterpret_cast<const bf16x8*>(x_lane + (c & 1) * C::X_BYTES + t * 16 * (C::LDX * 2) + 64 * j);
-  };
-  auto products = [&](int j) {
+    for (int i = 0; i < LOOK; ++i) read(i);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int t = 0; t < MT; ++t)
-      if (KIND == PLAIN || t < nt) {
+    for (int i = 0; i < N; ++i) {
+      const int j = J0 + i / MT, t = i % MT;
+      if (i + LOOK < N) read(i + LOOK);
 #pragma unroll
-        for (int f = 0; f < NF; ++f) acc[f][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[f][j], b[j % NB][t], acc[f][t], 0, 0, 0);
+      for (int f = 0; f < NF; ++f) acc[f][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.a[f][j % AHEAD], b[i % (LOOK + 1)], acc[f][t], 0, 0, 0);
+      if (t == MT - 1) {
+        if (j + AHEAD < KS) w.load(kc + 32 * (j + AHEAD), j % AHEAD);
+        else if (decltype(morec)::value) w.load(next + 32 * (j + AHEAD - KS), j % AHEAD);
       }
+      __builtin_amdgcn_sched_barrier(0);
+    }
   };
-  load_x(chunk_k(0));
+  typedef std::integral_constant<int, 0> Zero;
+  typedef std::integral_constant<int, KS < 4 ? KS : 4> Half;
+  typedef std::integral_constant<int, KS> Whole;
+  load_x(w.template chunk<KC>(0));
   park_x(0);
   __syncthreads();
   for (int c = 0; c + 1 < nc; ++c) {  // every chunk but the last is whole
-    const int kn = chunk_k(c + 1);
+    const int kn = w.template chunk<KC>(c + 1);
     load_x(kn);
-    if (NB == 2) read_x(c, 0);
-#pragma unroll
-    for (int j = 0; j < KS; ++j) {
-      if (NB == 1 || j + 1 < KS) read_x(c, NB == 1 ? j : j + 1);
-      products(j);
-      load_w(kn, j);
-      // (left alone, the compiler gathers all loads at the chunk's end, with nothing in flight by then)
-      asm volatile("" ::: "memory");
-    }
+    steps(c, w.template chunk<KC>(c), kn, Zero(), Whole(), std::true_type());
     park_x((c + 1) & 1);
     __syncthreads();
   }
   {
-    const int c = nc - 1;
-    auto last = [&](int j0, int j1) {
-      if (NB == 2) read_x(c, j0);
-#pragma unroll
-      for (int j = j0; j < j1; ++j) {
-        if (NB == 1 || j + 1 < j1) read_x(c, NB == 1 ? j : j + 1);
-        products(j);
-      }
-    };
-    last(0, 4);
-    if (KS > 4 && (k1 - k0) % KC == 0) last(4, KS);
+    const int c = nc - 1, kc = w.template chunk<KC>(c);
+    steps(c, kc, 0, Zero(), Half(), std::false_type());
+    if (KS > 4 && (k1 - k0) % KC == 0) steps(c, kc, 0, Half(), Whole(), std::false_type());
   }
 
-  // lane (r, g) holds, for output row 16 t + r, columns block + 4 g + (0..3)
+  // A lane holds, for output row 16 t + r, columns (the wave's, 16 per fragment) + 4 g + (0..3): stored as it is, every
+  // instruction would write 64 bytes of each of 16 rows (a 57 MB result of odd width: 41 us, and 18 like this).  So the rows are laid
+  // out in LDS, as many as its X buffers hold at a time, and go out whole.
+  constexpr int COLS = strip_rows(NF), LDO = COLS + 4, FIT = C::SMEM / (16 * LDO * 4), RT = FIT < MT ? FIT : MT;
+  constexpr int OUT = KIND == PAIR ? COLS / 2 : COLS;  // output columns (PAIR: the gate's in front of the up projection's)
+  static_assert(RT >= 1, "an output block fits");
   const bool vec = (p.n & 3) == 0 && (reinterpret_cast<size_t>(p.y) & 15) == 0 && (reinterpret_cast<size_t>(p.residual) & 7) == 0 &&
                    (reinterpret_cast<size_t>(p.out_bf16) & 7) == 0;
-  if (KIND == PAIR && p.act) {
-    uint16_t* h = p.act + (long long)e * p.act_batch;
+  float* tile = reinterpret_cast<float*>(xbuf);
+  const int n0 = (int)blockIdx.x * OUT;
+  // emit4 (emit1): element offset in the output, and where its four values (its value) are in LDS
+  auto put = [&](auto emit4, auto emit1) {
 #pragma unroll
-    for (int t = 0; t < MT; ++t) {
-      const int row = 16 * t + r, n = n_base + 4 * g;
-      if (row >= m || n >= p.n) continue;
-      float o[4];
+    for (int t0 = 0; t0 < MT; t0 += RT) {
+      if (16 * t0 >= m) break;
+      __syncthreads();  // what was read here before has been used
 #pragma unroll
-      for (int i = 0; i < 4; ++i) o[i] = acc[0][t][i] / (1.f + expf(-acc[0][t][i])) * acc[NF - 1][t][i];
-      uint2 v;
-      v.x = bf16_bits_rne(o[0]) | (bf16_bits_rne(o[1]) << 16);
-      v.y = bf16_bits_rne(o[2]) | (bf16_bits_rne(o[3]) << 16);
-      *reinterpret_cast<uint2*>(h + (long long)row * p.n + n) = v;  // (n is a multiple of 128)
+      for (int t = t0; t < (t0 + RT < MT ? t0 + RT : MT); ++t)
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+          *reinterpret_cast<floatx4*>(tile + (16 * (t - t0) + r) * LDO + wave * 16 * NF + 16 * f + 4 * g) = acc[f][t];
+      __syncthreads();
+      const int rows = min(16 * RT, m - 16 * t0);
+      if (vec) {
+#pragma unroll 4
+        for (int i = tid; i < rows * (OUT / 4); i += kThreads) {
+          const int row = i / (OUT / 4), col = i % (OUT / 4) * 4;
+          if (n0 + col < p.n) emit4((long long)(16 * t0 + row) * p.n + n0 + col, reinterpret_cast<const floatx4*>(tile + row * LDO + col));
+        }
+      } else {
+        for (int i = tid; i < rows * OUT; i += kThreads) {
+          const int row = i / OUT, col = i % OUT;
+          if (n0 + col < p.n) emit1((long long)(16 * t0 + row) * p.n + n0 + col, tile + row * LDO + col);
+        }
+      }
     }
-    return;
-  }
-#pragma unroll
-  for (int f = 0; f < NF; ++f) {
-    float* y = (KIND == PAIR && f == 1 ? p.y2 : p.y) + (long long)e * p.y_batch + (long long)blockIdx.z * p.y_split;
-    const int n = n_base + (KIND == PAIR ? 0 : 16 * f) + 4 * g;
-#pragma unroll
-    for (int t = 0; t < MT; ++t) {
-      const int row = 16 * t + r;
-      if (row >= m) continue;
-      const long long at = (long long)row * p.n + n;
-      if (KIND == PLAIN && p.finish) {  // an undivided k range: the finished layer
-        const uint16_t* res = p.residual;
-        if (vec && n < p.n) {
-          floatx4 v = acc[f][t];
+  };
+  const long long part = (long long)e * p.y_batch + (long long)blockIdx.z * p.y_split;
+  float* y = p.y + part;
+  if constexpr (KIND == PAIR) {
+    float* y2 = p.y2 + part;
+    uint16_t* h = p.act + (long long)e * p.act_batch;
+    auto gated = [](float a, float b) { return a / (1.f + expf(-a)) * b; };
+    if (p.act) {
+      put(
+          [&](long long at, const floatx4* v) {
+            const floatx4 a = v[0], b = v[OUT / 4];
+            uint2 o;
+            o.x = bf16_bits_rne(gated(a[0], b[0])) | (bf16_bits_rne(gated(a[1], b[1])) << 16);
+            o.y = bf16_bits_rne(gated(a[2], b[2])) | (bf16_bits_rne(gated(a[3], b[3])) << 16);
+            *reinterpret_cast<uint2*>(h + at) = o;
+          },
+          [&](long long at, const float* v) { h[at] = (uint16_t)bf16_bits_rne(gated(v[0], v[OUT])); });
+    } else {
+      put(
+          [&](long long at, const floatx4* v) {
+            *reinterpret_cast<floatx4*>(y + at) = v[0];
+            *reinterpret_cast<floatx4*>(y2 + at) = v[OUT / 4];
+          },
+          [&](long long at, const float* v) {
+            y[at] = v[0];
+            y2[at] = v[OUT];
+          });
+    }
+  } else if (KIND == PLAIN && p.finish) {  // an undivided k range: the finished layer
+    const uint16_t* res = p.residual;
+    put(
+        [&](long long at, const floatx4* pv) {
+          floatx4 v = *pv;
           if (res) {
             const uint2 q = *reinterpret_cast<const uint2*>(res + at);
             v += floatx4{bf16_lo(q.x), bf16_hi(q.x), bf16_lo(q.y), bf16_hi(q.y)};
           }
-          if (p.y) *reinterpret_cast<floatx4*>(y + at) = v;
+          if (p.y) *reinterpret_cast<floatx4*>(p.y + at) = v;
           if (p.out_bf16) {
             uint2 o;
             o.x = bf16_bits_rne(v[0]) | (bf16_bits_rne(v[1]) << 16);
             o.y = bf16_bits_rne(v[2]) | (bf16_bits_rne(v[3]) << 16);
             *reinterpret_cast<uint2*>(p.out_bf16 + at) = o;
           }
-        } else {
+        },
+        [&](long long at, const float* pv) {
+          float v = *pv;
+          if (res) v += bf16_lo(res[at]);
+          if (p.y) p.y[at] = v;
+          if (p.out_bf16) p.out_bf16[at] = (uint16_t)bf16_bits_rne(v);
+        });
+  } else {
+    // (parts of a split product are small and read again at once; whole results of tens of megabytes only push the
+    // weights' way through the caches: 128256 x 4096, 80 rows: 253 us with ordinary stores, 242 with these)
+    const bool parts = p.ksplit > 1;
+    put(
+        [&](long long at, const floatx4* v) {
+          if (parts) *reinterpret_cast<floatx4*>(y + at) = *v;
+          else __builtin_nontemporal_store(*v, reinterpret_cast<floatx4*>(y + at));
+        },
+        [&](long long at, const float* v) { y[at] = *v; });
+  }
+}
+
+template <int MT, int NF, Kind KIND>
+__global__ __launch_bounds__(kThreads, 2) void stream_gemm_kernel(StreamGemmArgs p) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, e = blockIdx.y;
+  // (PAIR: four waves have gate rows, four the same rows of the up projection; with both in one wave, two fragments of
+  // half as many k steps each, the short pieces of a row cost 5 - 9 % of the bandwidth unless rows are a power of two long)
+  const int n_base = KIND == PAIR ? ((int)blockIdx.x * 4 + (wave & 3)) * 16 * NF : ((int)blockIdx.x * 8 + wave) * 16 * NF;
+  Weights<NF, KIND> w;
+  w.start(p, n_base, e, wave, lane & 15, lane >> 4);
+  // (chunks have the same order whatever their number of rows: KC is 256 in all of a kernel's variants)
+  constexpr int KC = Cfg<MT, NF>::KC;
+  const int first = w.template chunk<KC>(0);
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (n + i < p.n) {
-              float v = acc[f][t][i];
-              if (res) v += bf16_lo(res[at + i]);
-              if (p.y) y[at + i] = v;
-              if (p.out_bf16) p.out_bf16[at + i] = (uint16_t)bf16_bits_rne(v);
-            }
-        }
-      } else if (vec && n < p.n) {
-        *reinterpret_cast<floatx4*>(y + at) = acc[f][t];
-      } else {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (n + i < p.n) y[at + i] = acc[f][t][i];
+  for (int j = 0; j < steps_ahead(NF); ++j) w.load(first + 32 * j, j);
+  if constexpr (KIND == PLAIN) {
+    strip_products<MT, NF, KIND>(p, w, p.m, nullptr, smem, e);
+  } else {
+    // The rows that chose expert e, in order.  Every wave makes the whole list (the same one) for itself: its LDS
+    // operations complete in order, so no barrier is needed before it reads its own entries.
+    int* list = reinterpret_cast<int*>(smem);
+    int m = 0;
+    for (int i0 = 0; i0 < p.m; i0 += 64) {
+      const int row = i0 + lane;
+      const bool mine = row < p.m && (p.sel[2 * row] == e || p.sel[2 * row + 1] == e);
+      const unsigned long long v = __ballot(mine);
+      if (mine) list[m + __popcll(v & ((1ull << lane) - 1ull))] = row;
+      m += __popcll(v);
+    }
+    if (m == 0) return;  // nobody chose it (the whole workgroup: nobody waits at a later barrier)
+    unsigned char* xbuf = smem + kListBytes;
+    if constexpr (MT <= 2) {
+      strip_products<MT, NF, KIND>(p, w, m, list, xbuf, e);
+    } else {
+      // The loop for just as many 16-row blocks as there are: conditions inside one loop for the most keep its loads and
+      // products apart (75 rows, two experts of 4992 x 11136: 223 us for the call, 194 like this).
+      auto run = [&](auto t) {
+        constexpr int T = decltype(t)::value;
+        if constexpr (T <= MT) strip_products<T, NF, KIND>(p, w, m, list, xbuf, e);
+      };
+      switch ((m + 15) / 16) {
+        case 1:
+        case 2: run(std::integral_constant<int, 2>()); break;
+        case 3: run(std::integral_constant<int, 3>()); break;
+        case 4: run(std::integral_constant<int, 4>()); break;
+        case 5: run(std::integral_constant<int, 5>()); break;
+        case 6: run(std::integral_constant<int, 6>()); break;
+        default: run(std::integral_constant<int, 8>()); break;
       }
     }
   }
 }
 
-template <int MT, int KC, Kind KIND>
+template <int MT, int NF, Kind KIND>
 hipError_t launch(const StreamGemmArgs& p, hipStream_t stream) {
-  using C = Cfg<MT, KC, KIND>;
   static LdsLimitRaised raised;
-  if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(stream_gemm_kernel<MT, KC, KIND>), C::SMEM, raised); e != hipSuccess)
+  // (more than half of the LDS: one workgroup per CU.  Two of them fit a CU's registers with few rows, and are put there
+  // while other CUs have none: 1 row, two of 5 experts of 5632 x 12928: 280 us for the call, 215 like this)
+  constexpr int need = Cfg<MT, NF>::SMEM + (KIND == PLAIN ? 0 : kListBytes), smem = need > 82 * 1024 ? need : 82 * 1024;
+  if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(stream_gemm_kernel<MT, NF, KIND>), smem, raised); e != hipSuccess)
     return e;
-  hipLaunchKernelGGL((stream_gemm_kernel<MT, KC, KIND>), dim3((unsigned)((p.n + C::COLS - 1) / C::COLS), (unsigned)p.batch, (unsigned)p.ksplit),
-                     dim3(kThreads), C::SMEM, stream, p);
+  constexpr int COLS = strip_rows(NF) / (KIND == PAIR ? 2 : 1);
+  hipLaunchKernelGGL((stream_gemm_kernel<MT, NF, KIND>), dim3((unsigned)((p.n + COLS - 1) / COLS), (unsigned)p.batch, (unsigned)p.ksplit),
+                     dim3(kThreads), smem, stream, p);
   return hipGetLastError();
 }
 
 }  // namespace
 
-// Parts of the k range.  A CU draws at most about 31 bytes per ns, all of them together 5 750 (their HBM share); a part
-// more costs its fp32 partial results, written and read once at about 4 000 bytes per ns.  The count with the least
-// time by this estimate (in ns), fewer parts where it is a tie; a part keeps at least 128 of k.  `batch`: products in
-// one launch that really run.
-int stream_gemm_ksplit(int m, int n, int k, int batch, bool pair) {
+// Parts of the k range.  A CU draws at most about 31 bytes per ns, all of them together 5 750 (their HBM share): a turn
+// of fewer workgroups than CUs takes as long as its workgroups alone.  A part more costs its fp32 partial results,
+// written and read once at about 4 000 bytes per ns, and the first one what `split_ns` says (another launch).  The count
+// with the least time by this estimate (in ns), fewer parts where it is a tie; a part keeps at least 128 of k.
+// `batch`: products in one launch that really run.
+int stream_gemm_ksplit(int m, int n, int k, int batch, bool pair, int split_ns) {
   const int cus = device_cu_count();
-  const int cols = pair || m <= 128 ? 128 : 256;
-  const double strips = (double)((n + cols - 1) / cols) * batch;
-  const double weights = 2.0 * n * k * batch * (pair ? 2 : 1);
+  const double rows = strip_rows(m <= 128 ? 1 : 2), out = (double)n * (pair ? 2 : 1);
   const int units = k / 128, top = units < 64 ? units : 64;
   double best_t = 0.0;
   int best = 1;
   for (int s = 1; s <= top; ++s) {
-    const double part_k = 128.0 * ((units + s - 1) / s);
-    const double turns = (double)(((long long)strips * s + cus - 1) / cus);
-    const double cu_t = turns * 2.0 * cols * (pair ? 2 : 1) * part_k / 31.0, hbm_t = weights / 5750.0;
-    const double parts_t = s > 1 ? 2.0 * 4.0 * s * m * (double)n * batch * (pair ? 2 : 1) / 4000.0 : 0.0;
-    const double t = (cu_t > hbm_t ? cu_t : hbm_t) + parts_t;
+    const double bytes = 2.0 * rows * 128.0 * ((units + s - 1) / s), alone = bytes / 31.0;
+    const long long all = (long long)std::ceil(out / rows) * batch * s, full = all / cus, rest = all % cus;
+    auto turn = [&](double wgs) { return 1500.0 + (alone > bytes * wgs / 5750.0 ? alone : bytes * wgs / 5750.0); };
+    const double parts_t = s > 1 ? split_ns + 2.0 * 4.0 * s * m * out * batch / 4000.0 : 0.0;
+    const double t = (double)full * turn(cus) + (rest ? turn((double)rest) : 0.0) + parts_t;
     if (s == 1 || t < 0.98 * best_t) {
       best_t = t;
       best = s;
@@ -296,50 +377,76 @@ int stream_gemm_ksplit(int m, int n, int k, int batch, bool pair) {
   return best;
 }
 
+namespace {
+// Columns of a strip / 128 where a workgroup has the whole k range.  Wide strips start less often (about 2 us a turn of
+// workgroups), narrow ones fill the last turn better.  (m = 112, 127835 x 1408: 115 us in strips of 128, 104 in strips of
+// 256; 142, 74527 x 5888: 335 and 265 in strips of 256 and 384; 80, 128256 x 4096: 204 and 207 in strips of 128 and 256.)
+// More than 128 rows leave no LDS for strips of 128, more than 160 no registers for strips of 384.
+int strip_width(int n, int k, int narrowest, int widest) {
+  double best_t = 0.0;
+  int best = narrowest;
+  for (int nf = narrowest; nf <= widest; ++nf) {
+    const int strips = (n + 128 * nf - 1) / (128 * nf), turns = (strips + device_cu_count() - 1) / device_cu_count();
+    const double cu_t = turns * 2.0 * k * 128.0 * nf / 31.0, hbm_t = 2.0 * n * k / 5750.0;
+    const double t = (cu_t > hbm_t ? cu_t : hbm_t) + 2000.0 * turns;
+    if (nf == narrowest || t < 0.97 * best_t) {
+      best_t = t;
+      best = nf;
+    }
+  }
+  return best;
+}
+
+template <int MT>
+hipError_t launch_plain(const StreamGemmArgs& p, hipStream_t stream) {
+  if constexpr (MT <= 8) {
+    return p.ksplit == 1 && strip_width(p.n, p.k, 1, 2) == 2 ? launch<MT, 2, PLAIN>(p, stream) : launch<MT, 1, PLAIN>(p, stream);
+  } else if constexpr (MT <= 10) {
+    return p.ksplit == 1 && strip_width(p.n, p.k, 2, 3) == 3 ? launch<MT, 3, PLAIN>(p, stream) : launch<MT, 2, PLAIN>(p, stream);
+  } else {
+    return launch<MT, 2, PLAIN>(p, stream);
+  }
+}
+}  // namespace
+
 hipError_t launch_stream_gemm(const StreamGemmArgs& p, hipStream_t stream) {
   switch ((p.m + 15) / 16) {
-    case 1: return launch<1, 256, PLAIN>(p, stream);
-    case 2: return launch<2, 256, PLAIN>(p, stream);
-    case 3: return launch<3, 256, PLAIN>(p, stream);
-    case 4: return launch<4, 256, PLAIN>(p, stream);
-    case 5: return launch<5, 256, PLAIN>(p, stream);
-    case 6: return launch<6, 256, PLAIN>(p, stream);
+    case 1: return launch_plain<1>(p, stream);
+    case 2: return launch_plain<2>(p, stream);
+    case 3: return launch_plain<3>(p, stream);
+    case 4: return launch_plain<4>(p, stream);
+    case 5: return launch_plain<5>(p, stream);
+    case 6: return launch_plain<6>(p, stream);
     case 7:
-    case 8: return launch<8, 256, PLAIN>(p, stream);
+    case 8: return launch_plain<8>(p, stream);
     case 9:
-    case 10: return launch<10, 128, PLAIN>(p, stream);
+    case 10: return launch_plain<10>(p, stream);
     case 11:
-    case 12: return launch<12, 128, PLAIN>(p, stream);
+    case 12: return launch_plain<12>(p, stream);
     case 13: case 14: case 15:
-    case 16: return launch<16, 128, PLAIN>(p, stream);
+    case 16: return launch_plain<16>(p, stream);
     default: return hipErrorInvalidValue;
   }
 }
-hipError_t launch_stream_gemm_pair(const StreamGemmArgs& p, hipStream_t stream) {
+namespace {
+// (an expert may have been chosen by every row)
+template <Kind KIND>
+hipError_t launch_experts(const StreamGemmArgs& p, hipStream_t stream) {
   switch ((p.m + 15) / 16) {
-    case 1: return launch<1, 256, PAIR>(p, stream);
-    case 2: return launch<2, 256, PAIR>(p, stream);
-    case 3: return launch<3, 256, PAIR>(p, stream);
-    case 4: return launch<4, 256, PAIR>(p, stream);
+    case 1: return launch<1, 1, KIND>(p, stream);
+    case 2: return launch<2, 1, KIND>(p, stream);
+    case 3:
+    case 4: return launch<4, 1, KIND>(p, stream);
     case 5:
-    case 6: return launch<6, 256, PAIR>(p, stream);
+    case 6: return launch<6, 1, KIND>(p, stream);
     case 7:
-    case 8: return launch<8, 128, PAIR>(p, stream);
+    case 8: return launch<8, 1, KIND>(p, stream);
     default: return hipErrorInvalidValue;
   }
 }
-hipError_t launch_stream_gemm_down(const StreamGemmArgs& p, hipStream_t stream) {
-  switch ((p.m + 15) / 16) {
-    case 1: return launch<1, 256, DOWN>(p, stream);
-    case 2: return launch<2, 256, DOWN>(p, stream);
-    case 3: return launch<3, 256, DOWN>(p, stream);
-    case 4: return launch<4, 256, DOWN>(p, stream);
-    case 5:
-    case 6: return launch<6, 256, DOWN>(p, stream);
-    case 7:
-    case 8: return launch<8, 256, DOWN>(p, stream);
-    default: return hipErrorInvalidValue;
-  }
-}
+}  // namespace
+
+hipError_t launch_stream_gemm_pair(const StreamGemmArgs& p, hipStream_t stream) { return launch_experts<PAIR>(p, stream); }
+hipError_t launch_stream_gemm_down(const StreamGemmArgs& p, hipStream_t stream) { return launch_experts<DOWN>(p, stream); }
 
 }  // namespace jk

@@ -31,6 +31,17 @@ def test_exact_arithmetic_inputs_are_bit_exact(m, n, k):
     np.testing.assert_array_equal(got, round_to_bf16(dh.linear(x, w, r).astype(np.float32)))
 
 
+@pytest.mark.parametrize("m,n,k", [(20, 40001, 128), (128, 33000, 384), (130, 70001, 128), (160, 70016, 384)])
+def test_wide_strips_are_bit_exact(m, n, k):
+    """Outputs so wide that strips of 256 or 384 columns save a turn of workgroups: whole and ragged last strips, rows
+    stored in one and in several groups, half chunks of k."""
+    rng = np.random.default_rng(n)
+    x = rng.integers(-2, 3, size=(m, k)).astype(np.float32)
+    w = (rng.integers(-1, 2, size=(n, k)) * 0.125).astype(np.float32)
+    got = jk.linear(_bf(x), _bf(w), out_dtype=torch.float32).cpu().numpy()
+    np.testing.assert_array_equal(got.astype(np.float64), dh.linear(x, w))
+
+
 def test_random_inputs_within_fp32_accumulation_error():
     rng = np.random.default_rng(1)
     m, n, k = 40, 2000, 2048
