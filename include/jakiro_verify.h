@@ -121,7 +121,7 @@ size_t jk_tree_verify_attention_workspace(const jk_attn_desc* desc, int32_t max_
  *
  * Supported: JK_BF16 with head_dim 64 or 128 (MFMA path), JK_F32 with
  * head_dim <= 256 and a multiple of 4 and max_prefix_len + n_tree <= 65536
- * (plain-ALU path); 1 <= n_tree <= JK_MAX_TREE;
+ * (fp32 MFMA path); 1 <= n_tree <= JK_MAX_TREE;
  * n_q_heads a multiple of n_kv_heads; JK_BF16: kc_stride_l and kt_stride_t at
  * most 2^24 elements (JK_ERR_UNSUPPORTED beyond).  Value rows of tree nodes that a query
  * cannot see must be finite (they are multiplied by an exact zero); their key

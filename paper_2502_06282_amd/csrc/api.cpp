@@ -220,6 +220,7 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
       }
     }
     if (!have) return false;
+    pl->parts = pl->splits;
     pl->m_pad = pl->n_qtiles * pl->q_rows;
     // (the kernel ranks a batch with a lane per sequence, and the XCDs get whole units)
     pl->ranked = d.batch >= 2 && d.batch <= 64 && units % 8 == 0 ? 1 : 0;
@@ -232,13 +233,23 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
     pl->n_qtiles = pl->m_rows;
     pl->m_pad = pl->m_rows;
     const long long keys = (long long)max_prefix_len + d.n_tree;
-    long long s = (keys + 1023) / 1024;  // each fp32 workgroup holds at most 1024 scores
+    long long s = (keys + 1023) / 1024;  // ranges of 1024 keys, for 16 query rows a workgroup
     if (s > kMaxSplits) return false;  // fp32 path: at most 64 * 1024 keys
     pl->splits = (int)s;
+    // Few workgroups: each range in up to eight parts, where the merging launch (3 us) is needed anyway or costs less than
+    // what the parts save (20 nodes, 8 heads of 128: 420 keys 18.0 us whole, 13.3 in parts; 138 keys of 64 8.0 and 9.8).
+    const long long wgs = units * ((pl->m_rows + 15) / 16) * s;
+    pl->parts = pl->splits;
+    if (s > 1 || keys >= 256)
+      for (int sub = 8; sub > 1; --sub)
+        if (wgs * sub <= device_cu_count() && s * sub <= kMaxSplits) {
+          pl->parts = pl->splits * sub;
+          break;
+        }
   }
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
-  const size_t rows = (size_t)units * pl->splits * pl->m_pad;
-  const bool need_parts = (d.dtype == JK_F32) || pl->splits > 1;
+  const size_t rows = (size_t)units * pl->parts * pl->m_pad;
+  const bool need_parts = pl->parts > 1;
   pl->part_o_bytes = need_parts ? up(rows * d.head_dim * (d.dtype == JK_BF16 ? 2 : sizeof(float))) : 0;
   pl->part_ml_bytes = need_parts ? up(rows * sizeof(float2)) : 0;
   pl->total_bytes = kAttnHeaderBytes + pl->part_o_bytes + pl->part_ml_bytes;
@@ -362,7 +373,7 @@ static jk_status attention_common(const jk_attn_desc* desc, const jk_paged_kv* p
   } else {
     a.scale_log2 = scale;  // the fp32 path works in natural units
     e = launch_tva_f32(a, pl, stream);
-    if (e == hipSuccess) e = launch_tva_combine(a, pl, stream);
+    if (e == hipSuccess && pl.parts > 1) e = launch_tva_combine(a, pl, stream);
   }
   return e == hipSuccess ? JK_OK : JK_ERR_HIP;
 }

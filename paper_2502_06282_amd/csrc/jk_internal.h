@@ -43,6 +43,7 @@ struct AttnPlan {
   int m_rows;      // T * G query rows per KV head
   int m_pad;       // n_qtiles * q_rows
   int splits;      // KV splits
+  int parts;       // partial results per row: the splits, or (fp32) parts of them
   int fused;       // bf16 path: the splits are merged inside the attention kernel (no second launch)
   int ranked;      // bf16 path: sequences taken by falling length, dealt to the XCDs in turn
   int deep;        // bf16 path, 2x2 waves: the six-tile K/V ring (one workgroup per CU, two rounds in flight)

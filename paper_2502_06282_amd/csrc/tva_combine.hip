@@ -234,7 +234,7 @@ hipError_t launch_tva_combine(const AttnArgs& a, const AttnPlan& pl, hipStream_t
   cp.out = a.out;
   const jk_attn_desc& d = a.d;
   cp.B = d.batch; cp.Hkv = d.n_kv_heads; cp.G = d.n_q_heads / d.n_kv_heads;
-  cp.M = pl.m_rows; cp.m_pad = pl.m_pad; cp.D = d.head_dim; cp.splits = pl.splits;
+  cp.M = pl.m_rows; cp.m_pad = pl.m_pad; cp.D = d.head_dim; cp.splits = pl.parts;
   cp.o_sb = d.o_stride_b; cp.o_st = d.o_stride_t; cp.o_sh = d.o_stride_h;
   auto magic = [](int v) { return (1ull << 32) / (unsigned long long)v + 1ull; };
   cp.mg_hkv = magic(cp.Hkv);

@@ -1,156 +1,244 @@
-// Tree-masked verification attention, fp32 inputs, plain-ALU path.
+// Tree-masked verification attention, fp32 inputs.
 //
-// Same definition as the bf16 kernel (Section 2.1 step 2; Section 3.1.2 tree
-// mask), kept in fp32 end to end for small, accuracy-critical shapes: one
-// workgroup per (sequence, query row, key split) computes the scores of its
-// keys, a two-pass softmax over them (max, then exp and sum) and the weighted
-// value sum, and writes one partial (max, sum, unnormalised output) that the
-// combine kernel merges.
+// Same definition as the bf16 kernel (Section 2.1 step 2; Section 3.1.2 tree mask), fp32 end to end for accuracy-critical
+// shapes.  One workgroup per (sequence, KV head, 16 query rows, key split); its waves take blocks of 16 keys in turn, keep
+// a running maximum and sum per row, and meet once at the end, in LDS.
+//
+// What bounds it: for small calls one trip to memory after the other, so a wave has a block's K and V in flight at once and
+// the next block's K behind them, and the first block's K is asked for before the prefix length is known; for large ones
+// the products, which run on v_mfma_f32_16x16x4_f32 (full fp32) with K and V straight from L2 in operand layout, each
+// read once for 16 rows.  S^T = K Q^T leaves a lane with four keys of one row: exactly what the second product,
+// O^T = V^T P^T, takes as its operand, so the weights never leave their registers.  An undivided key range needs no second
+// launch.  With one workgroup per query row, a thread per key and column, 4 heads of 64, 10 nodes and 138 keys took
+// 16.9 us (the second launch included), 8.0 like this; 4 sequences, 8 heads of 128, 52 nodes, 2100 keys 481 and 57.
 #include "jk_internal.h"
+#include "jk_wave.h"
 
 namespace jk {
 namespace {
 
-constexpr int kF32Chunk = 1024;  // keys per workgroup
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 struct FParams {
   const float *q, *kc, *vc, *kt, *vt;
   const int32_t *parent, *prefix_len;
   float* part_o;
   float2* part_ml;
+  float* out;     // undivided key range: the result
   unsigned* err;  // the workspace's sticky device error word
   int B, T, Hkv, G, M, m_pad, D, max_prefix, splits;
-  long long q_sb, q_st, q_sh, kc_sb, kc_sl, kc_sh, kt_sb, kt_st, kt_sh;
+  long long q_sb, q_st, q_sh, kc_sb, kc_sl, kc_sh, kt_sb, kt_st, kt_sh, o_sb, o_st, o_sh;
   float scale;
 };
 
-__device__ float block_reduce_max(float v, float* red) {
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  float r = red[0];
-  for (int w = 1; w < 4; ++w) r = fmaxf(r, red[w]);
-  __syncthreads();
-  return r;
-}
-__device__ float block_reduce_sum(float v, float* red) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  float r = red[0] + red[1] + red[2] + red[3];
-  __syncthreads();
-  return r;
-}
-
-__global__ __launch_bounds__(256) void tva_f32_kernel(FParams p) {
-  __shared__ float qs[256];
-  __shared__ float sc[kF32Chunk];
-  __shared__ float red[4];
-  __shared__ float osum[256];
-  __shared__ int par_s[JK_MAX_TREE];
-  __shared__ unsigned long long anc_me[2];
-
-  const int tid = threadIdx.x;
-  const int split = blockIdx.x;
-  const int m = blockIdx.y;
-  const int kv = blockIdx.z % p.Hkv;
-  const int b = blockIdx.z / p.Hkv;
-  const int node = m / p.G, hg = m % p.G;
-  const int D = p.D;
-
-  int L = p.prefix_len[b];
-  L = L < 0 ? 0 : (L > p.max_prefix ? p.max_prefix : L);
-  const int ktot = L + p.T;
-  const int k_begin = (int)((long long)split * ktot / p.splits);
-  const int k_end = (int)((long long)(split + 1) * ktot / p.splits);
-
-  if (tid < p.T) {
-    int pa = p.parent[(long long)b * p.T + tid];
-    const bool ok = pa >= -1 && pa < tid;
-    par_s[tid] = ok ? pa : -1;
-    if (!ok && split == 0 && m == 0 && kv == 0)  // reported once per sequence
-      __hip_atomic_fetch_or(p.err, kDevErrBadTree, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  if (tid < D) qs[tid] = p.q[b * p.q_sb + node * p.q_st + (long long)(kv * p.G + hg) * p.q_sh + tid];
-  __syncthreads();
-  if (tid == 0) {
-    unsigned long long lo = 0, hi = 0;
-    int a = node;
-    while (a >= 0) {
-      if (a < 64) lo |= 1ull << a; else hi |= 1ull << (a - 64);
-      a = par_s[a];
+// Ancestor sets (with the node itself) of all nodes, by one wave: sets and pointers double their reach every round.
+__device__ __forceinline__ void ancestor_sets(const FParams& p, int b, bool report, unsigned long long (*anc)[2], int* up) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int n = lane + 64 * h;
+    if (n < p.T) {
+      const int pa = p.parent[(long long)b * p.T + n];
+      const bool ok = pa >= -1 && pa < n;
+      up[n] = ok ? pa : -1;
+      anc[n][0] = h == 0 ? 1ull << lane : 0ull;
+      anc[n][1] = h == 1 ? 1ull << lane : 0ull;
+      if (!ok && report) __hip_atomic_fetch_or(p.err, kDevErrBadTree, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    anc_me[0] = lo;
-    anc_me[1] = hi;
   }
-  __syncthreads();
+  for (;;) {
+    asm volatile("" ::: "memory");  // (the LDS operations of a wave complete in order)
+    unsigned long long lo[2] = {0ull, 0ull}, hi[2] = {0ull, 0ull};
+    int next[2] = {-1, -1};
+    bool more[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int n = lane + 64 * h, a = n < p.T ? up[n] : -1;
+      more[h] = a >= 0;
+      if (more[h]) {
+        lo[h] = anc[a][0];
+        hi[h] = anc[a][1];
+        next[h] = up[a];
+      }
+    }
+    if (!__any(more[0] || more[1])) return;
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      if (more[h]) {
+        anc[lane + 64 * h][0] |= lo[h];
+        anc[lane + 64 * h][1] |= hi[h];
+        up[lane + 64 * h] = next[h];
+      }
+  }
+}
 
+// KJ: 16-column chunks of a head (rounded up); WAVES: by how many registers that leaves
+template <int KJ>
+constexpr int waves_for() { return KJ <= 8 ? 8 : 4; }
+
+template <int KJ>
+__global__ __launch_bounds__(64 * waves_for<KJ>(), KJ <= 8 ? 2 : 1) void tva_f32_kernel(FParams p) {
+  constexpr int WAVES = waves_for<KJ>(), DB = (KJ + 3) / 4, LDO = 64 * DB + 4;
+  __shared__ unsigned long long anc[JK_MAX_TREE][2];
+  __shared__ int up[JK_MAX_TREE];
+  __shared__ float2 ml[WAVES][16];
+  extern __shared__ __attribute__((aligned(16))) float osum[];  // [WAVES][16][LDO]
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, g = lane >> 4;
+  const int split = blockIdx.x, row0 = blockIdx.y * 16;
+  const int kv = blockIdx.z % p.Hkv, b = blockIdx.z / p.Hkv;
+  const int D = p.D;
   const float* kc = p.kc + b * p.kc_sb + (long long)kv * p.kc_sh;
   const float* vc = p.vc + b * p.kc_sb + (long long)kv * p.kc_sh;
   const float* kt = p.kt + b * p.kt_sb + (long long)kv * p.kt_sh;
   const float* vt = p.vt + b * p.kt_sb + (long long)kv * p.kt_sh;
 
-  // the host guarantees k_end - k_begin <= kF32Chunk
-  float lmax = -INFINITY;
-  for (int j = k_begin + tid; j < k_end; j += 256) {
-    float s;
-    bool vis = true;
-    const float* krow;
-    if (j < L) {
-      krow = kc + (long long)j * p.kc_sl;
-    } else {
-      const int tj = j - L;
-      vis = (anc_me[tj >> 6] >> (tj & 63)) & 1ull;
-      krow = kt + (long long)tj * p.kt_st;
+  int L = p.prefix_len[b];
+  const int m = min(row0 + c, p.M - 1), node = m / p.G;  // this lane's query row (rows past the end repeat the last one)
+  floatx4 q[KJ], k[KJ];
+  // column 16 j + 4 g of a row; columns past the end: the row's first ones, against zeros of q
+  auto col = [&](int j) { return 16 * j + 4 * g < D ? 16 * j + 4 * g : 0; };
+  auto load_k = [&](const float* row) {
+#pragma unroll
+    for (int j = 0; j < KJ; ++j) k[j] = *reinterpret_cast<const floatx4*>(row + col(j));
+  };
+  if (split == 0 && p.max_prefix > 0) load_k(kc + (long long)min(16 * wave + c, p.max_prefix - 1) * p.kc_sl);
+  {
+    const float* src = p.q + b * p.q_sb + node * p.q_st + (long long)(kv * p.G + m - node * p.G) * p.q_sh;
+#pragma unroll
+    for (int j = 0; j < KJ; ++j) {
+      q[j] = *reinterpret_cast<const floatx4*>(src + col(j));
+      if (16 * j + 4 * g >= D) q[j] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
-    if (vis) {
-      float acc = 0.f;
-      for (int d = 0; d < D; d += 4) {
-        const float4 kk = *reinterpret_cast<const float4*>(krow + d);
-        acc = fmaf(qs[d], kk.x, acc);
-        acc = fmaf(qs[d + 1], kk.y, acc);
-        acc = fmaf(qs[d + 2], kk.z, acc);
-        acc = fmaf(qs[d + 3], kk.w, acc);
-      }
-      s = acc * p.scale;
-    } else {
-      s = -INFINITY;
-    }
-    sc[j - k_begin] = s;
-    lmax = fmaxf(lmax, s);
   }
-  const float mx = block_reduce_max(lmax, red);
-  const float mx_use = (mx == -INFINITY) ? 0.f : mx;
-  float lsum = 0.f;
-  for (int j = k_begin + tid; j < k_end; j += 256) {
-    const float e = expf(sc[j - k_begin] - mx_use);
-    sc[j - k_begin] = e;
-    lsum += e;
-  }
-  const float tot = block_reduce_sum(lsum, red);  // also orders the sc[] writes
+  if (wave == WAVES - 1) ancestor_sets(p, b, split == 0 && row0 == 0 && kv == 0, anc, up);
+  L = L < 0 ? 0 : (L > p.max_prefix ? p.max_prefix : L);
+  const int ktot = L + p.T;
+  const int k_begin = (int)((long long)split * ktot / p.splits), k_end = (int)((long long)(split + 1) * ktot / p.splits);
+  const int p_end = min(k_end, L), t_begin = max(k_begin, L);
+  const int n_prefix = p_end > k_begin ? (p_end - k_begin + 15) / 16 : 0, n_tree = k_end > t_begin ? (k_end - t_begin + 15) / 16 : 0;
 
-  // weighted value sum: thread (kg, d) adds every ngroups-th key for output column d
-  const int ngroups = 256 / D;  // >= 1 because D <= 256
-  const int d = tid % D, kg = tid / D;
-  float acc = 0.f;
-  if (kg < ngroups) {
-    for (int j = k_begin + kg; j < k_end; j += ngroups) {
-      const float w = sc[j - k_begin];
-      if (w != 0.f) {  // skips masked tree rows entirely
-        const float* vrow = (j < L) ? vc + (long long)j * p.kc_sl : vt + (long long)(j - L) * p.kt_st;
-        acc = fmaf(w, vrow[d], acc);
-      }
+  floatx4 o[DB][4];
+#pragma unroll
+  for (int d = 0; d < DB; ++d)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[d][i] = floatx4{0.f, 0.f, 0.f, 0.f};
+  float mx = -INFINITY, sum = 0.f;
+  // 16 keys: `v_row(i)` is where key 4 g + i has its values, visible(i) whether this lane's row sees it; `next` asks for
+  // the K of the block behind this one as soon as this one's is used
+  auto block = [&](auto v_row, auto visible, auto next) {
+    floatx4 v[DB][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float* row = v_row(i);
+#pragma unroll
+      for (int d = 0; d < DB; ++d) v[d][i] = *reinterpret_cast<const floatx4*>(row + (64 * d + 4 * c < D ? 64 * d + 4 * c : 0));
+    }
+    floatx4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < KJ; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_mfma_f32_16x16x4f32(k[j][i], q[j][i], s, 0, 0, 0);
+    next();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s[i] = visible(i) ? s[i] * p.scale : -INFINITY;
+    float top = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+    top = fmaxf(top, __uint_as_float(dev::other16(__float_as_uint(top), lane & 16)));
+    top = fmaxf(top, __uint_as_float(dev::other32(__float_as_uint(top), lane & 32)));
+    const float mn = fmaxf(mx, top), base = mn == -INFINITY ? 0.f : mn;
+    if (__any(mn > mx)) {
+      const float f = expf(mx - base);
+      sum *= f;
+#pragma unroll
+      for (int d = 0; d < DB; ++d)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[d][i] *= f;
+      mx = mn;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      s[i] = expf(s[i] - base);
+      sum += s[i];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int d = 0; d < DB; ++d)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[d][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[d][i][e], s[i], o[d][e], 0, 0, 0);
+  };
+  auto prefix_k = [&](int blk) { load_k(kc + (long long)min(k_begin + 16 * blk + c, p_end - 1) * p.kc_sl); };
+  if (split != 0 && wave < n_prefix) prefix_k(wave);
+  for (int blk = wave; blk < n_prefix; blk += WAVES) {
+    const int key0 = k_begin + 16 * blk + 4 * g;
+    block([&](int i) { return vc + (long long)min(key0 + i, p_end - 1) * p.kc_sl; }, [&](int i) { return key0 + i < p_end; },
+          [&]() {
+            if (blk + WAVES < n_prefix) prefix_k(blk + WAVES);
+          });
+  }
+  __syncthreads();  // the ancestor sets are there
+  const unsigned long long lo = anc[node][0], hi = anc[node][1];
+  for (int blk = (wave + WAVES - n_prefix % WAVES) % WAVES; blk < n_tree; blk += WAVES) {  // (the waves with fewer blocks first)
+    const int key0 = t_begin - L + 16 * blk, last = k_end - L - 1;
+    load_k(kt + (long long)min(key0 + c, last) * p.kt_st);
+    block([&](int i) { return vt + (long long)min(key0 + 4 * g + i, last) * p.kt_st; },
+          [&](int i) {
+            const int t = key0 + 4 * g + i;
+            return t <= last && (((t < 64 ? lo : hi) >> (t & 63)) & 1ull);
+          },
+          []() {});
+  }
+
+  // ---- the waves' shares of a row meet
+  sum += __uint_as_float(dev::other16(__float_as_uint(sum), lane & 16));
+  sum += __uint_as_float(dev::other32(__float_as_uint(sum), lane & 32));
+  if (g == 0) ml[wave][c] = make_float2(mx, sum);
+  __syncthreads();
+  float all = -INFINITY;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) all = fmaxf(all, ml[w][c].x);
+  const float f = mx == -INFINITY ? 0.f : expf(mx - all);
+  float* mine = osum + (wave * 16 + c) * LDO + 16 * g;  // (a lane has 16 columns of its row in each 64)
+#pragma unroll
+  for (int d = 0; d < DB; ++d)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      *reinterpret_cast<floatx4*>(mine + 64 * d + 4 * r) = floatx4{o[d][0][r] * f, o[d][1][r] * f, o[d][2][r] * f, o[d][3][r] * f};
+  __syncthreads();
+  const int d4 = D / 4;
+  for (int i = tid; i < 16 * d4; i += 64 * WAVES) {
+    const int r = i / d4, x = i % d4 * 4, row = row0 + r;
+    if (row >= p.M) break;
+    floatx4 t = {0.f, 0.f, 0.f, 0.f};
+    float top = -INFINITY, tot = 0.f;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+      t += *reinterpret_cast<const floatx4*>(osum + (w * 16 + r) * LDO + x);
+      top = fmaxf(top, ml[w][r].x);
+    }
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) tot += ml[w][r].x == -INFINITY ? 0.f : ml[w][r].y * expf(ml[w][r].x - top);
+    if (p.splits == 1) {
+      const int n = row / p.G;
+      float* dst = p.out + b * p.o_sb + n * p.o_st + (long long)(kv * p.G + row - n * p.G) * p.o_sh;
+      const float inv = 1.f / tot;  // (tot > 0: every row sees at least its own tree key)
+      *reinterpret_cast<floatx4*>(dst + x) = floatx4{t[0] * inv, t[1] * inv, t[2] * inv, t[3] * inv};
+    } else {
+      const long long prow = ((long long)(b * p.Hkv + kv) * p.splits + split) * p.m_pad + row;
+      *reinterpret_cast<floatx4*>(p.part_o + prow * D + x) = t;
+      if (x == 0) p.part_ml[prow] = make_float2(top, tot);
     }
   }
-  osum[tid] = acc;
-  __syncthreads();
-  if (tid < D) {
-    float o = 0.f;
-    for (int g2 = 0; g2 < ngroups; ++g2) o += osum[g2 * D + tid];
-    const long long prow = ((long long)(b * p.Hkv + kv) * p.splits + split) * p.m_pad + m;
-    p.part_o[prow * D + tid] = o;
-    if (tid == 0) p.part_ml[prow] = make_float2(mx, tot);
-  }
+}
+
+template <int KJ>
+hipError_t launch_kj(const FParams& fp, hipStream_t stream) {
+  constexpr int WAVES = waves_for<KJ>(), SMEM = WAVES * 16 * (64 * ((KJ + 3) / 4) + 4) * 4;
+  static LdsLimitRaised raised;
+  if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(tva_f32_kernel<KJ>), SMEM, raised); e != hipSuccess) return e;
+  hipLaunchKernelGGL(tva_f32_kernel<KJ>, dim3(fp.splits, (fp.M + 15) / 16, fp.B * fp.Hkv), dim3(64 * WAVES), SMEM, stream, fp);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -170,14 +258,22 @@ hipError_t launch_tva_f32(const AttnArgs& a, const AttnPlan& pl, hipStream_t str
   const jk_attn_desc& d = a.d;
   fp.B = d.batch; fp.T = d.n_tree; fp.Hkv = d.n_kv_heads; fp.G = d.n_q_heads / d.n_kv_heads;
   fp.M = pl.m_rows; fp.m_pad = pl.m_pad; fp.D = d.head_dim; fp.max_prefix = a.max_prefix_len;
-  fp.splits = pl.splits;
+  fp.splits = pl.parts;
   fp.q_sb = d.q_stride_b; fp.q_st = d.q_stride_t; fp.q_sh = d.q_stride_h;
   fp.kc_sb = d.kc_stride_b; fp.kc_sl = d.kc_stride_l; fp.kc_sh = d.kc_stride_h;
   fp.kt_sb = d.kt_stride_b; fp.kt_st = d.kt_stride_t; fp.kt_sh = d.kt_stride_h;
+  fp.out = static_cast<float*>(a.out);
+  fp.o_sb = d.o_stride_b; fp.o_st = d.o_stride_t; fp.o_sh = d.o_stride_h;
   fp.scale = a.scale_log2;  // for this path the host passes the plain softmax scale here
-  hipLaunchKernelGGL(tva_f32_kernel, dim3(pl.splits, pl.m_rows, d.batch * d.n_kv_heads), dim3(256), 0,
-                     stream, fp);
-  return hipGetLastError();
+  switch ((d.head_dim + 15) / 16) {
+    case 1: case 2: case 3:
+    case 4: return launch_kj<4>(fp, stream);
+    case 5: return launch_kj<5>(fp, stream);
+    case 6: return launch_kj<6>(fp, stream);
+    case 7:
+    case 8: return launch_kj<8>(fp, stream);
+    default: return launch_kj<16>(fp, stream);
+  }
 }
 
 }  // namespace jk

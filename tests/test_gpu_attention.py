@@ -32,6 +32,17 @@ def test_fp32_prefix_lengths(L):
     check_attention(attention_inputs(cfg, seed=L), par, [L], "f32", F32_TOL)
 
 
+@pytest.mark.parametrize("D,T,G,L", [(4, 1, 1, 3), (64, 17, 1, 16), (80, 64, 2, 1000), (96, 5, 4, 1019), (100, 33, 1, 1024), (128, 128, 1, 129),
+                                     (128, 6, 3, 2100), (200, 9, 2, 60), (256, 20, 4, 1500), (68, 16, 1, 0)])
+def test_fp32_head_dims_rows_and_key_ranges(D, T, G, L):
+    """Head dimensions between the kernel's variants, row tiles of 16 whole, ragged and nearly empty, one key range and
+    several, prefixes that end at, before and behind a block of 16 keys; sequences shorter than the bound."""
+    cfg = _cfg("c1_tiny", batch=3, n_q_heads=2 * G, n_kv_heads=2, head_dim=D, n_tree=T, prefix_len=L)
+    rng = np.random.default_rng(D + T)
+    par = np.stack([np.array([-1] + [int(rng.integers(max(-1, i - 9), i)) for i in range(1, T)], dtype=np.int32) for _ in range(3)])
+    check_attention(attention_inputs(cfg, seed=L + D), par, [L, max(0, L - 17), L // 3], "f32", F32_TOL)
+
+
 def test_fp32_batched_ragged_and_wide_tree():
     cfg = _cfg("c5_llama2_70b", batch=3, n_q_heads=4, n_kv_heads=2, head_dim=32, prefix_len=300, dtype="f32",
                input_scale=1.0)
