@@ -20,16 +20,54 @@ namespace jk {
 namespace {
 
 constexpr int kTreeThreads = 256;
+constexpr int kTreeWaves = kTreeThreads / 64;
 constexpr int kMaxGrowNodes = 1024;  // node capacity per sequence the kernels are laid out for
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 // larger score first, equal scores by increasing index (both operands always evaluated)
 __device__ __forceinline__ int beats(float av, int ai, float bv, int bi) {
   return (int)(av > bv) | ((int)(av == bv) & (int)(ai < bi));
 }
 
-// How many threads with a smaller index raised `flag`, and how many did in all: ballots within
-// the waves, the four wave totals through LDS (s_cnt: kTreeThreads / 64 ints; the caller's
-// later use of it must follow a barrier).
+// s_rank[i] += how many of the n entries of s_sc beat entry i; s_sc holds -inf from n to the next multiple of four (an
+// index beyond n never wins a tie), s_rank starts at zero, and a barrier on either side is the caller's.  A wave takes
+// 64 entries i and a part of the entries j that they are held against: a few entries still occupy every wave (one wave
+// for 50 candidates spent as long comparing as a trip to memory takes).  Whether j or i is lower is known for all but
+// the wave's own 64 entries, and one comparison is enough there.
+template <int kWaves>
+__device__ __forceinline__ void count_beaten(const float* s_sc, int n, int* s_rank, int t) {
+  const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int chunks = (n + 63) >> 6, parts = chunks >= kWaves ? 1 : kWaves / max(chunks, 1);
+  const int len = ((n + parts - 1) / parts + 3) & ~3;
+  for (int u = wave; u < chunks * parts; u += kWaves) {
+    const int c0 = (u / parts) * 64, p = u - (u / parts) * parts;
+    const int j0 = p * len, j1 = min(j0 + len, (n + 3) & ~3);
+    const int i = c0 + lane;
+    const float sc = s_sc[min(i, n - 1)];
+    int rank = 0, j = j0;
+#pragma unroll 4
+    for (; j < min(j1, c0); j += 4) {
+      const floatx4 v = *reinterpret_cast<const floatx4*>(s_sc + j);
+      rank += (int)(v[0] >= sc) + (int)(v[1] >= sc) + (int)(v[2] >= sc) + (int)(v[3] >= sc);
+    }
+#pragma unroll 4
+    for (; j < min(j1, c0 + 64); j += 4) {
+      const floatx4 v = *reinterpret_cast<const floatx4*>(s_sc + j);
+      rank += beats(v[0], j, sc, i) + beats(v[1], j + 1, sc, i) + beats(v[2], j + 2, sc, i) + beats(v[3], j + 3, sc, i);
+    }
+#pragma unroll 4
+    for (; j < j1; j += 4) {
+      const floatx4 v = *reinterpret_cast<const floatx4*>(s_sc + j);
+      rank += (int)(v[0] > sc) + (int)(v[1] > sc) + (int)(v[2] > sc) + (int)(v[3] > sc);
+    }
+    if (i < n) atomicAdd(&s_rank[i], rank);
+  }
+}
+
+// How many threads with a smaller index raised `flag`, and how many did in all: ballots within the waves, the waves'
+// totals through LDS (s_cnt: kWaves ints; the caller's later use of it must follow a barrier).
+template <int kWaves>
 __device__ __forceinline__ int count_before(bool flag, int t, int* s_cnt, int& total) {
   const unsigned long long m = __ballot(flag);
   const int lane = t & 63, wave = t >> 6;
@@ -39,7 +77,7 @@ __device__ __forceinline__ int count_before(bool flag, int t, int* s_cnt, int& t
   int before = in_wave;
   total = 0;
 #pragma unroll
-  for (int w = 0; w < kTreeThreads / 64; ++w) {
+  for (int w = 0; w < kWaves; ++w) {
     const int c = s_cnt[w];
     before += w < wave ? c : 0;
     total += c;
@@ -47,38 +85,45 @@ __device__ __forceinline__ int count_before(bool flag, int t, int* s_cnt, int& t
   return before;
 }
 
+// Bound by latency: a few hundred bytes per sequence, so what counts is how many trips to memory follow each other.
+// The candidate, its token, the frontier entry and the node count are asked for together; only the parent's score
+// depends on one of them.  @GROW@
 __global__ __launch_bounds__(kTreeThreads) void grow_kernel(TreeGrowArgs a) {
-  __shared__ float s_sc[kTreeThreads];
-  __shared__ int s_cnt[kTreeThreads / 64];
+  __shared__ __align__(16) float s_sc[kTreeThreads];
+  __shared__ int s_rank[kTreeThreads];
+  __shared__ int s_cnt[kTreeWaves];
   __shared__ int s_first;
   const int b = blockIdx.x, t = threadIdx.x;
   const int C = a.n_front * 2 * a.top_k;  // <= kTreeThreads (checked by the host)
+  const int f = min(t / (2 * a.top_k), a.n_front - 1), e = (t / a.top_k) & 1;
+  const long long row = (long long)b * a.n_front + f, at_c = (long long)b * C + min(t, C - 1);
+  const float p = a.cand_p[at_c];
+  const int tok = a.cand_tok[at_c];
+  const int pid = a.frontier_in ? a.frontier_in[row] : -1;
   const int n0 = min(max(a.n_nodes[b], 0), a.max_nodes);  // (a count the caller forgot to clear must not fault)
+  const bool has_parent = pid >= 0 && pid < a.max_nodes;
+  const float parent_score = has_parent ? a.score[(long long)b * a.max_nodes + pid] : 1.0f;
   const int id = n0 + t;
   const bool valid = t < C && id < a.max_nodes;
   float sc = -INFINITY;
   if (valid) {
-    const int f = t / (2 * a.top_k), e = (t / a.top_k) & 1;
-    const long long row = (long long)b * a.n_front + f;
-    const int pid = a.frontier_in ? a.frontier_in[row] : -1;
-    const bool has_parent = pid >= 0 && pid < n0;
-    const float ps = has_parent ? a.score[(long long)b * a.max_nodes + pid] : 1.0f;
-    sc = ps * a.cand_p[row * 2 * a.top_k + (t - f * 2 * a.top_k)];
+    const bool old = has_parent && pid < n0;
+    sc = (old ? parent_score : 1.0f) * p;
     const long long at = (long long)b * a.max_nodes + id;
-    a.tokens[at] = a.cand_tok[row * 2 * a.top_k + (t - f * 2 * a.top_k)];
-    a.parent[at] = has_parent ? pid : -1;
+    a.tokens[at] = tok;
+    a.parent[at] = old ? pid : -1;
     a.score[at] = sc;
     a.q_row[at] = a.q_row_base + (int)(2 * row) + e;
   }
-  s_sc[t] = sc;
+  s_sc[t] = sc;  // (entries from C on hold -inf and a larger index: they beat nobody)
+  s_rank[t] = 0;
   if (t == 0) s_first = INT_MAX;
   __syncthreads();
-  int rank = 0;  // (entries from C on hold -inf and a larger index: they beat nobody)
-#pragma unroll 8
-  for (int i = 0; i < C; ++i) rank += beats(s_sc[i], i, sc, t);
-  const bool sel = valid && rank < a.width;
+  count_beaten<kTreeWaves>(s_sc, C, s_rank, t);
+  __syncthreads();
+  const bool sel = valid && s_rank[t] < a.width;
   int total;
-  const int slot = count_before(sel, t, s_cnt, total);
+  const int slot = count_before<kTreeWaves>(sel, t, s_cnt, total);
   if (sel) {
     a.frontier_out[(long long)b * a.width + slot] = id;
     if (slot == 0) s_first = id;
@@ -92,8 +137,9 @@ __global__ __launch_bounds__(kTreeThreads) void grow_kernel(TreeGrowArgs a) {
 // The last draft pass with a mixture head and a contrastive head (Section 3.2): children from
 // head 0's list, then the `width` best children get head 1's list of their parent as children.
 __global__ __launch_bounds__(kTreeThreads) void grow_tail_kernel(TreeGrowArgs a, int k1, int k2) {
-  __shared__ float s_sc[kTreeThreads];
-  __shared__ int s_cnt[kTreeThreads / 64];
+  __shared__ __align__(16) float s_sc[kTreeThreads];
+  __shared__ int s_rank[kTreeThreads];
+  __shared__ int s_cnt[kTreeWaves];
   __shared__ int s_child[kTreeThreads];  // chosen children by slot: node id, frontier slot
   __shared__ int s_slot_f[kTreeThreads];
   const int b = blockIdx.x, t = threadIdx.x;
@@ -116,13 +162,13 @@ __global__ __launch_bounds__(kTreeThreads) void grow_tail_kernel(TreeGrowArgs a,
     a.q_row[base + id] = a.q_row_base + (int)(2 * row);
   }
   s_sc[t] = sc;
+  s_rank[t] = 0;
   __syncthreads();
-  int rank = 0;
-#pragma unroll 8
-  for (int i = 0; i < C; ++i) rank += beats(s_sc[i], i, sc, t);
-  const bool sel = valid && rank < a.width;
+  count_beaten<kTreeWaves>(s_sc, C, s_rank, t);
+  __syncthreads();
+  const bool sel = valid && s_rank[t] < a.width;
   int total;
-  const int slot = count_before(sel, t, s_cnt, total);
+  const int slot = count_before<kTreeWaves>(sel, t, s_cnt, total);
   if (sel) {
     s_child[slot] = id;
     s_slot_f[slot] = f;
@@ -180,46 +226,39 @@ __global__ __launch_bounds__(kTreeThreads) void fill_static_kernel(TreeGrowArgs 
   if (t == 0) a.n_nodes[b] = min(n0 + n_new, a.max_nodes);
 }
 
-__global__ __launch_bounds__(kTreeThreads) void finalize_kernel(TreeFinalArgs a) {
-  __shared__ float s_sc[kMaxGrowNodes];
-  __shared__ short s_keep[kMaxGrowNodes];
+// A thread per node.  Everything a node holds is asked for before its sequence's node count is known (the arrays are
+// max_nodes long): one trip to memory instead of three, and the comparisons are spread over sixteen waves.
+// @FIN@
+__global__ __launch_bounds__(kMaxGrowNodes) void finalize_kernel(TreeFinalArgs a) {
+  constexpr int kWaves = kMaxGrowNodes / 64;
+  __shared__ __align__(16) float s_sc[kMaxGrowNodes];
+  __shared__ int s_rank[kMaxGrowNodes];
   __shared__ short s_new[kMaxGrowNodes];
-  __shared__ int s_cnt[kTreeThreads / 64];
+  __shared__ int s_cnt[kWaves];
   const int b = blockIdx.x, t = threadIdx.x;
+  const long long at = (long long)b * a.max_nodes + min(t, a.max_nodes - 1);
+  const float sc = a.score[at];
+  const int pid = a.parent[at], tok = a.tokens[at], q_row = a.q_row[at];
   const int n = min(max(a.n_nodes[b], 0), a.max_nodes);
-  const long long base = (long long)b * a.max_nodes;
-  for (int i = t; i < kMaxGrowNodes; i += kTreeThreads) s_sc[i] = i < n ? a.score[base + i] : -INFINITY;
+  s_sc[t] = t < n ? sc : -INFINITY;
+  s_rank[t] = 0;
   __syncthreads();
-  for (int i = t; i < kMaxGrowNodes; i += kTreeThreads) {
-    int rank = 0;
-    const float sc = s_sc[i];
-    if (i < n) {
-#pragma unroll 8
-      for (int j = 0; j < n; ++j) rank += beats(s_sc[j], j, sc, i);
-    }
-    s_keep[i] = (i < n && rank < a.n_keep) ? 1 : 0;
-  }
+  count_beaten<kWaves>(s_sc, n, s_rank, t);
   __syncthreads();
-  int carried = 0;  // kept nodes in the chunks before this one (the same in every thread)
-  for (int i0 = 0; i0 < n; i0 += kTreeThreads) {
-    const int i = i0 + t;
-    int total;
-    const int before = count_before(i < n && s_keep[i], t, s_cnt, total);
-    if (i < n) s_new[i] = (short)(carried + before);
-    carried += total;
-    __syncthreads();  // s_cnt is written again by the next chunk
-  }
-  for (int i = t; i < n; i += kTreeThreads) {
-    if (!s_keep[i]) continue;
-    const long long o = (long long)b * a.n_keep + s_new[i];
-    const int pid = a.parent[base + i];
-    a.out_tokens[o] = a.tokens[base + i];
-    a.out_parent[o] = (pid >= 0 && pid < i) ? (int)s_new[pid] : -1;  // (a kept node's parent is kept)
-    a.out_q_row[o] = a.q_row[base + i];
-    if (a.out_old) a.out_old[o] = i;
+  int total;
+  const bool kept = t < n && s_rank[t] < a.n_keep;
+  const int place = count_before<kWaves>(kept, t, s_cnt, total);
+  s_new[t] = (short)place;
+  __syncthreads();
+  if (kept && place < a.n_keep) {
+    const long long o = (long long)b * a.n_keep + place;
+    a.out_tokens[o] = tok;
+    a.out_parent[o] = (pid >= 0 && pid < t) ? (int)s_new[pid] : -1;  // (a kept node's parent is kept)
+    a.out_q_row[o] = q_row;
+    if (a.out_old) a.out_old[o] = t;
   }
   const int n_valid = min(n, a.n_keep);
-  for (int i = n_valid + t; i < a.n_keep; i += kTreeThreads) {  // a tree with fewer nodes than asked for
+  for (int i = n_valid + t; i < a.n_keep; i += kMaxGrowNodes) {  // a tree with fewer nodes than asked for
     const long long o = (long long)b * a.n_keep + i;
     a.out_tokens[o] = -1;
     a.out_parent[o] = -1;
@@ -228,8 +267,6 @@ __global__ __launch_bounds__(kTreeThreads) void finalize_kernel(TreeFinalArgs a)
   }
   if (t == 0) a.n_valid[b] = n_valid;
 }
-
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 __global__ __launch_bounds__(256) void gather_rows_kernel(const float* __restrict__ q_all, const int* __restrict__ q_row,
                                                           float* __restrict__ out, int vocab, long long n_q_rows) {
@@ -266,7 +303,7 @@ hipError_t launch_tree_fill_static(const TreeGrowArgs& a, const int* slot, const
   return hipGetLastError();
 }
 hipError_t launch_tree_finalize(const TreeFinalArgs& a, hipStream_t stream) {
-  hipLaunchKernelGGL(finalize_kernel, dim3(a.batch), dim3(kTreeThreads), 0, stream, a);
+  hipLaunchKernelGGL(finalize_kernel, dim3(a.batch), dim3(kMaxGrowNodes), 0, stream, a);
   return hipGetLastError();
 }
 hipError_t launch_gather_rows(const float* q_all, const int* q_row, float* out, long long n_nodes, int vocab,
