@@ -358,7 +358,8 @@ jk_status jk_draft_heads(const jk_draft_heads_desc* desc, const void* f_top, con
  * an input here):
  *
  *   s_j = softmax_j(u . e_j)                  router over the n_experts centroids (Eq. 2, fp32)
- *   top1, top2 = the two largest s_j, larger first, ties to the lower expert (Eq. 5)
+ *   top1, top2 = the two largest s_j, larger first, ties to the lower expert (Eq. 5); a NaN
+ *       score ranks below every other, so a row always names two different experts
  *   f_top[r][k] = Expert_topk(u_r) + u_r      Expert_j(x) = w_down_j (silu(w_gate_j x) * (w_up_j x))
  *   f_mix[r]    = s_top1 Expert_top1(u_r) + s_top2 Expert_top2(u_r) + u_r            (Eq. 3)
  *

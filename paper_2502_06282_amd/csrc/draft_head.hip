@@ -11,7 +11,6 @@
 //   router_kernel, gated_act_kernel, select_kernel   the draft layer's router (Eq. 2, 5) and what
 //                          surrounds the experts' three projections (Eq. 3).
 // The products with weight matrices run in stream_gemm.hip.
-#include <climits>
 
 #include "jk_internal.h"
 #include "jk_wave.h"
@@ -96,31 +95,8 @@ struct SoftParams {
   float inv_temp;
 };
 
-// order of candidates: larger value first, equal values by increasing token id
-__device__ __forceinline__ bool better(float av, int ai, float bv, int bi) {
-  return av > bv || (av == bv && ai < bi);
-}
-
-struct Best {
-  float v;
-  int id;
-};
-
-__device__ __forceinline__ Best wave_best(float v, int id) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float ov = __shfl_xor(v, o);
-    const int oi = __shfl_xor(id, o);
-    if (better(ov, oi, v, id)) {
-      v = ov;
-      id = oi;
-    }
-  }
-  return Best{v, id};
-}
-
-// The same order as one unsigned comparison: the value's bits made monotonic (+ 0: the two zeros are equal) above the
-// complement of the id.  No candidate has key 0.
+// Order of candidates - larger value first, equal values by increasing id - as one unsigned comparison: the value's bits
+// made monotonic (+ 0: the two zeros are equal) above the complement of the id.  No candidate has key 0.
 __device__ __forceinline__ unsigned ordered_bits(float v) {
   const unsigned u = __float_as_uint(v + 0.f);
   return u ^ ((u >> 31) ? 0xFFFFFFFFu : 0x80000000u);
@@ -417,8 +393,9 @@ struct RouterParams {
 };
 
 // One workgroup per row: the router scores s_j = softmax_j(u . e_j) (Eq. 2; fp32), of which it picks the two largest
-// (Eq. 5, K = 2, ties to the lower expert).  Bound by one trip to memory: a wave has the row and two centroids in
-// flight at once, and the softmax and both maxima are taken across the lanes of a wave.
+// (Eq. 5, K = 2, ties to the lower expert; a NaN score ranks below every other, so that the row always names two
+// different experts that exist - the experts' outputs are addressed with them).  Bound by one trip to memory: a wave has
+// the row and two centroids in flight at once, and the softmax and both maxima are taken across the lanes of a wave.
 __global__ __launch_bounds__(256) void router_kernel(RouterParams p) {
   __shared__ float score[kMaxExperts];
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -449,17 +426,19 @@ __global__ __launch_bounds__(256) void router_kernel(RouterParams p) {
   }
   __syncthreads();
   if (wave != 0) return;
-  const float mine = lane < p.n_experts ? score[lane] : -INFINITY;  // (at most 64 experts)
-  const Best b1 = wave_best(mine, lane);
-  const Best b2 = wave_best(lane == b1.id ? -INFINITY : mine, lane == b1.id ? INT_MAX : lane);
-  float z = lane < p.n_experts ? expf(mine - b1.v) : 0.f;
+  // (at most 64 experts; a lane without one has key 0, which loses to every expert's key, a NaN's 0 above ~id included)
+  const float mine = lane < p.n_experts ? score[lane] : -INFINITY;
+  const unsigned long long key = lane >= p.n_experts ? 0ull : mine == mine ? key_of(mine, lane) : (unsigned long long)(unsigned)~lane;
+  const int i1 = key_id(wave_max_key(key)), i2 = key_id(wave_max_key(lane == i1 ? 0ull : key));
+  const float v1 = __shfl(mine, i1), v2 = __shfl(mine, i2);
+  float z = lane < p.n_experts ? expf(mine - v1) : 0.f;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) z += __shfl_xor(z, o);
   if (lane == 0) {
     p.s_top[2 * row] = 1.f / z;
-    p.s_top[2 * row + 1] = expf(b2.v - b1.v) / z;
-    p.idx[2 * row] = b1.id;
-    p.idx[2 * row + 1] = b2.id;
+    p.s_top[2 * row + 1] = expf(v2 - v1) / z;
+    p.idx[2 * row] = i1;
+    p.idx[2 * row + 1] = i2;
   }
 }
 
@@ -523,13 +502,15 @@ struct SelectParams {
   const int* idx;
   uint16_t* f_top;    // [rows][2][d] bf16
   uint16_t* f_mix;    // [rows][d] bf16 or null
-  int rows, d;
+  int rows, d, n_experts;
 };
 
 // f_top[r][k] = Expert_{idx[r][k]}(u_r) + u_r; f_mix[r] = sum_k s_k Expert_k(u_r) + u_r (Eq. 3)
 __global__ __launch_bounds__(256) void select_kernel(SelectParams p) {
   const int row = blockIdx.x;
-  const int i1 = p.idx[2 * row], i2 = p.idx[2 * row + 1];
+  // (expert_idx is the caller's memory: what comes back from it is kept inside the workspace's experts)
+  auto expert = [&](int i) { return min(max(p.idx[i], 0), p.n_experts - 1); };
+  const int i1 = expert(2 * row), i2 = expert(2 * row + 1);
   const float s1 = p.s_top[2 * row], s2 = p.s_top[2 * row + 1];
   const float* y1 = p.y + ((long long)i1 * p.rows + rows_with(p.idx, row, i1)) * p.d;
   const float* y2 = p.y + ((long long)i2 * p.rows + rows_with(p.idx, row, i2)) * p.d;
@@ -730,7 +711,7 @@ hipError_t launch_moe_experts(const MoeArgs& a, hipStream_t stream) {
   SelectParams sp;
   sp.y = o.y; sp.u = rp.u; sp.s_top = a.s_top; sp.idx = a.expert_idx;
   sp.f_top = static_cast<uint16_t*>(a.f_top); sp.f_mix = static_cast<uint16_t*>(a.f_mix);
-  sp.rows = a.rows; sp.d = a.d_model;
+  sp.rows = a.rows; sp.d = a.d_model; sp.n_experts = a.n_experts;
   sp.ksplit = mp.split2; sp.split_stride = o.y_split;
   hipLaunchKernelGGL(select_kernel, dim3(a.rows, (unsigned)((a.d_model / 4 + 255) / 256)), dim3(256), 0, stream, sp);
   return hipGetLastError();

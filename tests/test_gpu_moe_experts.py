@@ -220,3 +220,28 @@ def test_rows_gathered_per_expert(rows, d, f, n):
     """Every row-block count an expert can have (all rows may choose the same two), with divided and undivided k ranges
     and half chunks of k."""
     _check(moe_inputs(rows, d, f, n, seed=rows + 1), min_gap=1e-6)
+
+
+@pytest.mark.parametrize("n", [2, 3, 8, 63, 64])
+def test_a_nan_score_ranks_below_every_other(n):
+    """A row whose router scores are NaN (all of them, or one expert's) still names two different experts that exist,
+    in the order "NaN below everything, ties to the lower expert", and touches no other row's results."""
+    x = moe_inputs(9, 128, 128, n, seed=n)
+    clean = _call(x)
+    bad = dict(x, u=x["u"].copy())
+    bad["u"][4] = np.nan
+    got = _call(bad)
+    np.testing.assert_array_equal(got[2][4], [0, 1])
+    assert np.isnan(got[1][4]).all() and np.isnan(got[0][4]).all() and np.isnan(got[3][4]).all()
+    others = [r for r in range(9) if r != 4]
+    for a, b in zip(clean, got):
+        np.testing.assert_array_equal(a[others], b[others])
+    # one expert's centroid NaN: it is chosen only where a row has nothing else to choose
+    worst = int(clean[2][4, 0])
+    cen = x["centroids"].copy()
+    cen[worst] = np.nan
+    got = _call(dict(x, centroids=cen))
+    s = x["u"].astype(np.float64) @ x["centroids"].astype(np.float64).T
+    s[:, worst] = -np.inf
+    np.testing.assert_array_equal(got[2], np.argsort(-s, axis=1, kind="stable")[:, :2])
+    assert np.isnan(got[1]).all() and np.isfinite(got[0]).all()
