@@ -99,8 +99,10 @@ typedef struct {
   int32_t dtype;  /* jk_dtype of q, k, v and out */
 } jk_attn_desc;
 
-/* Bytes of workspace jk_tree_verify_attention needs for this shape and this
- * upper bound on the prefix length.  Returns 0 for an invalid descriptor. */
+/* Bytes of workspace for jk_tree_verify_attention(_paged) with this shape and this upper
+ * bound on the prefix length, and for every call of the same dtype that exceeds neither in
+ * batch, n_tree, n_kv_heads, n_q_heads / n_kv_heads, head_dim or the bound (a call itself
+ * may need less).  Returns 0 for an invalid descriptor. */
 size_t jk_tree_verify_attention_workspace(const jk_attn_desc* desc, int32_t max_prefix_len);
 
 /* Tree-masked verification attention (Section 2.1 step 2; Section 3.1.2 tree mask).

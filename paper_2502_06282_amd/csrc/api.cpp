@@ -94,12 +94,39 @@ struct PlanModel {
 };
 
 namespace {
+// A workspace serves every call that is no larger in batch, nodes, heads, head_dim and prefix bound than the one it was
+// sized for.  Partial results alone do not have that order - a smaller call may be cut into more splits, and take more
+// room - so a plan's partial rows stay below a bound that grows with each of those numbers, and the size query answers
+// with the bound.  bf16: as many splits as the keys allow, but no more than ten full turns of the widest workgroups
+// (kTurns; 84 MB at head_dim 128) unless that is less than kEach results per query row: 38 of 120000 plans of drawn
+// shapes would be cut into more (at eight turns and four results 250, at six 962).
+size_t most_part_rows(const jk_attn_desc& d, int max_prefix_len) {  // over all (sequence, KV head) units
+  constexpr long long kTurns = 10, kEach = 3;
+  const long long units = (long long)d.batch * d.n_kv_heads, m = (long long)d.n_tree * (d.n_q_heads / d.n_kv_heads);
+  const long long cus = device_cu_count();
+  auto least = [](long long a, long long b) { return a < b ? a : b; };
+  auto most = [](long long a, long long b) { return a > b ? a : b; };
+  if (d.dtype == JK_BF16) {
+    const long long n_tiles = (max_prefix_len + kTileKeys - 1) / kTileKeys + (d.n_tree + kTileKeys - 1) / kTileKeys;
+    const long long s_min = (n_tiles + kMaxTilesPerSplit - 1) / kMaxTilesPerSplit;
+    const long long s_top = least(most(n_tiles / 4, s_min), kMaxSplits);  // (at least two rounds of two tiles per split)
+    if (s_top <= 1) return 0;
+    const long long base = units * ((m + 127) / 128 * 128);
+    return (size_t)least(base * s_top, most(kTurns * cus * 128, base * most(kEach, s_min)));
+  }
+  // fp32: a result per range of 1024 keys, or, where workgroups of sixteen rows are fewer than CUs, up to eight of it
+  const long long keys = (long long)max_prefix_len + d.n_tree, s = (keys + 1023) / 1024;
+  const long long whole = s > 1 ? units * m * s : 0, divided = keys >= 256 ? least(16 * cus, units * m * least(8 * s, kMaxSplits)) : 0;
+  return (size_t)most(whole, divided);
+}
+
 bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_allowed, AttnPlan* pl) {
   static const PlanModel km;
   if (!desc_ok(d) || !shape_supported(d) || max_prefix_len < 0 || max_prefix_len > (1 << 24)) return false;
   const int G = d.n_q_heads / d.n_kv_heads;
   pl->m_rows = d.n_tree * G;
   const long long units = (long long)d.batch * d.n_kv_heads;
+  const size_t most_rows = most_part_rows(d, max_prefix_len);
   if (d.dtype == JK_BF16) {
     // Candidates: 4x1 or 2x2 waves (32-row blocks x key interleave) per workgroup.  Fewer
     // rows per workgroup means more workgroups per KV head without more KV splits: the K/V
@@ -133,6 +160,7 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
         const long long s_min = (n_tiles + kMaxTilesPerSplit - 1) / kMaxTilesPerSplit;
         if (s < s_min) s = s_min;
         if (s > kMaxSplits) continue;
+        if (s > 1 && forced_s < 1 && (size_t)(wgs * s * q_rows) > most_rows) continue;  // (one split always fits)
         // rounds of the longest split: the 4x1 arrangement deals tiles (an odd last tile costs about
         // half a round), the 2x2 arrangement whole rounds
         double rounds;
@@ -248,11 +276,12 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
         }
   }
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
-  const size_t rows = (size_t)units * pl->parts * pl->m_pad;
-  const bool need_parts = pl->parts > 1;
-  pl->part_o_bytes = need_parts ? up(rows * d.head_dim * (d.dtype == JK_BF16 ? 2 : sizeof(float))) : 0;
-  pl->part_ml_bytes = need_parts ? up(rows * sizeof(float2)) : 0;
+  const size_t rows = pl->parts > 1 ? (size_t)units * pl->parts * pl->m_pad : 0, o_row = (size_t)d.head_dim * (d.dtype == JK_BF16 ? 2 : sizeof(float));
+  pl->part_o_bytes = up(rows * o_row);
+  pl->part_ml_bytes = up(rows * sizeof(float2));
   pl->total_bytes = kAttnHeaderBytes + pl->part_o_bytes + pl->part_ml_bytes;
+  const size_t covers = kAttnHeaderBytes + up(most_rows * o_row) + up(most_rows * sizeof(float2));
+  pl->covers_bytes = covers > pl->total_bytes ? covers : pl->total_bytes;  // (a forced split count may need more)
   return true;
 }
 }  // namespace
@@ -292,11 +321,11 @@ extern "C" {
 size_t jk_tree_verify_attention_workspace(const jk_attn_desc* desc, int32_t max_prefix_len) {
   // Whether the splits are merged inside the kernel depends on jk_init having verified the device,
   // and the two plans may cut the work differently: the size covers both, so that it is a function
-  // of the descriptor and the bound alone.
+  // of the descriptor and the bound alone (see most_part_rows).
   AttnPlan a, b;
   if (!desc || !make_attn_plan(*desc, max_prefix_len, false, &a) || !make_attn_plan(*desc, max_prefix_len, true, &b))
     return 0;
-  return a.total_bytes > b.total_bytes ? a.total_bytes : b.total_bytes;
+  return a.covers_bytes > b.covers_bytes ? a.covers_bytes : b.covers_bytes;
 }
 
 jk_status jk_tree_verify_attention_plan(const jk_attn_desc* desc, int32_t max_prefix_len, int32_t* plan_out) {

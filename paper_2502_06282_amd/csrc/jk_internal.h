@@ -32,8 +32,7 @@ constexpr int kMaxSplits = 64;     // upper bound on KV splits per (sequence, KV
 constexpr int kMaxTilesPerSplit = 1024;  // so that a split's page ids (paged caches) fit a workgroup's LDS table
 
 // How one attention call is cut into workgroups.  Derived on the host from the
-// descriptor and the prefix bound only, so that the workspace query and the
-// launch always agree.
+// descriptor and the prefix bound only.
 struct AttnPlan {
   int wm;          // waves along the query-row axis (32 rows each)
   int wn;          // waves along the key axis (key columns of a round)
@@ -48,6 +47,7 @@ struct AttnPlan {
   int ranked;      // bf16 path: sequences taken by falling length, dealt to the XCDs in turn
   int deep;        // bf16 path, 2x2 waves: the six-tile K/V ring (one workgroup per CU, two rounds in flight)
   size_t part_o_bytes, part_ml_bytes, total_bytes;  // total = header + partials
+  size_t covers_bytes;  // what the size query answers: enough for every smaller call as well
 };
 
 // Every attention and acceptance workspace starts with a header: 256 bytes whose first word is the

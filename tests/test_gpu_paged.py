@@ -230,8 +230,7 @@ def test_sequences_of_a_batch_give_what_each_gives_alone(hkv, lens):
     bound = L + 5  # (no sequence is as long as the bound)
     for wm, splits, fused in ((2, 1, -1), (4, 1, -1), (2, 3, 0), (4, 3, 1)):
         tune("attn_wm", wm); tune("attn_wn", 4 // wm); tune("attn_splits", splits); tune("attn_fused", fused)
-        n = max(jk.tree_verify_attention_workspace(d["q"], d["k_cache"], d["k_tree"], m) for m in (L, bound))
-        ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+        ws = torch.empty(jk.tree_verify_attention_workspace(d["q"], d["k_cache"], d["k_tree"], bound), dtype=torch.uint8, device="cuda")
         jk.workspace_init(ws)
         for most, order in ((L, list(range(B))), (L, list(range(B))[::-1]), (bound, list(range(B)))):
             pl = torch.tensor([lens[i] for i in order], dtype=torch.int32).cuda()

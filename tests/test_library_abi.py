@@ -197,3 +197,39 @@ def test_attention_plans_of_random_shapes_keep_their_invariants(lib):
     finally:
         for k, v in ((b"attn_wm", 0), (b"attn_wn", 0), (b"attn_splits", 0), (b"attn_fused", -1)):
             lib.jk_set_tuning(k, v)
+
+
+def test_an_attention_workspace_covers_every_smaller_call(lib):
+    """A workspace "can be reused for calls of any shape it is large enough for": sized for the largest call of a
+    program, it is large enough for every call that is no larger in batch, nodes, heads, head_dim and prefix bound,
+    however finely that one is cut.  A call needs at most what the query answers for it, so the query must not
+    answer more for the smaller one."""
+    import random
+    rng = random.Random(9)
+    for case in range(4000):
+        dtype = rng.choice([0, 0, 0, 1])
+        hkv, G = rng.choice([1, 2, 4, 8, 32, 40]), rng.choice([1, 1, 2, 4, 8])
+        D = rng.choice([64, 128]) if dtype == 0 else rng.choice([64, 80, 128])
+        top = 16384 if dtype else rng.choice([600, 4096, 65536, 1 << 20])
+        B, T, L = rng.choice([1, 1, 2, 4, 8, 16, 33]), rng.randint(1, 128), rng.randint(0, top)
+        large = _desc(B, T, hkv * G, hkv, D, L, dtype)
+        have = lib.jk_tree_verify_attention_workspace(ctypes.byref(large), L)
+        assert have > 0
+        for _ in range(6):
+            b, t, l = (rng.choice([v, rng.randint(min(lo, v), v)]) for v, lo in ((B, 1), (T, 1), (L, 0)))
+            h, g, d = rng.choice([hkv, max(1, hkv // 2)]), rng.choice([G, max(1, G // 2)]), rng.choice([D, 64])
+            small = _desc(b, t, h * g, h, d, l, dtype)
+            assert 0 < lib.jk_tree_verify_attention_workspace(ctypes.byref(small), l) <= have, (dtype, (B, T, hkv, G, D, L), (b, t, h, g, d, l))
+
+
+def test_the_example_rounds_workspace_serves_each_of_its_calls(lib):
+    """`example_round.Round` sizes one workspace for the target's calls and for the draft layer's last pass; its
+    earlier passes have fewer nodes."""
+    for batch in (1, 2, 4, 8):
+        for hq, hkv in ((32, 32), (32, 8), (16, 2), (64, 8)):
+            for prefix in (100, 256, 1000, 2048, 4096, 10000):
+                for depth, width in ((4, 4), (6, 5), (8, 8)):
+                    ask = lambda t: lib.jk_tree_verify_attention_workspace(ctypes.byref(_desc(batch, t, hq, hkv, 128, prefix)), prefix)
+                    have = max(ask(60), ask(1 + width * (depth - 1)))
+                    for dep in range(depth):
+                        assert ask(1 + width * dep) <= have, (batch, hq, hkv, prefix, depth, width, dep)
