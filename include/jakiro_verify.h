@@ -348,6 +348,8 @@ typedef struct {
   float alpha, beta; /* Eq. 7; ignored for JK_HEADS_DECOUPLED */
 } jk_draft_heads_desc;
 
+/* Enough for every call with these weights and at most `rows` rows; 0 for sizes outside the ranges above.  (So are
+ * jk_moe_experts_workspace and jk_linear_workspace for theirs.) */
 size_t jk_draft_heads_workspace(int32_t rows, int32_t d_model, int32_t vocab);
 
 jk_status jk_draft_heads(const jk_draft_heads_desc* desc, const void* f_top, const float* s_top,

@@ -41,7 +41,7 @@ def _native_command(output: str):
     tdir = os.path.dirname(os.path.abspath(torch.__file__))
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     return ["g++", "-O2", "-std=c++17", "-fPIC", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-            "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(tdir, "include"),
+            "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-isystem", os.path.join(tdir, "include"),
             "-isystem", os.path.join(tdir, "include", "torch", "csrc", "api", "include"), "-isystem", os.path.join(rocm, "include"),
             "-isystem", sysconfig.get_paths()["include"], "-c", os.path.join(CSRC, "native.cpp"), "-o", output], os.path.join(tdir, "lib")
 

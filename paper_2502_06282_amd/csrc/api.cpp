@@ -312,6 +312,41 @@ bool make_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_allowe
   return true;
 }
 
+namespace {
+bool heads_shape_ok(int rows, int d_model, int vocab) {
+  return rows >= 1 && rows <= 128 && d_model >= 128 && d_model <= 16384 && d_model % 128 == 0 && vocab >= 1 && vocab <= (1 << 24);
+}
+bool moe_desc_ok(const jk_moe_desc& d) { return d.rows >= 1 && d.d_model >= 1 && d.d_ff >= 1 && d.n_experts >= 2; }
+bool moe_desc_supported(const jk_moe_desc& d) {
+  return d.rows <= 128 && d.d_model >= 128 && d.d_model <= 65536 && d.d_model % 128 == 0 && d.d_ff >= 128 &&
+         d.d_ff <= 65536 && d.d_ff % 128 == 0 && d.n_experts <= 64;
+}
+bool linear_shape_ok(int m, int n, int k) {
+  return m >= 1 && m <= 256 && n >= 1 && k >= 128 && k % 128 == 0 && k <= (1 << 20) && n <= (1 << 24);
+}
+
+// What the calls with the same weights and at most `rows` rows need: fewer rows may be cut into more parts and need more
+// room, and a program sizes its workspace once.  (Up to 256 plans to make, 20 - 110 us: callers that allocate per call
+// ask for that call's own need.)
+template <class Bytes>
+size_t most_bytes(int rows, Bytes bytes_of_rows) {
+  size_t most = 0;
+  for (int r = 1; r <= rows; ++r) {
+    const size_t n = bytes_of_rows(r);
+    if (n > most) most = n;
+  }
+  return most;
+}
+}  // namespace
+
+size_t draft_heads_call_bytes(int rows, int d_model, int vocab) {
+  return heads_shape_ok(rows, d_model, vocab) ? draft_heads_workspace_bytes(rows, d_model, vocab) : 0;
+}
+size_t moe_experts_call_bytes(const jk_moe_desc& d) {
+  return moe_desc_ok(d) && moe_desc_supported(d) ? moe_experts_workspace_bytes(d.rows, d.d_model, d.d_ff, d.n_experts) : 0;
+}
+size_t linear_call_bytes(int m, int n, int k) { return linear_shape_ok(m, n, k) ? linear_workspace_bytes(m, n, k) : 0; }
+
 }  // namespace jk
 
 using namespace jk;
@@ -581,10 +616,8 @@ jk_status jk_commit_path_layers_paged(const jk_attn_desc* desc, const jk_paged_k
 }
 
 size_t jk_draft_heads_workspace(int32_t rows, int32_t d_model, int32_t vocab) {
-  if (rows < 1 || rows > 128 || d_model < 128 || d_model > 16384 || d_model % 128 || vocab < 1 ||
-      vocab > (1 << 24))
-    return 0;
-  return draft_heads_workspace_bytes(rows, d_model, vocab);
+  if (!heads_shape_ok(rows, d_model, vocab)) return 0;
+  return most_bytes(rows, [&](int r) { return draft_heads_workspace_bytes(r, d_model, vocab); });
 }
 
 jk_status jk_draft_heads(const jk_draft_heads_desc* desc, const void* f_top, const float* s_top,
@@ -611,17 +644,9 @@ jk_status jk_draft_heads(const jk_draft_heads_desc* desc, const void* f_top, con
   return launch_draft_heads(a, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? JK_OK : JK_ERR_HIP;
 }
 
-static bool moe_desc_ok(const jk_moe_desc& d) {
-  return d.rows >= 1 && d.d_model >= 1 && d.d_ff >= 1 && d.n_experts >= 2;
-}
-static bool moe_desc_supported(const jk_moe_desc& d) {
-  return d.rows <= 128 && d.d_model >= 128 && d.d_model <= 65536 && d.d_model % 128 == 0 && d.d_ff >= 128 &&
-         d.d_ff <= 65536 && d.d_ff % 128 == 0 && d.n_experts <= 64;
-}
-
 size_t jk_moe_experts_workspace(const jk_moe_desc* desc) {
   if (!desc || !moe_desc_ok(*desc) || !moe_desc_supported(*desc)) return 0;
-  return moe_experts_workspace_bytes(desc->rows, desc->d_model, desc->d_ff, desc->n_experts);
+  return most_bytes(desc->rows, [&](int r) { return moe_experts_workspace_bytes(r, desc->d_model, desc->d_ff, desc->n_experts); });
 }
 
 jk_status jk_moe_experts(const jk_moe_desc* desc, const void* u, const void* centroids, const void* w_gate,
@@ -731,12 +756,9 @@ jk_status jk_gather_draft_probs(int32_t batch, int32_t n_tree, int32_t vocab, co
              : JK_ERR_HIP;
 }
 
-static bool linear_shape_ok(int32_t m, int32_t n, int32_t k) {
-  return m >= 1 && m <= 256 && n >= 1 && k >= 128 && k % 128 == 0 && k <= (1 << 20) && n <= (1 << 24);
-}
-
 size_t jk_linear_workspace(int32_t m, int32_t n, int32_t k) {
-  return linear_shape_ok(m, n, k) ? linear_workspace_bytes(m, n, k) : 0;
+  if (!linear_shape_ok(m, n, k)) return 0;
+  return most_bytes(m, [&](int r) { return linear_workspace_bytes(r, n, k); });
 }
 
 jk_status jk_linear(int32_t m, int32_t n, int32_t k, const void* x, const void* w, const void* residual,

@@ -228,6 +228,11 @@ struct LinearArgs {
   void* workspace;
 };
 size_t linear_workspace_bytes(int m, int n, int k);
+
+// what one call of these sizes needs, 0 where it is not supported (the public size queries cover fewer rows as well)
+size_t draft_heads_call_bytes(int rows, int d_model, int vocab);
+size_t moe_experts_call_bytes(const jk_moe_desc& d);
+size_t linear_call_bytes(int m, int n, int k);
 hipError_t launch_linear(const LinearArgs& a, hipStream_t stream);
 
 }  // namespace jk

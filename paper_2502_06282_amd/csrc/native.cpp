@@ -21,7 +21,7 @@
 #include <hip/hip_runtime.h>
 #include <torch/csrc/autograd/python_variable.h>
 
-#include "jakiro_verify.h"
+#include "jk_internal.h"
 
 namespace {
 
@@ -514,7 +514,7 @@ PyObject* heads(Args& a) {
     fail(PyExc_ValueError, "out_probs must be [R, 2, V]");
   if (given && !is_f32(*given)) fail(PyExc_TypeError, "s_top, logits, draft_probs and topk_probs must be contiguous float32");
   if (K < 0) fail(PyExc_RuntimeError, "top_k must not be negative");
-  const size_t need = jk_draft_heads_workspace(c.d.rows, c.d.d_model, c.d.vocab);
+  const size_t need = jk::draft_heads_call_bytes(c.d.rows, c.d.d_model, c.d.vocab);
   if (need == 0) fail_status(JK_ERR_UNSUPPORTED, "jk_draft_heads_workspace");
   at::Tensor logits = empty({R, 2, V}, at::kFloat, *f), probs;
   if (!given && want) probs = empty({R, 2, V}, at::kFloat, *f);
@@ -582,7 +582,7 @@ PyObject* moe(Args& a) {
   Moe c = read_moe(a, &u);
   const bool want = a.truth();
   const int64_t R = c.d.rows, d = c.d.d_model;
-  const size_t need = jk_moe_experts_workspace(&c.d);
+  const size_t need = jk::moe_experts_call_bytes(c.d);
   if (need == 0) fail_status(JK_ERR_UNSUPPORTED, "jk_moe_experts_workspace");
   at::Tensor f = empty({R, 2, d}, at::kBFloat16, *u), s = empty({R, 2}, at::kFloat, *u), idx = empty({R, 2}, at::kInt, *u), mix;
   if (want) mix = empty({R, d}, at::kBFloat16, *u);
@@ -618,7 +618,7 @@ PyObject* linear(Args& a) {
   const int64_t m = x.size(0), k = x.size(1), n = w.size(0);
   if (w.size(1) != k || (res && (res->dim() != 2 || res->size(0) != m || res->size(1) != n)))
     fail(PyExc_ValueError, "x [m,k], w [n,k], residual [m,n]");
-  const size_t need = jk_linear_workspace((int32_t)m, (int32_t)n, (int32_t)k);
+  const size_t need = jk::linear_call_bytes((int)m, (int)n, (int)k);
   if (need == 0) fail_status(JK_ERR_UNSUPPORTED, "jk_linear_workspace");
   at::Tensor out = empty({m, n}, f32 ? at::kFloat : at::kBFloat16, x), ws = empty({(int64_t)need}, at::kByte, x);
   check(jk_linear((int32_t)m, (int32_t)n, (int32_t)k, ptr(x), ptr(w), ptr(res), f32 ? nullptr : ptr(out),

@@ -233,3 +233,18 @@ def test_the_example_rounds_workspace_serves_each_of_its_calls(lib):
                     have = max(ask(60), ask(1 + width * (depth - 1)))
                     for dep in range(depth):
                         assert ask(1 + width * dep) <= have, (batch, hq, hkv, prefix, depth, width, dep)
+
+
+def test_a_draft_workspace_covers_fewer_rows(lib):
+    """The same for the draft side's calls: the weights stay, the number of rows changes from call to call, and fewer
+    rows may be cut into more parts."""
+    moe = lambda r, d, f, n: lib.jk_moe_experts_workspace(ctypes.byref(binding.MoeDesc(r, d, f, n)))
+    for d, f, n in ((4096, 4096, 8), (4096, 4096, 4), (1024, 2816, 8), (128, 128, 2), (5120, 13824, 5), (256, 8192, 64)):
+        sizes = [moe(r, d, f, n) for r in range(1, 129)]
+        assert sizes[0] > 0 and sizes == sorted(sizes), (d, f, n)
+    for d, v in ((4096, 128256), (4096, 32000), (512, 4000), (128, 1 << 20), (16384, 999)):
+        sizes = [lib.jk_draft_heads_workspace(r, d, v) for r in range(1, 129)]
+        assert sizes[0] > 0 and sizes == sorted(sizes), (d, v)
+    for n, k in ((4096, 8192), (6144, 4096), (4096, 4096), (512, 1024), (128, 16384), (100000, 128), (777, 2944)):
+        sizes = [lib.jk_linear_workspace(m, n, k) for m in range(1, 257)]
+        assert sizes[0] > 0 and sizes == sorted(sizes), (n, k)
