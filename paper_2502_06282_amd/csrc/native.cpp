@@ -7,10 +7,12 @@
 // six 87 us, with the GPU idle for most of it.  Here a call costs its allocations and its launches.
 //
 // Nothing is computed here: shapes and types are checked, outputs allocated from torch's caching allocator, and the
-// C ABI is called on torch's current stream (or the given one).
+// C ABI is called on torch's current stream (or the given one).  Allocating and launching both may wait (for memory, for
+// room in a full queue): they run without the interpreter lock, released once per call.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
+#include <atomic>
 #include <functional>
 #include <mutex>
 #include <string>
@@ -46,6 +48,24 @@ struct PyFailure {};
 }
 void check(int status, const char* where) {
   if (status != JK_OK) fail_status(status, where);
+}
+
+// Other Python threads run while this one allocates or launches.  (Nothing in the scope may touch a Python object; the
+// tensors of the arguments are kept alive by the caller's references.)
+class Unlocked {
+ public:
+  Unlocked() : state_(PyEval_SaveThread()) {}
+  ~Unlocked() { PyEval_RestoreThread(state_); }
+  Unlocked(const Unlocked&) = delete;
+  Unlocked& operator=(const Unlocked&) = delete;
+
+ private:
+  PyThreadState* state_;
+};
+template <class F>
+int unlocked(F f) {
+  Unlocked u;
+  return f();
 }
 
 // ------------------------------------------------------------------ arguments
@@ -134,7 +154,7 @@ PyObject* none() {
 // The hipStream_t to launch on: torch's current stream, or the given torch.cuda.Stream.  The first use on a device
 // also runs jk_init there (a short synchronous probe), unless that stream is being captured into a graph.
 void* stream_handle(PyObject* stream) {
-  static bool initialised[64];
+  static std::atomic<bool> initialised[64];
   void* handle = nullptr;
   if (stream == nullptr || stream == Py_None) {
     handle = c10::hip::getCurrentHIPStream().stream();
@@ -147,13 +167,13 @@ void* stream_handle(PyObject* stream) {
   }
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) fail_status(JK_ERR_HIP, "hipGetDevice");
-  if (dev >= 0 && dev < 64 && !initialised[dev]) {  // (the GIL is held)
+  if (dev >= 0 && dev < 64 && !initialised[dev]) {  // (two threads at once: both probe, with the same result)
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     void* current = c10::hip::getCurrentHIPStream().stream();
     if (hipStreamIsCapturing(static_cast<hipStream_t>(current), &st) != hipSuccess)
       fail_status(JK_ERR_HIP, "hipStreamIsCapturing");
     if (st == hipStreamCaptureStatusNone) {
-      check(jk_init(handle), "jk_init");
+      check(unlocked([&] { return jk_init(handle); }), "jk_init");
       initialised[dev] = true;
     }
   }
@@ -185,7 +205,8 @@ PyObject* prepared_launch(PyObject* o, PyObject* const* a, Py_ssize_t n, PyObjec
   if (n + named == 1) stream = a[0];
   PreparedCall* p = reinterpret_cast<PreparedCall*>(o);
   try {
-    check((*p->call)(stream_handle(stream)), p->where);
+    void* on = stream_handle(stream);
+    check(unlocked([&] { return (*p->call)(on); }), p->where);
   } catch (const PyFailure&) {
     return nullptr;
   } catch (const std::exception& e) {
@@ -274,6 +295,7 @@ Attention read_attention(Args& a, at::Tensor* new_out) {
   dims(kt, 4, "k_tree must be [B, T, Hkv, D]");
   if (!out) {
     if (!new_out) fail(PyExc_TypeError, "out is required");
+    Unlocked u;
     *new_out = empty(q.sizes(), q.scalar_type(), q);
     out = new_out;
   }
@@ -313,7 +335,8 @@ Attention read_attention(Args& a, at::Tensor* new_out) {
 PyObject* attention(Args& a) {
   at::Tensor made;
   const Attention c = read_attention(a, &made);
-  const int st = c(stream_handle(a.next()));
+  void* stream = stream_handle(a.next());
+  const int st = unlocked([&] { return c(stream); });
   if (st != JK_OK) {
     if (jk_tree_verify_attention_workspace(&c.d, c.max_prefix) == 0) fail_status(JK_ERR_UNSUPPORTED, "jk_tree_verify_attention_workspace");
     fail_status(st, c.where());
@@ -387,9 +410,13 @@ PyObject* accept(Args& a) {
   }
   const at::Tensor& ws = a.tensor();
   c.ws = ptr(ws); c.ws_bytes = bytes_of(ws);
-  at::Tensor path = empty({c.b, c.depth}, at::kInt, *tokens), len = empty({c.b}, at::kInt, *tokens), bonus = empty({c.b}, at::kInt, *tokens);
-  c.path = static_cast<int32_t*>(ptr(path)); c.len = static_cast<int32_t*>(ptr(len)); c.bonus = static_cast<int32_t*>(ptr(bonus));
-  const int st = c(stream_handle(a.next()));
+  void* stream = stream_handle(a.next());
+  at::Tensor path, len, bonus;
+  const int st = unlocked([&] {
+    path = empty({c.b, c.depth}, at::kInt, *tokens); len = empty({c.b}, at::kInt, *tokens); bonus = empty({c.b}, at::kInt, *tokens);
+    c.path = static_cast<int32_t*>(ptr(path)); c.len = static_cast<int32_t*>(ptr(len)); c.bonus = static_cast<int32_t*>(ptr(bonus));
+    return c(stream);
+  });
   if (st != JK_OK) {
     if (jk_accept_path_workspace(c.b, c.n, c.v, c.mode) == 0) fail_status(JK_ERR_UNSUPPORTED, "jk_accept_path_workspace");
     fail_status(st, c.where());
@@ -468,7 +495,8 @@ Commit read_commit(Args& a) {
 }
 PyObject* commit(Args& a) {  // ... , stream
   const Commit c = read_commit(a);
-  check(c(stream_handle(a.next())), c.where());
+  void* stream = stream_handle(a.next());
+  check(unlocked([&] { return c(stream); }), c.where());
   return none();
 }
 PyObject* prepare_commit(Args& a) {  // ... (and whatever else is to be kept alive)
@@ -516,14 +544,19 @@ PyObject* heads(Args& a) {
   if (K < 0) fail(PyExc_RuntimeError, "top_k must not be negative");
   const size_t need = jk::draft_heads_call_bytes(c.d.rows, c.d.d_model, c.d.vocab);
   if (need == 0) fail_status(JK_ERR_UNSUPPORTED, "jk_draft_heads_workspace");
-  at::Tensor logits = empty({R, 2, V}, at::kFloat, *f), probs;
-  if (!given && want) probs = empty({R, 2, V}, at::kFloat, *f);
-  at::Tensor tk = empty({R, 2, K}, at::kInt, *f), tp = empty({R, 2, K}, at::kFloat, *f), ws = empty({(int64_t)need}, at::kByte, *f);
-  c.logits = static_cast<float*>(ptr(logits));
-  c.probs = static_cast<float*>(given ? ptr(given) : probs.defined() ? ptr(probs) : nullptr);
-  c.topk = static_cast<int32_t*>(ptr(tk)); c.topp = static_cast<float*>(ptr(tp));
-  c.ws = ptr(ws); c.ws_bytes = need;
-  check(c(stream_handle(a.next())), "jk_draft_heads");
+  void* stream = stream_handle(a.next());
+  at::Tensor logits, probs, tk, tp, ws;
+  check(unlocked([&] {
+          logits = empty({R, 2, V}, at::kFloat, *f);
+          if (!given && want) probs = empty({R, 2, V}, at::kFloat, *f);
+          tk = empty({R, 2, K}, at::kInt, *f); tp = empty({R, 2, K}, at::kFloat, *f); ws = empty({(int64_t)need}, at::kByte, *f);
+          c.logits = static_cast<float*>(ptr(logits));
+          c.probs = static_cast<float*>(given ? ptr(given) : probs.defined() ? ptr(probs) : nullptr);
+          c.topk = static_cast<int32_t*>(ptr(tk)); c.topp = static_cast<float*>(ptr(tp));
+          c.ws = ptr(ws); c.ws_bytes = need;
+          return c(stream);
+        }),
+        "jk_draft_heads");
   PyObject* p;
   if (given) {
     p = a.a[9];
@@ -584,12 +617,17 @@ PyObject* moe(Args& a) {
   const int64_t R = c.d.rows, d = c.d.d_model;
   const size_t need = jk::moe_experts_call_bytes(c.d);
   if (need == 0) fail_status(JK_ERR_UNSUPPORTED, "jk_moe_experts_workspace");
-  at::Tensor f = empty({R, 2, d}, at::kBFloat16, *u), s = empty({R, 2}, at::kFloat, *u), idx = empty({R, 2}, at::kInt, *u), mix;
-  if (want) mix = empty({R, d}, at::kBFloat16, *u);
-  at::Tensor ws = empty({(int64_t)need}, at::kByte, *u);
-  c.f_top = ptr(f); c.s_top = static_cast<float*>(ptr(s)); c.idx = static_cast<int32_t*>(ptr(idx));
-  c.f_mix = want ? ptr(mix) : nullptr; c.ws = ptr(ws); c.ws_bytes = need;
-  check(c(stream_handle(a.next())), "jk_moe_experts");
+  void* stream = stream_handle(a.next());
+  at::Tensor f, s, idx, mix, ws;
+  check(unlocked([&] {
+          f = empty({R, 2, d}, at::kBFloat16, *u); s = empty({R, 2}, at::kFloat, *u); idx = empty({R, 2}, at::kInt, *u);
+          if (want) mix = empty({R, d}, at::kBFloat16, *u);
+          ws = empty({(int64_t)need}, at::kByte, *u);
+          c.f_top = ptr(f); c.s_top = static_cast<float*>(ptr(s)); c.idx = static_cast<int32_t*>(ptr(idx));
+          c.f_mix = want ? ptr(mix) : nullptr; c.ws = ptr(ws); c.ws_bytes = need;
+          return c(stream);
+        }),
+        "jk_moe_experts");
   return pack(wrap(std::move(f)), wrap(std::move(s)), wrap(std::move(idx)), want ? wrap(std::move(mix)) : none());
 }
 // ... , f_top, s_top, expert_idx, f_mix or None, workspace
@@ -620,9 +658,13 @@ PyObject* linear(Args& a) {
     fail(PyExc_ValueError, "x [m,k], w [n,k], residual [m,n]");
   const size_t need = jk::linear_call_bytes((int)m, (int)n, (int)k);
   if (need == 0) fail_status(JK_ERR_UNSUPPORTED, "jk_linear_workspace");
-  at::Tensor out = empty({m, n}, f32 ? at::kFloat : at::kBFloat16, x), ws = empty({(int64_t)need}, at::kByte, x);
-  check(jk_linear((int32_t)m, (int32_t)n, (int32_t)k, ptr(x), ptr(w), ptr(res), f32 ? nullptr : ptr(out),
-                  f32 ? static_cast<float*>(ptr(out)) : nullptr, ptr(ws), need, stream_handle(a.next())),
+  void* stream = stream_handle(a.next());
+  at::Tensor out, ws;
+  check(unlocked([&] {
+          out = empty({m, n}, f32 ? at::kFloat : at::kBFloat16, x); ws = empty({(int64_t)need}, at::kByte, x);
+          return jk_linear((int32_t)m, (int32_t)n, (int32_t)k, ptr(x), ptr(w), ptr(res), f32 ? nullptr : ptr(out),
+                           f32 ? static_cast<float*>(ptr(out)) : nullptr, ptr(ws), need, stream);
+        }),
         "jk_linear");
   return wrap(std::move(out));
 }
@@ -666,9 +708,13 @@ PyObject* tree_grow(Args& a) {  // state, candidates, width, q_row_base, stream 
   const TreeState t = read_tree_state(a);
   const Candidates c = read_candidates(a, t.batch);
   const int32_t width = a.i32(), base = a.i32();
-  at::Tensor out = empty({t.batch, width > 0 ? width : 0}, at::kInt, *c.tok);
-  check(jk_tree_grow(&t.s, t.batch, c.n_front, c.k, width, base, ints(c.front), ints(c.tok), static_cast<const float*>(ptr(c.p)),
-                     static_cast<int32_t*>(ptr(out)), stream_handle(a.next())),
+  void* stream = stream_handle(a.next());
+  at::Tensor out;
+  check(unlocked([&] {
+          out = empty({t.batch, width > 0 ? width : 0}, at::kInt, *c.tok);
+          return jk_tree_grow(&t.s, t.batch, c.n_front, c.k, width, base, ints(c.front), ints(c.tok), static_cast<const float*>(ptr(c.p)),
+                              static_cast<int32_t*>(ptr(out)), stream);
+        }),
         "jk_tree_grow");
   return wrap(std::move(out));
 }
@@ -676,8 +722,11 @@ PyObject* tree_grow_tail(Args& a) {  // state, candidates, k1, k2, width, q_row_
   const TreeState t = read_tree_state(a);
   const Candidates c = read_candidates(a, t.batch);
   const int32_t k1 = a.i32(), k2 = a.i32(), width = a.i32(), base = a.i32();
-  check(jk_tree_grow_tail(&t.s, t.batch, c.n_front, c.k, k1, k2, width, base, ints(c.front), ints(c.tok),
-                          static_cast<const float*>(ptr(c.p)), stream_handle(a.next())),
+  void* stream = stream_handle(a.next());
+  check(unlocked([&] {
+          return jk_tree_grow_tail(&t.s, t.batch, c.n_front, c.k, k1, k2, width, base, ints(c.front), ints(c.tok),
+                                   static_cast<const float*>(ptr(c.p)), stream);
+        }),
         "jk_tree_grow_tail");
   return none();
 }
@@ -687,11 +736,15 @@ PyObject* tree_fill_static(Args& a) {  // state, candidates, slot, expert, rank,
   const at::Tensor &slot = a.tensor(), &expert = a.tensor(), &rank = a.tensor();
   const at::Tensor* next = a.optional_tensor();
   const int32_t base = a.i32(), n_new = (int32_t)slot.numel(), n_next = next ? (int32_t)next->numel() : 0;
-  at::Tensor ids = empty({t.batch, n_new}, at::kInt, *c.tok), out;
-  if (n_next) out = empty({t.batch, n_next}, at::kInt, *c.tok);
-  check(jk_tree_fill_static(&t.s, t.batch, c.n_front, c.k, base, ints(c.front), ints(c.tok), static_cast<const float*>(ptr(c.p)),
-                            ints(&slot), ints(&expert), ints(&rank), n_new, ints(next), n_next,
-                            n_next ? static_cast<int32_t*>(ptr(out)) : nullptr, static_cast<int32_t*>(ptr(ids)), stream_handle(a.next())),
+  void* stream = stream_handle(a.next());
+  at::Tensor ids, out;
+  check(unlocked([&] {
+          ids = empty({t.batch, n_new}, at::kInt, *c.tok);
+          if (n_next) out = empty({t.batch, n_next}, at::kInt, *c.tok);
+          return jk_tree_fill_static(&t.s, t.batch, c.n_front, c.k, base, ints(c.front), ints(c.tok), static_cast<const float*>(ptr(c.p)),
+                                     ints(&slot), ints(&expert), ints(&rank), n_new, ints(next), n_next,
+                                     n_next ? static_cast<int32_t*>(ptr(out)) : nullptr, static_cast<int32_t*>(ptr(ids)), stream);
+        }),
         "jk_tree_fill_static");
   return pack(n_next ? wrap(std::move(out)) : none(), wrap(std::move(ids)));
 }
@@ -700,10 +753,14 @@ PyObject* tree_finalize(Args& a) {  // state, n_keep, stream -> (tokens, parent,
   const TreeState t = read_tree_state(a);
   const at::Tensor& like = THPVariable_Unpack(a.a[first]);
   const int32_t keep = a.i32();
-  at::Tensor o[4], n = empty({t.batch}, at::kInt, like);
-  for (at::Tensor& x : o) x = empty({t.batch, keep > 0 ? keep : 0}, at::kInt, like);
-  auto out = [&](int i) { return static_cast<int32_t*>(ptr(o[i])); };
-  check(jk_tree_finalize(&t.s, t.batch, keep, out(0), out(1), out(2), out(3), static_cast<int32_t*>(ptr(n)), stream_handle(a.next())),
+  void* stream = stream_handle(a.next());
+  at::Tensor o[4], n;
+  check(unlocked([&] {
+          n = empty({t.batch}, at::kInt, like);
+          for (at::Tensor& x : o) x = empty({t.batch, keep > 0 ? keep : 0}, at::kInt, like);
+          auto out = [&](int i) { return static_cast<int32_t*>(ptr(o[i])); };
+          return jk_tree_finalize(&t.s, t.batch, keep, out(0), out(1), out(2), out(3), static_cast<int32_t*>(ptr(n)), stream);
+        }),
         "jk_tree_finalize");
   return pack(wrap(std::move(o[0])), wrap(std::move(o[1])), wrap(std::move(o[2])), wrap(std::move(o[3])), wrap(std::move(n)));
 }
@@ -712,9 +769,13 @@ PyObject* gather_draft_probs(Args& a) {  // q_all, q_row, stream
   if (!is_f32(q) || !is_i32(row)) fail(PyExc_TypeError, "q_all contiguous float32, q_row contiguous int32");
   dims(row, 2, "q_row must be [B, N]");
   const int64_t V = q.size(-1), B = row.size(0), N = row.size(1);
-  at::Tensor out = empty({B, N, V}, at::kFloat, q);
-  check(jk_gather_draft_probs((int32_t)B, (int32_t)N, (int32_t)V, static_cast<const float*>(ptr(q)), V ? q.numel() / V : 0, ints(&row),
-                              static_cast<float*>(ptr(out)), stream_handle(a.next())),
+  void* stream = stream_handle(a.next());
+  at::Tensor out;
+  check(unlocked([&] {
+          out = empty({B, N, V}, at::kFloat, q);
+          return jk_gather_draft_probs((int32_t)B, (int32_t)N, (int32_t)V, static_cast<const float*>(ptr(q)), V ? q.numel() / V : 0,
+                                       ints(&row), static_cast<float*>(ptr(out)), stream);
+        }),
         "jk_gather_draft_probs");
   return wrap(std::move(out));
 }

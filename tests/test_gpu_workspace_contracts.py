@@ -163,3 +163,58 @@ def test_attention_calls_on_several_streams_at_once():
             continue
         for g, w in zip(got, acc_alone):
             assert torch.equal(g, w)
+
+
+_OTHER_THREADS = """
+import sys, threading, time
+import torch
+import paper_2502_06282_amd as jk
+
+x = torch.randn((8, 1024), device="cuda").to(torch.bfloat16)
+w = torch.randn((512, 1024), device="cuda").to(torch.bfloat16)
+a = torch.randn((4096, 4096), device="cuda")
+b = torch.empty_like(a)
+for _ in range(3):
+    torch.mm(a, a, out=b)
+torch.cuda.synchronize()
+t0 = time.perf_counter()
+for _ in range(10):
+    torch.mm(a, a, out=b)
+torch.cuda.synchronize()
+each = (time.perf_counter() - t0) / 10
+gaps, stop = [], threading.Event()
+
+def tick():
+    last = time.perf_counter()
+    while not stop.is_set():
+        time.sleep(0.001)
+        now = time.perf_counter()
+        gaps.append((last, now - last))
+        last = now
+
+t = threading.Thread(target=tick)
+t.start()
+for _ in range(max(1, min(1000, int(0.4 / each)))):   # 0.4 s of work in front of the call
+    torch.mm(a, a, out=b)
+begin = time.perf_counter()
+out = jk.linear(x, w)    # the process's first call: it waits for the stream to probe the device
+took = time.perf_counter() - begin
+stop.set()
+t.join()
+torch.cuda.synchronize()
+longest = max([g for at, g in gaps if begin <= at + g and at <= begin + took], default=took)
+print(took, longest, bool(torch.isfinite(out.float()).all()))
+"""
+
+
+def test_other_python_threads_run_while_a_call_waits():
+    """A call that has to wait (here the process's first one, which probes the device behind 0.4 s of queued work) does
+    not hold the interpreter lock: a thread that wakes every millisecond keeps doing so."""
+    import subprocess
+    import sys
+    from conftest import ROOT
+    r = subprocess.run([sys.executable, "-c", _OTHER_THREADS], cwd=ROOT, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stderr[-2000:]
+    took, longest, finite = r.stdout.split()
+    assert finite == "True" and float(took) > 0.1, r.stdout
+    assert float(longest) < 0.5 * float(took), r.stdout
