@@ -125,9 +125,10 @@ size_t jk_tree_verify_attention_workspace(const jk_attn_desc* desc, int32_t max_
  * head_dim <= 256 and a multiple of 4 and max_prefix_len + n_tree <= 65536
  * (fp32 MFMA path); 1 <= n_tree <= JK_MAX_TREE;
  * n_q_heads a multiple of n_kv_heads; JK_BF16: kc_stride_l and kt_stride_t at
- * most 2^24 elements (JK_ERR_UNSUPPORTED beyond).  Value rows of tree nodes that a query
- * cannot see must be finite (they are multiplied by an exact zero); their key
- * rows, and anything in the cache beyond prefix_len, are never used.
+ * most 2^24 elements (JK_ERR_UNSUPPORTED beyond).  JK_BF16: value rows of tree nodes that a
+ * query cannot see must be finite (they are multiplied by an exact zero; JK_F32 leaves a value
+ * with a weight of zero out, whatever it is); their key rows, and anything in the cache beyond
+ * prefix_len, are never used.
  * Accumulation is fp32; JK_BF16 rounds the softmax weights to bf16 before the
  * value product and, when the key range is split over several workgroups, the
  * partial outputs to bf16 before they are merged (running maxima and sums stay

@@ -11,6 +11,8 @@
 // O^T = V^T P^T, takes as its operand, so the weights never leave their registers.  An undivided key range needs no second
 // launch.  With one workgroup per query row, a thread per key and column, 4 heads of 64, 10 nodes and 138 keys took
 // 16.9 us (the second launch included), 8.0 like this; 4 sequences, 8 heads of 128, 52 nodes, 2100 keys 481 and 57.
+#include <type_traits>
+
 #include "jk_internal.h"
 #include "jk_wave.h"
 
@@ -85,7 +87,8 @@ __global__ __launch_bounds__(64 * waves_for<KJ>(), KJ <= 8 ? 2 : 1) void tva_f32
   __shared__ float2 ml[WAVES][16];
   extern __shared__ __attribute__((aligned(16))) float osum[];  // [WAVES][16][LDO]
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, g = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int c = lane & 15, g = lane >> 4;
   const int split = blockIdx.x, row0 = blockIdx.y * 16;
   const int kv = blockIdx.z % p.Hkv, b = blockIdx.z / p.Hkv;
   const int D = p.D;
@@ -119,21 +122,27 @@ __global__ __launch_bounds__(64 * waves_for<KJ>(), KJ <= 8 ? 2 : 1) void tva_f32
   const int p_end = min(k_end, L), t_begin = max(k_begin, L);
   const int n_prefix = p_end > k_begin ? (p_end - k_begin + 15) / 16 : 0, n_tree = k_end > t_begin ? (k_end - t_begin + 15) / 16 : 0;
 
+  // A weight of zero - an unseen key's above all - leaves its value out, whatever that is.  The matrix product has one
+  // value for sixteen rows' weights, so an infinity or a NaN reaches them all; it stays in the accumulators to the end, and
+  // a wave that finds one there takes its keys once more, key by key.  (Looked for in the values themselves, in front of
+  // each product: 57.0 us for 4 sequences, 8 heads of 128, 52 nodes, 2100 keys became 59.8.)
   floatx4 o[DB][4];
-#pragma unroll
-  for (int d = 0; d < DB; ++d)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) o[d][i] = floatx4{0.f, 0.f, 0.f, 0.f};
-  float mx = -INFINITY, sum = 0.f;
-  // 16 keys: `v_row(i)` is where key 4 g + i has its values, visible(i) whether this lane's row sees it; `next` asks for
+  float mx, sum;
+  // 16 keys: `v_at(i)` is where key i has its values, visible(i) whether this lane's row sees key 4 g + i; `next` asks for
   // the K of the block behind this one as soon as this one's is used
-  auto block = [&](auto v_row, auto visible, auto next) {
+  auto block = [&](auto careful, auto v_at, auto visible, auto next) {
     floatx4 v[DB][4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float* row = v_row(i);
+      if (careful) break;
+      const float* row = v_at(4 * g + i);
 #pragma unroll
       for (int d = 0; d < DB; ++d) v[d][i] = *reinterpret_cast<const floatx4*>(row + (64 * d + 4 * c < D ? 64 * d + 4 * c : 0));
+    }
+    if (16 * KJ != D) {  // (uniform; what stands in for columns past the end of a key with an infinity must not meet q's zeros)
+#pragma unroll
+      for (int j = 0; j < KJ; ++j)
+        if (16 * j + 4 * g >= D) k[j] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
     floatx4 s = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -161,6 +170,24 @@ __global__ __launch_bounds__(64 * waves_for<KJ>(), KJ <= 8 ? 2 : 1) void tva_f32
       s[i] = expf(s[i] - base);
       sum += s[i];
     }
+    if (careful) {
+#pragma unroll 1
+      for (int key = 0; key < 16; ++key) {
+        const float mine = (key & 2) ? ((key & 1) ? s[3] : s[2]) : ((key & 1) ? s[1] : s[0]);
+        const float w = __shfl(mine, 16 * (key >> 2) + c);
+        const float* row = v_at(key);
+#pragma unroll
+        for (int d = 0; d < DB; ++d)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {  // (as everywhere: columns past the end take the row's first ones, and are not stored)
+            const int at = 64 * d + 16 * g + 4 * r;
+            const floatx4 x = *reinterpret_cast<const floatx4*>(row + (at < D ? at : 0));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[d][e][r] = w != 0.f ? fmaf(x[e], w, o[d][e][r]) : o[d][e][r];
+          }
+      }
+      return;
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -169,25 +196,45 @@ __global__ __launch_bounds__(64 * waves_for<KJ>(), KJ <= 8 ? 2 : 1) void tva_f32
         for (int e = 0; e < 4; ++e) o[d][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[d][i][e], s[i], o[d][e], 0, 0, 0);
   };
   auto prefix_k = [&](int blk) { load_k(kc + (long long)min(k_begin + 16 * blk + c, p_end - 1) * p.kc_sl); };
-  if (split != 0 && wave < n_prefix) prefix_k(wave);
-  for (int blk = wave; blk < n_prefix; blk += WAVES) {
-    const int key0 = k_begin + 16 * blk + 4 * g;
-    block([&](int i) { return vc + (long long)min(key0 + i, p_end - 1) * p.kc_sl; }, [&](int i) { return key0 + i < p_end; },
-          [&]() {
-            if (blk + WAVES < n_prefix) prefix_k(blk + WAVES);
-          });
-  }
-  __syncthreads();  // the ancestor sets are there
-  const unsigned long long lo = anc[node][0], hi = anc[node][1];
-  for (int blk = (wave + WAVES - n_prefix % WAVES) % WAVES; blk < n_tree; blk += WAVES) {  // (the waves with fewer blocks first)
-    const int key0 = t_begin - L + 16 * blk, last = k_end - L - 1;
-    load_k(kt + (long long)min(key0 + c, last) * p.kt_st);
-    block([&](int i) { return vt + (long long)min(key0 + 4 * g + i, last) * p.kt_st; },
-          [&](int i) {
-            const int t = key0 + 4 * g + i;
-            return t <= last && (((t < 64 ? lo : hi) >> (t & 63)) & 1ull);
-          },
-          []() {});
+  auto pass = [&](auto careful) {
+#pragma unroll
+    for (int d = 0; d < DB; ++d)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[d][i] = floatx4{0.f, 0.f, 0.f, 0.f};
+    mx = -INFINITY;
+    sum = 0.f;
+    if ((split != 0 || careful) && wave < n_prefix) prefix_k(wave);
+    for (int blk = wave; blk < n_prefix; blk += WAVES) {
+      const int key0 = k_begin + 16 * blk;
+      block(careful, [&](int i) { return vc + (long long)min(key0 + i, p_end - 1) * p.kc_sl; }, [&](int i) { return key0 + 4 * g + i < p_end; },
+            [&]() {
+              if (blk + WAVES < n_prefix) prefix_k(blk + WAVES);
+            });
+    }
+    if (!careful) __syncthreads();  // the ancestor sets are there (once in every wave)
+    const unsigned long long lo = anc[node][0], hi = anc[node][1];
+    for (int blk = (wave + WAVES - n_prefix % WAVES) % WAVES; blk < n_tree; blk += WAVES) {  // (the waves with fewer blocks first)
+      const int key0 = t_begin - L + 16 * blk, last = k_end - L - 1;
+      load_k(kt + (long long)min(key0 + c, last) * p.kt_st);
+      block(careful, [&](int i) { return vt + (long long)min(key0 + i, last) * p.kt_st; },
+            [&](int i) {
+              const int t = key0 + 4 * g + i;
+              return t <= last && (((t < 64 ? lo : hi) >> (t & 63)) & 1ull);
+            },
+            []() {});
+    }
+  };
+  pass(std::false_type());
+  float wild = 0.f;
+#pragma unroll
+  for (int d = 0; d < DB; ++d)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) wild = fmaf(o[d][i][e], 0.f, wild);
+  if (__any(wild != 0.f)) {
+    asm volatile("" : "+v"(c), "+v"(g));  // (addresses are worked out afresh, not kept for this)
+    pass(std::true_type());
   }
 
   // ---- the waves' shares of a row meet

@@ -717,3 +717,35 @@ def test_bf16_deeper_ring_of_the_2x2_arrangement_changes_nothing_but_the_speed(p
         ref = oracle_attention(**x, parent=par, prefix_len=lens)
         err = np.abs(outs[1].float().cpu().numpy() - ref).max()
         assert err <= BF16_TOL and err <= 1.5e-2 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("D,T,L", [(64, 24, 40), (20, 24, 40), (128, 100, 300), (80, 60, 5), (200, 17, 1200)])
+def test_f32_leaves_out_values_with_a_weight_of_zero(D, T, L):
+    """fp32: a value row of infinities and NaN reaches the nodes that see it and no other; a key of infinities whose score
+    is -inf weighs nothing, whatever its value (head_dims with and without a remainder of the 16-column chunks)."""
+    cfg = _cfg("c1_tiny", batch=1, n_q_heads=4, n_kv_heads=2, head_dim=D, n_tree=T, prefix_len=L)
+    rng = np.random.default_rng(T)
+    par = np.array([[int(rng.integers(-1, i)) for i in range(T)]], dtype=np.int32)
+    par[0, T // 2 + 1] = T // 2                    # (somebody below the bad node)
+    x = attention_inputs(cfg)
+    bad = T // 2
+    x["q"][..., 0] = np.abs(x["q"][..., 0]) + 0.5
+    clean = {k: v.copy() for k, v in x.items()}
+    x["v_tree"][:, bad, :, 0::3] = np.nan
+    x["v_tree"][:, bad, :, 1::3] = np.inf
+    x["k_cache"][:, L // 3, :, 0] = -np.inf        # every score of this key is -inf
+    x["v_cache"][:, L // 3] = np.nan
+    got = gpu_attention(x, par, [L], "f32")
+    sees = np.zeros(T, dtype=bool)
+    for n in range(T):
+        a = n
+        while a >= 0:
+            sees[n] |= a == bad
+            a = int(par[0, a])
+    assert sees.any() and not sees.all()
+    assert not np.isfinite(got[:, sees]).all(axis=-1).any()
+    # the oracle without that key: the cache with its position removed
+    keep = [i for i in range(L) if i != L // 3]
+    clean["k_cache"], clean["v_cache"] = clean["k_cache"][:, keep], clean["v_cache"][:, keep]
+    ref = oracle_attention(**clean, parent=par, prefix_len=[L - 1])
+    assert np.abs(got[:, ~sees] - ref[:, ~sees]).max() <= F32_TOL
