@@ -14,8 +14,9 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libjakiro_verify.so")
 NATIVE = os.path.join(HERE, "_native.so")
-SOURCES = ["api.cpp", "tva_bf16.hip", "tva_f32.hip", "tva_combine.hip", "accept.hip", "accept_coop.hip", "commit.hip",
+SOURCES = ["api.cpp", "tva_f32.hip", "tva_combine.hip", "accept.hip", "accept_coop.hip", "commit.hip",
            "draft_head.hip", "draft_tree.hip", "stream_gemm.hip"]
+MERGES = 6  # tva_bf16.hip is compiled once for each of its merges (JK_MSH)
 # packed-fp32 code generation is switched off for all device code
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -49,10 +50,13 @@ def _native_command(output: str):
 def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(OBJ, exist_ok=True)
-    objects = [os.path.join(OBJ, os.path.splitext(s)[0] + ".o") for s in SOURCES]
+    units = [("tva_bf16.hip", f"tva_bf16_{m}.o", [f"-DJK_MSH={m}"]) for m in range(MERGES)]
+    units += [(s, os.path.splitext(s)[0] + ".o", []) for s in SOURCES]
+    objects = [os.path.join(OBJ, o) for _, o, _ in units]
     native_obj = os.path.join(OBJ, "native.o")
     native_cmd, torch_lib = _native_command(native_obj)
-    jobs = [[hipcc] + FLAGS + ["-x", "hip", "-c", os.path.join(CSRC, s), "-o", o] for s, o in zip(SOURCES, objects)] + [native_cmd]
+    jobs = [[hipcc] + FLAGS + defines + ["-x", "hip", "-c", os.path.join(CSRC, s), "-o", os.path.join(OBJ, o)]
+            for s, o, defines in units] + [native_cmd]
     with ThreadPoolExecutor(min(8, int(os.environ.get("MAX_JOBS", "8")))) as pool:
         list(pool.map(lambda c: _run(c, verbose), jobs))
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objects + ["-o", LIB], verbose)

@@ -36,8 +36,50 @@
 #include "jk_device.h"
 #include "jk_internal.h"
 
+// This file is compiled once for each way of merging the splits (JK_MSH = 0 - 5, see tva_bf16_kernel): the instances build
+// side by side.  The host's part is in the first.
+#ifndef JK_MSH
+#error "compile with -DJK_MSH=0 ... 5"
+#endif
+
 namespace jk {
+namespace tva {
+struct KParams {
+  const uint16_t *q, *kc, *vc, *kt, *vt;
+  const int32_t *parent, *prefix_len;
+  uint16_t* out;
+  float* part_o;
+  float2* part_ml;
+  int B, T, Hkv, G, M, m_pad, max_prefix, splits, n_qtiles, total_wgs;
+  unsigned long long mg_qtiles, mg_splits, mg_hkv, mg_g;  // floor(2^32 / d) + 1: n / d == (n * mg) >> 32 for n * d < 2^32
+  unsigned long long mg_splits_m1;                        // the same for max(splits - 1, 1)
+  long long q_sb, q_st, q_sh, kc_sb, kc_sl, kc_sh, kt_sb, kt_st, kt_sh, o_sb, o_st, o_sh;
+  float scale_log2;
+  // paged cache (block_table != nullptr): kc / vc are page pools, token t of sequence b lives in page
+  // block_table[b * max_blocks + t / page_size], slot t % page_size; tpp = 32-key tiles per page
+  const int32_t* block_table;
+  int max_blocks, tpp, n_pages;
+  int through;  // bit 0: outputs and partials, bit 1: the partials' (max, sum) pairs go through to memory (see the epilogue)
+  long long page_stride;
+  unsigned long long mg_tpp;
+  // split merge inside this kernel (MSH > 0; see merge_rows and the end of the kernel): sync = one
+  // 64-byte line of words per (unit, row tile) group in the workspace header, spin_limit = polls a
+  // workgroup spends waiting for its group before it leaves its slice to the group's last arriver
+  unsigned* sync;
+  unsigned* err;  // the workspace's sticky device error word
+  unsigned spin_limit;
+  int merge_rows, merge_shift;  // rows per slice = ceil(tile rows / splits); splits padded to 2^merge_shift
+  // batches: the sequences by falling length, dealt to the XCDs in turn (units_per_xcd > 0; see the kernel's start)
+  int units_per_xcd, second_turn;
+  unsigned long long mg_upx;
+};
+// One call, merged as MSH says, with the kernel for its head_dim and wave arrangement
+template <int MSH>
+hipError_t launch_merged(const KParams& kp, int head_dim, const AttnPlan& pl, hipStream_t stream);
+}  // namespace tva
+
 namespace {
+using tva::KParams;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -67,37 +109,6 @@ constexpr int kWaveRows = 32;   // query rows per wave
 #define JK_SPREAD 1
 #endif
 constexpr int kSpread = JK_SPREAD;  // score phases of a pipelined tile pair that carry the next round's transfers (0: none)
-
-struct KParams {
-  const uint16_t *q, *kc, *vc, *kt, *vt;
-  const int32_t *parent, *prefix_len;
-  uint16_t* out;
-  float* part_o;
-  float2* part_ml;
-  int B, T, Hkv, G, M, m_pad, max_prefix, splits, n_qtiles, total_wgs;
-  unsigned long long mg_qtiles, mg_splits, mg_hkv, mg_g;  // floor(2^32 / d) + 1: n / d == (n * mg) >> 32 for n * d < 2^32
-  unsigned long long mg_splits_m1;                        // the same for max(splits - 1, 1)
-  long long q_sb, q_st, q_sh, kc_sb, kc_sl, kc_sh, kt_sb, kt_st, kt_sh, o_sb, o_st, o_sh;
-  float scale_log2;
-  // paged cache (block_table != nullptr): kc / vc are page pools, token t of sequence b lives in page
-  // block_table[b * max_blocks + t / page_size], slot t % page_size; tpp = 32-key tiles per page
-  const int32_t* block_table;
-  int max_blocks, tpp, n_pages;
-  int through;  // bit 0: outputs and partials, bit 1: the partials' (max, sum) pairs go through to memory (see the epilogue)
-  long long page_stride;
-  unsigned long long mg_tpp;
-  // split merge inside this kernel (fused != 0; see merge_slice and the end of the kernel): sync = one
-  // 64-byte line of words per (unit, row tile) group in the workspace header, spin_limit = polls a
-  // workgroup spends waiting for its group before it leaves its slice to the group's last arriver
-  unsigned* sync;
-  unsigned* err;  // the workspace's sticky device error word
-  int fused;
-  unsigned spin_limit;
-  int merge_rows, merge_shift;  // rows per slice = ceil(tile rows / splits); splits padded to 2^merge_shift
-  // batches: the sequences by falling length, dealt to the XCDs in turn (units_per_xcd > 0; see the kernel's start)
-  int units_per_xcd, second_turn;
-  unsigned long long mg_upx;
-};
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -642,7 +653,7 @@ __device__ __forceinline__ void lone_tile(WaveState<D>& st, unsigned k_addr, uns
 // Profiling build only (-DJK_TIMING, not part of the shipped library): thread 0 of every
 // workgroup records the 100 MHz wall clock at points of the kernel (entry, speculative
 // transfers issued, prefix length known, transfers issued, first round landed, loop done,
-// columns parked, partials stored, arrived at the group word, group complete, end); jk_debug_read_timing copies the table of the last launch to the host
+// columns parked, partials stored, arrived at the group word, group complete, end); jk_debug_read_timing<JK_MSH> copies the table of the last launch to the host
 // (grids of at most 4096 workgroups).  Phase times of the kernel are measured with it.
 #ifdef JK_TIMING
 __device__ unsigned long long g_jk_ts[4096 * 16];
@@ -768,21 +779,24 @@ __device__ __forceinline__ MergeThread merge_prepare(const MergeArgs& p, int uni
 template <int D, int THREADS, int QROWS, int SH>
 __device__ __forceinline__ void merge_rows(const MergeArgs& p, const MergeThread& t, int sh, int b, int kv, int tile_row0,
                                            int tid, float* wbuf) {
-  constexpr int CPR = D / 4, RPP = THREADS / CPR, SP = 1 << SH, ROWS = 16 >> SH;
+  constexpr int CPR = D / 4, RPP = THREADS / CPR, SP = SH < 4 ? 1 << SH : 16, ROWS = 16 / SP;
   const int S = p.splits;
   const unsigned char* part = reinterpret_cast<const unsigned char*>(p.part_o);
   const unsigned po_step = (unsigned)p.m_pad * D * 2;  // bytes from one split's partial to the next
   const int rows_end = min(t.row_hi, p.M - tile_row0);
   u32x2 raw[16];
-  auto fetch = [&](int r0, int s0) {  // (32-bit offsets from one base)
+  // (Only branches that a wave takes as one: a row past the slice next to one inside it takes that one's data, and is not
+  // stored.  A lane mask for each of the sixteen loads would not fit the scalar registers.)
+  auto fetch = [&](int r0, int s0) {
+    const int wave_r0 = __builtin_amdgcn_readfirstlane(r0);
 #pragma unroll
     for (int k = 0; k < ROWS; ++k) {
-      unsigned off = t.raw_off + (unsigned)s0 * po_step + (unsigned)((r0 - t.r_b + k * RPP) * (D * 2));
-      const bool live = r0 + k * RPP < rows_end;
+      const bool any = wave_r0 + k * RPP < rows_end;
+      unsigned off = t.raw_off + (unsigned)s0 * po_step + (unsigned)((min(r0 + k * RPP, rows_end - 1) - t.r_b) * (D * 2));  // (32-bit offsets from one base)
 #pragma unroll
       for (int u = 0; u < SP; ++u) {
         raw[k * SP + u] = u32x2{0u, 0u};
-        if (live && s0 + u < S) raw[k * SP + u] = *reinterpret_cast<const u32x2*>(part + off);
+        if (any && s0 + u < S) raw[k * SP + u] = *reinterpret_cast<const u32x2*>(part + off);
         off += po_step;
       }
     }
@@ -813,7 +827,7 @@ __device__ __forceinline__ void merge_rows(const MergeArgs& p, const MergeThread
     float acc[ROWS][4];
 #pragma unroll
     for (int k = 0; k < ROWS; ++k) acc[k][0] = acc[k][1] = acc[k][2] = acc[k][3] = 0.f;
-    for (int s0 = 0; s0 < S; s0 += SP) {
+    for (int s0 = 0; s0 < (SH < 5 ? 1 : S); s0 += SP) {  // (SH < 5: no more than SP splits)
       if (r0 != t.r_b || s0 > 0) fetch(r0, s0);  // (beyond what went out above)
 #pragma unroll
       for (int k = 0; k < ROWS; ++k) {
@@ -860,19 +874,6 @@ __device__ __forceinline__ void merge_rows(const MergeArgs& p, const MergeThread
   }
 }
 
-template <int D, int THREADS, int QROWS>
-__device__ __forceinline__ void merge_run(const MergeArgs& p, const MergeThread& t, int sh, int b, int kv, int tile_row0,
-                                          int tid, float* wbuf) {
-  if (t.row_lo >= t.row_hi) return;  // (uniform)
-  switch (sh) {
-    case 1: merge_rows<D, THREADS, QROWS, 1>(p, t, sh, b, kv, tile_row0, tid, wbuf); break;
-    case 2: merge_rows<D, THREADS, QROWS, 2>(p, t, sh, b, kv, tile_row0, tid, wbuf); break;
-    case 3: merge_rows<D, THREADS, QROWS, 3>(p, t, sh, b, kv, tile_row0, tid, wbuf); break;
-    default: merge_rows<D, THREADS, QROWS, 4>(p, t, sh, b, kv, tile_row0, tid, wbuf); break;
-  }
-  __syncthreads();  // wbuf is free again (another slice may follow)
-}
-
 // LDS plan of one workgroup, shared by the kernel and its launcher.
 template <int D, int WM, int WN, int KT, bool PAGED = false, bool DEEP = false>
 struct Plan {
@@ -905,7 +906,11 @@ struct Plan {
   static_assert(THREADS >= JK_MAX_TREE, "one thread per tree node in the prologue");
 };
 
-template <int D, int WM, int WN, int KT, bool PAGED, bool DEEP>
+// MSH: the merge of the splits in this kernel (0: none, a second launch or nothing to merge; see merge_rows).  The host
+// picks the instance, so that a kernel holds the code of one merge: with all four behind a switch (3400 instructions, and
+// 113 - 146 scalar registers spilled, some of them in front of the tile loop) a layer of an 8B model, 4096 keys in sixteen
+// splits, took 15.2 us, and 14.7 like this.
+template <int D, int WM, int WN, int KT, bool PAGED, bool DEEP, int MSH>
 __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<D, WM, WN, KT, PAGED, DEEP>::REG_WGS)) void tva_bf16_kernel(
     const KParams p) {
   using G_ = Geo<D>;
@@ -1451,7 +1456,7 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
       }
     }
   }
-  if (splits > 1) {
+  if constexpr (MSH > 0) {
     // ---- merge of the group's splits in this kernel.  Every workgroup of the group owns the slice
     // of R = ceil(QROWS / splits) rows numbered like its split and merges it once all partials are
     // in L2.  Waiting is bounded: a workgroup that gives up records its slice in the group's mask
@@ -1463,17 +1468,17 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
     KArgs* late = (KArgs*)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(late));
     const int tid_e = wave * 64 + lane_e;  // (the thread id, rebuilt: see the note on lane_e above)
-    if (late->fused) {
+    {
       int* mode_s = repeat_s + 1;  // 0 leave, 1 merge own slice, 2 also the slices in mode_s[1..2]
       // (what the merge of this workgroup's own slice needs besides the partials: computed now, while
       // the partial stores travel and before the wait for the group)
       MergeArgs ma;
-      ma.part_o = p.part_o; ma.part_ml = p.part_ml; ma.out = p.out;
-      ma.M = M; ma.m_pad = p.m_pad; ma.splits = splits; ma.G = G; ma.mg_g = p.mg_g;
-      ma.o_sb = p.o_sb; ma.o_st = p.o_st; ma.o_sh = p.o_sh;
-      const int merge_rows = late->merge_rows, merge_shift = late->merge_shift;
+      ma.part_o = late->part_o; ma.part_ml = late->part_ml; ma.out = late->out;
+      ma.M = late->M; ma.m_pad = late->m_pad; ma.splits = late->splits; ma.G = late->G; ma.mg_g = late->mg_g;
+      ma.o_sb = late->o_sb; ma.o_st = late->o_st; ma.o_sh = late->o_sh;
+      const int slice_rows = late->merge_rows, merge_shift = MSH < 5 ? MSH : late->merge_shift;
       const int tile_row0 = qtile * QROWS;
-      const MergeThread mt = merge_prepare<D, THREADS, QROWS>(ma, unit_id, b, kv, split, merge_rows, merge_shift, tile_row0, tid_e);
+      MergeThread mt = merge_prepare<D, THREADS, QROWS>(ma, unit_id, b, kv, split, slice_rows, merge_shift, tile_row0, tid_e);
       JK_TS(7);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's partial stores have reached L2
       __syncthreads();
@@ -1524,15 +1529,20 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
         // is complete.  The loads below therefore go to L2 without an invalidate in front of them.)
         asm volatile("" ::: "memory");
         float* wbuf = reinterpret_cast<float*>(smem);  // (ring and epilogue buffers are dead: every wave is past its stores)
-        merge_run<D, THREADS, QROWS>(ma, mt, merge_shift, b, kv, tile_row0, tid_e, wbuf);
-        if (mode == 2) {
-          const unsigned long long left_over =
-              ((unsigned long long)(unsigned)mode_s[2] << 32) | (unsigned long long)(unsigned)mode_s[1];
-          for (int j = 0; j < splits; ++j)
-            if (j != split && ((left_over >> j) & 1ull)) {
-              const MergeThread mj = merge_prepare<D, THREADS, QROWS>(ma, unit_id, b, kv, j, merge_rows, merge_shift, tile_row0, tid_e);
-              merge_run<D, THREADS, QROWS>(ma, mj, merge_shift, b, kv, tile_row0, tid_e, wbuf);
-            }
+        unsigned long long left_over = 0ull;  // the slices of workgroups that gave up waiting
+        if (mode == 2)
+          left_over = ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane(mode_s[2]) << 32) |
+                      (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane(mode_s[1]);
+        left_over &= ~(1ull << split);
+        for (;;) {
+          if (mt.row_lo < mt.row_hi) {  // (uniform)
+            merge_rows<D, THREADS, QROWS, MSH>(ma, mt, merge_shift, b, kv, tile_row0, tid_e, wbuf);
+            __syncthreads();  // wbuf is free again
+          }
+          if (left_over == 0ull) break;
+          const int j = __ffsll((long long)left_over) - 1;
+          left_over &= left_over - 1ull;
+          mt = merge_prepare<D, THREADS, QROWS>(ma, unit_id, b, kv, j, slice_rows, merge_shift, tile_row0, tid_e);
         }
       }
     }
@@ -1543,24 +1553,44 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
   JK_TS(10);
 }
 
-template <int D, int WM, int WN, int KT, bool PAGED, bool DEEP = false>
+template <int D, int WM, int WN, int KT, bool PAGED, bool DEEP>
 hipError_t launch_one(const KParams& kp, hipStream_t stream) {
   using P_ = Plan<D, WM, WN, KT, PAGED, DEEP>;
-  auto kern = tva_bf16_kernel<D, WM, WN, KT, PAGED, DEEP>;
+  auto kern = tva_bf16_kernel<D, WM, WN, KT, PAGED, DEEP, JK_MSH>;
   static LdsLimitRaised raised;
   if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), P_::SMEM, raised); e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(kp.total_wgs), dim3(P_::THREADS), P_::SMEM, stream, kp);
   return hipGetLastError();
 }
+template <int D, bool PAGED>
+hipError_t launch_arranged(const KParams& kp, const AttnPlan& pl, hipStream_t stream) {
+  if (pl.wm == 4 && pl.wn == 1 && pl.kt == 2) return launch_one<D, 4, 1, 2, PAGED, false>(kp, stream);
+  if (pl.wm == 2 && pl.wn == 2 && pl.kt == 1)
+    return pl.deep ? launch_one<D, 2, 2, 1, PAGED, true>(kp, stream) : launch_one<D, 2, 2, 1, PAGED, false>(kp, stream);
+  return hipErrorInvalidValue;
+}
 
 }  // namespace
 
 #ifdef JK_TIMING
-extern "C" int jk_debug_read_timing(unsigned long long* host, size_t n) {
+#define JK_CAT2(a, b) a##b
+#define JK_CAT(a, b) JK_CAT2(a, b)
+extern "C" int JK_CAT(jk_debug_read_timing, JK_MSH)(unsigned long long* host, size_t n) {
   return (int)hipMemcpyFromSymbol(host, HIP_SYMBOL(g_jk_ts), n * sizeof(unsigned long long));
 }
 #endif
 
+namespace tva {
+template <>
+hipError_t launch_merged<JK_MSH>(const KParams& kp, int head_dim, const AttnPlan& pl, hipStream_t stream) {
+  const bool paged = kp.block_table != nullptr;
+  if (head_dim == 128) return paged ? launch_arranged<128, true>(kp, pl, stream) : launch_arranged<128, false>(kp, pl, stream);
+  if (head_dim == 64) return paged ? launch_arranged<64, true>(kp, pl, stream) : launch_arranged<64, false>(kp, pl, stream);
+  return hipErrorInvalidValue;
+}
+}  // namespace tva
+
+#if JK_MSH == 0
 hipError_t launch_tva_bf16(const AttnArgs& a, const AttnPlan& pl, hipStream_t stream) {
   KParams kp;
   kp.q = static_cast<const uint16_t*>(a.q);
@@ -1608,8 +1638,8 @@ hipError_t launch_tva_bf16(const AttnArgs& a, const AttnPlan& pl, hipStream_t st
   kp.through = (one_wave ? 1 : 0) | (one_wave && pl.wn > 1 ? 2 : 0);
   // merged in the kernel: ordinary stores (measured: the L2 passes them on and keeps no line of them, but they are
   // acknowledged after 0.7 us and read back in 0.4; stores through to memory take 1.3 and 1.0)
-  kp.fused = pl.fused;
-  if (pl.fused && pl.splits > 1) kp.through = 0;
+  const bool fused = pl.fused && pl.splits > 1;
+  if (fused) kp.through = 0;
   kp.sync = a.sync;
   // (a lane per sequence in the ranking; the XCDs get whole units)
   const long long units = (long long)d.batch * d.n_kv_heads;
@@ -1623,22 +1653,15 @@ hipError_t launch_tva_bf16(const AttnArgs& a, const AttnPlan& pl, hipStream_t st
   kp.merge_rows = (pl.q_rows + pl.splits - 1) / pl.splits;
   kp.merge_shift = 0;
   while ((1 << kp.merge_shift) < pl.splits) ++kp.merge_shift;
-  const int key = (d.head_dim * 1000 + pl.wm * 100 + pl.wn * 10 + pl.kt) * 2 + (a.block_table ? 1 : 0);
-  if (pl.deep && pl.wm == 2 && pl.wn == 2 && pl.kt == 1) {
-    if (d.head_dim == 128) return a.block_table ? launch_one<128, 2, 2, 1, true, true>(kp, stream) : launch_one<128, 2, 2, 1, false, true>(kp, stream);
-    if (d.head_dim == 64) return a.block_table ? launch_one<64, 2, 2, 1, true, true>(kp, stream) : launch_one<64, 2, 2, 1, false, true>(kp, stream);
+  if (!fused) return tva::launch_merged<0>(kp, d.head_dim, pl, stream);
+  switch (kp.merge_shift) {
+    case 1: return tva::launch_merged<1>(kp, d.head_dim, pl, stream);
+    case 2: return tva::launch_merged<2>(kp, d.head_dim, pl, stream);
+    case 3: return tva::launch_merged<3>(kp, d.head_dim, pl, stream);
+    case 4: return tva::launch_merged<4>(kp, d.head_dim, pl, stream);
+    default: return tva::launch_merged<5>(kp, d.head_dim, pl, stream);  // seventeen splits and more
   }
-#define JK_CASE(D_, WM_, WN_, KT_)                                                                  \
-  case ((D_) * 1000 + (WM_) * 100 + (WN_) * 10 + (KT_)) * 2: return launch_one<D_, WM_, WN_, KT_, false>(kp, stream); \
-  case ((D_) * 1000 + (WM_) * 100 + (WN_) * 10 + (KT_)) * 2 + 1: return launch_one<D_, WM_, WN_, KT_, true>(kp, stream);
-  switch (key) {
-    JK_CASE(128, 4, 1, 2)
-    JK_CASE(128, 2, 2, 1)
-    JK_CASE(64, 4, 1, 2)
-    JK_CASE(64, 2, 2, 1)
-    default: return hipErrorInvalidValue;
-  }
-#undef JK_CASE
 }
+#endif
 
 }  // namespace jk

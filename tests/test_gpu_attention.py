@@ -415,6 +415,30 @@ def test_bf16_merge_inside_the_kernel_agrees_with_the_merge_kernel(name, kw, arr
         assert np.abs(a - ref).max() <= BF16_TOL
 
 
+@pytest.mark.parametrize("arr,T", [((2, 2), 50), ((4, 1), 110)])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("splits", [2, 3, 4, 5, 8, 9, 16, 17, 33, 64])
+def test_bf16_every_merge_instance(splits, D, arr, T):
+    """The merge inside the kernel has an instance for each power of two of splits up to sixteen and one for more: at the
+    edges of each (rows per slice that do and do not divide the tile, a last slice without rows, splits without keys)
+    it agrees with the merge kernel as above, and slices left to the last arriver give the same bits."""
+    import paper_2502_06282_amd as jk
+    cfg = _cfg("c3_llama3_8b", n_q_heads=8, n_kv_heads=8, head_dim=D, prefix_len=700, n_tree=T)
+    par = np.array([[max(-1, (i - 1) // 2) for i in range(T)]], dtype=np.int32)
+    x = attention_inputs(cfg, scale_mult=np.sqrt(float(D)))
+    tune("attn_wm", arr[0]); tune("attn_wn", arr[1]); tune("attn_splits", splits)
+    a, ws, plan = _attn_with_ws(x, par, [700], 1)
+    b, _, plan_b = _attn_with_ws(x, par, [700], 0)
+    assert plan["fused"] == 1 and plan_b["fused"] == 0 and plan["splits"] == plan_b["splits"] == splits
+    assert np.isfinite(a).all() and jk.last_device_error(ws) == 0
+    assert (np.abs(a - b) <= 1.01 * 2.0 ** -7 * np.maximum(np.abs(a), np.abs(b)) + 1e-6 * np.abs(a).max()).all()
+    assert (a != b).mean() < 0.02
+    tune("spin_limit", 0)
+    late, ws, _ = _attn_with_ws(x, par, [700], 1)
+    np.testing.assert_array_equal(late, a)
+    assert jk.last_device_error(ws) in (0, jk.JK_DEVERR_MERGE_WAIT)   # (0: every partner was there at the first look)
+
+
 def test_bf16_merge_inside_the_kernel_when_the_wait_expires():
     """spin_limit 0: no workgroup waits for its partners.  Every workgroup but a group's last arriver records its
     slice and leaves, the last arriver merges them all: same bits as the normal run, the workspace's error word
