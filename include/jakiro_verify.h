@@ -130,9 +130,10 @@ size_t jk_tree_verify_attention_workspace(const jk_attn_desc* desc, int32_t max_
  * with a weight of zero out, whatever it is); their key rows, and anything in the cache beyond
  * prefix_len, are never used.
  * Accumulation is fp32; JK_BF16 rounds the softmax weights to bf16 before the
- * value product and, when the key range is split over several workgroups, the
- * partial outputs to bf16 before they are merged (running maxima and sums stay
- * fp32). */
+ * value product.  When the key range is split over several workgroups, the partial
+ * outputs that are merged are fp32 for two and three splits (and for more where the
+ * workgroups of an undivided call would fill most of the card), up to 64 MB of them,
+ * and rounded to bf16 otherwise (running maxima and sums are always fp32). */
 jk_status jk_tree_verify_attention(const jk_attn_desc* desc, const void* q, const void* k_cache,
                                    const void* v_cache, const void* k_tree, const void* v_tree,
                                    const int32_t* parent, const int32_t* prefix_len,

@@ -16,7 +16,7 @@ LIB = os.path.join(HERE, "libjakiro_verify.so")
 NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["api.cpp", "tva_f32.hip", "tva_combine.hip", "accept.hip", "accept_coop.hip", "commit.hip",
            "draft_head.hip", "draft_tree.hip", "stream_gemm.hip"]
-MERGES = 6  # tva_bf16.hip is compiled once for each of its merges (JK_MSH)
+MERGES = 7  # tva_bf16.hip is compiled once for each of its merges (JK_MERGE)
 # packed-fp32 code generation is switched off for all device code
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -50,7 +50,7 @@ def _native_command(output: str):
 def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(OBJ, exist_ok=True)
-    units = [("tva_bf16.hip", f"tva_bf16_{m}.o", [f"-DJK_MSH={m}"]) for m in range(MERGES)]
+    units = [("tva_bf16.hip", f"tva_bf16_{m}.o", [f"-DJK_MERGE={m}"]) for m in range(MERGES)]
     units += [(s, os.path.splitext(s)[0] + ".o", []) for s in SOURCES]
     objects = [os.path.join(OBJ, o) for _, o, _ in units]
     native_obj = os.path.join(OBJ, "native.o")

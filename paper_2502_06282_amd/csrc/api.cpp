@@ -120,6 +120,22 @@ size_t most_part_rows(const jk_attn_desc& d, int max_prefix_len) {  // over all 
   return (size_t)most(whole, divided);
 }
 
+// Whether the splits' partial results are held in fp32 rather than bf16.  In bf16 a result carries one more rounding than
+// an undivided one (error against fp64 2.9e-3 instead of 2.35e-3 of its norm for N(0, 1) inputs, however many splits; with
+// fp32 partials 2.3e-3), but they are the largest avoidable traffic of a call, and half of it.  They are fp32 for two and
+// three splits, and for any number where the row tiles would have given most CUs a workgroup undivided: there the keys are
+// divided for the balance of a batch, not because the card would be idle; never more than 64 MB of them.  What it costs
+// (us, bf16 / fp32): sixteen ragged sequences of up to 4096 keys, 8B, two splits 62.4 / 65.9; 13B, four sequences, three
+// splits 40.4 / 42.0; 7B, six sequences of 2048, two splits 47.8 / 49.2; two sequences of 300 keys 9.36 / 9.47; and, left
+// in bf16, eight sequences, four splits 36.6 / 39.7.
+constexpr int kFineSplits = 3;
+constexpr size_t kFineBytes = (size_t)64 << 20;
+bool fine_partials(const AttnPlan& pl, long long units, int head_dim) {
+  if (pl.splits < 2 || (size_t)units * pl.splits * pl.m_pad * head_dim * sizeof(float) > kFineBytes) return false;
+  const int cus = device_cu_count();
+  return pl.splits <= kFineSplits || (!pl.fused && pl.n_qtiles == 1 && 16 * units >= 11 * cus && units <= cus);
+}
+
 bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_allowed, AttnPlan* pl) {
   static const PlanModel km;
   if (!desc_ok(d) || !shape_supported(d) || max_prefix_len < 0 || max_prefix_len > (1 << 24)) return false;
@@ -250,10 +266,12 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
     if (!have) return false;
     pl->parts = pl->splits;
     pl->m_pad = pl->n_qtiles * pl->q_rows;
+    pl->fine = fine_partials(*pl, units, d.head_dim) ? 1 : 0;
     // (the kernel ranks a batch with a lane per sequence, and the XCDs get whole units)
     pl->ranked = d.batch >= 2 && d.batch <= 64 && units % 8 == 0 ? 1 : 0;
   } else {
     pl->fused = 0;
+    pl->fine = 0;
     pl->ranked = 0;
     pl->deep = 0;
     pl->wm = pl->wn = pl->kt = 1;
@@ -277,10 +295,15 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
   }
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
   const size_t rows = pl->parts > 1 ? (size_t)units * pl->parts * pl->m_pad : 0, o_row = (size_t)d.head_dim * (d.dtype == JK_BF16 ? 2 : sizeof(float));
-  pl->part_o_bytes = up(rows * o_row);
+  pl->part_o_bytes = up(rows * (pl->fine ? 2 * o_row : o_row));
   pl->part_ml_bytes = up(rows * sizeof(float2));
   pl->total_bytes = kAttnHeaderBytes + pl->part_o_bytes + pl->part_ml_bytes;
-  const size_t covers = kAttnHeaderBytes + up(most_rows * o_row) + up(most_rows * sizeof(float2));
+  size_t most_o = most_rows * o_row;
+  if (d.dtype == JK_BF16) {  // (a smaller call's partials may be fp32)
+    const size_t fine_o = 2 * most_rows * o_row < kFineBytes ? 2 * most_rows * o_row : kFineBytes;
+    if (fine_o > most_o) most_o = fine_o;
+  }
+  const size_t covers = kAttnHeaderBytes + up(most_o) + up(most_rows * sizeof(float2));
   pl->covers_bytes = covers > pl->total_bytes ? covers : pl->total_bytes;  // (a forced split count may need more)
   return true;
 }

@@ -45,6 +45,7 @@ struct AttnPlan {
   int parts;       // partial results per row: the splits, or (fp32) parts of them
   int fused;       // bf16 path: the splits are merged inside the attention kernel (no second launch)
   int ranked;      // bf16 path: sequences taken by falling length, dealt to the XCDs in turn
+  int fine;        // bf16 path: partial results in fp32 rather than bf16
   int deep;        // bf16 path, 2x2 waves: the six-tile K/V ring (one workgroup per CU, two rounds in flight)
   size_t part_o_bytes, part_ml_bytes, total_bytes;  // total = header + partials
   size_t covers_bytes;  // what the size query answers: enough for every smaller call as well
@@ -85,7 +86,7 @@ struct AttnArgs {
   const int32_t* parent;
   const int32_t* prefix_len;
   void* out;
-  float* part_o;    // [B*Hkv][splits][m_pad][D], fp32 (fp32 path) or bf16 (bf16 path)
+  float* part_o;    // [B*Hkv][splits][m_pad][D], fp32, or bf16 (bf16 path, see AttnPlan::fine)
   float2* part_ml;  // [B*Hkv][splits][m_pad]  (running max in log2 units, sum)
   unsigned* err;    // the workspace's device error word
   unsigned* sync;   // the workspace's group synchronisation words (merge inside the kernel)

@@ -36,10 +36,10 @@
 #include "jk_device.h"
 #include "jk_internal.h"
 
-// This file is compiled once for each way of merging the splits (JK_MSH = 0 - 5, see tva_bf16_kernel): the instances build
+// This file is compiled once for each way of merging the splits (JK_MERGE = 0 - 6, see merge_of): the instances build
 // side by side.  The host's part is in the first.
-#ifndef JK_MSH
-#error "compile with -DJK_MSH=0 ... 5"
+#ifndef JK_MERGE
+#error "compile with -DJK_MERGE=0 ... 6"
 #endif
 
 namespace jk {
@@ -59,10 +59,11 @@ struct KParams {
   // block_table[b * max_blocks + t / page_size], slot t % page_size; tpp = 32-key tiles per page
   const int32_t* block_table;
   int max_blocks, tpp, n_pages;
-  int through;  // bit 0: outputs and partials, bit 1: the partials' (max, sum) pairs go through to memory (see the epilogue)
+  int through;  // bit 0: outputs and partials, bit 1: the partials' (max, sum) pairs go through to memory; bit 2: the partials
+                // are fp32 (see the epilogue)
   long long page_stride;
   unsigned long long mg_tpp;
-  // split merge inside this kernel (MSH > 0; see merge_rows and the end of the kernel): sync = one
+  // split merge inside this kernel (MERGE > 0; see merge_rows and the end of the kernel): sync = one
   // 64-byte line of words per (unit, row tile) group in the workspace header, spin_limit = polls a
   // workgroup spends waiting for its group before it leaves its slice to the group's last arriver
   unsigned* sync;
@@ -73,8 +74,16 @@ struct KParams {
   int units_per_xcd, second_turn;
   unsigned long long mg_upx;
 };
-// One call, merged as MSH says, with the kernel for its head_dim and wave arrangement
-template <int MSH>
+// How a kernel merges its splits (MERGE): 0 not at all (one split, or a second launch), then
+//   1 two splits, 2 three: fp32 partials (see AttnPlan::fine)    3 four, 4 up to eight, 5 up to sixteen, 6 more: bf16
+constexpr int merge_of(int splits) {
+  return splits <= 4 ? splits - 1 : splits <= 8 ? 4 : splits <= 16 ? 5 : 6;
+}
+// 2^shift splits go through merge_rows at once (6: sixteen of more)
+constexpr int merge_shift_of(int merge) { return merge <= 2 ? merge : merge - 1; }
+
+// One call, merged as MERGE says, with the kernel for its head_dim and wave arrangement
+template <int MERGE>
 hipError_t launch_merged(const KParams& kp, int head_dim, const AttnPlan& pl, hipStream_t stream);
 }  // namespace tva
 
@@ -653,7 +662,7 @@ __device__ __forceinline__ void lone_tile(WaveState<D>& st, unsigned k_addr, uns
 // Profiling build only (-DJK_TIMING, not part of the shipped library): thread 0 of every
 // workgroup records the 100 MHz wall clock at points of the kernel (entry, speculative
 // transfers issued, prefix length known, transfers issued, first round landed, loop done,
-// columns parked, partials stored, arrived at the group word, group complete, end); jk_debug_read_timing<JK_MSH> copies the table of the last launch to the host
+// columns parked, partials stored, arrived at the group word, group complete, end); jk_debug_read_timing<JK_MERGE> copies the table of the last launch to the host
 // (grids of at most 4096 workgroups).  Phase times of the kernel are measured with it.
 #ifdef JK_TIMING
 __device__ unsigned long long g_jk_ts[4096 * 16];
@@ -740,18 +749,18 @@ __device__ __forceinline__ float group_sum(float x, int sh) {
 // byte offsets, the output address) is worked out by merge_prepare while the workgroup still
 // waits for its partners; then (A) one thread per (row, split) fetches that pair's (max, sum)
 // once, the 2^sh lanes of a row find the row's maximum and sum and park the normalised weight
-// 2^(m_s - m) / l in LDS, while (B) one thread per (row, 4 columns) has its 8 bytes of every
+// 2^(m_s - m) / l in LDS, while (B) one thread per (row, 4 columns) has its 8 (fp32: 16) bytes of every
 // split's partial in flight and afterwards only multiplies and adds.  At most THREADS (row, split)
-// pairs exist per slice (R = ceil(tile rows / S), S padded to 2^sh), one per thread.
+// pairs exist per slice (R = ceil(tile rows / S), S padded to 2^sh), one per thread.  FINE: the partials are fp32.
 struct MergeThread {
-  unsigned raw_off;   // byte offset of this thread's 8 bytes in split 0's partial (rows of the first pass)
+  unsigned raw_off;   // byte offset of this thread's 4 columns in split 0's partial (rows of the first pass)
   unsigned ml_off;    // byte offset of this thread's (row, split) pair
   unsigned dst_off;   // element offset of this thread's 4 output columns in `out` (first pass)
   int r_b, row_lo, row_hi;
   bool live_a, live_b;
 };
 
-template <int D, int THREADS, int QROWS>
+template <int D, int THREADS, int QROWS, bool FINE>
 __device__ __forceinline__ MergeThread merge_prepare(const MergeArgs& p, int unit_id, int b, int kv, int slice, int R,
                                                      int sh, int tile_row0, int tid) {
   constexpr int CPR = D / 4;
@@ -763,7 +772,7 @@ __device__ __forceinline__ MergeThread merge_prepare(const MergeArgs& p, int uni
   t.r_b = t.row_lo + tid / CPR;
   const unsigned unit_row0 = (unsigned)(unit_id * S) * (unsigned)p.m_pad + (unsigned)tile_row0;  // (the host keeps the
   t.live_b = t.r_b < t.row_hi && tile_row0 + t.r_b < p.M;                                        // partials below 2^31 bytes)
-  t.raw_off = ((unit_row0 + (unsigned)t.r_b) * (unsigned)D + (unsigned)chunk * 4u) * 2u;
+  t.raw_off = ((unit_row0 + (unsigned)t.r_b) * (unsigned)D + (unsigned)chunk * 4u) * (FINE ? 4u : 2u);
   const int ra = t.row_lo + (tid >> sh), sa = tid & ((1 << sh) - 1);
   t.live_a = ra < t.row_hi && tile_row0 + ra < p.M && sa < S;
   t.ml_off = (unit_row0 + (unsigned)ra + (unsigned)sa * (unsigned)p.m_pad) * 8u;
@@ -773,18 +782,20 @@ __device__ __forceinline__ MergeThread merge_prepare(const MergeArgs& p, int uni
   return t;
 }
 
-// (B) for up to 2^SH splits at a time, of as many rows as a thread's sixteen 8-byte slots hold: all of a slice's rows
+// (B) for up to 2^SH splits at a time, of as many rows as a thread's sixteen slots hold: all of a slice's rows
 // go out together (a 128-row tile in 2^k splits leaves a thread exactly 16 / 2^k of them).  One row after the other,
 // each a round trip to L2, two splits of a 4x1 workgroup took 5.7 us longer to merge than sixteen.
-template <int D, int THREADS, int QROWS, int SH>
+template <int D, int THREADS, int QROWS, int SH, bool FINE>
 __device__ __forceinline__ void merge_rows(const MergeArgs& p, const MergeThread& t, int sh, int b, int kv, int tile_row0,
                                            int tid, float* wbuf) {
   constexpr int CPR = D / 4, RPP = THREADS / CPR, SP = SH < 4 ? 1 << SH : 16, ROWS = 16 / SP;
   const int S = p.splits;
   const unsigned char* part = reinterpret_cast<const unsigned char*>(p.part_o);
-  const unsigned po_step = (unsigned)p.m_pad * D * 2;  // bytes from one split's partial to the next
+  typedef std::conditional_t<FINE, u32x4, u32x2> Raw;
+  constexpr unsigned ROW_BYTES = D * (FINE ? 4 : 2);
+  const unsigned po_step = (unsigned)p.m_pad * ROW_BYTES;  // from one split's partial to the next
   const int rows_end = min(t.row_hi, p.M - tile_row0);
-  u32x2 raw[16];
+  Raw raw[16];
   // (Only branches that a wave takes as one: a row past the slice next to one inside it takes that one's data, and is not
   // stored.  A lane mask for each of the sixteen loads would not fit the scalar registers.)
   auto fetch = [&](int r0, int s0) {
@@ -792,11 +803,11 @@ __device__ __forceinline__ void merge_rows(const MergeArgs& p, const MergeThread
 #pragma unroll
     for (int k = 0; k < ROWS; ++k) {
       const bool any = wave_r0 + k * RPP < rows_end;
-      unsigned off = t.raw_off + (unsigned)s0 * po_step + (unsigned)((min(r0 + k * RPP, rows_end - 1) - t.r_b) * (D * 2));  // (32-bit offsets from one base)
+      unsigned off = t.raw_off + (unsigned)s0 * po_step + (unsigned)(min(r0 + k * RPP, rows_end - 1) - t.r_b) * ROW_BYTES;  // (32-bit offsets from one base)
 #pragma unroll
       for (int u = 0; u < SP; ++u) {
-        raw[k * SP + u] = u32x2{0u, 0u};
-        if (any && s0 + u < S) raw[k * SP + u] = *reinterpret_cast<const u32x2*>(part + off);
+        raw[k * SP + u] = Raw(0u);
+        if (any && s0 + u < S) raw[k * SP + u] = *reinterpret_cast<const Raw*>(part + off);
         off += po_step;
       }
     }
@@ -839,12 +850,15 @@ __device__ __forceinline__ void merge_rows(const MergeArgs& p, const MergeThread
           const float w[4] = {w4.x, w4.y, w4.z, w4.w};
 #pragma unroll
           for (int v = 0; v < 4 && u + v < SP; ++v) {
-            const u32x2 x = raw[k * SP + u + v];
+            const Raw x = raw[k * SP + u + v];
             const float wu = s0 + u + v < S ? w[v] : 0.f;
-            acc[k][0] = fmaf(__uint_as_float(x[0] << 16), wu, acc[k][0]);
-            acc[k][1] = fmaf(__uint_as_float(x[0] & 0xffff0000u), wu, acc[k][1]);
-            acc[k][2] = fmaf(__uint_as_float(x[1] << 16), wu, acc[k][2]);
-            acc[k][3] = fmaf(__uint_as_float(x[1] & 0xffff0000u), wu, acc[k][3]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              unsigned bits;
+              if constexpr (FINE) bits = x[e];
+              else bits = (e & 1) ? x[e / 2] & 0xffff0000u : x[e / 2] << 16;
+              acc[k][e] = fmaf(__uint_as_float(bits), wu, acc[k][e]);
+            }
           }
         }
       }
@@ -906,11 +920,10 @@ struct Plan {
   static_assert(THREADS >= JK_MAX_TREE, "one thread per tree node in the prologue");
 };
 
-// MSH: the merge of the splits in this kernel (0: none, a second launch or nothing to merge; see merge_rows).  The host
-// picks the instance, so that a kernel holds the code of one merge: with all four behind a switch (3400 instructions, and
+// MERGE: see merge_of.  The host picks the instance, so that a kernel holds the code of one merge: with all four behind a switch (3400 instructions, and
 // 113 - 146 scalar registers spilled, some of them in front of the tile loop) a layer of an 8B model, 4096 keys in sixteen
 // splits, took 15.2 us, and 14.7 like this.
-template <int D, int WM, int WN, int KT, bool PAGED, bool DEEP, int MSH>
+template <int D, int WM, int WN, int KT, bool PAGED, bool DEEP, int MERGE>
 __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<D, WM, WN, KT, PAGED, DEEP>::REG_WGS)) void tva_bf16_kernel(
     const KParams p) {
   using G_ = Geo<D>;
@@ -922,6 +935,8 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
   constexpr int STAGE_BYTES = P_::STAGE_BYTES;
   constexpr int DMA_PER_ROUND = TPR * LaneChunks<D, NW>::N;  // transfers a wave issues per round
   static_assert(NR >= 2 && (NR - 2) * DMA_PER_ROUND <= 63, "wave arrangement");
+
+  constexpr bool FINE = MERGE == 1 || MERGE == 2;  // partials merged here are fp32
 
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];  // the kernel has no other LDS: offset 0
   unsigned char* ring = smem;
@@ -1380,18 +1395,47 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
     // stored as it is, every instruction would touch 32 rows with 16 bytes each.  So the wave
     // first lays its 32 finished rows out in LDS as bf16 (a private patch behind the parked
     // columns) and reads them back row-wise: 16 lanes x 16 bytes per row, whole 128-byte lines
-    // per store.  Holds the final result (no splits) or the split's partial in bf16 (the
-    // running max and sum stay fp32): partials are written, flushed and read back once per
-    // split, and are the largest avoidable traffic of a call.
-    const float mul = splits == 1 ? 1.f / lsum : 1.f;  // lsum > 0: every row sees at least its own tree key
+    // per store.  Holds the final result (no splits) or the split's partial, in fp32 or in bf16
+    // (AttnPlan::fine; the running max and sum are always fp32).
+    const bool whole = MERGE == 0 && splits == 1;
+    const float mul = whole ? 1.f / lsum : 1.f;  // lsum > 0: every row sees at least its own tree key
     const long long prow0 = ((long long)unit_id * splits + split) * p.m_pad + qtile * QROWS + wm * kWaveRows;
-    if (splits > 1 && row_ok_e && g_e == 0) {
+    if (!whole && row_ok_e && g_e == 0) {
       if (p.through & 2) dev::store_through(p.part_ml + prow0 + c32_e, dev::store_u32x2{__float_as_uint(mx), __float_as_uint(lsum)});
       else p.part_ml[prow0 + c32_e] = make_float2(mx, lsum);
     }
     unsigned char* patch = smem + P_::OBUF_BYTES + wm * P_::PATCH_BYTES;
+    unsigned char* prow = patch + c32_e * P_::PATCH_LD;
+    constexpr int CPR = G_::CPR;             // 16-byte chunks per row
+    constexpr int RPI = 64 / CPR;            // rows per store instruction
+    const int chunk = lane_e % CPR, rsub = lane_e / CPR;
+    const int rows_valid = M - (qtile * QROWS + wm * kWaveRows);  // rows of this wave that exist (32 or more: all)
+    if (FINE || (MERGE == 0 && !whole && (p.through & 4))) {
+      // the split's partial in fp32: half of the columns at a time, as many bytes a row as all of them in bf16
+      unsigned char* dst0 = reinterpret_cast<unsigned char*>(p.part_o) + ((prow0 + rsub) * D + chunk * 4) * 4;
+      const unsigned char* src0 = patch + rsub * P_::PATCH_LD + chunk * 16;
+      const bool thr = p.through & 1;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int db = 0; db < DB / 2; ++db)
+#pragma unroll
+          for (int q4 = 0; q4 < 4; ++q4) {
+            const floatx16& o = st.o[h * (DB / 2) + db];
+            *reinterpret_cast<float4*>(prow + (32 * db + 8 * q4 + 4 * g_e) * 4) = make_float4(o[4 * q4], o[4 * q4 + 1], o[4 * q4 + 2], o[4 * q4 + 3]);
+          }
+#pragma unroll
+        for (int k = 0; k < kWaveRows / RPI; ++k) {
+          const u32x4 v = *reinterpret_cast<const u32x4*>(src0 + k * RPI * P_::PATCH_LD);
+          unsigned char* dst = dst0 + k * RPI * D * 4 + h * D * 2;
+          if (k * RPI + rsub < rows_valid) {
+            if (MERGE == 0 && thr) dev::store_through(dst, v);
+            else *reinterpret_cast<u32x4*>(dst) = v;
+          }
+        }
+      }
+    } else {
     {
-      unsigned char* prow = patch + c32_e * P_::PATCH_LD;
       // (a lone wave per SIMD issues an instruction every five to eight cycles: this part of the
       // kernel is bound by its instruction count, hence the uniform branches around whole loops
       // rather than conditions inside them)
@@ -1411,15 +1455,11 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
             *reinterpret_cast<uint2*>(prow + (32 * db + 8 * q4 + 4 * g_e) * 2) = pk;
           }
       };
-      if (splits == 1) to_patch(std::true_type{});
+      if (whole) to_patch(std::true_type{});
       else to_patch(std::false_type{});
     }
     // (same wave wrote and reads: LDS operations of a wave complete in order)
-    constexpr int CPR = G_::CPR;             // 16-byte chunks per row
-    constexpr int RPI = 64 / CPR;            // rows per store instruction
-    const int chunk = lane_e % CPR, rsub = lane_e / CPR;
-    const int rows_valid = M - (qtile * QROWS + wm * kWaveRows);  // rows of this wave that exist (32 or more: all)
-    if (splits == 1) {
+    if (whole) {
 #pragma unroll
       for (int k = 0; k < kWaveRows / RPI; ++k) {
         const int rr = k * RPI + rsub;                               // row of the wave
@@ -1455,8 +1495,9 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
         else store_rows(std::false_type{}, std::true_type{});
       }
     }
+    }
   }
-  if constexpr (MSH > 0) {
+  if constexpr (MERGE > 0) {
     // ---- merge of the group's splits in this kernel.  Every workgroup of the group owns the slice
     // of R = ceil(QROWS / splits) rows numbered like its split and merges it once all partials are
     // in L2.  Waiting is bounded: a workgroup that gives up records its slice in the group's mask
@@ -1476,9 +1517,9 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
       ma.part_o = late->part_o; ma.part_ml = late->part_ml; ma.out = late->out;
       ma.M = late->M; ma.m_pad = late->m_pad; ma.splits = late->splits; ma.G = late->G; ma.mg_g = late->mg_g;
       ma.o_sb = late->o_sb; ma.o_st = late->o_st; ma.o_sh = late->o_sh;
-      const int slice_rows = late->merge_rows, merge_shift = MSH < 5 ? MSH : late->merge_shift;
+      const int slice_rows = late->merge_rows, merge_shift = MERGE < 6 ? tva::merge_shift_of(MERGE) : late->merge_shift;
       const int tile_row0 = qtile * QROWS;
-      MergeThread mt = merge_prepare<D, THREADS, QROWS>(ma, unit_id, b, kv, split, slice_rows, merge_shift, tile_row0, tid_e);
+      MergeThread mt = merge_prepare<D, THREADS, QROWS, FINE>(ma, unit_id, b, kv, split, slice_rows, merge_shift, tile_row0, tid_e);
       JK_TS(7);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's partial stores have reached L2
       __syncthreads();
@@ -1536,13 +1577,13 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
         left_over &= ~(1ull << split);
         for (;;) {
           if (mt.row_lo < mt.row_hi) {  // (uniform)
-            merge_rows<D, THREADS, QROWS, MSH>(ma, mt, merge_shift, b, kv, tile_row0, tid_e, wbuf);
+            merge_rows<D, THREADS, QROWS, tva::merge_shift_of(MERGE), FINE>(ma, mt, merge_shift, b, kv, tile_row0, tid_e, wbuf);
             __syncthreads();  // wbuf is free again
           }
           if (left_over == 0ull) break;
           const int j = __ffsll((long long)left_over) - 1;
           left_over &= left_over - 1ull;
-          mt = merge_prepare<D, THREADS, QROWS>(ma, unit_id, b, kv, j, slice_rows, merge_shift, tile_row0, tid_e);
+          mt = merge_prepare<D, THREADS, QROWS, FINE>(ma, unit_id, b, kv, j, slice_rows, merge_shift, tile_row0, tid_e);
         }
       }
     }
@@ -1556,7 +1597,7 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
 template <int D, int WM, int WN, int KT, bool PAGED, bool DEEP>
 hipError_t launch_one(const KParams& kp, hipStream_t stream) {
   using P_ = Plan<D, WM, WN, KT, PAGED, DEEP>;
-  auto kern = tva_bf16_kernel<D, WM, WN, KT, PAGED, DEEP, JK_MSH>;
+  auto kern = tva_bf16_kernel<D, WM, WN, KT, PAGED, DEEP, JK_MERGE>;
   static LdsLimitRaised raised;
   if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), P_::SMEM, raised); e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(kp.total_wgs), dim3(P_::THREADS), P_::SMEM, stream, kp);
@@ -1575,14 +1616,14 @@ hipError_t launch_arranged(const KParams& kp, const AttnPlan& pl, hipStream_t st
 #ifdef JK_TIMING
 #define JK_CAT2(a, b) a##b
 #define JK_CAT(a, b) JK_CAT2(a, b)
-extern "C" int JK_CAT(jk_debug_read_timing, JK_MSH)(unsigned long long* host, size_t n) {
+extern "C" int JK_CAT(jk_debug_read_timing, JK_MERGE)(unsigned long long* host, size_t n) {
   return (int)hipMemcpyFromSymbol(host, HIP_SYMBOL(g_jk_ts), n * sizeof(unsigned long long));
 }
 #endif
 
 namespace tva {
 template <>
-hipError_t launch_merged<JK_MSH>(const KParams& kp, int head_dim, const AttnPlan& pl, hipStream_t stream) {
+hipError_t launch_merged<JK_MERGE>(const KParams& kp, int head_dim, const AttnPlan& pl, hipStream_t stream) {
   const bool paged = kp.block_table != nullptr;
   if (head_dim == 128) return paged ? launch_arranged<128, true>(kp, pl, stream) : launch_arranged<128, false>(kp, pl, stream);
   if (head_dim == 64) return paged ? launch_arranged<64, true>(kp, pl, stream) : launch_arranged<64, false>(kp, pl, stream);
@@ -1590,7 +1631,7 @@ hipError_t launch_merged<JK_MSH>(const KParams& kp, int head_dim, const AttnPlan
 }
 }  // namespace tva
 
-#if JK_MSH == 0
+#if JK_MERGE == 0
 hipError_t launch_tva_bf16(const AttnArgs& a, const AttnPlan& pl, hipStream_t stream) {
   KParams kp;
   kp.q = static_cast<const uint16_t*>(a.q);
@@ -1640,6 +1681,8 @@ hipError_t launch_tva_bf16(const AttnArgs& a, const AttnPlan& pl, hipStream_t st
   // acknowledged after 0.7 us and read back in 0.4; stores through to memory take 1.3 and 1.0)
   const bool fused = pl.fused && pl.splits > 1;
   if (fused) kp.through = 0;
+  if (pl.fine) kp.through |= 4;
+  if (fused && (pl.fine != 0) != (pl.splits <= 3)) return hipErrorInvalidValue;  // (what the instances assume)
   kp.sync = a.sync;
   // (a lane per sequence in the ranking; the XCDs get whole units)
   const long long units = (long long)d.batch * d.n_kv_heads;
@@ -1653,13 +1696,14 @@ hipError_t launch_tva_bf16(const AttnArgs& a, const AttnPlan& pl, hipStream_t st
   kp.merge_rows = (pl.q_rows + pl.splits - 1) / pl.splits;
   kp.merge_shift = 0;
   while ((1 << kp.merge_shift) < pl.splits) ++kp.merge_shift;
-  if (!fused) return tva::launch_merged<0>(kp, d.head_dim, pl, stream);
-  switch (kp.merge_shift) {
+  switch (fused ? tva::merge_of(pl.splits) : 0) {
+    case 0: return tva::launch_merged<0>(kp, d.head_dim, pl, stream);
     case 1: return tva::launch_merged<1>(kp, d.head_dim, pl, stream);
     case 2: return tva::launch_merged<2>(kp, d.head_dim, pl, stream);
     case 3: return tva::launch_merged<3>(kp, d.head_dim, pl, stream);
     case 4: return tva::launch_merged<4>(kp, d.head_dim, pl, stream);
-    default: return tva::launch_merged<5>(kp, d.head_dim, pl, stream);  // seventeen splits and more
+    case 5: return tva::launch_merged<5>(kp, d.head_dim, pl, stream);
+    default: return tva::launch_merged<6>(kp, d.head_dim, pl, stream);
   }
 }
 #endif

@@ -4,6 +4,8 @@
 // which is the same softmax-weighted sum the unsplit definition gives
 // (Section 2.1 step 2 of the paper defines the result; the split is an
 // implementation device of this library).
+#include <type_traits>
+
 #include "jk_device.h"
 #include "jk_internal.h"
 
@@ -157,7 +159,7 @@ __global__ __launch_bounds__(256) void tva_combine_kernel(CParams p) {
 // (scalar) loads and every lane derives the same weights; splits go by in chunks of 8 with
 // all of a chunk's loads in flight together, merged with a running maximum.  Grid: x = unit
 // (sequence, KV head), y = blocks of 4 rows.
-template <int D>
+template <int D, bool FINE>
 __global__ __launch_bounds__(256) void tva_combine_bf16_kernel(CParams p) {
   constexpr int CPL = D / 64;
   static_assert(CPL == 1 || CPL == 2, "head_dim 64 or 128");
@@ -168,23 +170,27 @@ __global__ __launch_bounds__(256) void tva_combine_bf16_kernel(CParams p) {
   if (m >= p.M) return;
   const int S = p.splits;
   const long long prow0 = (long long)unit * S * p.m_pad + m;
-  const uint16_t* po = reinterpret_cast<const uint16_t*>(p.part_o) + prow0 * D + CPL * lane;
+  typedef std::conditional_t<FINE, float, uint16_t> Part;
+  typedef std::conditional_t<FINE, float2, unsigned> Raw;  // a lane's columns (one of them: in the first place, or the low half)
+  const Part* po = reinterpret_cast<const Part*>(p.part_o) + prow0 * D + CPL * lane;
   const float2* pml = p.part_ml + prow0;
   const long long po_step = (long long)p.m_pad * D;  // one split further
 
   float m_run = -INFINITY, l_run = 0.f, acc0 = 0.f, acc1 = 0.f;
   for (int s0 = 0; s0 < S; s0 += 8) {
     float2 ml[8];
-    unsigned raw[8];
+    Raw raw[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const bool ok = s0 + u < S;
       ml[u] = ok ? pml[(long long)(s0 + u) * p.m_pad] : make_float2(-INFINITY, 0.f);
       if (!(ml[u].y > 0.f)) ml[u] = make_float2(-INFINITY, 0.f);  // an empty split carries no weight
-      raw[u] = 0u;
+      raw[u] = Raw{};
       if (ok) {
-        const uint16_t* src = po + (long long)(s0 + u) * po_step;
-        raw[u] = CPL == 2 ? *reinterpret_cast<const unsigned*>(src) : (unsigned)*src;
+        const Part* src = po + (long long)(s0 + u) * po_step;
+        if constexpr (CPL == 2) raw[u] = *reinterpret_cast<const Raw*>(src);
+        else if constexpr (FINE) raw[u].x = *src;
+        else raw[u] = *src;
       }
     }
     float cm = ml[0].x;
@@ -202,8 +208,14 @@ __global__ __launch_bounds__(256) void tva_combine_bf16_kernel(CParams p) {
       const float w = __builtin_amdgcn_exp2f(ml[u].x - m_use);  // exp2(-inf) = 0 for empty or absent splits
       l_run = fmaf(ml[u].y, w, l_run);
       if (w != 0.f) {  // an unused split may hold anything
-        const float v0 = __uint_as_float(raw[u] << 16);  // the lane's first (or only) column sits in the low half
-        const float v1 = __uint_as_float(raw[u] & 0xffff0000u);
+        float v0, v1;
+        if constexpr (FINE) {
+          v0 = raw[u].x;
+          v1 = raw[u].y;
+        } else {
+          v0 = __uint_as_float(raw[u] << 16);
+          v1 = __uint_as_float(raw[u] & 0xffff0000u);
+        }
         acc0 = fmaf(v0, w, acc0);
         if (CPL == 2) acc1 = fmaf(v1, w, acc1);
       }
@@ -241,10 +253,9 @@ hipError_t launch_tva_combine(const AttnArgs& a, const AttnPlan& pl, hipStream_t
   cp.mg_g = magic(cp.G);
   if (d.dtype == JK_BF16) {
     const dim3 grid((unsigned)(d.batch * d.n_kv_heads), (unsigned)((pl.m_rows + 3) / 4));
-    if (d.head_dim == 128)
-      hipLaunchKernelGGL((tva_combine_bf16_kernel<128>), grid, dim3(256), 0, stream, cp);
-    else
-      hipLaunchKernelGGL((tva_combine_bf16_kernel<64>), grid, dim3(256), 0, stream, cp);
+    auto* kernel = d.head_dim == 128 ? (pl.fine ? tva_combine_bf16_kernel<128, true> : tva_combine_bf16_kernel<128, false>)
+                                     : (pl.fine ? tva_combine_bf16_kernel<64, true> : tva_combine_bf16_kernel<64, false>);
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, cp);
   } else {
     const int tpr = 2 * (d.head_dim / 4);
     const int rpw = 256 / (tpr > 64 ? tpr : 64);

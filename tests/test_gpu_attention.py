@@ -439,6 +439,32 @@ def test_bf16_every_merge_instance(splits, D, arr, T):
     assert jk.last_device_error(ws) in (0, jk.JK_DEVERR_MERGE_WAIT)   # (0: every partner was there at the first look)
 
 
+@pytest.mark.parametrize("kw,arr,splits,fused", [
+    (dict(n_q_heads=8, n_kv_heads=8, prefix_len=1500, n_tree=40), (2, 2), (1, 2, 3), 1),
+    (dict(n_q_heads=32, n_kv_heads=8, prefix_len=900, n_tree=30), (4, 1), (1, 2, 3), 1),
+    (dict(n_q_heads=8, n_kv_heads=8, prefix_len=1500, n_tree=40, head_dim=64), (2, 2), (1, 2, 3), 0),
+    (dict(n_q_heads=32, n_kv_heads=8, prefix_len=900, n_tree=30), (4, 1), (1, 2, 3), 0),
+    (dict(batch=22, n_q_heads=8, n_kv_heads=8, prefix_len=400, n_tree=6), (2, 2), (1, 3, 5, 9), 0),   # most CUs undivided
+    (dict(batch=22, n_q_heads=8, n_kv_heads=8, prefix_len=400, n_tree=6, head_dim=64), (2, 2), (1, 4), 0),
+])
+def test_bf16_few_splits_are_as_exact_as_one(kw, arr, splits, fused):
+    """Partial results of two or three splits, and of any number where the undivided grid fills most of the card, are
+    fp32: the error against fp64 is that of an undivided call (the final rounding to bf16 and the softmax weights'),
+    where a rounding of the partials would add 20 % to it."""
+    cfg = _cfg("c3_llama3_8b", **kw)
+    T, L = cfg.n_tree, cfg.prefix_len
+    par = np.array([[max(-1, (i - 1) // 2) for i in range(T)]] * cfg.batch, dtype=np.int32)
+    x = {k: round_to_bf16(v) for k, v in attention_inputs(cfg, scale_mult=np.sqrt(float(cfg.head_dim))).items()}
+    ref = oracle_attention(**x, parent=par, prefix_len=[L] * cfg.batch)
+    errs = []
+    for s in splits:
+        tune("attn_wm", arr[0]); tune("attn_wn", arr[1]); tune("attn_splits", s)
+        got, _, plan = _attn_with_ws(x, par, [L] * cfg.batch, fused)
+        assert plan["splits"] == s and plan["fused"] == (fused if s > 1 else 0)
+        errs.append(np.sqrt(((got - ref) ** 2).sum() / (ref ** 2).sum()))
+    assert max(errs[1:]) <= 1.05 * errs[0], errs
+
+
 def test_bf16_merge_inside_the_kernel_when_the_wait_expires():
     """spin_limit 0: no workgroup waits for its partners.  Every workgroup but a group's last arriver records its
     slice and leaves, the last arriver merges them all: same bits as the normal run, the workspace's error word
