@@ -132,8 +132,9 @@ size_t jk_tree_verify_attention_workspace(const jk_attn_desc* desc, int32_t max_
  * Accumulation is fp32; JK_BF16 rounds the softmax weights to bf16 before the
  * value product.  When the key range is split over several workgroups, the partial
  * outputs that are merged are fp32 for two and three splits (and for more where the
- * workgroups of an undivided call would fill most of the card), up to 64 MB of them,
- * and rounded to bf16 otherwise (running maxima and sums are always fp32). */
+ * workgroups of an undivided call would fill most of the card) unless that would cost
+ * a noticeable part of the call, and rounded to bf16 otherwise (running maxima and
+ * sums are always fp32). */
 jk_status jk_tree_verify_attention(const jk_attn_desc* desc, const void* q, const void* k_cache,
                                    const void* v_cache, const void* k_tree, const void* v_tree,
                                    const int32_t* parent, const int32_t* prefix_len,

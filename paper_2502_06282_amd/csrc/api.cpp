@@ -124,16 +124,22 @@ size_t most_part_rows(const jk_attn_desc& d, int max_prefix_len) {  // over all 
 // an undivided one (error against fp64 2.9e-3 instead of 2.35e-3 of its norm for N(0, 1) inputs, however many splits; with
 // fp32 partials 2.3e-3), but they are the largest avoidable traffic of a call, and half of it.  They are fp32 for two and
 // three splits, and for any number where the row tiles would have given most CUs a workgroup undivided: there the keys are
-// divided for the balance of a batch, not because the card would be idle; never more than 64 MB of them.  What it costs
-// (us, bf16 / fp32): sixteen ragged sequences of up to 4096 keys, 8B, two splits 62.4 / 65.9; 13B, four sequences, three
-// splits 40.4 / 42.0; 7B, six sequences of 2048, two splits 47.8 / 49.2; two sequences of 300 keys 9.36 / 9.47; and, left
-// in bf16, eight sequences, four splits 36.6 / 39.7.
+// divided for the balance of a batch, not because the card would be idle.  Where the undivided grid is more than one turn
+// already they are only if that adds no more than 3 % to the estimated time; and there are never more than 64 MB of them.
+// (Of 40000 drawn shapes 1698 run divided that an earlier plan left undivided; 1524 of those have fp32 partials.)  What it
+// costs (us, bf16 / fp32): sixteen ragged sequences of up to 4096 keys, 8B, two splits 62.4 / 65.9; 13B, four sequences,
+// three splits 40.4 / 42.0; 7B, six sequences of 2048, two splits 47.8 / 49.2; two sequences of 300 keys 9.36 / 9.47; and,
+// left in bf16, eight sequences, four splits 36.6 / 39.7, twenty-four, two splits and a second launch 144 / 148 - 160.
 constexpr int kFineSplits = 3;
 constexpr size_t kFineBytes = (size_t)64 << 20;
-bool fine_partials(const AttnPlan& pl, long long units, int head_dim) {
-  if (pl.splits < 2 || (size_t)units * pl.splits * pl.m_pad * head_dim * sizeof(float) > kFineBytes) return false;
+bool fine_partials(const AttnPlan& pl, long long units, int head_dim, double added_us, double call_us) {
+  if (pl.splits < 2) return false;
+  if (pl.fused) return pl.splits <= kFineSplits;  // (what the kernel's instances assume; at most 512 workgroups: 34 MB)
   const int cus = device_cu_count();
-  return pl.splits <= kFineSplits || (!pl.fused && pl.n_qtiles == 1 && 16 * units >= 11 * cus && units <= cus);
+  const long long wgs = units * pl.n_qtiles;  // undivided
+  const bool balance = pl.n_qtiles == 1 && 16 * wgs >= 11 * cus && wgs <= cus;
+  return (pl.splits <= kFineSplits || balance) && (wgs <= cus || added_us <= 0.03 * call_us) &&
+         (size_t)units * pl.splits * pl.m_pad * head_dim * sizeof(float) <= kFineBytes;
 }
 
 bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_allowed, AttnPlan* pl) {
@@ -157,7 +163,7 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
     static const int kArr[][2] = {{2, 2}, {4, 1}};  // waves along rows x along keys
     bool forced_ok = false;
     for (const auto& a : kArr) forced_ok |= (a[0] == forced_wm && a[1] == forced_wn);
-    double best_cost = 0.0;
+    double best_cost = 0.0, best_part_mb = 0.0;
     bool have = false;
     for (const auto& a : kArr) {
       const int wm = a[0], wn = a[1];
@@ -257,6 +263,7 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
         if (!have || cost < best_cost) {
           have = true;
           best_cost = cost;
+          best_part_mb = part_mb;
           pl->wm = wm; pl->wn = wn; pl->kt = kt; pl->q_rows = q_rows; pl->n_qtiles = n_qtiles; pl->splits = (int)s;
           pl->fused = can_fuse ? 1 : 0;
           pl->deep = deep ? 1 : 0;
@@ -266,7 +273,7 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
     if (!have) return false;
     pl->parts = pl->splits;
     pl->m_pad = pl->n_qtiles * pl->q_rows;
-    pl->fine = fine_partials(*pl, units, d.head_dim) ? 1 : 0;
+    pl->fine = fine_partials(*pl, units, d.head_dim, km.merge_kernel_per_mb * best_part_mb, best_cost) ? 1 : 0;
     // (the kernel ranks a batch with a lane per sequence, and the XCDs get whole units)
     pl->ranked = d.batch >= 2 && d.batch <= 64 && units % 8 == 0 ? 1 : 0;
   } else {
