@@ -374,9 +374,8 @@ jk_status jk_draft_heads(const jk_draft_heads_desc* desc, const void* f_top, con
  * layers; the gated form is this library's reading.)  The projections run
  * through the same MFMA kernel as jk_draft_heads with bf16 operands and fp32
  * accumulation; the hidden activation silu(gate)*up and the outputs are rounded
- * to bf16 once each.  Every expert that at least one row selected is evaluated
- * for all rows (its weights are streamed once either way; gathering rows would
- * cost more than the MFMAs it saves); experts that no row selected are skipped.
+ * to bf16 once each.  An expert is evaluated for the rows that selected it and for no
+ * others; the weights of experts that no row selected are not read.
  *
  *   rows        1..128;  d_model, d_ff multiples of 128 up to 65536;  n_experts 2..64
  *   u           device bf16 [rows][d_model], 16-byte aligned
