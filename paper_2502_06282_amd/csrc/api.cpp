@@ -71,11 +71,12 @@ bool shape_supported(const jk_attn_desc& d) {
 }
 }  // namespace
 
-// Constants of the attention plan's time estimate. All were fitted together to 2100 shapes drawn over batch 1 - 32,
-// 1 - 128 tree nodes, 2 - 40 KV heads, head_dim 64/128 and prefixes up to 32k, contiguous and paged, the K/V warm in
-// the caches or cold, each timed on an MI355X with every plan that could be the best one. The plan the estimate takes
-// is 2 % (geometric mean; 6 % at the 90th percentile) slower than the best of each shape's plans, runs of one plan
-// differing by about as much; the estimate before it, from sweeps of five shapes, was 10 % (28 %) off.
+// Constants of the attention plan's time estimate, fitted together to timed plans of drawn shapes (those timings were not
+// kept).  What they are worth is measured by profiles/attention_plan_times.py: over the 1000 shapes and 10968 plans of
+// profiles/attention_plan_times.csv (batch 1 - 32, 1 - 128 tree nodes, 2 - 40 KV heads, head_dim 64/128, prefixes up to
+// 32k) the plan the estimate takes is 1.4 % slower than the best one timed (geometric mean; 5 % at the 90th percentile,
+// 16 % at the 99th); runs of one plan differ by about 1 %.  The fit is of the whole estimate: single constants are near,
+// not at, what a part takes when it is timed alone.
 struct PlanModel {
   double round_4x1 = 1.13, round_4x1_d64 = 0.84;  // us per round (a pair of 32-key tiles) of a 4x1 workgroup alone on its CU
   double round_2x2 = 0.90, round_2x2_d64 = 0.58;  // us per round (one tile per key column) of a 2x2 workgroup
@@ -84,7 +85,7 @@ struct PlanModel {
   double far_bytes = 9.0e7;     // K/V beyond this come from HBM, not from a cache: the longer latency shows with
   double far_2x2 = 1.24, far_2x2_shared = 1.11, far_deep = 1.02;  // the 2x2 arrangement's one round in flight
   double stream = 7.0e6;        // bytes per us all CUs together
-  double startup = 5.7;         // us before a workgroup's first K/V data are there, and after its last
+  double startup = 5.7;         // us of a call outside its rounds: launch, first K/V data (2.6 - 2.8 us after it), epilogue
   double startup_4x1 = 1.03;    // (more for twice the rows)
   double turn_0 = 0.35, turn_step = 0.14, turn_min = 0.02;  // how much of a last, partly filled turn of two workgroups per CU
                                 // shows: a third after one full turn, less with each further one (they drift apart)
