@@ -29,13 +29,13 @@ if ROOT not in sys.path:
 HBM_PEAK_GBPS = 8000.0
 MFMA_BF16_PEAK_TFLOPS = 2500.0
 
-# HBM bytes per launch of the attention kernel (tva_bf16_kernel; for c5 without its merge kernel) from
+# HBM bytes per attention call (tva_bf16_kernel; for c5 with the merge kernel behind it) from
 # rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs (KiB per dispatch), each scaled by the same counter's reading
 # for a 256 MiB device copy (factors 2.00 and 1.00); source: profiles/<workload>_attention_and_acceptance.md.
 # {workload: bytes}; None for workloads that were not measured.
-MEASURED_TRAFFIC = {"c2_vicuna7b": 26704104, "c3_llama3_8b": 34393582, "c4_llama2_13b": 191863442,
-                    "c5_llama2_70b": 714200829, "c6_chain_sps": 269956059,
-                    "c7_static_tree": 77957017}
+MEASURED_TRAFFIC = {"c2_vicuna7b": 24614686, "c3_llama3_8b": 34364172, "c4_llama2_13b": 207000971,
+                    "c5_llama2_70b": 774242447, "c6_chain_sps": 272082512,
+                    "c7_static_tree": 77767665}
 
 
 def attn_bytes(cfg) -> int:
