@@ -521,7 +521,8 @@ int32_t jk_last_device_error(const void* workspace);
  * into workgroups on the current device (for reports and tests; the plan is the library's own
  * business and may change): plan_out[0..5] = waves along the query rows, waves along the keys,
  * 32-key tiles per wave and round, row tiles, key splits, 1 if the splits are merged inside the
- * attention kernel (0: by a second kernel; always 0 for the fp32 path and for one split). */
+ * attention kernel (0: by a second kernel; always 0 for the fp32 path and for one split).  The fp32 path
+ * reports tiles of one row and ranges of 1024 keys; its workgroups take 16 rows of a range or of a part of it. */
 jk_status jk_tree_verify_attention_plan(const jk_attn_desc* desc, int32_t max_prefix_len, int32_t* plan_out);
 
 /* Once per device and process, before the first jk_tree_verify_attention call that should merge

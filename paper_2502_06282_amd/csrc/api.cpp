@@ -252,8 +252,9 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
           for (long long u = 0; u < units && can_fuse; ++u)
             can_fuse = (u * per_unit) / per_xcd == ((u + 1) * per_unit - 1) / per_xcd;
         }
-        // Partials (bf16) are merged inside the kernel where that is possible (an exchange through the XCD's L2 instead
-        // of a second launch: 0.2 - 1.8 us less at every number of splits).
+        // Partials are merged inside the kernel where that is possible: an exchange through the XCD's L2 instead of a
+        // second launch, 0.2 - 4.8 us less over five shapes with 2 - 32 splits, but 0.4 - 1.1 us more for two or three
+        // splits of 2x2 workgroups with a head dimension of 64.
         const double part_mb = 1.0e-6 * (double)units * s * pl->m_rows * d.head_dim * 2.0;
         const double fused_us = km.merge_fused_fixed + km.merge_fused_per_mb * part_mb;
         const double kernel_us = km.merge_kernel_fixed + km.merge_kernel_per_mb * part_mb;
@@ -283,7 +284,7 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
     pl->ranked = 0;
     pl->deep = 0;
     pl->wm = pl->wn = pl->kt = 1;
-    pl->q_rows = 1;
+    pl->q_rows = 1;  // (as reported; the kernel's workgroups take 16 rows and the parts below)
     pl->n_qtiles = pl->m_rows;
     pl->m_pad = pl->m_rows;
     const long long keys = (long long)max_prefix_len + d.n_tree;

@@ -388,7 +388,7 @@ def _attn_with_ws(x, par, plens, fused, ws=None, max_prefix_len=None):
 ])
 def test_bf16_merge_inside_the_kernel_agrees_with_the_merge_kernel(name, kw, arr, splits):
     """The key splits of a row tile are merged either by a second kernel or, when the grid allows it, by the
-    attention kernel's own workgroups meeting in their XCD's L2.  Both merge the same bf16 partials in fp32 (in a
+    attention kernel's own workgroups meeting in their XCD's L2.  Both merge the same partials in fp32 (in a
     different order of operations): the bf16 outputs may differ in the last place of an element, no more, and both
     are within tolerance of the oracle."""
     cfg = _cfg(name, **kw)

@@ -181,7 +181,7 @@ def test_attention_plans_of_random_shapes_keep_their_invariants(lib):
             assert lib.jk_tree_verify_attention_workspace(ctypes.byref(d), L) >= need, what
         for k in (b"attn_wm", b"attn_wn", b"attn_splits"):
             lib.jk_set_tuning(k, 0)
-        # fp32 path: one workgroup per query row and 1024-key split; 64 splits at most
+        # fp32 path: reported as tiles of one query row and ranges of 1024 keys; 64 ranges at most
         for L, T in ((0, 1), (1000, 24), (1024, 1), (5000, 60), (65536 - 60, 60)):
             d = _desc(2, T, 8, 4, 64, L, dtype=1)
             out = (ctypes.c_int32 * 6)()
