@@ -91,7 +91,7 @@ def _unit_jobs(cfg, x, par):
 def cpu_baseline(cfg, par, x0, acc, budget_s=8.0):
     """The oracle as it stands on a bounded sample of the same workload, in the metric's unit (algorithmic
     attention bytes per second): (a) one thread: the attention of whole layers (all heads) until about
-    `budget_s` seconds are spent, and one acceptance walk; (b) all host cores this box gives a one-GPU job
+    `budget_s` seconds are spent, and one acceptance walk; (b) all host cores this machine gives a one-GPU job
     (at most 16 processes), one (sequence, KV head) unit of a layer per task, for about as long.  The
     all-cores figure is the reported `value`; the one-thread figure sits beside it."""
     import multiprocessing as mp
@@ -361,7 +361,7 @@ def main():
 
     probe = commit = deep = acc_b2b = None
     if not args.no_extras:
-        # ceiling for one layer's K/V on this machine: a kernel that only streams as many bytes as one
+        # ceiling for one layer's K/V on this card: a kernel that only streams as many bytes as one
         # layer's K and V prefix (16.8 MB), from its own ring of buffers larger than the Infinity Cache
         sink = torch.zeros(4, dtype=torch.int32, device=dev)
         probe_bytes = 2 * layers[0]["k_cache"].numel() * layers[0]["k_cache"].element_size()
