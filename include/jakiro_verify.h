@@ -519,10 +519,11 @@ int32_t jk_last_device_error(const void* workspace);
 
 /* How the next jk_tree_verify_attention(_paged) call with this descriptor and bound would be cut
  * into workgroups on the current device (for reports and tests; the plan is the library's own
- * business and may change): plan_out[0..5] = waves along the query rows, waves along the keys,
- * 32-key tiles per wave and round, row tiles, key splits, 1 if the splits are merged inside the
- * attention kernel (0: by a second kernel; always 0 for the fp32 path and for one split).  The fp32 path
- * reports tiles of one row and ranges of 1024 keys; its workgroups take 16 rows of a range or of a part of it. */
+ * business and may change): plan_out[0..5] = waves of 32 rows along the query rows (8: the kernel
+ * of four waves with 64 rows each), waves along the keys, 32-key tiles per wave and round, row
+ * tiles, key splits, 1 if the splits are merged inside the attention kernel (0: by a second
+ * kernel; always 0 for the fp32 path and for one split).  The fp32 path reports tiles of one row
+ * and ranges of 1024 keys; its workgroups take 16 rows of a range or of a part of it. */
 jk_status jk_tree_verify_attention_plan(const jk_attn_desc* desc, int32_t max_prefix_len, int32_t* plan_out);
 
 /* Once per device and process, before the first jk_tree_verify_attention call that should merge
@@ -538,10 +539,11 @@ jk_status jk_init(void* hip_stream);
 /* Overrides for experiments and tests; nothing in normal use needs them.  The library's launch
  * plans are functions of the descriptors and the device; these knobs force parts of them.
  * Process-wide, not thread-safe against concurrent calls.  Names: "attn_wm", "attn_wn" (wave
- * arrangement of the bf16 attention kernel: 4x1 or 2x2; 0 = automatic), "attn_splits" (key
- * splits, 0 = automatic), "attn_fused" (-1 automatic, 0 never merge inside the kernel, 1 whenever
- * the grid allows it), "attn_deep" (-1 automatic, 0 never use the deeper K/V ring of the 2x2
- * arrangement, 1 whenever one workgroup per CU is planned), "accept_single" (1: one-workgroup sampling walk), "spin_limit" (polls of
+ * arrangement of the bf16 attention kernel: 4x1 or 2x2, or 8x1 for four waves of 64 rows each; 0 =
+ * automatic), "attn_splits" (key splits, 0 = automatic), "attn_fused" (-1 automatic, 0 never merge
+ * inside the kernel - which keeps the 8x1 arrangement out of automatic plans, its splits merge in
+ * no other way -, 1 whenever the grid allows it), "attn_deep" (-1 automatic, 0 never use the deeper
+ * K/V ring of the 2x2 arrangement, 1 whenever one workgroup per CU is planned), "accept_single" (1: one-workgroup sampling walk), "spin_limit" (polls of
  * the bounded waits; -1 default, 0 = give up at once: the give-up paths run with every kernel
  * ending normally), "verbose" (1: print attention plans to stderr).  The same knobs are seeded
  * once, when the library is loaded, from the environment variables JK_ATTN_WM, JK_ATTN_WN,

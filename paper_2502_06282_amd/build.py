@@ -15,7 +15,10 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libjakiro_verify.so")
 NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["api.cpp", "tva_f32.hip", "tva_combine.hip", "accept.hip", "accept_coop.hip", "commit.hip",
-           "draft_head.hip", "draft_tree.hip", "stream_gemm.hip"]
+           "draft_head.hip", "draft_tree.hip", "stream_gemm.hip", "tva_wide.hip"]
+# matrix results in ordinary registers: by default a kernel of more than 256 registers keeps all of them in accumulation
+# registers, which the vector unit cannot read (32 moves per tile for the scores of tva_wide.hip)
+UNIT_FLAGS = {"tva_wide.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 MERGES = 7  # tva_bf16.hip is compiled once for each of its merges (JK_MERGE)
 # packed-fp32 code generation is switched off for all device code
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -51,7 +54,7 @@ def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(OBJ, exist_ok=True)
     units = [("tva_bf16.hip", f"tva_bf16_{m}.o", [f"-DJK_MERGE={m}"]) for m in range(MERGES)]
-    units += [(s, os.path.splitext(s)[0] + ".o", []) for s in SOURCES]
+    units += [(s, os.path.splitext(s)[0] + ".o", UNIT_FLAGS.get(s, [])) for s in SOURCES]
     objects = [os.path.join(OBJ, o) for _, o, _ in units]
     native_obj = os.path.join(OBJ, "native.o")
     native_cmd, torch_lib = _native_command(native_obj)

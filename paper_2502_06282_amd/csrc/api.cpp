@@ -72,9 +72,9 @@ bool shape_supported(const jk_attn_desc& d) {
 }  // namespace
 
 // Constants of the attention plan's time estimate, fitted together to timed plans of drawn shapes (those timings were not
-// kept).  What they are worth is measured by profiles/attention_plan_times.py: over the 1000 shapes and 10968 plans of
+// kept).  What they are worth is measured by profiles/attention_plan_times.py: over the 1000 shapes and 11146 plans of
 // profiles/attention_plan_times.csv (batch 1 - 32, 1 - 128 tree nodes, 2 - 40 KV heads, head_dim 64/128, prefixes up to
-// 32k) the plan the estimate takes is 1.4 % slower than the best one timed (geometric mean; 5 % at the 90th percentile,
+// 32k) the plan the estimate takes is 1.2 % slower than the best one timed (geometric mean; 5 % at the 90th percentile,
 // 16 % at the 99th); runs of one plan differ by about 1 %.  The fit is of the whole estimate: single constants are near,
 // not at, what a part takes when it is timed alone.
 struct PlanModel {
@@ -92,6 +92,15 @@ struct PlanModel {
   double merge_fused_fixed = 1.63, merge_fused_per_mb = 0.30;  // merge inside the kernel
   double merge_kernel_fixed = 2.1, merge_kernel_per_mb = 0.36; // second launch
   double merge_16 = 1.4;        // either way, for each 16 splits beyond the first (their loads go out in turns)
+  // 256 rows per workgroup (tva_wide.hip), one of them per CU: us per tile without a mask, per other tile (the first, tree
+  // and ragged ones, those that four does not divide), per turn of workgroups, per call, per level of the pairwise merge
+  // and per MB that changes hands there.  (Searched together for the least loss against the best of the timed plans of
+  // 1600 shapes, on average 3.1 % without this kernel, 1.1 % with it; a tile takes 0.55 us timed alone.)
+  double wide_tile = 0.44, wide_tile_d64 = 0.385, wide_slow = 1.06, wide_slow_d64 = 0.70;
+  double wide_hot = 0.31, wide_hot_tiles = 500.0;  // the clock falls under the matrix units' load: the tiles of a long call
+                                // take up to this much longer
+  double wide_stream = 1.0e7, wide_turn = 5.3, wide_call = 2.8, wide_level = 2.0, wide_merge_per_mb = 0.57;
+  double wide_margin = 1.02;    // (near ties go to the others)
 };
 
 namespace {
@@ -135,6 +144,7 @@ constexpr int kFineSplits = 3;
 constexpr size_t kFineBytes = (size_t)64 << 20;
 bool fine_partials(const AttnPlan& pl, long long units, int head_dim, double added_us, double call_us) {
   if (pl.splits < 2) return false;
+  if (pl.wm == 8) return true;
   if (pl.fused) return pl.splits <= kFineSplits;  // (what the kernel's instances assume; at most 512 workgroups: 34 MB)
   const int cus = device_cu_count();
   const long long wgs = units * pl.n_qtiles;  // undivided
@@ -161,19 +171,20 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
     const Tuning& tn = tuning();
     const int forced_wm = tn.attn_wm, forced_wn = tn.attn_wn, forced_s = tn.attn_splits;  // tuning overrides
     const int fused_mode = !fused_allowed ? 0 : tn.attn_fused;  // 0 never, 1 whenever possible, -1 when it pays
-    static const int kArr[][2] = {{2, 2}, {4, 1}};  // waves along rows x along keys
+    static const int kArr[][2] = {{2, 2}, {4, 1}, {8, 1}};  // waves along rows x along keys
     bool forced_ok = false;
     for (const auto& a : kArr) forced_ok |= (a[0] == forced_wm && a[1] == forced_wn);
     double best_cost = 0.0, best_part_mb = 0.0;
     bool have = false;
     for (const auto& a : kArr) {
       const int wm = a[0], wn = a[1];
+      if (wm == 8 && !forced_ok && (pl->m_rows <= 96 || tn.attn_fused == 0)) continue;  // (mostly padding rows; it has no second launch)
       if (forced_ok ? (wm != forced_wm || wn != forced_wn) : (wm > 2 && pl->m_rows <= 16 * wm)) continue;  // mostly padding rows
       const int q_rows = 32 * wm;
       const int n_qtiles = (pl->m_rows + q_rows - 1) / q_rows;
       const long long wgs = units * n_qtiles;
-      const int kt = wn == 1 ? 2 : 1;  // a lone key column pairs its tiles (hand-pipelined two-tile path)
-      const int max_by_tiles = n_tiles / (2 * wn * kt) > 0 ? n_tiles / (2 * wn * kt) : 1;  // >= 2 rounds per split
+      const int kt = wm == 4 ? 2 : 1;  // (4x1: tiles in pairs, the hand-pipelined two-tile path)
+      const int max_by_tiles = n_tiles >= 4 ? n_tiles / 4 : 1;  // at least two rounds of two tiles per split
       // every split count that leaves a split at least two rounds is priced
       const long long s_top = forced_s >= 1 && forced_s <= kMaxSplits ? 1 : (max_by_tiles < kMaxSplits ? max_by_tiles : kMaxSplits);
       for (long long sc = 1; sc <= s_top; ++sc) {
@@ -184,6 +195,7 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
         if (s < s_min) s = s_min;
         if (s > kMaxSplits) continue;
         if (s > 1 && forced_s < 1 && (size_t)(wgs * s * q_rows) > most_rows) continue;  // (one split always fits)
+        if (wm == 8 && s > 1 && (wgs * s > kMaxWideMerged || (size_t)wgs * s * q_rows * d.head_dim * sizeof(float) > kFineBytes)) continue;
         // rounds of the longest split: the 4x1 arrangement deals tiles (an odd last tile costs about
         // half a round), the 2x2 arrangement whole rounds
         double rounds;
@@ -247,7 +259,8 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
                         ((q_rows + s - 1) / s) * s_pow2 <= 64 * wm * wn &&
                         (double)units * s * n_qtiles * q_rows * d.head_dim * 2.0 < 2.0e9 &&
                         all_wgs <= (long long)slots * 2;  // (two of these workgroups fit a CU: all resident)
-        if (can_fuse) {
+        if (wm == 8) can_fuse = s > 1;  // (that kernel always merges its splits, wherever they run)
+        else if (can_fuse) {
           const long long per_unit = s * n_qtiles, per_xcd = (all_wgs + 7) / 8;
           for (long long u = 0; u < units && can_fuse; ++u)
             can_fuse = (u * per_unit) / per_xcd == ((u + 1) * per_unit - 1) / per_xcd;
@@ -261,7 +274,21 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
         const double merge_us = s <= 1 ? 0.0 : (can_fuse ? fused_us : kernel_us) + km.merge_16 * (double)((s - 1) / 16);
         const double start_us = km.startup * (wn == 1 ? km.startup_4x1 : 1.0);
         // (near ties go to the count that gives every CU a workgroup: 2 % for idle CUs)
-        const double cost = (body + merge_us + start_us) * (all_wgs < slots ? 1.02 : 1.0);
+        double cost = (body + merge_us + start_us) * (all_wgs < slots ? 1.02 : 1.0);
+        if (wm == 8) {
+          const int per = (int)((n_tiles + s - 1) / s), masked = n_tiles - max_prefix_len / kTileKeys;
+          const int plain = per > masked + 2 ? per - masked - 2 : 0;  // (the first tile, and those that four does not divide)
+          const double turns = (double)((all_wgs + slots - 1) / slots);
+          const double load = (all_wgs < slots ? (double)all_wgs / slots : 1.0) * plain / km.wide_hot_tiles;
+          const double loop = plain * (d.head_dim == 64 ? km.wide_tile_d64 : km.wide_tile) * (1.0 + km.wide_hot * (load < 1.0 ? load : 1.0)) +
+                              (per - plain) * (d.head_dim == 64 ? km.wide_slow_d64 : km.wide_slow);
+          const double stream = (double)units * kv_bytes / turns / km.wide_stream;
+          const double l2 = loop * loop, m2 = stream * stream;
+          int levels = 0;
+          while ((1 << levels) < s) ++levels;
+          cost = km.wide_margin * (km.wide_call + turns * (km.wide_turn + std::sqrt(std::sqrt(l2 * l2 + m2 * m2))) + km.wide_level * levels +
+                                   km.wide_merge_per_mb * 2.0 * part_mb * (double)(s - 1) / (double)s);
+        }
         if (!have || cost < best_cost) {
           have = true;
           best_cost = cost;
@@ -277,7 +304,7 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
     pl->m_pad = pl->n_qtiles * pl->q_rows;
     pl->fine = fine_partials(*pl, units, d.head_dim, km.merge_kernel_per_mb * best_part_mb, best_cost) ? 1 : 0;
     // (the kernel ranks a batch with a lane per sequence, and the XCDs get whole units)
-    pl->ranked = d.batch >= 2 && d.batch <= 64 && units % 8 == 0 ? 1 : 0;
+    pl->ranked = d.batch >= 2 && d.batch <= 64 && (pl->wm == 8 || units % 8 == 0) ? 1 : 0;
   } else {
     pl->fused = 0;
     pl->fine = 0;

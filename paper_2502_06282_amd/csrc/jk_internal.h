@@ -34,7 +34,7 @@ constexpr int kMaxTilesPerSplit = 1024;  // so that a split's page ids (paged ca
 // How one attention call is cut into workgroups.  Derived on the host from the
 // descriptor and the prefix bound only.
 struct AttnPlan {
-  int wm;          // waves along the query-row axis (32 rows each)
+  int wm;          // 32-row blocks along the query-row axis (8: four waves of two each, tva_wide.hip; else one per wave)
   int wn;          // waves along the key axis (key columns of a round)
   int kt;          // consecutive 32-key tiles a wave takes per round (1 or 2)
   int q_rows;      // query rows per workgroup = 32 * wm
@@ -58,6 +58,8 @@ struct AttnPlan {
 constexpr size_t kWsErrBytes = 256;
 constexpr int kMaxFusedGroups = 508;
 constexpr size_t kAttnHeaderBytes = kWsErrBytes + (size_t)kMaxFusedGroups * 64;  // 32 KiB
+constexpr int kWideWords = 13;       // of each line: words of the merge in tva_wide.hip, one per workgroup
+constexpr int kMaxWideMerged = kMaxFusedGroups * kWideWords;
 static_assert(kAttnHeaderBytes == JK_WORKSPACE_HEADER_BYTES, "public constant");
 
 // Device error bits (public names in jakiro_verify.h)
@@ -68,7 +70,7 @@ constexpr unsigned kDevErrBadTree = 1u, kDevErrBadToken = 2u, kDevErrBadPage = 4
 // variables when the library is loaded).  0 / -1 mean "let the library decide".
 struct Tuning {
   int attn_wm = 0, attn_wn = 0, attn_splits = 0;
-  int attn_fused = -1;     // -1 automatic, 0 never, 1 whenever the grid allows it
+  int attn_fused = -1;     // -1 automatic, 0 never (nor the kernel that cannot do without, tva_wide.hip), 1 whenever the grid allows it
   int attn_deep = -1;      // six-tile K/V ring of the 2x2 arrangement: -1 automatic, 0 never, 1 whenever one workgroup per CU is planned
   int accept_single = 0;   // 1: one-workgroup sampling walk
   int spin_limit = -1;     // polls of the bounded waits (-1: default)

@@ -1,0 +1,736 @@
+// Tree-masked verification attention, bf16 inputs, 64 query rows per wave (gfx950): the kernel of calls with many query
+// rows per KV head and long key ranges.  The problem, the packing of query rows, the tiles and their swizzles are those of
+// tva_bf16.hip; this one differs in how much a wave holds and in how it fills its SIMD.
+//
+// A workgroup of four waves has 256 query rows and a CU to itself: a wave holds two blocks of 32 rows, their queries and
+// accumulators (192 of its 512 registers), and every K or V operand read from LDS serves both.  With 32 rows per wave the
+// operand reads alone ask for all of the LDS bandwidth that a matrix pipe at full rate leaves (1 KB per 32 cycles and
+// SIMD), and every 128 rows stream K and V once more.
+//
+// A tile of 32 keys takes two phases.  In each the score product of one block, the value product of one block and the
+// softmax of one block run side by side, all independent of each other:
+//     A(t):  S1(t)    O1 += V(t-1) P1(t-1)    softmax of S0(t)
+//     B(t):  S0(t+1)  O0 += V(t)   P0(t)      softmax of S1(t)
+// written out slot by slot: a matrix instruction of 32 cycles, and the vector instructions and LDS reads that a lone wave
+// can issue beside it (about six).  K(t+1) and V(t) are read over the registers of K(t) and V(t-1) once those are used up.
+// What a slot may hold was measured (a lone wave per SIMD, cycles per 16 slots of 32): with a fused multiply-add, an
+// exponential and an addition 532; a bf16 dot product among them 796 (it runs on the matrix pipe, and not beside it).  So
+// a row's sum is one more matrix product: v_mfma_f32_16x16x32_bf16 with a matrix that adds up the eight weights of a lane
+// and of its partner in the other half-wave (16 cycles for 512 weights), of the weights as they are rounded.
+//
+// What bounds it: the vector instructions beside the matrix instructions, and the clock, which the card lowers under this
+// load (1.6 to 1.9 GHz).  A tile takes 1330 cycles, of which 1120 are matrix instructions.  Measured against the kernel of
+// four waves with 32 rows: 8 sequences of 16384 keys, 8 KV heads, 800 rows 476 -> 399 us; 16 sequences of at most 4096 keys
+// in pages, 8 KV heads, 240 rows 70 -> 59 us; 29 sequences of 10023 keys, 46 nodes, D = 64 255 -> 178 us.
+#include <type_traits>
+
+#include "tva_tiles.h"
+
+namespace jk {
+namespace {
+using tva::KParams;
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ void load_by_hand(u32x4& v, const void* src) {
+  asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(v) : "v"(src) : "memory");
+}
+__device__ __forceinline__ void load_by_hand(int& v, const void* src) {
+  asm volatile("global_load_dword %0, %1, off" : "=v"(v) : "v"(src) : "memory");
+}
+
+constexpr int kWideThreads = 256, kWideWaves = 4, kBlocks = 2, kWideRows = kBlocks * kWaveRows;
+
+template <int D, bool PAGED>
+struct WidePlan {
+  using G_ = Geo<D>;
+  static constexpr int HALF_BYTES = 64 * 1024;                   // K's half of the ring, in front of V's
+  static constexpr int NR = HALF_BYTES / G_::TILE_BYTES;         // tiles in the ring: 8 (D = 128) or 16
+  static constexpr int AHEAD = NR - 1;                           // tiles asked for in front of the one in use
+  static constexpr int RING_BYTES = 2 * HALF_BYTES;
+  static constexpr int QROWS = kWideWaves * kWideRows;
+  static constexpr int PATCH_LD = D * 2 + 16;                    // padded row of the store patches (after the loop)
+  static constexpr int PATCH_BYTES = kWaveRows * PATCH_LD;
+  static constexpr int PAGES_BYTES = PAGED ? kMaxPagesPerSplit * 4 : 0;
+  static constexpr int DUMP_BYTES = 2 * G_::TILE_BYTES;          // where transfers go that nobody needs
+  static constexpr int SMEM = RING_BYTES + DUMP_BYTES + JK_MAX_TREE * 16 + JK_MAX_TREE * 4 + 16 + PAGES_BYTES;
+  static_assert(kWideWaves * PATCH_BYTES <= RING_BYTES && SMEM <= 160 * 1024, "LDS plan");
+};
+
+// What a wave holds: two blocks of 32 query rows (a lane has row lane % 32 of each), and the operands in flight
+template <int D>
+struct WideState {
+  static constexpr int DK = Geo<D>::DK, DB = Geo<D>::DB;
+  bf16x8 q[kBlocks][DK];
+  floatx16 o[kBlocks][DB];
+  floatx4 l[kBlocks];       // row sums (four times the same)
+  float m[kBlocks], mu[kBlocks];  // reference of the row's weights in log2 units; 0 instead of -inf
+  floatx16 s[kBlocks];      // scores
+  floatx16 x[kBlocks];      // weights in fp32, on their way
+  bf16x8 p[kBlocks][2];     // weights in bf16: operands of the value product
+  bf16x8 kf[DK], vf[2 * DB];
+  bf16x8 adds;              // the matrix that adds up weights (see row_sums)
+};
+
+// One phase.  X: the block whose scores are computed (of K in st.kf); Y: the block whose output takes V (st.vf) times its
+// weights; Z: the block whose softmax runs.  A: X = Y = 1, Z = 0; B: X = Y = 0, Z = 1.  The softmax of element e of a
+// block: fma in slot e / EPS of its phase, exponential one later, rounding two later, the sums four later; what lies
+// past the phase's end runs in the next phase.  `reads(slot)`: LDS reads (over operands that the slots so far have used
+// up) and transfers.
+template <int D, int Z>
+__device__ __forceinline__ void softmax_slot(WideState<D>& st, int slot, float scale_log2) {
+  constexpr int NS = 2 * WideState<D>::DK, EPS = 16 / NS;  // slots of a phase; elements a slot
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int at = e / EPS;
+    if (slot == at) st.x[Z][e] = fmaf(st.s[Z][e], scale_log2, -st.mu[Z]);
+    if (slot == at + 1) st.x[Z][e] = fast_exp2(st.x[Z][e]);
+    if ((e & 1) && slot == at + 2) {
+      bf16x2 two;
+      two[0] = (__bf16)st.x[Z][e - 1];
+      two[1] = (__bf16)st.x[Z][e];
+      unsigned w = __builtin_bit_cast(unsigned, two);
+      asm volatile("" : "+v"(w));  // (rounded here: left alone, the compiler rounds all eight weights of an operand at once)
+      u32x4 all = __builtin_bit_cast(u32x4, st.p[Z][e / 8]);
+      all[e % 8 / 2] = w;
+      st.p[Z][e / 8] = __builtin_bit_cast(bf16x8, all);
+    }
+    if (e % 8 == 7 && slot == at + 4) st.l[Z] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(st.adds, st.p[Z][e / 8], st.l[Z], 0, 0, 0);
+  }
+}
+template <int D, int Z>
+__device__ __forceinline__ void softmax_rest(WideState<D>& st, float scale_log2) {  // past the phase's end
+  constexpr int NS = 2 * WideState<D>::DK;
+#pragma unroll
+  for (int slot = NS; slot < NS + 4; ++slot) softmax_slot<D, Z>(st, slot, scale_log2);
+}
+template <int D, int X, class Reads>
+__device__ __forceinline__ void phase(WideState<D>& st, float scale_log2, const Reads& reads) {
+  constexpr int DK = WideState<D>::DK, DB = WideState<D>::DB, NS = 2 * DK, Z = 1 - X;
+  static_assert(2 * DB == DK, "as many value products as score products");
+#pragma unroll
+  for (int slot = 0; slot < NS; ++slot) {
+    const int h = slot / 2;
+    if (slot % 2 == 0) {
+      const floatx16 zero = {};
+      st.s[X] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(st.kf[h], st.q[X][h], h == 0 ? zero : st.s[X], 0, 0, 0);
+    } else {
+      st.o[X][h % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(st.vf[h], st.p[X][h / DB], st.o[X][h % DB], 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    reads(slot);
+    if (slot < 4) softmax_slot<D, X>(st, NS + slot, scale_log2);
+    softmax_slot<D, Z>(st, slot, scale_log2);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// x / d, both positive, x below 2^20: half a unit keeps the quotient away from whole numbers by more than its error
+__device__ __forceinline__ int divided(int x, int d) { return (int)(((float)x + 0.5f) * __builtin_amdgcn_rcpf((float)d)); }
+
+// Paged cache: how far tile `i` of the piece, a full prefix tile, lies behind the pool's start, one tile per lane
+struct PagedTile {
+  long long at;
+  __device__ __forceinline__ long long offset(int lane) const {
+    const unsigned lo = __builtin_amdgcn_readlane((int)at, lane), hi = __builtin_amdgcn_readlane((int)(at >> 32), lane);
+    return (long long)((unsigned long long)hi << 32 | lo);
+  }
+};
+__device__ __forceinline__ PagedTile paged_tile(const TileSrc& ts, int i, float inv_tpp) {
+  const int t = ts.t_begin + i, pi = (int)(((float)t + 0.5f) * inv_tpp);  // (see `divided`)
+  PagedTile p;
+  p.at = (long long)ts.pg_s[pi - ts.pg_first] * ts.page_stride + (long long)((t - pi * ts.tpp) * kTileKeys) * ts.kc_sl;
+  return p;
+}
+
+// A batch of `batch` (at most 64) sequences is cut into at most batch * splits pieces (per KV head) of equal length, as
+// nearly as whole pieces of whole sequences allow: the pieces are as short as they can be without being more.  Lane b
+// brings sequence b's tiles, and gets the number of its first piece and of its pieces.  64 lengths are tried at once: from
+// the mean piece to a `splits`th of the longest sequence, which always does (and keeps a paged cache's pieces as short as
+// the host assumes).
+struct Deal {
+  int first, pieces;
+};
+__device__ __forceinline__ Deal deal_pieces(int tiles, int batch, int splits, int lane) {
+  const int places = batch * splits;
+  int total = 0, longest = 0;
+  for (int i = 0; i < batch; ++i) {
+    const int n = __builtin_amdgcn_readlane(tiles, i);
+    total += n;
+    longest = n > longest ? n : longest;
+  }
+  const int hi = (longest + splits - 1) / splits;
+  const int lo = min(max((int)((float)total / (float)places), 1), hi);
+  const int len = lane == 63 ? hi : lo + (int)((float)(hi - lo) * (float)lane * (1.f / 63.f));
+  int count = 0;
+  for (int i = 0; i < batch; ++i) count += divided(__builtin_amdgcn_readlane(tiles, i) + len - 1, len);
+  const int best = __builtin_amdgcn_readlane(len, __ffsll((long long)__ballot(count <= places)) - 1);
+  Deal d;
+  d.pieces = tiles > 0 ? divided(tiles + best - 1, best) : 0;
+  d.first = 0;
+  for (int i = 0; i < batch; ++i) {
+    const int n = __builtin_amdgcn_readlane(d.pieces, i);
+    d.first += i < lane ? n : 0;
+  }
+  return d;
+}
+
+template <int D, bool PAGED>
+__global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams p) {
+  using G_ = Geo<D>;
+  using P_ = WidePlan<D, PAGED>;
+  constexpr int DK = G_::DK, DB = G_::DB, NR = P_::NR, TILE_BYTES = G_::TILE_BYTES, QROWS = P_::QROWS;
+  constexpr int N = LaneChunks<D, kWideWaves>::N;  // transfers of a wave per tile
+
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];  // the kernel has no other LDS: offset 0
+  unsigned long long* anc = reinterpret_cast<unsigned long long*>(smem + P_::RING_BYTES + P_::DUMP_BYTES);  // [128][2]
+  int* par_s = reinterpret_cast<int*>(anc + 2 * JK_MAX_TREE);                                               // [128]
+  int* repeat_s = par_s + JK_MAX_TREE;  // set by a wave whose scores left the fixed reference frame
+  int* pg_s = repeat_s + 4;             // [1024], paged caches only
+
+  {  // (every line of the kernel arguments asked for at once)
+    typedef __attribute__((address_space(4))) const unsigned kernarg_word;
+    kernarg_word* ka = (kernarg_word*)__builtin_amdgcn_kernarg_segment_ptr();
+    static_assert(sizeof(KParams) > 320 && sizeof(KParams) <= 384, "six lines of kernel arguments");
+    const unsigned a0 = ka[0], a1 = ka[16], a2 = ka[32], a3 = ka[48], a4 = ka[64], a5 = ka[80];
+    asm volatile("" ::"s"(a0), "s"(a1), "s"(a2), "s"(a3), "s"(a4), "s"(a5));
+  }
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c32 = lane & 31, g = lane >> 5;
+  const int T = p.T, G = p.G, M = p.M, splits = p.splits;
+  const float scale_log2 = p.scale_log2;
+
+  // ---- which piece of work: each XCD a contiguous range of logical ids, the row tiles of one piece side by side.  One
+  // sequence (or more than 64): its KV heads, each cut into `splits` pieces.  A batch waits for its lengths here.  Cut
+  // into as many pieces as there are sequences times splits, it deals them by length (deal_pieces), the KV heads of a
+  // piece side by side (they read the same rows of the cache); uncut, the longest sequences go first.
+  const bool batch = p.units_per_xcd > 0, dealt = batch && splits > 1;
+  const int wid = (blockIdx.x & 7) * (p.total_wgs >> 3) + (blockIdx.x >> 3);
+  const int rest = div_mg(wid, p.mg_qtiles), qtile = wid - rest * p.n_qtiles;
+  int b, kv, split = 0, pieces = splits;  // the sequence, its KV head, which piece of how many
+  int place0, place_step;                 // its pieces' places among all: place0 + s * place_step
+  // Ordinary loads are issued by hand like the transfers behind them, and waited for by number: the compiler, which does
+  // not know of the transfers, would wait for the oldest of its loads by waiting for all but a few of everything issued
+  // since.
+  constexpr int ROW_LOADS = kBlocks * DK + 2;
+  int L_raw, L = p.max_prefix;
+  auto bounded = [&](int len) { return len < 0 ? 0 : (len > p.max_prefix ? p.max_prefix : len); };
+  const int n_ttiles = (T + kTileKeys - 1) / kTileKeys;
+  if (batch) {
+    load_by_hand(L_raw, p.prefix_len + min(lane, p.B - 1));  // (lane i: sequence i's)
+    const int order = div_mg(rest, p.mg_hkv);  // of the piece, or of the sequence
+    kv = rest - order * p.Hkv;
+    if (order >= p.B * splits) return;  // padding workgroup
+    dev::wait_vm<0>();
+    asm volatile("" : "+v"(L_raw));
+    const int len = bounded(L_raw);
+    if (dealt) {
+      const Deal d = deal_pieces(lane < p.B ? (len + kTileKeys - 1) / kTileKeys + n_ttiles : 0, p.B, splits, lane);
+      b = __popcll(__ballot(lane < p.B && d.first <= order)) - 1;
+      split = order - __builtin_amdgcn_readlane(d.first, b);
+      pieces = __builtin_amdgcn_readlane(d.pieces, b);
+      if (split >= pieces) return;  // (fewer pieces than places)
+    } else {
+      int my_rank = 0;  // of sequence `lane`: longer ones, and equal ones in front of it
+      for (int i = 0; i < p.B; ++i) {
+        const int other = __builtin_amdgcn_readlane(len, i);
+        my_rank += (int)(other > len) | ((int)(other == len) & (int)(i < lane));
+      }
+      b = __ffsll((long long)__ballot(lane < p.B && my_rank == order)) - 1;
+    }
+    L = __builtin_amdgcn_readlane(len, b);
+    place0 = (order - split) * p.Hkv + kv;
+    place_step = p.Hkv;
+  } else {
+    const int unit = div_mg(rest, p.mg_splits);
+    if (unit >= p.B * p.Hkv) return;
+    split = rest - unit * splits;
+    b = div_mg(unit, p.mg_hkv);
+    kv = unit - b * p.Hkv;
+    place0 = unit * splits;
+    place_step = 1;
+    // (starts its K/V stream as if its prefix had the length of the bound, and again if it turns out shorter)
+    load_by_hand(L_raw, p.prefix_len + b);
+  }
+  // ---- the split's tiles
+  TileSrc ts;
+  ts.T = T;
+  ts.kc_sl = p.kc_sl;
+  ts.kt_st = p.kt_st;
+  ts.pg_s = pg_s;
+  ts.pg_first = 0;
+  ts.tpp = p.tpp;
+  ts.mg_tpp = p.mg_tpp;
+  ts.page_stride = p.page_stride;
+  auto set_range = [&](int len) {  // tiles dealt evenly, the longer shares first (the last piece has the masked ones)
+    ts.L = len;
+    ts.n_ptiles = (len + kTileKeys - 1) / kTileKeys;
+    const int nt = ts.n_ptiles + n_ttiles, base = divided(nt, pieces), rem = nt - base * pieces;
+    ts.t_begin = split * base + min(split, rem);
+    ts.t_end = ts.t_begin + base + (split < rem ? 1 : 0);
+  };
+  const unsigned ring_addr = (unsigned)(size_t)LDS_PTR(unsigned char, smem);
+  LaneChunks<D, kWideWaves> lc;
+  lane_chunks<D, kWideWaves>(lc, wave, lane, ts, p.kc + (PAGED ? 0 : b * p.kc_sb) + (long long)kv * p.kc_sh,
+                             p.vc + (PAGED ? 0 : b * p.kc_sb) + (long long)kv * p.kc_sh, p.kt + b * p.kt_sb + (long long)kv * p.kt_sh,
+                             p.vt + b * p.kt_sb + (long long)kv * p.kt_sh);
+#pragma unroll
+  for (int i = 0; i < N; ++i) lc.lds[i] = (wave * N) / G_::NB * P_::HALF_BYTES + (wave * N + i) % G_::NB * 1024;
+  set_range(L);
+  int n = ts.t_end - ts.t_begin;
+  bool bad_page = false;
+  auto fill_pages = [&]() {  // (see tva_bf16.hip)
+    bad_page = false;
+    const int te = min(ts.n_ptiles, ts.t_end);
+    if (te > ts.t_begin) {
+      ts.pg_first = div_mg(ts.t_begin, p.mg_tpp);
+      const int n_pg = div_mg(te - 1, p.mg_tpp) - ts.pg_first + 1;  // <= kMaxPagesPerSplit by the host's plan
+      for (int i = tid; i < n_pg && i < kMaxPagesPerSplit; i += kWideThreads) {
+        const int pi = ts.pg_first + i;
+        const int id = pi < p.max_blocks ? p.block_table[(long long)b * p.max_blocks + pi] : 0;
+        bad_page = bad_page || id < 0 || id >= p.n_pages;
+        pg_s[i] = id < 0 ? 0 : (id >= p.n_pages ? p.n_pages - 1 : id);
+      }
+    }
+    __syncthreads();
+  };
+  if (PAGED) fill_pages();
+  const int row0 = qtile * QROWS + wave * kWideRows;  // the wave's first query row
+  u32x4 q_raw[kBlocks][DK];
+  int parent_lo, parent_hi;  // of nodes lane and lane + 64
+#pragma unroll
+  for (int r = 0; r < kBlocks; ++r) {
+    const int mm = min(row0 + r * kWaveRows + c32, M - 1), node = div_mg(mm, p.mg_g);
+    const uint16_t* src = p.q + b * p.q_sb + node * p.q_st + (long long)(kv * G + (mm - node * G)) * p.q_sh + 8 * g;
+#pragma unroll
+    for (int ks = 0; ks < DK; ++ks) load_by_hand(q_raw[r][ks], src + ks * 16);
+  }
+  load_by_hand(parent_lo, p.parent + (long long)b * T + min(lane, T - 1));
+  load_by_hand(parent_hi, p.parent + (long long)b * T + min(lane + 64, T - 1));
+
+  auto transfer = [&](int i) { dma_round<D, kWideWaves, 1, PAGED>(i, ts, lc, ring_addr + i % NR * TILE_BYTES); };
+  const float inv_tpp = PAGED ? __builtin_amdgcn_rcpf((float)ts.tpp) : 0.f;
+  auto first_transfers = [&]() {  // as many tiles as the ring takes, full prefix tiles in the shorter way
+    const int most = min(n, (int)P_::AHEAD), full = min(ts.L / kTileKeys - ts.t_begin, most);
+    const long long tile = (long long)kTileKeys * ts.kc_sl;
+    PagedTile at;  // (lane i: tile i's)
+    if (PAGED && full > 0) at = paged_tile(ts, min(lane, full - 1), inv_tpp);
+    const uint16_t* base = lc.cache + (PAGED ? 0 : ts.t_begin * tile);
+    int i = 0;
+    for (; i < full; ++i) {
+      const uint16_t* src = PAGED ? base + at.offset(i) : base;
+#pragma unroll
+      for (int c = 0; c < N; ++c) dma16(src, lc.off[c], ring_addr + i * TILE_BYTES + lc.lds[c]);
+      if (!PAGED) base += tile;
+    }
+    for (; i < most; ++i) transfer(i);
+  };
+  first_transfers();
+  if (!batch) {
+    if (n >= P_::AHEAD) dev::wait_vm<ROW_LOADS + P_::AHEAD * N>();
+    else dev::wait_vm<ROW_LOADS>();  // (no less than needed)
+    asm volatile("" : "+v"(L_raw));
+    L = bounded(__builtin_amdgcn_readfirstlane(L_raw));
+    if (L != p.max_prefix) {  // (uniform over the workgroup)
+      dev::wait_vm<0>();  // the ring must be quiet before the same places are filled again
+      __syncthreads();
+      set_range(L);
+      n = ts.t_end - ts.t_begin;
+      if (PAGED) fill_pages();
+      first_transfers();
+    }
+  }
+  if (PAGED && bad_page) __hip_atomic_fetch_or(p.err, kDevErrBadPage, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (n >= P_::AHEAD) dev::wait_vm<P_::AHEAD * N>();
+  else wait_dma<N>(n);
+#pragma unroll
+  for (int r = 0; r < kBlocks; ++r)
+#pragma unroll
+    for (int ks = 0; ks < DK; ++ks) asm volatile("" : "+v"(q_raw[r][ks]));
+  asm volatile("" : "+v"(parent_lo), "+v"(parent_hi));
+  if (lane >= T) parent_lo = -1;
+  if (lane + 64 >= T) parent_hi = -1;
+  // the sets are published by the barrier in front of the first tile
+  if (ts.t_end > ts.n_ptiles && wave == 0) build_ancestor_sets(lane, T, parent_lo, parent_hi, par_s, anc);
+  if (tid == 0) *repeat_s = 0;  // (read behind the barrier that follows the loop)
+
+  WideState<D> st;
+#pragma unroll
+  for (int r = 0; r < kBlocks; ++r) {
+    const bool ok = row0 + r * kWaveRows + c32 < M;
+#pragma unroll
+    for (int ks = 0; ks < DK; ++ks) {
+      u32x4 v = q_raw[r][ks];
+      if (!ok) v = u32x4{0u, 0u, 0u, 0u};
+      st.q[r][ks] = __builtin_bit_cast(bf16x8, v);
+      // (D = 128: in accumulation registers, from which only matrix instructions read it.  Left alone, the compiler moves
+      // it between the two files in the tile loop.)
+      if (D == 128) asm volatile("" : "+a"(st.q[r][ks]));
+    }
+  }
+  // adds[i][k]: rows 4 G' ... of the result reach the lanes 16 G' ...; they add up the k groups (lanes 16 k' ... of the
+  // weights) that hold the same query rows, i.e. those of equal parity
+  {
+    const bool one = (((lane >> 4) ^ (lane >> 2)) & 1) == 0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) st.adds[e] = (__bf16)(one ? 1.f : 0.f);
+  }
+  auto clear = [&]() {
+#pragma unroll
+    for (int r = 0; r < kBlocks; ++r) {
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) st.o[r][db][i] = 0.f;
+      st.l[r] = floatx4{0.f, 0.f, 0.f, 0.f};
+      st.m[r] = -INFINITY;
+      st.mu[r] = 0.f;
+    }
+  };
+  clear();
+
+  const unsigned k_lane = ring_addr + G_::k_lane(lane), v_lane = ring_addr + P_::HALF_BYTES + G_::v_lane(lane);
+  auto k_read = [&](unsigned tile, int ks) { return lds_read128((k_lane ^ (ks << 5)) + tile); };
+  auto v_read = [&](unsigned tile, int h) {
+    return lds_read_tr2((v_lane ^ ((h % DB) << 6)) + tile + 16 * (h / DB) * G_::ROW_BYTES, 8 * G_::ROW_BYTES);
+  };
+  // The first tile and tiles with masks.  Hides the keys of tile t that rows must not see (those of a ragged prefix tile,
+  // tree tiles) in block r's scores: a bit per key, spread over a register and used to choose between the score and -inf
+  // (register i of a lane is key 8 * (i / 4) + 4 * g + i % 4 of the tile).  Then the rows' references: the largest score of
+  // the first tile in which a row sees a key.  Weights 2^(s - m) may grow to 2^64 from there (bf16 and fp32 have the same
+  // exponents): a larger one shows in the row's sum after the loop.  (No branches: a step is one run of code.)
+  auto hide = [&](int t, int r) {
+    const int tt = t - ts.n_ptiles, left = L - t * kTileKeys;
+    const int node = div_mg(min(row0 + r * kWaveRows + c32, M - 1), p.mg_g);
+    unsigned seen = reinterpret_cast<const unsigned*>(anc)[4 * node + (tt >= 0 ? tt : 0)];
+    if (tt < 0) seen = left >= kTileKeys ? ~0u : (1u << left) - 1u;
+    seen >>= 4 * g;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const unsigned keep = (unsigned)__builtin_amdgcn_sbfe((int)seen, 8 * (i / 4) + i % 4, 1);
+      st.s[r][i] = __uint_as_float((__float_as_uint(st.s[r][i]) & keep) | (0xff800000u & ~keep));
+    }
+  };
+  auto look = [&](int t, int r) {
+    hide(t, r);
+    const float tmax = half_swap_max(max16(st.s[r])) * scale_log2;
+    st.m[r] = st.m[r] == -INFINITY ? tmax : st.m[r];
+    st.mu[r] = st.m[r] == -INFINITY ? 0.f : st.m[r];
+  };
+  // Before a tile: this wave's transfers of it have landed, then everybody's; everybody is also done with the tile
+  // in front of the one in use, whose place is therefore free.
+  int issued = min(n, (int)P_::AHEAD);  // tiles asked for, in order
+  auto landed = [&](int i) {
+    const int younger = min(issued - 1 - i, P_::AHEAD - 2);
+    if (younger == P_::AHEAD - 2) dev::wait_vm<(P_::AHEAD - 2) * N>();
+    else wait_dma<N>(younger);  // (waits for more than it has to where more than six tiles are younger)
+    __syncthreads();
+  };
+  const int n_full = min(max(L / kTileKeys - ts.t_begin, 0), n);  // tiles without a mask, the split's first ones
+
+  if (n > 0) {
+    // ---- tile 0: its scores for block 0; everything else of the pipeline starts with zeros
+    if (n >= P_::AHEAD) dev::wait_vm<(P_::AHEAD - 1) * N>();
+    else wait_dma<N>(n - 1);
+    __syncthreads();
+#pragma unroll
+    for (int ks = 0; ks < DK; ++ks) st.kf[ks] = k_read(0, ks);
+    {
+      const floatx16 zero = {};
+      const bf16x8 none = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
+#pragma unroll
+      for (int h = 0; h < 2 * DB; ++h) st.vf[h] = none;
+      st.p[1][0] = st.p[1][1] = none;
+      st.x[1] = zero;
+#pragma unroll
+      for (int e = 16 - 16 / (2 * DK); e < 16; ++e) st.x[1][e] = -INFINITY;  // (their exponentials are taken in A(0))
+#pragma unroll
+      for (int ks = 0; ks < DK; ++ks)
+        st.s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(st.kf[ks], st.q[0][ks], ks == 0 ? zero : st.s[0], 0, 0, 0);
+    }
+    // ---- the tiles.  Step i needs K of tile i + 1 and V of tile i, and frees the place of tile i - 1.
+    constexpr int HK = DK / 2;
+    int i = 0;
+    auto step = [&](int i, auto special) {
+      constexpr bool LOOK = decltype(special)::value;
+      const unsigned kt = (unsigned)((i + 1) % NR) * TILE_BYTES, vt = (unsigned)(i % NR) * TILE_BYTES;
+      if (LOOK) look(ts.t_begin + i, 0);
+      phase<D, 1>(st, scale_log2, [&](int slot) {
+        if (slot % 4 == 0) st.kf[slot / 4] = k_read(kt, slot / 4);
+        if (slot % 4 == 2) st.vf[slot / 4] = v_read(vt, slot / 4);
+      });
+      if (LOOK) look(ts.t_begin + i, 1);
+      phase<D, 0>(st, scale_log2, [&](int slot) {
+        if (slot < DK && slot % 2 == 0) st.kf[HK + slot / 2] = k_read(kt, HK + slot / 2);
+        if (slot < DK && slot % 2 == 1) st.vf[HK + slot / 2] = v_read(vt, HK + slot / 2);
+      });
+    };
+    if (row0 >= M) {  // a wave of padding rows only moves tiles
+      for (; i + 1 < n; ++i) {
+        landed(i + 1);
+        for (; issued < min(n, i + NR); ++issued) transfer(issued);
+      }
+      if (n_full >= 5 && ((n_full - 1) & ~3) + 1 == n) __syncthreads();  // (the others' last step of four met for a tile that does not exist)
+    } else {
+      // One tile, wherever it lies
+      auto one = [&]() {
+        if (i + 1 < n) landed(i + 1);
+        for (; issued < min(n, i + NR); ++issued) transfer(issued);
+        step(i, std::true_type{});
+        ++i;
+      };
+      one();
+      // Four tiles without masks at a time, from tile 1 of the piece on: their places in the ring are known but for the
+      // upper bits, and every LDS address is one of twelve registers and an immediate.  One run of code without branches:
+      // its steps ask for full prefix tiles, or for the last of these once more where there is none left (to where
+      // nobody reads it); tiles with masks are asked for between the runs, once their places are free.
+      const unsigned dump = ring_addr + P_::RING_BYTES + wave * (N * 1024);
+      for (; i + 4 <= n_full; i += 4) {
+        for (issued = max(issued, n_full); issued < min(n, i + P_::AHEAD); ++issued) transfer(issued);
+        const unsigned here = (unsigned)((i - 1) % NR) * TILE_BYTES, there = (unsigned)((i + 3) % NR) * TILE_BYTES;
+        unsigned ka[DK], va[DB];
+#pragma unroll
+        for (int ks = 0; ks < DK; ++ks) ka[ks] = (k_lane ^ (ks << 5)) + here;
+#pragma unroll
+        for (int db = 0; db < DB; ++db) va[db] = (v_lane ^ (db << 6)) + here;
+        PagedTile at;
+        if (PAGED) at = paged_tile(ts, min(i + P_::AHEAD + (lane & 3), n_full - 1), inv_tpp);
+        const uint16_t* next = lc.cache + (PAGED ? 0 : (long long)(ts.t_begin + min(i + P_::AHEAD, n_full - 1)) * kTileKeys * ts.kc_sl);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (u == 2) {
+#pragma unroll
+            for (int ks = 0; ks < DK; ++ks) ka[ks] += there - here;
+          }
+          if (u == 3) {
+#pragma unroll
+            for (int db = 0; db < DB; ++db) va[db] += there - here;
+          }
+          dev::wait_vm<(P_::AHEAD - 2) * N>();
+          __syncthreads();
+          const unsigned kt = (unsigned)((u + 2) % 4) * TILE_BYTES, vt = (unsigned)((u + 1) % 4) * TILE_BYTES;
+          auto k_at = [&](int ks) { st.kf[ks] = lds_read128(ka[ks] + kt); };
+          auto v_at = [&](int h) {
+            st.vf[h] = lds_read_tr2(va[h % DB] + vt + 16 * (h / DB) * G_::ROW_BYTES, 8 * G_::ROW_BYTES);
+          };
+          phase<D, 1>(st, scale_log2, [&](int slot) {
+            if (slot % 4 == 0) k_at(slot / 4);
+            if (slot % 4 == 2) v_at(slot / 4);
+          });
+          const uint16_t* src = next;
+          if (PAGED) src += at.offset(u);
+          else next += i + u + P_::AHEAD < n_full - 1 ? (long long)kTileKeys * ts.kc_sl : 0;
+          const unsigned to = i + u + P_::AHEAD < n_full ? ring_addr + lc.lds[0] + here + u * TILE_BYTES : dump;  // (the place of tile i + u - 1)
+          phase<D, 0>(st, scale_log2, [&](int slot) {
+            if (slot < DK && slot % 2 == 0) k_at(HK + slot / 2);
+            if (slot < DK && slot % 2 == 1) v_at(HK + slot / 2);
+#pragma unroll
+            for (int c = 0; c < N; ++c)
+              if (slot == DK + c * DK / N) dma16(src, lc.off[c], to + c * 1024);
+          });
+        }
+      }
+      dev::wait_vm<0>();  // (what is still on its way: the last tile once more, tiles with masks)
+      issued = max(issued, min(n_full, i + P_::AHEAD));
+      while (i < n) one();
+    }
+    // ---- the last tile's value product for block 1
+    softmax_rest<D, 1>(st, scale_log2);
+#pragma unroll
+    for (int h = 0; h < 2 * DB; ++h)
+      st.o[1][h % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(st.vf[h], st.p[1][h / DB], st.o[1][h % DB], 0, 0, 0);
+  }
+  if (!(st.l[0][0] < 1.8446744e19f) || !(st.l[1][0] < 1.8446744e19f)) *repeat_s = 1;
+  __syncthreads();  // everybody is done with the ring
+  if (__builtin_amdgcn_readfirstlane(*repeat_s) != 0) {
+    // ---- A weight beyond 2^64 (a score 44 nats above the row's first): the split once more, with a reference that
+    // moves and accumulators that follow it.  Rare, and in no hurry: one tile after the other.
+    clear();
+    for (int i = 0; i < n; ++i) {
+      transfer(i);
+      dev::wait_vm<0>();
+      __syncthreads();
+      const unsigned tile = (unsigned)(i % NR) * TILE_BYTES;
+      const int t = ts.t_begin + i;
+#pragma unroll
+      for (int r = 0; r < kBlocks; ++r) {
+        const floatx16 zero = {};
+#pragma unroll
+        for (int ks = 0; ks < DK; ++ks)
+          st.s[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_read(tile, ks), st.q[r][ks], ks == 0 ? zero : st.s[r], 0, 0, 0);
+        if (i >= n_full) hide(t, r);
+        const float tmax = half_swap_max(max16(st.s[r])) * scale_log2;
+        const float m_new = fmaxf(st.m[r], tmax), mu = m_new == -INFINITY ? 0.f : m_new;
+        const float alpha = fast_exp2(st.m[r] - mu);  // 0 before the first key: the accumulators are zero then
+        st.m[r] = m_new;
+        st.mu[r] = mu;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) st.p[r][e / 8][e % 8] = (__bf16)fast_exp2(fmaf(st.s[r][e], scale_log2, -mu));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) st.l[r][k] *= alpha;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) st.l[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(st.adds, st.p[r][j], st.l[r], 0, 0, 0);
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int k = 0; k < 16; ++k) st.o[r][db][k] *= alpha;
+#pragma unroll
+        for (int h = 0; h < 2 * DB; ++h)
+          st.o[r][h % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_read(tile, h), st.p[r][h / DB], st.o[r][h % DB], 0, 0, 0);
+      }
+    }
+    __syncthreads();
+  }
+
+  // ---- Merge of the pieces, two and two: 0 with 1, 2 with 3, then those with each other, and so on.  Of two that meet the
+  // first to come leaves its results in memory, in fp32 and in the order of its registers, and is done; the second, which
+  // still has its own in registers, adds them: half the traffic of leaving all results for another kernel, and nobody
+  // waits for a workgroup that has not come yet (so any number of them may still be to start).  The sum is the same
+  // whoever comes first.  The meeting of two groups of pieces has the place of the right one's first piece: a word of the
+  // workspace's header (arrivals, and kWritten once the first one's results are in memory; zero again behind it), and
+  // the results.  The two may run on different XCDs, whose L2s know nothing of each other: stores go through to memory, and
+  // the loads bypass them (sc1, the scope of the device).
+  constexpr unsigned kWritten = 0x100u, kMostPolls = 1u << 20;
+  constexpr int QUADS = kBlocks * DB * 4;  // float4 per lane
+  constexpr int kDeviceScope = 16;         // (the sc1 bit of a buffer load)
+  for (int held = 1, lo = split; held < pieces; held *= 2) {  // this workgroup holds pieces lo ... lo + held - 1
+    const bool right = (lo & held) != 0;
+    if (!right && lo + held >= pieces) continue;  // (nobody there)
+    const int place = (place0 + (right ? lo : lo + held) * place_step) * p.n_qtiles + qtile;
+    unsigned* word = p.sync + place / kWideWords * 16 + 3 + place % kWideWords;  // (the first three of a line belong to tva_bf16.hip)
+    float4* part = reinterpret_cast<float4*>(p.part_o) + (size_t)(place * kWideWaves + wave) * (QUADS * 64) + lane;
+    float2* ml = p.part_ml + (size_t)place * QROWS + wave * kWideRows + c32;
+    if (tid == 0) repeat_s[1] = (int)__hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(repeat_s[1]) == 0) {
+      if (row0 < M) {
+#pragma unroll
+        for (int r = 0; r < kBlocks; ++r) {
+          dev::store_through(ml + r * kWaveRows, dev::store_u32x2{__float_as_uint(st.m[r]), __float_as_uint(st.l[r][0])});
+#pragma unroll
+          for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+              const floatx16& o = st.o[r][db];
+              dev::store_through(part + ((r * DB + db) * 4 + q4) * 64,
+                                 dev::store_u32x4{__float_as_uint(o[4 * q4]), __float_as_uint(o[4 * q4 + 1]), __float_as_uint(o[4 * q4 + 2]), __float_as_uint(o[4 * q4 + 3])});
+            }
+        }
+      }
+      dev::wait_vm<0>();
+      __syncthreads();
+      if (tid == 0) __hip_atomic_fetch_add(word, kWritten, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return;
+    }
+    if (tid == 0) {
+      // (the other workgroup has come: it has nothing left to do but its stores.  The bound, about a second, is for a
+      // workspace that was never initialised.)
+      unsigned polls = 0;
+      while (!(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kWritten)) {
+        if (++polls > kMostPolls) {
+          __hip_atomic_fetch_or(p.err, kDevErrMergeWait, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          break;
+        }
+        __builtin_amdgcn_s_sleep(1);
+      }
+      __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (row0 < M) {
+      const auto theirs = __builtin_amdgcn_make_buffer_rsrc(p.part_o + (size_t)(place * kWideWaves + wave) * (QUADS * 64 * 4), 0, QUADS * 64 * 16, 0x00020000);
+#pragma unroll
+      for (int r = 0; r < kBlocks; ++r) {
+        const u32x2 other = __builtin_bit_cast(u32x2, __hip_atomic_load(reinterpret_cast<const uint64_t*>(ml + r * kWaveRows), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        const float other_m = __uint_as_float(other[0]), other_l = __uint_as_float(other[1]);
+        u32x4 v[DB * 4];  // (all on their way before the first is used)
+#pragma unroll
+        for (int i = 0; i < DB * 4; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(theirs, lane * 16, (r * DB * 4 + i) * 1024, kDeviceScope);
+        __builtin_amdgcn_sched_barrier(0);
+        const float m = fmaxf(st.m[r], other_m), mu = m == -INFINITY ? 0.f : m;
+        const float w0 = fast_exp2(st.m[r] - mu), w1 = fast_exp2(other_m - mu);  // (exp2(-inf) = 0: a row without a key)
+        st.m[r] = m;
+        // (no fused multiply-add: it would round one of the two products only, and which one would be up to who came first)
+        auto sum = [&](float x, float y) {
+#pragma clang fp contract(off)
+          const float a = x * w0, c = y * w1;
+          return a + c;
+        };
+        st.l[r][0] = sum(st.l[r][0], other_l);
+#pragma unroll
+        for (int i = 0; i < DB * 4; ++i) {
+          floatx16& o = st.o[r][i / 4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) o[4 * (i % 4) + k] = sum(o[4 * (i % 4) + k], __uint_as_float(v[i][k]));
+        }
+      }
+    }
+    lo &= ~held;
+  }
+
+  // ---- the finished rows, a block of 32 at a time through a patch of LDS so that they leave in whole 128-byte lines (see
+  // tva_bf16.hip)
+  const bool thr = (p.through & 1) != 0;
+  constexpr int CPR = G_::CPR, RPI = 64 / CPR;
+  const int chunk = lane % CPR, rsub = lane / CPR;
+  unsigned char* patch = smem + wave * P_::PATCH_BYTES;
+  unsigned char* prow = patch + c32 * P_::PATCH_LD;
+  const unsigned char* src0 = patch + rsub * P_::PATCH_LD + chunk * 16;
+  uint16_t* out0 = p.out + b * p.o_sb + (long long)kv * G * p.o_sh + chunk * 8;
+#pragma unroll
+  for (int r = 0; r < kBlocks; ++r) {
+    const int first = row0 + r * kWaveRows, rows_valid = M - first;
+    if (rows_valid <= 0) break;
+    const float mul = 1.f / st.l[r][0];  // > 0: every row sees at least its own tree key
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        bf16x2 lo, hi;
+        lo[0] = (__bf16)(st.o[r][db][4 * q4] * mul);
+        lo[1] = (__bf16)(st.o[r][db][4 * q4 + 1] * mul);
+        hi[0] = (__bf16)(st.o[r][db][4 * q4 + 2] * mul);
+        hi[1] = (__bf16)(st.o[r][db][4 * q4 + 3] * mul);
+        uint2 pk;
+        pk.x = __builtin_bit_cast(unsigned int, lo);
+        pk.y = __builtin_bit_cast(unsigned int, hi);
+        *reinterpret_cast<uint2*>(prow + (32 * db + 8 * q4 + 4 * g) * 2) = pk;
+      }
+    // (same wave wrote and reads: LDS operations of a wave complete in order)
+    auto store_rows = [&](auto through) {
+#pragma unroll
+      for (int k = 0; k < kWaveRows / RPI; ++k) {
+        const u32x4 v = *reinterpret_cast<const u32x4*>(src0 + k * RPI * P_::PATCH_LD);
+        const int m = first + k * RPI + rsub, node = div_mg(m, p.mg_g);
+        uint16_t* dst = out0 + node * p.o_st + (long long)(m - node * G) * p.o_sh;
+        if (m >= M) continue;
+        if (decltype(through)::value) dev::store_through(dst, v);
+        else *reinterpret_cast<u32x4*>(dst) = v;
+      }
+    };
+    if (thr) store_rows(std::true_type{});
+    else store_rows(std::false_type{});
+  }
+}
+
+template <int D, bool PAGED>
+hipError_t launch_one(const KParams& kp, hipStream_t stream) {
+  using P_ = WidePlan<D, PAGED>;
+  auto kern = tva_wide_kernel<D, PAGED>;
+  static LdsLimitRaised raised;
+  if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), P_::SMEM, raised); e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3(kp.total_wgs), dim3(kWideThreads), P_::SMEM, stream, kp);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+namespace tva {
+hipError_t launch_wide(const KParams& kp, int head_dim, hipStream_t stream) {
+  const bool paged = kp.block_table != nullptr;
+  if (head_dim == 128) return paged ? launch_one<128, true>(kp, stream) : launch_one<128, false>(kp, stream);
+  if (head_dim == 64) return paged ? launch_one<64, true>(kp, stream) : launch_one<64, false>(kp, stream);
+  return hipErrorInvalidValue;
+}
+}  // namespace tva
+
+}  // namespace jk
