@@ -229,8 +229,8 @@ jk_status jk_accept_path(int32_t batch, int32_t n_tree, int32_t vocab, int32_t m
 
 /* jk_accept_path in JK_GREEDY mode for callers that cannot allocate device memory or hand
  * over a workspace: code running under HIP-graph capture, tight serving loops, harnesses
- * that forbid hipMalloc.  Same arguments, results and kernels as jk_accept_path(...,
- * JK_GREEDY, ...) minus the workspace: the per-chunk (max, argmax) partials live in a buffer
+ * that forbid hipMalloc.  Same arguments and results as jk_accept_path(...,
+ * JK_GREEDY, ...) minus the workspace, in two launches: the per-chunk (max, argmax) partials live in a buffer
  * of JK_STATIC_SCRATCH_BYTES that is part of the library's device image (one copy per GPU the
  * library runs on, held until the process ends).  The call allocates and frees nothing.
  *

@@ -8,9 +8,11 @@
 // left), each node carrying its own draft distribution.
 //
 // Kernels
+//   greedy_kernel       greedy calls: rows reduced and trees walked in one launch
 //   row_reduce_kernel   one pass over the [rows, vocab] logits: per (row,
 //                       chunk) either (max, argmax) or (max, sum exp) partials
-//   walk_greedy_kernel  one workgroup per tree: merges the partials per row,
+//   walk_greedy_kernel  (calls without a workspace, or of more trees than the
+//                       workspace has words) one workgroup per tree: merges the partials per row,
 //                       marks every node whose token equals its parent row's
 //                       argmax, then descends from the prefix
 //   walk_sample_kernel  one workgroup per tree: descends from the prefix; a
@@ -23,7 +25,9 @@
 #include <cstdlib>
 #include <mutex>
 
+#include "jk_device.h"
 #include "jk_internal.h"
+#include "jk_wave.h"
 
 namespace jk {
 namespace {
@@ -171,6 +175,157 @@ __global__ __launch_bounds__(128) void walk_greedy_kernel(int n_tree, int nch, i
     out_len[b] = len;
     out_bonus[b] = amax[c + 1];
   }
+}
+
+// ------------------------------------------------------------------ greedy walk in one launch
+constexpr int kGreedyLoads = 8;  // 16 bytes a load, at most so many of them per thread, all in flight
+constexpr int greedy_chunk(int threads) { return threads * kGreedyLoads * 4; }  // most vocabulary entries per workgroup
+
+struct GreedyParams {
+  int n_tree, vocab, max_depth, chunk;
+  unsigned long long mg_rows;  // floor(2^32 / rows of a tree) + 1
+  const int *tokens, *parent;
+  const float* logits;
+  uint64_t* part;   // [rows][chunks] (bits of the maximum, its lowest index)
+  unsigned* words;  // 508 lines of 16; see greedy_word
+  int *out_path, *out_len, *out_bonus;
+  unsigned* err;
+};
+
+// Words in which the workgroups of a call count themselves, zero between calls: number i's line and word in it, neighbours
+// 256 bytes apart.  (An atomic takes about 11 ns of the memory channel that has the word: with the words of four trees in
+// one channel, four trees of 61 rows in two parts each spent 5 us on them.)
+constexpr int kGreedyWords = kMaxFusedGroups * 12;  // (the first four words of a line: attention's, and one spare)
+__device__ __forceinline__ unsigned* greedy_word(unsigned* words, int i) {
+  const int line = i % kMaxFusedGroups, blocks = kMaxFusedGroups / 4;
+  return words + ((line % blocks) * 4 + line / blocks) * 16 + 4 + i / kMaxFusedGroups;
+}
+
+// The rows' maxima and the walk in one kernel: a workgroup per (chunk, row) leaves its (max, argmax) in memory and counts
+// itself; the one that finds itself the last of its tree walks it.  Nobody waits, so it does not matter how many run at
+// once.  What bounds it is the stream of logits behind a launch, a reduction and three trips to memory (result, counter,
+// results back); a second launch for the walk cost more than the last two.  Measured (us, two launches / one): four trees of
+// 60 nodes, 32000 entries 10.5 / 8.9 (31 MB); one tree 7.4 / 5.7; one tree, 128256 entries 12.2 / 9.4; 20 nodes 6.1 / 4.8;
+// 64 trees 90 / 88.  The workgroups of a tree run on different XCDs, whose L2s know nothing of each other: results go through to memory
+// and are on their way back before the counter moves, and are read past the caches (device scope).
+template <int THREADS, int LOADS>
+__global__ __launch_bounds__(THREADS) void greedy_kernel(GreedyParams p) {
+  constexpr int kWaves = THREADS / 64;
+  __shared__ float s_max[kWaves];
+  __shared__ int s_idx[kWaves];
+  __shared__ int amax[JK_MAX_TREE + 1];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int rows = p.n_tree + 1, nch = gridDim.x, vocab = p.vocab;
+  const int row = blockIdx.y, b = (int)(((unsigned long long)(unsigned)row * p.mg_rows) >> 32);
+  const float* src = p.logits + (long long)row * vocab;
+  const int v0 = (int)blockIdx.x * p.chunk, v1 = min(vocab, v0 + p.chunk);
+  const bool vec = (vocab & 3) == 0;  // rows stay 16-byte aligned
+  float4 x[LOADS];
+#pragma unroll
+  for (int j = 0; j < LOADS; ++j) {
+    const int v = v0 + (j * THREADS + tid) * 4;
+    x[j] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+    if (vec) {
+      if (v < v1) x[j] = *reinterpret_cast<const float4*>(src + v);  // (chunks are multiples of four)
+    } else {
+      if (v < v1) x[j].x = src[v];
+      if (v + 1 < v1) x[j].y = src[v + 1];
+      if (v + 2 < v1) x[j].z = src[v + 2];
+      if (v + 3 < v1) x[j].w = src[v + 3];
+    }
+  }
+  // (what the walk needs besides, on its way as well: only the first wave walks, nodes lane and lane + 64)
+  const int n0 = min(lane, p.n_tree - 1), n1 = min(lane + 64, p.n_tree - 1);
+  int pa0 = 0, pa1 = 0, tk0 = 0, tk1 = 0;
+  if (wave == 0) {
+    const long long base = (long long)b * p.n_tree;
+    pa0 = p.parent[base + n0]; pa1 = p.parent[base + n1];
+    tk0 = p.tokens[base + n0]; tk1 = p.tokens[base + n1];
+  }
+  float best = -INFINITY;
+  int bidx = 0x7fffffff;
+#pragma unroll
+  for (int j = 0; j < LOADS; ++j) {  // ascending inside a thread: strict > keeps the lowest id
+    const int v = v0 + (j * THREADS + tid) * 4;
+    if (x[j].x > best) { best = x[j].x; bidx = v; }
+    if (x[j].y > best) { best = x[j].y; bidx = v + 1; }
+    if (x[j].z > best) { best = x[j].z; bidx = v + 2; }
+    if (x[j].w > best) { best = x[j].w; bidx = v + 3; }
+  }
+  const float wmax = dev::wave_max(best);
+  const int widx = dev::wave_min(best == wmax ? bidx : 0x7fffffff);
+  if (lane == 0) { s_max[wave] = wmax; s_idx[wave] = widx; }
+  __syncthreads();
+  if (wave != 0) return;
+  best = lane < kWaves ? s_max[lane] : -INFINITY;
+  bidx = lane < kWaves ? s_idx[lane] : 0x7fffffff;
+  const float bmax = dev::wave_max(best);
+  const int bmin = dev::wave_min(best == bmax ? bidx : 0x7fffffff);
+  // first among the parts of the row, then, the row's last one, among the rows of the tree (words: the trees', then the rows')
+  bool last = true;
+  if (lane == 0) {
+    dev::store_through(p.part + (size_t)row * nch + blockIdx.x, dev::store_u32x2{__float_as_uint(bmax), (unsigned)bmin});
+    dev::wait_vm<0>();
+    auto arrive = [&](int i, int of) {
+      unsigned* word = greedy_word(p.words, i);
+      if (of > 1 && __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != (unsigned)of - 1) return false;
+      if (of > 1) __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return true;
+    };
+    last = arrive((int)gridDim.y / rows + row, nch) && arrive(b, rows);
+  }
+  if (!__builtin_amdgcn_readfirstlane((int)last)) return;
+
+  // ---- the tree's last workgroup: everybody's results are in memory
+  for (int r = lane; r < rows; r += 64) {
+    const uint64_t* part = p.part + ((size_t)b * rows + r) * nch;
+    float m = -INFINITY;
+    int id = 0x7fffffff;
+    for (int c0 = 0; c0 < nch; c0 += 8) {  // eight partials in flight at a time
+      uint64_t w[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) w[u] = __hip_atomic_load(part + min(c0 + u, nch - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int u = 0; u < 8; ++u)  // chunks ascend in token id: strict > keeps the lowest id (the last one again changes nothing)
+        if (__uint_as_float((unsigned)w[u]) > m) { m = __uint_as_float((unsigned)w[u]); id = (int)(w[u] >> 32); }
+    }
+    amax[r] = id == 0x7fffffff ? 0 : id;  // a row of -inf only: id 0, the first maximum
+  }
+  auto checked = [&](int k, int& pa, int& tk) {
+    if (k >= p.n_tree) { pa = -2; return; }
+    pa = sanitize_parent(pa, k, p.err);
+    const int tc = min(max(tk, 0), vocab - 1);  // an id outside the vocabulary is clamped, and reported
+    if (tc != tk) report(p.err, kDevErrBadToken);
+    tk = tc;
+  };
+  checked(lane, pa0, tk0);
+  checked(lane + 64, pa1, tk1);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // (one wave: its LDS operations complete in order)
+  const bool ok0 = pa0 > -2 && tk0 == amax[max(pa0, -1) + 1], ok1 = pa1 > -2 && tk1 == amax[max(pa1, -1) + 1];
+  int c = -1, len = 0;
+  // (nodes are numbered topologically: a child has a larger index than its parent; the walk stops at max_depth accepted
+  // nodes, and the extra token then comes from the last one's row)
+  while (len < p.max_depth) {
+    const unsigned long long m0 = __ballot(ok0 && pa0 == c), m1 = __ballot(ok1 && pa1 == c);
+    const int k = m0 ? __ffsll((long long)m0) - 1 : (m1 ? 63 + __ffsll((long long)m1) : -1);
+    if (k < 0) break;
+    if (lane == 0) p.out_path[(long long)b * p.max_depth + len] = k;
+    ++len;
+    c = k;
+  }
+  for (int i = len + lane; i < p.max_depth; i += 64) p.out_path[(long long)b * p.max_depth + i] = -1;
+  if (lane == 0) {
+    p.out_len[b] = len;
+    p.out_bonus[b] = amax[c + 1];
+  }
+}
+
+template <int THREADS>
+void launch_greedy(const GreedyParams& p, int loads, dim3 grid, hipStream_t stream) {
+  if (loads <= 1) hipLaunchKernelGGL((greedy_kernel<THREADS, 1>), grid, dim3(THREADS), 0, stream, p);
+  else if (loads <= 2) hipLaunchKernelGGL((greedy_kernel<THREADS, 2>), grid, dim3(THREADS), 0, stream, p);
+  else if (loads <= 4) hipLaunchKernelGGL((greedy_kernel<THREADS, 4>), grid, dim3(THREADS), 0, stream, p);
+  else hipLaunchKernelGGL((greedy_kernel<THREADS, kGreedyLoads>), grid, dim3(THREADS), 0, stream, p);
 }
 
 // ------------------------------------------------------------------ sampling walk
@@ -376,7 +531,7 @@ __global__ void xcd_probe_kernel(unsigned* out) {
 }
 
 struct WsLayout {
-  size_t coop, pmax, pidx, psum, resid, total;  // (the error word's header sits in front of them)
+  size_t words, coop, pmax, pidx, psum, resid, total;  // (the error word's header sits in front of them)
 };
 WsLayout ws_layout(int batch, int n_tree, int vocab, int mode, bool caller_workspace = true) {
   WsLayout w{};
@@ -388,6 +543,8 @@ WsLayout ws_layout(int batch, int n_tree, int vocab, int mode, bool caller_works
   // every mode: their words keep their place and are never overlaid by another call's partials,
   // so a workspace needs zeroing only once whatever calls take turns on it (the library's own
   // scratch array serves greedy calls only and has no such blocks)
+  // (greedy calls count in words that attention calls use too and leave at zero, at their place in an attention workspace)
+  w.words = off; off = caller_workspace ? kAttnHeaderBytes : off;
   w.coop = off; off += caller_workspace ? up(accept_coop_bytes()) : 0;
   w.pmax = off; off += up(slots * sizeof(float));
   w.pidx = off; off += up(slots * sizeof(int));
@@ -459,6 +616,32 @@ hipError_t launch_accept(const AcceptArgs& a, hipStream_t stream) {
   double* resid = reinterpret_cast<double*>(ws + w.resid);
   const int nch = n_chunks(a.vocab);
   const dim3 grid(nch, a.batch * (a.n_tree + 1));
+  const int rows = a.batch * (a.n_tree + 1);
+  if (a.mode == JK_GREEDY && a.batch + rows <= kGreedyWords) {
+    // A workgroup for each CU at least, in chunks no smaller than the two launches'.  Workgroups of 1024 threads where all of
+    // them are resident at once, else of 512 (us, 512 / 1024 threads: four trees of 60 nodes, 32000 entries 9.3 / 8.9, eight
+    // 16.3 / 15.3; five, 50257 entries 20.6 / 22.4; four of 100 nodes, 128256 entries 40.7 / 43.1).
+    const int cus = device_cu_count();
+    int threads = 1024, parts = (a.vocab + greedy_chunk(threads) - 1) / greedy_chunk(threads);
+    if ((long long)parts * rows > 2 * cus) {  // (more than are resident at once)
+      threads = 512;
+      parts = (a.vocab + greedy_chunk(threads) - 1) / greedy_chunk(threads);
+    }
+    if (parts < cus / rows) parts = cus / rows < nch ? cus / rows : nch;
+    GreedyParams gp;
+    gp.n_tree = a.n_tree; gp.vocab = a.vocab; gp.max_depth = a.max_depth;
+    gp.chunk = ((a.vocab + parts - 1) / parts + 3) / 4 * 4;
+    gp.mg_rows = (1ull << 32) / (unsigned)(a.n_tree + 1) + 1;
+    gp.tokens = a.tokens; gp.parent = a.parent; gp.logits = a.logits;
+    gp.part = reinterpret_cast<uint64_t*>(ws + w.pmax);
+    gp.words = reinterpret_cast<unsigned*>(ws + w.words);
+    gp.out_path = a.out_path; gp.out_len = a.out_len; gp.out_bonus = a.out_bonus;
+    gp.err = reinterpret_cast<unsigned*>(ws);
+    const int loads = (gp.chunk + threads * 4 - 1) / (threads * 4);
+    if (threads == 1024) launch_greedy<1024>(gp, loads, dim3(parts, rows), stream);
+    else launch_greedy<512>(gp, loads, dim3(parts, rows), stream);
+    return hipGetLastError();
+  }
   if (a.mode == JK_GREEDY) {
     hipLaunchKernelGGL(row_reduce_kernel<false>, grid, dim3(256), 0, stream, a.logits, a.vocab, 1.0, pmax, pidx,
                        psum);

@@ -59,6 +59,16 @@ __device__ __forceinline__ float wave_max(float v) {
   v = fmaxf(v, __uint_as_float(other32(__float_as_uint(v), lane & 32)));
   return v;
 }
+__device__ __forceinline__ int wave_min(int v) {
+  v = min(v, dpp<0xB1>(v));
+  v = min(v, dpp<0x4E>(v));
+  v = min(v, dpp<0x141>(v));
+  v = min(v, dpp<0x140>(v));
+  const int lane = __lane_id();
+  v = min(v, (int)other16((unsigned)v, lane & 16));
+  v = min(v, (int)other32((unsigned)v, lane & 32));
+  return v;
+}
 __device__ __forceinline__ float wave_sum(float v) {
   v += __int_as_float(dpp<0xB1>(__float_as_int(v)));
   v += __int_as_float(dpp<0x4E>(__float_as_int(v)));

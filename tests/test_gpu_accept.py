@@ -571,3 +571,53 @@ def test_sample_residual_that_vanishes_in_the_middle_of_the_siblings():
         for single in (0, 1):
             tune("accept_single", single)
             assert _compare(a, par, "sample") == 0
+
+
+@pytest.mark.parametrize("B,T,V", [
+    (1, 1, 1), (1, 1, 70000), (1, 63, 4100), (1, 64, 16383), (2, 65, 16388), (1, 128, 33000),   # nodes: one and two per lane
+    (3, 60, 32764), (4, 60, 32768), (4, 63, 32772),          # one and two loads' worth more or less than a workgroup takes
+    (8, 63, 4097), (9, 63, 16390),                           # 512 and 576 rows: workgroups of 1024 and of 512 threads
+    (2032, 1, 40), (2033, 1, 40),                            # as many words as the workspace has; one tree more: two launches
+])
+def test_greedy_in_one_launch_at_its_edges(B, T, V):
+    """Ties and maxima on either side of every chunk boundary, rows of -inf and of NaN; the same workspace three times, with
+    attention calls that merge inside their kernel in between (they use the same header words)."""
+    rng = np.random.default_rng(B * 1000 + T)
+    logits = rng.standard_normal((B, T + 1, V)).astype(np.float32)
+    edges = [e for c in (0, 4, 4096, 8192, 16384, 32768, V // 2, V) for e in (c - 1, c) if 0 <= e < V]
+    for b in range(B):
+        for r in range(T + 1):
+            for e in rng.choice(edges, 2):
+                logits[b, r, e] = 9.0                        # (twice: the lower id counts)
+    logits[0, T] = -np.inf
+    if V > 1:
+        logits[B - 1, 0, 0] = np.nan                         # a NaN is no maximum
+    par = np.stack([np.array([-1] + [int(rng.integers(-1, i)) for i in range(1, T)], dtype=np.int32) for _ in range(B)])
+    amax = np.array([[0 if np.isneginf(x).all() else int(np.nanargmax(x)) for x in rows] for rows in logits])
+    tokens = rng.integers(0, V, (B, T)).astype(np.int32)
+    for b in range(B):
+        for k in range(T):
+            if rng.random() < 0.6:
+                tokens[b, k] = amax[b, par[b, k] + 1]
+    x = [torch.from_numpy(v).cuda() for v in (tokens, par, logits)]
+    q = torch.randn((1, 8, 8, 128), device="cuda").to(torch.bfloat16)
+    kv = [torch.randn((1, n, 2, 128), device="cuda").to(torch.bfloat16) for n in (2000, 2000, 8, 8)]
+    chain, plen = torch.arange(-1, 7, dtype=torch.int32, device="cuda")[None], torch.tensor([2000], dtype=torch.int32, device="cuda")
+    need = max(jk.accept_path_workspace(B, T, V, jk.JK_GREEDY), jk.tree_verify_attention_workspace(q, kv[0], kv[2], 2000))
+    ws = torch.zeros(need, dtype=torch.uint8, device="cuda")
+    for arrangement in (None, (8, 1), (4, 1)):
+        path, alen, bonus = (v.cpu().numpy() for v in jk.accept_path(*x, jk.JK_GREEDY, max_depth=5, workspace=ws))
+        for b in range(B):
+            c, want = -1, []
+            while len(want) < 5:
+                kids = [k for k in range(T) if par[b, k] == c and tokens[b, k] == amax[b, c + 1]]
+                if not kids:
+                    break
+                c = kids[0]
+                want.append(c)
+            assert alen[b] == len(want) and path[b].tolist() == want + [-1] * (5 - len(want)) and bonus[b] == amax[b, c + 1]
+        if arrangement:
+            tune("attn_wm", arrangement[0]); tune("attn_wn", arrangement[1]); tune("attn_splits", 4)
+        if jk.tree_verify_attention_workspace(q, kv[0], kv[2], 2000) <= ws.numel():
+            jk.tree_verify_attention(q, *kv, chain, plen, workspace=ws)
+    assert jk.last_device_error(ws) == 0
