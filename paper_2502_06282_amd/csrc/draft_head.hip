@@ -592,8 +592,8 @@ __global__ __launch_bounds__(256) void linear_finish_kernel(LinFinishParams p) {
 }
 
 // parts of a product with few output columns, at most 64 MB of partial results
-int capped_ksplit(int m, int n, int k, int split_ns) {
-  int s = stream_gemm_ksplit(m, n, k, 1, false, split_ns);
+int capped_ksplit(int m, int n, int k, int split_ns, double* ns = nullptr) {
+  int s = stream_gemm_ksplit(m, n, k, 1, false, split_ns, ns);
   while (s > 1 && (size_t)s * m * n * 4 > ((size_t)64 << 20)) --s;
   return s;
 }
@@ -726,14 +726,16 @@ size_t linear_workspace_bytes(int m, int n, int k) {
 }
 
 hipError_t launch_linear(const LinearArgs& a, hipStream_t stream) {
-  const int ks = capped_ksplit(a.m, a.n, a.k, kLinearSplitNs);
+  double ns = 0.0;
+  const int ks = capped_ksplit(a.m, a.n, a.k, kLinearSplitNs, &ns);
   StreamGemmArgs g{};
   g.x = static_cast<const uint16_t*>(a.x); g.w = static_cast<const uint16_t*>(a.w);
   g.m = a.m; g.n = a.n; g.k = a.k; g.ksplit = ks; g.y_split = (long long)a.m * a.n; g.batch = 1;
-  if (ks == 1) {
+  const bool narrow = narrow_gemm_takes(a.m, a.n, a.k, ns);
+  if (ks == 1 || narrow) {
     g.finish = true;
     g.y = a.out_f32; g.residual = static_cast<const uint16_t*>(a.residual); g.out_bf16 = static_cast<uint16_t*>(a.out_bf16);
-    return launch_stream_gemm(g, stream);
+    return narrow ? launch_narrow_gemm(g, stream) : launch_stream_gemm(g, stream);
   }
   g.y = static_cast<float*>(a.workspace);
   hipError_t e = launch_stream_gemm(g, stream);

@@ -167,8 +167,11 @@ struct StreamGemmArgs {
   uint16_t* act;
   long long act_batch;
 };
-int stream_gemm_ksplit(int m, int n, int k, int batch, bool pair, int split_ns);
+int stream_gemm_ksplit(int m, int n, int k, int batch, bool pair, int split_ns, double* ns = nullptr);
 hipError_t launch_stream_gemm(const StreamGemmArgs& p, hipStream_t stream);       // m <= 256
+// plain products with `finish` of few rows and columns, in one launch; others_ns: what launch_stream_gemm is estimated to take
+bool narrow_gemm_takes(int m, int n, int k, double others_ns);
+hipError_t launch_narrow_gemm(const StreamGemmArgs& p, hipStream_t stream);
 hipError_t launch_stream_gemm_pair(const StreamGemmArgs& p, hipStream_t stream);  // m <= 128
 hipError_t launch_stream_gemm_down(const StreamGemmArgs& p, hipStream_t stream);  // m <= 128
 

@@ -356,8 +356,8 @@ hipError_t launch(const StreamGemmArgs& p, hipStream_t stream) {
 // of fewer workgroups than CUs takes as long as its workgroups alone.  A part more costs its fp32 partial results,
 // written and read once at about 4 000 bytes per ns, and the first one what `split_ns` says (another launch).  The count
 // with the least time by this estimate (in ns), fewer parts where it is a tie; a part keeps at least 128 of k.
-// `batch`: products in one launch that really run.
-int stream_gemm_ksplit(int m, int n, int k, int batch, bool pair, int split_ns) {
+// `batch`: products in one launch that really run.  *ns (or null): the estimate.
+int stream_gemm_ksplit(int m, int n, int k, int batch, bool pair, int split_ns, double* ns) {
   const int cus = device_cu_count();
   const double rows = strip_rows(m <= 128 ? 1 : 2), out = (double)n * (pair ? 2 : 1);
   const int units = k / 128, top = units < 64 ? units : 64;
@@ -374,6 +374,7 @@ int stream_gemm_ksplit(int m, int n, int k, int batch, bool pair, int split_ns) 
       best = s;
     }
   }
+  if (ns) *ns = best_t;
   return best;
 }
 
@@ -448,5 +449,216 @@ hipError_t launch_experts(const StreamGemmArgs& p, hipStream_t stream) {
 
 hipError_t launch_stream_gemm_pair(const StreamGemmArgs& p, hipStream_t stream) { return launch_experts<PAIR>(p, stream); }
 hipError_t launch_stream_gemm_down(const StreamGemmArgs& p, hipStream_t stream) { return launch_experts<DOWN>(p, stream); }
+
+// ------------------------------------------------------------------ few output columns, few rows
+namespace {
+struct NarrowArgs {
+  const uint16_t *x, *w, *residual;
+  float* y;
+  uint16_t* out_bf16;
+  int m, n, k, strip;
+};
+constexpr int kNarrowWaves = 8;
+constexpr int kNarrowLd = 144;  // bytes per row of X in LDS: 64 k and 16 bytes of padding
+constexpr int narrow_lds(int mt, int nf) {
+  const int x = kNarrowWaves * mt * 16 * kNarrowLd, sums = kNarrowWaves * nf * mt * 1024;
+  return x > sums ? x : sums;
+}
+
+// Y = X . W^T (+ residual) for up to 64 rows and at most 64 columns per CU: a workgroup per CU has its strip of weight rows
+// and all of k, its eight waves every eighth 64 of k each (128-byte lines of 16 rows), and adds the waves' sums up in LDS.
+// Against parts of k per workgroup it saves writing the partial results, the launch that adds them up, and the barriers of
+// X's way through LDS; in exchange every CU draws all of X from L2.  That is what bounds it beyond some twenty rows: with
+// X straight in MFMA layout, 16 rows by 16 bytes an instruction, a CU drew 31 bytes per ns (its address unit takes a lane a
+// cycle unless neighbours are neighbours in memory too); eight rows by 128 bytes, turned round in the wave's own piece of
+// LDS, come at 60.  The weights, read once, stay in MFMA layout.  (Loads return in order: X asked for later than the
+// weights in flight would wait for them, so both are as far ahead.)
+// Measured (us, parts and a second launch / this): 4096 x 4096, 8 rows 12.1 / 8.2, 24 12.7 / 10.3, 40 14.5 / 12.5; 6144 x
+// 4096 15.3 / 11.3, 16.2 / 13.9, 17.4 / 15.7; 4096 x 8192 19.1 / 14.3, 20.1 / 17.3, 21.5 / 21.5; 16384 x 2048 19.0 / 13.7,
+// 22.7 / 15.2, 24.4 / 16.9; 2048 x 2048 8.2 / 4.0, 8.0 / 4.7, 9.3 / 5.9.
+// RG: groups of eight rows of X; NF: groups of 16 weight rows
+template <int RG, int NF>
+__global__ __launch_bounds__(64 * kNarrowWaves, 2) void narrow_gemm_kernel(NarrowArgs p) {
+  constexpr int MT = (RG + 1) / 2, TILES = NF * MT;
+  constexpr int AHEAD = 2;  // units whose operands are in flight (four: no difference)
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  floatx4* sums = reinterpret_cast<floatx4*>(smem);  // [wave][tile][lane], behind the loop
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, g = lane >> 4;
+  const int all = gridDim.x, blk = blockIdx.x;
+  const int strip = all % 8 == 0 ? (blk & 7) * (all >> 3) + (blk >> 3) : blk;  // (neighbours on one XCD share lines of Y)
+  const int n_base = strip * p.strip, n_end = min(n_base + p.strip, p.n);
+  // (byte offsets from one scalar address each; rows past the end repeat the last one, and are not stored)
+  const char *w0 = reinterpret_cast<const char*>(p.w + (long long)n_base * p.k), *x0 = reinterpret_cast<const char*>(p.x);
+  unsigned wr[NF], xr[RG];
+#pragma unroll
+  for (int f = 0; f < NF; ++f) wr[f] = (unsigned)min(16 * f + r, n_end - 1 - n_base) * (unsigned)p.k * 2u + 16 * g;
+#pragma unroll
+  for (int i = 0; i < RG; ++i) xr[i] = (unsigned)min(8 * i + (lane >> 3), p.m - 1) * (unsigned)p.k * 2u + 16 * (lane & 7);
+  unsigned char* own = smem + wave * (MT * 16 * kNarrowLd);  // this wave's part of X, a unit at a time
+  unsigned char* put = own + (lane >> 3) * kNarrowLd + 16 * (lane & 7);
+  const unsigned char* get = own + r * kNarrowLd + 16 * g;
+  const int count = (p.k / 64 - wave + kNarrowWaves - 1) / kNarrowWaves;  // this wave's units
+  // (workgroups start at different units: see Weights::chunk)
+  const int rot = count > 0 ? (int)((5u * blk + (blk >> 3)) % (unsigned)count) : 0;
+  bf16x8 a[AHEAD][NF][2];
+  u32x4 b[AHEAD][RG];
+  auto load = [&](int j, int slot) {
+    const int u = j + rot, at = (wave + kNarrowWaves * (u < count ? u : u - count)) * 128;
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) a[slot][f][s] = *reinterpret_cast<const bf16x8*>(w0 + at + wr[f] + 64 * s);
+#pragma unroll
+    for (int i = 0; i < RG; ++i) b[slot][i] = *reinterpret_cast<const u32x4*>(x0 + at + xr[i]);
+  };
+  floatx4 acc[NF][MT];
+#pragma unroll
+  for (int f = 0; f < NF; ++f)
+#pragma unroll
+    for (int t = 0; t < MT; ++t) acc[f][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+  auto use = [&](int slot) {  // (LDS operations of a wave complete in order)
+#pragma unroll
+    for (int i = 0; i < RG; ++i) *reinterpret_cast<u32x4*>(put + i * 8 * kNarrowLd) = b[slot][i];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    bf16x8 x[MT][2];  // (all of them asked for before the first is used)
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) x[t][s] = *reinterpret_cast<const bf16x8*>(get + t * 16 * kNarrowLd + 64 * s);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int f = 0; f < NF; ++f) acc[f][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[slot][f][s], x[t][s], acc[f][t], 0, 0, 0);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  if (count < AHEAD) {  // (k below 1024)
+    for (int j = 0; j < count; ++j) {
+      load(j, 0);
+      use(0);
+    }
+  } else {
+    // (no load under a condition: behind one the compiler waits as if it had not been issued, i.e. for all others)
+#pragma unroll
+    for (int j = 0; j < AHEAD; ++j) load(j, j);
+    int j = 0;
+    for (; j + 2 * AHEAD <= count; j += AHEAD) {
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) {
+        use(u);
+        load(j + u + AHEAD, u);
+      }
+    }
+    if (count - j == AHEAD) {
+      use(0);
+      use(1);
+    } else {
+      use(0);
+      load(j + 2, 0);
+      use(1);
+      use(0);
+    }
+  }
+  __syncthreads();  // (the sums take the place of X)
+#pragma unroll
+  for (int f = 0; f < NF; ++f)
+#pragma unroll
+    for (int t = 0; t < MT; ++t) sums[(wave * TILES + f * MT + t) * 64 + lane] = acc[f][t];
+  __syncthreads();
+  const bool vec = (p.n & 3) == 0 && (reinterpret_cast<size_t>(p.y) & 15) == 0 && (reinterpret_cast<size_t>(p.residual) & 7) == 0 &&
+                   (reinterpret_cast<size_t>(p.out_bf16) & 7) == 0;
+  for (int i = tid; i < TILES * 64; i += 64 * kNarrowWaves) {
+    floatx4 part[kNarrowWaves];
+#pragma unroll
+    for (int w = 0; w < kNarrowWaves; ++w) part[w] = sums[w * TILES * 64 + i];
+#pragma unroll
+    for (int d = 1; d < kNarrowWaves; d *= 2)  // (two and two: fewer roundings on the way of each)
+#pragma unroll
+      for (int w = 0; w < kNarrowWaves; w += 2 * d) part[w] += part[w + d];
+    floatx4 v = part[0];
+    // (a lane of a tile has row lane % 16 of X and four consecutive columns)
+    const int tile = i >> 6, row = (tile % MT) * 16 + (i & 15), col = n_base + (tile / MT) * 16 + ((i & 63) >> 4) * 4;
+    if (row >= p.m || col >= n_end) continue;
+    const long long at = (long long)row * p.n + col;
+    if (vec && col + 4 <= n_end) {
+      if (p.residual) {
+        const uint2 q = *reinterpret_cast<const uint2*>(p.residual + at);
+        v += floatx4{bf16_lo(q.x), bf16_hi(q.x), bf16_lo(q.y), bf16_hi(q.y)};
+      }
+      if (p.y) *reinterpret_cast<floatx4*>(p.y + at) = v;
+      if (p.out_bf16) {
+        uint2 o;
+        o.x = bf16_bits_rne(v[0]) | (bf16_bits_rne(v[1]) << 16);
+        o.y = bf16_bits_rne(v[2]) | (bf16_bits_rne(v[3]) << 16);
+        *reinterpret_cast<uint2*>(p.out_bf16 + at) = o;
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (col + e >= n_end) break;
+        float s = v[e];
+        if (p.residual) s += bf16_lo(p.residual[at + e]);
+        if (p.y) p.y[at + e] = s;
+        if (p.out_bf16) p.out_bf16[at + e] = (uint16_t)bf16_bits_rne(s);
+      }
+    }
+  }
+}
+
+template <int RG, int NF>
+hipError_t launch_narrow(const NarrowArgs& p, hipStream_t stream) {
+  static LdsLimitRaised raised;
+  constexpr int smem = narrow_lds((RG + 1) / 2, NF);
+  if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(narrow_gemm_kernel<RG, NF>), smem, raised); e != hipSuccess) return e;
+  hipLaunchKernelGGL((narrow_gemm_kernel<RG, NF>), dim3((unsigned)((p.n + p.strip - 1) / p.strip)), dim3(64 * kNarrowWaves), smem, stream, p);
+  return hipGetLastError();
+}
+template <int RG>
+hipError_t launch_narrow_rows(const NarrowArgs& p, hipStream_t stream) {
+  const int groups = (p.strip + 15) / 16;
+  if (groups == 1) return launch_narrow<RG, 1>(p, stream);
+  if (groups == 2) return launch_narrow<RG, 2>(p, stream);
+  if constexpr (RG <= 6) {
+    if (groups == 3) return launch_narrow<RG, 3>(p, stream);
+    if (groups == 4) return launch_narrow<RG, 4>(p, stream);
+  }
+  return hipErrorInvalidValue;
+}
+}  // namespace
+
+// By its estimated time against that of the other way (`others_ns`, which comes out 10 % low on average): the HBM share of
+// the weights, or what a CU draws of its weights and of X at 31 and 60 bytes per ns.  Over 144 timed products (3 - 64 rows,
+// 768 - 16384 columns, k 768 - 14336) the choice is 0.7 % behind the faster one, 1.6 % at most where it takes this one.
+// (More than 48 rows with strips of more than 32 leave it without registers.)
+namespace {
+int narrow_strip(int n) { return ((n + device_cu_count() - 1) / device_cu_count() + 3) / 4 * 4; }
+}  // namespace
+bool narrow_gemm_takes(int m, int n, int k, double others_ns) {
+  const int strip = n <= 64 * device_cu_count() ? narrow_strip(n) : 65, groups = (m + 7) / 8;
+  if (m > 64 || strip > 64 || (m > 48 && strip > 32)) return false;
+  const double hbm = 2.0 * n * k / 6000.0, cu = 2.0 * k * (strip / 31.0 + 8.0 * groups / 60.0);
+  const double h2 = hbm * hbm, c2 = cu * cu, ns = 2200.0 + std::sqrt(std::sqrt(h2 * h2 + c2 * c2));
+  return ns * (groups > 4 ? 1.0 + 0.05 * (groups - 4) : 1.0) < 1.04 * others_ns;
+}
+hipError_t launch_narrow_gemm(const StreamGemmArgs& g, hipStream_t stream) {
+  NarrowArgs p;
+  p.x = g.x; p.w = g.w; p.residual = g.residual; p.y = g.y; p.out_bf16 = g.out_bf16;
+  p.m = g.m; p.n = g.n; p.k = g.k;
+  p.strip = narrow_strip(g.n);
+  switch ((g.m + 7) / 8) {
+    case 1: return launch_narrow_rows<1>(p, stream);
+    case 2: return launch_narrow_rows<2>(p, stream);
+    case 3: return launch_narrow_rows<3>(p, stream);
+    case 4: return launch_narrow_rows<4>(p, stream);
+    case 5: return launch_narrow_rows<5>(p, stream);
+    case 6: return launch_narrow_rows<6>(p, stream);
+    case 7: return launch_narrow_rows<7>(p, stream);
+    case 8: return launch_narrow_rows<8>(p, stream);
+    default: return hipErrorInvalidValue;
+  }
+}
 
 }  // namespace jk

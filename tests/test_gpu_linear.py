@@ -110,3 +110,22 @@ def test_row_blocks_strips_and_k_parts_at_their_edges(m, n, k):
     np.testing.assert_array_equal(both[1, 1:].cpu().numpy().reshape(m, n).astype(np.float64), want)
     np.testing.assert_array_equal(out16.float().cpu().numpy().reshape(m, n), round_to_bf16(want.astype(np.float32)))
     assert torch.isnan(both[0]).all() and torch.isnan(both[1, 0])
+
+
+@pytest.mark.parametrize("m", [1, 8, 9, 16, 17, 40, 48, 49, 64])
+@pytest.mark.parametrize("n,k", [
+    (1, 128), (7, 384), (1025, 640), (2047, 1024), (2500, 1152),        # strips of 4 - 12 rows; waves without a share of k,
+    (4096, 2048), (4100, 1664), (6144, 4096), (8190, 1024),             # with one, with an odd number of them
+    (12288, 512), (16384, 1024), (16385, 512),                          # strips of 48 and 64 rows; one more than that
+])
+def test_few_columns_are_bit_exact(m, n, k):
+    """Products for which a workgroup takes a strip of a few weight rows and all of k, and those just beyond; small whole
+    numbers, so that every order of summation gives the same."""
+    rng = np.random.default_rng(m + n + k)
+    x = rng.integers(-2, 3, size=(m, k)).astype(np.float32)
+    w = rng.integers(-1, 2, size=(n, k)).astype(np.float32) * np.float32(0.125)
+    r = rng.integers(-4, 5, size=(m, n)).astype(np.float32)
+    want = x @ w.T + r                                                    # (exact in fp32: multiples of 1/8 below 2^12)
+    got = jk.linear(_bf(x), _bf(w), _bf(r), out_dtype=torch.float32).cpu().numpy()
+    np.testing.assert_array_equal(got, want)
+    np.testing.assert_array_equal(jk.linear(_bf(x), _bf(w), _bf(r)).float().cpu().numpy(), round_to_bf16(want))
