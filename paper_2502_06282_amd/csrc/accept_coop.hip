@@ -15,7 +15,7 @@
 // W partials once all tags have appeared.  All workgroups reduce the same values
 // in the same order, so they take identical decisions.
 //
-// What bounds it: the chain of exchanges, 2 - 2.5 us each through memory (a store that every
+// What bounds it: the chain of exchanges, 1.5 - 2 us each through memory (a store that every
 // XCD can see, then a poll that sees it), not the bytes.  So the walk makes as few as it can and
 // hides its other work behind them:
 //   - an exchange carries, beside what it is needed for, the statistics of the row that comes
@@ -28,8 +28,10 @@
 //     before the exchange in front of them.
 // Reductions across a wave are DPP moves (a shuffle through LDS takes several times as long), one
 // wave polls and reduces for the workgroup.  Measured (MI355X, us per call): one 60-node tree over a 128K vocabulary
-// 43.6 -> 22.7, eight 100-node trees over a 32K vocabulary 48.4 -> 25.8 (mean of three draws each, two or three
-// accepted tokens); ten rejections in a row 30, i.e. 2.5 a rejection, which is the exchange itself.
+// 21.6 -> 18.7, eight 100-node trees over a 32K vocabulary 29.2 -> 23.0 (means of six draws), by asking for the words of an
+// exchange together (a poll used to be three or four trips to memory in a row) and by their layout.  (Tried: a tree's
+// workgroups on one XCD, exchanges through its L2: no faster than that, and one XCD's share of the memory bandwidth
+// is too little for large vocabularies: one tree over 128K 25 - 31 us.)
 //
 // Waiting is bounded: if a partner never shows up (the W workgroups of a tree are not all
 // resident) the walk gives up and reports accept_len = -1 instead of hanging; the last workgroup
@@ -45,14 +47,15 @@ constexpr int kCoopThreads = 256;
 constexpr int kCoopWaves = kCoopThreads / 64;
 constexpr unsigned kDefaultSpinLimit = 1u << 12;  // polls before giving up: a few milliseconds
 
-// One workgroup's contribution to an exchange.  Every 64-bit word holds the exchange's 32-bit tag
+// The workgroups' contributions to an exchange, word by word: a wave that looks for one word of all of them reads 512
+// bytes in a row (64 bytes per workgroup, all its words together, were 7 - 11 % slower).  Every 64-bit word holds the exchange's 32-bit tag
 // and 32 bits of payload and is written and read with one access, so a reader that sees the tag
 // also sees the payload that belongs to it: no fences and no ordering between the words are needed.
 // Words 0 - 3 are what the exchange is for: a residual's mass (a double in two words) and the
 // residual's value at the next candidate's token (likewise; only the owner's counts), or a logits row's sum of
 // exponentials (two words) and largest logit (word 2).  Words 4 - 6: the same of the row that may come next.
-struct Slot {
-  unsigned long long word[8];
+struct Table {
+  unsigned long long word[8][64];
 };
 
 // Per-tree words in the workspace header.  `epoch` numbers the calls: every exchange of a call is
@@ -61,19 +64,19 @@ struct Slot {
 // even after the others have given up and left - still read the call's own epoch and can never
 // publish a tag that a later call would take for its own.  The length and the bonus token are written
 // through to memory by the workgroups that know them; where one gave up, the last to finish overwrites them.
-struct TreeWords {  // 64 bytes
+struct TreeWords {  // 128 bytes: a line of its own
   unsigned long long epoch;
   unsigned finish;  // finished workgroups, and << 16 those that gave up
-  unsigned pad[13];
+  unsigned pad[29];
 };
 
 // What a tree owns in the workspace: its words and two exchange tables of up to 64 slots.  Tree b's
 // block sits at b * sizeof(TreeBlock) whatever the batch size, mode or vocabulary of a call is, and
 // the blocks of all kCoopMaxTrees trees are set aside in every acceptance workspace (see
 // accept_coop_bytes), so calls of different shapes and modes can share one workspace.
-struct TreeBlock {  // 8256 bytes
+struct TreeBlock {  // 8320 bytes
   TreeWords words;
-  Slot slots[2 * 64];
+  Table tables[2];
 };
 
 struct CoopParams {
@@ -233,14 +236,14 @@ __global__ __launch_bounds__(kCoopThreads, 2) void walk_sample_coop_kernel(CoopP
   // Tags: 22 bits of call epoch, 10 bits of exchange number (at most N + depth + 2 < 1024 per call).  The two tables take
   // turns from exchange to exchange and from call to call, and every exchange writes all its words.
   unsigned n_exch = 0, tag = 0;
-  Slot* tab = nullptr;
+  Table* tab = nullptr;
   auto open_exchange = [&] {
     ++n_exch;
     tag = (unsigned)(((epoch + 1) & 0x3FFFFFull) << 10) | (n_exch & 0x3FFu);
-    tab = p.trees[b].slots + ((n_exch + (unsigned)epoch) & 1u) * 64;
+    tab = p.trees[b].tables + ((n_exch + (unsigned)epoch) & 1u);
   };
   auto put = [&](int word, unsigned payload) {
-    __hip_atomic_store(&tab[w].word[word], ((unsigned long long)tag << 32) | payload, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&tab->word[word][w], ((unsigned long long)tag << 32) | payload, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
   auto publish4 = [&](double a, double v) {  // words 0 - 3
     if (tid < 4) {
@@ -260,13 +263,18 @@ __global__ __launch_bounds__(kCoopThreads, 2) void walk_sample_coop_kernel(CoopP
     unsigned spins = 0;
     for (;;) {
       bool ok = true;
+      unsigned long long v[4] = {};
+      if (in) {  // (one condition around all loads: with one around each the compiler waits for a word before it asks for the next)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (i < n && in) {
-          const unsigned long long v = __hip_atomic_load(&tab[lane].word[at + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          ok = ok && (unsigned)(v >> 32) == tag;
-          pay[i] = (unsigned)v;
-        }
+        for (int i = 0; i < 4; ++i)
+          if (i < n) v[i] = __hip_atomic_load(&tab->word[at + i][lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (i < n) {
+            ok = ok & ((unsigned)(v[i] >> 32) == tag);
+            pay[i] = (unsigned)v[i];
+          }
+      }
       if (__all(ok)) return true;
       if (++spins > p.spin_limit) return false;
       __builtin_amdgcn_s_sleep(1);
@@ -566,12 +574,12 @@ bool accept_coop_plan(int batch, int vocab, int cus, int* W, int* per) {
   if (batch > kCoopMaxTrees) return false;
   int most = (2 * cus) / batch;  // two workgroups per CU are resident together
   if (most > 64) most = 64;
-  // Entries per thread: fewer of them mean more workgroups to wait for, more of them longer rows of exponentials.  Eight
-  // trees of 32 000 entries: 2 a thread (63 workgroups a tree) 28.1, 4 (32) 25.9, 8 (16) 27.4, 16 (8) 34.7 us; one tree of
-  // 128 256: 8 (63) 24.4, 16 (32) 30.0 us.
-  for (int n = 4; n <= 16; n *= 2) {
+  // Entries per thread: fewer of them mean more workgroups to wait for, more of them longer rows of exponentials.  (us, trees x
+  // entries: 8 x 32000 with 2 a thread (63 workgroups a tree) 24.4, 4 (32) 23.1; 16 x 32000 with 4 25.2, 8 27.6; 64 x 8000
+  // 30.6, 34.3.)  Two only where every workgroup has a CU to itself: 1 x 8000 12.4, with four 13.3; 8 x 8000 20.4 and 22.7.
+  for (int n = 2; n <= 16; n *= 2) {
     const int need = (vocab + kCoopThreads * n - 1) / (kCoopThreads * n);
-    if (need <= most) {
+    if (need <= most && (n > 2 || need * batch <= cus)) {
       *W = need;
       *per = n;
       return true;
@@ -593,6 +601,7 @@ hipError_t launch_accept_coop(const AcceptArgs& a, void* coop_ws, int W, int per
   cp.out_path = a.out_path; cp.out_len = a.out_len; cp.out_bonus = a.out_bonus;
   const dim3 grid((unsigned)(a.batch * W)), block(kCoopThreads);
   switch (per) {
+    case 2: hipLaunchKernelGGL(walk_sample_coop_kernel<2>, grid, block, 0, stream, cp); break;
     case 4: hipLaunchKernelGGL(walk_sample_coop_kernel<4>, grid, block, 0, stream, cp); break;
     case 8: hipLaunchKernelGGL(walk_sample_coop_kernel<8>, grid, block, 0, stream, cp); break;
     case 16: hipLaunchKernelGGL(walk_sample_coop_kernel<16>, grid, block, 0, stream, cp); break;

@@ -621,3 +621,13 @@ def test_greedy_in_one_launch_at_its_edges(B, T, V):
         if jk.tree_verify_attention_workspace(q, kv[0], kv[2], 2000) <= ws.numel():
             jk.tree_verify_attention(q, *kv, chain, plen, workspace=ws)
     assert jk.last_device_error(ws) == 0
+
+
+@pytest.mark.parametrize("B,V", [(1, 511), (1, 513), (3, 1025), (9, 7680), (1, 32768), (1, 32769), (16, 8192), (16, 8193), (17, 8000)])
+def test_sample_few_workgroups_at_the_edges_of_their_shares(B, V):
+    """Two entries per thread while all workgroups have a CU to themselves (511 to 32768 entries of one tree, sixteen trees
+    of 8192 on 256 CUs), four beyond; full and partial last workgroups."""
+    cfg = CONFIGS["c3_llama3_8b"].with_(vocab=V, batch=B, n_tree=40)
+    par = tree_for_config(cfg, seed=V)
+    skipped = _compare(accept_inputs(cfg, par, seed=V), par, "sample")
+    assert skipped < B or B == 1
