@@ -5,7 +5,8 @@
 // divides by, and each head's top-k candidates.
 //
 // Kernels:
-//   head_inputs_kernel     X[2R, d] bf16 from f_top, s_top (elementwise, tiny)
+//   head_inputs_kernel     X[2R, d] bf16 from f_top, s_top (elementwise; more than 16 tokens:
+//                          of fewer the product makes its rows itself)
 //   row_parts_kernel, row_finish_kernel   per logits row: maximum, normaliser,
 //                          top-k by value (ties to the lower token id), probabilities.
 //   router_kernel, gated_act_kernel, select_kernel   the draft layer's router (Eq. 2, 5) and what
@@ -651,17 +652,21 @@ hipError_t launch_draft_heads(const DraftHeadsArgs& a, hipStream_t stream) {
   mp.s_top = a.s_top;
   mp.x = reinterpret_cast<unsigned short*>(ws);
   mp.rows = a.rows; mp.d = a.d_model; mp.mode = a.mode; mp.alpha = a.alpha; mp.beta = a.beta;
-  hipLaunchKernelGGL(head_inputs_kernel, dim3((unsigned)(((long long)a.rows * (a.d_model / 8) + 63) / 64)), dim3(64), 0, stream, mp);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  const bool mixes = m <= 32;  // the product makes its rows itself (see launch_stream_gemm_heads)
+  hipError_t e = hipSuccess;
+  if (!mixes) {
+    hipLaunchKernelGGL(head_inputs_kernel, dim3((unsigned)(((long long)a.rows * (a.d_model / 8) + 63) / 64)), dim3(64), 0, stream, mp);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
 
-  const uint16_t *x = reinterpret_cast<const uint16_t*>(ws), *w = static_cast<const uint16_t*>(a.w_head);
+  const uint16_t *x = mixes ? mp.f_top : reinterpret_cast<const uint16_t*>(ws), *w = static_cast<const uint16_t*>(a.w_head);
   float* parts = rp.ksplit > 1 ? reinterpret_cast<float*>(ws + rp.part_off) : nullptr;
   StreamGemmArgs g{};
   g.x = x; g.w = w; g.y = parts ? parts : a.logits;
   g.m = m; g.n = a.vocab; g.k = a.d_model;
   g.ksplit = rp.ksplit; g.y_split = (long long)m * a.vocab; g.batch = 1;
-  e = launch_stream_gemm(g, stream);
+  g.s_top = a.s_top; g.heads_mode = a.mode; g.alpha = a.alpha; g.beta = a.beta;
+  e = mixes ? launch_stream_gemm_heads(g, stream) : launch_stream_gemm(g, stream);
   if (e != hipSuccess) return e;
 
   SoftParams sp;

@@ -166,12 +166,19 @@ struct StreamGemmArgs {
   float* y2;            // act[e][row][n] = silu(x . w^T) * (x . w2^T) in bf16, act_batch elements between experts
   uint16_t* act;
   long long act_batch;
+  // output heads: row 2 r + h of the product's left side is made of rows 2 r and 2 r + 1 of x, token r's two features f1 and
+  // f2 with router scores s1 and s2 = s_top[2 r], s_top[2 r + 1]: s_(h + 1) f_(h + 1) (JK_HEADS_DECOUPLED), or
+  // s1 f1 + s2 f2 (h = 0) and beta f1 - alpha f2 (h = 1)
+  const float* s_top;
+  int heads_mode;
+  float alpha, beta;
 };
 int stream_gemm_ksplit(int m, int n, int k, int batch, bool pair, int split_ns, double* ns = nullptr);
 hipError_t launch_stream_gemm(const StreamGemmArgs& p, hipStream_t stream);       // m <= 256
 // plain products with `finish` of few rows and columns, in one launch; others_ns: what launch_stream_gemm is estimated to take
 bool narrow_gemm_takes(int m, int n, int k, double others_ns);
 hipError_t launch_narrow_gemm(const StreamGemmArgs& p, hipStream_t stream);
+hipError_t launch_stream_gemm_heads(const StreamGemmArgs& p, hipStream_t stream);  // m <= 32
 hipError_t launch_stream_gemm_pair(const StreamGemmArgs& p, hipStream_t stream);  // m <= 128
 hipError_t launch_stream_gemm_down(const StreamGemmArgs& p, hipStream_t stream);  // m <= 128
 

@@ -40,7 +40,9 @@ __device__ __forceinline__ float bf16_hi(unsigned w) { return __uint_as_float(w 
 //   PAIR   the same strip of two weight tensors (an expert's gate and up projections), for the rows of X that chose the
 //          expert; with an undivided k range the epilogue applies silu(gate) * up
 //   DOWN   a strip of an expert's output projection, for the rows it has
-enum Kind { PLAIN, PAIR, DOWN };
+//   HEADS  as PLAIN, of the rows that the two output heads see: row 2 r + h is c f_(h + 1) + c' f_(2 - h) of token r's two
+//          features, rows 2 r and 2 r + 1 of x, rounded to bf16 (see StreamGemmArgs)
+enum Kind { PLAIN, PAIR, DOWN, HEADS };
 
 // NF: 16-row weight fragments of a wave, side by side; a workgroup has a strip of 128 NF weight rows
 constexpr int strip_rows(int nf) { return 128 * nf; }
@@ -112,7 +114,10 @@ __device__ __forceinline__ void strip_products(const StreamGemmArgs& p, Weights<
   const int k0 = w.k0, k1 = w.k1, nc = (k1 - k0 + KC - 1) / KC;
   const uint16_t* px = p.x + (long long)e * p.x_batch;
   const uint16_t* xp[C::XP];
-  u32x4 xr[C::XP];
+  u32x4 xr[C::XP], xo[KIND == HEADS ? C::XP : 1];  // (HEADS: the token's other feature)
+  float c_own[C::XP], c_other[C::XP];
+  long long other[C::XP];
+  const bool mixed = KIND == HEADS && p.heads_mode != JK_HEADS_DECOUPLED;
   auto x_row = [&](int q) { return (tid + q * kThreads) / (KC / 8); };
   auto x_col = [&](int q) { return ((tid + q * kThreads) % (KC / 8)) * 8; };
   auto x_used = [&](int q) {
@@ -123,13 +128,43 @@ __device__ __forceinline__ void strip_products(const StreamGemmArgs& p, Weights<
     int row = min(x_row(q), m - 1);
     if (KIND == PAIR) row = list[row];
     xp[q] = px + (long long)row * p.k;
+    if constexpr (KIND == HEADS) {
+      other[q] = (row & 1) ? -(long long)p.k : (long long)p.k;
+      const float s_own = p.s_top[row], s_other = p.s_top[row ^ 1];
+      c_own[q] = mixed && (row & 1) ? -p.alpha : s_own;
+      c_other[q] = !mixed ? 0.f : (row & 1) ? p.beta : s_other;
+    }
   }
   auto load_x = [&](int kc) {
 #pragma unroll
     for (int q = 0; q < C::XP; ++q)
-      if (x_used(q)) xr[q] = *reinterpret_cast<const u32x4*>(xp[q] + min(kc + x_col(q), k1 - 8));
+      if (x_used(q)) {
+        const uint16_t* at = xp[q] + min(kc + x_col(q), k1 - 8);
+        xr[q] = *reinterpret_cast<const u32x4*>(at);
+        if constexpr (KIND == HEADS)
+          if (mixed) xo[q] = *reinterpret_cast<const u32x4*>(at + other[q]);
+      }
+  };
+  // (a term whose coefficient is zero is left out, so that a NaN in the other expert's feature cannot leak into a
+  // decoupled head)
+  auto mix = [&](u32x4 own, u32x4 oth, float c, float co) {
+    u32x4 o;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      float lo = c != 0.f ? c * bf16_lo(own[j]) : 0.f, hi = c != 0.f ? c * bf16_hi(own[j]) : 0.f;
+      if (mixed && co != 0.f) {
+        lo += co * bf16_lo(oth[j]);
+        hi += co * bf16_hi(oth[j]);
+      }
+      o[j] = bf16_bits_rne(lo) | (bf16_bits_rne(hi) << 16);
+    }
+    return o;
   };
   auto park_x = [&](int buf) {
+    if constexpr (KIND == HEADS) {
+#pragma unroll
+      for (int q = 0; q < C::XP; ++q) xr[q] = mix(xr[q], xo[q], c_own[q], c_other[q]);
+    }
 #pragma unroll
     for (int q = 0; q < C::XP; ++q)
       if (x_used(q)) *reinterpret_cast<u32x4*>(xbuf + buf * C::X_BYTES + x_row(q) * (C::LDX * 2) + x_col(q) * 2) = xr[q];
@@ -298,7 +333,7 @@ __global__ __launch_bounds__(kThreads, 2) void stream_gemm_kernel(StreamGemmArgs
   const int first = w.template chunk<KC>(0);
 #pragma unroll
   for (int j = 0; j < steps_ahead(NF); ++j) w.load(first + 32 * j, j);
-  if constexpr (KIND == PLAIN) {
+  if constexpr (KIND == PLAIN || KIND == HEADS) {
     strip_products<MT, NF, KIND>(p, w, p.m, nullptr, smem, e);
   } else {
     // The rows that chose expert e, in order.  Every wave makes the whole list (the same one) for itself: its LDS
@@ -341,7 +376,7 @@ hipError_t launch(const StreamGemmArgs& p, hipStream_t stream) {
   static LdsLimitRaised raised;
   // (more than half of the LDS: one workgroup per CU.  Two of them fit a CU's registers with few rows, and are put there
   // while other CUs have none: 1 row, two of 5 experts of 5632 x 12928: 280 us for the call, 215 like this)
-  constexpr int need = Cfg<MT, NF>::SMEM + (KIND == PLAIN ? 0 : kListBytes), smem = need > 82 * 1024 ? need : 82 * 1024;
+  constexpr int need = Cfg<MT, NF>::SMEM + (KIND == PLAIN || KIND == HEADS ? 0 : kListBytes), smem = need > 82 * 1024 ? need : 82 * 1024;
   if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(stream_gemm_kernel<MT, NF, KIND>), smem, raised); e != hipSuccess)
     return e;
   constexpr int COLS = strip_rows(NF) / (KIND == PAIR ? 2 : 1);
@@ -398,10 +433,10 @@ int strip_width(int n, int k, int narrowest, int widest) {
   return best;
 }
 
-template <int MT>
+template <int MT, Kind KIND = PLAIN>
 hipError_t launch_plain(const StreamGemmArgs& p, hipStream_t stream) {
   if constexpr (MT <= 8) {
-    return p.ksplit == 1 && strip_width(p.n, p.k, 1, 2) == 2 ? launch<MT, 2, PLAIN>(p, stream) : launch<MT, 1, PLAIN>(p, stream);
+    return p.ksplit == 1 && strip_width(p.n, p.k, 1, 2) == 2 ? launch<MT, 2, KIND>(p, stream) : launch<MT, 1, KIND>(p, stream);
   } else if constexpr (MT <= 10) {
     return p.ksplit == 1 && strip_width(p.n, p.k, 2, 3) == 3 ? launch<MT, 3, PLAIN>(p, stream) : launch<MT, 2, PLAIN>(p, stream);
   } else {
@@ -410,6 +445,16 @@ hipError_t launch_plain(const StreamGemmArgs& p, hipStream_t stream) {
 }
 }  // namespace
 
+// Every workgroup mixes the rows for itself instead of a launch in front of it (5 us, of which 2.5 show).  All kernels, us,
+// with the launch / without: 2 rows of 32000 x 4096 57.7 / 55.0, 20 rows 59.7 / 57.1, 128256 x 4096 197.7 / 195.8; 64
+// rows of 32000 x 4096 69.0 / 72.3, of 128256 x 4096 233 / 256: so up to two row blocks of 16.
+hipError_t launch_stream_gemm_heads(const StreamGemmArgs& p, hipStream_t stream) {
+  switch ((p.m + 15) / 16) {
+    case 1: return launch_plain<1, HEADS>(p, stream);
+    case 2: return launch_plain<2, HEADS>(p, stream);
+    default: return hipErrorInvalidValue;
+  }
+}
 hipError_t launch_stream_gemm(const StreamGemmArgs& p, hipStream_t stream) {
   switch ((p.m + 15) / 16) {
     case 1: return launch_plain<1>(p, stream);

@@ -220,3 +220,14 @@ def test_rows_with_fewer_finite_logits_than_candidates():
             assert tk[r, h, :3].tolist() == order
             np.testing.assert_allclose(tp[r, h, :3], q[r, h, order], rtol=1e-6)
             assert (tk[r, h, 3:] == 0).all() and (tp[r, h, 3:] == 0).all()
+
+
+@pytest.mark.parametrize("rows", [1, 8, 9, 16, 17])      # one and two row blocks of 16 mixed by the product itself; one more
+@pytest.mark.parametrize("d,vocab", [(128, 257), (640, 1025), (2048, 300), (384, 40000)])   # half chunks of k, divided k, whole k
+def test_rows_mixed_by_the_product_are_bit_exact(rows, d, vocab):
+    x = _exact_inputs(rows, d, vocab, rows + d)
+    _check(x, exact=True)
+    _check(x, mode=jk.JK_HEADS_CONTRASTIVE, alpha=0.5, beta=2.0, exact=True)
+    x["f_top"][0, 1, 3] = np.nan                         # left out where its coefficient is zero
+    lg, *_ = _call(x, mode=jk.JK_HEADS_CONTRASTIVE, alpha=0.0, beta=2.0)
+    assert np.isnan(lg[0, 0]).all() and np.isfinite(lg[0, 1]).all() and np.isfinite(lg[1:]).all()
