@@ -33,9 +33,9 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs (KiB per dispatch), each scaled by the same counter's reading
 # for a 256 MiB device copy (factors 2.00 and 1.00); source: profiles/<workload>_attention_and_acceptance.md.
 # {workload: bytes}; None for workloads that were not measured.
-MEASURED_TRAFFIC = {"c2_vicuna7b": 24614686, "c3_llama3_8b": 34364172, "c4_llama2_13b": 207000971,
-                    "c5_llama2_70b": 774242447, "c6_chain_sps": 272082512,
-                    "c7_static_tree": 77767665}
+MEASURED_TRAFFIC = {"c2_vicuna7b": 24614521, "c3_llama3_8b": 34363178, "c4_llama2_13b": 207014644,
+                    "c5_llama2_70b": 635371129, "c6_chain_sps": 272084630,
+                    "c7_static_tree": 77765133}
 
 
 def attn_bytes(cfg) -> int:
@@ -631,7 +631,8 @@ def main():
     # Which roof binds: the attention of one KV head is a dense contraction with T*G query rows per key;
     # above the ridge (peak flop/s / peak bytes/s = 312 flop/B) the matrix unit is the roof, below it HBM.
     intensity = flops_call / bytes_call
-    kernel_name = ("tva_bf16_kernel" + ("" if plan["splits"] == 1 or plan["fused"] else " + tva_combine_bf16_kernel")
+    bf16_kernel = "tva_wide_kernel" if plan["wm"] == 8 else "tva_bf16_kernel"
+    kernel_name = (bf16_kernel + ("" if plan["splits"] == 1 or plan["fused"] else " + tva_combine_bf16_kernel")
                    if cfg.dtype == "bf16" else "tva_f32_kernel + tva_combine_kernel")
     if intensity > MFMA_BF16_PEAK_TFLOPS * 1e3 / HBM_PEAK_GBPS and cfg.dtype == "bf16":
         roofline = {"bound": "mfma", "achieved": round(tflops, 1), "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",

@@ -52,8 +52,9 @@ struct AttnPlan {
 };
 
 // Every attention and acceptance workspace starts with a header: 256 bytes whose first word is the
-// sticky device error word (jk_last_device_error), then, in an attention workspace, one 64-byte line
-// of synchronisation words per (unit, row tile) group for the merge inside the kernel.  The header
+// sticky device error word (jk_last_device_error), then 64-byte lines of synchronisation words: in an
+// attention workspace one line per (unit, row tile) group for the merges inside the kernels, in an
+// acceptance workspace the counting words of the greedy launch (accept.hip).  The header
 // must be zero before the first use of a workspace and is kept consistent by the calls themselves.
 constexpr size_t kWsErrBytes = 256;
 constexpr int kMaxFusedGroups = 508;
