@@ -25,6 +25,7 @@
 #include <type_traits>
 
 #include "tva_tiles.h"
+#include "tva_wide_order.h"
 
 namespace jk {
 namespace {
@@ -46,7 +47,7 @@ struct WidePlan {
   using G_ = Geo<D>;
   static constexpr int HALF_BYTES = 64 * 1024;                   // K's half of the ring, in front of V's
   static constexpr int NR = HALF_BYTES / G_::TILE_BYTES;         // tiles in the ring: 8 (D = 128) or 16
-  static constexpr int AHEAD = NR - 1;                           // tiles asked for in front of the one in use
+  static constexpr int AHEAD = tva::wide_ahead(D);               // tiles asked for in front of the one in use
   static constexpr int RING_BYTES = 2 * HALF_BYTES;
   static constexpr int QROWS = kWideWaves * kWideRows;
   static constexpr int PATCH_LD = D * 2 + 16;                    // padded row of the store patches (after the loop)
@@ -54,7 +55,7 @@ struct WidePlan {
   static constexpr int PAGES_BYTES = PAGED ? kMaxPagesPerSplit * 4 : 0;
   static constexpr int DUMP_BYTES = 2 * G_::TILE_BYTES;          // where transfers go that nobody needs
   static constexpr int SMEM = RING_BYTES + DUMP_BYTES + JK_MAX_TREE * 16 + JK_MAX_TREE * 4 + 16 + PAGES_BYTES;
-  static_assert(kWideWaves * PATCH_BYTES <= RING_BYTES && SMEM <= 160 * 1024, "LDS plan");
+  static_assert(kWideWaves * PATCH_BYTES <= RING_BYTES && SMEM <= 160 * 1024 && AHEAD == NR - 1, "LDS plan");
 };
 
 // What a wave holds: two blocks of 32 query rows (a lane has row lane % 32 of each), and the operands in flight
@@ -417,25 +418,27 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
     st.m[r] = st.m[r] == -INFINITY ? tmax : st.m[r];
     st.mu[r] = st.m[r] == -INFINITY ? 0.f : st.m[r];
   };
-  // Before a tile: this wave's transfers of it have landed, then everybody's; everybody is also done with the tile
-  // in front of the one in use, whose place is therefore free.
-  int issued = min(n, (int)P_::AHEAD);  // tiles asked for, in order
-  auto landed = [&](int i) {
-    const int younger = min(issued - 1 - i, P_::AHEAD - 2);
-    if (younger == P_::AHEAD - 2) dev::wait_vm<(P_::AHEAD - 2) * N>();
-    else wait_dma<N>(younger);  // (waits for more than it has to where more than six tiles are younger)
-    __syncthreads();
-  };
   const int n_full = min(max(L / kTileKeys - ts.t_begin, 0), n);  // tiles without a mask, the split's first ones
 
   if (n > 0) {
-    // ---- tile 0: its scores for block 0; everything else of the pipeline starts with zeros
-    if (n >= P_::AHEAD) dev::wait_vm<(P_::AHEAD - 1) * N>();
-    else wait_dma<N>(n - 1);
-    __syncthreads();
+    // ---- the tiles: the steps that walk_tiles puts in order (tva_wide_order.h)
+    constexpr int HK = DK / 2;
+    auto wait = [&](int left, auto most) {
+      constexpr int MOST = decltype(most)::value;
+      if (left >= MOST) dev::wait_vm<MOST * N>();
+      else wait_dma<N>(left);  // (waits for more than it has to where more than six tiles may be left)
+    };
+    // where spare transfers go, and what they bring: the last tile without a mask once more
+    const unsigned dump = ring_addr + P_::RING_BYTES + wave * (N * 1024);
+    auto spare = [&]() {
+      const uint16_t* src = prefix_tile_base<PAGED>(ts, lc.cache, ts.t_begin + n_full - 1);
 #pragma unroll
-    for (int ks = 0; ks < DK; ++ks) st.kf[ks] = k_read(0, ks);
-    {
+      for (int c = 0; c < N; ++c) dma16(src, lc.off[c], dump + c * 1024);
+    };
+    // Tile 0: its scores for block 0; everything else of the pipeline starts with zeros
+    auto first = [&]() {
+#pragma unroll
+      for (int ks = 0; ks < DK; ++ks) st.kf[ks] = k_read(0, ks);
       const floatx16 zero = {};
       const bf16x8 none = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
 #pragma unroll
@@ -447,93 +450,76 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
 #pragma unroll
       for (int ks = 0; ks < DK; ++ks)
         st.s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(st.kf[ks], st.q[0][ks], ks == 0 ? zero : st.s[0], 0, 0, 0);
-    }
-    // ---- the tiles.  Step i needs K of tile i + 1 and V of tile i, and frees the place of tile i - 1.
-    constexpr int HK = DK / 2;
-    int i = 0;
-    auto step = [&](int i, auto special) {
-      constexpr bool LOOK = decltype(special)::value;
+    };
+    // One tile, wherever it lies
+    auto step = [&](int i) {
       const unsigned kt = (unsigned)((i + 1) % NR) * TILE_BYTES, vt = (unsigned)(i % NR) * TILE_BYTES;
-      if (LOOK) look(ts.t_begin + i, 0);
+      look(ts.t_begin + i, 0);
       phase<D, 1>(st, scale_log2, [&](int slot) {
         if (slot % 4 == 0) st.kf[slot / 4] = k_read(kt, slot / 4);
         if (slot % 4 == 2) st.vf[slot / 4] = v_read(vt, slot / 4);
       });
-      if (LOOK) look(ts.t_begin + i, 1);
+      look(ts.t_begin + i, 1);
       phase<D, 0>(st, scale_log2, [&](int slot) {
         if (slot < DK && slot % 2 == 0) st.kf[HK + slot / 2] = k_read(kt, HK + slot / 2);
         if (slot < DK && slot % 2 == 1) st.vf[HK + slot / 2] = v_read(vt, HK + slot / 2);
       });
     };
-    if (row0 >= M) {  // a wave of padding rows only moves tiles
-      for (; i + 1 < n; ++i) {
-        landed(i + 1);
-        for (; issued < min(n, i + NR); ++issued) transfer(issued);
+    // Four tiles without masks at a time, from tile 1 of the piece on: their places in the ring are known but for the
+    // upper bits, and every LDS address is one of twelve registers and an immediate.  One run of code without branches:
+    // its steps ask for full prefix tiles, or for the last of these once more where there is none left (to where
+    // nobody reads it).
+    unsigned here, there, ka[DK], va[DB];
+    PagedTile at;
+    const uint16_t* next;
+    auto run = [&](int i) {
+      here = (unsigned)((i - 1) % NR) * TILE_BYTES;
+      there = (unsigned)((i + 3) % NR) * TILE_BYTES;
+#pragma unroll
+      for (int ks = 0; ks < DK; ++ks) {
+        ka[ks] = (k_lane ^ (ks << 5)) + here;
+        asm volatile("" : "+v"(ka[ks]));  // (held: else made anew at u == 2, out of accumulation registers, between matrix instructions)
       }
-      if (n_full >= 5 && ((n_full - 1) & ~3) + 1 == n) __syncthreads();  // (the others' last step of four met for a tile that does not exist)
-    } else {
-      // One tile, wherever it lies
-      auto one = [&]() {
-        if (i + 1 < n) landed(i + 1);
-        for (; issued < min(n, i + NR); ++issued) transfer(issued);
-        step(i, std::true_type{});
-        ++i;
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
+        va[db] = (v_lane ^ (db << 6)) + here;
+        asm volatile("" : "+v"(va[db]));
+      }
+      if (PAGED) at = paged_tile(ts, min(i + P_::AHEAD + (lane & 3), n_full - 1), inv_tpp);
+      next = lc.cache + (PAGED ? 0 : (long long)(ts.t_begin + min(i + P_::AHEAD, n_full - 1)) * kTileKeys * ts.kc_sl);
+    };
+    auto run_step = [&](int i, int u) {
+      if (u == 2) {
+#pragma unroll
+        for (int ks = 0; ks < DK; ++ks) ka[ks] += there - here;
+      }
+      if (u == 3) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db) va[db] += there - here;
+      }
+      const unsigned kt = (unsigned)((u + 2) % 4) * TILE_BYTES, vt = (unsigned)((u + 1) % 4) * TILE_BYTES;
+      auto k_at = [&](int ks) { st.kf[ks] = lds_read128(ka[ks] + kt); };
+      auto v_at = [&](int h) {
+        st.vf[h] = lds_read_tr2(va[h % DB] + vt + 16 * (h / DB) * G_::ROW_BYTES, 8 * G_::ROW_BYTES);
       };
-      one();
-      // Four tiles without masks at a time, from tile 1 of the piece on: their places in the ring are known but for the
-      // upper bits, and every LDS address is one of twelve registers and an immediate.  One run of code without branches:
-      // its steps ask for full prefix tiles, or for the last of these once more where there is none left (to where
-      // nobody reads it); tiles with masks are asked for between the runs, once their places are free.
-      const unsigned dump = ring_addr + P_::RING_BYTES + wave * (N * 1024);
-      for (; i + 4 <= n_full; i += 4) {
-        for (issued = max(issued, n_full); issued < min(n, i + P_::AHEAD); ++issued) transfer(issued);
-        const unsigned here = (unsigned)((i - 1) % NR) * TILE_BYTES, there = (unsigned)((i + 3) % NR) * TILE_BYTES;
-        unsigned ka[DK], va[DB];
+      phase<D, 1>(st, scale_log2, [&](int slot) {
+        if (slot % 4 == 0) k_at(slot / 4);
+        if (slot % 4 == 2) v_at(slot / 4);
+      });
+      const uint16_t* src = next;
+      if (PAGED) src += at.offset(u);
+      else next += i + u + P_::AHEAD < n_full - 1 ? (long long)kTileKeys * ts.kc_sl : 0;
+      const unsigned to = i + u + P_::AHEAD < n_full ? ring_addr + lc.lds[0] + here + u * TILE_BYTES : dump;  // (the place of tile i + u - 1)
+      phase<D, 0>(st, scale_log2, [&](int slot) {
+        if (slot < DK && slot % 2 == 0) k_at(HK + slot / 2);
+        if (slot < DK && slot % 2 == 1) v_at(HK + slot / 2);
 #pragma unroll
-        for (int ks = 0; ks < DK; ++ks) ka[ks] = (k_lane ^ (ks << 5)) + here;
-#pragma unroll
-        for (int db = 0; db < DB; ++db) va[db] = (v_lane ^ (db << 6)) + here;
-        PagedTile at;
-        if (PAGED) at = paged_tile(ts, min(i + P_::AHEAD + (lane & 3), n_full - 1), inv_tpp);
-        const uint16_t* next = lc.cache + (PAGED ? 0 : (long long)(ts.t_begin + min(i + P_::AHEAD, n_full - 1)) * kTileKeys * ts.kc_sl);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          if (u == 2) {
-#pragma unroll
-            for (int ks = 0; ks < DK; ++ks) ka[ks] += there - here;
-          }
-          if (u == 3) {
-#pragma unroll
-            for (int db = 0; db < DB; ++db) va[db] += there - here;
-          }
-          dev::wait_vm<(P_::AHEAD - 2) * N>();
-          __syncthreads();
-          const unsigned kt = (unsigned)((u + 2) % 4) * TILE_BYTES, vt = (unsigned)((u + 1) % 4) * TILE_BYTES;
-          auto k_at = [&](int ks) { st.kf[ks] = lds_read128(ka[ks] + kt); };
-          auto v_at = [&](int h) {
-            st.vf[h] = lds_read_tr2(va[h % DB] + vt + 16 * (h / DB) * G_::ROW_BYTES, 8 * G_::ROW_BYTES);
-          };
-          phase<D, 1>(st, scale_log2, [&](int slot) {
-            if (slot % 4 == 0) k_at(slot / 4);
-            if (slot % 4 == 2) v_at(slot / 4);
-          });
-          const uint16_t* src = next;
-          if (PAGED) src += at.offset(u);
-          else next += i + u + P_::AHEAD < n_full - 1 ? (long long)kTileKeys * ts.kc_sl : 0;
-          const unsigned to = i + u + P_::AHEAD < n_full ? ring_addr + lc.lds[0] + here + u * TILE_BYTES : dump;  // (the place of tile i + u - 1)
-          phase<D, 0>(st, scale_log2, [&](int slot) {
-            if (slot < DK && slot % 2 == 0) k_at(HK + slot / 2);
-            if (slot < DK && slot % 2 == 1) v_at(HK + slot / 2);
-#pragma unroll
-            for (int c = 0; c < N; ++c)
-              if (slot == DK + c * DK / N) dma16(src, lc.off[c], to + c * 1024);
-          });
-        }
-      }
-      dev::wait_vm<0>();  // (what is still on its way: the last tile once more, tiles with masks)
-      issued = max(issued, min(n_full, i + P_::AHEAD));
-      while (i < n) one();
-    }
+        for (int c = 0; c < N; ++c)
+          if (slot == DK + c * DK / N) dma16(src, lc.off[c], to + c * 1024);
+      });
+    };
+    auto meet = [&]() { __syncthreads(); };
+    tva::walk_tiles<P_::AHEAD>(n, n_full, row0 >= M, transfer, spare, wait, meet, first, step, run, run_step);
     // ---- the last tile's value product for block 1
     softmax_rest<D, 1>(st, scale_log2);
 #pragma unroll
