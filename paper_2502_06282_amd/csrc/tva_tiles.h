@@ -28,6 +28,7 @@ struct KParams {
   // split merge inside this kernel (MERGE > 0; see merge_rows and the end of the kernel): sync = one
   // 64-byte line of words per (unit, row tile) group in the workspace header, spin_limit = polls a
   // workgroup spends waiting for its group before it leaves its slice to the group's last arriver
+  // (tva_wide.hip: for another one's stores, before it leaves its results too)
   unsigned* sync;
   unsigned* err;  // the workspace's sticky device error word
   unsigned spin_limit;

@@ -475,28 +475,22 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
     auto run = [&](int i) {
       here = (unsigned)((i - 1) % NR) * TILE_BYTES;
       there = (unsigned)((i + 3) % NR) * TILE_BYTES;
+      unsigned kl = k_lane, vl = v_lane;
+      asm volatile("" : "+v"(kl), "+v"(vl));  // (made anew: else twelve loop invariants, fetched from accumulation registers)
 #pragma unroll
       for (int ks = 0; ks < DK; ++ks) {
-        ka[ks] = (k_lane ^ (ks << 5)) + here;
+        ka[ks] = (kl ^ (ks << 5)) + here;
         asm volatile("" : "+v"(ka[ks]));  // (held: else made anew at u == 2, out of accumulation registers, between matrix instructions)
       }
 #pragma unroll
       for (int db = 0; db < DB; ++db) {
-        va[db] = (v_lane ^ (db << 6)) + here;
+        va[db] = (vl ^ (db << 6)) + here;
         asm volatile("" : "+v"(va[db]));
       }
       if (PAGED) at = paged_tile(ts, min(i + P_::AHEAD + (lane & 3), n_full - 1), inv_tpp);
       next = lc.cache + (PAGED ? 0 : (long long)(ts.t_begin + min(i + P_::AHEAD, n_full - 1)) * kTileKeys * ts.kc_sl);
     };
     auto run_step = [&](int i, int u) {
-      if (u == 2) {
-#pragma unroll
-        for (int ks = 0; ks < DK; ++ks) ka[ks] += there - here;
-      }
-      if (u == 3) {
-#pragma unroll
-        for (int db = 0; db < DB; ++db) va[db] += there - here;
-      }
       const unsigned kt = (unsigned)((u + 2) % 4) * TILE_BYTES, vt = (unsigned)((u + 1) % 4) * TILE_BYTES;
       auto k_at = [&](int ks) { st.kf[ks] = lds_read128(ka[ks] + kt); };
       auto v_at = [&](int h) {
@@ -517,8 +511,22 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
         for (int c = 0; c < N; ++c)
           if (slot == DK + c * DK / N) dma16(src, lc.off[c], to + c * 1024);
       });
+      // (for the next step, in front of its barrier)
+      if (u == 1) {
+#pragma unroll
+        for (int ks = 0; ks < DK; ++ks) ka[ks] += there - here;
+      }
+      if (u == 2) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db) va[db] += there - here;
+      }
     };
-    auto meet = [&]() { __syncthreads(); };
+    auto meet = [&]() {
+      __syncthreads();
+      // (a matrix instruction moved up in front of the barrier stalls the wave until the matrix unit takes it, and the
+      // others wait for the wave: 1 % of a long call)
+      __builtin_amdgcn_sched_barrier(0);
+    };
     tva::walk_tiles<P_::AHEAD>(n, n_full, row0 >= M, transfer, spare, wait, meet, first, step, run, run_step);
     // ---- the last tile's value product for block 1
     softmax_rest<D, 1>(st, scale_log2);
@@ -568,90 +576,101 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
     __syncthreads();
   }
 
-  // ---- Merge of the pieces, two and two: 0 with 1, 2 with 3, then those with each other, and so on.  Of two that meet the
-  // first to come leaves its results in memory, in fp32 and in the order of its registers, and is done; the second, which
-  // still has its own in registers, adds them: half the traffic of leaving all results for another kernel, and nobody
-  // waits for a workgroup that has not come yet (so any number of them may still be to start).  The sum is the same
-  // whoever comes first.  The meeting of two groups of pieces has the place of the right one's first piece: a word of the
-  // workspace's header (arrivals, and kWritten once the first one's results are in memory; zero again behind it), and
-  // the results.  The two may run on different XCDs, whose L2s know nothing of each other: stores go through to memory, and
-  // the loads bypass them (sc1, the scope of the device).
-  constexpr unsigned kWritten = 0x100u, kMostPolls = 1u << 20;
+  // ---- Merge of the pieces, two and two: the steps of merge_pieces (tva_wide_order.h).  Results are left in fp32 and in the
+  // order of the registers.  The sum is the same whoever comes first.  The two may run on different XCDs, whose L2s know
+  // nothing of each other: stores go through to memory, and the loads bypass them (sc1, the scope of the device).
   constexpr int QUADS = kBlocks * DB * 4;  // float4 per lane
   constexpr int kDeviceScope = 16;         // (the sc1 bit of a buffer load)
-  for (int held = 1, lo = split; held < pieces; held *= 2) {  // this workgroup holds pieces lo ... lo + held - 1
-    const bool right = (lo & held) != 0;
-    if (!right && lo + held >= pieces) continue;  // (nobody there)
-    const int place = (place0 + (right ? lo : lo + held) * place_step) * p.n_qtiles + qtile;
-    unsigned* word = p.sync + place / kWideWords * 16 + 3 + place % kWideWords;  // (the first three of a line belong to tva_bf16.hip)
-    float4* part = reinterpret_cast<float4*>(p.part_o) + (size_t)(place * kWideWaves + wave) * (QUADS * 64) + lane;
-    float2* ml = p.part_ml + (size_t)place * QROWS + wave * kWideRows + c32;
-    if (tid == 0) repeat_s[1] = (int)__hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  auto place_of = [&](int piece) { return (place0 + piece * place_step) * p.n_qtiles + qtile; };
+  auto word_of = [&](int m) {  // (the first three of a line belong to tva_bf16.hip)
+    const int place = place_of(m);
+    return p.sync + place / kWideWords * 16 + 3 + place % kWideWords;
+  };
+  int* answer_s = repeat_s + 1;  // thread 0's answer; two in turn, so that one barrier does
+  bool is_first = false;         // (thread 0's)
+  auto answered = [&]() {
     __syncthreads();
-    if (__builtin_amdgcn_readfirstlane(repeat_s[1]) == 0) {
-      if (row0 < M) {
-#pragma unroll
-        for (int r = 0; r < kBlocks; ++r) {
-          dev::store_through(ml + r * kWaveRows, dev::store_u32x2{__float_as_uint(st.m[r]), __float_as_uint(st.l[r][0])});
-#pragma unroll
-          for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-              const floatx16& o = st.o[r][db];
-              dev::store_through(part + ((r * DB + db) * 4 + q4) * 64,
-                                 dev::store_u32x4{__float_as_uint(o[4 * q4]), __float_as_uint(o[4 * q4 + 1]), __float_as_uint(o[4 * q4 + 2]), __float_as_uint(o[4 * q4 + 3])});
-            }
-        }
-      }
-      dev::wait_vm<0>();
-      __syncthreads();
-      if (tid == 0) __hip_atomic_fetch_add(word, kWritten, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      return;
-    }
+    return __builtin_amdgcn_readfirstlane(*answer_s);
+  };
+  auto arrive = [&](int m) {
+    answer_s = repeat_s + (answer_s == repeat_s + 1 ? 2 : 1);
     if (tid == 0) {
-      // (the other workgroup has come: it has nothing left to do but its stores.  The bound, about a second, is for a
-      // workspace that was never initialised.)
-      unsigned polls = 0;
-      while (!(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kWritten)) {
-        if (++polls > kMostPolls) {
-          __hip_atomic_fetch_or(p.err, kDevErrMergeWait, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          break;
+      unsigned* word = word_of(m);
+      is_first = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u;
+      int at = -1;
+      if (!is_first) {  // (the other workgroup has come: it has nothing left to do but its stores)
+        unsigned polls = 0;
+        for (;;) {
+          at = tva::others_results(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), false);
+          if (at >= 0) break;
+          if (++polls > p.spin_limit) {
+            __hip_atomic_fetch_or(p.err, kDevErrMergeWait, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            break;
+          }
+          __builtin_amdgcn_s_sleep(1);
         }
-        __builtin_amdgcn_s_sleep(1);
       }
-      __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      *answer_s = at;
     }
-    __syncthreads();
+    return answered();
+  };
+  auto leave = [&](int m) {
+    const int place = place_of(split);
     if (row0 < M) {
-      const auto theirs = __builtin_amdgcn_make_buffer_rsrc(p.part_o + (size_t)(place * kWideWaves + wave) * (QUADS * 64 * 4), 0, QUADS * 64 * 16, 0x00020000);
+      float4* part = reinterpret_cast<float4*>(p.part_o) + (size_t)(place * kWideWaves + wave) * (QUADS * 64) + lane;
+      float2* ml = p.part_ml + (size_t)place * QROWS + wave * kWideRows + c32;
 #pragma unroll
       for (int r = 0; r < kBlocks; ++r) {
-        const u32x2 other = __builtin_bit_cast(u32x2, __hip_atomic_load(reinterpret_cast<const uint64_t*>(ml + r * kWaveRows), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-        const float other_m = __uint_as_float(other[0]), other_l = __uint_as_float(other[1]);
-        u32x4 v[DB * 4];  // (all on their way before the first is used)
+        dev::store_through(ml + r * kWaveRows, dev::store_u32x2{__float_as_uint(st.m[r]), __float_as_uint(st.l[r][0])});
 #pragma unroll
-        for (int i = 0; i < DB * 4; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(theirs, lane * 16, (r * DB * 4 + i) * 1024, kDeviceScope);
-        __builtin_amdgcn_sched_barrier(0);
-        const float m = fmaxf(st.m[r], other_m), mu = m == -INFINITY ? 0.f : m;
-        const float w0 = fast_exp2(st.m[r] - mu), w1 = fast_exp2(other_m - mu);  // (exp2(-inf) = 0: a row without a key)
-        st.m[r] = m;
-        // (no fused multiply-add: it would round one of the two products only, and which one would be up to who came first)
-        auto sum = [&](float x, float y) {
-#pragma clang fp contract(off)
-          const float a = x * w0, c = y * w1;
-          return a + c;
-        };
-        st.l[r][0] = sum(st.l[r][0], other_l);
+        for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int i = 0; i < DB * 4; ++i) {
-          floatx16& o = st.o[r][i / 4];
-#pragma unroll
-          for (int k = 0; k < 4; ++k) o[4 * (i % 4) + k] = sum(o[4 * (i % 4) + k], __uint_as_float(v[i][k]));
-        }
+          for (int q4 = 0; q4 < 4; ++q4) {
+            const floatx16& o = st.o[r][db];
+            dev::store_through(part + ((r * DB + db) * 4 + q4) * 64,
+                               dev::store_u32x4{__float_as_uint(o[4 * q4]), __float_as_uint(o[4 * q4 + 1]), __float_as_uint(o[4 * q4 + 2]), __float_as_uint(o[4 * q4 + 3])});
+          }
       }
     }
-    lo &= ~held;
-  }
+    dev::wait_vm<0>();
+    __syncthreads();
+    if (tid == 0)
+      *answer_s = tva::others_results(__hip_atomic_fetch_or(word_of(m), tva::left_results(is_first, split), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), is_first);
+    return answered();
+  };
+  auto add = [&](int m, int at) {
+    if (tid == 0) __hip_atomic_store(word_of(m), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (row0 >= M) return;
+    const int place = place_of(at);
+    const float2* ml = p.part_ml + (size_t)place * QROWS + wave * kWideRows + c32;
+    const auto theirs = __builtin_amdgcn_make_buffer_rsrc(p.part_o + (size_t)(place * kWideWaves + wave) * (QUADS * 64 * 4), 0, QUADS * 64 * 16, 0x00020000);
+#pragma unroll
+    for (int r = 0; r < kBlocks; ++r) {
+      const u32x2 other = __builtin_bit_cast(u32x2, __hip_atomic_load(reinterpret_cast<const uint64_t*>(ml + r * kWaveRows), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+      const float other_m = __uint_as_float(other[0]), other_l = __uint_as_float(other[1]);
+      u32x4 v[DB * 4];  // (all on their way before the first is used)
+#pragma unroll
+      for (int i = 0; i < DB * 4; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b128(theirs, lane * 16, (r * DB * 4 + i) * 1024, kDeviceScope);
+      __builtin_amdgcn_sched_barrier(0);
+      const float m_new = fmaxf(st.m[r], other_m), mu = m_new == -INFINITY ? 0.f : m_new;
+      const float w0 = fast_exp2(st.m[r] - mu), w1 = fast_exp2(other_m - mu);  // (exp2(-inf) = 0: a row without a key)
+      st.m[r] = m_new;
+      // (no fused multiply-add: it would round one of the two products only, and which one would be up to who came first)
+      auto sum = [&](float x, float y) {
+#pragma clang fp contract(off)
+        const float a = x * w0, c = y * w1;
+        return a + c;
+      };
+      st.l[r][0] = sum(st.l[r][0], other_l);
+#pragma unroll
+      for (int i = 0; i < DB * 4; ++i) {
+        floatx16& o = st.o[r][i / 4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) o[4 * (i % 4) + k] = sum(o[4 * (i % 4) + k], __uint_as_float(v[i][k]));
+      }
+    }
+  };
+  if (!tva::merge_pieces(split, pieces, arrive, leave, add)) return;
 
   // ---- the finished rows, a block of 32 at a time through a patch of LDS so that they leave in whole 128-byte lines (see
   // tva_bf16.hip)

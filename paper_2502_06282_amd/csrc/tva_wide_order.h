@@ -1,7 +1,7 @@
-// The order in which a wave of tva_wide.hip asks for the tiles of its piece, waits for them and reads them, apart from what
-// it does with them: the kernel walks it with its own steps, and a host test with steps that keep a queue and check
-// that whatever is read has been waited for (nothing that a run on the card could show: a transfer that was not waited for
-// has usually arrived).  Not installed.
+// Two loops of tva_wide.hip, apart from what their steps do: the kernel walks them with its own steps, and a host test with
+// steps that check the order (nothing that a run on the card could show: a transfer that was not waited for has usually
+// arrived, and a workgroup hardly ever stops waiting for another).  The first is the order in which a wave asks for the tiles
+// of its piece, waits for them and reads them, the second the merge of the pieces.  Not installed.
 #pragma once
 
 namespace jk {
@@ -85,6 +85,50 @@ __attribute__((always_inline)) constexpr void walk_tiles(int n, int n_full, bool
   wait(0, Const<0>());  // (what is still on its way: spare ones, tiles with masks)
   asked = most(asked, least(n_full, i + AHEAD));
   while (i < n) one();
+}
+
+// Merge of the pieces of a row tile, two and two: 0 with 1, 2 with 3, then those with each other, and so on.  Of the two
+// workgroups that meet the first to come leaves its results in memory and is done; the second, which still has its own in
+// registers, adds them: half the traffic of leaving all results for another kernel, and nobody waits for a workgroup that has
+// not come yet (so any number of them may still be to start).  The second does wait for the first one's stores, but not
+// for ever: then it leaves its results as well, and of the two the one whose word about that is the later finds the other's
+// and adds them.  So everything is added whoever is held up, and for however long.
+//
+// A workgroup leaves its results at the place of its own piece (`split`), wherever it has got to: those that it left before it
+// went on after all are read by nobody.  The meeting of two groups of pieces has a word at the place of the right one's
+// first piece: arrivals, and for each of the two that its results are in memory, and the piece where.  Zero again behind it.
+constexpr unsigned kFirstLeft = 0x10u, kSecondLeft = 0x20u;
+constexpr int kMeetingPieces = 1 << 12;  // (a sequence's pieces: at most the batch's places, 64 sequences times 64 splits)
+constexpr unsigned left_results(bool first, int piece) { return first ? kFirstLeft | (unsigned)piece << 8 : kSecondLeft | (unsigned)piece << 20; }
+constexpr int others_results(unsigned word, bool first) {  // where the other one's are, or -1
+  if (!(word & (first ? kSecondLeft : kFirstLeft))) return -1;
+  return (int)(word >> (first ? 20 : 8)) & (kMeetingPieces - 1);
+}
+
+// The steps:
+//   arrive(m)    at meeting m: where the other one's results are, if this is the second to come and they are there in time,
+//                or -1
+//   leave(m)     leaves the own results, says so, and returns where the other one's are if those were left before, or -1
+//   add(m, at)   adds the results at place `at` to the own, and clears the meeting's word (both have said their last)
+// True for the workgroup that has all pieces in the end.
+template <class Arrive, class Leave, class Add>
+__attribute__((always_inline)) constexpr bool merge_pieces(int split, int pieces, Arrive& arrive, Leave& leave, Add& add) {
+  int lo = split;  // this workgroup holds pieces lo ... lo + held - 1
+  for (int held = 1; held < pieces; held *= 2) {
+    const bool right = (lo & held) != 0;
+    if (!right && lo + held >= pieces) continue;  // (nobody there)
+    const int m = right ? lo : lo + held;
+    int at = arrive(m);
+    if (at < 0) {
+      at = leave(m);
+      if (at < 0) return false;
+    }
+    // (of the other group, whatever a workspace that was never initialised says)
+    const int first = right ? lo - held : m, last = (right || m + held < pieces ? first + held : pieces) - 1;
+    add(m, at < first ? first : (at > last ? last : at));
+    lo &= ~held;
+  }
+  return true;
 }
 
 }  // namespace tva

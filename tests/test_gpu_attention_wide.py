@@ -75,6 +75,40 @@ def test_pieces(D, splits):
 
 
 @gpu
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("splits", [2, 3, 5, 8])
+def test_merge_when_the_wait_expires(D, splits):
+    """spin_limit 0: nobody waits for the other one's stores, the later of two that have left their results adds them.  Same
+    bits, the error word says that waits expired, and the workspace (its words are zero again) serves normal calls."""
+    cfg = _cfg(100, 8, 8, D, 1500, 2)
+    x, par = attention_inputs(cfg, scale_mult=np.sqrt(float(D))), _tree(2, 100, splits)
+    d = to_dev(x, "bf16")
+    parent, plen = torch.from_numpy(par).cuda(), torch.tensor([1500, 1490], dtype=torch.int32, device="cuda")
+    wide(splits)
+    ws = torch.empty(jk.tree_verify_attention_workspace(d["q"], d["k_cache"], d["k_tree"], 1500), dtype=torch.uint8, device="cuda")
+    jk.workspace_init(ws)
+
+    def call():
+        out = jk.tree_verify_attention(d["q"], d["k_cache"], d["v_cache"], d["k_tree"], d["v_tree"], parent, plen, workspace=ws)
+        torch.cuda.synchronize()
+        assert not ws[256:jk.JK_WORKSPACE_HEADER_BYTES].any()
+        return out
+
+    ref = call()
+    assert jk.last_device_error(ws) == 0
+    tune("spin_limit", 0)
+    for _ in range(5):
+        assert torch.equal(call(), ref)
+    # (of two pieces the one with the tree comes long after the other one's stores; of more, two of equal length meet)
+    assert jk.last_device_error(ws) in ((0, jk.JK_DEVERR_MERGE_WAIT) if splits == 2 else (jk.JK_DEVERR_MERGE_WAIT,))
+    tune("spin_limit", -1)
+    jk.workspace_init(ws[:jk.JK_WORKSPACE_HEADER_BYTES])
+    for _ in range(3):
+        assert torch.equal(call(), ref)
+    assert jk.last_device_error(ws) == 0
+
+
+@gpu
 @pytest.mark.parametrize("splits", [1, 2, 3, 6])
 @pytest.mark.parametrize("lens", [[600, 3, 90], [0, 600, 599, 1, 64], [600] * 4, [600] + [7] * 63])
 def test_batches(lens, splits):

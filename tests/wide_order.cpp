@@ -1,8 +1,18 @@
-// Walks walk_tiles (csrc/tva_wide_order.h) with steps that keep a wave's queue of transfers, and checks for every piece of up
-// to `kMostTiles` tiles that what a step reads has landed for every wave of the workgroup before the barrier in front of it, that a
-// place of the ring is filled again only when everybody is done with it, and that all waves meet as often.
+// Walks the two loops of csrc/tva_wide_order.h with steps that check them.
+// "tiles": walk_tiles with a wave's queue of transfers.  For every piece of up to `kMostTiles` tiles: what a step reads has
+// landed for every wave of the workgroup before the barrier in front of it, a place of the ring is filled again only when
+// everybody is done with it, and all waves meet as often.
+// "pieces": merge_pieces with a thread per workgroup, one of which runs at a time, another at every access to memory, chosen
+// by a seed.  However long each is held up, and however soon the second of two stops waiting: one has all pieces in the
+// end, once each, made of results that were whole when they were read; the words are zero again.
+#include <condition_variable>
 #include <cstdio>
+#include <cstring>
 #include <map>
+#include <mutex>
+#include <random>
+#include <set>
+#include <thread>
 #include <vector>
 
 #include "tva_wide_order.h"
@@ -79,6 +89,124 @@ int check() {
   std::printf("ahead %d: %d pieces, %d wrong\n", AHEAD, pieces, bad);
   return bad;
 }
+
+// One thread at a time: a thread that is about to touch memory hands the turn to one that the seed chooses, now and then
+// always the same one for a while (the others are held up)
+class Turns {
+ public:
+  Turns(int n, unsigned seed) : rng_(seed), alive_(n) {
+    for (int i = 0; i < n; ++i) alive_[i] = i;
+    turn_ = pick();
+  }
+  void wait(int me) {
+    std::unique_lock<std::mutex> l(m_);
+    cv_.wait(l, [&] { return turn_ == me; });
+  }
+  void pass(int me) {
+    {
+      std::lock_guard<std::mutex> l(m_);
+      turn_ = pick();
+      if (turn_ == me) return;
+    }
+    cv_.notify_all();
+    wait(me);
+  }
+  void end(int me) {
+    std::lock_guard<std::mutex> l(m_);
+    for (size_t k = 0; k < alive_.size(); ++k)
+      if (alive_[k] == me) alive_.erase(alive_.begin() + k);
+    turn_ = alive_.empty() ? -1 : pick();
+    cv_.notify_all();
+  }
+
+ private:
+  int pick() {
+    if (rng_() % 8 == 0) favourite_ = (int)(rng_() % 64);
+    const int n = (int)alive_.size();
+    return alive_[favourite_ >= 0 && rng_() % 4 ? favourite_ % n : (int)(rng_() % n)];
+  }
+  std::mt19937 rng_;
+  std::vector<int> alive_;
+  int turn_ = -1, favourite_ = -1;
+  std::mutex m_;
+  std::condition_variable cv_;
+};
+
+struct Slot {
+  std::multiset<int> results;
+  bool whole = true;
+};
+
+int merge(int pieces, unsigned limit, unsigned seed, int* took_over) {
+  std::vector<unsigned> word(pieces, 0u);
+  std::vector<Slot> slot(pieces);
+  std::vector<std::multiset<int>> has_all;
+  int bad = 0;
+  Turns turns(pieces, seed);
+  std::vector<std::thread> threads;
+  for (int me = 0; me < pieces; ++me)
+    threads.emplace_back([&, me] {
+      turns.wait(me);
+      std::multiset<int> mine{me};
+      bool first = false;
+      auto arrive = [&](int m) {
+        turns.pass(me);
+        first = word[m]++ == 0u;
+        for (unsigned polls = 0; !first && polls <= limit; ++polls) {
+          turns.pass(me);
+          const int at = jk::tva::others_results(word[m], false);
+          if (at >= 0) return at;
+        }
+        return -1;
+      };
+      auto leave = [&](int m) {
+        slot[me].whole = false;
+        turns.pass(me);
+        slot[me].results = mine;
+        slot[me].whole = true;
+        turns.pass(me);
+        const unsigned w = word[m];
+        word[m] |= jk::tva::left_results(first, me);
+        const int at = jk::tva::others_results(w, first);
+        if (first && at >= 0) ++*took_over;
+        return at;
+      };
+      auto add = [&](int m, int at) {
+        word[m] = 0u;
+        for (int half = 0; half < 2; ++half) {
+          turns.pass(me);
+          if (!slot[at].whole) ++bad;
+        }
+        mine.insert(slot[at].results.begin(), slot[at].results.end());
+      };
+      if (jk::tva::merge_pieces(me, pieces, arrive, leave, add)) has_all.push_back(mine);
+      turns.end(me);
+    });
+  for (auto& t : threads) t.join();
+  std::multiset<int> all;
+  for (int i = 0; i < pieces; ++i) all.insert(i);
+  if (has_all.size() != 1 || has_all[0] != all) ++bad;
+  for (unsigned w : word) bad += w != 0u;
+  if (bad) std::printf("%d pieces, %u polls, seed %u: wrong\n", pieces, limit, seed);
+  return bad;
+}
+
+int check_pieces() {
+  int bad = 0, took_over = 0;
+  for (int pieces = 1; pieces <= 9; ++pieces)
+    for (unsigned limit : {0u, 1u, 3u, 1000u})
+      for (unsigned seed = 0; seed < 150; ++seed) bad += merge(pieces, limit, seed, &took_over);
+  for (int a : {0, 1, jk::tva::kMeetingPieces - 1})
+    for (int b : {0, 1, jk::tva::kMeetingPieces - 1}) {
+      const unsigned w = 2u | jk::tva::left_results(true, a) | jk::tva::left_results(false, b);
+      bad += jk::tva::others_results(w, false) != a || jk::tva::others_results(w, true) != b;
+    }
+  std::printf("merges: %d wrong; %d times the first to come went on\n", bad, took_over);
+  return bad + (took_over == 0);
+}
 }  // namespace
 
-int main() { return check<jk::tva::wide_ahead(128)>() + check<jk::tva::wide_ahead(64)>() == 0 ? 0 : 1; }
+int main(int argc, char** argv) {
+  if (argc > 1 && std::strcmp(argv[1], "pieces") == 0) return check_pieces() == 0 ? 0 : 1;
+  return check<jk::tva::wide_ahead(128)>() + check<jk::tva::wide_ahead(64)>() == 0 ? 0 : 1;
+}
