@@ -45,7 +45,10 @@ namespace {
 
 constexpr int kCoopThreads = 256;
 constexpr int kCoopWaves = kCoopThreads / 64;
-constexpr unsigned kDefaultSpinLimit = 1u << 12;  // polls before giving up: a few milliseconds
+// Polls before giving up: 27 ms at 0.21 us each (measured behind a kernel of another stream that left 8 CUs to the walk: 4096
+// polls end after 0.85 ms, 32768 after 6.9; more where the memory is busy).  Other streams' kernels hold partners up for
+// milliseconds, and what gives up has no result.  To be measured again when a poll or the words' layout changes.
+constexpr unsigned kDefaultSpinLimit = 1u << 17;
 
 // The workgroups' contributions to an exchange, word by word: a wave that looks for one word of all of them reads 512
 // bytes in a row (64 bytes per workgroup, all its words together, were 7 - 11 % slower).  Every 64-bit word holds the exchange's 32-bit tag

@@ -6,6 +6,8 @@ only (~1e-13 relative); a seed is compared when every decision on the oracle's
 walk has a relative margin above 1e-9, which the inverse-CDF draw (steps of
 ~1/vocab) still leaves to practically every seed.  Seeds below the margin are
 counted and reported, never silently dropped."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -305,6 +307,37 @@ def test_sample_walk_gives_up_cleanly_and_the_workspace_survives():
         path, alen, bonus = jk.accept_path(*args, workspace=ws)
         torch.cuda.synchronize()
         assert check(path, alen, bonus, False) == 0
+
+
+def test_sample_walk_outlasts_another_streams_kernel():
+    """A linear layer of 256 rows on another stream has all but eight CUs for 8 ms, and a walk of 63 workgroups has room for
+    some of them only: they wait until their partners get a CU, and the result is right."""
+    cfg = CONFIGS["c3_llama3_8b"]
+    par = tree_for_config(cfg)
+    a = accept_inputs(cfg, par)
+    dev = torch.device("cuda")
+    t = lambda v: torch.from_numpy(np.ascontiguousarray(v)).to(dev)
+    args = (t(a["tokens"]), t(par.astype(np.int32)), t(a["logits"]), jk.JK_SAMPLE, 1.0, t(a["draft_probs"]), t(a["uniforms"]))
+    ws = torch.empty(jk.accept_path_workspace(cfg.batch, cfg.n_tree, cfg.vocab, jk.JK_SAMPLE), dtype=torch.uint8, device=dev)
+    jk.workspace_init(ws)
+    want = jk.accept_path(*args, workspace=ws)
+    k, n = 262144, (torch.cuda.get_device_properties(0).multi_processor_count - 8) * 256   # a workgroup for each 256 columns
+    x, w = torch.zeros(256, k, dtype=torch.bfloat16, device=dev), torch.empty(n, k, dtype=torch.bfloat16, device=dev)
+    jk.linear(x, w)                      # (the first call of a shape takes longer to launch)
+    torch.cuda.synchronize()
+    for _ in range(3):                   # (two streams may share a hardware queue: then the walk only starts later)
+        s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+        with torch.cuda.stream(s1):
+            begin = torch.cuda.Event()
+            begin.record()
+            jk.linear(x, w)
+        begin.synchronize()
+        time.sleep(0.0005)               # (its workgroups have their CUs)
+        with torch.cuda.stream(s2):
+            got = jk.accept_path(*args, workspace=ws)
+        torch.cuda.synchronize()
+        assert all(torch.equal(g, e) for g, e in zip(got, want))
+        assert jk.last_device_error(ws) == 0
 
 
 def test_sample_calls_of_different_batch_sizes_share_a_workspace():
