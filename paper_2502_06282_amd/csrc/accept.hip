@@ -585,9 +585,10 @@ size_t accept_greedy_static_bytes(int batch, int n_tree, int vocab) {
   return ws_layout(batch, n_tree, vocab, JK_GREEDY, false).total;
 }
 
-// Greedy acceptance with the partials in the library's own scratch array: the same two
-// kernels as launch_accept, no workspace argument, nothing allocated.  Nothing in the array
-// needs clearing: every partial the walk reads is written by the reduction of the same call.
+// Greedy acceptance with the partials in the library's own scratch array: no workspace argument, nothing allocated, and the
+// two kernels that launch_accept has for calls without counting words (the scratch array has none that are known to be
+// zero, as the one launch needs them).  Nothing in the array needs clearing: every partial the walk reads is written by the
+// reduction of the same call.
 hipError_t launch_accept_greedy_static(const AcceptArgs& a, hipStream_t stream) {
   void* base = nullptr;
   hipError_t e = scratch_address(&base);

@@ -27,9 +27,11 @@
 //   - the draft and logits slices of the next candidate and of its first child are asked for
 //     before the exchange in front of them.
 // Reductions across a wave are DPP moves (a shuffle through LDS takes several times as long), one
-// wave polls and reduces for the workgroup.  Measured (MI355X, us per call): one 60-node tree over a 128K vocabulary
-// 21.6 -> 18.7, eight 100-node trees over a 32K vocabulary 29.2 -> 23.0 (means of six draws), by asking for the words of an
-// exchange together (a poll used to be three or four trips to memory in a row) and by their layout.  (Tried: a tree's
+// wave polls and reduces for the workgroup.  Measured (MI355X, us per call, twelve draws of the inputs, the same ones for
+// both, repeats within 0.7 %): one 60-node tree over a 128K vocabulary 18.1 -> 15.6 in the mean (1.13 to 1.20 times as fast; a
+// draw takes 11.8 to 21.7, by its number of exchanges), eight 100-node trees over a 32K vocabulary 30.9 -> 24.4 (1.14 to
+// 1.35 times; 17.8 to 29.6), by asking for the words of an exchange together (a poll used to be three or four trips to memory
+// in a row) and by their layout.  (Tried: a tree's
 // workgroups on one XCD, exchanges through its L2: no faster than that, and one XCD's share of the memory bandwidth
 // is too little for large vocabularies: one tree over 128K 25 - 31 us.)
 //

@@ -94,8 +94,9 @@ struct PlanModel {
   double merge_16 = 1.4;        // either way, for each 16 splits beyond the first (their loads go out in turns)
   // 256 rows per workgroup (tva_wide.hip), one of them per CU: us per tile without a mask, per other tile (the first, tree
   // and ragged ones, those that four does not divide), per turn of workgroups, per call, per level of the pairwise merge
-  // and per MB that changes hands there.  (Searched together for the least loss against the best of the timed plans of
-  // 1600 shapes, on average 3.1 % without this kernel, 1.1 % with it; a tile takes 0.55 us timed alone.)
+  // and per MB that changes hands there.  (Searched together like the others; a tile takes 0.55 us timed alone.  The plan takes
+  // this kernel for 72 of the 1000 shapes above, as many as it is the fastest for; over those the best plan of the other
+  // kernels is 1.13 times as slow in the geometric mean, 0.86 to 1.38.)
   double wide_tile = 0.44, wide_tile_d64 = 0.385, wide_slow = 1.06, wide_slow_d64 = 0.70;
   double wide_hot = 0.31, wide_hot_tiles = 500.0;  // the clock falls under the matrix units' load: the tiles of a long call
                                 // take up to this much longer

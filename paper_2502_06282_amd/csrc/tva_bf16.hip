@@ -1369,7 +1369,7 @@ hipError_t launch_tva_bf16(const AttnArgs& a, const AttnPlan& pl, hipStream_t st
   const int xcd_cus = device_cu_count() / 8, per_xcd = kp.total_wgs / 8;
   kp.second_turn = ranked && per_xcd > xcd_cus && per_xcd <= 2 * xcd_cus ? xcd_cus : kp.total_wgs;
   kp.err = a.err;
-  kp.spin_limit = tuning().spin_limit >= 0 ? (unsigned)tuning().spin_limit : 4096u;  // about 2 ms of polling
+  kp.spin_limit = tuning().spin_limit >= 0 ? (unsigned)tuning().spin_limit : 4096u;  // about 2 ms of polling here, 1 ms in tva_wide.hip
   kp.merge_rows = (pl.q_rows + pl.splits - 1) / pl.splits;
   kp.merge_shift = 0;
   while ((1 << kp.merge_shift) < pl.splits) ++kp.merge_shift;
