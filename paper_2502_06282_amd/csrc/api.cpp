@@ -1,10 +1,12 @@
 // C-ABI entry points of libjakiro_verify: argument checks, launch planning,
 // kernel launches.  No device memory is allocated here and nothing synchronises.
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <initializer_list>
+#include <random>
 
 #include "jk_internal.h"
 
@@ -21,6 +23,22 @@ int device_cu_count() {
       cus = 256;
   }
   return cus;
+}
+
+// A word that no launch of this process had before (up to 2^47 launches) and that memory is not likely
+// to hold
+unsigned long long meeting_tag() {
+  static const unsigned long long seed = [] {
+    std::random_device r;
+    return ((unsigned long long)r() << 32) | r();
+  }();
+  static std::atomic<unsigned long long> count{0};
+  // (a bijection of 47 bits: odd multiplications and shifts to the right)
+  unsigned long long v = (seed + count.fetch_add(1, std::memory_order_relaxed)) & 0x7FFFFFFFFFFFull;
+  v = (v * 0x9E3779B97F4Bull) & 0x7FFFFFFFFFFFull;
+  v ^= v >> 23;
+  v = (v * 0xC2B2AE3D27D5ull) & 0x7FFFFFFFFFFFull;
+  return ((v ^ (v >> 25)) << 16) | (1ull << 63);
 }
 
 namespace {

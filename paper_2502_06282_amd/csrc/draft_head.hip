@@ -739,30 +739,45 @@ hipError_t launch_moe_experts(const MoeArgs& a, hipStream_t stream) {
 
 namespace {
 constexpr int kLinearSplitNs = 3500;  // linear_finish_kernel
+
+// Either narrow_gemm_kernel (narrow.parts > 0) or stream_gemm_kernel with ksplit parts of k
+struct LinearPlan {
+  NarrowPlan narrow;
+  int ksplit;
+};
+LinearPlan linear_plan(int m, int n, int k) {
+  LinearPlan p{narrow_plan(m, n, k), 1};
+  if (p.narrow.parts > 0 && 2 * p.narrow.strips * p.narrow.parts > device_cu_count()) return p;
+  // (few columns leave CUs without a strip; the estimate of the other way comes out 10 % low)
+  double ns = 0.0;
+  p.ksplit = capped_ksplit(m, n, k, kLinearSplitNs, &ns);
+  if (p.narrow.ns >= 1.04 * ns) p.narrow.parts = 0;
+  return p;
 }
+}  // namespace
 
 size_t linear_workspace_bytes(int m, int n, int k) {
-  return ((size_t)capped_ksplit(m, n, k, kLinearSplitNs) * m * n * 4 + 255) / 256 * 256;
+  const LinearPlan p = linear_plan(m, n, k);
+  const size_t need = p.narrow.parts > 0 ? narrow_gemm_bytes(p.narrow, m) : p.ksplit > 1 ? (size_t)p.ksplit * m * n * 4 : 0;
+  return need < 256 ? 256 : (need + 255) / 256 * 256;
 }
 
 hipError_t launch_linear(const LinearArgs& a, hipStream_t stream) {
-  double ns = 0.0;
-  const int ks = capped_ksplit(a.m, a.n, a.k, kLinearSplitNs, &ns);
+  const LinearPlan lp = linear_plan(a.m, a.n, a.k);
   StreamGemmArgs g{};
   g.x = static_cast<const uint16_t*>(a.x); g.w = static_cast<const uint16_t*>(a.w);
-  g.m = a.m; g.n = a.n; g.k = a.k; g.ksplit = ks; g.y_split = (long long)a.m * a.n; g.batch = 1;
-  const bool narrow = narrow_gemm_takes(a.m, a.n, a.k, ns);
-  if (ks == 1 || narrow) {
+  g.m = a.m; g.n = a.n; g.k = a.k; g.ksplit = lp.ksplit; g.y_split = (long long)a.m * a.n; g.batch = 1;
+  if (lp.narrow.parts > 0 || lp.ksplit == 1) {
     g.finish = true;
     g.y = a.out_f32; g.residual = static_cast<const uint16_t*>(a.residual); g.out_bf16 = static_cast<uint16_t*>(a.out_bf16);
-    return narrow ? launch_narrow_gemm(g, stream) : launch_stream_gemm(g, stream);
+    return lp.narrow.parts > 0 ? launch_narrow_gemm(g, lp.narrow, a.workspace, stream) : launch_stream_gemm(g, stream);
   }
   g.y = static_cast<float*>(a.workspace);
   hipError_t e = launch_stream_gemm(g, stream);
   if (e != hipSuccess) return e;
   LinFinishParams fp;
   fp.part = g.y; fp.residual = static_cast<const uint16_t*>(a.residual); fp.out_f32 = a.out_f32;
-  fp.out_bf16 = static_cast<uint16_t*>(a.out_bf16); fp.n_out = (long long)a.m * a.n; fp.ksplit = ks;
+  fp.out_bf16 = static_cast<uint16_t*>(a.out_bf16); fp.n_out = (long long)a.m * a.n; fp.ksplit = lp.ksplit;
   hipLaunchKernelGGL(linear_finish_kernel, dim3((unsigned)((fp.n_out + 1023) / 1024)), dim3(256), 0, stream, fp);
   return hipGetLastError();
 }

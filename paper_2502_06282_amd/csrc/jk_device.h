@@ -58,5 +58,23 @@ __device__ __forceinline__ void store_through(void* dst, unsigned int v) {
   asm volatile("global_store_dword %0, %1, off sc0 sc1" ::"v"(dst), "v"(v) : "memory");
 }
 
+constexpr int kDeviceScope = 16;  // the sc1 bit of a buffer load: past the L2 of the XCD
+
+// Of two workgroups the second to come, in every thread: its own results and, with loads of the device's scope, those that
+// the other left with store_through are there.  Nobody waits for a workgroup that has not come.  The word need not be cleared
+// before: what it holds counts only if it is the launch's tag, which memory has by chance once in 2^47 times, and the second
+// clears it, so that a graph's replays may keep their tag.
+__device__ __forceinline__ bool second_to_meet(unsigned long long* word, unsigned long long tag, int* answer_s) {
+  wait_vm<0>();     // this wave's results are in memory,
+  __syncthreads();  // and everybody's
+  if (threadIdx.x == 0) {
+    const bool second = __hip_atomic_exchange(word, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == tag;
+    if (second) __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *answer_s = second;
+  }
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane(*answer_s) != 0;
+}
+
 }  // namespace dev
 }  // namespace jk

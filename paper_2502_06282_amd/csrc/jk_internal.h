@@ -176,9 +176,15 @@ struct StreamGemmArgs {
 };
 int stream_gemm_ksplit(int m, int n, int k, int batch, bool pair, int split_ns, double* ns = nullptr);
 hipError_t launch_stream_gemm(const StreamGemmArgs& p, hipStream_t stream);       // m <= 256
-// plain products with `finish` of few rows and columns, in one launch; others_ns: what launch_stream_gemm is estimated to take
-bool narrow_gemm_takes(int m, int n, int k, double others_ns);
-hipError_t launch_narrow_gemm(const StreamGemmArgs& p, hipStream_t stream);
+// plain products with `finish` of few rows and columns, in one launch
+struct NarrowPlan {
+  int strip, strips, parts;  // weight rows of a workgroup, strips, parts of k (1 or 2; 0: not possible)
+  double ns;
+};
+NarrowPlan narrow_plan(int m, int n, int k);
+size_t narrow_gemm_bytes(const NarrowPlan& plan, int m);
+hipError_t launch_narrow_gemm(const StreamGemmArgs& p, const NarrowPlan& plan, void* workspace, hipStream_t stream);
+unsigned long long meeting_tag();  // another one for every launch (see dev::second_to_meet)
 hipError_t launch_stream_gemm_heads(const StreamGemmArgs& p, hipStream_t stream);  // m <= 32
 hipError_t launch_stream_gemm_pair(const StreamGemmArgs& p, hipStream_t stream);  // m <= 128
 hipError_t launch_stream_gemm_down(const StreamGemmArgs& p, hipStream_t stream);  // m <= 128

@@ -15,6 +15,7 @@
 #include <cmath>
 #include <type_traits>
 
+#include "jk_device.h"
 #include "jk_internal.h"
 
 namespace jk {
@@ -501,132 +502,158 @@ struct NarrowArgs {
   const uint16_t *x, *w, *residual;
   float* y;
   uint16_t* out_bf16;
-  int m, n, k, strip;
+  int m, n, k, strip, strips;
+  int parts;               // of the k range
+  float* part;             // parts > 1: their sums, one workgroup's behind the other's
+  unsigned long long* words;  // and a word per strip, kWordStep apart
+  unsigned long long tag;
 };
-constexpr int kNarrowWaves = 8;
-constexpr int kNarrowLd = 144;  // bytes per row of X in LDS: 64 k and 16 bytes of padding
-constexpr int narrow_lds(int mt, int nf) {
-  const int x = kNarrowWaves * mt * 16 * kNarrowLd, sums = kNarrowWaves * nf * mt * 1024;
-  return x > sums ? x : sums;
-}
-
-// Y = X . W^T (+ residual) for up to 64 rows and at most 64 columns per CU: a workgroup per CU has its strip of weight rows
-// and all of k, its eight waves every eighth 64 of k each (128-byte lines of 16 rows), and adds the waves' sums up in LDS.
-// Against parts of k per workgroup it saves writing the partial results, the launch that adds them up, and the barriers of
-// X's way through LDS; in exchange every CU draws all of X from L2.  That is what bounds it beyond some twenty rows: with
-// X straight in MFMA layout, 16 rows by 16 bytes an instruction, a CU drew 31 bytes per ns (its address unit takes a lane a
-// cycle unless neighbours are neighbours in memory too); eight rows by 128 bytes, turned round in the wave's own piece of
-// LDS, come at 60.  The weights, read once, stay in MFMA layout.  (Loads return in order: X asked for later than the
-// weights in flight would wait for them, so both are as far ahead.)
-// Measured (us, parts and a second launch / this): 4096 x 4096, 8 rows 12.1 / 8.2, 24 12.7 / 10.3, 40 14.5 / 12.5; 6144 x
-// 4096 15.3 / 11.3, 16.2 / 13.9, 17.4 / 15.7; 4096 x 8192 19.1 / 14.3, 20.1 / 17.3, 21.5 / 21.5; 16384 x 2048 19.0 / 13.7,
-// 22.7 / 15.2, 24.4 / 16.9; 2048 x 2048 8.2 / 4.0, 8.0 / 4.7, 9.3 / 5.9.
+// Y = X . W^T (+ residual) for up to 64 rows and at most 64 columns per CU: a workgroup per CU has its strip of weight rows and
+// all of k, its waves every eighth (fourth) 64 of k each (128-byte lines of W's and X's rows), and adds the waves' sums up
+// in LDS.  Against parts of k per workgroup it saves writing the partial results and the launch that adds them up; in exchange
+// every CU draws all of X from its L2.  What bounds it is HBM's share of the weights and, beyond some twenty rows, what a CU
+// draws: 51 bytes per ns straight into LDS (global_load_lds_dwordx4), 47 through registers, 38 where neighbouring lanes do not
+// ask for neighbouring addresses, as in the matrix operands' layout, whoever else draws.  So both operands come by LDS, each
+// wave's through a ring of its own, up to six units ahead: no barriers, no registers.  With many rows and a long k two
+// workgroups share a strip of twice the rows: half of X for each, and the second of them to finish adds up both (1.3 us:
+// four parts save no more than their meeting costs).
+// Measured (us, weights cold, before / now; before: weights in the operands' layout, X through registers, or strips of 128
+// rows in parts of k and a second launch): 4096 x 4096, 8 rows 8.0 / 7.9, 16 8.9 / 8.3, 40 12.3 / 10.9, 64 15.0 / 12.1; 6144 x
+// 4096, 8 11.1 / 10.7, 40 15.3 / 13.5, 64 18.2 / 15.9; 4096 x 8192, 8 14.4 / 14.1, 40 21.3 / 17.4, 64 22.9 / 20.0; 12288 x
+// 4096, 45 26.9 / 21.3; 8192 x 16384, 20 60.0 / 48.6.  Reading the weights alone takes 7.0, 9.5, 12.3, ..., 43.
 // RG: groups of eight rows of X; NF: groups of 16 weight rows
-template <int RG, int NF>
-__global__ __launch_bounds__(64 * kNarrowWaves, 2) void narrow_gemm_kernel(NarrowArgs p) {
-  constexpr int MT = (RG + 1) / 2, TILES = NF * MT;
-  constexpr int AHEAD = 2;  // units whose operands are in flight (four: no difference)
+
+// waves of a workgroup: eight, or four where LDS has no room for two units of each
+constexpr int narrow_waves(int groups, int frags) { return 2 * 8 * (2 * frags + groups) <= 158 ? 8 : 4; }
+constexpr int kWordStep = 32;  // (256 bytes: an atomic takes 11 ns of the memory channel that has its word)
+
+// A wave's units of W and X, UK of k each, on their way through its own part of LDS: rows of 128 bytes, their 16-byte chunks
+// in an order that spreads the matrix operands' reads over the banks
+template <int RG, int NF, int WAVES>
+struct NarrowCfg {
+  static constexpr int UK = 64;
+  static constexpr int MT = (RG + 1) / 2, TILES = NF * MT;
+  static constexpr int ROW = 2 * UK, CHUNKS = ROW / 16, RPI = 8;  // bytes and chunks of a row, rows of a transfer
+  static constexpr int WI = 2 * NF, XI = RG, PER = WI + XI;  // transfers of a unit
+  static constexpr int FIT = 158 / (WAVES * PER), DEPTH = FIT < 6 ? FIT : 6;  // units in flight
+  static constexpr int RING = DEPTH * PER * 1024;  // bytes of a wave
+  static constexpr int SUMS = WAVES * TILES * 1024;
+  static constexpr int SMEM = WAVES * RING + 1024 > SUMS ? WAVES * RING + 1024 : SUMS;  // (the rows that the last of 16 lack)
+  static_assert(DEPTH >= 2, "LDS plan");
+  static __device__ __forceinline__ int swizzle(int row) { return row & 7; }
+};
+
+template <int RG, int NF, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, WAVES / 4) void narrow_gemm_kernel(NarrowArgs p) {
+  using C = NarrowCfg<RG, NF, WAVES>;
+  constexpr int MT = C::MT, TILES = C::TILES, UK = C::UK, STEPS = UK / 32;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   floatx4* sums = reinterpret_cast<floatx4*>(smem);  // [wave][tile][lane], behind the loop
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, g = lane >> 4;
   const int all = gridDim.x, blk = blockIdx.x;
-  const int strip = all % 8 == 0 ? (blk & 7) * (all >> 3) + (blk >> 3) : blk;  // (neighbours on one XCD share lines of Y)
+  const int id = all % 8 == 0 ? (blk & 7) * (all >> 3) + (blk >> 3) : blk;  // (neighbours on one XCD share lines of Y)
+  const int strip = id / p.parts, z = id - strip * p.parts;
   const int n_base = strip * p.strip, n_end = min(n_base + p.strip, p.n);
+  const int units = p.k / UK, u0 = (int)((long long)z * units / p.parts), u1 = (int)((long long)(z + 1) * units / p.parts);
   // (byte offsets from one scalar address each; rows past the end repeat the last one, and are not stored)
-  const char *w0 = reinterpret_cast<const char*>(p.w + (long long)n_base * p.k), *x0 = reinterpret_cast<const char*>(p.x);
-  unsigned wr[NF], xr[RG];
+  const uint16_t *w0 = dev::uniform_ptr(p.w + (long long)n_base * p.k), *x0 = dev::uniform_ptr(p.x);
+  const int lrow = lane / C::CHUNKS, lcol = 16 * (lane % C::CHUNKS ^ C::swizzle(lrow));
+  unsigned wr[C::WI], xr[C::XI];
 #pragma unroll
-  for (int f = 0; f < NF; ++f) wr[f] = (unsigned)min(16 * f + r, n_end - 1 - n_base) * (unsigned)p.k * 2u + 16 * g;
+  for (int i = 0; i < C::WI; ++i) wr[i] = (unsigned)min(C::RPI * i + lrow, n_end - 1 - n_base) * (unsigned)p.k * 2u + lcol;
 #pragma unroll
-  for (int i = 0; i < RG; ++i) xr[i] = (unsigned)min(8 * i + (lane >> 3), p.m - 1) * (unsigned)p.k * 2u + 16 * (lane & 7);
-  unsigned char* own = smem + wave * (MT * 16 * kNarrowLd);  // this wave's part of X, a unit at a time
-  unsigned char* put = own + (lane >> 3) * kNarrowLd + 16 * (lane & 7);
-  const unsigned char* get = own + r * kNarrowLd + 16 * g;
-  const int count = (p.k / 64 - wave + kNarrowWaves - 1) / kNarrowWaves;  // this wave's units
+  for (int i = 0; i < C::XI; ++i) xr[i] = (unsigned)min(C::RPI * i + lrow, p.m - 1) * (unsigned)p.k * 2u + lcol;
+  unsigned char* ring = smem + wave * C::RING;
+  const unsigned ring_at = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)ring;
+  const int count = (u1 - u0 - wave + WAVES - 1) / WAVES;  // this wave's units
   // (workgroups start at different units: see Weights::chunk)
   const int rot = count > 0 ? (int)((5u * blk + (blk >> 3)) % (unsigned)count) : 0;
-  bf16x8 a[AHEAD][NF][2];
-  u32x4 b[AHEAD][RG];
-  auto load = [&](int j, int slot) {
-    const int u = j + rot, at = (wave + kNarrowWaves * (u < count ? u : u - count)) * 128;
+  auto ask = [&](int j, int slot) {
+    const int u = j + rot, at = (u0 + wave + WAVES * (u < count ? u : u - count)) * UK;
+    const unsigned to = ring_at + slot * (C::PER * 1024);
+#pragma unroll
+    for (int i = 0; i < C::WI; ++i) dev::dma16(w0 + at, wr[i], to + 1024 * i);
+#pragma unroll
+    for (int i = 0; i < C::XI; ++i) dev::dma16(x0 + at, xr[i], to + 1024 * (C::WI + i));
+  };
+  // (four waves: two sums each, so that none is of more products than with eight)
+  constexpr int SETS = 8 / WAVES;
+  static_assert(SETS == 1 || SETS == STEPS, "a set per step");
+  floatx4 acc[SETS][NF][MT];
+#pragma unroll
+  for (int q = 0; q < SETS; ++q)
 #pragma unroll
     for (int f = 0; f < NF; ++f)
 #pragma unroll
-      for (int s = 0; s < 2; ++s) a[slot][f][s] = *reinterpret_cast<const bf16x8*>(w0 + at + wr[f] + 64 * s);
+      for (int t = 0; t < MT; ++t) acc[q][f][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+  int at[STEPS];  // of a lane's chunk of a row
 #pragma unroll
-    for (int i = 0; i < RG; ++i) b[slot][i] = *reinterpret_cast<const u32x4*>(x0 + at + xr[i]);
+  for (int s = 0; s < STEPS; ++s) at[s] = r * C::ROW + 16 * ((4 * s + g) ^ C::swizzle(r));
+  bf16x8 a[NF][STEPS], b[MT][STEPS];
+  auto take = [&](int slot) {  // (and the slot may be filled again)
+    const unsigned char* from = ring + slot * (C::PER * 1024);
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+#pragma unroll
+      for (int f = 0; f < NF; ++f) a[f][s] = *reinterpret_cast<const bf16x8*>(from + f * 16 * C::ROW + at[s]);
+#pragma unroll
+      for (int t = 0; t < MT; ++t) b[t][s] = *reinterpret_cast<const bf16x8*>(from + C::WI * 1024 + t * 16 * C::ROW + at[s]);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   };
-  floatx4 acc[NF][MT];
+  auto multiply = [&] {
 #pragma unroll
-  for (int f = 0; f < NF; ++f)
-#pragma unroll
-    for (int t = 0; t < MT; ++t) acc[f][t] = floatx4{0.f, 0.f, 0.f, 0.f};
-  auto use = [&](int slot) {  // (LDS operations of a wave complete in order)
-#pragma unroll
-    for (int i = 0; i < RG; ++i) *reinterpret_cast<u32x4*>(put + i * 8 * kNarrowLd) = b[slot][i];
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    bf16x8 x[MT][2];  // (all of them asked for before the first is used)
-#pragma unroll
-    for (int t = 0; t < MT; ++t)
-#pragma unroll
-      for (int s = 0; s < 2; ++s) x[t][s] = *reinterpret_cast<const bf16x8*>(get + t * 16 * kNarrowLd + 64 * s);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
+    for (int s = 0; s < STEPS; ++s)
 #pragma unroll
       for (int t = 0; t < MT; ++t)
 #pragma unroll
-        for (int f = 0; f < NF; ++f) acc[f][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[slot][f][s], x[t][s], acc[f][t], 0, 0, 0);
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_sched_barrier(0);
+        for (int f = 0; f < NF; ++f) {
+          floatx4& sum = acc[s % SETS][f][t];
+          sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[f][s], b[t][s], sum, 0, 0, 0);
+        }
   };
-  if (count < AHEAD) {  // (k below 1024)
-    for (int j = 0; j < count; ++j) {
-      load(j, 0);
-      use(0);
-    }
-  } else {
-    // (no load under a condition: behind one the compiler waits as if it had not been issued, i.e. for all others)
 #pragma unroll
-    for (int j = 0; j < AHEAD; ++j) load(j, j);
-    int j = 0;
-    for (; j + 2 * AHEAD <= count; j += AHEAD) {
-#pragma unroll
-      for (int u = 0; u < AHEAD; ++u) {
-        use(u);
-        load(j + u + AHEAD, u);
-      }
-    }
-    if (count - j == AHEAD) {
-      use(0);
-      use(1);
-    } else {
-      use(0);
-      load(j + 2, 0);
-      use(1);
-      use(0);
-    }
+  for (int j = 0; j < C::DEPTH; ++j)
+    if (j < count) ask(j, j);
+  int j = 0, slot = 0;
+  for (; j + C::DEPTH < count; ++j) {
+    dev::wait_vm<(C::DEPTH - 1) * C::PER>();
+    take(slot);
+    ask(j + C::DEPTH, slot);
+    multiply();
+    slot = slot + 1 == C::DEPTH ? 0 : slot + 1;
   }
-  __syncthreads();  // (the sums take the place of X)
+  // (count - j units are on their way, at most DEPTH)
+  auto rest = [&](auto self, auto leftc) -> void {
+    constexpr int LEFT = decltype(leftc)::value;
+    if constexpr (LEFT > 0) {
+      if (count - j >= LEFT) {
+        dev::wait_vm<(LEFT - 1) * C::PER>();
+        take(slot);
+        multiply();
+        slot = slot + 1 == C::DEPTH ? 0 : slot + 1;
+        ++j;
+      }
+      self(self, std::integral_constant<int, LEFT - 1>());
+    }
+  };
+  rest(rest, std::integral_constant<int, C::DEPTH>());
+  __syncthreads();  // (the sums take the place of the ring)
 #pragma unroll
   for (int f = 0; f < NF; ++f)
 #pragma unroll
-    for (int t = 0; t < MT; ++t) sums[(wave * TILES + f * MT + t) * 64 + lane] = acc[f][t];
+    for (int t = 0; t < MT; ++t) {
+      floatx4 v = acc[0][f][t];
+      if constexpr (SETS == 2) v += acc[1][f][t];
+      sums[(wave * TILES + f * MT + t) * 64 + lane] = v;
+    }
   __syncthreads();
   const bool vec = (p.n & 3) == 0 && (reinterpret_cast<size_t>(p.y) & 15) == 0 && (reinterpret_cast<size_t>(p.residual) & 7) == 0 &&
                    (reinterpret_cast<size_t>(p.out_bf16) & 7) == 0;
-  for (int i = tid; i < TILES * 64; i += 64 * kNarrowWaves) {
-    floatx4 part[kNarrowWaves];
-#pragma unroll
-    for (int w = 0; w < kNarrowWaves; ++w) part[w] = sums[w * TILES * 64 + i];
-#pragma unroll
-    for (int d = 1; d < kNarrowWaves; d *= 2)  // (two and two: fewer roundings on the way of each)
-#pragma unroll
-      for (int w = 0; w < kNarrowWaves; w += 2 * d) part[w] += part[w + d];
-    floatx4 v = part[0];
+  auto finish = [&](int i, floatx4 v) {
     // (a lane of a tile has row lane % 16 of X and four consecutive columns)
     const int tile = i >> 6, row = (tile % MT) * 16 + (i & 15), col = n_base + (tile / MT) * 16 + ((i & 63) >> 4) * 4;
-    if (row >= p.m || col >= n_end) continue;
+    if (row >= p.m || col >= n_end) return;
     const long long at = (long long)row * p.n + col;
     if (vec && col + 4 <= n_end) {
       if (p.residual) {
@@ -650,49 +677,81 @@ __global__ __launch_bounds__(64 * kNarrowWaves, 2) void narrow_gemm_kernel(Narro
         if (p.out_bf16) p.out_bf16[at + e] = (uint16_t)bf16_bits_rne(s);
       }
     }
+  };
+  constexpr int QUADS = TILES * 64;  // of a workgroup's results
+  float* own_part = p.part + (size_t)id * (QUADS * 4);
+  for (int i = tid; i < QUADS; i += 64 * WAVES) {
+    floatx4 part[WAVES];
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) part[w] = sums[w * QUADS + i];
+#pragma unroll
+    for (int d = 1; d < WAVES; d *= 2)  // (two and two: fewer roundings on the way of each)
+#pragma unroll
+      for (int w = 0; w < WAVES; w += 2 * d) part[w] += part[w + d];
+    if (p.parts == 1) finish(i, part[0]);
+    else dev::store_through(own_part + 4 * i, __builtin_bit_cast(dev::store_u32x4, part[0]));
+  }
+  if (p.parts == 1) return;
+  if (!dev::second_to_meet(p.words + (size_t)strip * kWordStep, p.tag, reinterpret_cast<int*>(smem))) return;
+  const auto both = __builtin_amdgcn_make_buffer_rsrc(p.part + (size_t)strip * (2 * QUADS * 4), 0, 2 * QUADS * 16, 0x00020000);
+  for (int i = tid; i < QUADS; i += 64 * WAVES) {  // (the same sum whoever comes second)
+    const u32x4 low = __builtin_amdgcn_raw_buffer_load_b128(both, i * 16, 0, dev::kDeviceScope);
+    const u32x4 high = __builtin_amdgcn_raw_buffer_load_b128(both, i * 16, QUADS * 16, dev::kDeviceScope);
+    finish(i, __builtin_bit_cast(floatx4, low) + __builtin_bit_cast(floatx4, high));
   }
 }
 
 template <int RG, int NF>
 hipError_t launch_narrow(const NarrowArgs& p, hipStream_t stream) {
   static LdsLimitRaised raised;
-  constexpr int smem = narrow_lds((RG + 1) / 2, NF);
-  if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(narrow_gemm_kernel<RG, NF>), smem, raised); e != hipSuccess) return e;
-  hipLaunchKernelGGL((narrow_gemm_kernel<RG, NF>), dim3((unsigned)((p.n + p.strip - 1) / p.strip)), dim3(64 * kNarrowWaves), smem, stream, p);
+  constexpr int WAVES = narrow_waves(RG, NF);
+  constexpr int smem = NarrowCfg<RG, NF, WAVES>::SMEM;
+  if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(narrow_gemm_kernel<RG, NF, WAVES>), smem, raised); e != hipSuccess) return e;
+  hipLaunchKernelGGL((narrow_gemm_kernel<RG, NF, WAVES>), dim3((unsigned)(p.strips * p.parts)), dim3(64 * WAVES), smem, stream, p);
   return hipGetLastError();
 }
 template <int RG>
 hipError_t launch_narrow_rows(const NarrowArgs& p, hipStream_t stream) {
-  const int groups = (p.strip + 15) / 16;
-  if (groups == 1) return launch_narrow<RG, 1>(p, stream);
-  if (groups == 2) return launch_narrow<RG, 2>(p, stream);
-  if constexpr (RG <= 6) {
-    if (groups == 3) return launch_narrow<RG, 3>(p, stream);
-    if (groups == 4) return launch_narrow<RG, 4>(p, stream);
+  switch ((p.strip + 15) / 16) {
+    case 1: return launch_narrow<RG, 1>(p, stream);
+    case 2: return launch_narrow<RG, 2>(p, stream);
+    case 3: return launch_narrow<RG, 3>(p, stream);
+    case 4: return launch_narrow<RG, 4>(p, stream);
+    default: return hipErrorInvalidValue;
   }
-  return hipErrorInvalidValue;
 }
 }  // namespace
 
-// By its estimated time against that of the other way (`others_ns`, which comes out 10 % low on average): the HBM share of
-// the weights, or what a CU draws of its weights and of X at 31 and 60 bytes per ns.  Over 144 timed products (3 - 64 rows,
-// 768 - 16384 columns, k 768 - 14336) the choice is 0.7 % behind the faster one, 1.6 % at most where it takes this one.
-// (More than 48 rows with strips of more than 32 leave it without registers.)
-namespace {
-int narrow_strip(int n) { return ((n + device_cu_count() - 1) / device_cu_count() + 3) / 4 * 4; }
-}  // namespace
-bool narrow_gemm_takes(int m, int n, int k, double others_ns) {
-  const int strip = n <= 64 * device_cu_count() ? narrow_strip(n) : 65, groups = (m + 7) / 8;
-  if (m > 64 || strip > 64 || (m > 48 && strip > 32)) return false;
-  const double hbm = 2.0 * n * k / 6000.0, cu = 2.0 * k * (strip / 31.0 + 8.0 * groups / 60.0);
-  const double h2 = hbm * hbm, c2 = cu * cu, ns = 2200.0 + std::sqrt(std::sqrt(h2 * h2 + c2 * c2));
-  return ns * (groups > 4 ? 1.0 + 0.05 * (groups - 4) : 1.0) < 1.04 * others_ns;
+// Strips of at most 64 weight rows, and k in one or two parts, by the estimated time: HBM's share of the weights beside what
+// a CU draws of its weights and of X, a start and an end, the meeting of two parts, and four waves instead of eight.  Over 45
+// shapes (1 - 64 rows, 832 - 16384 columns, k 768 - 16384) the estimate is off by 4 % and the choice 0.4 % behind the better.
+NarrowPlan narrow_plan(int m, int n, int k) {
+  const int cus = device_cu_count(), groups = (m + 7) / 8;
+  NarrowPlan best{0, 0, 0, 0.0};
+  if (m > 64) return best;
+  for (int parts = 1; parts <= 2; ++parts) {
+    const int most = cus / parts;  // strips
+    if (most < 1 || n > 64 * (long long)most) break;
+    const int strip = ((n + most - 1) / most + 3) / 4 * 4, frags = (strip + 15) / 16;
+    const double cu = 2.0 * k / parts * (strip + 8.0 * groups) / 65.0, hbm = 2.0 * n * k / 6400.0;
+    const double ns = 2700.0 + std::cbrt(cu * cu * cu + hbm * hbm * hbm) + (parts > 1 ? 1250.0 : 0.0) + (narrow_waves(groups, frags) == 4 ? 1350.0 : 0.0);
+    if (best.parts == 0 || ns < best.ns) best = NarrowPlan{strip, (n + strip - 1) / strip, parts, ns};
+  }
+  return best;
 }
-hipError_t launch_narrow_gemm(const StreamGemmArgs& g, hipStream_t stream) {
+size_t narrow_gemm_bytes(const NarrowPlan& plan, int m) {
+  if (plan.parts <= 1) return 0;
+  const size_t tiles = (size_t)((plan.strip + 15) / 16) * ((m + 15) / 16);
+  return (size_t)plan.strips * (kWordStep * 8 + plan.parts * tiles * 1024);
+}
+hipError_t launch_narrow_gemm(const StreamGemmArgs& g, const NarrowPlan& plan, void* workspace, hipStream_t stream) {
   NarrowArgs p;
   p.x = g.x; p.w = g.w; p.residual = g.residual; p.y = g.y; p.out_bf16 = g.out_bf16;
   p.m = g.m; p.n = g.n; p.k = g.k;
-  p.strip = narrow_strip(g.n);
+  p.strip = plan.strip; p.strips = plan.strips; p.parts = plan.parts;
+  p.words = static_cast<unsigned long long*>(workspace);
+  p.part = reinterpret_cast<float*>(static_cast<char*>(workspace) + (size_t)plan.strips * (kWordStep * 8));
+  p.tag = meeting_tag();
   switch ((g.m + 7) / 8) {
     case 1: return launch_narrow_rows<1>(p, stream);
     case 2: return launch_narrow_rows<2>(p, stream);

@@ -129,3 +129,52 @@ def test_few_columns_are_bit_exact(m, n, k):
     got = jk.linear(_bf(x), _bf(w), _bf(r), out_dtype=torch.float32).cpu().numpy()
     np.testing.assert_array_equal(got, want)
     np.testing.assert_array_equal(jk.linear(_bf(x), _bf(w), _bf(r)).float().cpu().numpy(), round_to_bf16(want))
+
+
+def _exact_case(m, n, k, seed):
+    rng = np.random.default_rng(seed)
+    x = rng.integers(-2, 3, size=(m, k)).astype(np.float32)
+    w = rng.integers(-1, 2, size=(n, k)).astype(np.float32) * np.float32(0.125)
+    r = rng.integers(-4, 5, size=(m, n)).astype(np.float32)
+    return x, w, r, x @ w.T + r                                           # (exact in fp32: multiples of 1/8 below 2^14)
+
+
+@pytest.mark.parametrize("m,n,k", [(64, 4096, 4096), (41, 4096, 8192), (24, 4100, 8320), (57, 8191, 8192), (64, 2049, 8064), (33, 5120, 10240)])
+def test_two_workgroups_per_strip_are_bit_exact(m, n, k):
+    """Products whose k is cut in two: the second workgroup of a strip to finish adds up both.  The workspace may hold
+    anything (its words are not cleared for the call), is used by several calls in turn, and nothing is written behind it."""
+    x, w, r, want = _exact_case(m, n, k, m + n)
+    xd, wd, rd = _bf(x), _bf(w), _bf(r)
+    need = jk.lib().jk_linear_workspace(m, n, k)
+    out = torch.empty((m, n), dtype=torch.float32, device="cuda")
+    for fill in (0, 0xFF, 0x80):
+        ws = torch.full((need + 256,), fill, dtype=torch.uint8, device="cuda")
+        for _ in range(3):
+            out.fill_(float("nan"))
+            assert jk.lib().jk_linear(m, n, k, xd.data_ptr(), wd.data_ptr(), rd.data_ptr(), None, out.data_ptr(), ws.data_ptr(), need,
+                                      torch.cuda.current_stream().cuda_stream) == 0
+            np.testing.assert_array_equal(out.cpu().numpy(), want)
+        assert (ws[need:] == fill).all()
+
+
+def test_linear_layers_replay_in_a_graph():
+    """A graph keeps the words of its launches' meetings: every replay gives the eager result, with eager calls on the same
+    buffers between them."""
+    x, w, r, want = _exact_case(48, 4096, 8192, 5)
+    x2, w2, r2, want2 = _exact_case(64, 4096, 4096, 6)
+    a = [_bf(v) for v in (x, w, r)], [_bf(v) for v in (x2, w2, r2)]
+    for t in a:
+        jk.linear(*t)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        got = [jk.linear(*t, out_dtype=torch.float32) for t in a for _ in range(2)]
+    for _ in range(6):
+        for g in got:
+            g.fill_(float("nan"))
+        graph.replay()
+        eager = jk.linear(*a[0], out_dtype=torch.float32)
+        torch.cuda.synchronize()
+        for g, e in zip(got, (want, want, want2, want2)):
+            np.testing.assert_array_equal(g.cpu().numpy(), e)
+        np.testing.assert_array_equal(eager.cpu().numpy(), want)
