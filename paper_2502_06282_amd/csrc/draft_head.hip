@@ -13,6 +13,8 @@
 //                          surrounds the experts' three projections (Eq. 3).
 // The products with weight matrices run in stream_gemm.hip.
 
+#include <cmath>
+
 #include "jk_internal.h"
 #include "jk_wave.h"
 
@@ -547,6 +549,7 @@ __global__ __launch_bounds__(256) void select_kernel(SelectParams p) {
 }
 
 struct MoePlan {
+  int ring_rows, used;  // ring_rows > 0: the products in ring_gemm.hip, `used` experts with at most so many rows each, as is likely
   int split1, split2;
   size_t g_off, up_off, h_off, y_off, total;
 };
@@ -558,8 +561,11 @@ MoePlan moe_plan(int rows, int d, int f, int n) {
   for (int r = 0; r < rows; ++r) missed *= 1.0 - 2.0 / n;
   const int used = n * (1.0 - missed) < 2.0 ? 2 : (int)(n * (1.0 - missed) + 0.5);
   const int each = (2 * rows + used - 1) / used;
-  m.split1 = stream_gemm_ksplit(each, f, d, used, true, 7000);  // gate and up in one launch
-  m.split2 = stream_gemm_ksplit(each, d, f, used, false, 0);
+  const double mean = 2.0 * rows / n, likely = std::ceil(mean + 3.0 * std::sqrt(mean * (1.0 - 2.0 / n)));
+  m.used = used;
+  m.ring_rows = ring_gemm_takes_experts((int)likely, used, d, f) ? (int)likely : 0;
+  m.split1 = m.ring_rows ? 1 : stream_gemm_ksplit(each, f, d, used, true, 7000);  // gate and up in one launch
+  m.split2 = m.ring_rows ? 1 : stream_gemm_ksplit(each, d, f, used, false, 0);
   const size_t pre = m.split1 > 1 ? up((size_t)m.split1 * n * rows * f * 4) : 0;
   m.g_off = 0;
   m.up_off = pre;
@@ -615,6 +621,7 @@ int capped_ksplit(int m, int n, int k, int split_ns, double* ns = nullptr) {
 }
 
 struct RowPlan {
+  bool ring;
   int per_thread, parts, part_len, ksplit;
   size_t x_bytes, ms_off, key_off, part_off, total;
 };
@@ -635,7 +642,8 @@ RowPlan row_plan(int rows, int d_model, int vocab) {
   r.ms_off = r.x_bytes;
   r.key_off = r.ms_off + up(m * r.parts * 2 * 4);
   r.part_off = r.key_off + up(m * r.parts * kMaxTopK * 8);
-  r.ksplit = capped_ksplit((int)m, vocab, d_model, 0);
+  r.ring = ring_gemm_takes_heads((int)m, vocab);
+  r.ksplit = r.ring ? 1 : capped_ksplit((int)m, vocab, d_model, 0);
   r.total = r.part_off + (r.ksplit > 1 ? up((size_t)r.ksplit * m * vocab * 4) : 0);
   return r;
 }
@@ -653,7 +661,7 @@ hipError_t launch_draft_heads(const DraftHeadsArgs& a, hipStream_t stream) {
   mp.s_top = a.s_top;
   mp.x = reinterpret_cast<unsigned short*>(ws);
   mp.rows = a.rows; mp.d = a.d_model; mp.mode = a.mode; mp.alpha = a.alpha; mp.beta = a.beta;
-  const bool mixes = m <= 32;  // the product makes its rows itself (see launch_stream_gemm_heads)
+  const bool mixes = rp.ring || m <= 32;  // the product makes its rows itself (see launch_stream_gemm_heads)
   hipError_t e = hipSuccess;
   if (!mixes) {
     hipLaunchKernelGGL(head_inputs_kernel, dim3((unsigned)(((long long)a.rows * (a.d_model / 8) + 63) / 64)), dim3(64), 0, stream, mp);
@@ -667,7 +675,7 @@ hipError_t launch_draft_heads(const DraftHeadsArgs& a, hipStream_t stream) {
   g.m = m; g.n = a.vocab; g.k = a.d_model;
   g.ksplit = rp.ksplit; g.y_split = (long long)m * a.vocab; g.batch = 1;
   g.s_top = a.s_top; g.heads_mode = a.mode; g.alpha = a.alpha; g.beta = a.beta;
-  e = mixes ? launch_stream_gemm_heads(g, stream) : launch_stream_gemm(g, stream);
+  e = rp.ring ? launch_ring_gemm_heads(g, stream) : mixes ? launch_stream_gemm_heads(g, stream) : launch_stream_gemm(g, stream);
   if (e != hipSuccess) return e;
 
   SoftParams sp;
@@ -712,7 +720,7 @@ hipError_t launch_moe_experts(const MoeArgs& a, hipStream_t stream) {
   } else {
     g.act = h; g.act_batch = (long long)a.rows * a.d_ff;
   }
-  if ((e = launch_stream_gemm_pair(g, stream)) != hipSuccess) return e;  // gate and up projections of all experts
+  if ((e = mp.ring_rows ? launch_ring_gemm_pair(g, mp.ring_rows, mp.used, stream) : launch_stream_gemm_pair(g, stream)) != hipSuccess) return e;  // gate and up projections of all experts
   if (mp.split1 > 1) {
     ActParams ap;
     ap.g = g.y; ap.up = g.y2; ap.h = h; ap.sel = a.expert_idx;
@@ -726,7 +734,7 @@ hipError_t launch_moe_experts(const MoeArgs& a, hipStream_t stream) {
   o.y_batch = (long long)a.rows * a.d_model; o.sel = a.expert_idx;
   o.ksplit = mp.split2; o.y_split = (long long)a.n_experts * a.rows * a.d_model;
   o.w = static_cast<const uint16_t*>(a.w_down); o.y = reinterpret_cast<float*>(ws + mp.y_off);
-  if ((e = launch_stream_gemm_down(o, stream)) != hipSuccess) return e;
+  if ((e = mp.ring_rows ? launch_ring_gemm_down(o, mp.ring_rows, mp.used, stream) : launch_stream_gemm_down(o, stream)) != hipSuccess) return e;
 
   SelectParams sp;
   sp.y = o.y; sp.u = rp.u; sp.s_top = a.s_top; sp.idx = a.expert_idx;

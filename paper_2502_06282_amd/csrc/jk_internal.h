@@ -188,6 +188,13 @@ unsigned long long meeting_tag();  // another one for every launch (see dev::sec
 hipError_t launch_stream_gemm_heads(const StreamGemmArgs& p, hipStream_t stream);  // m <= 32
 hipError_t launch_stream_gemm_pair(const StreamGemmArgs& p, hipStream_t stream);  // m <= 128
 hipError_t launch_stream_gemm_down(const StreamGemmArgs& p, hipStream_t stream);  // m <= 128
+// the same products with equal shares of the weight rows.  rows: how many an expert is likely to have at most (others take
+// several passes over its weights), items: how many experts are likely to be chosen
+bool ring_gemm_takes_heads(int m, int n);
+bool ring_gemm_takes_experts(int rows, int items, int d_model, int d_ff);
+hipError_t launch_ring_gemm_heads(const StreamGemmArgs& p, hipStream_t stream);
+hipError_t launch_ring_gemm_pair(const StreamGemmArgs& p, int rows, int items, hipStream_t stream);
+hipError_t launch_ring_gemm_down(const StreamGemmArgs& p, int rows, int items, hipStream_t stream);
 
 // draft head step (two heads over the shared output embedding)
 struct DraftHeadsArgs {

@@ -1,0 +1,380 @@
+// Products of few rows with large weight matrices (gfx950), Y[M, N] = X[M, K] . W[N, K]^T, bf16 operands, fp32
+// accumulation: the output heads and the experts' projections of up to 32 rows (an expert's rows in blocks of so many).
+//
+// What bounds it: the weight stream.  stream_gemm.hip gives every workgroup a strip of 128 weight rows, which leaves CUs idle in
+// the last turn of workgroups and wherever there are fewer strips than CUs.  Here a workgroup per CU has an equal share of all
+// weight rows, counted in groups of 16, whichever expert they belong to, and goes through it in batches of a few groups and all
+// of k.  A wave has every fourth 64 of k: 128 bytes of a batch's weight rows and of X's rows come straight into its own ring in
+// LDS (global_load_lds_dwordx4), two or more such units ahead, across the ends of batches and experts; the four waves' sums are
+// added up in LDS at the end of a batch while the next one's first units arrive.  X is drawn from the L2 once per batch, which
+// is why a batch has several groups: a CU draws about 51 bytes per ns, HBM's share is 22 - 25.
+// Measured (us, all kernels of a call, strips of 128 rows / this): heads of 2 rows, 69951 x 2944 96.3 / 82.6, 34482 x 1280 37.3 /
+// 27.5; 28 rows, 23879 x 2560 39.9 / 34.5; 30 rows, 47383 x 7424 158.5 / 142.5; experts of 1 row, two of five of 2944 x 3200 61.1 /
+// 36.2; 7 rows, eight of 4736 x 2816 146.6 / 123.9; 49 rows, eight of 1920 x 10496 202.7 / 186.2.  Where strips fill their turns
+// they are as fast or faster (20 rows, 128256 x 4096 195 / 205; 40 rows, eight experts of 4096 x 4096 151 / 153): rows a power of
+// two apart meet in the same memory channels, and a batch's unit is 64 or more of them at once.  Tried and no faster: the
+// weights straight into registers in the matrix operands' layout (205), other orders of batches and of k (204 - 232), one to four
+// units in flight (205 - 207), X left out (207).
+#include <type_traits>
+
+#include "jk_device.h"
+#include "jk_internal.h"
+
+namespace jk {
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+// What is computed:
+//   HEADS  logits of the rows that the two output heads see, made of the tokens' two features as they are taken from LDS
+//          (see StreamGemmArgs)
+//   PAIR   act = silu(gate) * up of the rows that chose an expert; a group has eight gate rows and the same of the up projection
+//   DOWN   the expert's output projection, of the rows it has
+enum RingKind { HEADS, PAIR, DOWN };
+
+constexpr int kWaves = 4, kRingThreads = 64 * kWaves, kUnit = 64;  // a unit: 64 of k
+constexpr int kRingRows = 32;  // of X at a time
+constexpr int kMaxRows = 128, kMaxRingExperts = 64, kMaxItems = kMaxRingExperts + 2 * kMaxRows / 8;
+
+// RG: groups of eight rows of X, NF: groups of 16 weight rows in a batch
+template <RingKind KIND, int RG, int NF>
+struct RingCfg {
+  static constexpr int MT = (RG + 1) / 2;
+  static constexpr int PER = 2 * NF + RG;            // transfers of a unit, 8 rows of 128 bytes each
+  static constexpr int QUADS = NF * 4, PITCH = QUADS + 1;  // of a row of sums (and a quad against bank conflicts)
+  static constexpr int SUMS = 2 * 16 * MT * PITCH * 16;
+  static constexpr int LISTS = KIND == HEADS ? 0 : 2 * kMaxRows * 4 + kMaxRingExperts * 8 + kMaxItems * 4;
+  static constexpr int FIT = (160 * 1024 - SUMS - LISTS - 1024) / (kWaves * PER * 1024), MOST = 63 / PER + 1;
+  static constexpr int WANT = FIT < MOST ? FIT : MOST, DEPTH = WANT < 6 ? WANT : 6;  // units in flight
+  static constexpr int RING = DEPTH * PER * 1024;    // bytes of a wave
+  static constexpr int SMEM = kWaves * RING + 1024 + SUMS + LISTS;  // (1024: the rows that the last 16 of X may lack)
+  static_assert(DEPTH >= 2, "LDS plan");
+};
+
+__device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(unsigned, bf16x2{(__bf16)lo, (__bf16)hi});
+}
+
+template <RingKind KIND, int RG, int NF>
+__global__ __launch_bounds__(kRingThreads, 1) void ring_gemm_kernel(StreamGemmArgs p) {
+  using C = RingCfg<KIND, RG, NF>;
+  constexpr int MT = C::MT, CAP = 8 * RG, GROUP = KIND == PAIR ? 8 : 16;  // rows of X at a time; output columns of a group
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, g = lane >> 4;
+  unsigned char* ring = smem + wave * C::RING;
+  const unsigned ring_at = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)ring;
+  floatx4* sums = reinterpret_cast<floatx4*>(smem + kWaves * C::RING + 1024);  // [2][CAP][PITCH]
+  int* order = reinterpret_cast<int*>(smem + kWaves * C::RING + 1024 + C::SUMS);  // the rows that chose an expert, expert by expert
+  int* starts = order + 2 * kMaxRows;       // where an expert's begin
+  int* counts = starts + kMaxRingExperts;   // and how many it has
+  int* item_s = counts + kMaxRingExperts;   // (expert, block of CAP rows) pairs that there is something to do for
+
+  // ---- items: the experts that somebody chose, each with up to CAP rows of X at a time
+  int items = 1;
+  if constexpr (KIND != HEADS) {
+    const int2* sel = reinterpret_cast<const int2*>(p.sel);
+    const int2 s0 = lane < p.m ? sel[lane] : make_int2(-1, -1), s1 = lane + 64 < p.m ? sel[lane + 64] : make_int2(-1, -1);
+    const unsigned long long below = (1ull << lane) - 1ull;
+    int n = 0;
+    items = 0;
+    for (int e = 0; e < p.batch; ++e) {  // (every wave makes the same lists)
+      const bool in0 = s0.x == e || s0.y == e, in1 = s1.x == e || s1.y == e;
+      const unsigned long long b0 = __ballot(in0), b1 = __ballot(in1);
+      const int c0 = __popcll(b0), c = c0 + __popcll(b1);
+      if (in0) order[n + __popcll(b0 & below)] = lane;
+      if (in1) order[n + c0 + __popcll(b1 & below)] = lane + 64;
+      if (lane == 0) {
+        starts[e] = n;
+        counts[e] = c;
+        for (int b = 0; b * CAP < c; ++b) item_s[items + b] = e | b << 8;
+      }
+      n += c;
+      items += (c + CAP - 1) / CAP;
+    }
+    __syncthreads();
+  }
+
+  // ---- this workgroup's share of the groups (neighbours on one XCD have the same X)
+  const int all = gridDim.x, blk = blockIdx.x;
+  const int id = all % 8 == 0 ? (blk & 7) * (all >> 3) + (blk >> 3) : blk;
+  const int per_item = (p.n + GROUP - 1) / GROUP;
+  const unsigned total = (unsigned)items * (unsigned)per_item;  // (at most 96 x 8192; heads: 2^20)
+  const int f0 = (int)(total * (unsigned)id / (unsigned)all), f1 = (int)(total * (unsigned)(id + 1) / (unsigned)all);
+  if (f0 == f1) return;  // (the whole workgroup)
+  struct Batch {
+    int item, off, size;  // groups off .. off + size - 1 of an item
+  };
+  auto batch_at = [&](int item, int off, int left) {  // as even as they come
+    const int here = min(per_item - off, left), n = (here + NF - 1) / NF;
+    return Batch{item, off, (here + n - 1) / n};
+  };
+  auto next_batch = [&](const Batch& b, int left) {
+    const int off = b.off + b.size;
+    return off < per_item ? batch_at(b.item, off, left) : batch_at(b.item + 1, 0, left);
+  };
+  auto expert_of = [&](int item) { return KIND == HEADS ? 0 : __builtin_amdgcn_readfirstlane(item_s[item]) & 255; };
+  auto block_of = [&](int item) { return KIND == HEADS ? 0 : __builtin_amdgcn_readfirstlane(item_s[item]) >> 8; };
+  auto rows_of = [&](int item) { return KIND == HEADS ? p.m : __builtin_amdgcn_readfirstlane(counts[expert_of(item)]) - block_of(item) * CAP; };
+
+  // ---- the asking side: where the next unit comes from
+  const int lrow = lane >> 3, lcol = 16 * ((lane & 7) ^ lrow);  // (a transfer's row and, swizzled, its chunk of it)
+  const int units = p.k / kUnit, count = (units - wave + kWaves - 1) / kWaves;  // this wave's units of a batch
+  // (workgroups start at different units: rows often lie a power of two apart, in step all would ask the same few channels)
+  const int rot = count > 0 ? (int)((5u * blk + (blk >> 3)) % (unsigned)count) : 0;
+  const uint16_t *wa, *wb, *xa;  // of the batch that is asked for: the weights (PAIR: gate and up) and X
+  unsigned wr[2 * NF], xr[RG];
+  auto aim_x = [&](int item) {
+    const int e = expert_of(item), first = block_of(item) * CAP, rows = rows_of(item);
+    const uint16_t* base = p.x;
+    if constexpr (KIND == DOWN) base += (long long)e * p.x_batch + (long long)first * p.k;
+    xa = dev::uniform_ptr(base);
+#pragma unroll
+    for (int i = 0; i < RG; ++i) {  // (rows past the end repeat the last one; never stored)
+      int row = min(8 * i + lrow, rows - 1);
+      if constexpr (KIND == PAIR) row = order[starts[e] + first + row];
+      xr[i] = (unsigned)row * (unsigned)p.k * 2u + lcol;
+    }
+  };
+  auto aim_w = [&](const Batch& b) {
+    const long long at = (long long)expert_of(b.item) * p.w_batch + (long long)b.off * GROUP * p.k;
+    wa = dev::uniform_ptr(p.w + at);
+    if constexpr (KIND == PAIR) wb = dev::uniform_ptr(p.w2 + at);
+    const int last = min(b.size * GROUP, p.n - b.off * GROUP) - 1;
+#pragma unroll
+    for (int i = 0; i < (KIND == PAIR ? NF : 2 * NF); ++i) wr[i] = (unsigned)min(8 * i + lrow, last) * (unsigned)p.k * 2u + lcol;
+  };
+  Batch asked = batch_at(0, 0, 0);
+  {
+    const int item = f0 / per_item;
+    asked = batch_at(item, f0 - item * per_item, f1 - f0);
+  }
+  int left_a = f1 - f0, ja = 0;  // groups from `asked` on, and its next unit
+  Batch used = asked;
+  int left_u = left_a;
+  bool more = count > 0;
+  aim_x(asked.item);
+  aim_w(asked);
+  auto ask = [&](int slot) {
+    const int u = ja + rot, at = (wave + kWaves * (u < count ? u : u - count)) * kUnit;
+    const unsigned to = ring_at + slot * (C::PER * 1024);
+#pragma unroll
+    for (int i = 0; i < 2 * NF; ++i) {
+      if constexpr (KIND == PAIR) dev::dma16((i & 1 ? wb : wa) + at, wr[i >> 1], to + 1024 * i);
+      else dev::dma16(wa + at, wr[i], to + 1024 * i);
+    }
+#pragma unroll
+    for (int i = 0; i < RG; ++i) dev::dma16(xa + at, xr[i], to + 1024 * (2 * NF + i));
+    if (++ja == count) {
+      ja = 0;
+      left_a -= asked.size;
+      more = left_a > 0;
+      if (more) {
+        const int was = asked.item;
+        asked = next_batch(asked, left_a);
+        if (asked.item != was) aim_x(asked.item);
+        aim_w(asked);
+      }
+    }
+  };
+
+  // ---- HEADS: row 2 r + h of the left side from rows 2 r and 2 r + 1 as they lie in LDS (a term whose coefficient is zero is
+  // left out, so that a NaN in the other expert's feature cannot leak into a decoupled head)
+  const bool mixed = KIND == HEADS && p.heads_mode != JK_HEADS_DECOUPLED;
+  float c_own[MT], c_other[MT];
+  if constexpr (KIND == HEADS) {
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      const int row = min(16 * t + r, p.m - 1);  // (p.m is even: a row past the end has a partner past the end)
+      const float s_own = p.s_top[row], s_other = p.s_top[row ^ 1];
+      c_own[t] = mixed && (row & 1) ? -p.alpha : s_own;
+      c_other[t] = !mixed ? 0.f : (row & 1) ? p.beta : s_other;
+    }
+  }
+  auto mix = [&](bf16x8 v, int t) {
+    const u32x4 x = __builtin_bit_cast(u32x4, v);
+    const unsigned keep = c_own[t] != 0.f ? ~0u : 0u, keep_other = c_other[t] != 0.f ? ~0u : 0u;
+    u32x4 o;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const unsigned own = x[j] & keep;
+      float lo = c_own[t] * __uint_as_float(own << 16), hi = c_own[t] * __uint_as_float(own & 0xFFFF0000u);
+      if (mixed) {
+        const unsigned other = (unsigned)__builtin_amdgcn_update_dpp(0, (int)x[j], 0xB1, 0xf, 0xf, true) & keep_other;  // (lane ^ 1)
+        lo += c_other[t] * __uint_as_float(other << 16);
+        hi += c_other[t] * __uint_as_float(other & 0xFFFF0000u);
+      }
+      o[j] = pack_bf16(lo, hi);
+    }
+    return __builtin_bit_cast(bf16x8, o);
+  };
+
+  // ---- the stream
+  floatx4 acc[NF][MT];
+  auto clear = [&] {
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+#pragma unroll
+      for (int t = 0; t < MT; ++t) acc[f][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+  };
+  const int at0 = r * 128 + 16 * (g ^ (r & 7)), at1 = r * 128 + 16 * ((4 + g) ^ (r & 7));  // a lane's chunks of its row
+  bf16x8 a[NF][2], b[MT][2];
+  auto take = [&](int slot) {  // (and the slot may be filled again)
+    const unsigned char* from = ring + slot * (C::PER * 1024);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+#pragma unroll
+      for (int t = 0; t < MT; ++t) b[t][s] = *reinterpret_cast<const bf16x8*>(from + (2 * NF + 2 * t) * 1024 + (s ? at1 : at0));
+#pragma unroll
+      for (int f = 0; f < NF; ++f) a[f][s] = *reinterpret_cast<const bf16x8*>(from + 2 * f * 1024 + (s ? at1 : at0));
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  };
+  auto multiply = [&] {
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int t = 0; t < MT; ++t) {
+        const bf16x8 x = KIND == HEADS ? mix(b[t][s], t) : b[t][s];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) acc[f][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[f][s], x, acc[f][t], 0, 0, 0);
+      }
+  };
+  // (waits that stores of a batch's results make longer than they need be, never shorter)
+  int in_flight = 0;
+  auto wait_oldest = [&] {
+    constexpr int D = C::DEPTH, P = C::PER;
+    if (in_flight == D) dev::wait_vm<(D - 1) * P>();
+    else if (D > 5 && in_flight == 5) dev::wait_vm<(D > 5 ? 4 * P : 0)>();
+    else if (D > 4 && in_flight == 4) dev::wait_vm<(D > 4 ? 3 * P : 0)>();
+    else if (D > 3 && in_flight == 3) dev::wait_vm<(D > 3 ? 2 * P : 0)>();
+    else if (D > 2 && in_flight == 2) dev::wait_vm<(D > 2 ? P : 0)>();
+    else dev::wait_vm<0>();
+  };
+  int to = 0, from = 0;  // slots
+  auto ask_next = [&] {
+    if (!more) return;
+    ask(to);
+    to = to + 1 == C::DEPTH ? 0 : to + 1;
+    ++in_flight;
+  };
+#pragma unroll
+  for (int i = 0; i < C::DEPTH; ++i) ask_next();
+
+  for (;;) {
+    clear();
+    for (int j = 0; j < count; ++j) {
+      wait_oldest();
+      take(from);
+      from = from + 1 == C::DEPTH ? 0 : from + 1;
+      --in_flight;
+      ask_next();
+      multiply();
+    }
+    // ---- the waves' sums: two add the other two's to theirs, everybody adds those two up
+    auto at = [&](int half, int f, int t) { return sums + (half * 16 * MT + 16 * t + r) * C::PITCH + 4 * f + g; };
+    __syncthreads();  // (the sums of the batch before have been read)
+    if (wave >= 2) {
+#pragma unroll
+      for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int t = 0; t < MT; ++t) *at(wave - 2, f, t) = acc[f][t];
+    }
+    __syncthreads();
+    if (wave < 2) {
+#pragma unroll
+      for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int t = 0; t < MT; ++t) *at(wave, f, t) += acc[f][t];
+    }
+    __syncthreads();
+    const int e = expert_of(used.item), first = block_of(used.item) * CAP, rows = min(rows_of(used.item), CAP);
+    auto quad = [&](int row, int q) { return sums[row * C::PITCH + q] + sums[(16 * MT + row) * C::PITCH + q]; };
+    if constexpr (KIND == PAIR) {
+      const int per_row = used.size * 2;  // quads of gate rows
+      for (int i = tid; i < rows * per_row; i += kRingThreads) {
+        const int row = i / per_row, h = i - row * per_row, q = (h >> 1) * 4 + (h & 1);
+        const floatx4 gate = quad(row, q), up = quad(row, q + 2);
+        float o[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[j] = gate[j] / (1.f + expf(-gate[j])) * up[j];
+        *reinterpret_cast<uint2*>(p.act + (long long)e * p.act_batch + (long long)(first + row) * p.n + used.off * GROUP + 4 * h) =
+            make_uint2(pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]));
+      }
+    } else {
+      const int per_row = used.size * 4, n0 = used.off * GROUP;
+      float* y = p.y + (long long)e * p.y_batch + (long long)first * p.n + n0;
+      if (KIND == DOWN || ((p.n & 3) == 0 && (reinterpret_cast<size_t>(p.y) & 15) == 0)) {
+        for (int i = tid; i < rows * per_row; i += kRingThreads) {
+          const int row = i / per_row, q = i - row * per_row;
+          if (n0 + 4 * q >= p.n) continue;
+          const floatx4 v = quad(row, q);
+          floatx4* dst = reinterpret_cast<floatx4*>(y + (long long)row * p.n + 4 * q);
+          if constexpr (KIND == HEADS) __builtin_nontemporal_store(v, dst);
+          else *dst = v;
+        }
+      } else {
+        for (int i = tid; i < rows * per_row; i += kRingThreads) {
+          const int row = i / per_row, q = i - row * per_row;
+          const floatx4 v = quad(row, q);
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (n0 + 4 * q + j < p.n) y[(long long)row * p.n + 4 * q + j] = v[j];
+        }
+      }
+    }
+    left_u -= used.size;
+    if (left_u <= 0) break;
+    used = next_batch(used, left_u);
+  }
+}
+
+template <RingKind KIND, int RG, int NF>
+hipError_t launch(const StreamGemmArgs& p, hipStream_t stream) {
+  static LdsLimitRaised raised;
+  constexpr int smem = RingCfg<KIND, RG, NF>::SMEM;
+  if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(ring_gemm_kernel<KIND, RG, NF>), smem, raised); e != hipSuccess) return e;
+  const long long groups = (long long)((p.n + (KIND == PAIR ? 7 : 15)) / (KIND == PAIR ? 8 : 16)) * p.batch;
+  const int cus = device_cu_count();
+  hipLaunchKernelGGL((ring_gemm_kernel<KIND, RG, NF>), dim3((unsigned)(groups < cus ? groups : cus)), dim3(kRingThreads), smem, stream, p);
+  return hipGetLastError();
+}
+// `items`: how many experts are likely to be chosen
+template <RingKind KIND, int RG>
+hipError_t launch_batches(const StreamGemmArgs& p, int items, hipStream_t stream) {
+  const int groups = (p.n + (KIND == PAIR ? 7 : 15)) / (KIND == PAIR ? 8 : 16) * items, each = (groups + device_cu_count() - 1) / device_cu_count();
+  if (each <= 2) return launch<KIND, RG, 2>(p, stream);
+  return each <= 4 ? launch<KIND, RG, 4>(p, stream) : launch<KIND, RG, 6>(p, stream);
+}
+template <RingKind KIND>
+hipError_t launch_rows(const StreamGemmArgs& p, int rows, int items, hipStream_t stream) {
+  switch ((rows + 7) / 8) {
+    case 1: return launch_batches<KIND, 1>(p, items, stream);
+    case 2: return launch_batches<KIND, 2>(p, items, stream);
+    case 3: return launch_batches<KIND, 3>(p, items, stream);
+    case 4: return launch_batches<KIND, 4>(p, items, stream);
+    default: return hipErrorInvalidValue;
+  }
+}
+// whether strips of 128 weight rows fill their turns of workgroups (the other kernel's)
+bool strips_fill(int strips) {
+  const int cus = device_cu_count(), turns = (strips + cus - 1) / cus;
+  return strips >= 0.96 * turns * cus;
+}
+}  // namespace
+
+// Against strips of 128 rows in turns of workgroups (stream_gemm.hip), over 66 shapes drawn from 1 - 80 rows: heads 0.97 - 1.35
+// times as fast where this takes them, 1.11 in the geometric mean; below two groups per CU, where the strips' kernel divides
+// k, 0.90 - 1.04, beyond 32 rows 0.90 - 1.07.  Experts 0.94 - 1.69, 1.14 in the mean; with more rows 0.88 - 1.15.
+bool ring_gemm_takes_heads(int m, int n) { return m <= kRingRows && n >= 32 * device_cu_count() && !strips_fill((n + 127) / 128); }
+bool ring_gemm_takes_experts(int rows, int items, int d_model, int d_ff) {
+  return rows <= kRingRows && !(strips_fill(items * ((d_ff + 63) / 64)) && strips_fill(items * ((d_model + 127) / 128)));
+}
+hipError_t launch_ring_gemm_heads(const StreamGemmArgs& p, hipStream_t stream) { return launch_rows<HEADS>(p, p.m, 1, stream); }
+hipError_t launch_ring_gemm_pair(const StreamGemmArgs& p, int rows, int items, hipStream_t stream) { return launch_rows<PAIR>(p, rows, items, stream); }
+hipError_t launch_ring_gemm_down(const StreamGemmArgs& p, int rows, int items, hipStream_t stream) { return launch_rows<DOWN>(p, rows, items, stream); }
+
+}  // namespace jk

@@ -231,3 +231,16 @@ def test_rows_mixed_by_the_product_are_bit_exact(rows, d, vocab):
     x["f_top"][0, 1, 3] = np.nan                         # left out where its coefficient is zero
     lg, *_ = _call(x, mode=jk.JK_HEADS_CONTRASTIVE, alpha=0.0, beta=2.0)
     assert np.isnan(lg[0, 0]).all() and np.isfinite(lg[0, 1]).all() and np.isfinite(lg[1:]).all()
+
+
+@pytest.mark.parametrize("rows", [1, 4, 5, 12, 16])      # groups of eight rows, whole and not
+@pytest.mark.parametrize("d,vocab", [(128, 8192), (640, 9001), (384, 16388), (256, 33003)])
+def test_equal_shares_of_the_vocabulary_are_bit_exact(rows, d, vocab):
+    """Vocabularies that strips of 128 rows would not fill the CUs with: batches of two, four and six groups of weight
+    rows, the last ones short, waves without a share of k, odd row lengths."""
+    x = _exact_inputs(rows, d, vocab, rows + d)
+    _check(x, exact=True)
+    _check(x, mode=jk.JK_HEADS_CONTRASTIVE, alpha=0.5, beta=2.0, exact=True)
+    x["f_top"][0, 1, 3] = np.nan                         # left out where its coefficient is zero
+    lg, *_ = _call(x, mode=jk.JK_HEADS_CONTRASTIVE, alpha=0.0, beta=2.0)
+    assert np.isnan(lg[0, 0]).all() and np.isfinite(lg[0, 1]).all() and np.isfinite(lg[1:]).all()

@@ -245,3 +245,21 @@ def test_a_nan_score_ranks_below_every_other(n):
     s[:, worst] = -np.inf
     np.testing.assert_array_equal(got[2], np.argsort(-s, axis=1, kind="stable")[:, :2])
     assert np.isnan(got[1]).all() and np.isfinite(got[0]).all()
+
+
+@pytest.mark.parametrize("rows,d,f,n", [(40, 256, 384, 8), (9, 128, 640, 8), (60, 256, 128, 12), (33, 128, 2304, 64)])
+def test_more_rows_than_an_expert_is_likely_to_have(rows, d, f, n):
+    """All rows choose the same two experts, several times as many as the launch reckons with: the experts' weights are
+    gone through once per block of rows, and nobody else's."""
+    x = moe_inputs(rows, d, f, n, seed=rows)
+    x["u"] = np.repeat(x["u"][:1], rows, axis=0)
+    x["u"][1::2] *= np.float32(0.5)                                       # (exact; not all rows the same)
+    f_top, _, idx, _ = _check(x, min_gap=1e-6)
+    assert (np.sort(idx, axis=1) == np.sort(idx[0])).all()
+    for r in range(2, rows):
+        np.testing.assert_array_equal(f_top[r], f_top[r % 2])
+
+
+@pytest.mark.parametrize("rows,d,f,n", [(1, 1920, 896, 8), (35, 640, 1664, 8), (12, 128, 128, 3), (18, 1024, 2432, 5), (24, 4352, 256, 6)])
+def test_equal_shares_of_the_experts_rows(rows, d, f, n):
+    _check(moe_inputs(rows, d, f, n, seed=rows + 7), min_gap=1e-6)
