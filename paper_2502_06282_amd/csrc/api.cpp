@@ -338,10 +338,11 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
     if (s > kMaxSplits) return false;  // fp32 path: at most 64 * 1024 keys
     pl->splits = (int)s;
     // Few workgroups: each range in up to eight parts, where the merging launch (3 us) is needed anyway or costs less than
-    // what the parts save (20 nodes, 8 heads of 128: 420 keys 18.0 us whole, 13.3 in parts; 138 keys of 64 8.0 and 9.8).
+    // what the parts save (20 nodes, 8 heads, whole / in parts: 200 keys of 128 12.2 / 11.1 us, 120 10.0 / 10.9; 340 of 64 9.8 /
+    // 8.8, 276 8.5 / 8.9).
     const long long wgs = units * ((pl->m_rows + 15) / 16) * s;
     pl->parts = pl->splits;
-    if (s > 1 || keys >= 256)
+    if (s > 1 || keys * d.head_dim >= 19200)
       for (int sub = 8; sub > 1; --sub)
         if (wgs * sub <= device_cu_count() && s * sub <= kMaxSplits) {
           pl->parts = pl->splits * sub;

@@ -4,13 +4,17 @@
 // shapes.  One workgroup per (sequence, KV head, 16 query rows, key split); its waves take blocks of 16 keys in turn, keep
 // a running maximum and sum per row, and meet once at the end, in LDS.
 //
-// What bounds it: for small calls one trip to memory after the other, so a wave has a block's K and V in flight at once and
-// the next block's K behind them, and the first block's K is asked for before the prefix length is known; for large ones
-// the products, which run on v_mfma_f32_16x16x4_f32 (full fp32) with K and V straight from L2 in operand layout, each
-// read once for 16 rows.  S^T = K Q^T leaves a lane with four keys of one row: exactly what the second product,
-// O^T = V^T P^T, takes as its operand, so the weights never leave their registers.  An undivided key range needs no second
-// launch.  With one workgroup per query row, a thread per key and column, 4 heads of 64, 10 nodes and 138 keys took
-// 16.9 us (the second launch included), 8.0 like this; 4 sequences, 8 heads of 128, 52 nodes, 2100 keys 481 and 57.
+// What bounds it: for small calls the instructions of a lone wave (5 - 8 cycles each; a block of 16 keys takes 2400 cycles with
+// its operands there) and the trips to memory in front of them.  So a wave has a block's K and V in flight at once and the next
+// block's K behind them, the prefix's and the tree's alike, and asks for the first block's K before the prefix length is known;
+// who has a block of the tree makes the ancestors of its rows while the keys come; at the end a wave scales its own sums, and
+// what is left to do for the result is adding.  For large calls the products bind, which run on v_mfma_f32_16x16x4_f32 (full
+// fp32) with K and V straight from L2 in operand layout, each read once for 16 rows.  S^T = K Q^T leaves a lane with four keys
+// of one row: exactly what the second product, O^T = V^T P^T, takes as its operand, so the weights never leave their registers.
+// An undivided key range needs no second launch.  4 heads of 64, 10 nodes and 138 keys: 16.9 us with one workgroup per query
+// row and a thread per key and column (the second launch included), 7.9 with the tree's ancestors made by one wave for all, its
+// keys asked for behind a barrier and the waves' weights worked out by every thread of the result, 6.2 like this; 4 sequences, 8
+// heads of 128, 52 nodes, 2100 keys 481, 56.4 and 56.
 #include <type_traits>
 
 #include "jk_internal.h"
@@ -33,46 +37,48 @@ struct FParams {
   float scale;
 };
 
-// Ancestor sets (with the node itself) of all nodes, by one wave: sets and pointers double their reach every round.
-__device__ __forceinline__ void ancestor_sets(const FParams& p, int b, bool report, unsigned long long (*anc)[2], int* up) {
+// The ancestors of a node (with itself), as a lane needs them for its row: bits of nodes 0 - 63 and 64 - 127.  A lane holds
+// nodes lane and lane + 64; sets and pointers double their reach every round, by exchanges across the wave: no barrier, and no
+// wave that the others wait for.  (One wave for all, through LDS: it came 2500 cycles after the others to the barrier.)
+struct Ancestors {
+  unsigned long long lo, hi;
+};
+__device__ __forceinline__ unsigned long long shfl64(unsigned long long v, int lane) {
+  return (unsigned)__shfl((int)(unsigned)v, lane) | (unsigned long long)(unsigned)__shfl((int)(unsigned)(v >> 32), lane) << 32;
+}
+__device__ __forceinline__ Ancestors ancestors_of(const FParams& p, int pa0, int pa1, int node, bool report) {
   const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int n = lane + 64 * h;
-    if (n < p.T) {
-      const int pa = p.parent[(long long)b * p.T + n];
-      const bool ok = pa >= -1 && pa < n;
-      up[n] = ok ? pa : -1;
-      anc[n][0] = h == 0 ? 1ull << lane : 0ull;
-      anc[n][1] = h == 1 ? 1ull << lane : 0ull;
-      if (!ok && report) __hip_atomic_fetch_or(p.err, kDevErrBadTree, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const bool ok0 = lane >= p.T || (pa0 >= -1 && pa0 < lane), ok1 = lane + 64 >= p.T || (pa1 >= -1 && pa1 < lane + 64);
+  if (report && __any(!ok0 || !ok1) && lane == 0) __hip_atomic_fetch_or(p.err, kDevErrBadTree, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  int up0 = ok0 && lane < p.T ? pa0 : -1;
+  unsigned long long own0 = 1ull << lane;  // of node `lane`: all its ancestors are below 64
+  while (__any(up0 >= 0)) {
+    const int from = max(up0, 0);
+    const unsigned long long set = shfl64(own0, from);
+    const int next = __shfl(up0, from);
+    if (up0 >= 0) {
+      own0 |= set;
+      up0 = next;
     }
   }
-  for (;;) {
-    asm volatile("" ::: "memory");  // (the LDS operations of a wave complete in order)
-    unsigned long long lo[2] = {0ull, 0ull}, hi[2] = {0ull, 0ull};
-    int next[2] = {-1, -1};
-    bool more[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int n = lane + 64 * h, a = n < p.T ? up[n] : -1;
-      more[h] = a >= 0;
-      if (more[h]) {
-        lo[h] = anc[a][0];
-        hi[h] = anc[a][1];
-        next[h] = up[a];
-      }
+  if (p.T <= 64) return Ancestors{shfl64(own0, node), 0ull};
+  int up1 = ok1 && lane + 64 < p.T ? pa1 : -1;
+  unsigned long long low1 = 0ull, own1 = 1ull << lane;  // of node lane + 64
+  while (__any(up1 >= 0)) {
+    const int from = max(up1, 0) & 63;
+    const unsigned long long below = shfl64(own0, from), low = shfl64(low1, from), set = shfl64(own1, from);
+    const int next = __shfl(up1, from);
+    if (up1 >= 64) {
+      low1 |= low;
+      own1 |= set;
+      up1 = next;
+    } else if (up1 >= 0) {
+      low1 |= below;
+      up1 = -1;
     }
-    if (!__any(more[0] || more[1])) return;
-    asm volatile("" ::: "memory");
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-      if (more[h]) {
-        anc[lane + 64 * h][0] |= lo[h];
-        anc[lane + 64 * h][1] |= hi[h];
-        up[lane + 64 * h] = next[h];
-      }
   }
+  const unsigned long long a = shfl64(own0, node & 63), l = shfl64(low1, node & 63), h = shfl64(own1, node & 63);
+  return node < 64 ? Ancestors{a, 0ull} : Ancestors{l, h};
 }
 
 // KJ: 16-column chunks of a head (rounded up); WAVES: by how many registers that leaves
@@ -82,9 +88,8 @@ constexpr int waves_for() { return KJ <= 8 ? 8 : 4; }
 template <int KJ>
 __global__ __launch_bounds__(64 * waves_for<KJ>(), KJ <= 8 ? 2 : 1) void tva_f32_kernel(FParams p) {
   constexpr int WAVES = waves_for<KJ>(), DB = (KJ + 3) / 4, LDO = 64 * DB + 4;
-  __shared__ unsigned long long anc[JK_MAX_TREE][2];
-  __shared__ int up[JK_MAX_TREE];
-  __shared__ float2 ml[WAVES][16];
+  __shared__ float tops[WAVES][16];     // a wave's maximum of a row,
+  __shared__ float2 shares[WAVES][16];  // and its share of the row's sum, beside the maximum of all
   extern __shared__ __attribute__((aligned(16))) float osum[];  // [WAVES][16][LDO]
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -98,29 +103,45 @@ __global__ __launch_bounds__(64 * waves_for<KJ>(), KJ <= 8 ? 2 : 1) void tva_f32
   const float* vt = p.vt + b * p.kt_sb + (long long)kv * p.kt_sh;
 
   int L = p.prefix_len[b];
+  const int pa0 = lane < p.T ? p.parent[(long long)b * p.T + lane] : -1, pa1 = lane + 64 < p.T ? p.parent[(long long)b * p.T + lane + 64] : -1;
   const int m = min(row0 + c, p.M - 1), node = m / p.G;  // this lane's query row (rows past the end repeat the last one)
-  floatx4 q[KJ], k[KJ];
+  floatx4 q[KJ], k[KJ], v[DB][4];  // the row, and a block's K and V
   // column 16 j + 4 g of a row; columns past the end: the row's first ones, against zeros of q
   auto col = [&](int j) { return 16 * j + 4 * g < D ? 16 * j + 4 * g : 0; };
   auto load_k = [&](const float* row) {
 #pragma unroll
     for (int j = 0; j < KJ; ++j) k[j] = *reinterpret_cast<const floatx4*>(row + col(j));
   };
+  auto load_v = [&](auto v_at) {  // v_at(i): where key i of the block has its values
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float* row = v_at(4 * g + i);
+#pragma unroll
+      for (int d = 0; d < DB; ++d) v[d][i] = *reinterpret_cast<const floatx4*>(row + (64 * d + 4 * c < D ? 64 * d + 4 * c : 0));
+    }
+  };
   if (split == 0 && p.max_prefix > 0) load_k(kc + (long long)min(16 * wave + c, p.max_prefix - 1) * p.kc_sl);
   {
     const float* src = p.q + b * p.q_sb + node * p.q_st + (long long)(kv * p.G + m - node * p.G) * p.q_sh;
 #pragma unroll
-    for (int j = 0; j < KJ; ++j) {
-      q[j] = *reinterpret_cast<const floatx4*>(src + col(j));
-      if (16 * j + 4 * g >= D) q[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < KJ; ++j) q[j] = *reinterpret_cast<const floatx4*>(src + col(j));
+    if (16 * KJ != D) {
+#pragma unroll
+      for (int j = 0; j < KJ; ++j)
+        if (16 * j + 4 * g >= D) q[j] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
   }
-  if (wave == WAVES - 1) ancestor_sets(p, b, split == 0 && row0 == 0 && kv == 0, anc, up);
   L = L < 0 ? 0 : (L > p.max_prefix ? p.max_prefix : L);
-  const int ktot = L + p.T;
-  const int k_begin = (int)((long long)split * ktot / p.splits), k_end = (int)((long long)(split + 1) * ktot / p.splits);
+  const int ktot = L + p.T;  // (at most 512 ranges of at most 65 664 keys)
+  const int k_begin = p.splits == 1 ? 0 : (int)((unsigned)split * (unsigned)ktot / (unsigned)p.splits);
+  const int k_end = p.splits == 1 ? ktot : (int)((unsigned)(split + 1) * (unsigned)ktot / (unsigned)p.splits);
   const int p_end = min(k_end, L), t_begin = max(k_begin, L);
   const int n_prefix = p_end > k_begin ? (p_end - k_begin + 15) / 16 : 0, n_tree = k_end > t_begin ? (k_end - t_begin + 15) / 16 : 0;
+
+  // The waves with fewer blocks of the prefix take the tree's first; who has one makes its rows' ancestors while the keys come
+  const int first = (wave + WAVES - n_prefix % WAVES) % WAVES;
+  Ancestors seen{0ull, 0ull};
+  if (first < n_tree || (split == 0 && wave == 0)) seen = ancestors_of(p, pa0, pa1, node, split == 0 && row0 == 0 && kv == 0 && wave == 0);
 
   // A weight of zero - an unseen key's above all - leaves its value out, whatever that is.  The matrix product has one
   // value for sixteen rows' weights, so an infinity or a NaN reaches them all; it stays in the accumulators to the end, and
@@ -128,17 +149,9 @@ __global__ __launch_bounds__(64 * waves_for<KJ>(), KJ <= 8 ? 2 : 1) void tva_f32
   // each product: 57.0 us for 4 sequences, 8 heads of 128, 52 nodes, 2100 keys became 59.8.)
   floatx4 o[DB][4];
   float mx, sum;
-  // 16 keys: `v_at(i)` is where key i has its values, visible(i) whether this lane's row sees key 4 g + i; `next` asks for
-  // the K of the block behind this one as soon as this one's is used
+  // 16 keys, whose K and V have been asked for: visible(i) whether this lane's row sees key 4 g + i; `next` asks for the K of
+  // the block behind this one as soon as this one's is used.  (careful: V at v_at(i))
   auto block = [&](auto careful, auto v_at, auto visible, auto next) {
-    floatx4 v[DB][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (careful) break;
-      const float* row = v_at(4 * g + i);
-#pragma unroll
-      for (int d = 0; d < DB; ++d) v[d][i] = *reinterpret_cast<const floatx4*>(row + (64 * d + 4 * c < D ? 64 * d + 4 * c : 0));
-    }
     if (16 * KJ != D) {  // (uniform; what stands in for columns past the end of a key with an infinity must not meet q's zeros)
 #pragma unroll
       for (int j = 0; j < KJ; ++j)
@@ -156,15 +169,15 @@ __global__ __launch_bounds__(64 * waves_for<KJ>(), KJ <= 8 ? 2 : 1) void tva_f32
     top = fmaxf(top, __uint_as_float(dev::other16(__float_as_uint(top), lane & 16)));
     top = fmaxf(top, __uint_as_float(dev::other32(__float_as_uint(top), lane & 32)));
     const float mn = fmaxf(mx, top), base = mn == -INFINITY ? 0.f : mn;
-    if (__any(mn > mx)) {
+    if (__any(mn > mx && mx > -INFINITY)) {  // (nothing to rescale before the row's first key)
       const float f = expf(mx - base);
       sum *= f;
 #pragma unroll
       for (int d = 0; d < DB; ++d)
 #pragma unroll
         for (int i = 0; i < 4; ++i) o[d][i] *= f;
-      mx = mn;
     }
+    mx = mn;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       s[i] = expf(s[i] - base);
@@ -204,24 +217,31 @@ __global__ __launch_bounds__(64 * waves_for<KJ>(), KJ <= 8 ? 2 : 1) void tva_f32
     mx = -INFINITY;
     sum = 0.f;
     if ((split != 0 || careful) && wave < n_prefix) prefix_k(wave);
+    const int tree_begin = t_begin - L, last = k_end - L - 1;
+    auto tree_k = [&](int blk) { load_k(kt + (long long)min(tree_begin + 16 * blk + c, last) * p.kt_st); };
+    if (wave >= n_prefix && first < n_tree) tree_k(first);
     for (int blk = wave; blk < n_prefix; blk += WAVES) {
-      const int key0 = k_begin + 16 * blk;
-      block(careful, [&](int i) { return vc + (long long)min(key0 + i, p_end - 1) * p.kc_sl; }, [&](int i) { return key0 + 4 * g + i < p_end; },
+      const int key0 = k_begin + 16 * blk, left = p_end - key0 - 4 * g;
+      auto v_at = [&](int i) { return vc + (long long)min(key0 + i, p_end - 1) * p.kc_sl; };
+      if (!careful) load_v(v_at);
+      block(careful, v_at, [&](int i) { return i < left; },
             [&]() {
               if (blk + WAVES < n_prefix) prefix_k(blk + WAVES);
+              else if (first < n_tree) tree_k(first);
             });
     }
-    if (!careful) __syncthreads();  // the ancestor sets are there (once in every wave)
-    const unsigned long long lo = anc[node][0], hi = anc[node][1];
-    for (int blk = (wave + WAVES - n_prefix % WAVES) % WAVES; blk < n_tree; blk += WAVES) {  // (the waves with fewer blocks first)
-      const int key0 = t_begin - L + 16 * blk, last = k_end - L - 1;
-      load_k(kt + (long long)min(key0 + c, last) * p.kt_st);
-      block(careful, [&](int i) { return vt + (long long)min(key0 + i, last) * p.kt_st; },
-            [&](int i) {
-              const int t = key0 + 4 * g + i;
-              return t <= last && (((t < 64 ? lo : hi) >> (t & 63)) & 1ull);
-            },
-            []() {});
+    const unsigned long long lo = seen.lo, hi = seen.hi;
+    for (int blk = first; blk < n_tree; blk += WAVES) {
+      const int key0 = tree_begin + 16 * blk, left = last + 1 - key0 - 4 * g;
+      auto v_at = [&](int i) { return vt + (long long)min(key0 + i, last) * p.kt_st; };
+      if (!careful) load_v(v_at);
+      // the bits of keys key0 .. key0 + 63, then this lane's four
+      const unsigned long long set = key0 >= 64 ? hi >> (key0 - 64) : key0 > 0 ? lo >> key0 | hi << (64 - key0) : lo;
+      const unsigned mine = (unsigned)(set >> (4 * g));
+      block(careful, v_at, [&](int i) { return i < left && ((mine >> i) & 1u); },
+            [&]() {
+              if (blk + WAVES < n_tree) tree_k(blk + WAVES);
+            });
     }
   };
   pass(std::false_type());
@@ -237,15 +257,20 @@ __global__ __launch_bounds__(64 * waves_for<KJ>(), KJ <= 8 ? 2 : 1) void tva_f32
     pass(std::true_type());
   }
 
-  // ---- the waves' shares of a row meet
+  // ---- the waves' shares of a row meet (each scaled by its own wave: worked out per column of the result, eight exponentials in
+  // every thread, 7.9 us became 7.2 for the tiny call)
   sum += __uint_as_float(dev::other16(__float_as_uint(sum), lane & 16));
   sum += __uint_as_float(dev::other32(__float_as_uint(sum), lane & 32));
-  if (g == 0) ml[wave][c] = make_float2(mx, sum);
+  if (g == 0) tops[wave][c] = mx;
+  // (where this thread's columns of the result go, worked out while the others come)
+  const int d4 = D / 4;
+  int r = tid / d4, x = tid - r * d4;
   __syncthreads();
   float all = -INFINITY;
 #pragma unroll
-  for (int w = 0; w < WAVES; ++w) all = fmaxf(all, ml[w][c].x);
+  for (int w = 0; w < WAVES; ++w) all = fmaxf(all, tops[w][c]);
   const float f = mx == -INFINITY ? 0.f : expf(mx - all);
+  if (g == 0) shares[wave][c] = make_float2(sum * f, all);
   float* mine = osum + (wave * 16 + c) * LDO + 16 * g;  // (a lane has 16 columns of its row in each 64)
 #pragma unroll
   for (int d = 0; d < DB; ++d)
@@ -253,28 +278,29 @@ __global__ __launch_bounds__(64 * waves_for<KJ>(), KJ <= 8 ? 2 : 1) void tva_f32
     for (int r = 0; r < 4; ++r)
       *reinterpret_cast<floatx4*>(mine + 64 * d + 4 * r) = floatx4{o[d][0][r] * f, o[d][1][r] * f, o[d][2][r] * f, o[d][3][r] * f};
   __syncthreads();
-  const int d4 = D / 4;
   for (int i = tid; i < 16 * d4; i += 64 * WAVES) {
-    const int r = i / d4, x = i % d4 * 4, row = row0 + r;
+    if (i != tid) {
+      r = i / d4;
+      x = i - r * d4;
+    }
+    const int row = row0 + r;
     if (row >= p.M) break;
     floatx4 t = {0.f, 0.f, 0.f, 0.f};
-    float top = -INFINITY, tot = 0.f;
+    float tot = 0.f;
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) {
-      t += *reinterpret_cast<const floatx4*>(osum + (w * 16 + r) * LDO + x);
-      top = fmaxf(top, ml[w][r].x);
+      t += *reinterpret_cast<const floatx4*>(osum + (w * 16 + r) * LDO + 4 * x);
+      tot += shares[w][r].x;
     }
-#pragma unroll
-    for (int w = 0; w < WAVES; ++w) tot += ml[w][r].x == -INFINITY ? 0.f : ml[w][r].y * expf(ml[w][r].x - top);
     if (p.splits == 1) {
       const int n = row / p.G;
       float* dst = p.out + b * p.o_sb + n * p.o_st + (long long)(kv * p.G + row - n * p.G) * p.o_sh;
       const float inv = 1.f / tot;  // (tot > 0: every row sees at least its own tree key)
-      *reinterpret_cast<floatx4*>(dst + x) = floatx4{t[0] * inv, t[1] * inv, t[2] * inv, t[3] * inv};
+      *reinterpret_cast<floatx4*>(dst + 4 * x) = floatx4{t[0] * inv, t[1] * inv, t[2] * inv, t[3] * inv};
     } else {
       const long long prow = ((long long)(b * p.Hkv + kv) * p.splits + split) * p.m_pad + row;
-      *reinterpret_cast<floatx4*>(p.part_o + prow * D + x) = t;
-      if (x == 0) p.part_ml[prow] = make_float2(top, tot);
+      *reinterpret_cast<floatx4*>(p.part_o + prow * D + 4 * x) = t;
+      if (x == 0) p.part_ml[prow] = make_float2(shares[0][r].y, tot);
     }
   }
 }

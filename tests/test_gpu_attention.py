@@ -799,3 +799,17 @@ def test_f32_leaves_out_values_with_a_weight_of_zero(D, T, L):
     clean["k_cache"], clean["v_cache"] = clean["k_cache"][:, keep], clean["v_cache"][:, keep]
     ref = oracle_attention(**clean, parent=par, prefix_len=[L - 1])
     assert np.abs(got[:, ~sees] - ref[:, ~sees]).max() <= F32_TOL
+
+
+@pytest.mark.parametrize("n_tree", [1, 15, 16, 17, 63, 64, 65, 100, 128])
+@pytest.mark.parametrize("shape", ["chain", "wide", "mixed"])
+def test_f32_ancestors_and_blocks_at_their_edges(n_tree, shape):
+    """Ancestors across both halves of the node numbers and at every depth, with the tree's blocks of keys falling to every
+    wave (the prefix length decides which), no prefix at all, and lengths below the bound."""
+    rng = np.random.default_rng(n_tree)
+    par = [-1] + [i - 1 if shape == "chain" else max(-1, i // 9 - 1) if shape == "wide" else int(rng.integers(-1, i)) for i in range(1, n_tree)]
+    for D, lens in ((64, [0, 1, 16]), (64, [17, 113, 128]), (40, [129, 250, 66]), (128, [100, 31, 160])):
+        x = {k: rng.standard_normal(s, dtype=np.float32) for k, s in
+             (("q", (3, n_tree, 4, D)), ("k_cache", (3, max(lens) + 3, 2, D)), ("v_cache", (3, max(lens) + 3, 2, D)),
+              ("k_tree", (3, n_tree, 2, D)), ("v_tree", (3, n_tree, 2, D)))}
+        check_attention(x, np.array([par] * 3, dtype=np.int32), lens, "f32", 1e-5)
