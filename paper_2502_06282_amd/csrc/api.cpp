@@ -123,6 +123,8 @@ struct PlanModel {
 };
 
 namespace {
+bool f32_in_parts(long long keys, int head_dim) { return keys > 1024 || keys * head_dim >= 19200; }  // the line: see compute_attn_plan
+
 // A workspace serves every call that is no larger in batch, nodes, heads, head_dim and prefix bound than the one it was
 // sized for.  Partial results alone do not have that order - a smaller call may be cut into more splits, and take more
 // room - so a plan's partial rows stay below a bound that grows with each of those numbers, and the size query answers
@@ -145,7 +147,7 @@ size_t most_part_rows(const jk_attn_desc& d, int max_prefix_len) {  // over all 
   }
   // fp32: a result per range of 1024 keys, or, where workgroups of sixteen rows are fewer than CUs, up to eight of it
   const long long keys = (long long)max_prefix_len + d.n_tree, s = (keys + 1023) / 1024;
-  const long long whole = s > 1 ? units * m * s : 0, divided = keys >= 256 ? least(16 * cus, units * m * least(8 * s, kMaxSplits)) : 0;
+  const long long whole = s > 1 ? units * m * s : 0, divided = f32_in_parts(keys, d.head_dim) ? least(16 * cus, units * m * least(8 * s, kMaxSplits)) : 0;
   return (size_t)most(whole, divided);
 }
 
@@ -342,7 +344,7 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
     // 8.8, 276 8.5 / 8.9).
     const long long wgs = units * ((pl->m_rows + 15) / 16) * s;
     pl->parts = pl->splits;
-    if (s > 1 || keys * d.head_dim >= 19200)
+    if (f32_in_parts(keys, d.head_dim))
       for (int sub = 8; sub > 1; --sub)
         if (wgs * sub <= device_cu_count() && s * sub <= kMaxSplits) {
           pl->parts = pl->splits * sub;
