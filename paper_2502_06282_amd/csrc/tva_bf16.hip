@@ -629,14 +629,16 @@ struct Plan {
   static constexpr int QROWS = kWaveRows * WM;
   static constexpr int STAGE_BYTES = TPR * 2 * G_::TILE_BYTES;  // one round: TPR tiles of K and V
   static constexpr int RING_BYTES = NR * STAGE_BYTES;
-  static constexpr int OBUF_BYTES = (WN - 1) * QROWS * G_::O_LD * 4;  // epilogue: O^T of key columns 1..WN-1
-  static constexpr int PATCH_LD = D * 2 + 16;                         // padded bf16 row of the store patches
-  static constexpr int PATCH_BYTES = kWaveRows * PATCH_LD;            // one owner wave's 32 finished rows
-  static constexpr int EPI_BYTES = OBUF_BYTES + WM * PATCH_BYTES;
-  static constexpr int UNION_BYTES = RING_BYTES > EPI_BYTES ? RING_BYTES : EPI_BYTES;
+  static_assert(WN == 1 || WN == 2, "one key column, or two that share the epilogue");
+  static constexpr int OB = G_::DB / WN, OCOLS = D / WN;  // 32-wide blocks (columns) of its rows that a wave finishes
+  static constexpr int PARK_BYTES = 64 * OB * 64;  // two key columns: what one parks for a wave of the other
+  static constexpr int PATCH_LD = OCOLS * 2 + 16;  // padded row of a wave's store patch: bf16, or half of the columns in fp32
+  static constexpr int PATCH_BYTES = kWaveRows * PATCH_LD;
+  static constexpr int SLOT_BYTES = WN == 2 ? PARK_BYTES : PATCH_BYTES;  // a wave's share of the epilogue's LDS
+  static_assert(PATCH_BYTES <= SLOT_BYTES && NW * SLOT_BYTES <= (WN == 2 ? STAGE_BYTES : RING_BYTES), "the epilogue fits a slot of the ring (one key column: the ring)");
   static constexpr int ML_BYTES = NW * kWaveRows * 8;
   static constexpr int PAGES_BYTES = PAGED ? kMaxPagesPerSplit * 4 : 0;
-  static constexpr int SMEM = UNION_BYTES + ML_BYTES + JK_MAX_TREE * 16 + JK_MAX_TREE * 4 + 16 + PAGES_BYTES;
+  static constexpr int SMEM = RING_BYTES + ML_BYTES + JK_MAX_TREE * 16 + JK_MAX_TREE * 4 + 16 + PAGES_BYTES;
   static constexpr int WGS_PER_CU = 2 * SMEM <= 160 * 1024 && NW <= 4 ? 2 : 1;
   static constexpr int REG_WGS = NW <= 4 ? 2 : 1;  // register budget: at most 256 VGPRs, no detour through AGPRs
   static_assert(SMEM <= 160 * 1024, "LDS budget");
@@ -663,10 +665,9 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
 
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];  // the kernel has no other LDS: offset 0
   unsigned char* ring = smem;
-  float* obuf = reinterpret_cast<float*>(smem);                                   // [WN-1][QROWS][O_LD], after the loop
-  float2* mlbuf = reinterpret_cast<float2*>(smem + P_::UNION_BYTES);              // [WN-1][QROWS]
-  unsigned long long* anc = reinterpret_cast<unsigned long long*>(smem + P_::UNION_BYTES + P_::ML_BYTES);  // [128][2]
-  int* par_s = reinterpret_cast<int*>(smem + P_::UNION_BYTES + P_::ML_BYTES + JK_MAX_TREE * 16);           // [128]
+  float2* mlbuf = reinterpret_cast<float2*>(smem + P_::RING_BYTES);              // [NW][32]
+  unsigned long long* anc = reinterpret_cast<unsigned long long*>(smem + P_::RING_BYTES + P_::ML_BYTES);  // [128][2]
+  int* par_s = reinterpret_cast<int*>(smem + P_::RING_BYTES + P_::ML_BYTES + JK_MAX_TREE * 16);           // [128]
   int* repeat_s = par_s + JK_MAX_TREE;  // set by a wave whose scores left the pipelined pairs' fixed reference frame
   int* pg_s = repeat_s + 4;             // [1024], paged caches only
 
@@ -818,7 +819,9 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
     }
   };
   const unsigned ring_addr = (unsigned)(size_t)LDS_PTR(unsigned char, ring);  // a multiple of 1024
-  const unsigned k_lane = G_::k_lane(lane), v_lane = G_::v_lane(lane);
+  // (A wave of key column 1 takes the blocks of the head dimension second half first: its first accumulators then are the
+  // half that it finishes, and no register is chosen by the wave.)
+  const unsigned k_lane = G_::k_lane(lane), v_lane = G_::v_lane(lane) ^ ((unsigned)(wn * P_::OB) << 6);
   LaneChunks<D, NW> lc;
   auto set_streams = [&]() {
     lane_chunks<D, NW>(lc, wave, lane, ts, p.kc + (PAGED ? 0 : b * p.kc_sb) + (long long)kv * p.kc_sh,
@@ -996,8 +999,9 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
   }
   if (KT == 2 && !general && (left || PairPipe<D>::left_frame(st))) *repeat_s = 1;
   JK_TS(5);
-  __syncthreads();  // every wave is done with the ring before it becomes the epilogue buffer (or is filled again)
-  if (KT != 2 || general || __builtin_amdgcn_readfirstlane(*repeat_s) == 0) break;
+  if (KT != 2) break;
+  __syncthreads();  // every wave is done with the ring before it is filled again
+  if (general || __builtin_amdgcn_readfirstlane(*repeat_s) == 0) break;
   general = true;
 #pragma unroll
   for (int db = 0; db < DB; ++db)
@@ -1010,87 +1014,113 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
     if (r < n_rounds) dma_round<D, NW, TPR, PAGED>(r, ts, lc, ring_addr + r * STAGE_BYTES);
   }
 
-  // ---- epilogue: the waves of key column 0 own the result of their 32 rows.  The other
-  // columns park their O^T and (max, sum) in LDS (the ring is dead by now); the owners fold
-  // them into their own accumulators, register for register (all waves share one layout),
-  // and store straight from that layout: lane (row, g) holds, per 32-wide block db and
-  // quarter q4, the 4 columns 32*db + 8*q4 + 4*g .. +3 of its row.
+  // ---- epilogue.  A wave of a single key column owns the result of its 32 rows.  Two key columns share theirs: column
+  // wn finishes the half of the columns that its first accumulators hold (see v_lane), parks the other half and its
+  // (max, sum) in LDS for the other column's wave of the same rows, and folds what that one parked for it into its own,
+  // register for register (all waves share one layout, so a lane reads what its double wrote: consecutive 16 bytes a
+  // lane, no bank conflict).  They park in the ring slot of the last round but one, which every wave left before the last
+  // round's barrier.  This part is bound by the instructions of a lone wave per SIMD: with column 0 folding and storing
+  // whole rows behind column 1's a layer of a 7B model of 1024 keys took 10.1 us and takes 9.8, eleven sequences of 120
+  // keys (8 heads, six nodes, undivided) 7.5 and 7.1, two of 377 keys in two splits 8.9 and 8.4.
+  // Lane (row, g) holds, per 32-wide block db and quarter q4, the 4 columns 32*db + 8*q4 + 4*g .. +3 of its row.
   // (the lane's indices are worked out afresh, from the execution mask: kept in registers
   // across the tile loop, which has none to spare, they - or the thread id they come from -
   // are spilled to memory and read back here)
+  constexpr int OB = P_::OB, OCOLS = P_::OCOLS;  // 32-wide blocks, and columns, that a wave finishes
   const int lane_e = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
   const int c32_e = lane_e & 31, g_e = lane_e >> 5;
-  const bool row_ok_e = qtile * QROWS + wm * kWaveRows + c32_e < M;
-  const float l_own = half_swap_sum(st.l);
-  const int row = wm * kWaveRows + c32_e;
-  if (wn != 0) {
-    float* orow = obuf + ((size_t)(wn - 1) * QROWS + row) * G_::O_LD;
+  const bool whole = MERGE == 0 && splits == 1;  // the final result, not a split's partial
+  float mx = st.m, lsum = half_swap_sum(st.l);
+  unsigned char* slots = smem + (WN == 2 ? ((n_rounds + NR - 2) % NR) * STAGE_BYTES : 0);
+  unsigned char* patch = slots + wave * P_::SLOT_BYTES;
+  if constexpr (WN == 2) {
+    const int partner = wave ^ WM;  // the same rows' wave of the other column
+    float4* park = reinterpret_cast<float4*>(slots + partner * P_::SLOT_BYTES) + lane_e;
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+    for (int db = 0; db < OB; ++db)
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
-        float4 v = make_float4(st.o[db][4 * q4], st.o[db][4 * q4 + 1], st.o[db][4 * q4 + 2], st.o[db][4 * q4 + 3]);
-        *reinterpret_cast<float4*>(orow + 32 * db + 8 * q4 + 4 * g_e) = v;
+        const floatx16& o = st.o[OB + db];
+        park[(db * 4 + q4) * 64] = make_float4(o[4 * q4], o[4 * q4 + 1], o[4 * q4 + 2], o[4 * q4 + 3]);
       }
-    if (g_e == 0) mlbuf[(wn - 1) * QROWS + row] = make_float2(st.m, l_own);
+    mlbuf[wave * kWaveRows + c32_e] = make_float2(mx, lsum);  // (both halves of the wave hold the row's)
+    __syncthreads();
+    const float2 ml = mlbuf[partner * kWaveRows + c32_e];
+    const float m_all = fmaxf(mx, ml.x);
+    const float m_use = (m_all == -INFINITY) ? 0.f : m_all;
+    float w0 = fast_exp2(mx - m_use), w1 = fast_exp2(ml.x - m_use);
+    lsum = fmaf(ml.y, w1, lsum * w0);
+    mx = m_all;
+    if (whole) {  // lsum > 0: every row sees at least its own tree key
+      w0 /= lsum;
+      w1 /= lsum;
+    }
+    const float4* parked = reinterpret_cast<const float4*>(patch) + lane_e;
+#pragma unroll
+    for (int db = 0; db < OB; ++db)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const float4 v = parked[(db * 4 + q4) * 64];
+        floatx16& o = st.o[db];
+        o[4 * q4] = fmaf(v.x, w1, o[4 * q4] * w0);
+        o[4 * q4 + 1] = fmaf(v.y, w1, o[4 * q4 + 1] * w0);
+        o[4 * q4 + 2] = fmaf(v.z, w1, o[4 * q4 + 2] * w0);
+        o[4 * q4 + 3] = fmaf(v.w, w1, o[4 * q4 + 3] * w0);
+      }
+  } else if (whole) {
+    const float mul = 1.f / lsum;
+#pragma unroll
+    for (int db = 0; db < OB; ++db)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) st.o[db][i] *= mul;
   }
-  if (WN > 1) __syncthreads();
   JK_TS(6);
-  if (wn == 0) {
-    float mx = st.m;
+  // ---- store: the final result (no splits) or the split's partial, in fp32 or in bf16 (AttnPlan::fine; the running max and
+  // sum are always fp32).
+  // (a lone wave per SIMD issues an instruction every five to eight cycles: this part of the
+  // kernel is bound by its instruction count, hence the uniform branches around whole loops
+  // rather than conditions inside them)
+  const long long prow0 = ((long long)unit_id * splits + split) * p.m_pad + qtile * QROWS + wm * kWaveRows;
+  const int rows_valid = M - (qtile * QROWS + wm * kWaveRows);  // rows of this wave that exist (32 or more: all)
+  if (!whole && wn == 0 && c32_e < rows_valid && g_e == 0) {
+    if (p.through & 2) dev::store_through(p.part_ml + prow0 + c32_e, dev::store_u32x2{__float_as_uint(mx), __float_as_uint(lsum)});
+    else p.part_ml[prow0 + c32_e] = make_float2(mx, lsum);
+  }
+  const bool thr = MERGE == 0 && (p.through & 1);
+  constexpr int LD = P_::PATCH_LD, LPR = OCOLS / 8, RPI = 64 / LPR;  // bytes a patch row, lanes a row, rows a store
+  const int chunk = lane_e % LPR, rsub = lane_e / LPR;
+  const unsigned char* src0 = patch + rsub * LD + chunk * 16;
+  if (FINE || (MERGE == 0 && !whole && (p.through & 4))) {
+    if constexpr (WN == 2) {
+      // a block of 32 columns at a time by way of the patch (see below): 128-byte rows, their 16-byte chunks swizzled by the
+      // row.  (Straight from the accumulators, 32 bytes into each of 32 rows a store, four sequences of 400 keys, 8B, took 12.8
+      // us instead of 12.2.)
+      typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+      const unsigned prow = (unsigned)(size_t)LDS_PTR(unsigned char, patch) + c32_e * 128 + ((g_e ^ (c32_e & 7)) << 4);
+      const int r8 = lane_e / 8, c8 = lane_e % 8;
+      const unsigned char* from = patch + r8 * 128 + ((c8 ^ r8) << 4);
+      float* dst0 = reinterpret_cast<float*>(p.part_o) + (prow0 + r8) * D + wn * OCOLS + c8 * 4;
 #pragma unroll
-    for (int w = 1; w < WN; ++w) mx = fmaxf(mx, mlbuf[(w - 1) * QROWS + row].x);
-    const float mx_use = (mx == -INFINITY) ? 0.f : mx;
-    float lsum = l_own;
-    if (WN > 1) {
-      const float w0 = fast_exp2(st.m - mx_use);
-      lsum *= w0;
+      for (int db = 0; db < OB; ++db) {
 #pragma unroll
-      for (int db = 0; db < DB; ++db)
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const floatx16& o = st.o[db];
+          *(lds_u32x4*)(size_t)(prow ^ (q4 << 5)) = u32x4{__float_as_uint(o[4 * q4]), __float_as_uint(o[4 * q4 + 1]),
+                                                          __float_as_uint(o[4 * q4 + 2]), __float_as_uint(o[4 * q4 + 3])};
+        }
 #pragma unroll
-        for (int i = 0; i < 16; ++i) st.o[db][i] *= w0;
-#pragma unroll
-      for (int w = 1; w < WN; ++w) {
-        const float2 ml = mlbuf[(w - 1) * QROWS + row];
-        const float wgt = fast_exp2(ml.x - mx_use);
-        lsum = fmaf(ml.y, wgt, lsum);
-        const float* orow = obuf + ((size_t)(w - 1) * QROWS + row) * G_::O_LD;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-          for (int q4 = 0; q4 < 4; ++q4) {
-            const float4 v = *reinterpret_cast<const float4*>(orow + 32 * db + 8 * q4 + 4 * g_e);
-            st.o[db][4 * q4] = fmaf(v.x, wgt, st.o[db][4 * q4]);
-            st.o[db][4 * q4 + 1] = fmaf(v.y, wgt, st.o[db][4 * q4 + 1]);
-            st.o[db][4 * q4 + 2] = fmaf(v.z, wgt, st.o[db][4 * q4 + 2]);
-            st.o[db][4 * q4 + 3] = fmaf(v.w, wgt, st.o[db][4 * q4 + 3]);
+        for (int k = 0; k < kWaveRows / 8; ++k) {
+          const u32x4 v = *reinterpret_cast<const u32x4*>(from + k * 1024);
+          if (k * 8 + r8 < rows_valid) {
+            if (thr) dev::store_through(dst0 + k * 8 * D + 32 * db, v);
+            else *reinterpret_cast<u32x4*>(dst0 + k * 8 * D + 32 * db) = v;
           }
+        }
       }
-    }
-    // ---- store.  The accumulator layout gives a lane 4 columns here and 4 there of one row:
-    // stored as it is, every instruction would touch 32 rows with 16 bytes each.  So the wave
-    // first lays its 32 finished rows out in LDS as bf16 (a private patch behind the parked
-    // columns) and reads them back row-wise: 16 lanes x 16 bytes per row, whole 128-byte lines
-    // per store.  Holds the final result (no splits) or the split's partial, in fp32 or in bf16
-    // (AttnPlan::fine; the running max and sum are always fp32).
-    const bool whole = MERGE == 0 && splits == 1;
-    const float mul = whole ? 1.f / lsum : 1.f;  // lsum > 0: every row sees at least its own tree key
-    const long long prow0 = ((long long)unit_id * splits + split) * p.m_pad + qtile * QROWS + wm * kWaveRows;
-    if (!whole && row_ok_e && g_e == 0) {
-      if (p.through & 2) dev::store_through(p.part_ml + prow0 + c32_e, dev::store_u32x2{__float_as_uint(mx), __float_as_uint(lsum)});
-      else p.part_ml[prow0 + c32_e] = make_float2(mx, lsum);
-    }
-    unsigned char* patch = smem + P_::OBUF_BYTES + wm * P_::PATCH_BYTES;
-    unsigned char* prow = patch + c32_e * P_::PATCH_LD;
-    constexpr int CPR = G_::CPR;             // 16-byte chunks per row
-    constexpr int RPI = 64 / CPR;            // rows per store instruction
-    const int chunk = lane_e % CPR, rsub = lane_e / CPR;
-    const int rows_valid = M - (qtile * QROWS + wm * kWaveRows);  // rows of this wave that exist (32 or more: all)
-    if (FINE || (MERGE == 0 && !whole && (p.through & 4))) {
-      // the split's partial in fp32: half of the columns at a time, as many bytes a row as all of them in bf16
+    } else {
+      // half of the columns at a time by way of the patch (see below), as many bytes a row as all of them in bf16
+      unsigned char* prow = patch + c32_e * LD + g_e * 16;
       unsigned char* dst0 = reinterpret_cast<unsigned char*>(p.part_o) + ((prow0 + rsub) * D + chunk * 4) * 4;
-      const unsigned char* src0 = patch + rsub * P_::PATCH_LD + chunk * 16;
-      const bool thr = p.through & 1;
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
 #pragma unroll
@@ -1098,71 +1128,64 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
 #pragma unroll
           for (int q4 = 0; q4 < 4; ++q4) {
             const floatx16& o = st.o[h * (DB / 2) + db];
-            *reinterpret_cast<float4*>(prow + (32 * db + 8 * q4 + 4 * g_e) * 4) = make_float4(o[4 * q4], o[4 * q4 + 1], o[4 * q4 + 2], o[4 * q4 + 3]);
+            *reinterpret_cast<float4*>(prow + (32 * db + 8 * q4) * 4) = make_float4(o[4 * q4], o[4 * q4 + 1], o[4 * q4 + 2], o[4 * q4 + 3]);
           }
 #pragma unroll
         for (int k = 0; k < kWaveRows / RPI; ++k) {
-          const u32x4 v = *reinterpret_cast<const u32x4*>(src0 + k * RPI * P_::PATCH_LD);
+          const u32x4 v = *reinterpret_cast<const u32x4*>(src0 + k * RPI * LD);
           unsigned char* dst = dst0 + k * RPI * D * 4 + h * D * 2;
           if (k * RPI + rsub < rows_valid) {
-            if (MERGE == 0 && thr) dev::store_through(dst, v);
+            if (thr) dev::store_through(dst, v);
             else *reinterpret_cast<u32x4*>(dst) = v;
           }
         }
       }
-    } else {
-    {
-      // (a lone wave per SIMD issues an instruction every five to eight cycles: this part of the
-      // kernel is bound by its instruction count, hence the uniform branches around whole loops
-      // rather than conditions inside them)
-      auto to_patch = [&](auto scaled) {
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-          for (int q4 = 0; q4 < 4; ++q4) {
-            bf16x2 lo, hi;
-            lo[0] = (__bf16)(decltype(scaled)::value ? st.o[db][4 * q4] * mul : st.o[db][4 * q4]);
-            lo[1] = (__bf16)(decltype(scaled)::value ? st.o[db][4 * q4 + 1] * mul : st.o[db][4 * q4 + 1]);
-            hi[0] = (__bf16)(decltype(scaled)::value ? st.o[db][4 * q4 + 2] * mul : st.o[db][4 * q4 + 2]);
-            hi[1] = (__bf16)(decltype(scaled)::value ? st.o[db][4 * q4 + 3] * mul : st.o[db][4 * q4 + 3]);
-            uint2 pk;
-            pk.x = __builtin_bit_cast(unsigned int, lo);
-            pk.y = __builtin_bit_cast(unsigned int, hi);
-            *reinterpret_cast<uint2*>(prow + (32 * db + 8 * q4 + 4 * g_e) * 2) = pk;
-          }
-      };
-      if (whole) to_patch(std::true_type{});
-      else to_patch(std::false_type{});
     }
-    // (same wave wrote and reads: LDS operations of a wave complete in order)
+  } else {
+    // bf16: the accumulator layout gives a lane 4 columns here and 4 there of one row, 8 bytes each.  So the wave
+    // first lays its 32 rows out in LDS (where its partner's share was parked: LDS operations of a wave complete in
+    // order) and reads them back row-wise, and a store covers whole lines of a few rows.
+    unsigned char* prow = patch + c32_e * LD + g_e * 8;
+#pragma unroll
+    for (int db = 0; db < OB; ++db)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        bf16x2 lo, hi;
+        lo[0] = (__bf16)st.o[db][4 * q4];
+        lo[1] = (__bf16)st.o[db][4 * q4 + 1];
+        hi[0] = (__bf16)st.o[db][4 * q4 + 2];
+        hi[1] = (__bf16)st.o[db][4 * q4 + 3];
+        uint2 pk;
+        pk.x = __builtin_bit_cast(unsigned int, lo);
+        pk.y = __builtin_bit_cast(unsigned int, hi);
+        *reinterpret_cast<uint2*>(prow + (32 * db + 8 * q4) * 2) = pk;
+      }
     if (whole) {
 #pragma unroll
       for (int k = 0; k < kWaveRows / RPI; ++k) {
         const int rr = k * RPI + rsub;                               // row of the wave
         const int m = qtile * QROWS + wm * kWaveRows + rr;           // query row
-        const u32x4 v = *reinterpret_cast<const u32x4*>(patch + rr * P_::PATCH_LD + chunk * 16);
+        const u32x4 v = *reinterpret_cast<const u32x4*>(src0 + k * RPI * LD);
         if (rr < rows_valid) {
           const int node = div_mg(m, p.mg_g);
-          uint16_t* dst = p.out + b * p.o_sb + node * p.o_st + (long long)(kv * G + (m - node * G)) * p.o_sh;
-          if (p.through & 1) dev::store_through(dst + chunk * 8, v);
-          else *reinterpret_cast<u32x4*>(dst + chunk * 8) = v;
+          uint16_t* dst = p.out + b * p.o_sb + node * p.o_st + (long long)(kv * G + (m - node * G)) * p.o_sh + wn * OCOLS + chunk * 8;
+          if (thr) dev::store_through(dst, v);
+          else *reinterpret_cast<u32x4*>(dst) = v;
         }
       }
     } else {
       // partial rows are D elements apart: one address, constant steps
-      unsigned char* dst0 = reinterpret_cast<unsigned char*>(p.part_o) + ((prow0 + rsub) * D + chunk * 8) * 2;
-      const unsigned char* src0 = patch + rsub * P_::PATCH_LD + chunk * 16;
+      unsigned char* dst0 = reinterpret_cast<unsigned char*>(p.part_o) + ((prow0 + rsub) * D + wn * OCOLS + chunk * 8) * 2;
       auto store_rows = [&](auto through, auto guarded) {
 #pragma unroll
         for (int k = 0; k < kWaveRows / RPI; ++k) {
-          const u32x4 v = *reinterpret_cast<const u32x4*>(src0 + k * RPI * P_::PATCH_LD);
+          const u32x4 v = *reinterpret_cast<const u32x4*>(src0 + k * RPI * LD);
           if (!decltype(guarded)::value || k * RPI + rsub < rows_valid) {
             if (decltype(through)::value) dev::store_through(dst0 + k * RPI * D * 2, v);
             else *reinterpret_cast<u32x4*>(dst0 + k * RPI * D * 2) = v;
           }
         }
       };
-      const bool thr = p.through & 1;
       if (rows_valid >= kWaveRows) {
         if (thr) store_rows(std::true_type{}, std::false_type{});
         else store_rows(std::false_type{}, std::false_type{});
@@ -1170,7 +1193,6 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
         if (thr) store_rows(std::true_type{}, std::true_type{});
         else store_rows(std::false_type{}, std::true_type{});
       }
-    }
     }
   }
   if constexpr (MERGE > 0) {

@@ -93,7 +93,6 @@ struct Geo {
   static constexpr int CPR = D / 8;               // 16-byte chunks per row
   static constexpr int DK = D / 16;               // k-steps of Q.K^T
   static constexpr int DB = D / 32;               // 32-wide d blocks of the output
-  static constexpr int O_LD = D + 4;              // padded row of the epilogue buffer (floats)
   static constexpr int NB = TILE_BYTES / 1024;    // 1 KB transfers per tile and tensor
   __device__ static __forceinline__ int kswz(int row) { return (row / (16 / CPR)) % CPR; }
   __device__ static __forceinline__ int vswz(int row) { return (row / (4 / DB)) % DB; }

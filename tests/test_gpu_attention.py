@@ -813,3 +813,19 @@ def test_f32_ancestors_and_blocks_at_their_edges(n_tree, shape):
              (("q", (3, n_tree, 4, D)), ("k_cache", (3, max(lens) + 3, 2, D)), ("v_cache", (3, max(lens) + 3, 2, D)),
               ("k_tree", (3, n_tree, 2, D)), ("v_tree", (3, n_tree, 2, D)))}
         check_attention(x, np.array([par] * 3, dtype=np.int32), lens, "f32", 1e-5)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("deep,splits", [(0, 1), (1, 1), (0, 2), (0, 5)])
+def test_bf16_two_key_columns_share_their_results(D, deep, splits):
+    """Each of the two key columns finishes half of the head dimension, by way of the ring slot of the last round but one:
+    splits of no round, of one to five (a column of the last may have no tile), rows up to, at and past a wave's and a
+    workgroup's, results and partials in bf16 and fp32, merged in the kernel and by the merge kernel."""
+    tune("attn_wm", 2); tune("attn_wn", 2); tune("attn_deep", deep); tune("attn_splits", splits)
+    for T, G, L in ((1, 1, 0), (5, 1, 27), (31, 1, 33), (8, 4, 64), (33, 1, 95), (16, 4, 130), (13, 5, 160), (43, 3, 290)):
+        cfg = _cfg("c3_llama3_8b", batch=2, n_q_heads=2 * G, n_kv_heads=2, head_dim=D, n_tree=T, prefix_len=max(L, 1))
+        par = np.array([[max(-1, (i - 1) // 2) for i in range(T)]] * 2, dtype=np.int32)
+        x = {k: round_to_bf16(v) for k, v in attention_inputs(cfg, seed=L, scale_mult=np.sqrt(float(D))).items()}
+        for fused in (1, 0):
+            tune("attn_fused", fused)
+            check_attention(x, par, [L, L // 2], "bf16", BF16_TOL)
