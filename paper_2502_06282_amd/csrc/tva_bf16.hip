@@ -837,27 +837,38 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
   // the same assumption as with a contiguous cache (entries past a sequence's pages may hold anything; if the
   // length turns out shorter, the list is made again).  An id outside the pool is reported once the list is final.
   bool bad_page = false;
-  auto fill_pages = [&]() {
-    bad_page = false;
+  int n_pg = 0, first_id = 0;  // pages of the list; this thread's first entry
+  auto ask_pages = [&]() {
     const int te = min(ts.n_ptiles, ts.t_begin + n_rounds * TPR);
+    n_pg = 0;
     if (te > ts.t_begin) {
       ts.pg_first = div_mg(ts.t_begin, p.mg_tpp);
-      const int n_pg = div_mg(te - 1, p.mg_tpp) - ts.pg_first + 1;  // <= kMaxPagesPerSplit by the host's plan
-      for (int i = tid; i < n_pg && i < kMaxPagesPerSplit; i += THREADS) {
-        const int pi = ts.pg_first + i;
-        const int id = pi < p.max_blocks ? p.block_table[(long long)b * p.max_blocks + pi] : 0;
-        bad_page = bad_page || id < 0 || id >= p.n_pages;
-        pg_s[i] = id < 0 ? 0 : (id >= p.n_pages ? p.n_pages - 1 : id);
-      }
+      n_pg = div_mg(te - 1, p.mg_tpp) - ts.pg_first + 1;  // <= kMaxPagesPerSplit by the host's plan
+    }
+    first_id = tid < n_pg && ts.pg_first + tid < p.max_blocks ? p.block_table[(long long)b * p.max_blocks + ts.pg_first + tid] : 0;
+  };
+  auto fill_pages = [&]() {
+    bad_page = false;
+    for (int i = tid; i < n_pg && i < kMaxPagesPerSplit; i += THREADS) {
+      const int pi = ts.pg_first + i;
+      const int id = i == tid ? first_id : (pi < p.max_blocks ? p.block_table[(long long)b * p.max_blocks + pi] : 0);
+      bad_page = bad_page || id < 0 || id >= p.n_pages;
+      pg_s[i] = id < 0 ? 0 : (id >= p.n_pages ? p.n_pages - 1 : id);
     }
     __syncthreads();
   };
-  if (PAGED) fill_pages();
-  const bool spec_any = n_rounds > 0 && (ts.t_begin + TPR) * kTileKeys <= p.max_prefix;  // same for every wave
+  if (PAGED) ask_pages();
+  // (A paged batch asks for nothing on that assumption but the page ids, which take as long as the lengths: lengths are
+  // seldom all equal, and the rounds in vain had to land before the right ones took their places.  us, before / after:
+  // 6 sequences of up to 437 keys, 14 nodes, 32 heads 11.7 / 10.9; 24 of up to 36 keys, 12 nodes, 40 heads 18.0 / 15.9; 8 of up
+  // to 4933 keys 30.8 / 29.4; equal lengths the same within 1 %.  Contiguous caches lose 1 - 4 % by the wait where lengths are equal.)
+  const bool at_once = !PAGED || !ranked;
+  if (PAGED && at_once) fill_pages();
+  const bool spec_any = at_once && n_rounds > 0 && (ts.t_begin + TPR) * kTileKeys <= p.max_prefix;  // same for every wave
   int n_spec = 0;  // rounds already issued, all of them full prefix tiles under the assumption
 #pragma unroll
   for (int r = 0; r < NR - 1; ++r)
-    if (n_spec == r && r < n_rounds && (ts.t_begin + (r + 1) * TPR) * kTileKeys <= p.max_prefix) {
+    if (at_once && n_spec == r && r < n_rounds && (ts.t_begin + (r + 1) * TPR) * kTileKeys <= p.max_prefix) {
       dma_round<D, NW, TPR, PAGED>(r, ts, lc, ring_addr + r * STAGE_BYTES);
       n_spec = r + 1;
     }
@@ -869,12 +880,7 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
     const int len = L_raw < 0 ? 0 : (L_raw > p.max_prefix ? p.max_prefix : L_raw);
     L = p.max_prefix;
     if (!__all(len == p.max_prefix)) {
-      int my_rank = 0;  // of sequence `lane`: longer ones, and equal ones in front of it
-      for (int i = 0; i < p.B; ++i) {
-        const int other = __builtin_amdgcn_readlane(len, i);
-        my_rank += (int)(other > len) | ((int)(other == len) & (int)(i < lane));
-      }
-      const int mine = __ffsll((long long)__ballot(lane < p.B && my_rank == rank)) - 1;
+      const int mine = sequence_of_rank(len, p.B, rank, lane);
       moved = mine != b;
       b = mine;
       L = __builtin_amdgcn_readlane(len, mine);
@@ -896,8 +902,13 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
     n_spec = 0;
     set_range(L);
     n_rounds = (ts.t_end - ts.t_begin + TPR - 1) / TPR;
-    if (PAGED) fill_pages();
+    if (PAGED) ask_pages();
+    if (PAGED && at_once) {
+      __syncthreads();  // (nobody reads the first list any more)
+      fill_pages();
+    }
   }
+  if (PAGED && !at_once) fill_pages();
   const int unit_id = b * p.Hkv + kv;
   const bool has_tree = ts.t_end > ts.n_ptiles;
   if (PAGED && bad_page) __hip_atomic_fetch_or(p.err, kDevErrBadPage, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

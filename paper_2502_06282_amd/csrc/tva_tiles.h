@@ -207,6 +207,17 @@ __device__ __forceinline__ const uint16_t* prefix_tile_base(const TileSrc& ts, c
   return cache + (long long)page * ts.page_stride + (long long)(t - pi * ts.tpp) * kTileKeys * ts.kc_sl;
 }
 
+// Lane i < batch (at most 64) brings sequence i's length (at most 2^24): the sequence that `rank` others go in front of,
+// longer ones and equal ones of a lower number.
+__device__ __forceinline__ int sequence_of_rank(int len, int batch, int rank, int lane) {
+  const int key = lane < batch ? (len << 6) | (63 - lane) : -1;  // (all different: one comparison each)
+  int in_front = 0;
+  for (int i = 0; i < batch; i += 4)  // (what lies past the batch's end goes in front of nobody)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) in_front += (int)(__builtin_amdgcn_readlane(key, i + k) > key);
+  return __ffsll((long long)__ballot(lane < batch && in_front == rank)) - 1;
+}
+
 // Issue the transfers of round r (TPR tiles, K and V) into ring slot `slot` (byte address).
 template <int D, int NW, int TPR, bool PAGED>
 __device__ __forceinline__ void dma_round(int r, const TileSrc& ts, const LaneChunks<D, NW>& lc, unsigned slot) {

@@ -24,6 +24,7 @@
 // in pages, 8 KV heads, 240 rows 70 -> 59 us; 29 sequences of 10023 keys, 46 nodes, D = 64 255 -> 178 us.
 #include <type_traits>
 
+#include "jk_wave.h"
 #include "tva_tiles.h"
 #include "tva_wide_order.h"
 
@@ -153,26 +154,25 @@ struct Deal {
   int first, pieces;
 };
 __device__ __forceinline__ Deal deal_pieces(int tiles, int batch, int splits, int lane) {
+  // (Nothing else runs yet, and a call waits for these instructions: four sequences at a time, which those past the batch's
+  // end, without tiles, do not change.)
   const int places = batch * splits;
-  int total = 0, longest = 0;
-  for (int i = 0; i < batch; ++i) {
-    const int n = __builtin_amdgcn_readlane(tiles, i);
-    total += n;
-    longest = n > longest ? n : longest;
-  }
-  const int hi = (longest + splits - 1) / splits;
-  const int lo = min(max((int)((float)total / (float)places), 1), hi);
+  const float total = dev::wave_sum((float)tiles);
+  const int longest = __builtin_amdgcn_readfirstlane((int)dev::wave_max((float)tiles));  // (below 2^20: exact)
+  const int hi = divided(longest + splits - 1, splits);
+  const int lo = min(max((int)(total * __builtin_amdgcn_rcpf((float)places)), 1), hi);
   const int len = lane == 63 ? hi : lo + (int)((float)(hi - lo) * (float)lane * (1.f / 63.f));
   int count = 0;
-  for (int i = 0; i < batch; ++i) count += divided(__builtin_amdgcn_readlane(tiles, i) + len - 1, len);
+  for (int i = 0; i < batch; i += 4)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) count += divided(__builtin_amdgcn_readlane(tiles, i + k) + len - 1, len);
   const int best = __builtin_amdgcn_readlane(len, __ffsll((long long)__ballot(count <= places)) - 1);
   Deal d;
   d.pieces = tiles > 0 ? divided(tiles + best - 1, best) : 0;
   d.first = 0;
-  for (int i = 0; i < batch; ++i) {
-    const int n = __builtin_amdgcn_readlane(d.pieces, i);
-    d.first += i < lane ? n : 0;
-  }
+  for (int i = 0; i < batch; i += 4)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) d.first += i + k < lane ? __builtin_amdgcn_readlane(d.pieces, i + k) : 0;
   return d;
 }
 
@@ -232,12 +232,7 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
       pieces = __builtin_amdgcn_readlane(d.pieces, b);
       if (split >= pieces) return;  // (fewer pieces than places)
     } else {
-      int my_rank = 0;  // of sequence `lane`: longer ones, and equal ones in front of it
-      for (int i = 0; i < p.B; ++i) {
-        const int other = __builtin_amdgcn_readlane(len, i);
-        my_rank += (int)(other > len) | ((int)(other == len) & (int)(i < lane));
-      }
-      b = __ffsll((long long)__ballot(lane < p.B && my_rank == order)) - 1;
+      b = sequence_of_rank(len, p.B, order, lane);
     }
     L = __builtin_amdgcn_readlane(len, b);
     place0 = (order - split) * p.Hkv + kv;
@@ -280,22 +275,31 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
   set_range(L);
   int n = ts.t_end - ts.t_begin;
   bool bad_page = false;
-  auto fill_pages = [&]() {  // (see tva_bf16.hip)
-    bad_page = false;
+  int n_pg = 0, first_id;  // pages of the list; this thread's first entry
+  const int* table = p.block_table + (long long)b * p.max_blocks;
+  auto ask_pages = [&]() {  // (see tva_bf16.hip)
     const int te = min(ts.n_ptiles, ts.t_end);
+    n_pg = 0;
     if (te > ts.t_begin) {
       ts.pg_first = div_mg(ts.t_begin, p.mg_tpp);
-      const int n_pg = div_mg(te - 1, p.mg_tpp) - ts.pg_first + 1;  // <= kMaxPagesPerSplit by the host's plan
-      for (int i = tid; i < n_pg && i < kMaxPagesPerSplit; i += kWideThreads) {
-        const int pi = ts.pg_first + i;
-        const int id = pi < p.max_blocks ? p.block_table[(long long)b * p.max_blocks + pi] : 0;
-        bad_page = bad_page || id < 0 || id >= p.n_pages;
-        pg_s[i] = id < 0 ? 0 : (id >= p.n_pages ? p.n_pages - 1 : id);
-      }
+      n_pg = div_mg(te - 1, p.mg_tpp) - ts.pg_first + 1;  // <= kMaxPagesPerSplit by the host's plan
+    }
+    // (a load by hand in every lane: the compiler may not move its result before it has been waited for)
+    load_by_hand(first_id, tid < n_pg && ts.pg_first + tid < p.max_blocks ? table + ts.pg_first + tid : p.prefix_len);
+  };
+  auto fill_pages = [&]() {  // (the ids have been waited for)
+    asm volatile("" : "+v"(first_id));
+    bad_page = false;
+    for (int i = tid; i < n_pg && i < kMaxPagesPerSplit; i += kWideThreads) {
+      const int pi = ts.pg_first + i;
+      const int id = pi >= p.max_blocks ? 0 : (i == tid ? first_id : table[pi]);
+      bad_page = bad_page || id < 0 || id >= p.n_pages;
+      pg_s[i] = id < 0 ? 0 : (id >= p.n_pages ? p.n_pages - 1 : id);
     }
     __syncthreads();
   };
-  if (PAGED) fill_pages();
+  // (the query rows come while the page ids do: behind them, and the transfers, they took 4.9 us of a call's first 10.8)
+  if (PAGED) ask_pages();
   const int row0 = qtile * QROWS + wave * kWideRows;  // the wave's first query row
   u32x4 q_raw[kBlocks][DK];
   int parent_lo, parent_hi;  // of nodes lane and lane + 64
@@ -308,6 +312,10 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
   }
   load_by_hand(parent_lo, p.parent + (long long)b * T + min(lane, T - 1));
   load_by_hand(parent_hi, p.parent + (long long)b * T + min(lane + 64, T - 1));
+  if (PAGED) {
+    dev::wait_vm<ROW_LOADS>();
+    fill_pages();
+  }
 
   auto transfer = [&](int i) { dma_round<D, kWideWaves, 1, PAGED>(i, ts, lc, ring_addr + i % NR * TILE_BYTES); };
   const float inv_tpp = PAGED ? __builtin_amdgcn_rcpf((float)ts.tpp) : 0.f;
@@ -337,7 +345,11 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
       __syncthreads();
       set_range(L);
       n = ts.t_end - ts.t_begin;
-      if (PAGED) fill_pages();
+      if (PAGED) {
+        ask_pages();
+        dev::wait_vm<0>();
+        fill_pages();
+      }
       first_transfers();
     }
   }
@@ -596,18 +608,20 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
     answer_s = repeat_s + (answer_s == repeat_s + 1 ? 2 : 1);
     if (tid == 0) {
       unsigned* word = word_of(m);
-      is_first = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u;
+      unsigned was = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      is_first = was == 0u;
       int at = -1;
       if (!is_first) {  // (the other workgroup has come: it has nothing left to do but its stores)
         unsigned polls = 0;
         for (;;) {
-          at = tva::others_results(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), false);
+          at = tva::others_results(was, false);  // (usually in what the addition found: no trip more)
           if (at >= 0) break;
           if (++polls > p.spin_limit) {
             __hip_atomic_fetch_or(p.err, kDevErrMergeWait, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             break;
           }
           __builtin_amdgcn_s_sleep(1);
+          was = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
       }
       *answer_s = at;

@@ -49,6 +49,30 @@ def test_paged_attention_matches_oracle_and_contiguous(monkeypatch, wm, wn, page
         assert torch.equal(got, cont)          # same arithmetic in the same order, only the addresses differ
 
 
+@pytest.mark.parametrize("wm,wn", [(2, 2), (4, 1), (8, 1)], ids=["2x2", "4x1", "8x1"])
+@pytest.mark.parametrize("plen", [(9001, 8300), (9001, 9001), (33, 9001)], ids=["ragged", "equal", "swapped"])
+def test_paged_batch_with_more_pages_than_threads(wm, wn, plen):
+    """A batch's page ids are asked for before its lengths are there, a thread's first one at once and what lies past 256 of
+    them in turn; lengths that differ have the list made again.  Bitwise equal to the contiguous call."""
+    tune("attn_wm", str(wm))
+    tune("attn_wn", str(wn))
+    tune("attn_splits", "1")
+    g = torch.Generator(device="cuda").manual_seed(sum(plen))
+    B, T, H, Hkv, D, L, page = 2, 40, 32, 8, 128, max(plen), 32
+    par = torch.from_numpy(np.stack([tree_for_config(CONFIGS["c3_llama3_8b"].with_(n_tree=T), seed=b)[0] for b in range(B)])).cuda()
+    blocks = -(-L // page)
+    rand = lambda *s: torch.randn(s, device="cuda", generator=g).to(BF)
+    kp, vp = rand(B * blocks + 5, page, Hkv, D), rand(B * blocks + 5, page, Hkv, D)
+    table = torch.randperm(B * blocks + 5, device="cuda", generator=g)[:B * blocks].reshape(B, blocks).to(torch.int32).contiguous()
+    kc, vc = (x[table.long()].reshape(B, blocks * page, Hkv, D)[:, :L].contiguous() for x in (kp, vp))
+    q, kt, vt = rand(B, T, H, D), rand(B, T, Hkv, D), rand(B, T, Hkv, D)
+    pl = torch.tensor(plen, dtype=torch.int32, device="cuda")
+    got = jk.tree_verify_attention_paged(q, kp, vp, table, kt, vt, par, pl, max_prefix_len=L)
+    cont = jk.tree_verify_attention(q, kc, vc, kt, vt, par, pl, max_prefix_len=L)
+    torch.cuda.synchronize()
+    assert torch.isfinite(got.float()).all() and torch.equal(got, cont)
+
+
 def test_paged_attention_repeats_a_split_that_leaves_the_fixed_frame(monkeypatch):
     """A late key far above everything before it for one query row: the two-tile fast path of the 4x1
     arrangement gives up and the workgroup streams its split again on the general path, through the page
