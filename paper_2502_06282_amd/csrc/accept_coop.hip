@@ -15,25 +15,27 @@
 // W partials once all tags have appeared.  All workgroups reduce the same values
 // in the same order, so they take identical decisions.
 //
-// What bounds it: the chain of exchanges, 1.5 - 2 us each through memory (a store that every
-// XCD can see, then a poll that sees it), not the bytes.  So the walk makes as few as it can and
-// hides its other work behind them:
+// What bounds it: the chain of exchanges, each a trip through memory (a store that every XCD can see, then a poll that
+// sees it: 0.8 us) and, with as much time again, the instructions between one and the next, which a lone wave per SIMD
+// issues every five to eight cycles.  So the walk makes few exchanges and keeps long chains out of their way:
 //   - an exchange carries, beside what it is needed for, the statistics of the row that comes
 //     next if the next candidate is accepted (worked out while the first part is on its way),
 //     so that an accepted candidate behind a rejection or behind the start costs no exchange;
 //   - the residual's owner of the next candidate's token publishes its value with the residual
 //     mass: the test needs nothing else;
 //   - the final draw takes the slices' sums from the last exchange;
-//   - the draft and logits slices of the next candidate and of its first child are asked for
-//     before the exchange in front of them.
-// Reductions across a wave are DPP moves (a shuffle through LDS takes several times as long), one
-// wave polls and reduces for the workgroup.  Measured (MI355X, us per call, twelve draws of the inputs, the same ones for
-// both, repeats within 0.7 %): one 60-node tree over a 128K vocabulary 18.1 -> 15.6 in the mean (1.13 to 1.20 times as fast; a
-// draw takes 11.8 to 21.7, by its number of exchanges), eight 100-node trees over a 32K vocabulary 30.9 -> 24.4 (1.14 to
-// 1.35 times; 17.8 to 29.6), by asking for the words of an exchange together (a poll used to be three or four trips to memory
-// in a row) and by their layout.  (Tried: a tree's
-// workgroups on one XCD, exchanges through its L2: no faster than that, and one XCD's share of the memory bandwidth
-// is too little for large vocabularies: one tree over 128K 25 - 31 us.)
+//   - references of exponentials are powers of two (see Reference): no exponential between a wait and what it waits for;
+//   - nodes are looked up in a table (see Node);
+//   - a thread at the end of the vocabulary reads entries that are not its own instead of none (see Part): in a branch
+//     the compiler waited for every load under way, and every exchange waits for that workgroup.
+// Reductions across a wave are DPP moves (a shuffle through LDS takes several times as long), one wave polls and reduces for
+// the workgroup.  Measured (MI355X, us per call, the mean of six draws, before the last three of these and now; a draw takes
+// 12 to 28, by its number of exchanges): one 60-node tree over a 128K vocabulary 17.6 / 15.8, eight 100-node trees over 32K
+// 22.5 / 20.5, one tree over 32K 12.5 / 11.3, sixteen 27.0 / 25.1.  Tried on top of it and slower: both possible next candidates
+// asked for before the outcome is known, with a wave of its own that polls (a wave's loads complete in order, so one that has
+// asked for a slice polls behind it): the CU's address unit takes as long for their loads as the walk then waits less (16.5
+// against 14.6); a tree's workgroups on one XCD, exchanges through its L2: one XCD's share of the memory bandwidth is too
+// little for large vocabularies (one tree over 128K 25 - 31).
 //
 // Waiting is bounded: if a partner never shows up (the W workgroups of a tree are not all
 // resident) the walk gives up and reports accept_len = -1 instead of hanging; the last workgroup
@@ -46,7 +48,6 @@ namespace jk {
 namespace {
 
 constexpr int kCoopThreads = 256;
-constexpr int kCoopWaves = kCoopThreads / 64;
 // Polls before giving up: 27 ms at 0.21 us each (measured behind a kernel of another stream that left 8 CUs to the walk: 4096
 // polls end after 0.85 ms, 32768 after 6.9; more where the memory is busy).  Other streams' kernels hold partners up for
 // milliseconds, and what gives up has no result.  To be measured again when a poll or the words' layout changes.
@@ -128,142 +129,162 @@ __device__ __forceinline__ double pair_to_double(unsigned lo, unsigned hi) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-template <int PER>
-__global__ __launch_bounds__(kCoopThreads, 2) void walk_sample_coop_kernel(CoopParams p) {
-  constexpr int SLICE = kCoopThreads * PER;
-  __shared__ int par_s[JK_MAX_TREE];
-  __shared__ int tok_s[JK_MAX_TREE];
-  __shared__ int qrow_s[JK_MAX_TREE];
-  __shared__ float uni_s[JK_MAX_TREE + 1];
-  __shared__ double red_d[2][kCoopWaves];
-  __shared__ float red_f[2][kCoopWaves];
-  __shared__ double xs[64];    // the slices' sums under the current distribution
-  // What the polling wave found.  A wave may be two finds ahead of another one (a row adopted right behind another), so
-  // each kind has its own words.
-  __shared__ double got_row[2][2], got_res[2];
-  __shared__ int got_ok[3];
-  __shared__ int s_found;
-  __shared__ int s_lp[kCoopWaves];
-  __shared__ double pv_s;
+// The reference of a few logits' exponentials is a power of two near the exponential of the largest: sums with different
+// references are put together by changing exponents (an exponential there is a chain of 40 dependent instructions), and
+// a wave needs no other wave's maximum for its own.  exp(x / T) = 2^k exp(x / T - hi - lo).
+struct Reference {
+  double k, hi, lo;
+};
+__device__ __forceinline__ bool whole_exponent(double x) { return fabs(x) < 1099511627776.0; }
+__device__ __forceinline__ double exponent_of(float m, double inv_temp) {  // of the reference for a largest logit m
+  const double x = (double)m * inv_temp, k = x * 1.4426950408889634;
+  // (Beyond 2^40 a whole exponent would be too far off.  Two floats that differ are at least 2^16 apart there, divided by
+  // T: of sums that differ in their largest logits one is nothing beside the other.)
+  return whole_exponent(x) ? rint(k) : k;
+}
+__device__ __forceinline__ Reference reference_of(float m, double inv_temp) {
+  constexpr double kLn2 = 0.6931471805599453;
+  const double x = (double)m * inv_temp;
+  Reference r;
+  r.k = exponent_of(m, inv_temp);
+  r.hi = whole_exponent(x) ? r.k * kLn2 : (m == -INFINITY ? 0.0 : x);  // (only -inf: nothing sensible to subtract)
+  r.lo = whole_exponent(x) ? fma(r.k, kLn2, -r.hi) : 0.0;
+  return r;
+}
+__device__ __forceinline__ double exp_from(float x, double inv_temp, const Reference& r) {
+  return exp(fma((double)x, inv_temp, -r.hi) - r.lo);
+}
+// 2^(k - K) v, K the largest k
+__device__ __forceinline__ double scaled_down(double v, double k, double K) { return ldexp(v, (int)fmax(k - K, -4096.0)); }
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int W = p.W;
-  const int b = blockIdx.x / W, w = blockIdx.x % W;
-  const int N = p.n_tree, V = p.vocab, rows = N + 1;
-  const int v0 = w * SLICE + tid * PER;  // my first vocabulary entry
+// What a walk needs of a node.  Looked up step by step in the tree's arrays it took 0.4 us a candidate, a chain of some
+// hundred instructions of a lone wave per SIMD; one wave makes the table while the first row is on its way.
+struct Node {
+  int next, first;      // the next of its siblings, the first of its children, or -1
+  int tok, tok_first;   // its token, its first child's (its own, if it has none)
+  long long draft;      // where its draft distribution begins
+  int uni, pad;         // the bits of its uniform number
+};
+struct NodeTable {
+  int4 half[2][JK_MAX_TREE + 1];     // node k's at k + 1; the root's first child at 0
+  unsigned kids[JK_MAX_TREE + 1][4];  // a bit per child
+};
 
-  // PER consecutive floats of a row (rows are not aligned in general: loads of four at any multiple of four bytes)
-  typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
-  auto load_slice = [&](float (&dst)[PER], const float* row, float fill) {
-    if (PER >= 4 && v0 + PER <= V) {
-#pragma unroll
-      for (int u = 0; u < PER; u += 4) {
-        const f4 x = *reinterpret_cast<const f4*>(row + v0 + u);
-#pragma unroll
-        for (int i = 0; i < 4 && u + i < PER; ++i) dst[u + i] = x[i];
-      }
-    } else {
-#pragma unroll
-      for (int u = 0; u < PER; ++u) dst[u] = v0 + u < V ? row[v0 + u] : fill;
-    }
-  };
-  auto row_of = [&](int r) { return p.logits + ((long long)b * rows + r) * V; };
-
-  float lg[PER];
-  load_slice(lg, row_of(0), -INFINITY);  // (the first row is on its way before anything else is known)
-  int pa_reg = -1, tok_reg = 0;
-  TreeWords* tw = &p.trees[b].words;
-  const unsigned long long epoch = __hip_atomic_load(&tw->epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (tid < N) {
-    pa_reg = p.parent[(long long)b * N + tid];
-    tok_reg = p.tokens[(long long)b * N + tid];
-    long long r = (long long)b * N + tid;
-    if (p.draft_row) {
-      r = p.draft_row[r];
-      r = r < 0 ? 0 : (r >= p.n_draft_rows ? p.n_draft_rows - 1 : r);  // a bad row number must not fault
-    }
-    par_s[tid] = (pa_reg >= -1 && pa_reg < tid) ? pa_reg : -1;
-    tok_s[tid] = min(max(tok_reg, 0), V - 1);  // a token id outside the vocabulary must not fault
-    qrow_s[tid] = (int)r;
-    if (w == 0) {  // both repairs are recorded in the workspace's error word
-      if (par_s[tid] != pa_reg) __hip_atomic_fetch_or(p.err, kDevErrBadTree, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (tok_s[tid] != tok_reg) __hip_atomic_fetch_or(p.err, kDevErrBadToken, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-  }
-  if (tid <= N) uni_s[tid] = p.uniforms[(long long)b * rows + tid];
-  __syncthreads();
-  auto q_of = [&](int k) { return p.draft + (long long)qrow_s[k] * V; };  // the draft distribution of node k
-
-  // smallest j >= from with parent c, or -1: every wave looks at all (at most 128) nodes, two
-  // per lane, so no barrier is needed and all waves get the same answer
-  auto find_child = [&](int c, int from) -> int {
-    const bool h0 = lane < N && lane >= from && par_s[lane] == c;
-    const bool h1 = lane + 64 < N && lane + 64 >= from && par_s[lane + 64] == c;
-    const unsigned long long m0 = __ballot(h0), m1 = __ballot(h1);
-    return m0 ? __ffsll((long long)m0) - 1 : (m1 ? 63 + __ffsll((long long)m1) : -1);
-  };
-
-  // A candidate and what will be needed of it: its draft slice and value at its token, the logits slice of its own row
-  // (the one that counts if it is accepted) and that row's value at its first child's token.
-  struct Candidate {
-    int k, first;  // node, its first child (or -1)
-    float q[PER], lg[PER];
-    float qx, row_x;
-  };
-  auto fetch = [&](Candidate& n, int k) {
-    n.k = k;
-    n.first = -1;
-    if (k < 0) return;
-    n.first = find_child(k, k + 1);
-    const float *q = q_of(k), *row = row_of(k + 1);
-    load_slice(n.q, q, 0.f);
-    n.qx = q[tok_s[k]];
-    load_slice(n.lg, row, -INFINITY);
-    n.row_x = row[tok_s[n.first < 0 ? k : n.first]];
-  };
-
-  int flip = 0;  // alternates the LDS words of consecutive block reductions: one barrier each
-  auto block_sum = [&](double v) {
-    flip ^= 1;
-    v = wave_sum(v);
-    if (lane == 0) red_d[flip][wave] = v;
-    __syncthreads();
-    return (red_d[flip][0] + red_d[flip][1]) + (red_d[flip][2] + red_d[flip][3]);
-  };
-  auto block_max = [&](float v) {
-    flip ^= 1;
-    v = wave_max(v);
-    if (lane == 0) red_f[flip][wave] = v;
-    __syncthreads();
-    return fmaxf(fmaxf(red_f[flip][0], red_f[flip][1]), fmaxf(red_f[flip][2], red_f[flip][3]));
-  };
-
-  // Tags: 22 bits of call epoch, 10 bits of exchange number (at most N + depth + 2 < 1024 per call).  The two tables take
-  // turns from exchange to exchange and from call to call, and every exchange writes all its words.
+// A workgroup of a tree's: its place, the tree, and its side of the exchanges
+struct Walk {
+  const CoopParams& p;
+  NodeTable& table;
+  const int tid, lane, wave, W, b, w, N, V;
+  TreeWords* tw;
+  unsigned long long epoch;
+  float uni_last;
   unsigned n_exch = 0, tag = 0;
   Table* tab = nullptr;
-  auto open_exchange = [&] {
+
+  __device__ __forceinline__ Walk(const CoopParams& params, NodeTable& nodes)
+      : p(params), table(nodes), tid(threadIdx.x), lane(tid & 63), wave(__builtin_amdgcn_readfirstlane(tid >> 6)), W(p.W),
+        b(blockIdx.x / p.W), w(blockIdx.x % p.W), N(p.n_tree), V(p.vocab), tw(&p.trees[b].words) {}
+  __device__ __forceinline__ const float* row_of(int r) const { return p.logits + ((long long)b * (N + 1) + r) * V; }
+  __device__ __forceinline__ void load_words() {
+    epoch = __hip_atomic_load(&tw->epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uni_last = p.uniforms[(long long)b * (N + 1) + N];
+  }
+  // by one wave, in front of a barrier
+  __device__ __forceinline__ void make_table() {
+    int par[2], tok[2], uni[2];
+    long long draft[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int k = min(lane + 64 * h, N - 1);
+      const long long at = (long long)b * N + k;
+      par[h] = p.parent[at];
+      tok[h] = p.tokens[at];
+      uni[h] = __float_as_int(p.uniforms[at + b]);
+      draft[h] = p.draft_row ? p.draft_row[at] : at;
+    }
+    for (int i = lane; i <= N; i += 64) *reinterpret_cast<uint4*>(table.kids[i]) = make_uint4(0u, 0u, 0u, 0u);
+    auto in_order = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };  // (LDS operations of a wave complete in order)
+    in_order();
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int k = lane + 64 * h, pa = par[h], tk = tok[h];
+      par[h] = (pa >= -1 && pa < k) ? pa : -1;
+      tok[h] = min(max(tk, 0), V - 1);  // a token id outside the vocabulary must not fault
+      if (p.draft_row) draft[h] = draft[h] < 0 ? 0 : (draft[h] >= p.n_draft_rows ? p.n_draft_rows - 1 : draft[h]);  // nor a bad row
+      if (k >= N) continue;
+      if (w == 0) {  // both repairs are recorded in the workspace's error word
+        if (par[h] != pa) __hip_atomic_fetch_or(p.err, kDevErrBadTree, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tok[h] != tk) __hip_atomic_fetch_or(p.err, kDevErrBadToken, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      atomicOr(&table.kids[par[h] + 1][k >> 5], 1u << (k & 31));
+      table.half[0][k + 1].z = tok[h];
+    }
+    in_order();
+    auto lowest = [](const uint4& m, int above) {  // the lowest bit set beyond `above`
+      const unsigned words[4] = {m.x, m.y, m.z, m.w};
+      int at = -1;
+#pragma unroll
+      for (int i = 3; i >= 0; --i) {
+        const unsigned beyond = above < 32 * i ? ~0u : (above >= 32 * i + 31 ? 0u : ~0u << (above - 32 * i + 1));
+        const unsigned bits = words[i] & beyond;
+        at = bits ? 32 * i + __ffs((int)bits) - 1 : at;
+      }
+      return at;
+    };
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int k = lane + 64 * h;
+      if (k >= N) continue;
+      const int next = lowest(*reinterpret_cast<const uint4*>(table.kids[par[h] + 1]), k);
+      const int first = lowest(*reinterpret_cast<const uint4*>(table.kids[k + 1]), -1);
+      const int tok_first = table.half[0][(first < 0 ? k : first) + 1].z;
+      table.half[0][k + 1] = make_int4(next, first, tok[h], tok_first);
+      const long long at = draft[h] * V;
+      table.half[1][k + 1] = make_int4((int)at, (int)(at >> 32), uni[h], 0);
+    }
+    if (lane == 0) table.half[0][0].y = lowest(*reinterpret_cast<const uint4*>(table.kids[0]), -1);
+  }
+  __device__ __forceinline__ int first_of_root() const { return __builtin_amdgcn_readfirstlane(table.half[0][0].y); }
+  __device__ __forceinline__ Node node(int k) const {
+    const int4 a = table.half[0][k + 1], c = table.half[1][k + 1];
+    Node n;
+    n.next = __builtin_amdgcn_readfirstlane(a.x);
+    n.first = __builtin_amdgcn_readfirstlane(a.y);
+    n.tok = __builtin_amdgcn_readfirstlane(a.z);
+    n.tok_first = __builtin_amdgcn_readfirstlane(a.w);
+    n.draft = (long long)((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane(c.y) << 32 | (unsigned)__builtin_amdgcn_readfirstlane(c.x));
+    n.uni = __builtin_amdgcn_readfirstlane(c.z);
+    return n;
+  }
+
+  // Tags: 22 bits of call epoch, 10 bits of exchange number (at most N + depth + 2 < 1024 per call).  The two tables take
+  // turns from exchange to exchange and from call to call, and every exchange writes all words that are read in it.
+  __device__ __forceinline__ void open_exchange() {
     ++n_exch;
     tag = (unsigned)(((epoch + 1) & 0x3FFFFFull) << 10) | (n_exch & 0x3FFu);
     tab = p.trees[b].tables + ((n_exch + (unsigned)epoch) & 1u);
-  };
-  auto put = [&](int word, unsigned payload) {
+  }
+  __device__ __forceinline__ void put(int word, unsigned payload) {
     __hip_atomic_store(&tab->word[word][w], ((unsigned long long)tag << 32) | payload, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  };
-  auto publish4 = [&](double a, double v) {  // words 0 - 3
+  }
+  __device__ __forceinline__ void publish4(double a, double v) {  // words 0 - 3
     if (tid < 4) {
       const unsigned long long bits = (unsigned long long)__double_as_longlong(tid < 2 ? a : v);
       put(tid, (unsigned)(bits >> (32 * (tid & 1))));
     }
+  }
+  struct Stats {  // of a row's slice, in the first wave: its largest logit, and the sum of its exponentials by that one's reference
+    double z;
+    float m;
   };
-  auto publish_row = [&](int at, double z, float m) {  // words at, at + 1 (z), at + 2 (m)
+  __device__ __forceinline__ void publish_row(int at, const Stats& st) {  // words at, at + 1 (z), at + 2 (m)
     if (tid < 3) {
-      const unsigned long long bits = (unsigned long long)__double_as_longlong(z);
-      put(at + tid, tid == 2 ? __float_as_uint(m) : (unsigned)(bits >> (32 * tid)));
+      const unsigned long long bits = (unsigned long long)__double_as_longlong(st.z);
+      put(at + tid, tid == 2 ? __float_as_uint(st.m) : (unsigned)(bits >> (32 * tid)));
     }
-  };
-  // wave 0: lane i waits for words [at, at + n) of workgroup i and returns their payloads
-  auto await = [&](int at, int n, unsigned (&pay)[4]) -> bool {
+  }
+  // one wave: lane i waits for words [at, at + n) of workgroup i and returns their payloads
+  __device__ __forceinline__ bool await(int at, int n, unsigned (&pay)[4]) const {
     const bool in = lane < W;
     unsigned spins = 0;
     for (;;) {
@@ -284,220 +305,86 @@ __global__ __launch_bounds__(kCoopThreads, 2) void walk_sample_coop_kernel(CoopP
       if (++spins > p.spin_limit) return false;
       __builtin_amdgcn_s_sleep(1);
     }
-  };
-
-  double e[PER];               // exp(row / T - its slice's maximum) of the row that `e_m` belongs to
-  float e_m = 0.f;
-  double cur[PER];             // the current distribution
-  double row_m = 0.0, row_inv = 1.0;  // of the current row: maximum of row / T, 1 / sum of exp(row / T - maximum)
-
-  // slice statistics of a row: e[], e_m (largest logit of the slice) and the slice's sum
-  auto slice_stats = [&](const float (&x)[PER]) -> double {
-    float m = -INFINITY;
-#pragma unroll
-    for (int u = 0; u < PER; ++u) m = fmaxf(m, x[u]);
-    e_m = block_max(m);
-    const double ref = e_m == -INFINITY ? 0.0 : (double)e_m * p.inv_temp;
-    double z = 0.0;
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      e[u] = exp((double)x[u] * p.inv_temp - ref);
-      z += e[u];
-    }
-    return block_sum(z);
-  };
-  // everybody's statistics of a row -> its maximum, normaliser and slice sums; cur[] from e[]
-  auto adopt_row = [&](int at) -> bool {
-    if (wave == 0) {
-      unsigned pay[4] = {0u, 0u, 0u, 0u};
-      const bool ok = await(at, 3, pay);
-      const float m_w = lane < W ? __uint_as_float(pay[2]) : -INFINITY;
-      const float m = wave_max(m_w);
-      const double ref = m == -INFINITY ? 0.0 : (double)m * p.inv_temp;
-      const double z_w = lane < W ? pair_to_double(pay[0], pay[1]) * exp((m_w == -INFINITY ? 0.0 : (double)m_w * p.inv_temp) - ref) : 0.0;
-      const double z = wave_sum(lane < W && m_w != -INFINITY ? z_w : 0.0);
-      const double inv = 1.0 / z;
-      xs[lane] = (m_w == -INFINITY ? 0.0 : z_w) * inv;
-      if (lane == 0) {
-        got_row[at == 4][0] = ref;
-        got_row[at == 4][1] = inv;
-        got_ok[at == 4] = ok;
-      }
-    }
-    __syncthreads();
-    row_m = got_row[at == 4][0];
-    row_inv = got_row[at == 4][1];
-    const double ref = e_m == -INFINITY ? 0.0 : (double)e_m * p.inv_temp;
-    const double sc = exp(ref - row_m) * row_inv;
-#pragma unroll
-    for (int u = 0; u < PER; ++u) cur[u] = e[u] * sc;
-    return got_ok[at == 4] != 0;
-  };
-
-  Candidate cand, ahead;
-  fetch(cand, find_child(-1, 0));
-  bool row_known;  // e[] and the open exchange's words 4 - 6 are the statistics of cand's own row
-  // The statistics of candidate n's row, behind the exchange that is under way (zeros for none: the words are always written)
-  auto look_ahead = [&](const Candidate& n) {
-    double z = 0.0;
-    if (n.k >= 0) z = slice_stats(n.lg);
-    publish_row(4, z, n.k >= 0 ? e_m : 0.f);
-  };
-
-  int c = -1, len = 0;
-  double px = 0.0;  // probability of cand's token under the current distribution
-  bool alive;
-  {
-    const double z = slice_stats(lg);
-    open_exchange();
-    publish_row(0, z, e_m);
-    if (tid == 3) put(3, 0u);
-    double e0[PER];
-    const float m0 = e_m;
-#pragma unroll
-    for (int u = 0; u < PER; ++u) e0[u] = e[u];
-    const float row_x = row_of(0)[tok_s[cand.k < 0 ? 0 : cand.k]];
-    look_ahead(cand);
-    double e1[PER];
-    const float m1 = e_m;
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      e1[u] = e[u];
-      e[u] = e0[u];
-    }
-    e_m = m0;
-    alive = adopt_row(0);
-#pragma unroll
-    for (int u = 0; u < PER; ++u) e[u] = e1[u];
-    e_m = m1;
-    row_known = true;
-    px = exp((double)row_x * p.inv_temp - row_m) * row_inv;
   }
-  while (alive && cand.k >= 0) {
-    const int k = cand.k;
-    if ((double)uni_s[k] * (double)cand.qx < px) {
-      // ---- accepted: the row of k becomes the current one, its first child the candidate
-      if (tid == 0 && w == 0) p.out_path[(long long)b * p.max_depth + len] = k;
-      ++len;
-      c = k;
-      const float row_x = cand.row_x;
-      // at max_depth accepted nodes the walk stops: the token after c is drawn from c's own row
-      const int next = len < p.max_depth ? cand.first : -1;
-      if (row_known) {
-        fetch(ahead, next);
-        alive = adopt_row(4);
-        row_known = false;
+  // one wave, what it awaited of a residual (words 0 - 3): its mass, its value in workgroup `owner`, and this lane's slice's part
+  __device__ __forceinline__ double mass_total(const unsigned (&pay)[4], int owner, double& s, double& at_owner) const {
+    const double own = lane < W ? pair_to_double(pay[0], pay[1]) : 0.0;
+    s = wave_sum(own);
+    const int from = __builtin_amdgcn_readfirstlane(owner);
+    at_owner = pair_to_double(__builtin_amdgcn_readlane(pay[2], from), __builtin_amdgcn_readlane(pay[3], from));
+    return own;
+  }
+  // one wave, what it awaited of a row (words 0 - 2 of `pay`): the exponent of the row's reference, its normaliser, and this
+  // lane's slice's sum
+  __device__ __forceinline__ void row_total(const unsigned (&pay)[4], double& K, double& z, double& mine) const {
+    const float m_w = lane < W ? __uint_as_float(pay[2]) : -INFINITY;
+    K = exponent_of(wave_max(m_w), p.inv_temp);
+    mine = m_w == -INFINITY ? 0.0 : scaled_down(pair_to_double(pay[0], pay[1]), exponent_of(m_w, p.inv_temp), K);
+    z = wave_sum(mine);
+  }
+  // The waves' parts put together, lane i holding part i mod WAVES (a row of 16 lanes at most: four moves)
+  template <int WAVES>
+  __device__ __forceinline__ static double sum_of(double v) {
+    v += dev::dpp64<0xB1>(v);  // quad_perm [1,0,3,2]
+    v += dev::dpp64<0x4E>(v);  // quad_perm [2,3,0,1]
+    if (WAVES > 4) v += dev::dpp64<0x141>(v);  // row_half_mirror
+    if (WAVES > 8) v += dev::dpp64<0x140>(v);  // row_mirror
+    return v;
+  }
+  template <int WAVES>
+  __device__ __forceinline__ Stats put_together(double z, float m) const {
+    auto most = [](float v, int x) { return fmaxf(v, __int_as_float(x)); };
+    Stats st;
+    st.m = most(m, dev::dpp<0xB1>(__float_as_int(m)));
+    st.m = most(st.m, dev::dpp<0x4E>(__float_as_int(st.m)));
+    if (WAVES > 4) st.m = most(st.m, dev::dpp<0x141>(__float_as_int(st.m)));
+    if (WAVES > 8) st.m = most(st.m, dev::dpp<0x140>(__float_as_int(st.m)));
+    st.z = sum_of<WAVES>(scaled_down(z, exponent_of(m, p.inv_temp), exponent_of(st.m, p.inv_temp)));
+    return st;
+  }
+  // A thread's PER consecutive vocabulary entries from v0 on: entry u is at + u, and counts from u = skip on.  (No thread
+  // looks past the end of a row: those at the end read its last PER entries.  No branch, in which the compiler would wait
+  // for everything under way: every exchange waits for the workgroup at the end.)
+  template <int PER>
+  struct Part {
+    int v0, at, skip;
+    __device__ __forceinline__ Part(int first, int V) : v0(first), at(min(first, V - PER)), skip(first - at) {}
+    // (worked out where it is used: kept, the masks of all entries fill the scalar registers)
+    __device__ __forceinline__ int first_that_counts() const {
+      int s = skip;
+      asm volatile("" : "+v"(s));
+      return s;
+    }
+    __device__ __forceinline__ bool has(int x) const { return x >= v0 && x < v0 + PER; }
+    // (rows are not aligned in general: loads of four at any multiple of four bytes)
+    __device__ __forceinline__ void load(float (&dst)[PER], const float* row) const {
+      if constexpr (PER >= 4) {
+        typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+#pragma unroll
+        for (int u = 0; u < PER; u += 4) {
+          const f4 x = *reinterpret_cast<const f4*>(row + at + u);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) dst[u + i] = x[i];
+        }
       } else {
-        const double z = slice_stats(cand.lg);
-        fetch(ahead, next);
-        open_exchange();
-        publish_row(0, z, e_m);
-        if (tid == 3) put(3, 0u);
-        double e0[PER];
-        const float m0 = e_m;
 #pragma unroll
-        for (int u = 0; u < PER; ++u) e0[u] = e[u];
-        look_ahead(ahead);
-        double e1[PER];
-        const float m1 = e_m;
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-          e1[u] = e[u];
-          e[u] = e0[u];
-        }
-        e_m = m0;
-        alive = adopt_row(0);
-#pragma unroll
-        for (int u = 0; u < PER; ++u) e[u] = e1[u];
-        e_m = m1;
-        row_known = true;
-      }
-      px = exp((double)row_x * p.inv_temp - row_m) * row_inv;
-      cand = ahead;
-      continue;
-    }
-    // ---- rejected: the residual's mass, and its value at the next sibling's token
-    fetch(ahead, find_child(c, k + 1));
-    const int x = ahead.k >= 0 ? tok_s[ahead.k] : 0;
-    double part = 0.0, at_x = 0.0, res[PER];
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      res[u] = v0 + u < V ? fmax(0.0, cur[u] - (double)cand.q[u]) : 0.0;
-      part += res[u];
-      if (v0 + u == x) at_x = res[u];
-    }
-    if (x >= v0 && x < v0 + PER) pv_s = at_x;  // (one thread of one workgroup; the sum's barrier orders it)
-    const double s_w = block_sum(part);
-    open_exchange();
-    publish4(s_w, pv_s);
-    look_ahead(ahead);
-    row_known = true;
-    if (wave == 0) {
-      unsigned pay[4] = {0u, 0u, 0u, 0u};
-      const bool ok = await(0, 4, pay);
-      const double mine = lane < W ? pair_to_double(pay[0], pay[1]) : 0.0;
-      const double s = wave_sum(mine);
-      const int owner = __builtin_amdgcn_readfirstlane(x / SLICE);
-      const double v = pair_to_double(__builtin_amdgcn_readlane(pay[2], owner), __builtin_amdgcn_readlane(pay[3], owner));
-      if (s > 0.0) xs[lane] = mine * (1.0 / s);
-      if (lane == 0) {
-        got_res[0] = s;
-        got_res[1] = v;
-        got_ok[2] = ok;
+        for (int u = 0; u < PER; ++u) dst[u] = row[at + u];
       }
     }
-    __syncthreads();
-    alive = got_ok[2] != 0;
-    const double s = got_res[0];
-    if (s > 0.0) {
-      const double inv = 1.0 / s;
-#pragma unroll
-      for (int u = 0; u < PER; ++u) cur[u] = res[u] * inv;
-      px = got_res[1] * inv;
-    } else if (alive && ahead.k >= 0) {
-      // nothing left of the distribution: it stays as it was, and the next token's value under it has to be asked for
-      double e1[PER];
-      if (x >= v0 && x < v0 + PER) {
-#pragma unroll
-        for (int u = 0; u < PER; ++u)
-          if (v0 + u == x) pv_s = cur[u];
-      }
-      __syncthreads();
-      // (the row statistics ahead go along again: words 4 - 6 belong to the exchange that is open)
-#pragma unroll
-      for (int u = 0; u < PER; ++u) e1[u] = e[u];
-      const float m1 = e_m;
-      double z = 0.0;
-#pragma unroll
-      for (int u = 0; u < PER; ++u) z += e1[u];
-      z = block_sum(z);
-      open_exchange();
-      publish4(0.0, pv_s);
-      publish_row(4, z, m1);
-      if (wave == 0) {
-        unsigned pay[4] = {0u, 0u, 0u, 0u};
-        const bool ok = await(0, 4, pay);
-        const int owner = __builtin_amdgcn_readfirstlane(x / SLICE);
-        const double v = pair_to_double(__builtin_amdgcn_readlane(pay[2], owner), __builtin_amdgcn_readlane(pay[3], owner));
-        if (lane == 0) {
-          got_res[1] = v;
-          got_ok[2] = ok;
-        }
-      }
-      __syncthreads();
-      alive = got_ok[2] != 0;
-      px = got_res[1];
-    }
-    cand = ahead;
-  }
-  // ---- final draw: smallest v whose cumulative probability exceeds u * total
-  if (alive) {
+  };
+
+  // Final draw: smallest v whose cumulative probability exceeds u * total.  x: the sum of lane's slice under the current
+  // distribution; cur: this thread's part of that.
+  template <int PER, int WAVES>
+  __device__ __forceinline__ void draw(double x, const double (&cur)[PER], const Part<PER>& mine, int len) {
+    __shared__ double sum_s[WAVES];
+    __shared__ int last_s[WAVES], found_s;
     // workgroup i owns the crossing iff before(i) <= target < before(i) + its sum, with before(i) its left neighbour's
     // scanned sum: the intervals tile [0, total), rounding included, and every workgroup computes the same ones
-    const double upto = wave_scan(lane < W ? xs[lane] : 0.0);
+    const double upto = wave_scan(lane < W ? x : 0.0);
     const double before = lane_before(upto);
     const double total = lane_value(upto, 63);
-    const double target = (double)uni_s[N] * total;
+    const double target = (double)uni_last * total;
     const unsigned long long hit = __ballot(before <= target && upto > target);
     const int owner = hit ? __ffsll((long long)hit) - 1 : -1;
     const double owner_lo = hit ? lane_value(before, owner) : 0.0;
@@ -505,42 +392,44 @@ __global__ __launch_bounds__(kCoopThreads, 2) void walk_sample_coop_kernel(CoopP
       const double local = target - owner_lo;
       double part = 0.0;
       int last_pos = -1;
+      const int skip = mine.first_that_counts();
 #pragma unroll
       for (int u = 0; u < PER; ++u) {
-        if (v0 + u < V) {
+        if (u >= skip) {
           part += cur[u];
-          if (cur[u] > 0.0) last_pos = v0 + u;
+          if (cur[u] > 0.0) last_pos = mine.at + u;
         }
       }
       // scan of the threads' sums: wave scan, then wave offsets
       const double incl = wave_scan(part), excl = lane_before(incl);
-      flip ^= 1;
-      if (lane == 63) red_d[flip][wave] = incl;
       int lp = last_pos;
       for (int o = 32; o > 0; o >>= 1) lp = max(lp, __shfl_xor(lp, o));
-      if (lane == 0) s_lp[wave] = lp;
-      if (tid == 0) s_found = -1;
+      if (lane == 63) sum_s[wave] = incl;
+      if (lane == 0) last_s[wave] = lp;
+      if (tid == 0) found_s = -1;
       __syncthreads();
       double off = 0.0;
-      for (int i = 0; i < wave; ++i) off += red_d[flip][i];
+      for (int i = 0; i < wave; ++i) off += sum_s[i];
       const double lo = off + excl, hi = off + incl;
       if (lo <= local && hi > local) {
         double run = lo;
         int found = -1;
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
-          if (v0 + u < V) {
+          if (u >= skip) {
             run += cur[u];
-            if (found < 0 && run > local) found = v0 + u;
+            if (found < 0 && run > local) found = mine.at + u;
           }
         }
         if (found < 0) found = last_pos;  // rounding between the scanned and the re-added sums
-        atomicMax(&s_found, found);
+        atomicMax(&found_s, found);
       }
       __syncthreads();
       if (tid == 0) {
         // (the slice's published sum and the re-added one may differ in the last place: then its last entry with p > 0)
-        const int token = s_found >= 0 ? s_found : max(max(s_lp[0], s_lp[1]), max(s_lp[2], s_lp[3]));
+        int token = found_s;
+        if (token < 0)
+          for (int i = 0; i < WAVES; ++i) token = max(token, last_s[i]);
         __hip_atomic_store(&p.out_bonus[b], token < 0 ? 0 : token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
@@ -550,8 +439,9 @@ __global__ __launch_bounds__(kCoopThreads, 2) void walk_sample_coop_kernel(CoopP
       __hip_atomic_store(&p.out_len[b], len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
-  // ---- the end of this workgroup: say so; where one of the tree gave up, the last to finish takes the results back
-  if (tid == 0) {
+  // The end of this workgroup: it says so; where one of the tree gave up, the last to finish takes the results back
+  __device__ __forceinline__ void finish(bool alive) {
+    if (tid != 0) return;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the results went through to memory before the count can tell anybody)
     const unsigned mine = 1u + (alive ? 0u : 0x10000u);
     const unsigned all = __hip_atomic_fetch_add(&tw->finish, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + mine;
@@ -565,6 +455,232 @@ __global__ __launch_bounds__(kCoopThreads, 2) void walk_sample_coop_kernel(CoopP
       __hip_atomic_store(&tw->epoch, epoch + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
+};
+
+template <int PER, int THREADS>
+__global__ __launch_bounds__(THREADS, 2) void walk_sample_coop_kernel(CoopParams params) {
+  constexpr int SLICE = THREADS * PER, WAVES = THREADS / 64;
+  __shared__ NodeTable nodes;
+  __shared__ double red_d[2][WAVES];
+  __shared__ float red_f[2][WAVES];
+  __shared__ double xs[64];  // the slices' sums under the current distribution, still to be multiplied by xs_mul
+  // What the polling wave found.  A wave may be two finds ahead of another one (a row adopted right behind another), so
+  // each kind has its own words.
+  __shared__ double got_row[2][2], got_res[2];
+  __shared__ int got_ok[3];
+  __shared__ double pv_s;
+
+  Walk wk(params, nodes);
+  const CoopParams& p = wk.p;
+  const int tid = wk.tid, lane = wk.lane, wave = wk.wave, W = wk.W;
+  const Walk::Part<PER> mine(wk.w * SLICE + tid * PER, wk.V);
+
+  float lg[PER];
+  mine.load(lg, wk.row_of(0));  // (the first row is on its way before anything else is known)
+  wk.load_words();
+  if (wave == 0) wk.make_table();
+  __syncthreads();
+
+  // A candidate and what will be needed of it: its draft slice and value at its token, the logits slice of its own row
+  // (the one that counts if it is accepted) and that row's value at its first child's token.
+  struct Candidate {
+    int k;
+    Node node;
+    float q[PER], lg[PER];
+    float qx, row_x;
+  };
+  auto fetch = [&](Candidate& n, int k) {
+    n.k = k;
+    if (k < 0) return;
+    n.node = wk.node(k);
+    const float *q = p.draft + n.node.draft, *row = wk.row_of(k + 1);
+    mine.load(n.q, q);
+    n.qx = q[n.node.tok];
+    mine.load(n.lg, row);
+    n.row_x = row[n.node.tok_first];
+  };
+
+  using Stats = Walk::Stats;
+  struct Exponentials {  // of this thread's part of a row: 2^k e[]
+    double e[PER], k;
+  };
+  double cur[PER];      // the current distribution
+  double xs_mul = 1.0;  // (a division that only the final draw needs stays out of the polling wave's way)
+  double px = 0.0;      // probability of cand's token under the current distribution
+  bool alive = true;
+  int flip = 0;  // alternates the LDS words of consecutive block reductions: one barrier each
+
+  auto slice_stats = [&](const float (&x)[PER], Exponentials& out) -> Stats {
+    flip ^= 1;
+    float m = -INFINITY, y[PER];
+    const int skip = mine.first_that_counts();
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      y[u] = u >= skip ? x[u] : -INFINITY;
+      m = fmaxf(m, y[u]);
+    }
+    m = wave_max(m);
+    const Reference ref = reference_of(m, p.inv_temp);
+    out.k = ref.k;
+    double z = 0.0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      out.e[u] = exp_from(y[u], p.inv_temp, ref);
+      z += out.e[u];
+    }
+    z = wave_sum(z);
+    if (lane == 0) {
+      red_d[flip][wave] = z;
+      red_f[flip][wave] = m;
+    }
+    __syncthreads();
+    Stats st = {0.0, 0.f};
+    if (wave == 0) st = wk.put_together<WAVES>(red_d[flip][lane % WAVES], red_f[flip][lane % WAVES]);
+    return st;
+  };
+  // everybody's statistics of a row -> its reference, normaliser and slice sums; cur[] from the row's exponentials, and the
+  // probability of the token that has this logit (its exponential is taken in front of the wait, by a reference of its own:
+  // every workgroup must get the same bits)
+  auto adopt_row = [&](int at, const Exponentials& ex, float logit) {
+    const int kind = at == 4;
+    const Reference ref = reference_of(logit, p.inv_temp);
+    const double e_x = exp_from(logit, p.inv_temp, ref);
+    if (wave == 0) {
+      unsigned pay[4] = {0u, 0u, 0u, 0u};
+      const bool ok = wk.await(at, 3, pay);
+      double K, z, own;
+      wk.row_total(pay, K, z, own);
+      xs[lane] = own;
+      if (lane == 0) {
+        got_row[kind][0] = K;
+        got_row[kind][1] = z;
+        got_ok[kind] = ok;
+      }
+    }
+    __syncthreads();
+    const double row_k = got_row[kind][0], row_inv = 1.0 / got_row[kind][1];
+    alive = got_ok[kind] != 0;
+    xs_mul = row_inv;
+    px = scaled_down(e_x, ref.k, row_k) * row_inv;
+    const double sc = scaled_down(row_inv, ex.k, row_k);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) cur[u] = ex.e[u] * sc;
+  };
+
+  Candidate cand, then;  // `then`: fetched when the outcome names it, the next sibling or the first child
+  Exponentials ahead;    // of cand's own row, where it is known
+  Stats ahead_stats = {0.0, 0.f};
+  bool row_known = false;  // `ahead` and the open exchange's words 4 - 6 are those of cand's own row
+  // The statistics of cand's row, behind the exchange that is under way (zeros for none: the words are always written)
+  auto look_ahead = [&]() {
+    ahead_stats = Stats{0.0, 0.f};
+    if (cand.k >= 0) ahead_stats = slice_stats(cand.lg, ahead);
+    wk.publish_row(4, ahead_stats);
+    row_known = true;
+  };
+  // The row that becomes the current one, of which nothing is known yet, in an exchange that also carries the statistics of
+  // the row of the candidate behind it
+  auto exchange_row = [&](const float (&x)[PER], float row_x, const Candidate& next) {
+    Exponentials now;
+    const Stats st = slice_stats(x, now);
+    wk.open_exchange();
+    wk.publish_row(0, st);
+    if (tid == 3) wk.put(3, 0u);
+    cand = next;
+    look_ahead();
+    adopt_row(0, now, row_x);
+  };
+
+  int len = 0;
+  fetch(then, wk.first_of_root());
+  exchange_row(lg, wk.row_of(0)[then.node.tok], then);
+  while (alive && cand.k >= 0) {
+    if ((double)__int_as_float(cand.node.uni) * (double)cand.qx < px) {
+      // ---- accepted: its row becomes the current one, its first child the candidate
+      if (tid == 0 && wk.w == 0) p.out_path[(long long)wk.b * p.max_depth + len] = cand.k;
+      ++len;
+      // (at max_depth accepted nodes the walk stops: the token after the last one is drawn from that one's own row)
+      fetch(then, len < p.max_depth ? cand.node.first : -1);
+      const float row_x = cand.row_x;
+      if (row_known) {
+        cand = then;
+        row_known = false;
+        adopt_row(4, ahead, row_x);
+      } else {
+#pragma unroll
+        for (int u = 0; u < PER; ++u) lg[u] = cand.lg[u];
+        exchange_row(lg, row_x, then);
+      }
+      continue;
+    }
+    // ---- rejected: the residual's mass, and its value at the next sibling's token
+    fetch(then, cand.node.next);
+    const int x = then.k >= 0 ? then.node.tok : 0;
+    double part = 0.0, at_x = 0.0, res[PER];
+    const int skip = mine.first_that_counts();
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      res[u] = u >= skip ? fmax(0.0, cur[u] - (double)cand.q[u]) : 0.0;
+      part += res[u];
+      if (mine.at + u == x) at_x = res[u];
+    }
+    if (mine.has(x)) pv_s = at_x;  // (one thread of one workgroup; the sum's barrier orders it)
+    part = wave_sum(part);
+    flip ^= 1;
+    if (lane == 0) red_d[flip][wave] = part;
+    __syncthreads();
+    wk.open_exchange();
+    if (wave == 0) wk.publish4(Walk::sum_of<WAVES>(red_d[flip][lane % WAVES]), pv_s);
+    cand = then;
+    look_ahead();
+    if (wave == 0) {
+      unsigned pay[4] = {0u, 0u, 0u, 0u};
+      const bool ok = wk.await(0, 4, pay);
+      double s, at_owner;
+      const double own = wk.mass_total(pay, x / SLICE, s, at_owner);
+      if (s > 0.0) xs[lane] = own;
+      if (lane == 0) {
+        got_res[0] = s;
+        got_res[1] = at_owner;
+        got_ok[2] = ok;
+      }
+    }
+    __syncthreads();
+    alive = got_ok[2] != 0;
+    const double s = got_res[0];
+    if (s > 0.0) {
+      const double inv = xs_mul = 1.0 / s;
+      px = got_res[1] * inv;
+#pragma unroll
+      for (int u = 0; u < PER; ++u) cur[u] = res[u] * inv;
+    } else if (alive && cand.k >= 0) {
+      // nothing left of the distribution: it stays as it was, and the next token's value under it has to be asked for
+      if (mine.has(x)) {
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+          if (mine.at + u == x) pv_s = cur[u];
+      }
+      __syncthreads();
+      wk.open_exchange();
+      wk.publish4(0.0, pv_s);
+      wk.publish_row(4, ahead_stats);  // (again: words 4 - 6 belong to the exchange that is open)
+      if (wave == 0) {
+        unsigned pay[4] = {0u, 0u, 0u, 0u};
+        const bool ok = wk.await(0, 4, pay);
+        double none, at_owner;
+        wk.mass_total(pay, x / SLICE, none, at_owner);
+        if (lane == 0) {
+          got_res[1] = at_owner;
+          got_ok[2] = ok;
+        }
+      }
+      __syncthreads();
+      alive = got_ok[2] != 0;
+      px = got_res[1];
+    }
+  }
+  if (alive) wk.draw<PER, WAVES>(xs[lane] * xs_mul, cur, mine, len);
+  wk.finish(alive);
 }
 
 }  // namespace
@@ -575,25 +691,32 @@ __global__ __launch_bounds__(kCoopThreads, 2) void walk_sample_coop_kernel(CoopP
 constexpr int kCoopMaxTrees = 512;
 size_t accept_coop_bytes() { return (size_t)kCoopMaxTrees * sizeof(TreeBlock); }
 
-bool accept_coop_plan(int batch, int vocab, int cus, int* W, int* per) {
+template <int PER, int THREADS>
+hipError_t launch_walk(const CoopParams& cp, int wgs, hipStream_t stream) {
+  hipLaunchKernelGGL((walk_sample_coop_kernel<PER, THREADS>), dim3((unsigned)wgs), dim3(THREADS), 0, stream, cp);
+  return hipGetLastError();
+}
+
+bool accept_coop_plan(int batch, int vocab, int cus, int* W, int* slice) {
   if (batch > kCoopMaxTrees) return false;
-  int most = (2 * cus) / batch;  // two workgroups per CU are resident together
-  if (most > 64) most = 64;
-  // Entries per thread: fewer of them mean more workgroups to wait for, more of them longer rows of exponentials.  (us, trees x
-  // entries: 8 x 32000 with 2 a thread (63 workgroups a tree) 24.4, 4 (32) 23.1; 16 x 32000 with 4 25.2, 8 27.6; 64 x 8000
-  // 30.6, 34.3.)  Two only where every workgroup has a CU to itself: 1 x 8000 12.4, with four 13.3; 8 x 8000 20.4 and 22.7.
-  for (int n = 2; n <= 16; n *= 2) {
-    const int need = (vocab + kCoopThreads * n - 1) / (kCoopThreads * n);
-    if (need <= most && (n > 2 || need * batch <= cus)) {
-      *W = need;
-      *per = n;
-      return true;
-    }
-  }
+  auto fits = [&](int threads, int per, int wgs) {
+    const int need = (vocab + threads * per - 1) / (threads * per);
+    if (need > 64 || (long long)need * batch > wgs || vocab < per) return false;
+    *W = need;
+    *slice = threads * per;
+    return true;
+  };
+  // Entries per thread: fewer of them mean more workgroups to wait for, more of them longer rows of exponentials.  (us, the mean
+  // of six draws, trees x entries: 8 x 32000 with 2 a thread (63 workgroups a tree) 21.6, 4 20.8, 8 23.6; 16 x 32000 with 4 25.1,
+  // 8 26.8; 64 x 8000 24.9, 27.6.)  Two only where every workgroup has a CU to itself: 1 x 8000 11.7, with four 12.8; 8 x 8000
+  // 17.4 and 19.5.
+  if (fits(kCoopThreads, 2, cus)) return true;
+  for (int per = 4; per <= 16; per *= 2)
+    if (fits(kCoopThreads, per, 2 * cus)) return true;  // (two workgroups of 256 threads per CU are resident together)
   return false;
 }
 
-hipError_t launch_accept_coop(const AcceptArgs& a, void* coop_ws, int W, int per, hipStream_t stream) {
+hipError_t launch_accept_coop(const AcceptArgs& a, void* coop_ws, int W, int slice, hipStream_t stream) {
   CoopParams cp;
   cp.err = static_cast<unsigned*>(a.workspace);
   cp.n_tree = a.n_tree; cp.vocab = a.vocab; cp.max_depth = a.max_depth; cp.W = W;
@@ -604,15 +727,16 @@ hipError_t launch_accept_coop(const AcceptArgs& a, void* coop_ws, int W, int per
   cp.trees = static_cast<TreeBlock*>(coop_ws);
   cp.spin_limit = tuning().spin_limit >= 0 ? (unsigned)tuning().spin_limit : kDefaultSpinLimit;
   cp.out_path = a.out_path; cp.out_len = a.out_len; cp.out_bonus = a.out_bonus;
-  const dim3 grid((unsigned)(a.batch * W)), block(kCoopThreads);
-  switch (per) {
-    case 2: hipLaunchKernelGGL(walk_sample_coop_kernel<2>, grid, block, 0, stream, cp); break;
-    case 4: hipLaunchKernelGGL(walk_sample_coop_kernel<4>, grid, block, 0, stream, cp); break;
-    case 8: hipLaunchKernelGGL(walk_sample_coop_kernel<8>, grid, block, 0, stream, cp); break;
-    case 16: hipLaunchKernelGGL(walk_sample_coop_kernel<16>, grid, block, 0, stream, cp); break;
+  // A workgroup with a CU to itself has its slice among twice the threads: two waves on a SIMD fill each other's waits.  (us, 256
+  // threads / 512: 1 x 128256 16.5 / 15.8, 8 x 32000 20.8 / 20.5; slices of 512 entries 11.7 / 12.0 at 1 x 8000: not those.)
+  const bool lone = a.batch * W <= device_cu_count();
+  switch (slice) {
+    case kCoopThreads * 2: return launch_walk<2, kCoopThreads>(cp, a.batch * W, stream);
+    case kCoopThreads * 4: return lone ? launch_walk<2, 512>(cp, a.batch * W, stream) : launch_walk<4, kCoopThreads>(cp, a.batch * W, stream);
+    case kCoopThreads * 8: return lone ? launch_walk<4, 512>(cp, a.batch * W, stream) : launch_walk<8, kCoopThreads>(cp, a.batch * W, stream);
+    case kCoopThreads * 16: return lone ? launch_walk<8, 512>(cp, a.batch * W, stream) : launch_walk<16, kCoopThreads>(cp, a.batch * W, stream);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 // Calibration: a pure 128-bit streaming read of `bytes` bytes (nothing is computed or written

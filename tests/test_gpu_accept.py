@@ -606,6 +606,32 @@ def test_sample_residual_that_vanishes_in_the_middle_of_the_siblings():
             assert _compare(a, par, "sample") == 0
 
 
+@pytest.mark.parametrize("rows", ["huge", "lowest", "masked"])
+def test_sample_logits_of_extreme_size(rows):
+    """Logits whose exponentials need a reference far from zero (3e30, where a power of two is no longer near enough), rows
+    masked with the type's lowest value but for a few entries, in one slice only, and rows of -inf but for a few."""
+    rng = np.random.default_rng(5)
+    V, N = 9000, 5
+    z = rng.standard_normal((1, N + 1, V)).astype(np.float32)
+    if rows == "huge":
+        z = z * np.float32(3e30)
+    else:
+        keep = rng.choice(1000, 40, replace=False) + 3000
+        m = np.full_like(z, np.finfo(np.float32).min if rows == "lowest" else -np.inf)
+        m[..., keep] = z[..., keep] * 4
+        z = m
+    par = np.array([[-1, -1, 0, 0, 1]], dtype=np.int32)
+    a = {"logits": z, "draft_probs": np.empty((1, N, V), np.float32), "tokens": np.empty((1, N), np.int32)}
+    for k in range(N):
+        x = z[0, par[0, k] + 1].astype(np.float64)
+        e = np.exp(x - x.max())
+        a["draft_probs"][0, k] = (e / e.sum()).astype(np.float32)
+        a["tokens"][0, k] = int(np.argsort(-x)[k % 2])
+    for u in (0.05, 0.6, 0.95):
+        a["uniforms"] = np.full((1, N + 1), u, dtype=np.float32)
+        _compare(a, par, "sample")
+
+
 @pytest.mark.parametrize("B,T,V", [
     (1, 1, 1), (1, 1, 70000), (1, 63, 4100), (1, 64, 16383), (2, 65, 16388), (1, 128, 33000),   # nodes: one and two per lane
     (3, 60, 32764), (4, 60, 32768), (4, 63, 32772),          # one and two loads' worth more or less than a workgroup takes
