@@ -683,6 +683,174 @@ __global__ __launch_bounds__(THREADS, 2) void walk_sample_coop_kernel(CoopParams
   wk.finish(alive);
 }
 
+// The walk of many trees over large vocabularies, where slices of 4096 entries would be more workgroups than are resident
+// together: 512 threads, a workgroup for each CU at most, a slice of 8192 to 20480 entries each.  (The workgroups of a tree
+// follow each other in the grid: of a call that gets only some of the CUs at most one tree waits for others to end.)  A thread
+// holds the current distribution and one slice, of the candidate's draft or of the row that it brings, and looks at nothing
+// ahead.  What bounds it is the exponentials of a row (some 40 instructions of 4 cycles each) and the slices' bytes.
+// Measured (us; by a workgroup per tree, in front of it a pass over all logits / like this), trees x entries: 16 x 138253
+// 519 / 42, 21 x 103226 304 / 31, 32 x 128256 534 / 56, 64 x 70000 297 / 47, 128 x 32000 141 / 47, 200 x 9000 57 / 32, 250 x 12289
+// 73 / 37.
+constexpr int kWideThreads = 512;
+
+template <int PER>
+__global__ __launch_bounds__(kWideThreads) void walk_sample_wide_kernel(CoopParams params) {
+  constexpr int SLICE = kWideThreads * PER, WAVES = kWideThreads / 64;
+  __shared__ NodeTable nodes;
+  __shared__ double red_d[2][WAVES];
+  __shared__ float red_f[WAVES];
+  __shared__ double xs[64];  // (as above)
+  __shared__ double got[2];
+  __shared__ int got_ok;
+  __shared__ double pv_s;
+
+  Walk wk(params, nodes);
+  const CoopParams& p = wk.p;
+  const int tid = wk.tid, lane = wk.lane, wave = wk.wave;
+  const Walk::Part<PER> mine(wk.w * SLICE + tid * PER, wk.V);
+  float x[PER];     // a slice
+  double cur[PER];  // the current distribution
+  mine.load(x, wk.row_of(0));
+  wk.load_words();
+  if (wave == 0) wk.make_table();
+  __syncthreads();
+
+  double xs_mul = 1.0, px = 0.0;
+  bool alive = true;
+  int flip = 0, len = 0, k = wk.first_of_root();
+  Node node = wk.node(k);
+  float qx = 0.f;
+  // row `r`, whose slice is in x[] or on its way there, becomes the current one; behind it the draft slice of candidate k
+  auto adopt_row = [&](int r) {
+    const float logit = k >= 0 ? wk.row_of(r)[node.tok] : 0.f;
+    float m = -INFINITY;
+    const int skip = mine.first_that_counts();
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      x[u] = u >= skip ? x[u] : -INFINITY;
+      m = fmaxf(m, x[u]);
+    }
+    m = wave_max(m);
+    const Reference ref = reference_of(m, p.inv_temp);
+    double z = 0.0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      cur[u] = exp_from(x[u], p.inv_temp, ref);
+      z += cur[u];
+      __builtin_amdgcn_sched_barrier(0);  // (one after the other: there are no registers for several at a time)
+    }
+    z = wave_sum(z);
+    flip ^= 1;
+    if (lane == 0) {
+      red_d[flip][wave] = z;
+      red_f[wave] = m;
+    }
+    __syncthreads();
+    wk.open_exchange();
+    if (wave == 0) wk.publish_row(0, wk.put_together<WAVES>(red_d[flip][lane % WAVES], red_f[lane % WAVES]));
+    if (k >= 0) qx = (p.draft + node.draft)[node.tok];
+    const Reference ref_x = reference_of(logit, p.inv_temp);
+    const double e_x = exp_from(logit, p.inv_temp, ref_x);
+    if (wave == 0) {
+      unsigned pay[4] = {0u, 0u, 0u, 0u};
+      const bool ok = wk.await(0, 3, pay);
+      double K, total, own;
+      wk.row_total(pay, K, total, own);
+      xs[lane] = own;
+      if (lane == 0) {
+        got[0] = K;
+        got[1] = total;
+        got_ok = ok;
+      }
+    }
+    if (k >= 0) mine.load(x, p.draft + node.draft);
+    __syncthreads();
+    const double row_k = got[0], row_inv = 1.0 / got[1];
+    alive = got_ok != 0;
+    xs_mul = row_inv;
+    px = scaled_down(e_x, ref_x.k, row_k) * row_inv;
+    const double sc = scaled_down(row_inv, ref.k, row_k);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) cur[u] *= sc;
+  };
+  adopt_row(0);
+  while (alive && k >= 0) {
+    if ((double)__int_as_float(node.uni) * (double)qx < px) {
+      // ---- accepted: its row becomes the current one, its first child the candidate
+      if (tid == 0 && wk.w == 0) p.out_path[(long long)wk.b * p.max_depth + len] = k;
+      ++len;
+      const int row = k + 1;
+      mine.load(x, wk.row_of(row));
+      k = len < p.max_depth ? node.first : -1;
+      if (k >= 0) node = wk.node(k);
+      adopt_row(row);
+      continue;
+    }
+    // ---- rejected: the residual's mass, and its value at the next sibling's token
+    k = node.next;
+    if (k >= 0) node = wk.node(k);
+    const int next_tok = k >= 0 ? node.tok : 0;
+    double part = 0.0, at_x = 0.0, was_x = 0.0;
+    const int skip = mine.first_that_counts();
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const double res = u >= skip ? fmax(0.0, cur[u] - (double)x[u]) : 0.0;
+      part += res;
+      if (mine.at + u == next_tok) {
+        at_x = res;
+        was_x = cur[u];
+      }
+    }
+    if (mine.has(next_tok)) pv_s = at_x;  // (one thread of one workgroup; the sum's barrier orders it)
+    part = wave_sum(part);
+    flip ^= 1;
+    if (lane == 0) red_d[flip][wave] = part;
+    __syncthreads();
+    auto exchange = [&](double mass) {
+      wk.open_exchange();
+      if (wave == 0) {
+        wk.publish4(mass, pv_s);
+        unsigned pay[4] = {0u, 0u, 0u, 0u};
+        const bool ok = wk.await(0, 4, pay);
+        double s, at_owner;
+        const double own = wk.mass_total(pay, next_tok / SLICE, s, at_owner);
+        if (s > 0.0) xs[lane] = own;
+        if (lane == 0) {
+          got[0] = s;
+          got[1] = at_owner;
+          got_ok = ok;
+        }
+      }
+      __syncthreads();
+      alive = got_ok != 0;
+    };
+    exchange(wave == 0 ? Walk::sum_of<WAVES>(red_d[flip][lane % WAVES]) : 0.0);
+    const double s = got[0];
+    if (s > 0.0) {
+      const double inv = xs_mul = 1.0 / s;
+      px = got[1] * inv;
+      const int skip = mine.first_that_counts();
+#pragma unroll
+      for (int u = 0; u < PER; ++u) {
+        asm volatile("" : "+v"(x[u]));  // (worked out again: held since the sum, it would take as many registers as cur[])
+        cur[u] = u >= skip ? fmax(0.0, cur[u] - (double)x[u]) * inv : 0.0;
+      }
+    } else if (alive && k >= 0) {
+      // nothing left of the distribution: it stays as it was, and the next token's value under it has to be asked for
+      if (mine.has(next_tok)) pv_s = was_x;
+      __syncthreads();
+      exchange(0.0);
+      px = got[1];
+    }
+    if (k >= 0) {
+      qx = (p.draft + node.draft)[node.tok];
+      mine.load(x, p.draft + node.draft);
+    }
+  }
+  if (alive) wk.draw<PER, WAVES>(xs[lane] * xs_mul, cur, mine, len);
+  wk.finish(alive);
+}
+
 }  // namespace
 
 // The blocks of kCoopMaxTrees trees are part of every acceptance workspace, whatever a call's mode and
@@ -713,6 +881,8 @@ bool accept_coop_plan(int batch, int vocab, int cus, int* W, int* slice) {
   if (fits(kCoopThreads, 2, cus)) return true;
   for (int per = 4; per <= 16; per *= 2)
     if (fits(kCoopThreads, per, 2 * cus)) return true;  // (two workgroups of 256 threads per CU are resident together)
+  for (int per = 16; per <= 40; per += 8)
+    if (fits(kWideThreads, per, cus)) return true;
   return false;
 }
 
@@ -727,6 +897,7 @@ hipError_t launch_accept_coop(const AcceptArgs& a, void* coop_ws, int W, int sli
   cp.trees = static_cast<TreeBlock*>(coop_ws);
   cp.spin_limit = tuning().spin_limit >= 0 ? (unsigned)tuning().spin_limit : kDefaultSpinLimit;
   cp.out_path = a.out_path; cp.out_len = a.out_len; cp.out_bonus = a.out_bonus;
+  const dim3 grid((unsigned)(a.batch * W)), block_wide(kWideThreads);
   // A workgroup with a CU to itself has its slice among twice the threads: two waves on a SIMD fill each other's waits.  (us, 256
   // threads / 512: 1 x 128256 16.5 / 15.8, 8 x 32000 20.8 / 20.5; slices of 512 entries 11.7 / 12.0 at 1 x 8000: not those.)
   const bool lone = a.batch * W <= device_cu_count();
@@ -735,8 +906,13 @@ hipError_t launch_accept_coop(const AcceptArgs& a, void* coop_ws, int W, int sli
     case kCoopThreads * 4: return lone ? launch_walk<2, 512>(cp, a.batch * W, stream) : launch_walk<4, kCoopThreads>(cp, a.batch * W, stream);
     case kCoopThreads * 8: return lone ? launch_walk<4, 512>(cp, a.batch * W, stream) : launch_walk<8, kCoopThreads>(cp, a.batch * W, stream);
     case kCoopThreads * 16: return lone ? launch_walk<8, 512>(cp, a.batch * W, stream) : launch_walk<16, kCoopThreads>(cp, a.batch * W, stream);
+    case kWideThreads * 16: hipLaunchKernelGGL(walk_sample_wide_kernel<16>, grid, block_wide, 0, stream, cp); break;
+    case kWideThreads * 24: hipLaunchKernelGGL(walk_sample_wide_kernel<24>, grid, block_wide, 0, stream, cp); break;
+    case kWideThreads * 32: hipLaunchKernelGGL(walk_sample_wide_kernel<32>, grid, block_wide, 0, stream, cp); break;
+    case kWideThreads * 40: hipLaunchKernelGGL(walk_sample_wide_kernel<40>, grid, block_wide, 0, stream, cp); break;
     default: return hipErrorInvalidValue;
   }
+  return hipGetLastError();
 }
 
 // Calibration: a pure 128-bit streaming read of `bytes` bytes (nothing is computed or written

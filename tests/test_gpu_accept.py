@@ -571,7 +571,7 @@ def _near_the_target(a, par, rng, sigma):
 @pytest.mark.parametrize("V", [1, 2, 5, 1023, 1024, 1025, 4099, 65535, 65536, 65537, 131071, 131073, 262145])
 def test_sample_vocabularies_at_the_edges_of_a_threads_share(V):
     """4, 8 and 16 entries a thread, the last workgroup with one entry or a full slice, one workgroup per tree, and more
-    than 64 workgroups' worth (the one-workgroup walk); walks that accept several tokens with and without a rejection in
+    than 64 workgroups' worth (longer slices, 512 threads each); walks that accept several tokens with and without a rejection in
     front of them, at an odd depth limit too."""
     rng = np.random.default_rng(V)
     B = 2
@@ -586,11 +586,12 @@ def test_sample_vocabularies_at_the_edges_of_a_threads_share(V):
     assert skipped <= (3 if V <= 5 else 0)
 
 
-def test_sample_residual_that_vanishes_in_the_middle_of_the_siblings():
+@pytest.mark.parametrize("V", [3000, 262145], ids=["256-threads", "512-threads"])
+def test_sample_residual_that_vanishes_in_the_middle_of_the_siblings(V):
     """Draft probabilities that cover the target's everywhere (twice its distribution): after the rejection nothing is left,
     the distribution stays as it was, and the next siblings are tested against it."""
     rng = np.random.default_rng(3)
-    V, N = 3000, 6
+    N = 6
     a = {"logits": rng.standard_normal((1, N + 1, V)).astype(np.float32) * 2, "draft_probs": np.empty((1, N, V), np.float32)}
     z = a["logits"][0, 0].astype(np.float64)
     p = np.exp(z - z.max())
@@ -604,6 +605,19 @@ def test_sample_residual_that_vanishes_in_the_middle_of_the_siblings():
         for single in (0, 1):
             tune("accept_single", single)
             assert _compare(a, par, "sample") == 0
+
+
+@pytest.mark.parametrize("B,V", [(2, 262144 + 8192), (18, 114689), (22, 135169), (28, 147457), (250, 12289), (12, 327680 - 1)])
+def test_sample_many_trees_of_large_vocabularies(B, V):
+    """More than 512 workgroups of 4096 entries, or 64 of one tree: workgroups of 512 threads with 16, 24, 32 and 40 entries
+    each, the last one with a full slice or a single entry."""
+    rng = np.random.default_rng(B)
+    cfg = CONFIGS["c3_llama3_8b"].with_(vocab=V, batch=B, n_tree=4)
+    par = np.tile(np.array([-1, -1, 0, 1], dtype=np.int32), (B, 1))
+    par[B // 2] = [-1, 0, 1, 2]
+    a = accept_inputs(cfg, par, seed=V)
+    _near_the_target(a, par, rng, 0.3)
+    assert _compare(a, par, "sample", max_depth=3) <= 1 + B // 50
 
 
 @pytest.mark.parametrize("rows", ["huge", "lowest", "masked"])
