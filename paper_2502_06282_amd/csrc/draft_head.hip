@@ -563,7 +563,7 @@ MoePlan moe_plan(int rows, int d, int f, int n) {
   const int each = (2 * rows + used - 1) / used;
   const double mean = 2.0 * rows / n, likely = std::ceil(mean + 3.0 * std::sqrt(mean * (1.0 - 2.0 / n)));
   m.used = used;
-  m.ring_rows = ring_gemm_takes_experts((int)likely, used, d, f) ? (int)likely : 0;
+  m.ring_rows = ring_gemm_takes_experts(mean, (int)likely, used, d, f) ? (likely < kRingRows ? (int)likely : kRingRows) : 0;
   m.split1 = m.ring_rows ? 1 : stream_gemm_ksplit(each, f, d, used, true, 7000);  // gate and up in one launch
   m.split2 = m.ring_rows ? 1 : stream_gemm_ksplit(each, d, f, used, false, 0);
   const size_t pre = m.split1 > 1 ? up((size_t)m.split1 * n * rows * f * 4) : 0;

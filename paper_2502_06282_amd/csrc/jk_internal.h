@@ -190,8 +190,9 @@ hipError_t launch_stream_gemm_pair(const StreamGemmArgs& p, hipStream_t stream);
 hipError_t launch_stream_gemm_down(const StreamGemmArgs& p, hipStream_t stream);  // m <= 128
 // the same products with equal shares of the weight rows.  rows: how many an expert is likely to have at most (others take
 // several passes over its weights), items: how many experts are likely to be chosen
+constexpr int kRingRows = 32;  // of X at a time
 bool ring_gemm_takes_heads(int m, int n);
-bool ring_gemm_takes_experts(int rows, int items, int d_model, int d_ff);
+bool ring_gemm_takes_experts(double mean, int likely, int items, int d_model, int d_ff);
 hipError_t launch_ring_gemm_heads(const StreamGemmArgs& p, hipStream_t stream);
 hipError_t launch_ring_gemm_pair(const StreamGemmArgs& p, int rows, int items, hipStream_t stream);
 hipError_t launch_ring_gemm_down(const StreamGemmArgs& p, int rows, int items, hipStream_t stream);

@@ -36,7 +36,6 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 enum RingKind { HEADS, PAIR, DOWN };
 
 constexpr int kWaves = 4, kRingThreads = 64 * kWaves, kUnit = 64;  // a unit: 64 of k
-constexpr int kRingRows = 32;  // of X at a time
 constexpr int kMaxRows = 128, kMaxRingExperts = 64, kMaxItems = kMaxRingExperts + 2 * kMaxRows / 8;
 
 // RG: groups of eight rows of X, NF: groups of 16 weight rows in a batch
@@ -368,10 +367,15 @@ bool strips_fill(int strips) {
 
 // Against strips of 128 rows in turns of workgroups (stream_gemm.hip), over 66 shapes drawn from 1 - 80 rows: heads 0.97 - 1.35
 // times as fast where this takes them, 1.11 in the geometric mean; below two groups per CU, where the strips' kernel divides
-// k, 0.90 - 1.04, beyond 32 rows 0.90 - 1.07.  Experts 0.94 - 1.69, 1.14 in the mean; with more rows 0.88 - 1.15.
+// k, 0.90 - 1.04, beyond 32 rows 0.90 - 1.07.
 bool ring_gemm_takes_heads(int m, int n) { return m <= kRingRows && n >= 32 * device_cu_count() && !strips_fill((n + 127) / 128); }
-bool ring_gemm_takes_experts(int rows, int items, int d_model, int d_ff) {
-  return rows <= kRingRows && !(strips_fill(items * ((d_ff + 63) / 64)) && strips_fill(items * ((d_model + 127) / 128)));
+// Experts of `mean` rows, and hardly ever more than `likely`: 0.94 - 1.69 times as fast, 1.14 in the mean, over those 66.  One that
+// has more than 32 rows has its weights gone through once per block of so many.  That costs little where few experts do (up
+// to 25 rows in the mean: eleven shapes 1.02 - 1.21; 26 - 30 rows 0.86 - 1.14) or where both launches' strips would leave four
+// fifths of the CUs without work (nine shapes of 46 - 80 rows 1.08 - 1.40); elsewhere it was 0.59 - 1.09.
+bool ring_gemm_takes_experts(double mean, int likely, int items, int d_model, int d_ff) {
+  const int pair = items * ((d_ff + 63) / 64), down = items * ((d_model + 127) / 128), few = device_cu_count() / 5;
+  return (likely <= kRingRows || mean <= 25.0 || (pair <= few && down <= few)) && !(strips_fill(pair) && strips_fill(down));
 }
 hipError_t launch_ring_gemm_heads(const StreamGemmArgs& p, hipStream_t stream) { return launch_rows<HEADS>(p, p.m, 1, stream); }
 hipError_t launch_ring_gemm_pair(const StreamGemmArgs& p, int rows, int items, hipStream_t stream) { return launch_rows<PAIR>(p, rows, items, stream); }

@@ -260,6 +260,8 @@ def test_more_rows_than_an_expert_is_likely_to_have(rows, d, f, n):
         np.testing.assert_array_equal(f_top[r], f_top[r % 2])
 
 
-@pytest.mark.parametrize("rows,d,f,n", [(1, 1920, 896, 8), (35, 640, 1664, 8), (12, 128, 128, 3), (18, 1024, 2432, 5), (24, 4352, 256, 6)])
+@pytest.mark.parametrize("rows,d,f,n", [(1, 1920, 896, 8), (35, 640, 1664, 8), (12, 128, 128, 3), (18, 1024, 2432, 5), (24, 4352, 256, 6),
+                                        (46, 640, 512, 2), (80, 768, 512, 4), (128, 384, 256, 2),  # several blocks of 32 rows each
+                                        (62, 640, 1664, 5), (50, 256, 6400, 4)])                  # a mean just below 25 rows, and 25
 def test_equal_shares_of_the_experts_rows(rows, d, f, n):
     _check(moe_inputs(rows, d, f, n, seed=rows + 7), min_gap=1e-6)
