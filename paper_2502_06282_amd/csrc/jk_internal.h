@@ -178,11 +178,11 @@ int stream_gemm_ksplit(int m, int n, int k, int batch, bool pair, int split_ns, 
 hipError_t launch_stream_gemm(const StreamGemmArgs& p, hipStream_t stream);       // m <= 256
 // plain products with `finish` of few rows and columns, in one launch
 struct NarrowPlan {
-  int strip, strips, parts;  // weight rows of a workgroup, strips, parts of k (1 or 2; 0: not possible)
+  int strip, strips, rows, blocks, parts;  // weight rows of a workgroup, strips, rows of X, blocks of those, parts of k (1 or 2; 0: not possible)
   double ns;
 };
 NarrowPlan narrow_plan(int m, int n, int k);
-size_t narrow_gemm_bytes(const NarrowPlan& plan, int m);
+size_t narrow_gemm_bytes(const NarrowPlan& plan);
 hipError_t launch_narrow_gemm(const StreamGemmArgs& p, const NarrowPlan& plan, void* workspace, hipStream_t stream);
 unsigned long long meeting_tag();  // another one for every launch (see dev::second_to_meet)
 hipError_t launch_stream_gemm_heads(const StreamGemmArgs& p, hipStream_t stream);  // m <= 32

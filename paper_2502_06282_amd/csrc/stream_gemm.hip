@@ -503,12 +503,13 @@ struct NarrowArgs {
   float* y;
   uint16_t* out_bf16;
   int m, n, k, strip, strips;
+  int rows;                // of X for a workgroup
   int parts;               // of the k range
   float* part;             // parts > 1: their sums, one workgroup's behind the other's
-  unsigned long long* words;  // and a word per strip, kWordStep apart
+  unsigned long long* words;  // and a word per strip and block, kWordStep apart
   unsigned long long tag;
 };
-// Y = X . W^T (+ residual) for up to 64 rows and at most 64 columns per CU: a workgroup per CU has its strip of weight rows and
+// Y = X . W^T (+ residual) for up to 128 rows and at most 64 columns per CU: a workgroup per CU has its strip of weight rows and
 // all of k, its waves every eighth (fourth) 64 of k each (128-byte lines of W's and X's rows), and adds the waves' sums up
 // in LDS.  Against parts of k per workgroup it saves writing the partial results and the launch that adds them up; in exchange
 // every CU draws all of X from its L2.  What bounds it is HBM's share of the weights and, beyond some twenty rows, what a CU
@@ -516,11 +517,14 @@ struct NarrowArgs {
 // ask for neighbouring addresses, as in the matrix operands' layout, whoever else draws.  So both operands come by LDS, each
 // wave's through a ring of its own, up to six units ahead: no barriers, no registers.  With many rows and a long k two
 // workgroups share a strip of twice the rows: half of X for each, and the second of them to finish adds up both (1.3 us:
-// four parts save no more than their meeting costs).
+// four parts save no more than their meeting costs).  Many rows of few columns are shared instead: two workgroups have a strip
+// of twice the width and half of X's rows each and go through k in step, so that one of them draws the strip's weights from the
+// L2 that both share (each with a start of its own 80 x 8192 x 8192 took 47 us, and takes 35).
 // Measured (us, weights cold, before / now; before: weights in the operands' layout, X through registers, or strips of 128
 // rows in parts of k and a second launch): 4096 x 4096, 8 rows 8.0 / 7.9, 16 8.9 / 8.3, 40 12.3 / 10.9, 64 15.0 / 12.1; 6144 x
 // 4096, 8 11.1 / 10.7, 40 15.3 / 13.5, 64 18.2 / 15.9; 4096 x 8192, 8 14.4 / 14.1, 40 21.3 / 17.4, 64 22.9 / 20.0; 12288 x
-// 4096, 45 26.9 / 21.3; 8192 x 16384, 20 60.0 / 48.6.  Reading the weights alone takes 7.0, 9.5, 12.3, ..., 43.
+// 4096, 45 26.9 / 21.3; 8192 x 16384, 20 60.0 / 48.6.  With X's rows shared: 4096 x 4096, 64 rows 12.5 / 11.9, 80 18.3 / 13.0, 128
+// 21.3 / 15.8; 1024 x 2048, 64 6.2 / 5.2, 80 10.3 / 6.1; 3072 x 1024, 128 16.9 / 6.5; 8192 x 4096, 80 23.7 / 19.8.  Reading the weights alone takes 7.0, 9.5, 12.3, ..., 43.
 // RG: groups of eight rows of X; NF: groups of 16 weight rows
 
 // waves of a workgroup: eight, or four where LDS has no room for two units of each
@@ -552,17 +556,19 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void narrow_gemm_kernel(Narr
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, g = lane >> 4;
   const int all = gridDim.x, blk = blockIdx.x;
   const int id = all % 8 == 0 ? (blk & 7) * (all >> 3) + (blk >> 3) : blk;  // (neighbours on one XCD share lines of Y)
-  const int strip = id / p.parts, z = id - strip * p.parts;
+  // (the blocks of X's rows are the grid's second dimension: what shares a strip's weights runs on one XCD, and in step)
+  const int strip = id / p.parts, z = id - strip * p.parts, row0 = (int)blockIdx.y * p.rows, m = min(p.m - row0, p.rows);
+  const int meet = strip + (int)blockIdx.y * p.strips;
   const int n_base = strip * p.strip, n_end = min(n_base + p.strip, p.n);
   const int units = p.k / UK, u0 = (int)((long long)z * units / p.parts), u1 = (int)((long long)(z + 1) * units / p.parts);
   // (byte offsets from one scalar address each; rows past the end repeat the last one, and are not stored)
-  const uint16_t *w0 = dev::uniform_ptr(p.w + (long long)n_base * p.k), *x0 = dev::uniform_ptr(p.x);
+  const uint16_t *w0 = dev::uniform_ptr(p.w + (long long)n_base * p.k), *x0 = dev::uniform_ptr(p.x + (long long)row0 * p.k);
   const int lrow = lane / C::CHUNKS, lcol = 16 * (lane % C::CHUNKS ^ C::swizzle(lrow));
   unsigned wr[C::WI], xr[C::XI];
 #pragma unroll
   for (int i = 0; i < C::WI; ++i) wr[i] = (unsigned)min(C::RPI * i + lrow, n_end - 1 - n_base) * (unsigned)p.k * 2u + lcol;
 #pragma unroll
-  for (int i = 0; i < C::XI; ++i) xr[i] = (unsigned)min(C::RPI * i + lrow, p.m - 1) * (unsigned)p.k * 2u + lcol;
+  for (int i = 0; i < C::XI; ++i) xr[i] = (unsigned)min(C::RPI * i + lrow, m - 1) * (unsigned)p.k * 2u + lcol;
   unsigned char* ring = smem + wave * C::RING;
   const unsigned ring_at = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)ring;
   const int count = (u1 - u0 - wave + WAVES - 1) / WAVES;  // this wave's units
@@ -653,8 +659,8 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void narrow_gemm_kernel(Narr
   auto finish = [&](int i, floatx4 v) {
     // (a lane of a tile has row lane % 16 of X and four consecutive columns)
     const int tile = i >> 6, row = (tile % MT) * 16 + (i & 15), col = n_base + (tile / MT) * 16 + ((i & 63) >> 4) * 4;
-    if (row >= p.m || col >= n_end) return;
-    const long long at = (long long)row * p.n + col;
+    if (row >= m || col >= n_end) return;
+    const long long at = (long long)(row0 + row) * p.n + col;
     if (vec && col + 4 <= n_end) {
       if (p.residual) {
         const uint2 q = *reinterpret_cast<const uint2*>(p.residual + at);
@@ -679,7 +685,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void narrow_gemm_kernel(Narr
     }
   };
   constexpr int QUADS = TILES * 64;  // of a workgroup's results
-  float* own_part = p.part + (size_t)id * (QUADS * 4);
+  float* own_part = p.part + (size_t)(meet * p.parts + z) * (QUADS * 4);
   for (int i = tid; i < QUADS; i += 64 * WAVES) {
     floatx4 part[WAVES];
 #pragma unroll
@@ -692,8 +698,8 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void narrow_gemm_kernel(Narr
     else dev::store_through(own_part + 4 * i, __builtin_bit_cast(dev::store_u32x4, part[0]));
   }
   if (p.parts == 1) return;
-  if (!dev::second_to_meet(p.words + (size_t)strip * kWordStep, p.tag, reinterpret_cast<int*>(smem))) return;
-  const auto both = __builtin_amdgcn_make_buffer_rsrc(p.part + (size_t)strip * (2 * QUADS * 4), 0, 2 * QUADS * 16, 0x00020000);
+  if (!dev::second_to_meet(p.words + (size_t)meet * kWordStep, p.tag, reinterpret_cast<int*>(smem))) return;
+  const auto both = __builtin_amdgcn_make_buffer_rsrc(p.part + (size_t)meet * (2 * QUADS * 4), 0, 2 * QUADS * 16, 0x00020000);
   for (int i = tid; i < QUADS; i += 64 * WAVES) {  // (the same sum whoever comes second)
     const u32x4 low = __builtin_amdgcn_raw_buffer_load_b128(both, i * 16, 0, dev::kDeviceScope);
     const u32x4 high = __builtin_amdgcn_raw_buffer_load_b128(both, i * 16, QUADS * 16, dev::kDeviceScope);
@@ -702,65 +708,69 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void narrow_gemm_kernel(Narr
 }
 
 template <int RG, int NF>
-hipError_t launch_narrow(const NarrowArgs& p, hipStream_t stream) {
+hipError_t launch_narrow(const NarrowArgs& p, int blocks, hipStream_t stream) {
   static LdsLimitRaised raised;
   constexpr int WAVES = narrow_waves(RG, NF);
   constexpr int smem = NarrowCfg<RG, NF, WAVES>::SMEM;
   if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(narrow_gemm_kernel<RG, NF, WAVES>), smem, raised); e != hipSuccess) return e;
-  hipLaunchKernelGGL((narrow_gemm_kernel<RG, NF, WAVES>), dim3((unsigned)(p.strips * p.parts)), dim3(64 * WAVES), smem, stream, p);
+  hipLaunchKernelGGL((narrow_gemm_kernel<RG, NF, WAVES>), dim3((unsigned)(p.strips * p.parts), (unsigned)blocks), dim3(64 * WAVES), smem, stream, p);
   return hipGetLastError();
 }
 template <int RG>
-hipError_t launch_narrow_rows(const NarrowArgs& p, hipStream_t stream) {
+hipError_t launch_narrow_rows(const NarrowArgs& p, int blocks, hipStream_t stream) {
   switch ((p.strip + 15) / 16) {
-    case 1: return launch_narrow<RG, 1>(p, stream);
-    case 2: return launch_narrow<RG, 2>(p, stream);
-    case 3: return launch_narrow<RG, 3>(p, stream);
-    case 4: return launch_narrow<RG, 4>(p, stream);
+    case 1: return launch_narrow<RG, 1>(p, blocks, stream);
+    case 2: return launch_narrow<RG, 2>(p, blocks, stream);
+    case 3: return launch_narrow<RG, 3>(p, blocks, stream);
+    case 4: return launch_narrow<RG, 4>(p, blocks, stream);
     default: return hipErrorInvalidValue;
   }
 }
 }  // namespace
 
-// Strips of at most 64 weight rows, and k in one or two parts, by the estimated time: HBM's share of the weights beside what
-// a CU draws of its weights and of X, a start and an end, the meeting of two parts, and four waves instead of eight.  Over 45
-// shapes (1 - 64 rows, 832 - 16384 columns, k 768 - 16384) the estimate is off by 4 % and the choice 0.4 % behind the better.
+// Strips of at most 64 weight rows, X's rows in blocks of at most 64, and k in one or two parts, by the estimated time: HBM's
+// share of the weights beside what a CU draws of its weights and of X, a start and an end, the meeting of two parts, and four
+// waves instead of eight.  Over 45 shapes (1 - 64 rows, 832 - 16384 columns, k 768 - 16384) the estimate is off by 4 % and the choice 0.4 %
+// behind the better.
 NarrowPlan narrow_plan(int m, int n, int k) {
-  const int cus = device_cu_count(), groups = (m + 7) / 8;
-  NarrowPlan best{0, 0, 0, 0.0};
-  if (m > 64) return best;
-  for (int parts = 1; parts <= 2; ++parts) {
-    const int most = cus / parts;  // strips
-    if (most < 1 || n > 64 * (long long)most) break;
-    const int strip = ((n + most - 1) / most + 3) / 4 * 4, frags = (strip + 15) / 16;
-    const double cu = 2.0 * k / parts * (strip + 8.0 * groups) / 65.0, hbm = 2.0 * n * k / 6400.0;
-    const double ns = 2700.0 + std::cbrt(cu * cu * cu + hbm * hbm * hbm) + (parts > 1 ? 1250.0 : 0.0) + (narrow_waves(groups, frags) == 4 ? 1350.0 : 0.0);
-    if (best.parts == 0 || ns < best.ns) best = NarrowPlan{strip, (n + strip - 1) / strip, parts, ns};
+  const int cus = device_cu_count();
+  NarrowPlan best{0, 0, 0, 0, 0, 0.0};
+  for (int blocks = (m + 63) / 64; blocks <= 2; ++blocks) {
+    const int rows = ((m + blocks - 1) / blocks + 7) / 8 * 8;
+    if (rows * (blocks - 1) >= m) break;  // (nothing left for the last one)
+    for (int parts = 1; parts <= 2; ++parts) {
+      const int most = cus / (parts * blocks);  // strips
+      if (most < 1 || n > 64 * (long long)most) break;
+      const int strip = ((n + most - 1) / most + 3) / 4 * 4, frags = (strip + 15) / 16;
+      const double cu = 2.0 * k / parts * (strip + rows) / 65.0, hbm = 2.0 * n * k / 6400.0;
+      const double ns = 2700.0 + std::cbrt(cu * cu * cu + hbm * hbm * hbm) + (parts > 1 ? 1250.0 : 0.0) + (narrow_waves(rows / 8, frags) == 4 ? 1350.0 : 0.0);
+      if (best.parts == 0 || ns < best.ns) best = NarrowPlan{strip, (n + strip - 1) / strip, rows, blocks, parts, ns};
+    }
   }
   return best;
 }
-size_t narrow_gemm_bytes(const NarrowPlan& plan, int m) {
+size_t narrow_gemm_bytes(const NarrowPlan& plan) {
   if (plan.parts <= 1) return 0;
-  const size_t tiles = (size_t)((plan.strip + 15) / 16) * ((m + 15) / 16);
-  return (size_t)plan.strips * (kWordStep * 8 + plan.parts * tiles * 1024);
+  const size_t tiles = (size_t)((plan.strip + 15) / 16) * ((plan.rows + 15) / 16);
+  return (size_t)plan.strips * plan.blocks * (kWordStep * 8 + plan.parts * tiles * 1024);
 }
 hipError_t launch_narrow_gemm(const StreamGemmArgs& g, const NarrowPlan& plan, void* workspace, hipStream_t stream) {
   NarrowArgs p;
   p.x = g.x; p.w = g.w; p.residual = g.residual; p.y = g.y; p.out_bf16 = g.out_bf16;
   p.m = g.m; p.n = g.n; p.k = g.k;
-  p.strip = plan.strip; p.strips = plan.strips; p.parts = plan.parts;
+  p.strip = plan.strip; p.strips = plan.strips; p.rows = plan.rows; p.parts = plan.parts;
   p.words = static_cast<unsigned long long*>(workspace);
-  p.part = reinterpret_cast<float*>(static_cast<char*>(workspace) + (size_t)plan.strips * (kWordStep * 8));
+  p.part = reinterpret_cast<float*>(static_cast<char*>(workspace) + (size_t)plan.strips * plan.blocks * (kWordStep * 8));
   p.tag = meeting_tag();
-  switch ((g.m + 7) / 8) {
-    case 1: return launch_narrow_rows<1>(p, stream);
-    case 2: return launch_narrow_rows<2>(p, stream);
-    case 3: return launch_narrow_rows<3>(p, stream);
-    case 4: return launch_narrow_rows<4>(p, stream);
-    case 5: return launch_narrow_rows<5>(p, stream);
-    case 6: return launch_narrow_rows<6>(p, stream);
-    case 7: return launch_narrow_rows<7>(p, stream);
-    case 8: return launch_narrow_rows<8>(p, stream);
+  switch (plan.rows / 8) {
+    case 1: return launch_narrow_rows<1>(p, plan.blocks, stream);
+    case 2: return launch_narrow_rows<2>(p, plan.blocks, stream);
+    case 3: return launch_narrow_rows<3>(p, plan.blocks, stream);
+    case 4: return launch_narrow_rows<4>(p, plan.blocks, stream);
+    case 5: return launch_narrow_rows<5>(p, plan.blocks, stream);
+    case 6: return launch_narrow_rows<6>(p, plan.blocks, stream);
+    case 7: return launch_narrow_rows<7>(p, plan.blocks, stream);
+    case 8: return launch_narrow_rows<8>(p, plan.blocks, stream);
     default: return hipErrorInvalidValue;
   }
 }

@@ -112,7 +112,7 @@ def test_row_blocks_strips_and_k_parts_at_their_edges(m, n, k):
     assert torch.isnan(both[0]).all() and torch.isnan(both[1, 0])
 
 
-@pytest.mark.parametrize("m", [1, 8, 9, 16, 17, 40, 48, 49, 64])
+@pytest.mark.parametrize("m", [1, 8, 9, 16, 17, 40, 48, 49, 64, 65, 72, 81, 97, 113, 128])
 @pytest.mark.parametrize("n,k", [
     (1, 128), (7, 384), (1025, 640), (2047, 1024), (2500, 1152),        # strips of 4 - 12 rows; waves without a share of k,
     (4096, 2048), (4100, 1664), (6144, 4096), (8190, 1024),             # with one, with an odd number of them
@@ -139,7 +139,8 @@ def _exact_case(m, n, k, seed):
     return x, w, r, x @ w.T + r                                           # (exact in fp32: multiples of 1/8 below 2^14)
 
 
-@pytest.mark.parametrize("m,n,k", [(64, 4096, 4096), (41, 4096, 8192), (24, 4100, 8320), (57, 8191, 8192), (64, 2049, 8064), (33, 5120, 10240)])
+@pytest.mark.parametrize("m,n,k", [(64, 4096, 4096), (41, 4096, 8192), (24, 4100, 8320), (57, 8191, 8192), (64, 2049, 8064), (33, 5120, 10240),
+                                   (65, 4096, 4096), (128, 2048, 4096), (97, 4096, 8192), (73, 6141, 4096)])  # X in two blocks, with and without parts of k
 def test_two_workgroups_per_strip_are_bit_exact(m, n, k):
     """Products whose k is cut in two: the second workgroup of a strip to finish adds up both.  The workspace may hold
     anything (its words are not cleared for the call), is used by several calls in turn, and nothing is written behind it."""
