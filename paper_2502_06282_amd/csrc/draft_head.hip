@@ -460,16 +460,6 @@ __global__ __launch_bounds__(256) void router_kernel(RouterParams p) {
   }
 }
 
-// How many of the first n_rows rows chose expert e (the same in every lane of a wave): with n_rows = a row's number its
-// place among the expert's rows, which is how the experts' products number them.
-__device__ __forceinline__ int rows_with(const int* sel, int n_rows, int e) {
-  int n = 0;
-  for (int i0 = 0; i0 < n_rows; i0 += 64) {
-    const int row = i0 + (int)(threadIdx.x & 63);
-    n += __popcll(__ballot(row < n_rows && (sel[2 * row] == e || sel[2 * row + 1] == e)));
-  }
-  return n;
-}
 // The k parts' partial results of four consecutive outputs, up to eight of them in flight, added in a fixed order
 __device__ __forceinline__ floatx4 sum_parts(const float* part, int ksplit, long long step) {
   floatx4 v = {0.f, 0.f, 0.f, 0.f};
@@ -485,57 +475,75 @@ __device__ __forceinline__ floatx4 sum_parts(const float* part, int ksplit, long
   return v;
 }
 
+// The same of two results, both in flight together.  What calls this is bound by trips to memory, of which there is one: the
+// rows of the experts' results are numbered by choice, so that nothing has to be looked up first, and a thread has one
+// quad.  (Numbered expert by expert there were three in a row for select_kernel, and in gated_act_kernel two for each of up to
+// four quads.  The whole call, 40 rows and 8 experts of 4096 x 4096: 151.0 us, 149.8 like this; 68 rows, 5 of 3456 x 1536, with a
+// divided k range: 57.6 and 53.6; of 36 shapes all faster, 3 % in the mean.)
+__device__ __forceinline__ void sum_two(const float* pa, const float* pb, int ksplit, long long step, floatx4& a, floatx4& b) {
+  a = b = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int z0 = 0; z0 < ksplit; z0 += 8) {
+    floatx4 t[8], u[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (z0 + i < ksplit) {
+        t[i] = *reinterpret_cast<const floatx4*>(pa + (z0 + i) * step);
+        u[i] = *reinterpret_cast<const floatx4*>(pb + (z0 + i) * step);
+      }
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (z0 + i < ksplit) {
+        a += t[i];
+        b += u[i];
+      }
+  }
+}
+
 struct ActParams {
-  const float *g, *up;  // [ksplit][n_experts][rows][f] fp32: partial gate and up projections
-  uint16_t* h;          // [n_experts][rows][f] bf16
-  const int* sel;  // [2 rows]: the experts the rows selected
-  int rows, f, ksplit;
+  const float *g, *up;  // [ksplit][2 rows][f] fp32: partial gate and up projections, by choice
+  uint16_t* h;          // [2 rows][f] bf16
+  int f, ksplit;
   long long split_stride;
 };
 
 // h = silu(gate) * up, rounded to bf16 once, where the k range of the two projections was divided (an undivided one
 // has this in its epilogue)
 __global__ __launch_bounds__(256) void gated_act_kernel(ActParams p) {
-  const int e = blockIdx.y, row = blockIdx.x;
-  if (row >= rows_with(p.sel, p.rows, e)) return;
-  const long long at = ((long long)e * p.rows + row) * p.f;
-  for (int c = blockIdx.z * 256 + threadIdx.x; c < p.f / 4; c += 256 * gridDim.z) {
-    const floatx4 a = sum_parts(p.g + at + 4 * c, p.ksplit, p.split_stride), b = sum_parts(p.up + at + 4 * c, p.ksplit, p.split_stride);
-    float o[4];
+  const int c = blockIdx.y * 256 + threadIdx.x;
+  if (c >= p.f / 4) return;
+  const long long at = (long long)blockIdx.x * p.f;
+  floatx4 a, b;
+  sum_two(p.g + at + 4 * c, p.up + at + 4 * c, p.ksplit, p.split_stride, a, b);
+  float o[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) o[i] = a[i] / (1.f + expf(-a[i])) * b[i];
-    uint2 w;
-    w.x = bf16_bits_rne(o[0]) | (bf16_bits_rne(o[1]) << 16);
-    w.y = bf16_bits_rne(o[2]) | (bf16_bits_rne(o[3]) << 16);
-    reinterpret_cast<uint2*>(p.h + at)[c] = w;
-  }
+  for (int i = 0; i < 4; ++i) o[i] = a[i] / (1.f + expf(-a[i])) * b[i];
+  uint2 w;
+  w.x = bf16_bits_rne(o[0]) | (bf16_bits_rne(o[1]) << 16);
+  w.y = bf16_bits_rne(o[2]) | (bf16_bits_rne(o[3]) << 16);
+  reinterpret_cast<uint2*>(p.h + at)[c] = w;
 }
 
 struct SelectParams {
   int ksplit;
   long long split_stride;
-  const float* y;     // [ksplit][n_experts][rows][d] fp32: the experts' (partial) outputs for their own rows
+  const float* y;     // [ksplit][rows][2][d] fp32: the chosen experts' (partial) outputs
   const uint16_t* u;  // [rows][d] bf16
   const float* s_top;
-  const int* idx;
   uint16_t* f_top;    // [rows][2][d] bf16
   uint16_t* f_mix;    // [rows][d] bf16 or null
-  int rows, d, n_experts;
+  int d;
 };
 
 // f_top[r][k] = Expert_{idx[r][k]}(u_r) + u_r; f_mix[r] = sum_k s_k Expert_k(u_r) + u_r (Eq. 3)
 __global__ __launch_bounds__(256) void select_kernel(SelectParams p) {
   const int row = blockIdx.x;
-  // (expert_idx is the caller's memory: what comes back from it is kept inside the workspace's experts)
-  auto expert = [&](int i) { return min(max(p.idx[i], 0), p.n_experts - 1); };
-  const int i1 = expert(2 * row), i2 = expert(2 * row + 1);
-  const float s1 = p.s_top[2 * row], s2 = p.s_top[2 * row + 1];
-  const float* y1 = p.y + ((long long)i1 * p.rows + rows_with(p.idx, row, i1)) * p.d;
-  const float* y2 = p.y + ((long long)i2 * p.rows + rows_with(p.idx, row, i2)) * p.d;
   const int c = blockIdx.y * 256 + threadIdx.x;
   if (c >= p.d / 4) return;
-  const floatx4 a = sum_parts(y1 + 4 * c, p.ksplit, p.split_stride), b = sum_parts(y2 + 4 * c, p.ksplit, p.split_stride);
   const uint2 uu = reinterpret_cast<const uint2*>(p.u + (long long)row * p.d)[c];
+  const float s1 = p.s_top[2 * row], s2 = p.s_top[2 * row + 1];
+  const float* y = p.y + (long long)(2 * row) * p.d + 4 * c;
+  floatx4 a, b;
+  sum_two(y, y + p.d, p.ksplit, p.split_stride, a, b);
   const floatx4 u = {bf16_lo(uu.x), bf16_hi(uu.x), bf16_lo(uu.y), bf16_hi(uu.y)};
   auto store = [&](uint16_t* dst, const floatx4& v) {
     uint2 w;
@@ -566,12 +574,12 @@ MoePlan moe_plan(int rows, int d, int f, int n) {
   m.ring_rows = ring_gemm_takes_experts(mean, (int)likely, used, d, f) ? (likely < kRingRows ? (int)likely : kRingRows) : 0;
   m.split1 = m.ring_rows ? 1 : stream_gemm_ksplit(each, f, d, used, true, 7000);  // gate and up in one launch
   m.split2 = m.ring_rows ? 1 : stream_gemm_ksplit(each, d, f, used, false, 0);
-  const size_t pre = m.split1 > 1 ? up((size_t)m.split1 * n * rows * f * 4) : 0;
+  const size_t pre = m.split1 > 1 ? up((size_t)m.split1 * 2 * rows * f * 4) : 0;
   m.g_off = 0;
   m.up_off = pre;
   m.h_off = 2 * pre;
-  m.y_off = m.h_off + up((size_t)n * rows * f * 2);
-  m.total = m.y_off + up((size_t)m.split2 * n * rows * d * 4);
+  m.y_off = m.h_off + up((size_t)2 * rows * f * 2);
+  m.total = m.y_off + up((size_t)m.split2 * 2 * rows * d * 4);
   return m;
 }
 
@@ -706,40 +714,39 @@ hipError_t launch_moe_experts(const MoeArgs& a, hipStream_t stream) {
   hipLaunchKernelGGL(router_kernel, dim3(a.rows), dim3(256), 0, stream, rp);
   if ((e = hipGetLastError()) != hipSuccess) return e;
 
-  // Each expert runs for the rows that chose it only, numbered in order: row r's place among them is how many rows
-  // before it chose the same expert, which every kernel finds out for itself.
+  // Each expert runs for the rows that chose it only
   uint16_t* h = reinterpret_cast<uint16_t*>(ws + mp.h_off);
   StreamGemmArgs g{};
   g.x = rp.u; g.m = a.rows; g.n = a.d_ff; g.k = a.d_model;
-  g.batch = a.n_experts; g.x_batch = 0; g.w_batch = (long long)a.d_ff * a.d_model; g.y_batch = (long long)a.rows * a.d_ff;
+  g.batch = a.n_experts; g.w_batch = (long long)a.d_ff * a.d_model;
   g.sel = a.expert_idx;
-  g.ksplit = mp.split1; g.y_split = (long long)a.n_experts * a.rows * a.d_ff;
+  g.ksplit = mp.split1; g.y_split = (long long)a.rows * 2 * a.d_ff;
   g.w = static_cast<const uint16_t*>(a.w_gate); g.w2 = static_cast<const uint16_t*>(a.w_up);
   if (mp.split1 > 1) {
     g.y = reinterpret_cast<float*>(ws + mp.g_off); g.y2 = reinterpret_cast<float*>(ws + mp.up_off);
   } else {
-    g.act = h; g.act_batch = (long long)a.rows * a.d_ff;
+    g.act = h;
   }
   if ((e = mp.ring_rows ? launch_ring_gemm_pair(g, mp.ring_rows, mp.used, stream) : launch_stream_gemm_pair(g, stream)) != hipSuccess) return e;  // gate and up projections of all experts
   if (mp.split1 > 1) {
     ActParams ap;
-    ap.g = g.y; ap.up = g.y2; ap.h = h; ap.sel = a.expert_idx;
-    ap.rows = a.rows; ap.f = a.d_ff; ap.ksplit = mp.split1; ap.split_stride = g.y_split;
-    hipLaunchKernelGGL(gated_act_kernel, dim3(a.rows, a.n_experts, (unsigned)((a.d_ff + 4095) / 4096)), dim3(256), 0, stream, ap);
+    ap.g = g.y; ap.up = g.y2; ap.h = h;
+    ap.f = a.d_ff; ap.ksplit = mp.split1; ap.split_stride = g.y_split;
+    hipLaunchKernelGGL(gated_act_kernel, dim3(2 * a.rows, (unsigned)((a.d_ff / 4 + 255) / 256)), dim3(256), 0, stream, ap);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   StreamGemmArgs o{};
   o.x = h; o.m = a.rows; o.n = a.d_model; o.k = a.d_ff;
-  o.batch = a.n_experts; o.x_batch = (long long)a.rows * a.d_ff; o.w_batch = (long long)a.d_model * a.d_ff;
-  o.y_batch = (long long)a.rows * a.d_model; o.sel = a.expert_idx;
-  o.ksplit = mp.split2; o.y_split = (long long)a.n_experts * a.rows * a.d_model;
+  o.batch = a.n_experts; o.w_batch = (long long)a.d_model * a.d_ff;
+  o.sel = a.expert_idx;
+  o.ksplit = mp.split2; o.y_split = (long long)a.rows * 2 * a.d_model;
   o.w = static_cast<const uint16_t*>(a.w_down); o.y = reinterpret_cast<float*>(ws + mp.y_off);
   if ((e = mp.ring_rows ? launch_ring_gemm_down(o, mp.ring_rows, mp.used, stream) : launch_stream_gemm_down(o, stream)) != hipSuccess) return e;
 
   SelectParams sp;
-  sp.y = o.y; sp.u = rp.u; sp.s_top = a.s_top; sp.idx = a.expert_idx;
+  sp.y = o.y; sp.u = rp.u; sp.s_top = a.s_top;
   sp.f_top = static_cast<uint16_t*>(a.f_top); sp.f_mix = static_cast<uint16_t*>(a.f_mix);
-  sp.rows = a.rows; sp.d = a.d_model; sp.n_experts = a.n_experts;
+  sp.d = a.d_model;
   sp.ksplit = mp.split2; sp.split_stride = o.y_split;
   hipLaunchKernelGGL(select_kernel, dim3(a.rows, (unsigned)((a.d_model / 4 + 255) / 256)), dim3(256), 0, stream, sp);
   return hipGetLastError();

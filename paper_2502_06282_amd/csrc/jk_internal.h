@@ -158,15 +158,15 @@ struct StreamGemmArgs {
   bool finish;
   const uint16_t* residual;
   uint16_t* out_bf16;
-  // experts: `batch` problems, element offsets between them; problem e runs for the rows r of [0, m) with sel[2 r] or
-  // sel[2 r + 1] == e, numbered in order (its rows of y, of act and of the down projection's x), or not at all
+  // experts: `batch` problems, w_batch elements between their weights; problem e runs for the choices c = 2 r, 2 r + 1 of the
+  // rows r of [0, m) with sel[c] == e, or not at all.  Rows of y, of act and of the down projection's x are numbered by
+  // choice, so that no kernel has to find out how many rows before r chose the same expert; x of gate and up has the rows r
   int batch;
-  long long x_batch, w_batch, y_batch;
+  long long w_batch;
   const int* sel;
   const uint16_t* w2;   // gate and up projections in one launch: w, y and w2, y2; or, with `act` (undivided k range),
-  float* y2;            // act[e][row][n] = silu(x . w^T) * (x . w2^T) in bf16, act_batch elements between experts
+  float* y2;            // act[choice][n] = silu(x . w^T) * (x . w2^T) in bf16
   uint16_t* act;
-  long long act_batch;
   // output heads: row 2 r + h of the product's left side is made of rows 2 r and 2 r + 1 of x, token r's two features f1 and
   // f2 with router scores s1 and s2 = s_top[2 r], s_top[2 r + 1]: s_(h + 1) f_(h + 1) (JK_HEADS_DECOUPLED), or
   // s1 f1 + s2 f2 (h = 0) and beta f1 - alpha f2 (h = 1)

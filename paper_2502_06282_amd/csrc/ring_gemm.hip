@@ -67,7 +67,7 @@ __global__ __launch_bounds__(kRingThreads, 1) void ring_gemm_kernel(StreamGemmAr
   unsigned char* ring = smem + wave * C::RING;
   const unsigned ring_at = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)ring;
   floatx4* sums = reinterpret_cast<floatx4*>(smem + kWaves * C::RING + 1024);  // [2][CAP][PITCH]
-  int* order = reinterpret_cast<int*>(smem + kWaves * C::RING + 1024 + C::SUMS);  // the rows that chose an expert, expert by expert
+  int* order = reinterpret_cast<int*>(smem + kWaves * C::RING + 1024 + C::SUMS);  // the choices, expert by expert: 2 row + (first or second)
   int* starts = order + 2 * kMaxRows;       // where an expert's begin
   int* counts = starts + kMaxRingExperts;   // and how many it has
   int* item_s = counts + kMaxRingExperts;   // (expert, block of CAP rows) pairs that there is something to do for
@@ -84,8 +84,8 @@ __global__ __launch_bounds__(kRingThreads, 1) void ring_gemm_kernel(StreamGemmAr
       const bool in0 = s0.x == e || s0.y == e, in1 = s1.x == e || s1.y == e;
       const unsigned long long b0 = __ballot(in0), b1 = __ballot(in1);
       const int c0 = __popcll(b0), c = c0 + __popcll(b1);
-      if (in0) order[n + __popcll(b0 & below)] = lane;
-      if (in1) order[n + c0 + __popcll(b1 & below)] = lane + 64;
+      if (in0) order[n + __popcll(b0 & below)] = 2 * lane + (s0.x == e ? 0 : 1);
+      if (in1) order[n + c0 + __popcll(b1 & below)] = 2 * (lane + 64) + (s1.x == e ? 0 : 1);
       if (lane == 0) {
         starts[e] = n;
         counts[e] = c;
@@ -128,13 +128,11 @@ __global__ __launch_bounds__(kRingThreads, 1) void ring_gemm_kernel(StreamGemmAr
   unsigned wr[2 * NF], xr[RG];
   auto aim_x = [&](int item) {
     const int e = expert_of(item), first = block_of(item) * CAP, rows = rows_of(item);
-    const uint16_t* base = p.x;
-    if constexpr (KIND == DOWN) base += (long long)e * p.x_batch + (long long)first * p.k;
-    xa = dev::uniform_ptr(base);
+    xa = dev::uniform_ptr(p.x);
 #pragma unroll
     for (int i = 0; i < RG; ++i) {  // (rows past the end repeat the last one; never stored)
       int row = min(8 * i + lrow, rows - 1);
-      if constexpr (KIND == PAIR) row = order[starts[e] + first + row];
+      if constexpr (KIND != HEADS) row = order[starts[e] + first + row] >> (KIND == PAIR);
       xr[i] = (unsigned)row * (unsigned)p.k * 2u + lcol;
     }
   };
@@ -300,18 +298,19 @@ __global__ __launch_bounds__(kRingThreads, 1) void ring_gemm_kernel(StreamGemmAr
         float o[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) o[j] = gate[j] / (1.f + expf(-gate[j])) * up[j];
-        *reinterpret_cast<uint2*>(p.act + (long long)e * p.act_batch + (long long)(first + row) * p.n + used.off * GROUP + 4 * h) =
+        *reinterpret_cast<uint2*>(p.act + (long long)order[starts[e] + first + row] * p.n + used.off * GROUP + 4 * h) =
             make_uint2(pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]));
       }
     } else {
       const int per_row = used.size * 4, n0 = used.off * GROUP;
-      float* y = p.y + (long long)e * p.y_batch + (long long)first * p.n + n0;
+      float* y = p.y + n0;
+      auto place = [&](int row) { return (long long)(KIND == DOWN ? order[starts[e] + first + row] : row); };
       if (KIND == DOWN || ((p.n & 3) == 0 && (reinterpret_cast<size_t>(p.y) & 15) == 0)) {
         for (int i = tid; i < rows * per_row; i += kRingThreads) {
           const int row = i / per_row, q = i - row * per_row;
           if (n0 + 4 * q >= p.n) continue;
           const floatx4 v = quad(row, q);
-          floatx4* dst = reinterpret_cast<floatx4*>(y + (long long)row * p.n + 4 * q);
+          floatx4* dst = reinterpret_cast<floatx4*>(y + place(row) * p.n + 4 * q);
           if constexpr (KIND == HEADS) __builtin_nontemporal_store(v, dst);
           else *dst = v;
         }

@@ -26,7 +26,7 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 512;  // 8 waves
-constexpr int kListBytes = 512;  // the rows that chose an expert (at most 128)
+constexpr int kListBytes = 512;  // the choices of an expert (at most 128), 2 row + (first or second)
 
 __device__ __forceinline__ unsigned bf16_bits_rne(float f) {
   const unsigned u = __float_as_uint(f);
@@ -113,7 +113,6 @@ __device__ __forceinline__ void strip_products(const StreamGemmArgs& p, Weights<
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 15, g = lane >> 4;
   const int k0 = w.k0, k1 = w.k1, nc = (k1 - k0 + KC - 1) / KC;
-  const uint16_t* px = p.x + (long long)e * p.x_batch;
   const uint16_t* xp[C::XP];
   u32x4 xr[C::XP], xo[KIND == HEADS ? C::XP : 1];  // (HEADS: the token's other feature)
   float c_own[C::XP], c_other[C::XP];
@@ -127,8 +126,9 @@ __device__ __forceinline__ void strip_products(const StreamGemmArgs& p, Weights<
 #pragma unroll
   for (int q = 0; q < C::XP; ++q) {  // rows past the end repeat the last one; never stored
     int row = min(x_row(q), m - 1);
-    if (KIND == PAIR) row = list[row];
-    xp[q] = px + (long long)row * p.k;
+    if (KIND == PAIR) row = list[row] >> 1;
+    if (KIND == DOWN) row = list[row];
+    xp[q] = p.x + (long long)row * p.k;
     if constexpr (KIND == HEADS) {
       other[q] = (row & 1) ? -(long long)p.k : (long long)p.k;
       const float s_own = p.s_top[row], s_other = p.s_top[row ^ 1];
@@ -230,6 +230,7 @@ __device__ __forceinline__ void strip_products(const StreamGemmArgs& p, Weights<
                    (reinterpret_cast<size_t>(p.out_bf16) & 7) == 0;
   float* tile = reinterpret_cast<float*>(xbuf);
   const int n0 = (int)blockIdx.x * OUT;
+  auto y_row = [&](int row) { return (long long)(KIND == PAIR || KIND == DOWN ? list[row] : row); };
   // emit4 (emit1): element offset in the output, and where its four values (its value) are in LDS
   auto put = [&](auto emit4, auto emit1) {
 #pragma unroll
@@ -247,21 +248,21 @@ __device__ __forceinline__ void strip_products(const StreamGemmArgs& p, Weights<
 #pragma unroll 4
         for (int i = tid; i < rows * (OUT / 4); i += kThreads) {
           const int row = i / (OUT / 4), col = i % (OUT / 4) * 4;
-          if (n0 + col < p.n) emit4((long long)(16 * t0 + row) * p.n + n0 + col, reinterpret_cast<const floatx4*>(tile + row * LDO + col));
+          if (n0 + col < p.n) emit4(y_row(16 * t0 + row) * p.n + n0 + col, reinterpret_cast<const floatx4*>(tile + row * LDO + col));
         }
       } else {
         for (int i = tid; i < rows * OUT; i += kThreads) {
           const int row = i / OUT, col = i % OUT;
-          if (n0 + col < p.n) emit1((long long)(16 * t0 + row) * p.n + n0 + col, tile + row * LDO + col);
+          if (n0 + col < p.n) emit1(y_row(16 * t0 + row) * p.n + n0 + col, tile + row * LDO + col);
         }
       }
     }
   };
-  const long long part = (long long)e * p.y_batch + (long long)blockIdx.z * p.y_split;
+  const long long part = (long long)blockIdx.z * p.y_split;
   float* y = p.y + part;
   if constexpr (KIND == PAIR) {
     float* y2 = p.y2 + part;
-    uint16_t* h = p.act + (long long)e * p.act_batch;
+    uint16_t* h = p.act;
     auto gated = [](float a, float b) { return a / (1.f + expf(-a)) * b; };
     if (p.act) {
       put(
@@ -345,7 +346,7 @@ __global__ __launch_bounds__(kThreads, 2) void stream_gemm_kernel(StreamGemmArgs
       const int row = i0 + lane;
       const bool mine = row < p.m && (p.sel[2 * row] == e || p.sel[2 * row + 1] == e);
       const unsigned long long v = __ballot(mine);
-      if (mine) list[m + __popcll(v & ((1ull << lane) - 1ull))] = row;
+      if (mine) list[m + __popcll(v & ((1ull << lane) - 1ull))] = 2 * row + (p.sel[2 * row] == e ? 0 : 1);
       m += __popcll(v);
     }
     if (m == 0) return;  // nobody chose it (the whole workgroup: nobody waits at a later barrier)

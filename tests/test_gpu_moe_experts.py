@@ -222,6 +222,12 @@ def test_rows_gathered_per_expert(rows, d, f, n):
     _check(moe_inputs(rows, d, f, n, seed=rows + 1), min_gap=1e-6)
 
 
+@pytest.mark.parametrize("rows,d,f,n", [(64, 2048, 1152, 2), (70, 1152, 1664, 2), (128, 2048, 128, 3)])
+def test_activation_of_divided_projections(rows, d, f, n):
+    """Divided gate and up projections whose width is no multiple of what a workgroup of the activation has (1024)."""
+    _check(moe_inputs(rows, d, f, n, seed=rows + 3), min_gap=1e-6)
+
+
 @pytest.mark.parametrize("n", [2, 3, 8, 63, 64])
 def test_a_nan_score_ranks_below_every_other(n):
     """A row whose router scores are NaN (all of them, or one expert's) still names two different experts that exist,
