@@ -5,7 +5,7 @@
 // divides by, and each head's top-k candidates.
 //
 // Kernels:
-//   head_inputs_kernel     X[2R, d] bf16 from f_top, s_top (elementwise; more than 16 tokens:
+//   head_inputs_kernel     X[2R, d] bf16 from f_top, s_top (elementwise; more than 32 tokens:
 //                          of fewer the product makes its rows itself)
 //   row_parts_kernel, row_finish_kernel   per logits row: maximum, normaliser,
 //                          top-k by value (ties to the lower token id), probabilities.
@@ -669,7 +669,7 @@ hipError_t launch_draft_heads(const DraftHeadsArgs& a, hipStream_t stream) {
   mp.s_top = a.s_top;
   mp.x = reinterpret_cast<unsigned short*>(ws);
   mp.rows = a.rows; mp.d = a.d_model; mp.mode = a.mode; mp.alpha = a.alpha; mp.beta = a.beta;
-  const bool mixes = rp.ring || m <= 32;  // the product makes its rows itself (see launch_stream_gemm_heads)
+  const bool mixes = rp.ring || m <= 64;  // the product makes its rows itself (see launch_stream_gemm_heads)
   hipError_t e = hipSuccess;
   if (!mixes) {
     hipLaunchKernelGGL(head_inputs_kernel, dim3((unsigned)(((long long)a.rows * (a.d_model / 8) + 63) / 64)), dim3(64), 0, stream, mp);

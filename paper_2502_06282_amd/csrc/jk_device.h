@@ -20,6 +20,12 @@ __device__ __forceinline__ void dma16(const uint16_t* base, unsigned voff, unsig
                : "memory", "m0");
 }
 
+// Two values rounded to bf16 (one instruction)
+__device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(unsigned, bf16x2{(__bf16)lo, (__bf16)hi});
+}
+
 // A wave-uniform pointer, made so for the compiler (scalar registers)
 __device__ __forceinline__ const uint16_t* uniform_ptr(const uint16_t* p) {
   const unsigned long long v = reinterpret_cast<unsigned long long>(p);

@@ -53,11 +53,6 @@ struct RingCfg {
   static_assert(DEPTH >= 2, "LDS plan");
 };
 
-__device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
-  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  return __builtin_bit_cast(unsigned, bf16x2{(__bf16)lo, (__bf16)hi});
-}
-
 template <RingKind KIND, int RG, int NF>
 __global__ __launch_bounds__(kRingThreads, 1) void ring_gemm_kernel(StreamGemmArgs p) {
   using C = RingCfg<KIND, RG, NF>;
@@ -204,7 +199,7 @@ __global__ __launch_bounds__(kRingThreads, 1) void ring_gemm_kernel(StreamGemmAr
         lo += c_other[t] * __uint_as_float(other << 16);
         hi += c_other[t] * __uint_as_float(other & 0xFFFF0000u);
       }
-      o[j] = pack_bf16(lo, hi);
+      o[j] = dev::pack_bf16(lo, hi);
     }
     return __builtin_bit_cast(bf16x8, o);
   };
@@ -299,7 +294,7 @@ __global__ __launch_bounds__(kRingThreads, 1) void ring_gemm_kernel(StreamGemmAr
 #pragma unroll
         for (int j = 0; j < 4; ++j) o[j] = gate[j] / (1.f + expf(-gate[j])) * up[j];
         *reinterpret_cast<uint2*>(p.act + (long long)order[starts[e] + first + row] * p.n + used.off * GROUP + 4 * h) =
-            make_uint2(pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]));
+            make_uint2(dev::pack_bf16(o[0], o[1]), dev::pack_bf16(o[2], o[3]));
       }
     } else {
       const int per_row = used.size * 4, n0 = used.off * GROUP;

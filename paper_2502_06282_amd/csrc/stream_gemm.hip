@@ -150,14 +150,27 @@ __device__ __forceinline__ void strip_products(const StreamGemmArgs& p, Weights<
   // decoupled head)
   auto mix = [&](u32x4 own, u32x4 oth, float c, float co) {
     u32x4 o;
+    if constexpr (MT <= 2) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      float lo = c != 0.f ? c * bf16_lo(own[j]) : 0.f, hi = c != 0.f ? c * bf16_hi(own[j]) : 0.f;
-      if (mixed && co != 0.f) {
-        lo += co * bf16_lo(oth[j]);
-        hi += co * bf16_hi(oth[j]);
+      for (int j = 0; j < 4; ++j) {
+        float lo = c != 0.f ? c * bf16_lo(own[j]) : 0.f, hi = c != 0.f ? c * bf16_hi(own[j]) : 0.f;
+        if (mixed && co != 0.f) {
+          lo += co * bf16_lo(oth[j]);
+          hi += co * bf16_hi(oth[j]);
+        }
+        o[j] = bf16_bits_rne(lo) | (bf16_bits_rne(hi) << 16);
       }
-      o[j] = bf16_bits_rne(lo) | (bf16_bits_rne(hi) << 16);
+    } else {  // (a third of the instructions, which count here; few rows wait for their weights, and are up to 1 % slower like this)
+      const unsigned keep = c != 0.f ? ~0u : 0u, keep_other = co != 0.f ? ~0u : 0u;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        float lo = c * bf16_lo(own[j] & keep), hi = c * bf16_hi(own[j] & keep);
+        if (mixed) {
+          lo += co * bf16_lo(oth[j] & keep_other);
+          hi += co * bf16_hi(oth[j] & keep_other);
+        }
+        o[j] = dev::pack_bf16(lo, hi);
+      }
     }
     return o;
   };
@@ -448,12 +461,15 @@ hipError_t launch_plain(const StreamGemmArgs& p, hipStream_t stream) {
 }  // namespace
 
 // Every workgroup mixes the rows for itself instead of a launch in front of it (5 us, of which 2.5 show).  All kernels, us,
-// with the launch / without: 2 rows of 32000 x 4096 57.7 / 55.0, 20 rows 59.7 / 57.1, 128256 x 4096 197.7 / 195.8; 64
-// rows of 32000 x 4096 69.0 / 72.3, of 128256 x 4096 233 / 256: so up to two row blocks of 16.
+// with the launch / without: 2 rows of 32000 x 4096 57.7 / 55.0, 20 rows 59.7 / 57.1, 128256 x 4096 197.7 / 195.8; the whole
+// call, 40 rows of 32000 x 4096 64.0 / 62.3, 48 of 12159 x 5632 47.9 / 44.2, 64 of 128256 x 4096 232.3 / 225.6, with both
+// features in a row 232.5 / 231.4; 128 of 128256 x 4096 291 / 307 and 290 / 328: so up to four row blocks of 16.
 hipError_t launch_stream_gemm_heads(const StreamGemmArgs& p, hipStream_t stream) {
   switch ((p.m + 15) / 16) {
     case 1: return launch_plain<1, HEADS>(p, stream);
     case 2: return launch_plain<2, HEADS>(p, stream);
+    case 3: return launch_plain<3, HEADS>(p, stream);
+    case 4: return launch_plain<4, HEADS>(p, stream);
     default: return hipErrorInvalidValue;
   }
 }

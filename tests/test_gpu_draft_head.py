@@ -233,6 +233,16 @@ def test_rows_mixed_by_the_product_are_bit_exact(rows, d, vocab):
     assert np.isnan(lg[0, 0]).all() and np.isfinite(lg[0, 1]).all() and np.isfinite(lg[1:]).all()
 
 
+@pytest.mark.parametrize("rows", [18, 24, 25, 31, 32, 33])   # three and four row blocks of 16 mixed by the product; one more
+@pytest.mark.parametrize("d,vocab", [(640, 1025), (2048, 300), (384, 70003)])
+def test_more_rows_mixed_by_the_product_are_bit_exact(rows, d, vocab):
+    test_rows_mixed_by_the_product_are_bit_exact(rows, d, vocab)
+    x = _exact_inputs(rows, d, vocab, rows)
+    x["f_top"][rows - 1, 0, 5] = np.inf                  # and here the row's own feature, the last row's
+    lg, *_ = _call(x, mode=jk.JK_HEADS_CONTRASTIVE, alpha=0.5, beta=0.0)
+    assert np.isfinite(lg[:-1]).all() and np.isfinite(lg[-1, 1]).all() and not np.isfinite(lg[-1, 0]).all()
+
+
 @pytest.mark.parametrize("rows", [1, 4, 5, 12, 16])      # groups of eight rows, whole and not
 @pytest.mark.parametrize("d,vocab", [(128, 8192), (640, 9001), (384, 16388), (256, 33003)])
 def test_equal_shares_of_the_vocabulary_are_bit_exact(rows, d, vocab):
