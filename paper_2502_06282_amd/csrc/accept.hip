@@ -28,6 +28,7 @@
 #include "jk_device.h"
 #include "jk_internal.h"
 #include "jk_wave.h"
+#include "walk_alone.h"
 
 namespace jk {
 namespace {
@@ -102,16 +103,8 @@ __global__ __launch_bounds__(256) void row_reduce_kernel(const float* __restrict
   if (tid == 0) { pmax[slot] = best; psum[slot] = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3]; }
 }
 
-// A parent entry that breaks -1 <= parent[k] < k counts as -1, and a token id outside the vocabulary is
-// clamped into it; either is recorded in the workspace's sticky error word (err may be null).
-__device__ __forceinline__ void report(unsigned* err, unsigned bit) {
-  if (err) __hip_atomic_fetch_or(err, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ int sanitize_parent(int pa, int k, unsigned* err) {
-  if (pa >= -1 && pa < k) return pa;
-  report(err, kDevErrBadTree);
-  return -1;
-}
+using dev::report;
+using dev::sanitize_parent;
 
 // ------------------------------------------------------------------ greedy walk
 __global__ __launch_bounds__(128) void walk_greedy_kernel(int n_tree, int nch, int vocab, int max_depth,
@@ -329,168 +322,29 @@ void launch_greedy(const GreedyParams& p, int loads, dim3 grid, hipStream_t stre
 }
 
 // ------------------------------------------------------------------ sampling walk
-__device__ double block_sum_f64(double v, double* red) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  const int w = threadIdx.x >> 6;
-  __syncthreads();  // protects red[] against the previous use
-  if ((threadIdx.x & 63) == 0) red[w] = v;
-  __syncthreads();
-  double r = 0.0;
-  for (int i = 0; i < kWalkThreads / 64; ++i) r += red[i];
-  return r;
-}
-
 struct WalkParams {
-  int n_tree, vocab, nch, max_depth;
-  double temp;
-  const int *tokens, *parent;
-  const float *logits, *draft, *uniforms;
-  const int* draft_row;  // or null: row b*n_tree + k
-  long long n_draft_rows;
+  dev::AloneParams walk;
+  int nch;
   const float* pmax;
   const double* psum;
-  double* resid;  // [batch][2][vocab] unnormalised residuals (ping-pong)
-  int *out_path, *out_len, *out_bonus;
-  unsigned* err;  // the workspace's sticky device error word
 };
 
 __global__ __launch_bounds__(kWalkThreads) void walk_sample_kernel(WalkParams p) {
-  __shared__ int par_s[JK_MAX_TREE];
-  __shared__ double red[kWalkThreads / 64];
-  __shared__ double seg_incl[kWalkThreads];
-  __shared__ int s_found;
-
-  const int b = blockIdx.x, tid = threadIdx.x;
-  const int N = p.n_tree, V = p.vocab;
-  const int rows = N + 1;
-  if (tid < N) {
-    par_s[tid] = sanitize_parent(p.parent[(long long)b * N + tid], tid, p.err);
-    const int t = p.tokens[(long long)b * N + tid];
-    if (t < 0 || t >= V) report(p.err, kDevErrBadToken);
-  }
-  __syncthreads();
-
-  const int* tok = p.tokens + (long long)b * N;
-  const float* uni = p.uniforms + (long long)b * rows;
-  double* res0 = p.resid + (long long)b * 2 * V;
-
-  int c = -1, len = 0;
-  // current distribution at c: either softmax of row c+1 (fresh) or resid[cur] / res_s
-  bool fresh = true;
-  int cur = 0;
-  double res_s = 1.0;
-  double row_max = 0.0;  // max of row / T
-  double row_z = 1.0;
-  const float* row = nullptr;
-
-  auto load_row_stats = [&](int r) {
-    row = p.logits + ((long long)b * rows + r) * V;
-    const long long base = ((long long)b * rows + r) * p.nch;
+  __shared__ dev::AloneShared<kWalkThreads> sh;
+  const int b = blockIdx.x;
+  dev::walk_alone<kWalkThreads>(p.walk, b, sh, [&](int r, double& row_max, double& row_z) {
+    const long long base = ((long long)b * (p.walk.n_tree + 1) + r) * p.nch;
     float mx = -INFINITY;
     for (int i = 0; i < p.nch; ++i) mx = fmaxf(mx, p.pmax[base + i]);
-    const double mref = (mx == -INFINITY) ? 0.0 : (double)mx / p.temp;
+    const double mref = (mx == -INFINITY) ? 0.0 : (double)mx / p.walk.temp;
     double z = 0.0;
     for (int i = 0; i < p.nch; ++i) {
       const float mc = p.pmax[base + i];
-      if (mc != -INFINITY) z += p.psum[base + i] * exp((double)mc / p.temp - mref);
+      if (mc != -INFINITY) z += p.psum[base + i] * exp((double)mc / p.walk.temp - mref);
     }
     row_max = mref;
     row_z = z;
-  };
-  // probability of token v under the current distribution (every thread may call it)
-  auto prob = [&](int v) -> double {
-    if (fresh) return exp((double)row[v] / p.temp - row_max) / row_z;
-    return res0[(long long)cur * V + v] / res_s;
-  };
-
-  load_row_stats(0);
-  int k = 0;  // children of c are searched from k upwards (topological numbering)
-  while (len < p.max_depth) {  // (at the cap the token after c comes from c's own row, untouched)
-    // next child of c, left to right
-    int child = -1;
-    for (int j = k; j < N; ++j)
-      if (par_s[j] == c) { child = j; break; }
-    if (child < 0) break;
-    const int x = min(max(tok[child], 0), V - 1);  // a token id outside the vocabulary must not fault
-    long long qr = (long long)b * N + child;
-    if (p.draft_row) {
-      qr = p.draft_row[qr];
-      qr = qr < 0 ? 0 : (qr >= p.n_draft_rows ? p.n_draft_rows - 1 : qr);
-    }
-    const float* qk = p.draft + qr * V;
-    const double lhs = (double)uni[child] * (double)qk[x];
-    const double rhs = prob(x);
-    if (lhs < rhs) {
-      if (tid == 0) p.out_path[(long long)b * p.max_depth + len] = child;
-      ++len;
-      c = child;
-      k = child + 1;
-      fresh = true;
-      load_row_stats(c + 1);
-      continue;
-    }
-    // rejected: r = max(0, p - q_k), written unnormalised to the other buffer
-    double* dst = res0 + (long long)(fresh ? 0 : (cur ^ 1)) * V;
-    double part = 0.0;
-    for (int v = tid; v < V; v += kWalkThreads) {
-      const double r = fmax(0.0, prob(v) - (double)qk[v]);
-      dst[v] = r;
-      part += r;
-    }
-    const double s = block_sum_f64(part, red);  // its barriers also order dst[] for later readers
-    if (s > 0.0) {
-      cur = fresh ? 0 : (cur ^ 1);
-      fresh = false;
-      res_s = s;
-    }
-    k = child + 1;
-  }
-
-  // ---- bonus token: smallest v whose cumulative probability exceeds u * total
-  const int seg = (V + kWalkThreads - 1) / kWalkThreads;
-  const int s0 = min(V, tid * seg), s1 = min(V, s0 + seg);
-  double part = 0.0;
-  for (int v = s0; v < s1; ++v) part += prob(v);
-  seg_incl[tid] = part;
-  if (tid == 0) s_found = -1;
-  __syncthreads();
-  // inclusive scan over the 1024 segment sums (Hillis-Steele in LDS)
-  for (int o = 1; o < kWalkThreads; o <<= 1) {
-    const double add = (tid >= o) ? seg_incl[tid - o] : 0.0;
-    __syncthreads();
-    seg_incl[tid] += add;
-    __syncthreads();
-  }
-  const double total = seg_incl[kWalkThreads - 1];
-  const double target = (double)uni[N] * total;
-  const double excl = (tid == 0) ? 0.0 : seg_incl[tid - 1];
-  if (s1 > s0 && excl <= target && seg_incl[tid] > target) {
-    double run = excl;
-    int found = -1;
-    for (int v = s0; v < s1; ++v) {
-      run += prob(v);
-      if (run > target) { found = v; break; }
-    }
-    // rounding between the scanned and the re-added sums can leave the segment without a hit
-    if (found < 0) found = s1 - 1;
-    atomicMax(&s_found, found);
-  }
-  __syncthreads();
-  const int hit = s_found;  // every thread reads the same value before anyone may change it
-  __syncthreads();
-  if (hit < 0) {
-    // u * total not below the last cumulative value: largest v with positive probability
-    int last = -1;
-    for (int v = s0; v < s1; ++v)
-      if (prob(v) > 0.0) last = v;
-    if (last >= 0) atomicMax(&s_found, last);
-  }
-  __syncthreads();
-  if (tid == 0) {
-    for (int i = len; i < p.max_depth; ++i) p.out_path[(long long)b * p.max_depth + i] = -1;
-    p.out_len[b] = len;
-    p.out_bonus[b] = s_found < 0 ? 0 : s_found;
-  }
+  });
 }
 
 // ------------------------------------------------------------------ library-owned scratch
@@ -657,7 +511,7 @@ hipError_t launch_accept(const AcceptArgs& a, hipStream_t stream) {
     int W = 0, slice = 0;
     // (tuning/testing: accept_single forces the one-workgroup walk)
     if (!tuning().accept_single && accept_coop_plan(a.batch, a.vocab, device_cu_count(), &W, &slice))
-      return launch_accept_coop(a, ws + w.coop, W, slice, stream);
+      return launch_accept_coop(a, ws + w.coop, resid, W, slice, stream);
   }
   const double temp = (double)a.temperature;
   hipLaunchKernelGGL(row_reduce_kernel<true>, grid, dim3(256), 0, stream, a.logits, a.vocab, temp, pmax, pidx,
@@ -665,14 +519,8 @@ hipError_t launch_accept(const AcceptArgs& a, hipStream_t stream) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   WalkParams wp;
-  wp.n_tree = a.n_tree; wp.vocab = a.vocab; wp.nch = nch; wp.max_depth = a.max_depth;
-  wp.temp = temp;
-  wp.tokens = a.tokens; wp.parent = a.parent;
-  wp.logits = a.logits; wp.draft = a.draft_probs; wp.uniforms = a.uniforms;
-  wp.draft_row = a.draft_row; wp.n_draft_rows = a.n_draft_rows;
-  wp.pmax = pmax; wp.psum = psum; wp.resid = resid;
-  wp.out_path = a.out_path; wp.out_len = a.out_len; wp.out_bonus = a.out_bonus;
-  wp.err = reinterpret_cast<unsigned*>(ws);
+  wp.walk = dev::alone_params(a, resid);
+  wp.nch = nch; wp.pmax = pmax; wp.psum = psum;
   hipLaunchKernelGGL(walk_sample_kernel, dim3(a.batch), dim3(kWalkThreads), 0, stream, wp);
   return hipGetLastError();
 }

@@ -40,9 +40,11 @@
 // Waiting is bounded: if a partner never shows up (the W workgroups of a tree are not all
 // resident) the walk gives up and reports accept_len = -1 instead of hanging; the last workgroup
 // of a tree to finish finds out and moves the call number on (see TreeWords), so a call that
-// gave up leaves nothing behind that a later call could mistake.
+// gave up leaves nothing behind that a later call could mistake.  (Many trees over large vocabularies:
+// that workgroup walks the tree alone instead, see walk_sample_wide_kernel.)
 #include "jk_internal.h"
 #include "jk_wave.h"
+#include "walk_alone.h"
 
 namespace jk {
 namespace {
@@ -52,6 +54,8 @@ constexpr int kCoopThreads = 256;
 // polls end after 0.85 ms, 32768 after 6.9; more where the memory is busy).  Other streams' kernels hold partners up for
 // milliseconds, and what gives up has no result.  To be measured again when a poll or the words' layout changes.
 constexpr unsigned kDefaultSpinLimit = 1u << 17;
+// Of walk_sample_wide_kernel, which has a result all the same: 1.7 ms, where its last workgroup takes 0.3 - 1.4 for a tree alone.
+constexpr unsigned kWideSpinLimit = 1u << 13;
 
 // The workgroups' contributions to an exchange, word by word: a wave that looks for one word of all of them reads 512
 // bytes in a row (64 bytes per workgroup, all its words together, were 7 - 11 % slower).  Every 64-bit word holds the exchange's 32-bit tag
@@ -373,6 +377,11 @@ struct Walk {
     }
   };
 
+  // (through to memory, like all results: a last workgroup on another XCD may have to write them anew)
+  __device__ __forceinline__ void put_path(int i, int node) {
+    __hip_atomic_store(&p.out_path[(long long)b * p.max_depth + i], node, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+
   // Final draw: smallest v whose cumulative probability exceeds u * total.  x: the sum of lane's slice under the current
   // distribution; cur: this thread's part of that.
   template <int PER, int WAVES>
@@ -435,26 +444,22 @@ struct Walk {
     }
     if (w == 0 && tid == 0) {
       if (owner < 0) __hip_atomic_store(&p.out_bonus[b], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // no entry with p > 0
-      for (int i = len; i < p.max_depth; ++i) p.out_path[(long long)b * p.max_depth + i] = -1;
+      for (int i = len; i < p.max_depth; ++i) put_path(i, -1);
       __hip_atomic_store(&p.out_len[b], len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
-  // The end of this workgroup: it says so; where one of the tree gave up, the last to finish takes the results back
-  __device__ __forceinline__ void finish(bool alive) {
-    if (tid != 0) return;
+  // The end of this workgroup, by its first thread: it says so.  True for the last one of a tree where one gave up, which takes
+  // the results back
+  __device__ __forceinline__ bool finish(bool alive) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the results went through to memory before the count can tell anybody)
     const unsigned mine = 1u + (alive ? 0u : 0x10000u);
     const unsigned all = __hip_atomic_fetch_add(&tw->finish, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + mine;
-    if ((all & 0xFFFFu) == (unsigned)W) {
-      __hip_atomic_store(&tw->finish, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (all >> 16) {
-        __hip_atomic_store(&p.out_len[b], -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&p.out_bonus[b], -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_or(p.err, kDevErrWalkWait, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      __hip_atomic_store(&tw->epoch, epoch + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    if ((all & 0xFFFFu) != (unsigned)W) return false;
+    __hip_atomic_store(&tw->finish, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&tw->epoch, epoch + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return all >> 16 != 0u;
   }
+  __device__ __forceinline__ unsigned finished() const { return __hip_atomic_load(&tw->finish, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 };
 
 template <int PER, int THREADS>
@@ -680,21 +685,28 @@ __global__ __launch_bounds__(THREADS, 2) void walk_sample_coop_kernel(CoopParams
     }
   }
   if (alive) wk.draw<PER, WAVES>(xs[lane] * xs_mul, cur, mine, len);
-  wk.finish(alive);
+  if (tid == 0 && wk.finish(alive)) {
+    __hip_atomic_store(&p.out_len[wk.b], -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&p.out_bonus[wk.b], -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_or(p.err, kDevErrWalkWait, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
 }
 
 // The walk of many trees over large vocabularies, where slices of 4096 entries would be more workgroups than are resident
 // together: 512 threads, a workgroup for each CU at most, a slice of 8192 to 20480 entries each.  (The workgroups of a tree
 // follow each other in the grid: of a call that gets only some of the CUs at most one tree waits for others to end.)  A thread
 // holds the current distribution and one slice, of the candidate's draft or of the row that it brings, and looks at nothing
-// ahead.  What bounds it is the exponentials of a row (some 40 instructions of 4 cycles each) and the slices' bytes.
+// ahead.  Where a workgroup gives up (another stream's kernel has its partners' CUs), those of its tree that start later do not
+// wait any more, and the last one walks the tree alone, with the residuals in the workspace, as a kernel of a workgroup per tree
+// would: no result is missing.  (All trees like that: 16 x 138253 1240 us, 128 x 32000 349.  The possibility costs 0 - 2 %.)
+// What bounds it is the exponentials of a row (some 40 instructions of 4 cycles each) and the slices' bytes.
 // Measured (us; by a workgroup per tree, in front of it a pass over all logits / like this), trees x entries: 16 x 138253
 // 519 / 42, 21 x 103226 304 / 31, 32 x 128256 534 / 56, 64 x 70000 297 / 47, 128 x 32000 141 / 47, 200 x 9000 57 / 32, 250 x 12289
 // 73 / 37.
 constexpr int kWideThreads = 512;
 
 template <int PER>
-__global__ __launch_bounds__(kWideThreads) void walk_sample_wide_kernel(CoopParams params) {
+__global__ __launch_bounds__(kWideThreads) void walk_sample_wide_kernel(CoopParams params, dev::AloneParams) {
   constexpr int SLICE = kWideThreads * PER, WAVES = kWideThreads / 64;
   __shared__ NodeTable nodes;
   __shared__ double red_d[2][WAVES];
@@ -712,11 +724,15 @@ __global__ __launch_bounds__(kWideThreads) void walk_sample_wide_kernel(CoopPara
   double cur[PER];  // the current distribution
   mine.load(x, wk.row_of(0));
   wk.load_words();
-  if (wave == 0) wk.make_table();
+  const unsigned before = wk.finished();
+  if (wave == 0) {
+    wk.make_table();
+    if (lane == 0) got_ok = before >> 16 == 0u;  // (where somebody of the tree has given up there is nothing to wait for)
+  }
   __syncthreads();
 
   double xs_mul = 1.0, px = 0.0;
-  bool alive = true;
+  bool alive = got_ok != 0;
   int flip = 0, len = 0, k = wk.first_of_root();
   Node node = wk.node(k);
   float qx = 0.f;
@@ -773,11 +789,11 @@ __global__ __launch_bounds__(kWideThreads) void walk_sample_wide_kernel(CoopPara
 #pragma unroll
     for (int u = 0; u < PER; ++u) cur[u] *= sc;
   };
-  adopt_row(0);
+  if (alive) adopt_row(0);
   while (alive && k >= 0) {
     if ((double)__int_as_float(node.uni) * (double)qx < px) {
       // ---- accepted: its row becomes the current one, its first child the candidate
-      if (tid == 0 && wk.w == 0) p.out_path[(long long)wk.b * p.max_depth + len] = k;
+      if (tid == 0 && wk.w == 0) wk.put_path(len, k);
       ++len;
       const int row = k + 1;
       mine.load(x, wk.row_of(row));
@@ -848,7 +864,41 @@ __global__ __launch_bounds__(kWideThreads) void walk_sample_wide_kernel(CoopPara
     }
   }
   if (alive) wk.draw<PER, WAVES>(xs[lane] * xs_mul, cur, mine, len);
-  wk.finish(alive);
+
+  __shared__ dev::AloneShared<kWideThreads> sh;
+  if (tid == 0) sh.found = wk.finish(alive);
+  __syncthreads();
+  if (__builtin_amdgcn_readfirstlane(sh.found) == 0) return;
+  __syncthreads();
+  // (fetched from the kernel's arguments here: held in scalar registers across the walk, which has none to spare, they cost
+  // every call some of them)
+  struct Arguments {
+    CoopParams params;
+    dev::AloneParams alone;
+  };
+  typedef __attribute__((address_space(4))) const Arguments KArgs;
+  KArgs* late = (KArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(late));
+  dev::AloneParams alone;
+  alone.n_tree = late->alone.n_tree; alone.vocab = late->alone.vocab; alone.max_depth = late->alone.max_depth;
+  alone.temp = late->alone.temp;
+  alone.tokens = late->alone.tokens; alone.parent = late->alone.parent;
+  alone.logits = late->alone.logits; alone.draft = late->alone.draft; alone.uniforms = late->alone.uniforms;
+  alone.draft_row = late->alone.draft_row; alone.n_draft_rows = late->alone.n_draft_rows;
+  alone.resid = late->alone.resid;
+  alone.out_path = late->alone.out_path; alone.out_len = late->alone.out_len; alone.out_bonus = late->alone.out_bonus;
+  alone.err = late->alone.err;
+  const int b = (int)(blockIdx.x / (unsigned)late->params.W);
+  dev::walk_alone<kWideThreads>(alone, b, sh, [&](int r, double& row_max, double& row_z) {
+    const float* row = alone.logits + ((long long)b * (alone.n_tree + 1) + r) * alone.vocab;
+    float m = -INFINITY;
+    for (int v = tid; v < alone.vocab; v += kWideThreads) m = fmaxf(m, row[v]);
+    m = dev::block_max_f32<kWideThreads>(m, sh.red);
+    row_max = m == -INFINITY ? 0.0 : (double)m / alone.temp;
+    double z = 0.0;
+    for (int v = tid; v < alone.vocab; v += kWideThreads) z += exp((double)row[v] / alone.temp - row_max);
+    row_z = dev::block_sum_f64<kWideThreads>(z, sh.red);
+  });
 }
 
 }  // namespace
@@ -862,6 +912,13 @@ size_t accept_coop_bytes() { return (size_t)kCoopMaxTrees * sizeof(TreeBlock); }
 template <int PER, int THREADS>
 hipError_t launch_walk(const CoopParams& cp, int wgs, hipStream_t stream) {
   hipLaunchKernelGGL((walk_sample_coop_kernel<PER, THREADS>), dim3((unsigned)wgs), dim3(THREADS), 0, stream, cp);
+  return hipGetLastError();
+}
+
+template <int PER>
+hipError_t launch_wide(CoopParams cp, const dev::AloneParams& alone, int wgs, hipStream_t stream) {
+  if (tuning().spin_limit < 0) cp.spin_limit = kWideSpinLimit;
+  hipLaunchKernelGGL(walk_sample_wide_kernel<PER>, dim3((unsigned)wgs), dim3(kWideThreads), 0, stream, cp, alone);
   return hipGetLastError();
 }
 
@@ -886,7 +943,7 @@ bool accept_coop_plan(int batch, int vocab, int cus, int* W, int* slice) {
   return false;
 }
 
-hipError_t launch_accept_coop(const AcceptArgs& a, void* coop_ws, int W, int slice, hipStream_t stream) {
+hipError_t launch_accept_coop(const AcceptArgs& a, void* coop_ws, double* resid, int W, int slice, hipStream_t stream) {
   CoopParams cp;
   cp.err = static_cast<unsigned*>(a.workspace);
   cp.n_tree = a.n_tree; cp.vocab = a.vocab; cp.max_depth = a.max_depth; cp.W = W;
@@ -897,7 +954,7 @@ hipError_t launch_accept_coop(const AcceptArgs& a, void* coop_ws, int W, int sli
   cp.trees = static_cast<TreeBlock*>(coop_ws);
   cp.spin_limit = tuning().spin_limit >= 0 ? (unsigned)tuning().spin_limit : kDefaultSpinLimit;
   cp.out_path = a.out_path; cp.out_len = a.out_len; cp.out_bonus = a.out_bonus;
-  const dim3 grid((unsigned)(a.batch * W)), block_wide(kWideThreads);
+  const dev::AloneParams alone = dev::alone_params(a, resid);
   // A workgroup with a CU to itself has its slice among twice the threads: two waves on a SIMD fill each other's waits.  (us, 256
   // threads / 512: 1 x 128256 16.5 / 15.8, 8 x 32000 20.8 / 20.5; slices of 512 entries 11.7 / 12.0 at 1 x 8000: not those.)
   const bool lone = a.batch * W <= device_cu_count();
@@ -906,13 +963,12 @@ hipError_t launch_accept_coop(const AcceptArgs& a, void* coop_ws, int W, int sli
     case kCoopThreads * 4: return lone ? launch_walk<2, 512>(cp, a.batch * W, stream) : launch_walk<4, kCoopThreads>(cp, a.batch * W, stream);
     case kCoopThreads * 8: return lone ? launch_walk<4, 512>(cp, a.batch * W, stream) : launch_walk<8, kCoopThreads>(cp, a.batch * W, stream);
     case kCoopThreads * 16: return lone ? launch_walk<8, 512>(cp, a.batch * W, stream) : launch_walk<16, kCoopThreads>(cp, a.batch * W, stream);
-    case kWideThreads * 16: hipLaunchKernelGGL(walk_sample_wide_kernel<16>, grid, block_wide, 0, stream, cp); break;
-    case kWideThreads * 24: hipLaunchKernelGGL(walk_sample_wide_kernel<24>, grid, block_wide, 0, stream, cp); break;
-    case kWideThreads * 32: hipLaunchKernelGGL(walk_sample_wide_kernel<32>, grid, block_wide, 0, stream, cp); break;
-    case kWideThreads * 40: hipLaunchKernelGGL(walk_sample_wide_kernel<40>, grid, block_wide, 0, stream, cp); break;
+    case kWideThreads * 16: return launch_wide<16>(cp, alone, a.batch * W, stream);
+    case kWideThreads * 24: return launch_wide<24>(cp, alone, a.batch * W, stream);
+    case kWideThreads * 32: return launch_wide<32>(cp, alone, a.batch * W, stream);
+    case kWideThreads * 40: return launch_wide<40>(cp, alone, a.batch * W, stream);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 // Calibration: a pure 128-bit streaming read of `bytes` bytes (nothing is computed or written

@@ -620,6 +620,102 @@ def test_sample_many_trees_of_large_vocabularies(B, V):
     assert _compare(a, par, "sample", max_depth=3) <= 1 + B // 50
 
 
+def _many_trees(B, V, seed=0):
+    """Arguments of a call that the walk of many trees over large vocabularies takes, and the oracle's results."""
+    rng = np.random.default_rng(B + seed)
+    cfg = CONFIGS["c3_llama3_8b"].with_(vocab=V, batch=B, n_tree=5)
+    par = np.tile(np.array([-1, -1, 0, 0, 1], dtype=np.int32), (B, 1))
+    a = accept_inputs(cfg, par, seed=V + seed)
+    _near_the_target(a, par, rng, 0.3)
+    t = lambda v: torch.from_numpy(np.ascontiguousarray(v)).cuda()
+    args = (t(a["tokens"]), t(par), t(a["logits"]), jk.JK_SAMPLE, 1.0, t(a["draft_probs"]), t(a["uniforms"]))
+    ref = [oracle_accept(a["tokens"][b], par[b], a["logits"][b], "sample", a["draft_probs"][b], a["uniforms"][b], max_depth=3) for b in range(B)]
+    assert sum(r.min_margin <= MARGIN for r in ref) <= 1 + B // 50
+    return args, ref
+
+
+def _same_as(ref, got):
+    path, alen, bonus = (x.cpu().numpy() for x in got)
+    for b, r in enumerate(ref):
+        if r.min_margin > MARGIN:
+            assert alen[b] == r.accept_len and bonus[b] == r.bonus_token, b
+            assert path[b, :r.accept_len].tolist() == r.path and (path[b, r.accept_len:] == -1).all()
+
+
+@pytest.mark.parametrize("B,V", [(18, 114689), (28, 147457), (250, 12289), (2, 262144 + 8192)])
+def test_sample_walk_of_many_trees_needs_nobody(B, V):
+    """spin_limit 0: workgroups of the walk of many trees over large vocabularies that do not find their partners' words at
+    once give up, and the tree's last one walks it alone: every result is there and right, the error word stays clear, and
+    calls with and without waits, of other shapes too, take turns on the workspace."""
+    args, ref = _many_trees(B, V)
+    small, small_ref = _many_trees(3, 9001, seed=1)
+    ws = torch.empty(max(jk.accept_path_workspace(B, 5, V, jk.JK_SAMPLE), jk.accept_path_workspace(3, 5, 9001, jk.JK_SAMPLE)),
+                     dtype=torch.uint8, device="cuda")
+    jk.workspace_init(ws)
+    for limit in (-1, 0, 0, 3, -1, 0, -1):
+        tune("spin_limit", limit)
+        got = jk.accept_path(*args, max_depth=3, workspace=ws)
+        tune("spin_limit", -1)
+        other = jk.accept_path(*small, max_depth=3, workspace=ws)
+        torch.cuda.synchronize()
+        _same_as(ref, got)
+        _same_as(small_ref, other)
+    assert jk.last_device_error(ws) == 0
+
+
+def test_sample_walk_of_many_trees_behind_another_streams_kernel():
+    """A linear layer of 256 rows on another stream has all but eight CUs for 8 ms, longer than the walk's workgroups wait for
+    those of their tree that have not started: every result is there and right."""
+    args, ref = _many_trees(18, 114689)
+    ws = torch.empty(jk.accept_path_workspace(18, 5, 114689, jk.JK_SAMPLE), dtype=torch.uint8, device="cuda")
+    jk.workspace_init(ws)
+    k, n = 262144, (torch.cuda.get_device_properties(0).multi_processor_count - 8) * 256   # a workgroup for each 256 columns
+    x, w = torch.zeros(256, k, dtype=torch.bfloat16, device="cuda"), torch.empty(n, k, dtype=torch.bfloat16, device="cuda")
+    jk.linear(x, w)                      # (the first call of a shape takes longer to launch)
+    jk.accept_path(*args, max_depth=3, workspace=ws)
+    torch.cuda.synchronize()
+    for limit in (-1, 1000, 1000, 1000, 1000):   # (1000: 0.2 ms; two streams may share a hardware queue, then the walk starts later)
+        tune("spin_limit", limit)
+        s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+        with torch.cuda.stream(s1):
+            begin = torch.cuda.Event()
+            begin.record()
+            jk.linear(x, w)
+        begin.synchronize()
+        time.sleep(0.0005)               # (its workgroups have their CUs)
+        with torch.cuda.stream(s2):
+            got = jk.accept_path(*args, max_depth=3, workspace=ws)
+        torch.cuda.synchronize()
+        _same_as(ref, got)
+    assert jk.last_device_error(ws) == 0
+
+
+@pytest.mark.parametrize("limit", [-1, 0])
+def test_sample_walk_of_many_trees_replays_in_a_graph(limit):
+    """Every replay gives the eager call's result, with eager calls on the same workspace between the replays."""
+    args, ref = _many_trees(28, 147457)
+    dev = torch.device("cuda")
+    out = [torch.empty(s, dtype=torch.int32, device=dev) for s in ((28, 3), (28,), (28,))]
+    ws = torch.empty(jk.accept_path_workspace(28, 5, 147457, jk.JK_SAMPLE), dtype=torch.uint8, device=dev)
+    jk.workspace_init(ws)
+    tune("spin_limit", limit)
+    call = jk.prepare_accept_path(*args, *out, ws)
+    call.launch()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=torch.cuda.Stream()):
+        call.launch()
+    for _ in range(4):
+        for o in out:
+            o.fill_(-7)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        _same_as(ref, out)
+        _same_as(ref, jk.accept_path(*args, max_depth=3, workspace=ws))
+    assert jk.last_device_error(ws) == 0
+
+
 @pytest.mark.parametrize("rows", ["huge", "lowest", "masked"])
 def test_sample_logits_of_extreme_size(rows):
     """Logits whose exponentials need a reference far from zero (3e30, where a power of two is no longer near enough), rows
