@@ -19,12 +19,12 @@
 
 #include "jk_device.h"
 #include "jk_internal.h"
+#include "ring_share.h"
 
 namespace jk {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
@@ -96,20 +96,9 @@ __global__ __launch_bounds__(kRingThreads, 1) void ring_gemm_kernel(StreamGemmAr
   const int all = gridDim.x, blk = blockIdx.x;
   const int id = all % 8 == 0 ? (blk & 7) * (all >> 3) + (blk >> 3) : blk;
   const int per_item = (p.n + GROUP - 1) / GROUP;
-  const unsigned total = (unsigned)items * (unsigned)per_item;  // (at most 96 x 8192; heads: 2^20)
-  const int f0 = (int)(total * (unsigned)id / (unsigned)all), f1 = (int)(total * (unsigned)(id + 1) / (unsigned)all);
+  const ring::Shares shares{per_item, NF};
+  const int f0 = (int)shares.share_begin(items, id, all), f1 = (int)shares.share_begin(items, id + 1, all);
   if (f0 == f1) return;  // (the whole workgroup)
-  struct Batch {
-    int item, off, size;  // groups off .. off + size - 1 of an item
-  };
-  auto batch_at = [&](int item, int off, int left) {  // as even as they come
-    const int here = min(per_item - off, left), n = (here + NF - 1) / NF;
-    return Batch{item, off, (here + n - 1) / n};
-  };
-  auto next_batch = [&](const Batch& b, int left) {
-    const int off = b.off + b.size;
-    return off < per_item ? batch_at(b.item, off, left) : batch_at(b.item + 1, 0, left);
-  };
   auto expert_of = [&](int item) { return KIND == HEADS ? 0 : __builtin_amdgcn_readfirstlane(item_s[item]) & 255; };
   auto block_of = [&](int item) { return KIND == HEADS ? 0 : __builtin_amdgcn_readfirstlane(item_s[item]) >> 8; };
   auto rows_of = [&](int item) { return KIND == HEADS ? p.m : __builtin_amdgcn_readfirstlane(counts[expert_of(item)]) - block_of(item) * CAP; };
@@ -131,7 +120,7 @@ __global__ __launch_bounds__(kRingThreads, 1) void ring_gemm_kernel(StreamGemmAr
       xr[i] = (unsigned)row * (unsigned)p.k * 2u + lcol;
     }
   };
-  auto aim_w = [&](const Batch& b) {
+  auto aim_w = [&](const ring::Batch& b) {
     const long long at = (long long)expert_of(b.item) * p.w_batch + (long long)b.off * GROUP * p.k;
     wa = dev::uniform_ptr(p.w + at);
     if constexpr (KIND == PAIR) wb = dev::uniform_ptr(p.w2 + at);
@@ -139,13 +128,9 @@ __global__ __launch_bounds__(kRingThreads, 1) void ring_gemm_kernel(StreamGemmAr
 #pragma unroll
     for (int i = 0; i < (KIND == PAIR ? NF : 2 * NF); ++i) wr[i] = (unsigned)min(8 * i + lrow, last) * (unsigned)p.k * 2u + lcol;
   };
-  Batch asked = batch_at(0, 0, 0);
-  {
-    const int item = f0 / per_item;
-    asked = batch_at(item, f0 - item * per_item, f1 - f0);
-  }
+  ring::Batch asked = shares.first(f0, f1);
   int left_a = f1 - f0, ja = 0;  // groups from `asked` on, and its next unit
-  Batch used = asked;
+  ring::Batch used = asked;
   int left_u = left_a;
   bool more = count > 0;
   aim_x(asked.item);
@@ -166,7 +151,7 @@ __global__ __launch_bounds__(kRingThreads, 1) void ring_gemm_kernel(StreamGemmAr
       more = left_a > 0;
       if (more) {
         const int was = asked.item;
-        asked = next_batch(asked, left_a);
+        asked = shares.next(asked, left_a);
         if (asked.item != was) aim_x(asked.item);
         aim_w(asked);
       }
@@ -321,7 +306,7 @@ __global__ __launch_bounds__(kRingThreads, 1) void ring_gemm_kernel(StreamGemmAr
     }
     left_u -= used.size;
     if (left_u <= 0) break;
-    used = next_batch(used, left_u);
+    used = shares.next(used, left_u);
   }
 }
 
