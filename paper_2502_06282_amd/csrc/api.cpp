@@ -123,7 +123,7 @@ struct PlanModel {
 };
 
 namespace {
-bool f32_in_parts(long long keys, int head_dim) { return keys > 1024 || keys * head_dim >= 19200; }  // the line: see compute_attn_plan
+bool f32_in_parts(long long keys, int head_dim) { return keys >= (head_dim <= 64 ? 300 : head_dim <= 128 ? 200 : 112); }  // the line: see compute_attn_plan
 
 // A workspace serves every call that is no larger in batch, nodes, heads, head_dim and prefix bound than the one it was
 // sized for.  Partial results alone do not have that order - a smaller call may be cut into more splits, and take more
@@ -340,8 +340,11 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
     if (s > kMaxSplits) return false;  // fp32 path: at most 64 * 1024 keys
     pl->splits = (int)s;
     // Few workgroups: each range in up to eight parts, where the merging launch (3 us) is needed anyway or costs less than
-    // what the parts save (20 nodes, 8 heads, whole / in parts: 200 keys of 128 12.2 / 11.1 us, 120 10.0 / 10.9; 340 of 64 9.8 /
-    // 8.8, 276 8.5 / 8.9).
+    // what the parts save.  A wave's time for a block of keys hardly depends on head_dim up to 64 (maximum, exponentials, trips), so
+    // neither does the line; beyond 128 a workgroup has four waves instead of eight.  Whole / in parts, us, 20 nodes and 8 heads, of 4, 16,
+    // 32 and 64: 256 keys 8.6 / 9.1, 8.6 / 9.1, 8.6 / 9.1, 8.1 / 8.6; 320 10.1 / 9.0, 10.0 / 9.0, 10.1 / 9.1, 9.4 / 8.6; 640 13.8 /
+    // 9.9 and (64) 13.1 / 9.2.  Of 80, 96 and 128: 176 keys 8.3 / 9.5, 8.9 / 9.9, 10.2 / 10.8; 208 9.9 / 9.5, 10.6 / 9.9, 11.9 / 10.9.  Of 192
+    // and 256: 80 14.8 / 14.9, 14.7 / 15.0; 112 15.4 / 15.0, 15.2 / 15.1; 144 18.7 / 15.0, 18.3 / 15.1.
     const long long wgs = units * ((pl->m_rows + 15) / 16) * s;
     pl->parts = pl->splits;
     if (f32_in_parts(keys, d.head_dim))

@@ -209,7 +209,7 @@ def test_an_attention_workspace_covers_every_smaller_call(lib):
     for case in range(4000):
         dtype = rng.choice([0, 0, 0, 1])
         hkv, G = rng.choice([1, 2, 4, 8, 32, 40]), rng.choice([1, 1, 2, 4, 8])
-        D = rng.choice([64, 128]) if dtype == 0 else rng.choice([64, 80, 128])
+        D = rng.choice([64, 128]) if dtype == 0 else rng.choice([16, 64, 80, 128, 192])
         top = 16384 if dtype else rng.choice([600, 4096, 65536, 1 << 20])
         B, T, L = rng.choice([1, 1, 2, 4, 8, 16, 33]), rng.randint(1, 128), rng.randint(0, top)
         large = _desc(B, T, hkv * G, hkv, D, L, dtype)
@@ -217,9 +217,18 @@ def test_an_attention_workspace_covers_every_smaller_call(lib):
         assert have > 0
         for _ in range(6):
             b, t, l = (rng.choice([v, rng.randint(min(lo, v), v)]) for v, lo in ((B, 1), (T, 1), (L, 0)))
-            h, g, d = rng.choice([hkv, max(1, hkv // 2)]), rng.choice([G, max(1, G // 2)]), rng.choice([D, 64])
+            h, g, d = rng.choice([hkv, max(1, hkv // 2)]), rng.choice([G, max(1, G // 2)]), rng.choice([D, min(D, 64)])
             small = _desc(b, t, h * g, h, d, l, dtype)
             assert 0 < lib.jk_tree_verify_attention_workspace(ctypes.byref(small), l) <= have, (dtype, (B, T, hkv, G, D, L), (b, t, h, g, d, l))
+
+
+@pytest.mark.parametrize("D,whole,parts", [(4, 280, 320), (16, 280, 320), (16, 280, 640), (32, 280, 320), (48, 280, 640), (64, 280, 320),
+                                           (80, 190, 208), (128, 176, 208), (192, 104, 112), (256, 104, 112)])
+def test_fp32_calls_of_few_workgroups_are_divided_at_any_head_dim(lib, D, whole, parts):
+    """Partial results, and so bytes of workspace, from the number of keys on at which they pay; small head dimensions
+    take as long per key as 64 does."""
+    ask = lambda keys: lib.jk_tree_verify_attention_workspace(ctypes.byref(_desc(1, 20, 8, 8, D, keys - 20, 1)), keys - 20)
+    assert ask(whole) == ask(40) < ask(parts)
 
 
 def test_the_example_rounds_workspace_serves_each_of_its_calls(lib):
