@@ -140,7 +140,8 @@ def _exact_case(m, n, k, seed):
 
 
 @pytest.mark.parametrize("m,n,k", [(64, 4096, 4096), (41, 4096, 8192), (24, 4100, 8320), (57, 8191, 8192), (64, 2049, 8064), (33, 5120, 10240),
-                                   (65, 4096, 4096), (128, 2048, 4096), (97, 4096, 8192), (73, 6141, 4096)])  # X in two blocks, with and without parts of k
+                                   (65, 4096, 4096), (128, 2048, 4096), (97, 4096, 8192), (73, 6141, 4096),   # X in two blocks, with and without parts of k,
+                                   (80, 6760, 7296), (128, 7012, 2048), (65, 1028, 4096)])                    # and strips that the XCDs do not divide
 def test_two_workgroups_per_strip_are_bit_exact(m, n, k):
     """Products whose k is cut in two: the second workgroup of a strip to finish adds up both.  The workspace may hold
     anything (its words are not cleared for the call), is used by several calls in turn, and nothing is written behind it."""
