@@ -55,6 +55,8 @@ Tuning tuning_from_env() {
   t.attn_deep = env_int("JK_ATTN_DEEP", -1);
   t.accept_single = env_int("JK_ACCEPT_SINGLE", 0);
   t.spin_limit = env_int("JK_SPIN_LIMIT", -1);
+  t.ring_gemm = env_int("JK_RING_GEMM", -1);
+  t.narrow_gemm = env_int("JK_NARROW_GEMM", -1);
   t.verbose = env_int("JK_ATTN_VERBOSE", 0);
   return t;
 }
@@ -886,7 +888,7 @@ jk_status jk_set_tuning(const char* name, int32_t value) {
   const struct { const char* name; int* field; } table[] = {
       {"attn_wm", &t.attn_wm}, {"attn_wn", &t.attn_wn}, {"attn_splits", &t.attn_splits},
       {"attn_fused", &t.attn_fused}, {"attn_deep", &t.attn_deep}, {"accept_single", &t.accept_single}, {"spin_limit", &t.spin_limit},
-      {"verbose", &t.verbose}};
+      {"ring_gemm", &t.ring_gemm}, {"narrow_gemm", &t.narrow_gemm}, {"verbose", &t.verbose}};
   for (const auto& e : table)
     if (std::strcmp(name, e.name) == 0) {
       *e.field = value;

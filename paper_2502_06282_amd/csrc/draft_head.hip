@@ -11,7 +11,7 @@
 //                          top-k by value (ties to the lower token id), probabilities.
 //   router_kernel, gated_act_kernel, select_kernel   the draft layer's router (Eq. 2, 5) and what
 //                          surrounds the experts' three projections (Eq. 3).
-// The products with weight matrices run in stream_gemm.hip.
+// The products with weight matrices run in stream_gemm.hip and ring_gemm.hip.
 
 #include <cmath>
 
@@ -557,7 +557,8 @@ __global__ __launch_bounds__(256) void select_kernel(SelectParams p) {
 }
 
 struct MoePlan {
-  int ring_rows, used;  // ring_rows > 0: the products in ring_gemm.hip, `used` experts with at most so many rows each, as is likely
+  bool ring1, ring2;  // gate and up projections, output projection: in ring_gemm.hip
+  int rows, used;     // `used` experts with at most so many rows each, as is likely
   int split1, split2;
   size_t g_off, up_off, h_off, y_off, total;
 };
@@ -571,9 +572,12 @@ MoePlan moe_plan(int rows, int d, int f, int n) {
   const int each = (2 * rows + used - 1) / used;
   const double mean = 2.0 * rows / n, likely = std::ceil(mean + 3.0 * std::sqrt(mean * (1.0 - 2.0 / n)));
   m.used = used;
-  m.ring_rows = ring_gemm_takes_experts(mean, (int)likely, used, d, f) ? (likely < kRingRows ? (int)likely : kRingRows) : 0;
-  m.split1 = m.ring_rows ? 1 : stream_gemm_ksplit(each, f, d, used, true, 7000);  // gate and up in one launch
-  m.split2 = m.ring_rows ? 1 : stream_gemm_ksplit(each, d, f, used, false, 0);
+  m.rows = likely < kRingRows ? (int)likely : kRingRows;
+  const RingExperts x{mean, likely > kRingRows && mean > 28.0, used, n < 2 * rows ? n : 2 * rows};
+  m.ring1 = ring_gemm_takes_pair(x, f, d);
+  m.ring2 = ring_gemm_takes_down(x, d, f);
+  m.split1 = m.ring1 ? 1 : stream_gemm_ksplit(each, f, d, used, true, 7000);  // gate and up in one launch
+  m.split2 = m.ring2 ? 1 : stream_gemm_ksplit(each, d, f, used, false, 0);
   const size_t pre = m.split1 > 1 ? up((size_t)m.split1 * 2 * rows * f * 4) : 0;
   m.g_off = 0;
   m.up_off = pre;
@@ -727,7 +731,7 @@ hipError_t launch_moe_experts(const MoeArgs& a, hipStream_t stream) {
   } else {
     g.act = h;
   }
-  if ((e = mp.ring_rows ? launch_ring_gemm_pair(g, mp.ring_rows, mp.used, stream) : launch_stream_gemm_pair(g, stream)) != hipSuccess) return e;  // gate and up projections of all experts
+  if ((e = mp.ring1 ? launch_ring_gemm_pair(g, mp.rows, mp.used, stream) : launch_stream_gemm_pair(g, stream)) != hipSuccess) return e;  // gate and up projections of all experts
   if (mp.split1 > 1) {
     ActParams ap;
     ap.g = g.y; ap.up = g.y2; ap.h = h;
@@ -741,7 +745,7 @@ hipError_t launch_moe_experts(const MoeArgs& a, hipStream_t stream) {
   o.sel = a.expert_idx;
   o.ksplit = mp.split2; o.y_split = (long long)a.rows * 2 * a.d_model;
   o.w = static_cast<const uint16_t*>(a.w_down); o.y = reinterpret_cast<float*>(ws + mp.y_off);
-  if ((e = mp.ring_rows ? launch_ring_gemm_down(o, mp.ring_rows, mp.used, stream) : launch_stream_gemm_down(o, stream)) != hipSuccess) return e;
+  if ((e = mp.ring2 ? launch_ring_gemm_down(o, mp.rows, mp.used, stream) : launch_stream_gemm_down(o, stream)) != hipSuccess) return e;
 
   SelectParams sp;
   sp.y = o.y; sp.u = rp.u; sp.s_top = a.s_top;
@@ -762,25 +766,27 @@ struct LinearPlan {
 };
 LinearPlan plan_linear(int m, int n, int k) {
   LinearPlan p{narrow_plan(m, n, k), 1};
-  if (m <= 64 && p.narrow.parts > 0 && 2 * p.narrow.strips * p.narrow.blocks * p.narrow.parts > device_cu_count()) return p;
+  const int forced = tuning().narrow_gemm;
+  if (forced > 0 && p.narrow.parts > 0) return p;
+  if (forced < 0 && m <= 64 && p.narrow.parts > 0 && 2 * p.narrow.strips * p.narrow.blocks * p.narrow.parts > device_cu_count()) return p;
   // (few columns leave CUs without a strip; the estimate of the other way comes out 10 % low, more so for many rows.  Of 100 shapes
   // with 65 - 128 rows none that is taken here is slower, 0.99 - 2.6 times as fast; beyond the line, k very long beside the
   // number of columns: 128 x 4096 x 16384 46 against 57 us, 80 x 5120 x 10240 32 against 36.)
   double ns = 0.0;
   p.ksplit = capped_ksplit(m, n, k, kLinearSplitNs, &ns);
-  if (p.narrow.ns >= (m <= 64 ? 1.04 : 1.06) * ns) p.narrow.parts = 0;
+  if (forced == 0 || p.narrow.ns >= (m <= 64 ? 1.04 : 1.06) * ns) p.narrow.parts = 0;
   return p;
 }
 // A call asks for its plan three times (its bytes, their check, the launch), 0.1 - 1 us each of a thread that has 6 us for a small
 // layer: a thread keeps its last answer.  (A layer of 1024 columns for 10 rows, bound by its enqueueing: 24.0 us a pass, 23.7 like this.)
 LinearPlan linear_plan(int m, int n, int k) {
   struct Last {
-    int m, n, k, cus;
+    int m, n, k, cus, forced;
     LinearPlan plan;
   };
   static thread_local Last last{};
-  const int cus = device_cu_count();
-  if (last.m != m || last.n != n || last.k != k || last.cus != cus) last = Last{m, n, k, cus, plan_linear(m, n, k)};
+  const int cus = device_cu_count(), forced = tuning().narrow_gemm;
+  if (last.m != m || last.n != n || last.k != k || last.cus != cus || last.forced != forced) last = Last{m, n, k, cus, forced, plan_linear(m, n, k)};
   return last.plan;
 }
 }  // namespace

@@ -75,6 +75,9 @@ struct Tuning {
   int attn_deep = -1;      // six-tile K/V ring of the 2x2 arrangement: -1 automatic, 0 never, 1 whenever one workgroup per CU is planned
   int accept_single = 0;   // 1: one-workgroup sampling walk
   int spin_limit = -1;     // polls of the bounded waits (-1: default)
+  // heads and experts by the kernel of equal shares (ring_gemm.hip), linear layers by the one of few columns: -1 automatic, 0 never,
+  // 1 wherever they can be
+  int ring_gemm = -1, narrow_gemm = -1;
   int verbose = 0;
 };
 Tuning& tuning();
@@ -185,14 +188,20 @@ NarrowPlan narrow_plan(int m, int n, int k);
 size_t narrow_gemm_bytes(const NarrowPlan& plan);
 hipError_t launch_narrow_gemm(const StreamGemmArgs& p, const NarrowPlan& plan, void* workspace, hipStream_t stream);
 unsigned long long meeting_tag();  // another one for every launch (see dev::second_to_meet)
-hipError_t launch_stream_gemm_heads(const StreamGemmArgs& p, hipStream_t stream);  // m <= 32
+hipError_t launch_stream_gemm_heads(const StreamGemmArgs& p, hipStream_t stream);  // m <= 64
 hipError_t launch_stream_gemm_pair(const StreamGemmArgs& p, hipStream_t stream);  // m <= 128
 hipError_t launch_stream_gemm_down(const StreamGemmArgs& p, hipStream_t stream);  // m <= 128
 // the same products with equal shares of the weight rows.  rows: how many an expert is likely to have at most (others take
 // several passes over its weights), items: how many experts are likely to be chosen
 constexpr int kRingRows = 32;  // of X at a time
+struct RingExperts {
+  double mean;       // rows of an expert
+  bool many;         // more than kRingRows of them, mostly
+  int likely, most;  // experts that are chosen
+};
 bool ring_gemm_takes_heads(int m, int n);
-bool ring_gemm_takes_experts(double mean, int likely, int items, int d_model, int d_ff);
+bool ring_gemm_takes_pair(const RingExperts& x, int d_ff, int d_model);
+bool ring_gemm_takes_down(const RingExperts& x, int d_model, int d_ff);
 hipError_t launch_ring_gemm_heads(const StreamGemmArgs& p, hipStream_t stream);
 hipError_t launch_ring_gemm_pair(const StreamGemmArgs& p, int rows, int items, hipStream_t stream);
 hipError_t launch_ring_gemm_down(const StreamGemmArgs& p, int rows, int items, hipStream_t stream);

@@ -20,6 +20,7 @@
 #include "jk_device.h"
 #include "jk_internal.h"
 #include "ring_share.h"
+#include "xcd_grid.h"
 
 namespace jk {
 namespace {
@@ -94,7 +95,7 @@ __global__ __launch_bounds__(kRingThreads, 1) void ring_gemm_kernel(StreamGemmAr
 
   // ---- this workgroup's share of the groups (neighbours on one XCD have the same X)
   const int all = gridDim.x, blk = blockIdx.x;
-  const int id = all % 8 == 0 ? (blk & 7) * (all >> 3) + (blk >> 3) : blk;
+  const int id = xcd_place(blk, all);
   const int per_item = (p.n + GROUP - 1) / GROUP;
   const ring::Shares shares{per_item, NF};
   const int f0 = (int)shares.share_begin(items, id, all), f1 = (int)shares.share_begin(items, id + 1, all);
@@ -344,17 +345,40 @@ bool strips_fill(int strips) {
 }
 }  // namespace
 
-// Against strips of 128 rows in turns of workgroups (stream_gemm.hip), over 66 shapes drawn from 1 - 80 rows: heads 0.97 - 1.35
-// times as fast where this takes them, 1.11 in the geometric mean; below two groups per CU, where the strips' kernel divides
-// k, 0.90 - 1.04, beyond 32 rows 0.90 - 1.07.
-bool ring_gemm_takes_heads(int m, int n) { return m <= kRingRows && n >= 32 * device_cu_count() && !strips_fill((n + 127) / 128); }
-// Experts of `mean` rows, and hardly ever more than `likely`: 0.94 - 1.69 times as fast, 1.14 in the mean, over those 66.  One that
-// has more than 32 rows has its weights gone through once per block of so many.  That costs little where few experts do (up
-// to 25 rows in the mean: eleven shapes 1.02 - 1.21; 26 - 30 rows 0.86 - 1.14) or where both launches' strips would leave four
-// fifths of the CUs without work (nine shapes of 46 - 80 rows 1.08 - 1.40); elsewhere it was 0.59 - 1.09.
-bool ring_gemm_takes_experts(double mean, int likely, int items, int d_model, int d_ff) {
-  const int pair = items * ((d_ff + 63) / 64), down = items * ((d_model + 127) / 128), few = device_cu_count() / 5;
-  return (likely <= kRingRows || mean <= 25.0 || (pair <= few && down <= few)) && !(strips_fill(pair) && strips_fill(down));
+// Against strips of 128 rows in turns of workgroups (stream_gemm.hip): where strips fill their turns there is little to gain, and a
+// batch's end (three barriers, its first units, X once more) weighs the more the shorter k is.  Kernel times of 250 heads
+// and 1400 calls of experts, drawn over 1 - 16 tokens, 1 - 80 rows, k 512 - 8192 and 512 - 14336 rows of weights (heads 128256); strips /
+// this, geometric mean (least): heads of less than three quarters of a turn of strips 1.05 - 1.3 (0.93), of more than that
+// 0.99 (0.88); with more turns 1.16 (0.95).  More than 16 logits rows below 42 rows of weights a CU: 0.96 (0.93), three of them.
+bool ring_gemm_takes_heads(int m, int n) {
+  const int cus = device_cu_count(), strips = (n + 127) / 128;
+  if (tuning().ring_gemm >= 0) return tuning().ring_gemm > 0 && m <= kRingRows;
+  if (m > kRingRows || n < (m <= 16 ? 32 : 42) * cus || strips_fill(strips)) return false;
+  return strips < 0.75 * cus || strips > cus;
+}
+// Experts' projections.  Strips that may need another turn (of the experts that rows could choose at most) are slow, and so are strips of
+// experts that nobody chose; experts of more than 32 rows have their weights gone through once per block of so many.  Each of
+// the two launches goes by its own line.  Gate and up: 1.3 in the mean, with few rows and strips up to 2.4; one turn of 0.8 or
+// more 0.99 (0.78), with k up to 640 from half a turn on 0.97 (0.68); full turns of a k that 1024 divides 1.00 (40 rows, eight of 4096 x
+// 4096: the call 150.6 us, by strips 150.1); many rows 1.1 - 1.3 where the strips would leave four
+// fifths of the CUs without work and k is short, else 0.7 - 1.2.
+bool ring_gemm_takes_pair(const RingExperts& x, int d_ff, int d_model) {
+  const int cus = device_cu_count(), per = (d_ff + 63) / 64, strips = x.likely * per;
+  if (tuning().ring_gemm >= 0) return tuning().ring_gemm > 0;
+  if (x.many) return strips <= cus / 5 && d_model < 3072;
+  // (rows of weights a power of two apart meet in the same memory channels, and here more of them at once)
+  const bool turns = x.most * per > cus && !(strips_fill(strips) && d_model % 1024 == 0);
+  return x.mean <= 1.35 || turns || strips < (d_model > 640 ? 0.8 : 0.5) * cus;
+}
+// Output projection: a long k over few columns is divided by the strips' kernel, and not by this one: 0.8 (0.54) from 4096 on, 0.97 from
+// 3072.  Elsewhere up to three quarters of a turn 1.05 (0.75), beyond 0.94 (0.75); other turns 1.17 (0.95), experts of a row or so 1.2.
+// Both lines and the calls' other kernels: 1.174 times as fast as strips alone, one call of twenty more than 1 % slower and one
+// of a hundred 6 %; both projections on one kernel, by one line for both, 1.167, 4 % and 12 %.
+bool ring_gemm_takes_down(const RingExperts& x, int d_model, int d_ff) {
+  const int cus = device_cu_count(), per = (d_model + 127) / 128, strips = x.likely * per;
+  if (tuning().ring_gemm >= 0) return tuning().ring_gemm > 0;
+  if (x.many) return strips <= cus / 6 && d_ff <= 1024;
+  return x.mean <= 1.35 || x.most * per > cus || (strips <= 0.75 * cus && (strips > cus / 6 || d_ff <= 3072));
 }
 hipError_t launch_ring_gemm_heads(const StreamGemmArgs& p, hipStream_t stream) { return launch_rows<HEADS>(p, p.m, 1, stream); }
 hipError_t launch_ring_gemm_pair(const StreamGemmArgs& p, int rows, int items, hipStream_t stream) { return launch_rows<PAIR>(p, rows, items, stream); }

@@ -17,6 +17,7 @@ import pytest
 import torch
 
 import paper_2502_06282_amd as jk
+from gpu_util import tune
 from oracle import draft_head as dh
 from workloads import draft_head_inputs
 
@@ -254,3 +255,10 @@ def test_equal_shares_of_the_vocabulary_are_bit_exact(rows, d, vocab):
     x["f_top"][0, 1, 3] = np.nan                         # left out where its coefficient is zero
     lg, *_ = _call(x, mode=jk.JK_HEADS_CONTRASTIVE, alpha=0.0, beta=2.0)
     assert np.isnan(lg[0, 0]).all() and np.isfinite(lg[0, 1]).all() and np.isfinite(lg[1:]).all()
+
+
+@pytest.mark.parametrize("forced", [0, 1], ids=["strips", "equal_shares"])
+@pytest.mark.parametrize("rows,d,vocab", [(1, 128, 700), (5, 640, 9001), (9, 512, 25752), (16, 384, 32768), (12, 256, 24577)])
+def test_either_kernel_takes_the_heads(forced, rows, d, vocab):
+    tune("ring_gemm", forced)
+    test_equal_shares_of_the_vocabulary_are_bit_exact(rows, d, vocab)

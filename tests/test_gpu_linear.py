@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import paper_2502_06282_amd as jk
+from gpu_util import tune
 from oracle import draft_head as dh
 from workloads import round_to_bf16
 
@@ -180,3 +181,12 @@ def test_linear_layers_replay_in_a_graph():
         for g, e in zip(got, (want, want, want2, want2)):
             np.testing.assert_array_equal(g.cpu().numpy(), e)
         np.testing.assert_array_equal(eager.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("forced", [0, 1], ids=["strips", "few_columns"])
+@pytest.mark.parametrize("m,n,k", [(1, 60, 384), (64, 4100, 1152), (80, 6760, 640), (128, 8192, 256)])
+def test_either_kernel_takes_a_layer(forced, m, n, k):
+    x, w, r, want = _exact_case(m, n, k, m + k)
+    for force in (forced, -1, forced):                   # (a thread's last plan is that of the last call's knob)
+        tune("narrow_gemm", force)
+        np.testing.assert_array_equal(jk.linear(_bf(x), _bf(w), _bf(r), out_dtype=torch.float32).cpu().numpy(), want)

@@ -15,6 +15,7 @@ import pytest
 import torch
 
 import paper_2502_06282_amd as jk
+from gpu_util import tune
 from oracle import draft_head as dh
 from workloads import draft_head_inputs, moe_inputs
 
@@ -271,3 +272,21 @@ def test_more_rows_than_an_expert_is_likely_to_have(rows, d, f, n):
                                         (62, 640, 1664, 5), (50, 256, 6400, 4)])                  # a mean just below 25 rows, and 25
 def test_equal_shares_of_the_experts_rows(rows, d, f, n):
     _check(moe_inputs(rows, d, f, n, seed=rows + 7), min_gap=1e-6)
+
+
+@pytest.mark.parametrize("forced", [0, 1], ids=["strips", "equal_shares"])
+@pytest.mark.parametrize("rows,d,f,n", [(3, 384, 640, 5), (46, 640, 512, 2), (80, 768, 512, 4), (128, 384, 256, 2), (50, 256, 6400, 4)])
+def test_either_kernel_takes_the_projections(forced, rows, d, f, n):
+    """ring_gemm forces both projections onto one of the two kernels, experts of several blocks of 32 rows among them."""
+    tune("ring_gemm", forced)
+    x = moe_inputs(rows, d, f, n, seed=rows + 11)
+    _check(x, min_gap=1e-6)
+    x["u"] = np.repeat(x["u"][:1], rows, axis=0)                          # and all rows on the same two experts
+    _check(x, min_gap=1e-6)
+
+
+@pytest.mark.parametrize("rows,d,f,n", [(15, 768, 13312, 2),    # gate and up by equal shares, the output projection by strips, divided
+                                        (40, 1408, 1792, 8),    # the other way round
+                                        (14, 768, 2944, 5), (36, 7552, 640, 2), (30, 512, 2048, 8), (2, 512, 8192, 2)])
+def test_projections_on_different_kernels(rows, d, f, n):
+    _check(moe_inputs(rows, d, f, n, seed=rows + 13), min_gap=1e-6)

@@ -244,6 +244,19 @@ def test_the_example_rounds_workspace_serves_each_of_its_calls(lib):
                         assert ask(1 + width * dep) <= have, (batch, hq, hkv, prefix, depth, width, dep)
 
 
+@pytest.mark.parametrize("rows,d,f,n", [(15, 768, 13312, 2), (3, 768, 11008, 2), (25, 1024, 10368, 2), (44, 3072, 11008, 2)])
+def test_long_output_projections_of_few_strips_are_divided(lib, rows, d, f, n):
+    """The kernel of equal shares does not divide k: few columns and a long k go to the other one, whichever takes the gate
+    and up projections (by the bytes of partial results)."""
+    undivided = 2 * rows * (2 * f + 4 * d)
+    assert lib.jk_moe_experts_workspace(ctypes.byref(binding.MoeDesc(rows, d, f, n))) >= undivided + 2 * rows * 4 * d
+    try:
+        lib.jk_set_tuning(b"ring_gemm", 1)
+        assert lib.jk_moe_experts_workspace(ctypes.byref(binding.MoeDesc(rows, d, f, n))) < undivided + 1024
+    finally:
+        lib.jk_set_tuning(b"ring_gemm", -1)
+
+
 def test_a_draft_workspace_covers_fewer_rows(lib):
     """The same for the draft side's calls: the weights stay, the number of rows changes from call to call, and fewer
     rows may be cut into more parts."""
