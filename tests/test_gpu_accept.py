@@ -716,30 +716,39 @@ def test_sample_walk_of_many_trees_replays_in_a_graph(limit):
     assert jk.last_device_error(ws) == 0
 
 
+@pytest.mark.parametrize("V", [9000, 262145], ids=["256-threads", "512-threads"])
 @pytest.mark.parametrize("rows", ["huge", "lowest", "masked"])
-def test_sample_logits_of_extreme_size(rows):
+def test_sample_logits_of_extreme_size(rows, V):
     """Logits whose exponentials need a reference far from zero (3e30, where a power of two is no longer near enough), rows
-    masked with the type's lowest value but for a few entries, in one slice only, and rows of -inf but for a few."""
+    masked with the type's lowest value but for a few entries, in one slice only, and rows of -inf but for a few.  Drafts
+    that overstate their candidate, so that walks reject, go on with what is left of such a row, and accept behind it."""
     rng = np.random.default_rng(5)
-    V, N = 9000, 5
+    N = 5
     z = rng.standard_normal((1, N + 1, V)).astype(np.float32)
     if rows == "huge":
         z = z * np.float32(3e30)
     else:
-        keep = rng.choice(1000, 40, replace=False) + 3000
+        keep = rng.choice(1000, 40, replace=False) + V // 3
         m = np.full_like(z, np.finfo(np.float32).min if rows == "lowest" else -np.inf)
         m[..., keep] = z[..., keep] * 4
         z = m
     par = np.array([[-1, -1, 0, 0, 1]], dtype=np.int32)
     a = {"logits": z, "draft_probs": np.empty((1, N, V), np.float32), "tokens": np.empty((1, N), np.int32)}
-    for k in range(N):
-        x = z[0, par[0, k] + 1].astype(np.float64)
-        e = np.exp(x - x.max())
-        a["draft_probs"][0, k] = (e / e.sum()).astype(np.float32)
-        a["tokens"][0, k] = int(np.argsort(-x)[k % 2])
-    for u in (0.05, 0.6, 0.95):
-        a["uniforms"] = np.full((1, N + 1), u, dtype=np.float32)
-        _compare(a, par, "sample")
+    seen = set()
+    for other in (0, 1):
+        for k in range(N):
+            x = z[0, par[0, k] + 1].astype(np.float64)
+            e = np.exp(x - x.max())
+            a["tokens"][0, k] = int(np.argsort(-x)[(k + other) % 2])
+            q = 0.5 * e / e.sum()
+            q[a["tokens"][0, k]] += 0.5
+            a["draft_probs"][0, k] = q.astype(np.float32)
+        for u in (0.05, 0.6, 0.95):
+            a["uniforms"] = np.full((1, N + 1), u, dtype=np.float32)
+            assert _compare(a, par, "sample") == 0
+            r = oracle_accept(a["tokens"][0], par[0], a["logits"][0], "sample", a["draft_probs"][0], a["uniforms"][0])
+            seen.add("".join(d[0][0] for d in r.decisions))       # r(ejected), a(ccepted), b(onus)
+    assert any("ra" in w for w in seen) and any("rb" in w for w in seen) and any(w.startswith("a") for w in seen), seen
 
 
 @pytest.mark.parametrize("B,T,V", [
