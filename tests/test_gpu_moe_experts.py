@@ -275,7 +275,8 @@ def test_equal_shares_of_the_experts_rows(rows, d, f, n):
 
 
 @pytest.mark.parametrize("forced", [0, 1], ids=["strips", "equal_shares"])
-@pytest.mark.parametrize("rows,d,f,n", [(3, 384, 640, 5), (46, 640, 512, 2), (80, 768, 512, 4), (128, 384, 256, 2), (50, 256, 6400, 4)])
+@pytest.mark.parametrize("rows,d,f,n", [(3, 384, 640, 5), (46, 640, 512, 2), (80, 768, 512, 4), (128, 384, 256, 2), (50, 256, 6400, 4), (128, 128, 256, 64),
+                                        (65, 128, 128, 63)])
 def test_either_kernel_takes_the_projections(forced, rows, d, f, n):
     """ring_gemm forces both projections onto one of the two kernels, experts of several blocks of 32 rows among them."""
     tune("ring_gemm", forced)
