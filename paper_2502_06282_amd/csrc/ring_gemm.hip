@@ -381,27 +381,26 @@ bool ring_gemm_takes_heads(int m, int n) {
 }
 // Experts' projections.  Strips that may need another turn (of the experts that rows could choose at most) are slow, and so are strips of
 // experts that nobody chose; experts of more than 32 rows have their weights gone through once per block of so many.  Each of
-// the two launches goes by its own line.  Gate and up: 1.3 in the mean, with few rows and strips up to 2.4; one turn of 0.8 or
-// more 0.99 (0.78), with k up to 640 from half a turn on 0.97 (0.68); full turns of a k that 1024 divides 1.00 (40 rows, eight of 4096 x
-// 4096: the call 150.6 us, by strips 150.1); many rows 1.1 - 1.3 where the strips would leave four
-// fifths of the CUs without work and k is short, else 0.7 - 1.2.
+// the two launches goes by its own line.  Gate and up: 1.3 in the mean, with few rows and strips up to 2.7; one turn of 0.85 or
+// more 1.0 (0.8); full turns of a k that 1024 divides 1.00 (40 rows, eight of 4096 x 4096: the call 150.6 us, by strips 150.1); many
+// rows 1.1 - 1.3 where the strips would leave four fifths of the CUs without work and k is short, else 0.7 - 1.2.
 bool ring_gemm_takes_pair(const RingExperts& x, int d_ff, int d_model) {
   const int cus = device_cu_count(), per = (d_ff + 63) / 64, strips = x.likely * per;
   if (tuning().ring_gemm >= 0) return tuning().ring_gemm > 0;
   if (x.many) return strips <= cus / 5 && d_model < 3072;
   // (rows of weights a power of two apart meet in the same memory channels, and here more of them at once)
-  const bool turns = x.most * per > cus && !(strips_fill(strips) && d_model % 1024 == 0);
-  return x.mean <= 1.35 || turns || strips < (d_model > 640 ? 0.8 : 0.5) * cus;
+  const bool turns = x.most * per > cus && !(strips_fill(x.most * per) && d_model % 1024 == 0);
+  return x.mean <= 2.0 || turns || strips < 0.85 * cus;
 }
 // Output projection: a long k over few columns is divided by the strips' kernel, and not by this one: 0.8 (0.54) from 4096 on, 0.97 from
-// 3072.  Elsewhere up to three quarters of a turn 1.05 (0.75), beyond 0.94 (0.75); other turns 1.17 (0.95), experts of a row or so 1.2.
-// Both lines and the calls' other kernels: 1.174 times as fast as strips alone, one call of twenty more than 1 % slower and one
-// of a hundred 6 %; both projections on one kernel, by one line for both, 1.167, 4 % and 12 %.
+// 3072.  Elsewhere up to 0.85 of a turn 1.07 (0.76), beyond 0.95 (0.75); other turns 1.2 (0.95), experts of a row or so 1.25.
+// Both lines and the calls' other kernels: 1.207 times as fast as strips alone, one call of a hundred 6 % slower; both projections on
+// one kernel, by one line for both, 1.201 and 9 %.
 bool ring_gemm_takes_down(const RingExperts& x, int d_model, int d_ff) {
   const int cus = device_cu_count(), per = (d_model + 127) / 128, strips = x.likely * per;
   if (tuning().ring_gemm >= 0) return tuning().ring_gemm > 0;
   if (x.many) return strips <= cus / 6 && d_ff <= 1024;
-  return x.mean <= 1.35 || x.most * per > cus || (strips <= 0.75 * cus && (strips > cus / 6 || d_ff <= 3072));
+  return x.mean <= 2.0 || x.most * per > cus || (strips < 0.85 * cus && (strips > cus / 6 || d_ff <= 3072));
 }
 hipError_t launch_ring_gemm_heads(const StreamGemmArgs& p, hipStream_t stream) { return launch_rows<HEADS>(p, p.m, 1, stream); }
 hipError_t launch_ring_gemm_pair(const StreamGemmArgs& p, int rows, int items, hipStream_t stream) { return launch_rows<PAIR>(p, rows, items, stream); }
