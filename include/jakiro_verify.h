@@ -29,7 +29,9 @@
  * Conventions
  *   - "device" pointers are HIP device memory of the current device; "host"
  *     pointers are ordinary host memory.  The caller owns every buffer.  The
- *     library allocates no device memory and keeps no state between calls;
+ *     library allocates no device memory and keeps nothing between calls that a result
+ *     depends on (it counts linear layers, so that each has a tag of its own, and a thread
+ *     remembers the plan of its last one);
  *     scratch comes from the caller's workspace (sizes from the *_workspace
  *     functions; 256-byte aligned).  A workspace handed to jk_accept_path or
  *     jk_tree_verify_attention(_paged) must have been zero-filled once

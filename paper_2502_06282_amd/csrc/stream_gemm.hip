@@ -7,11 +7,10 @@
 // cycle on, each register asked for again as soon as its last product is issued; only X goes through LDS, one chunk of k
 // ahead of its use, shared by the workgroup's eight waves; one barrier per chunk.  Narrow strips (128 weight rows) and
 // whole k ranges where that gives every CU a workgroup, k split into as many parts as it takes otherwise.
-// Measured on an MI355X (weights cold, us): 40 rows, 4096 x 8192 15.2, 6144 x 4096 13.5, 4096 x 4096 9.4; 16 x 4096 x 4096
-// 98; 20 rows, 128256 x 4096 175 (6.0 TB/s), 80 rows 204; 32768 x 4096, 4 rows 47 (5.7 TB/s), 128 rows 63: with many
-// rows a CU draws as many bytes of X from L2 as of weights.  With weights through LDS rings and strips of 512 rows the
-// same products took 35.3, 22.9, 21.3, 114 and 177 us.  Non-temporal weight loads (-10 %), chunks of 512 and more
-// weights in flight (no difference) were tried.
+// Measured on an MI355X (weights cold, us): eight experts' gate and up projections of 4096 x 4096 98; 20 rows, 128256 x 4096
+// 175 (6.0 TB/s), 80 rows 204; 32768 x 4096, 4 rows 47 (5.7 TB/s), 128 rows 63: with many rows a CU draws as many bytes of X
+// from L2 as of weights.  With weights through LDS rings and strips of 512 rows the first two took 114 and 177 us.
+// Non-temporal weight loads (-10 %), chunks of 512 and more weights in flight (no difference) were tried.
 #include <cmath>
 #include <type_traits>
 
