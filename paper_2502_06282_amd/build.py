@@ -15,7 +15,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libjakiro_verify.so")
 NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["api.cpp", "tva_f32.hip", "tva_combine.hip", "accept.hip", "accept_coop.hip", "commit.hip",
-           "draft_head.hip", "draft_tree.hip", "stream_gemm.hip", "ring_gemm.hip", "tva_wide.hip"]
+           "draft_head.hip", "draft_tree.hip", "stream_gemm.hip", "ring_gemm.hip", "tva_wide.hip", "tva_direct.hip"]
 # matrix results in ordinary registers: by default a kernel of more than 256 registers keeps all of them in accumulation
 # registers, which the vector unit cannot read (32 moves per tile for the scores of tva_wide.hip)
 UNIT_FLAGS = {"tva_wide.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}

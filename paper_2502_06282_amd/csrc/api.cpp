@@ -122,6 +122,14 @@ struct PlanModel {
                                 // take up to this much longer
   double wide_stream = 1.0e7, wide_turn = 5.3, wide_call = 2.8, wide_level = 2.0, wide_merge_per_mb = 0.57;
   double wide_margin = 1.02;    // (near ties go to the others)
+  // 16 rows per workgroup and K, V in registers (tva_direct.hip): us of a call outside its blocks, per turn of four blocks of 32
+  // keys, per workgroup of a CU beyond the first, for trees of more than 64 nodes (their ancestors); bytes per us that a CU
+  // draws of K and V, and all CUs together.  Fitted to 371 timed calls of drawn shapes of up to 900 keys of prefix (5.4 % rms).
+  // The others' estimates of such short calls are 1.2 times what they take (2x2 waves, geometric mean): direct_level puts
+  // this one beside them.  (At 1.25 the 400 shapes take 0.856 of what they took without this kernel, the best choice would take
+  // 0.854; at 1.0 0.866, and some 1.28 of it.)
+  double direct_call = 3.78, direct_call_d64 = 3.59, direct_round = 0.90, direct_round_d64 = 0.75, direct_next = 0.78,
+         direct_deep_tree = 0.50, direct_draw = 6.73e4, direct_stream = 3.93e7, direct_level = 1.25;
 };
 
 namespace {
@@ -194,7 +202,7 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
     const Tuning& tn = tuning();
     const int forced_wm = tn.attn_wm, forced_wn = tn.attn_wn, forced_s = tn.attn_splits;  // tuning overrides
     const int fused_mode = !fused_allowed ? 0 : tn.attn_fused;  // 0 never, 1 whenever possible, -1 when it pays
-    static const int kArr[][2] = {{2, 2}, {4, 1}, {8, 1}};  // waves along rows x along keys
+    static const int kArr[][2] = {{2, 2}, {4, 1}, {8, 1}, {1, 4}};  // waves along rows x along keys ({1, 4}: tva_direct.hip, 16 rows)
     bool forced_ok = false;
     for (const auto& a : kArr) forced_ok |= (a[0] == forced_wm && a[1] == forced_wn);
     double best_cost = 0.0, best_part_mb = 0.0;
@@ -203,7 +211,8 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
       const int wm = a[0], wn = a[1];
       if (wm == 8 && !forced_ok && (pl->m_rows <= 96 || tn.attn_fused == 0)) continue;  // (mostly padding rows; it has no second launch)
       if (forced_ok ? (wm != forced_wm || wn != forced_wn) : (wm > 2 && pl->m_rows <= 16 * wm)) continue;  // mostly padding rows
-      const int q_rows = 32 * wm;
+      const bool direct = wm == 1;
+      const int q_rows = direct ? 16 : 32 * wm;
       const int n_qtiles = (pl->m_rows + q_rows - 1) / q_rows;
       const long long wgs = units * n_qtiles;
       const int kt = wm == 4 ? 2 : 1;  // (4x1: tiles in pairs, the hand-pipelined two-tile path)
@@ -217,6 +226,10 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
         const long long s_min = (n_tiles + kMaxTilesPerSplit - 1) / kMaxTilesPerSplit;
         if (s < s_min) s = s_min;
         if (s > kMaxSplits) continue;
+        if (direct && s > 1) break;
+        // (with more workgroups than CUs K and V are drawn again and again: 0.58 - 0.97 of the others' time up to seven tiles
+        // of keys, 0.94 - 1.13 beyond; nor is the estimate known to hold beyond the keys it was fitted to)
+        if (direct && !forced_ok && (n_tiles > 28 || (wgs > slots && n_tiles > 7))) break;
         if (s > 1 && forced_s < 1 && (size_t)(wgs * s * q_rows) > most_rows) continue;  // (one split always fits)
         if (wm == 8 && s > 1 && (wgs * s > kMaxWideMerged || (size_t)wgs * s * q_rows * d.head_dim * sizeof(float) > kFineBytes)) continue;
         // rounds of the longest split: the 4x1 arrangement deals tiles (an odd last tile costs about
@@ -311,6 +324,14 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
           while ((1 << levels) < s) ++levels;
           cost = km.wide_margin * (km.wide_call + turns * (km.wide_turn + std::sqrt(std::sqrt(l2 * l2 + m2 * m2))) + km.wide_level * levels +
                                    km.wide_merge_per_mb * 2.0 * part_mb * (double)(s - 1) / (double)s);
+        }
+        if (direct) {
+          const double per_cu = (double)((all_wgs + slots - 1) / slots);
+          const double loop = (double)((n_tiles + 3) / 4) * (d.head_dim == 64 ? km.direct_round_d64 : km.direct_round);
+          const double draw = per_cu * kv_bytes / km.direct_draw, l2 = loop * loop, m2 = draw * draw;
+          cost = km.direct_level * ((d.head_dim == 64 ? km.direct_call_d64 : km.direct_call) + std::sqrt(std::sqrt(l2 * l2 + m2 * m2)) +
+                                    (double)units * kv_bytes / km.direct_stream + (per_cu - 1.0) * km.direct_next +
+                                    (d.n_tree > 64 ? km.direct_deep_tree : 0.0));
         }
         if (!have || cost < best_cost) {
           have = true;

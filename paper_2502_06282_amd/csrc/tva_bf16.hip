@@ -1407,6 +1407,7 @@ hipError_t launch_tva_bf16(const AttnArgs& a, const AttnPlan& pl, hipStream_t st
   kp.merge_shift = 0;
   while ((1 << kp.merge_shift) < pl.splits) ++kp.merge_shift;
   if (pl.wm == 8) return tva::launch_wide(kp, d.head_dim, stream);
+  if (pl.wm == 1) return tva::launch_direct(kp, d.head_dim, stream);
   switch (fused ? tva::merge_of(pl.splits) : 0) {
     case 0: return tva::launch_merged<0>(kp, d.head_dim, pl, stream);
     case 1: return tva::launch_merged<1>(kp, d.head_dim, pl, stream);

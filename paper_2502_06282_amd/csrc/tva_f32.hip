@@ -17,7 +17,7 @@
 // heads of 128, 52 nodes, 2100 keys 481, 56.4 and 56.
 #include <type_traits>
 
-#include "jk_internal.h"
+#include "jk_ancestors.h"
 #include "jk_wave.h"
 
 namespace jk {
@@ -36,50 +36,6 @@ struct FParams {
   long long q_sb, q_st, q_sh, kc_sb, kc_sl, kc_sh, kt_sb, kt_st, kt_sh, o_sb, o_st, o_sh;
   float scale;
 };
-
-// The ancestors of a node (with itself), as a lane needs them for its row: bits of nodes 0 - 63 and 64 - 127.  A lane holds
-// nodes lane and lane + 64; sets and pointers double their reach every round, by exchanges across the wave: no barrier, and no
-// wave that the others wait for.  (One wave for all, through LDS: it came 2500 cycles after the others to the barrier.)
-struct Ancestors {
-  unsigned long long lo, hi;
-};
-__device__ __forceinline__ unsigned long long shfl64(unsigned long long v, int lane) {
-  return (unsigned)__shfl((int)(unsigned)v, lane) | (unsigned long long)(unsigned)__shfl((int)(unsigned)(v >> 32), lane) << 32;
-}
-__device__ __forceinline__ Ancestors ancestors_of(const FParams& p, int pa0, int pa1, int node, bool report) {
-  const int lane = threadIdx.x & 63;
-  const bool ok0 = lane >= p.T || (pa0 >= -1 && pa0 < lane), ok1 = lane + 64 >= p.T || (pa1 >= -1 && pa1 < lane + 64);
-  if (report && __any(!ok0 || !ok1) && lane == 0) __hip_atomic_fetch_or(p.err, kDevErrBadTree, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  int up0 = ok0 && lane < p.T ? pa0 : -1;
-  unsigned long long own0 = 1ull << lane;  // of node `lane`: all its ancestors are below 64
-  while (__any(up0 >= 0)) {
-    const int from = max(up0, 0);
-    const unsigned long long set = shfl64(own0, from);
-    const int next = __shfl(up0, from);
-    if (up0 >= 0) {
-      own0 |= set;
-      up0 = next;
-    }
-  }
-  if (p.T <= 64) return Ancestors{shfl64(own0, node), 0ull};
-  int up1 = ok1 && lane + 64 < p.T ? pa1 : -1;
-  unsigned long long low1 = 0ull, own1 = 1ull << lane;  // of node lane + 64
-  while (__any(up1 >= 0)) {
-    const int from = max(up1, 0) & 63;
-    const unsigned long long below = shfl64(own0, from), low = shfl64(low1, from), set = shfl64(own1, from);
-    const int next = __shfl(up1, from);
-    if (up1 >= 64) {
-      low1 |= low;
-      own1 |= set;
-      up1 = next;
-    } else if (up1 >= 0) {
-      low1 |= below;
-      up1 = -1;
-    }
-  }
-  const unsigned long long a = shfl64(own0, node & 63), l = shfl64(low1, node & 63), h = shfl64(own1, node & 63);
-  return node < 64 ? Ancestors{a, 0ull} : Ancestors{l, h};
-}
 
 // KJ: 16-column chunks of a head (rounded up); WAVES: by how many registers that leaves
 template <int KJ>
@@ -140,8 +96,8 @@ __global__ __launch_bounds__(64 * waves_for<KJ>(), KJ <= 8 ? 2 : 1) void tva_f32
 
   // The waves with fewer blocks of the prefix take the tree's first; who has one makes its rows' ancestors while the keys come
   const int first = (wave + WAVES - n_prefix % WAVES) % WAVES;
-  Ancestors seen{0ull, 0ull};
-  if (first < n_tree || (split == 0 && wave == 0)) seen = ancestors_of(p, pa0, pa1, node, split == 0 && row0 == 0 && kv == 0 && wave == 0);
+  dev::Ancestors seen{0ull, 0ull};
+  if (first < n_tree || (split == 0 && wave == 0)) seen = dev::ancestors_of(p.T, p.err, pa0, pa1, node, split == 0 && row0 == 0 && kv == 0 && wave == 0);
 
   // A weight of zero - an unseen key's above all - leaves its value out, whatever that is.  The matrix product has one
   // value for sixteen rows' weights, so an infinity or a NaN reaches them all; it stays in the accumulators to the end, and

@@ -40,6 +40,8 @@ struct KParams {
 
 // One call with the kernel of 256 query rows per workgroup (tva_wide.hip)
 hipError_t launch_wide(const KParams& kp, int head_dim, hipStream_t stream);
+// One undivided call with the kernel of 16 query rows per workgroup that takes K and V straight into registers (tva_direct.hip)
+hipError_t launch_direct(const KParams& kp, int head_dim, hipStream_t stream);
 }  // namespace tva
 
 namespace {
