@@ -792,6 +792,7 @@ jk_status jk_tree_grow(const jk_tree_state* state, int32_t batch, int32_t n_fron
   a.tokens = state->tokens; a.parent = state->parent; a.q_row = state->q_row; a.n_nodes = state->n_nodes;
   a.score = state->score;
   a.frontier_in = frontier_in; a.cand_tok = cand_tokens; a.cand_p = cand_probs; a.frontier_out = frontier_out;
+  a.mg_top_k = 65536u / (unsigned)top_k + 1u;
   return launch_tree_grow(a, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? JK_OK : JK_ERR_HIP;
 }
 

@@ -15,6 +15,7 @@
 #include <climits>
 
 #include "jk_internal.h"
+#include "jk_wave.h"
 
 namespace jk {
 namespace {
@@ -85,53 +86,67 @@ __device__ __forceinline__ int count_before(bool flag, int t, int* s_cnt, int& t
   return before;
 }
 
-// Bound by latency: a few hundred bytes per sequence, so what counts is how many trips to memory follow each other.
-// The candidate, its token, the frontier entry and the node count are asked for together; only the parent's score
-// depends on one of them.  Eight sequences, five expanded nodes of ten candidates: 3.4 us a launch, and 4.3 with the loads
-// one after the other.
-__global__ __launch_bounds__(kTreeThreads) void grow_kernel(TreeGrowArgs a) {
+// Bound by latency: a few hundred bytes per sequence, so what counts is how many trips to memory follow each other, and
+// behind them the instructions of a wave (8 cycles each where one waits for the other).  Everything is asked for at once: the
+// candidate, its token, the frontier entry, the node count, and the scores of all nodes, of which the parents' are then taken
+// from LDS instead of memory.  Four waves for each 64 candidates hold them against each other.  us under the tracer, eight
+// sequences, the parent's score asked for behind the frontier's entry and four waves for any number / like this: five expanded
+// nodes of ten candidates 3.8 / 3.7, ten of 18 6.2 / 5.1.
+template <int kWaves>
+__global__ __launch_bounds__(64 * kWaves) void grow_kernel(TreeGrowArgs a) {
+  constexpr int kThreads = 64 * kWaves, kOld = kMaxGrowNodes / kThreads;
   __shared__ __align__(16) float s_sc[kTreeThreads];
+  __shared__ float s_old[kMaxGrowNodes];
   __shared__ int s_rank[kTreeThreads];
-  __shared__ int s_cnt[kTreeWaves];
+  __shared__ int s_cnt[kWaves];
   __shared__ int s_first;
   const int b = blockIdx.x, t = threadIdx.x;
   const int C = a.n_front * 2 * a.top_k;  // <= kTreeThreads (checked by the host)
-  const int f = min(t / (2 * a.top_k), a.n_front - 1), e = (t / a.top_k) & 1;
-  const long long row = (long long)b * a.n_front + f, at_c = (long long)b * C + min(t, C - 1);
+  const int slot_e = (int)(((unsigned)min(t, C - 1) * a.mg_top_k) >> 16);  // candidate / top_k
+  const int f = slot_e >> 1, e = slot_e & 1;
+  const long long row = (long long)b * a.n_front + f, at_c = (long long)b * C + min(t, C - 1), first = (long long)b * a.max_nodes;
+  const int n_raw = a.n_nodes[b];
   const float p = a.cand_p[at_c];
   const int tok = a.cand_tok[at_c];
-  const int pid = a.frontier_in ? a.frontier_in[row] : -1;
-  const int n0 = min(max(a.n_nodes[b], 0), a.max_nodes);  // (a count the caller forgot to clear must not fault)
-  const bool has_parent = pid >= 0 && pid < a.max_nodes;
-  const float parent_score = has_parent ? a.score[(long long)b * a.max_nodes + pid] : 1.0f;
+  int pid = -1;
+  float old_score[kOld];
+  if (a.frontier_in) {
+    pid = a.frontier_in[row];
+#pragma unroll
+    for (int i = 0; i < kOld; ++i) old_score[i] = a.score[first + min(t + kThreads * i, a.max_nodes - 1)];
+#pragma unroll
+    for (int i = 0; i < kOld; ++i) s_old[t + kThreads * i] = old_score[i];
+  }
+  if (t < kTreeThreads) s_rank[t] = 0;
+  if (t == 0) s_first = INT_MAX;
+  __syncthreads();
+  const int n0 = min(max(n_raw, 0), a.max_nodes);  // (a count the caller forgot to clear must not fault)
   const int id = n0 + t;
   const bool valid = t < C && id < a.max_nodes;
-  float sc = -INFINITY;
+  const bool old = pid >= 0 && pid < n0;
+  const float sc = valid ? (old ? s_old[pid] : 1.0f) * p : -INFINITY;
+  if (t < kTreeThreads) s_sc[t] = sc;  // (entries from C on hold -inf and a larger index: they beat nobody)
   if (valid) {
-    const bool old = has_parent && pid < n0;
-    sc = (old ? parent_score : 1.0f) * p;
-    const long long at = (long long)b * a.max_nodes + id;
+    const long long at = first + id;
     a.tokens[at] = tok;
     a.parent[at] = old ? pid : -1;
     a.score[at] = sc;
     a.q_row[at] = a.q_row_base + (int)(2 * row) + e;
   }
-  s_sc[t] = sc;  // (entries from C on hold -inf and a larger index: they beat nobody)
-  s_rank[t] = 0;
-  if (t == 0) s_first = INT_MAX;
   __syncthreads();
-  count_beaten<kTreeWaves>(s_sc, C, s_rank, t);
+  count_beaten<kWaves>(s_sc, C, s_rank, t);
   __syncthreads();
   const bool sel = valid && s_rank[t] < a.width;
   int total;
-  const int slot = count_before<kTreeWaves>(sel, t, s_cnt, total);
+  const int slot = count_before<kWaves>(sel, t, s_cnt, total);
   if (sel) {
     a.frontier_out[(long long)b * a.width + slot] = id;
     if (slot == 0) s_first = id;
   }
-  __syncthreads();
-  // fewer new nodes than frontier slots: the rest repeats the first entry (-1 if there is none)
-  if (t >= total && t < a.width) a.frontier_out[(long long)b * a.width + t] = s_first == INT_MAX ? -1 : s_first;
+  if (total < a.width) {  // (uniform) fewer new nodes than frontier slots: the rest repeats the first entry (-1 if there is none)
+    __syncthreads();
+    if (t >= total && t < a.width) a.frontier_out[(long long)b * a.width + t] = s_first == INT_MAX ? -1 : s_first;
+  }
   if (t == 0) a.n_nodes[b] = min(n0 + C, a.max_nodes);
 }
 
@@ -227,27 +242,83 @@ __global__ __launch_bounds__(kTreeThreads) void fill_static_kernel(TreeGrowArgs 
   if (t == 0) a.n_nodes[b] = min(n0 + n_new, a.max_nodes);
 }
 
+// Order of scores as unsigned numbers (the two zeros are equal; a NaN's key is not used)
+__device__ __forceinline__ unsigned score_key(float v) {
+  const unsigned u = __float_as_uint(v + 0.f);
+  return (u >> 31) ? ~u : u | 0x80000000u;
+}
+
 // A thread per node.  Everything a node holds is asked for before its sequence's node count is known (the arrays are
-// max_nodes long): one trip to memory instead of three, and the comparisons are spread over sixteen waves.  Eight
-// sequences of 260 nodes, 60 kept: 6.0 us, and 18.2 with four waves and three trips.
+// max_nodes long): one trip to memory instead of three.  Which nodes are kept: a histogram of the scores' upper bits (sign,
+// exponent and two more: some five nodes to a bin) says in which bin the last one lies; the nodes of that bin alone are held
+// against each other.  us under the tracer, eight sequences, every node held against every other / like this: 260 nodes 6.4 / 5.2, 1020 nodes
+// 21.6 / 8.4 (and 18.2 for 260 with four waves and three trips).
 __global__ __launch_bounds__(kMaxGrowNodes) void finalize_kernel(TreeFinalArgs a) {
-  constexpr int kWaves = kMaxGrowNodes / 64;
-  __shared__ __align__(16) float s_sc[kMaxGrowNodes];
-  __shared__ int s_rank[kMaxGrowNodes];
+  constexpr int kWaves = kMaxGrowNodes / 64, kBins = 2 * kMaxGrowNodes;
+  static_assert(kBins == 2048, "eleven bits");
+  __shared__ __align__(16) int s_bins[kBins];
+  __shared__ unsigned s_key[kMaxGrowNodes];  // of the nodes in the last bin, and who they are
+  __shared__ short s_who[kMaxGrowNodes];
   __shared__ short s_new[kMaxGrowNodes];
-  __shared__ int s_cnt[kWaves];
-  const int b = blockIdx.x, t = threadIdx.x;
+  __shared__ int s_cnt[kWaves], s_above[kWaves];
+  __shared__ int s_bin, s_need, s_members;
+  const int b = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const long long at = (long long)b * a.max_nodes + min(t, a.max_nodes - 1);
+  const int n_raw = a.n_nodes[b];
   const float sc = a.score[at];
   const int pid = a.parent[at], tok = a.tokens[at], q_row = a.q_row[at];
-  const int n = min(max(a.n_nodes[b], 0), a.max_nodes);
-  s_sc[t] = t < n ? sc : -INFINITY;
-  s_rank[t] = 0;
+  *reinterpret_cast<int2*>(s_bins + 2 * t) = make_int2(0, 0);
+  if (t == 0) {
+    s_bin = -1;  // (as many nodes as are wanted, or fewer: all of them)
+    s_need = 0;
+    s_members = 0;
+  }
   __syncthreads();
-  count_beaten<kWaves>(s_sc, n, s_rank, t);
+  const int n = min(max(n_raw, 0), a.max_nodes);
+  const bool real = t < n, ranked = real && sc == sc;  // (a NaN is beaten by nobody and beats nobody)
+  const unsigned key = score_key(sc);
+  const int bin = (int)(key >> 21);
+  if (ranked) atomicAdd(&s_bins[bin], 1);
   __syncthreads();
+  {  // a thread has two bins, the highest first: the nodes in front of its own
+    const int2 mine = *reinterpret_cast<const int2*>(s_bins + kBins - 2 - 2 * t);
+    const int sum = mine.x + mine.y, upto = dev::wave_scan(sum);
+    if (lane == 63) s_above[wave] = upto;
+    __syncthreads();
+    int before = upto - sum;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) before += w < wave ? s_above[w] : 0;
+    if (before < a.n_keep && before + mine.y >= a.n_keep) {
+      s_bin = kBins - 1 - 2 * t;
+      s_need = a.n_keep - before;
+    }
+    before += mine.y;
+    if (before < a.n_keep && before + mine.x >= a.n_keep) {
+      s_bin = kBins - 2 - 2 * t;
+      s_need = a.n_keep - before;
+    }
+  }
+  __syncthreads();
+  const int last = s_bin, need = s_need;
+  bool kept = real && (!ranked || bin > last);
+  const bool member = ranked && bin == last;
+  if (member) {
+    const int i = atomicAdd(&s_members, 1);
+    s_key[i] = key;
+    s_who[i] = (short)t;
+  }
+  __syncthreads();
+  if (member) {
+    const int members = s_members;
+    int rank = 0;
+#pragma unroll 4
+    for (int i = 0; i < members; ++i) {
+      const unsigned other = s_key[i];
+      rank += (int)(other > key) | ((int)(other == key) & (int)(s_who[i] < t));
+    }
+    kept = rank < need;
+  }
   int total;
-  const bool kept = t < n && s_rank[t] < a.n_keep;
   const int place = count_before<kWaves>(kept, t, s_cnt, total);
   s_new[t] = (short)place;
   __syncthreads();
@@ -290,7 +361,11 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const float* __restric
 int tree_max_nodes() { return kMaxGrowNodes; }
 
 hipError_t launch_tree_grow(const TreeGrowArgs& a, hipStream_t stream) {
-  hipLaunchKernelGGL(grow_kernel, dim3(a.batch), dim3(kTreeThreads), 0, stream, a);
+  // Four waves for each 64 candidates (the state's stores and loads take 256 threads whatever their number)
+  const int chunks = (a.n_front * 2 * a.top_k + 63) / 64;
+  if (chunks <= 1) hipLaunchKernelGGL(grow_kernel<4>, dim3(a.batch), dim3(256), 0, stream, a);
+  else if (chunks == 2) hipLaunchKernelGGL(grow_kernel<8>, dim3(a.batch), dim3(512), 0, stream, a);
+  else hipLaunchKernelGGL(grow_kernel<16>, dim3(a.batch), dim3(1024), 0, stream, a);
   return hipGetLastError();
 }
 hipError_t launch_tree_grow_tail(const TreeGrowArgs& a, int k1, int k2, hipStream_t stream) {

@@ -240,6 +240,7 @@ struct TreeGrowArgs {
   const int32_t* cand_tok;     // [batch*n_front][2][top_k]
   const float* cand_p;
   int32_t* frontier_out;       // [batch][width]
+  unsigned mg_top_k = 0;       // 2^16 / top_k + 1: c / top_k == (c * mg_top_k) >> 16 for c and top_k up to 256
 };
 struct TreeFinalArgs {
   int batch, n_keep, max_nodes;

@@ -49,6 +49,16 @@ __device__ __forceinline__ double wave_sum(double v) {
   v += swap64(v, true);
   return v;
 }
+// Inclusive sums over the lanes: rows of 16 by shifts, then the rows' totals broadcast into the rows behind them
+__device__ __forceinline__ int wave_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+  return v;
+}
 __device__ __forceinline__ float wave_max(float v) {
   v = fmaxf(v, __int_as_float(dpp<0xB1>(__float_as_int(v))));
   v = fmaxf(v, __int_as_float(dpp<0x4E>(__float_as_int(v))));

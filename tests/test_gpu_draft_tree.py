@@ -78,6 +78,40 @@ def test_equal_scores_and_capacity():
     _run_round(9, 1, 2, 2, 3, 64, 30)        # fewer nodes than asked for: the rest of the output says so
 
 
+@pytest.mark.parametrize("k,width", [(4, 8), (11, 3), (8, 8), (13, 5), (16, 8), (1, 128), (128, 1)])
+def test_growth_at_the_edges_of_its_wave_counts(k, width):
+    """64, 66, 128, 130 and 256 candidates a sequence: 4, 8 and 16 waves."""
+    _run_round(50 + k, 2, 3, k, width, 1024, 40)
+    _run_round(60 + k, 2, 3, k, width, 1024, 40, ties=True)
+
+
+@pytest.mark.parametrize("n,n_keep", [(1, 1), (1, 5), (63, 20), (64, 64), (65, 64), (300, 1), (300, 299), (1000, 60), (1023, 128), (1024, 1024),
+                                      (1024, 1023), (1024, 7)])
+@pytest.mark.parametrize("scores", ["spread", "one bin", "ties", "equal", "zeros and signs", "extreme"])
+def test_cut_by_bins_of_scores(n, n_keep, scores):
+    """Nodes without parents and with any scores: the same as ranking all of them (greater first, then by index; nothing beats
+    a NaN, which beats nothing)."""
+    rng = np.random.default_rng(n * 31 + n_keep)
+    sc = {"spread": lambda: np.exp(-12 * rng.random((2, n))), "one bin": lambda: 0.5 + rng.random((2, n)) * 0.1,
+          "ties": lambda: rng.integers(1, 9, (2, n)) / 8, "equal": lambda: np.full((2, n), 0.25),
+          "zeros and signs": lambda: rng.choice([0.0, -0.0, 1e-45, -1e-45, -0.5, 0.5], (2, n)),
+          "extreme": lambda: rng.choice([np.inf, -np.inf, np.nan, 3e38, 1e-38, 1.0], (2, n))}[scores]().astype(np.float32)
+    st = jk.TreeState(2, 1024)
+    st.score.fill_(float("nan"))  # (behind the nodes: not looked at)
+    st.score[:, :n] = torch.from_numpy(sc).cuda()
+    st.tokens[:, :n] = torch.arange(n, dtype=torch.int32, device="cuda") + 7
+    st.n_nodes.fill_(n)
+    tokens, parent, q_row, old, n_valid = jk.tree_finalize(st, n_keep)
+    for b in range(2):
+        beats = (sc[b][None, :] > sc[b][:, None]) | ((sc[b][None, :] == sc[b][:, None]) & (np.arange(n)[None, :] < np.arange(n)[:, None]))
+        kept = np.nonzero(beats.sum(1) < n_keep)[0][:n_keep].tolist()
+        nv = min(n, n_keep)
+        assert int(n_valid[b]) == nv and len(kept) == nv
+        assert old[b, :nv].cpu().tolist() == kept
+        assert tokens[b, :nv].cpu().tolist() == [i + 7 for i in kept]
+        assert (parent[b] == -1).all() and (tokens[b, nv:] == -1).all()
+
+
 def test_gather_draft_probs():
     rng = np.random.default_rng(1)
     q_all = rng.random((37, 1003)).astype(np.float32)
