@@ -124,12 +124,12 @@ struct PlanModel {
   double wide_margin = 1.02;    // (near ties go to the others)
   // 16 rows per workgroup and K, V in registers (tva_direct.hip): us of a call outside its blocks, per turn of four blocks of 32
   // keys, per workgroup of a CU beyond the first, for trees of more than 64 nodes (their ancestors); bytes per us that a CU
-  // draws of K and V, and all CUs together.  Fitted to 371 timed calls of drawn shapes of up to 900 keys of prefix (5.4 % rms).
-  // The others' estimates of such short calls are 1.2 times what they take (2x2 waves, geometric mean): direct_level puts
-  // this one beside them.  (At 1.25 the 400 shapes take 0.856 of what they took without this kernel, the best choice would take
-  // 0.854; at 1.0 0.866, and some 1.28 of it.)
-  double direct_call = 3.78, direct_call_d64 = 3.59, direct_round = 0.90, direct_round_d64 = 0.75, direct_next = 0.78,
-         direct_deep_tree = 0.50, direct_draw = 6.73e4, direct_stream = 3.93e7, direct_level = 1.25;
+  // draws of K and V, and all CUs together.  Fitted to the times of 320 drawn calls of up to 1300 keys of prefix and 2000
+  // workgroups (5.0 % rms).  The others' estimates of such short calls are 1.2 times what they take (2x2 waves, geometric mean):
+  // direct_level puts this one beside them.  (At 1.3 the 320 calls take 0.840 of what they take without this kernel, the best choice
+  // would take 0.834, and three are slower than without it by more than 3 %, 7 % at most; at 1.2 ten are, at 1.4 they take 0.849.)
+  double direct_call = 3.31, direct_call_d64 = 2.97, direct_round = 0.66, direct_round_d64 = 0.63, direct_next = 0.81,
+         direct_deep_tree = 0.65, direct_draw = 6.05e4, direct_stream = 3.40e7, direct_level = 1.3;
 };
 
 namespace {
@@ -212,6 +212,7 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
       if (wm == 8 && !forced_ok && (pl->m_rows <= 96 || tn.attn_fused == 0)) continue;  // (mostly padding rows; it has no second launch)
       if (forced_ok ? (wm != forced_wm || wn != forced_wn) : (wm > 2 && pl->m_rows <= 16 * wm)) continue;  // mostly padding rows
       const bool direct = wm == 1;
+      if (direct && !forced_ok && tn.attn_fused >= 0) continue;  // (a forced merge asks for a kernel that has one)
       const int q_rows = direct ? 16 : 32 * wm;
       const int n_qtiles = (pl->m_rows + q_rows - 1) / q_rows;
       const long long wgs = units * n_qtiles;
@@ -227,9 +228,9 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
         if (s < s_min) s = s_min;
         if (s > kMaxSplits) continue;
         if (direct && s > 1) break;
-        // (with more workgroups than CUs K and V are drawn again and again: 0.58 - 0.97 of the others' time up to seven tiles
-        // of keys, 0.94 - 1.13 beyond; nor is the estimate known to hold beyond the keys it was fitted to)
-        if (direct && !forced_ok && (n_tiles > 28 || (wgs > slots && n_tiles > 7))) break;
+        // (beyond that the splits of the others are the better one in most calls, 1.15 - 1.7 times, and the estimate too coarse to
+        // tell the rest)
+        if (direct && !forced_ok && n_tiles > 28) break;
         if (s > 1 && forced_s < 1 && (size_t)(wgs * s * q_rows) > most_rows) continue;  // (one split always fits)
         if (wm == 8 && s > 1 && (wgs * s > kMaxWideMerged || (size_t)wgs * s * q_rows * d.head_dim * sizeof(float) > kFineBytes)) continue;
         // rounds of the longest split: the 4x1 arrangement deals tiles (an odd last tile costs about

@@ -71,7 +71,7 @@ constexpr unsigned kDevErrBadTree = 1u, kDevErrBadToken = 2u, kDevErrBadPage = 4
 // variables when the library is loaded).  0 / -1 mean "let the library decide".
 struct Tuning {
   int attn_wm = 0, attn_wn = 0, attn_splits = 0;
-  int attn_fused = -1;     // -1 automatic, 0 never (nor the kernel that cannot do without, tva_wide.hip), 1 whenever the grid allows it
+  int attn_fused = -1;     // -1 automatic, 0 never (nor the kernel that cannot do without, tva_wide.hip), 1 whenever the grid allows it; either: a kernel that has one
   int attn_deep = -1;      // six-tile K/V ring of the 2x2 arrangement: -1 automatic, 0 never, 1 whenever one workgroup per CU is planned
   int accept_single = 0;   // 1: one-workgroup sampling walk
   int spin_limit = -1;     // polls of the bounded waits (-1: default)

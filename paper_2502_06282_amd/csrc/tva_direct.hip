@@ -1,22 +1,24 @@
 // Tree-masked verification attention, bf16, for calls of few keys (gfx950): K and V straight into registers.
 //
 // Same definition as tva_bf16.hip.  What bounds a call of a few hundred keys is no rate but a launch, the trips to memory one
-// behind the other and the instructions of lone waves between them.  So there is one trip: a wave asks for its page ids, the
-// length, its query rows and the K and V of its first block together, on the assumption that the length is the host's bound;
-// and there is little to execute: 16 rows a workgroup, no LDS ring, no barrier before the waves' results meet, an undivided key
-// range and no second launch.  S^T = K Q^T on v_mfma_f32_16x16x32_bf16 leaves a lane with eight keys of one row, which is what
-// O^T = V^T P^T takes as its operand, so the weights stay in their registers.  A lane fetches 16 bytes of each of those eight
-// keys of V (whole rows across 16 lanes), and v_perm_b32 puts two keys of a column side by side: 32 of them a block, in place
-// of a transposed copy in LDS.
+// behind the other and the instructions of lone waves between them (8 cycles each where one waits for the other).  So there is
+// one trip: a wave asks for its page ids, the length, its query rows and the K and V of its first block together, on the
+// assumption that the length is the host's bound; a tree's blocks come first, so that a shorter length changes nothing of that.
+// None of it is asked for in a branch, and all of it by loads that count as nothing else: behind a branch, and with flat loads,
+// the compiler waited for K and V where it waited for the length (0.5 - 0.8 us of every call).  And there is little to execute:
+// 16 rows a workgroup, no LDS ring, no barrier before the waves' results meet, an undivided key range and no second launch.
+// S^T = K Q^T on v_mfma_f32_16x16x32_bf16 leaves a lane with eight keys of one row, which is what O^T = V^T P^T takes as its
+// operand, so the weights stay in their registers.  A lane fetches 16 bytes of each of those eight keys of V (whole rows across 16
+// lanes), and v_perm_b32 puts two keys of a column side by side: 32 of them a block, in place of a transposed copy in LDS.
 //
-// Every row tile draws K and V through its CU (some 67 bytes per ns), so with many keys or rows the kernels that share them
+// Every row tile draws K and V through its CU (some 60 bytes per ns), so with many keys or rows the kernels that share them
 // through LDS are faster: the line between them is the plan's estimate (PlanModel in api.cpp).  Measured, us, the other kernels
-// / this one: one sequence, 14 nodes, 32 heads, 36 keys 7.4 / 4.8; 19 sequences, 9 nodes, 16 heads on 2, 36 keys 7.6 / 5.2;
-// 8 sequences, 11 nodes, 32 heads on 8, 202 keys 9.0 / 6.0; 2 sequences, 32 nodes, 64 heads on 8, 289 keys 10.0 / 6.9; 400 drawn
-// calls of up to 900 keys 0.856 in the geometric mean.  Error against fp64 1.9 - 2.3e-3 of the norm (the others 1.9 - 2.9e-3).
-// With 32 rows a workgroup every call took 1.5 - 2 us more (twice the instructions at its start and end); with eight waves
-// calls of few keys took the same and those of many workgroups up to half as long again; splits of the keys over workgroups,
-// merged by the last to come, paid for themselves in 3 of 60 calls.
+// / this one with flat loads and branches / like this: one sequence, 14 nodes, 32 heads, 36 keys 6.3 / 4.8 / 4.1; 19 sequences, 9
+// nodes, 16 heads on 2, 36 keys 6.8 / 5.2 / 4.1; 8 sequences, 11 nodes, 32 heads on 8, 202 keys 9.0 / 6.0 / 5.7; 2 sequences, 32
+// nodes, 64 heads on 8, 289 keys 10.1 / 6.9 / 6.7; 320 drawn calls of 80 - 1300 keys 1 / 0.85 / 0.84 in the geometric mean.
+// Error against fp64 2.0 - 2.2e-3 of the norm (the others 1.9 - 2.9e-3).  With 32 rows a workgroup every call took 1.5 - 2 us more
+// (twice the instructions at its start and end); with eight waves calls of few workgroups took 0 - 0.9 us more and those of many up
+// to half as long again; splits of the keys over workgroups, merged by the last to come, paid for themselves in 3 of 60 calls.
 #include "jk_ancestors.h"
 #include "jk_wave.h"
 #include "tva_tiles.h"
@@ -34,6 +36,15 @@ template <>
 struct VRow<64> {
   typedef u32x2 type;
 };
+
+// Addresses that are known to be in device memory: made from a pointer in scalar registers, a load is otherwise a flat one, which
+// counts as an access to LDS as well and takes its 64-bit address from two vector registers
+typedef __attribute__((address_space(1))) const unsigned char device_bytes;
+__device__ __forceinline__ device_bytes* in_device(const uint16_t* p) { return (device_bytes*)(unsigned long long)uniform_ptr(p); }
+template <class T>
+__device__ __forceinline__ T load_at(device_bytes* base, unsigned off) {
+  return *(__attribute__((address_space(1))) const T*)(base + off);
+}
 
 // 16 query rows of one (sequence, KV head) a workgroup; its waves take blocks of 32 keys in turn
 constexpr int kRows = 16, kWaves = 4;
@@ -67,26 +78,31 @@ __global__ __launch_bounds__(64 * kWaves, 2) void tva_direct_kernel(const KParam
   asm volatile("" : "+v"(lane_zero));  // (a vector load: a scalar one would be waited for with the arguments)
   const int L_raw = __hip_atomic_load(p.prefix_len + b + lane_zero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
-  // ---- this wave's blocks of 32 keys: wave + 4 i, the prefix's in front of the tree's
+  // ---- this wave's blocks of 32 keys: wave + kWaves * i, the tree's in front of the prefix's, so that what a wave asks for
+  // first does not depend on the length
   const int n_tblk = (T + kTileKeys - 1) / kTileKeys;
   int L = p.max_prefix, n_pblk = (L + kTileKeys - 1) / kTileKeys;
+  const bool some = wave < n_tblk + n_pblk;  // (the length's bound)
+  // What is asked for here is asked for without a branch: the compiler waits for everything behind a load that it may have passed
+  // by.  A wave without keys asks for one address in all lanes.
+  const int tc = some ? c : 0, tg = some ? g : 0;
+  const int pa_lo = p.parent[(long long)b * T + min(lane, T - 1)], pa_hi = p.parent[(long long)b * T + min(lane + 64, T - 1)];
   // page ids of 64 blocks of this wave, a lane each; ids outside the pool are clamped (and reported where they count)
   int ids = 0;
   auto ask_pages = [&](int first) {
-    const int blk = first + kWaves * lane, at = div_mg(blk, p.mg_tpp);
-    ids = blk < n_pblk && at < p.max_blocks ? p.block_table[(long long)b * p.max_blocks + at] : 0;
+    const int at = div_mg(max(first + kWaves * lane - n_tblk, 0), p.mg_tpp);
+    ids = p.block_table[(long long)b * p.max_blocks + min(at, p.max_blocks - 1)];
   };
   if (PAGED) ask_pages(wave);
 
   const int m = min(row0 + c, M - 1), node = div_mg(m, p.mg_g);  // this lane's query row (rows past the end repeat the last one)
   bf16x8 q[DJ];
-  if (wave < n_pblk + n_tblk) {  // (the rows of a wave without keys would only stand in the others' way)
-    const uint16_t* src = p.q + b * p.q_sb + node * p.q_st + (long long)(kv * G + (m - node * G)) * p.q_sh + 8 * g;
+  {
+    const int tm = some ? m : row0, tn = some ? node : div_mg(row0, p.mg_g);
+    const uint16_t* src = p.q + b * p.q_sb + tn * p.q_st + (long long)(kv * G + (tm - tn * G)) * p.q_sh + 8 * tg;
 #pragma unroll
     for (int j = 0; j < DJ; ++j) q[j] = *reinterpret_cast<const bf16x8*>(src + 32 * j);
   }
-  const int pa0 = lane < T ? p.parent[(long long)b * T + lane] : -1;
-  const int pa1 = lane + 64 < T ? p.parent[(long long)b * T + lane + 64] : -1;
 
   bf16x8 k[2][DJ];
   v_row v[8];
@@ -104,66 +120,58 @@ __global__ __launch_bounds__(64 * kWaves, 2) void tva_direct_kernel(const KParam
   };
   auto block_at = [&](int blk) {
     Block x;
-    x.tree = blk >= n_pblk;
+    x.tree = blk < n_tblk;
     if (x.tree) {
-      x.at = (long long)(blk - n_pblk) * kTileKeys * p.kt_st;
+      x.at = (long long)blk * kTileKeys * p.kt_st;
       x.stride8 = (int)(p.kt_st >> 3);
-      x.last = min(kTileKeys, T - (blk - n_pblk) * kTileKeys) - 1;
+      x.last = min(kTileKeys, T - blk * kTileKeys) - 1;
     } else {
+      const int pb = blk - n_tblk;
       x.stride8 = (int)(p.kc_sl >> 3);
-      x.last = min(kTileKeys, L - blk * kTileKeys) - 1;
+      x.last = min(kTileKeys, L - pb * kTileKeys) - 1;
       if (PAGED) {
         const int id = __builtin_amdgcn_readlane(ids, (blk / kWaves) & 63), page = id < 0 ? 0 : (id >= p.n_pages ? p.n_pages - 1 : id);
-        const int slot = blk - div_mg(blk, p.mg_tpp) * p.tpp;
+        const int slot = pb - div_mg(pb, p.mg_tpp) * p.tpp;
         x.at = (long long)page * p.page_stride + (long long)slot * kTileKeys * p.kc_sl;
       } else {
-        x.at = (long long)blk * kTileKeys * p.kc_sl;
+        x.at = (long long)pb * kTileKeys * p.kc_sl;
       }
     }
     return x;
   };
   auto off16 = [&](const Block& x, int row) { return __umul24((unsigned)min(row, x.last), (unsigned)x.stride8) << 4; };
-  auto load_k = [&](const Block& x) {
-    const unsigned char* base = reinterpret_cast<const unsigned char*>(uniform_ptr((x.tree ? kt : kc) + x.at));
+  auto load_k = [&](const Block& x, int c, int g) {
+    device_bytes* base = in_device((x.tree ? kt : kc) + x.at);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const unsigned off = off16(x, 16 * h + c) + 16u * g;
 #pragma unroll
-      for (int j = 0; j < DJ; ++j) k[h][j] = *reinterpret_cast<const bf16x8*>(base + off + 64 * j);
+      for (int j = 0; j < DJ; ++j) k[h][j] = load_at<bf16x8>(base, off + 64 * j);
     }
   };
-  auto load_v = [&](const Block& x) {
-    const unsigned char* base = reinterpret_cast<const unsigned char*>(uniform_ptr((x.tree ? vt : vc) + x.at));
+  auto load_v = [&](const Block& x, int c, int g) {
+    device_bytes* base = in_device((x.tree ? vt : vc) + x.at);
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      v[i] = *reinterpret_cast<const v_row*>(base + off16(x, (i & 4) * 4 + 4 * g + (i & 3)) + (unsigned)(sizeof(v_row) * c));
+    for (int i = 0; i < 8; ++i) v[i] = load_at<v_row>(base, off16(x, (i & 4) * 4 + 4 * g + (i & 3)) + (unsigned)(sizeof(v_row) * c));
   };
 
   // ---- the first block on the assumption that the length is the host's bound
-  Block cur;
-  if (wave < n_pblk + n_tblk) {
-    cur = block_at(wave);
-    load_k(cur);
-    load_v(cur);
-  }
+  Block cur = block_at(some ? wave : 0);
+  if (!some) cur.stride8 = 0;
+  load_k(cur, tc, tg);
+  load_v(cur, tc, tg);
   {
     const int len = __builtin_amdgcn_readfirstlane(L_raw);
     L = len < 0 ? 0 : (len > p.max_prefix ? p.max_prefix : len);
   }
-  if (L != p.max_prefix) {  // (uniform)
-    n_pblk = (L + kTileKeys - 1) / kTileKeys;
-    if (wave < n_pblk + n_tblk && (wave + 1) * kTileKeys > L) {  // (never more blocks than assumed: its query rows are there)
-      cur = block_at(wave);
-      load_k(cur);
-      load_v(cur);
-    }
-  }
+  n_pblk = (L + kTileKeys - 1) / kTileKeys;
+  if (!cur.tree) cur.last = min(kTileKeys, L - (wave - n_tblk) * kTileKeys) - 1;  // (below zero: no block any more)
   const int end = n_pblk + n_tblk;
 
   dev::Ancestors seen{0ull, 0ull};
   const bool reports = row0 == 0 && kv == 0 && wave == 0;
-  if (reports || (wave < end && wave + (end - 1 - wave) / kWaves * kWaves >= n_pblk))  // the wave has a block of the tree
-    seen = dev::ancestors_of(T, p.err, pa0, pa1, node, reports);
+  if (reports || wave < n_tblk)  // the wave has a block of the tree
+    seen = dev::ancestors_of(T, p.err, lane < T ? pa_lo : -1, lane + 64 < T ? pa_hi : -1, node, reports);
 
   floatx4 o[E];
 #pragma unroll
@@ -185,19 +193,22 @@ __global__ __launch_bounds__(64 * kWaves, 2) void tva_direct_kernel(const KParam
     if (more) {
       if (PAGED && ((blk / kWaves + 1) & 63) == 0) ask_pages(blk + kWaves);
       cur = block_at(blk + kWaves);
-      load_k(cur);
+      load_k(cur, c, g);
     }
     if (now.tree || now.last < kTileKeys - 1) {  // (uniform) which of its keys the row sees: bits 4 g + r and 16 + 4 g + r
       unsigned bits = (2u << now.last) - 1u;
       if (now.tree) {
-        const int t = blk - n_pblk;
-        bits = (unsigned)((t & 2 ? seen.hi : seen.lo) >> (32 * (t & 1)));
+        bits = (unsigned)((blk & 2 ? seen.hi : seen.lo) >> (32 * (blk & 1)));
       }
       bits >>= 4 * g;
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
         for (int r = 0; r < 4; ++r) s[h][r] = (bits >> (16 * h + r)) & 1u ? s[h][r] : -INFINITY;
+      if (!now.tree) {  // (asked for beyond the prefix's end: what is there may be no number)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = (i & 4) * 4 + 4 * g + (i & 3) <= now.last ? v[i] : v_row{};
+      }
     }
     float top = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])), fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
     top = fmaxf(top, __uint_as_float(dev::other16(__float_as_uint(top), lane & 16)));
@@ -237,7 +248,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void tva_direct_kernel(const KParam
       for (int i = 0; i < 4; ++i) a[i] = __builtin_amdgcn_perm(v[2 * i + 1][e / 2], v[2 * i][e / 2], e & 1 ? 0x07060302u : 0x05040100u);
       o[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), w, o[e], 0, 0, 0);
     }
-    if (more) load_v(cur);
+    if (more) load_v(cur, c, g);
   }
   if (PAGED && bad_page && lane == 0) __hip_atomic_fetch_or(p.err, kDevErrBadPage, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
