@@ -31,11 +31,14 @@
 // Reductions across a wave are DPP moves (a shuffle through LDS takes several times as long), one wave polls and reduces for
 // the workgroup.  Measured (MI355X, us per call, the mean of six draws, before the last three of these and now; a draw takes
 // 12 to 28, by its number of exchanges): one 60-node tree over a 128K vocabulary 17.6 / 15.8, eight 100-node trees over 32K
-// 22.5 / 20.5, one tree over 32K 12.5 / 11.3, sixteen 27.0 / 25.1.  Tried on top of it and slower: both possible next candidates
-// asked for before the outcome is known, with a wave of its own that polls (a wave's loads complete in order, so one that has
-// asked for a slice polls behind it): the CU's address unit takes as long for their loads as the walk then waits less (16.5
-// against 14.6); a tree's workgroups on one XCD, exchanges through its L2: one XCD's share of the memory bandwidth is too
-// little for large vocabularies (one tree over 128K 25 - 31).
+// 22.5 / 20.5, one tree over 32K 12.5 / 11.3, sixteen 27.0 / 25.1.
+// What a walk starts from - words, table, the first two rows - in one trip to memory instead of three or four: 24 drawn
+// calls 1.021 times as fast (0.3 - 6 %).  The first draft slice in that trip as well, and the table made beside the first
+// exchange: 2 - 3 % faster with a table of rows, as much slower without.  Tried on top of it and slower: both possible next
+// candidates asked for before the outcome is known, with a wave of its own that polls (a wave's loads complete in order, so
+// one that has asked for a slice polls behind it): the CU's address unit takes as long for their loads as the walk then
+// waits less (16.5 against 14.6); a tree's workgroups on one XCD, exchanges through its L2: one XCD's share of the memory
+// bandwidth is too little for large vocabularies (one tree over 128K 25 - 31).
 //
 // Waiting is bounded: if a partner never shows up (the W workgroups of a tree are not all
 // resident) the walk gives up and reports accept_len = -1 instead of hanging; the last workgroup
@@ -182,6 +185,7 @@ struct Walk {
   TreeWords* tw;
   unsigned long long epoch;
   float uni_last;
+  int lane_zero = 0;
   unsigned n_exch = 0, tag = 0;
   Table* tab = nullptr;
 
@@ -189,14 +193,24 @@ struct Walk {
       : p(params), table(nodes), tid(threadIdx.x), lane(tid & 63), wave(__builtin_amdgcn_readfirstlane(tid >> 6)), W(p.W),
         b(blockIdx.x / p.W), w(blockIdx.x % p.W), N(p.n_tree), V(p.vocab), tw(&p.trees[b].words) {}
   __device__ __forceinline__ const float* row_of(int r) const { return p.logits + ((long long)b * (N + 1) + r) * V; }
+  // What a walk starts from is asked for in one trip to memory: a value that the compiler knows to be the same in all lanes it
+  // moves to a scalar register at once, and waits for everything asked for before it.  So these are different ones, to it,
+  // until settle().
   __device__ __forceinline__ void load_words() {
-    epoch = __hip_atomic_load(&tw->epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    uni_last = p.uniforms[(long long)b * (N + 1) + N];
+    asm volatile("" : "=v"(lane_zero) : "0"(0));
+    epoch = __hip_atomic_load(&tw->epoch + lane_zero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uni_last = p.uniforms[(long long)b * (N + 1) + N + lane_zero];
+  }
+  __device__ __forceinline__ void settle() {
+    const unsigned lo = __builtin_amdgcn_readfirstlane((int)(unsigned)epoch), hi = __builtin_amdgcn_readfirstlane((int)(epoch >> 32));
+    epoch = (unsigned long long)hi << 32 | lo;
+    uni_last = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(uni_last)));
   }
   // by one wave, in front of a barrier
   __device__ __forceinline__ void make_table() {
     int par[2], tok[2], uni[2];
     long long draft[2];
+    const int* rows = p.draft_row ? p.draft_row : p.parent;  // (asked for without a branch, see load_words)
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int k = min(lane + 64 * h, N - 1);
@@ -204,7 +218,7 @@ struct Walk {
       par[h] = p.parent[at];
       tok[h] = p.tokens[at];
       uni[h] = __float_as_int(p.uniforms[at + b]);
-      draft[h] = p.draft_row ? p.draft_row[at] : at;
+      draft[h] = rows[at];
     }
     for (int i = lane; i <= N; i += 64) *reinterpret_cast<uint4*>(table.kids[i]) = make_uint4(0u, 0u, 0u, 0u);
     auto in_order = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };  // (LDS operations of a wave complete in order)
@@ -215,6 +229,7 @@ struct Walk {
       par[h] = (pa >= -1 && pa < k) ? pa : -1;
       tok[h] = min(max(tk, 0), V - 1);  // a token id outside the vocabulary must not fault
       if (p.draft_row) draft[h] = draft[h] < 0 ? 0 : (draft[h] >= p.n_draft_rows ? p.n_draft_rows - 1 : draft[h]);  // nor a bad row
+      else draft[h] = (long long)b * N + k;
       if (k >= N) continue;
       if (w == 0) {  // both repairs are recorded in the workspace's error word
         if (par[h] != pa) __hip_atomic_fetch_or(p.err, kDevErrBadTree, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -459,7 +474,7 @@ struct Walk {
     __hip_atomic_store(&tw->epoch, epoch + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return all >> 16 != 0u;
   }
-  __device__ __forceinline__ unsigned finished() const { return __hip_atomic_load(&tw->finish, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+  __device__ __forceinline__ unsigned finished() const { return __hip_atomic_load(&tw->finish + lane_zero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 };
 
 template <int PER, int THREADS>
@@ -480,12 +495,6 @@ __global__ __launch_bounds__(THREADS, 2) void walk_sample_coop_kernel(CoopParams
   const int tid = wk.tid, lane = wk.lane, wave = wk.wave, W = wk.W;
   const Walk::Part<PER> mine(wk.w * SLICE + tid * PER, wk.V);
 
-  float lg[PER];
-  mine.load(lg, wk.row_of(0));  // (the first row is on its way before anything else is known)
-  wk.load_words();
-  if (wave == 0) wk.make_table();
-  __syncthreads();
-
   // A candidate and what will be needed of it: its draft slice and value at its token, the logits slice of its own row
   // (the one that counts if it is accepted) and that row's value at its first child's token.
   struct Candidate {
@@ -494,6 +503,21 @@ __global__ __launch_bounds__(THREADS, 2) void walk_sample_coop_kernel(CoopParams
     float q[PER], lg[PER];
     float qx, row_x;
   };
+  // (The root's first child is node 0, since a parent comes before its children: its own row is row 1.)
+  Candidate then;
+  float lg[PER];
+  mine.load(lg, wk.row_of(0));  // (the first rows are on their way before anything else is known)
+  mine.load(then.lg, wk.row_of(1));
+  wk.load_words();
+  if (wave == 0) wk.make_table();
+  wk.settle();
+  __syncthreads();
+  then.k = 0;
+  then.node = wk.node(0);
+  mine.load(then.q, p.draft + then.node.draft);
+  then.qx = p.draft[then.node.draft + then.node.tok];
+  then.row_x = wk.row_of(1)[then.node.tok_first];
+
   auto fetch = [&](Candidate& n, int k) {
     n.k = k;
     if (k < 0) return;
@@ -572,7 +596,7 @@ __global__ __launch_bounds__(THREADS, 2) void walk_sample_coop_kernel(CoopParams
     for (int u = 0; u < PER; ++u) cur[u] = ex.e[u] * sc;
   };
 
-  Candidate cand, then;  // `then`: fetched when the outcome names it, the next sibling or the first child
+  Candidate cand;  // (`then`: fetched when the outcome names it, the next sibling or the first child)
   Exponentials ahead;    // of cand's own row, where it is known
   Stats ahead_stats = {0.0, 0.f};
   bool row_known = false;  // `ahead` and the open exchange's words 4 - 6 are those of cand's own row
@@ -597,7 +621,6 @@ __global__ __launch_bounds__(THREADS, 2) void walk_sample_coop_kernel(CoopParams
   };
 
   int len = 0;
-  fetch(then, wk.first_of_root());
   exchange_row(lg, wk.row_of(0)[then.node.tok], then);
   while (alive && cand.k >= 0) {
     if ((double)__int_as_float(cand.node.uni) * (double)cand.qx < px) {
@@ -729,6 +752,7 @@ __global__ __launch_bounds__(kWideThreads) void walk_sample_wide_kernel(CoopPara
     wk.make_table();
     if (lane == 0) got_ok = before >> 16 == 0u;  // (where somebody of the tree has given up there is nothing to wait for)
   }
+  wk.settle();
   __syncthreads();
 
   double xs_mul = 1.0, px = 0.0;
