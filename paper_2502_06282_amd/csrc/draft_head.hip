@@ -14,6 +14,7 @@
 // The products with weight matrices run in stream_gemm.hip and ring_gemm.hip.
 
 #include <cmath>
+#include <type_traits>
 
 #include "jk_internal.h"
 #include "jk_wave.h"
@@ -112,12 +113,20 @@ __device__ __forceinline__ float key_value(unsigned long long k) {
   const unsigned u = (unsigned)(k >> 32);
   return __uint_as_float(u ^ ((u >> 31) ? 0x80000000u : 0xFFFFFFFFu));
 }
-__device__ __forceinline__ unsigned long long wave_max_key(unsigned long long k) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const unsigned long long other = __shfl_xor(k, o);
+__device__ __forceinline__ unsigned long long wave_max_key(unsigned long long k) {  // (see jk_wave.h)
+  auto most = [&](unsigned lo, unsigned hi) {
+    const unsigned long long other = (unsigned long long)hi << 32 | lo;
     k = other > k ? other : k;
-  }
+  };
+  auto lo = [&] { return (unsigned)k; };
+  auto hi = [&] { return (unsigned)(k >> 32); };
+  most((unsigned)dev::dpp<0xB1>((int)lo()), (unsigned)dev::dpp<0xB1>((int)hi()));    // quad_perm [1,0,3,2]
+  most((unsigned)dev::dpp<0x4E>((int)lo()), (unsigned)dev::dpp<0x4E>((int)hi()));    // quad_perm [2,3,0,1]
+  most((unsigned)dev::dpp<0x141>((int)lo()), (unsigned)dev::dpp<0x141>((int)hi()));  // row_half_mirror
+  most((unsigned)dev::dpp<0x140>((int)lo()), (unsigned)dev::dpp<0x140>((int)hi()));  // row_mirror
+  const int lane = __lane_id();
+  most(dev::other16(lo(), lane & 16), dev::other16(hi(), lane & 16));
+  most(dev::other32(lo(), lane & 32), dev::other32(hi(), lane & 32));
   return k;
 }
 
@@ -397,61 +406,64 @@ struct RouterParams {
 
 // One workgroup per row: the router scores s_j = softmax_j(u . e_j) (Eq. 2; fp32), of which it picks the two largest
 // (Eq. 5, K = 2, ties to the lower expert; a NaN score ranks below every other, so that the row always names two
-// different experts that exist - the experts' outputs are addressed with them).  Bound by a trip to memory: a wave asks for
+// different experts that exist - the experts' outputs are addressed with them).  Bound by a trip to memory: a wave asks for up to
 // 8 KB of the row and of two centroids together (left alone, the compiler asked for one 1 KB piece after the other: 40
 // rows of 4096, eight experts, 7.8 us, and 4.9 like this; of the whole call 153.6 and 151.0, of a small one - 64 rows of 1024,
 // four experts of 2048 - 29.0 and 29.4), and the softmax and both maxima are taken across the
-// lanes of a wave.
+// lanes of a wave, by lane moves.  (By shuffles, and with eight pieces whatever the row's length; and select_kernel with its
+// scores asked for, and waited for, in front of the results: 18 drawn calls of experts 1.036 times as long, small ones 1.04 - 1.09.)
 __global__ __launch_bounds__(256) void router_kernel(RouterParams p) {
   __shared__ float score[kMaxExperts];
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const u32x4* src = reinterpret_cast<const u32x4*>(p.u + (long long)row * p.d);
-  for (int j0 = wave; j0 < p.n_experts; j0 += 8) {  // two experts per pass: their loads share the trip to memory
-    const bool two = j0 + 4 < p.n_experts;
-    const u32x4* e0 = reinterpret_cast<const u32x4*>(p.centroids + (long long)j0 * p.d);
-    const u32x4* e1 = reinterpret_cast<const u32x4*>(p.centroids + (long long)(two ? j0 + 4 : j0) * p.d);
-    float acc0 = 0.f, acc1 = 0.f;
-    constexpr int PIECES = 8;
-    for (int c0 = 0; c0 < p.d / 8; c0 += 64 * PIECES) {
-      u32x4 a[PIECES], b0[PIECES], b1[PIECES];
+  // (as many pieces of 1 KB a time as a row has: 2, 4 or 8)
+  auto scores = [&](auto n_pieces) {
+    for (int j0 = wave; j0 < p.n_experts; j0 += 8) {  // two experts per pass: their loads share the trip to memory
+      const bool two = j0 + 4 < p.n_experts;
+      const u32x4* e0 = reinterpret_cast<const u32x4*>(p.centroids + (long long)j0 * p.d);
+      const u32x4* e1 = reinterpret_cast<const u32x4*>(p.centroids + (long long)(two ? j0 + 4 : j0) * p.d);
+      float acc0 = 0.f, acc1 = 0.f;
+      constexpr int PIECES = decltype(n_pieces)::value;
+      for (int c0 = 0; c0 < p.d / 8; c0 += 64 * PIECES) {
+        u32x4 a[PIECES], b0[PIECES], b1[PIECES];
 #pragma unroll
-      for (int u = 0; u < PIECES; ++u) {
-        const int c = min(c0 + 64 * u + lane, p.d / 8 - 1);
-        a[u] = src[c];
-        b0[u] = e0[c];
-        b1[u] = e1[c];
-      }
-      __builtin_amdgcn_sched_barrier(0);
+        for (int u = 0; u < PIECES; ++u) {
+          const int c = min(c0 + 64 * u + lane, p.d / 8 - 1);
+          a[u] = src[c];
+          b0[u] = e0[c];
+          b1[u] = e1[c];
+        }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int u = 0; u < PIECES; ++u) {
-        if (c0 + 64 * u + lane >= p.d / 8) break;
+        for (int u = 0; u < PIECES; ++u) {
+          if (c0 + 64 * u + lane >= p.d / 8) break;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          acc0 += bf16_lo(a[u][i]) * bf16_lo(b0[u][i]) + bf16_hi(a[u][i]) * bf16_hi(b0[u][i]);
-          acc1 += bf16_lo(a[u][i]) * bf16_lo(b1[u][i]) + bf16_hi(a[u][i]) * bf16_hi(b1[u][i]);
+          for (int i = 0; i < 4; ++i) {
+            acc0 += bf16_lo(a[u][i]) * bf16_lo(b0[u][i]) + bf16_hi(a[u][i]) * bf16_hi(b0[u][i]);
+            acc1 += bf16_lo(a[u][i]) * bf16_lo(b1[u][i]) + bf16_hi(a[u][i]) * bf16_hi(b1[u][i]);
+          }
         }
       }
+      acc0 = dev::wave_sum(acc0);
+      acc1 = dev::wave_sum(acc1);
+      if (lane == 0) {
+        score[j0] = acc0;
+        if (two) score[j0 + 4] = acc1;
+      }
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      acc0 += __shfl_xor(acc0, o);
-      acc1 += __shfl_xor(acc1, o);
-    }
-    if (lane == 0) {
-      score[j0] = acc0;
-      if (two) score[j0 + 4] = acc1;
-    }
-  }
+  };
+  if (p.d <= 1024) scores(std::integral_constant<int, 2>());
+  else if (p.d <= 2048) scores(std::integral_constant<int, 4>());
+  else scores(std::integral_constant<int, 8>());
   __syncthreads();
   if (wave != 0) return;
   // (at most 64 experts; a lane without one has key 0, which loses to every expert's key, a NaN's 0 above ~id included)
   const float mine = lane < p.n_experts ? score[lane] : -INFINITY;
   const unsigned long long key = lane >= p.n_experts ? 0ull : mine == mine ? key_of(mine, lane) : (unsigned long long)(unsigned)~lane;
   const int i1 = key_id(wave_max_key(key)), i2 = key_id(wave_max_key(lane == i1 ? 0ull : key));
-  const float v1 = __shfl(mine, i1), v2 = __shfl(mine, i2);
-  float z = lane < p.n_experts ? expf(mine - v1) : 0.f;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) z += __shfl_xor(z, o);
+  auto score_of = [&](int i) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mine), __builtin_amdgcn_readfirstlane(i))); };
+  const float v1 = score_of(i1), v2 = score_of(i2);
+  const float z = dev::wave_sum(lane < p.n_experts ? expf(mine - v1) : 0.f);
   if (lane == 0) {
     p.s_top[2 * row] = 1.f / z;
     p.s_top[2 * row + 1] = expf(v2 - v1) / z;
@@ -540,10 +552,17 @@ __global__ __launch_bounds__(256) void select_kernel(SelectParams p) {
   const int c = blockIdx.y * 256 + threadIdx.x;
   if (c >= p.d / 4) return;
   const uint2 uu = reinterpret_cast<const uint2*>(p.u + (long long)row * p.d)[c];
-  const float s1 = p.s_top[2 * row], s2 = p.s_top[2 * row + 1];
+  int lane_zero = 0;
+  asm volatile("" : "+v"(lane_zero));  // (a vector load: the scalar one's trip was waited for in front of the results')
+  const float s1 = p.s_top[2 * row + lane_zero], s2 = p.s_top[2 * row + 1 + lane_zero];
   const float* y = p.y + (long long)(2 * row) * p.d + 4 * c;
   floatx4 a, b;
-  sum_two(y, y + p.d, p.ksplit, p.split_stride, a, b);
+  if (p.ksplit == 1) {
+    a = *reinterpret_cast<const floatx4*>(y);
+    b = *reinterpret_cast<const floatx4*>(y + p.d);
+  } else {
+    sum_two(y, y + p.d, p.ksplit, p.split_stride, a, b);
+  }
   const floatx4 u = {bf16_lo(uu.x), bf16_hi(uu.x), bf16_lo(uu.y), bf16_hi(uu.y)};
   auto store = [&](uint16_t* dst, const floatx4& v) {
     uint2 w;

@@ -75,9 +75,14 @@ struct Weights {
   unsigned wg;
 
   __device__ __forceinline__ void start(const StreamGemmArgs& p, int n_base, int e, int wave, int r, int g) {
-    const int units = p.k / 128;
-    k0 = (int)((long long)blockIdx.z * units / p.ksplit) * 128;
-    k1 = (int)((long long)(blockIdx.z + 1) * units / p.ksplit) * 128;
+    // (64-bit divisions here were half of the 412 instructions in front of the first load: 2 - 4 % of a small call)
+    k0 = 0;
+    k1 = p.k;
+    if (p.ksplit > 1) {
+      const unsigned units = (unsigned)p.k / 128u, parts = (unsigned)p.ksplit;  // (at most 128 of each)
+      k0 = (int)(blockIdx.z * units / parts) * 128;
+      k1 = (int)((blockIdx.z + 1u) * units / parts) * 128;
+    }
     wg = blockIdx.x + gridDim.x * blockIdx.y;
     const uint16_t* base = (KIND == PAIR && wave >= 4 ? p.w2 : p.w) + (long long)e * p.w_batch;
 #pragma unroll
@@ -573,12 +578,12 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void narrow_gemm_kernel(Narr
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, g = lane >> 4;
   const int blk = blockIdx.x, id = xcd_place(blk, gridDim.x);  // (neighbours on one XCD share lines of Y)
   // (the blocks of X's rows are the grid's second dimension: what shares a strip's weights runs on one XCD, and in step)
-  const int strip = id / p.parts;
+  const int halves = p.parts - 1, strip = id >> halves;  // (one or two parts)
   if (strip >= p.strips) return;  // (the whole workgroup, see xcd_grid)
-  const int z = id - strip * p.parts, row0 = (int)blockIdx.y * p.rows, m = min(p.m - row0, p.rows);
+  const int z = id - (strip << halves), row0 = (int)blockIdx.y * p.rows, m = min(p.m - row0, p.rows);
   const int meet = strip + (int)blockIdx.y * p.strips;
   const int n_base = strip * p.strip, n_end = min(n_base + p.strip, p.n);
-  const int units = p.k / UK, u0 = (int)((long long)z * units / p.parts), u1 = (int)((long long)(z + 1) * units / p.parts);
+  const int units = (int)((unsigned)p.k / (unsigned)UK), u0 = (z * units) >> halves, u1 = ((z + 1) * units) >> halves;
   // (byte offsets from one scalar address each; rows past the end repeat the last one, and are not stored)
   const uint16_t *w0 = dev::uniform_ptr(p.w + (long long)n_base * p.k), *x0 = dev::uniform_ptr(p.x + (long long)row0 * p.k);
   const int lrow = lane / C::CHUNKS, lcol = 16 * (lane % C::CHUNKS ^ C::swizzle(lrow));
