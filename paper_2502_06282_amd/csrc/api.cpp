@@ -454,6 +454,26 @@ size_t moe_experts_call_bytes(const jk_moe_desc& d) {
   return moe_desc_ok(d) && moe_desc_supported(d) ? moe_experts_workspace_bytes(d.rows, d.d_model, d.d_ff, d.n_experts) : 0;
 }
 size_t linear_call_bytes(int m, int n, int k) { return linear_shape_ok(m, n, k) ? linear_workspace_bytes(m, n, k) : 0; }
+namespace {
+jk_status linear_refused(int32_t m, int32_t n, int32_t k, const void* x, const void* w, const void* out_bf16, const float* out_f32) {
+  if (!x || !w || (!out_bf16 && !out_f32) || m < 1 || n < 1 || k < 1) return JK_ERR_INVALID_ARG;
+  if (reinterpret_cast<uintptr_t>(x) % 16 || reinterpret_cast<uintptr_t>(w) % 16) return JK_ERR_INVALID_ARG;
+  return linear_shape_ok(m, n, k) ? JK_OK : JK_ERR_UNSUPPORTED;
+}
+jk_status linear_launched(int m, int n, int k, const void* x, const void* w, const void* residual, void* out_bf16, float* out_f32,
+                                 void* workspace, void* hip_stream) {
+  LinearArgs a;
+  a.m = m; a.n = n; a.k = k; a.x = x; a.w = w; a.residual = residual; a.out_f32 = out_f32; a.out_bf16 = out_bf16;
+  a.workspace = workspace;
+  return launch_linear(a, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? JK_OK : JK_ERR_HIP;
+}
+}  // namespace
+jk_status linear_call(int m, int n, int k, const void* x, const void* w, const void* residual, void* out_bf16, float* out_f32,
+                      void* workspace, void* hip_stream) {
+  if (jk_status s = linear_refused(m, n, k, x, w, out_bf16, out_f32); s != JK_OK) return s;
+  if (!workspace && linear_call_writes(m, n, k)) return JK_ERR_WORKSPACE;
+  return linear_launched(m, n, k, x, w, residual, out_bf16, out_f32, workspace, hip_stream);
+}
 
 }  // namespace jk
 
@@ -872,15 +892,10 @@ size_t jk_linear_workspace(int32_t m, int32_t n, int32_t k) {
 
 jk_status jk_linear(int32_t m, int32_t n, int32_t k, const void* x, const void* w, const void* residual,
                     void* out_bf16, float* out_f32, void* workspace, size_t workspace_bytes, void* hip_stream) {
-  if (!x || !w || (!out_bf16 && !out_f32) || m < 1 || n < 1 || k < 1) return JK_ERR_INVALID_ARG;
-  if (reinterpret_cast<uintptr_t>(x) % 16 || reinterpret_cast<uintptr_t>(w) % 16) return JK_ERR_INVALID_ARG;
-  if (!linear_shape_ok(m, n, k)) return JK_ERR_UNSUPPORTED;
+  if (jk_status s = linear_refused(m, n, k, x, w, out_bf16, out_f32); s != JK_OK) return s;
   if (!workspace || reinterpret_cast<uintptr_t>(workspace) % 256 || workspace_bytes < linear_workspace_bytes(m, n, k))
     return JK_ERR_WORKSPACE;
-  LinearArgs a;
-  a.m = m; a.n = n; a.k = k; a.x = x; a.w = w; a.residual = residual; a.out_f32 = out_f32; a.out_bf16 = out_bf16;
-  a.workspace = workspace;
-  return launch_linear(a, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? JK_OK : JK_ERR_HIP;
+  return linear_launched(m, n, k, x, w, residual, out_bf16, out_f32, workspace, hip_stream);
 }
 
 jk_status jk_workspace_init(void* workspace, size_t workspace_bytes, void* hip_stream) {

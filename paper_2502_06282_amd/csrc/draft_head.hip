@@ -810,9 +810,15 @@ LinearPlan linear_plan(int m, int n, int k) {
 }
 }  // namespace
 
+namespace {
+size_t linear_writes(const LinearPlan& p, int m, int n) {  // bytes
+  return p.narrow.parts > 0 ? narrow_gemm_bytes(p.narrow) : p.ksplit > 1 ? (size_t)p.ksplit * m * n * 4 : 0;
+}
+}  // namespace
+bool linear_call_writes(int m, int n, int k) { return linear_writes(linear_plan(m, n, k), m, n) > 0; }
+
 size_t linear_workspace_bytes(int m, int n, int k) {
-  const LinearPlan p = linear_plan(m, n, k);
-  const size_t need = p.narrow.parts > 0 ? narrow_gemm_bytes(p.narrow) : p.ksplit > 1 ? (size_t)p.ksplit * m * n * 4 : 0;
+  const size_t need = linear_writes(linear_plan(m, n, k), m, n);
   return need < 256 ? 256 : (need + 255) / 256 * 256;
 }
 

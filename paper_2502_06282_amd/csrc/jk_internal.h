@@ -271,6 +271,10 @@ size_t linear_workspace_bytes(int m, int n, int k);
 size_t draft_heads_call_bytes(int rows, int d_model, int vocab);
 size_t moe_experts_call_bytes(const jk_moe_desc& d);
 size_t linear_call_bytes(int m, int n, int k);
+bool linear_call_writes(int m, int n, int k);  // whether such a call uses its workspace
+// jk_linear with a workspace of linear_call_bytes, or none where the call uses none
+jk_status linear_call(int m, int n, int k, const void* x, const void* w, const void* residual, void* out_bf16, float* out_f32,
+                      void* workspace, void* hip_stream);
 hipError_t launch_linear(const LinearArgs& a, hipStream_t stream);
 
 }  // namespace jk

@@ -112,6 +112,18 @@ def test_cut_by_bins_of_scores(n, n_keep, scores):
         assert (parent[b] == -1).all() and (tokens[b, nv:] == -1).all()
 
 
+@pytest.mark.parametrize("n_keep", [1, 3, 64, 65])
+def test_cut_results_are_tensors_of_their_own(n_keep):
+    """They share an allocation: contiguous, apart from each other, beginning at multiples of 256 bytes."""
+    state = jk.TreeState(2, 256)
+    state.n_nodes.fill_(70)
+    out = jk.tree_finalize(state, n_keep)[:4]
+    for i, x in enumerate(out):
+        assert x.shape == (2, n_keep) and x.dtype == torch.int32 and x.is_contiguous() and x.data_ptr() % 256 == 0
+        x.fill_(i)
+    assert all((x == i).all() for i, x in enumerate(out))
+
+
 def test_gather_draft_probs():
     rng = np.random.default_rng(1)
     q_all = rng.random((37, 1003)).astype(np.float32)
