@@ -207,3 +207,26 @@ def test_commit_argument_errors():
         jk.commit_path(kt, vt, kc, vc.transpose(1, 2), path, one, one)        # K and V strides differ
     with pytest.raises(jk.JakiroError):
         jk.commit_path(kt[..., 1:], vt[..., 1:], kc[..., 1:], vc[..., 1:], path, one, one)  # rows are not whole 16-byte chunks
+
+
+@pytest.mark.parametrize("depth,accepted,bad_at", [(1, 1, -1), (63, 63, -1), (64, 64, 63), (65, 65, -1), (65, 65, 64), (128, 128, -1), (128, 128, 127),
+                                                   (128, 70, 64), (130, 140, 129), (128, 128, 0)])
+def test_paths_around_a_wave_of_entries(depth, accepted, bad_at):
+    """A path ends in front of its first entry that names no node, which may lie in any 64 of its entries."""
+    T, B, cap, start = 128, 3, 200, 7
+    g = torch.Generator("cuda").manual_seed(depth)
+    kt, vt = (torch.randn((B, T, 2, 64), device="cuda", generator=g).to(torch.bfloat16) for _ in range(2))
+    path = torch.randint(0, T, (B, depth), device="cuda", generator=g, dtype=torch.int32)
+    want = min(accepted, depth)
+    if bad_at >= 0:
+        path[1, bad_at] = T if bad_at % 2 else -1
+    rows = [want, min(want, bad_at) if bad_at >= 0 else want, 0]
+    kc, vc = (torch.zeros((B, cap, 2, 64), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    alen = torch.tensor([accepted, accepted, -1], dtype=torch.int32, device="cuda")
+    plen = torch.full((B,), start, dtype=torch.int32, device="cuda")
+    jk.commit_path(kt, vt, kc, vc, path, alen, plen)
+    assert plen.cpu().tolist() == [start + n for n in rows]
+    for b, n in enumerate(rows):
+        at = path[b, :n].long()
+        assert torch.equal(kc[b, start:start + n], kt[b][at]) and torch.equal(vc[b, start:start + n], vt[b][at])
+        assert not kc[b, :start].any() and not kc[b, start + n:].any()
