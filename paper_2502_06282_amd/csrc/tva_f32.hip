@@ -6,15 +6,20 @@
 //
 // What bounds it: for small calls the instructions of a lone wave (5 - 8 cycles each; a block of 16 keys takes 2400 cycles with
 // its operands there) and the trips to memory in front of them.  So a wave has a block's K and V in flight at once and the next
-// block's K behind them, the prefix's and the tree's alike, and asks for the first block's K before the prefix length is known;
-// who has a block of the tree makes the ancestors of its rows while the keys come; at the end a wave scales its own sums, and
-// what is left to do for the result is adding.  For large calls the products bind, which run on v_mfma_f32_16x16x4_f32 (full
-// fp32) with K and V straight from L2 in operand layout, each read once for 16 rows.  S^T = K Q^T leaves a lane with four keys
-// of one row: exactly what the second product, O^T = V^T P^T, takes as its operand, so the weights never leave their registers.
-// An undivided key range needs no second launch.  4 heads of 64, 10 nodes and 138 keys: 16.9 us with one workgroup per query
-// row and a thread per key and column (the second launch included), 7.9 with the tree's ancestors made by one wave for all, its
-// keys asked for behind a barrier and the waves' weights worked out by every thread of the result, 6.2 like this; 4 sequences, 8
-// heads of 128, 52 nodes, 2100 keys 481, 56.4 and 56.
+// block's K behind them, the prefix's and the tree's alike; who has a block of the tree makes the ancestors of its rows while the
+// keys come; at the end a wave scales its own sums, and what is left to do for the result is adding.  For large calls the
+// products bind, which run on v_mfma_f32_16x16x4_f32 (full fp32) with K and V straight from L2 in operand layout, each read once
+// for 16 rows.  S^T = K Q^T leaves a lane with four keys of one row: exactly what the second product, O^T = V^T P^T, takes as its
+// operand, so the weights never leave their registers.  An undivided key range needs no second launch.
+//
+// A small head's first block is asked for before the prefix length is known, K and V, where the key range is undivided; with more
+// than 64 columns it is not, and not in front of the ancestors either: what a CU draws (some 60 bytes per ns, 200 KB for eight
+// waves' rows, K and V of 128 columns) takes longer than the trip that it saves, and the exchanges between lanes wait among it (3 -
+// 10 % more for trees of 64 nodes).  4 heads of 64, 10 nodes and 138 keys: 16.9 us with one workgroup per query row and a thread
+// per key and column (the second launch included), 7.9 with the tree's ancestors made by one wave for all, 6.2 with the first
+// block's K alone asked for early, 5.8 like this (6.7 with sixteen waves, of which none has two blocks); 45 drawn and edge calls of
+// all head dimensions 1.025 times as fast as with the K of a divided range's first part and of larger heads asked for early too
+// (0.975 - 1.10); 4 sequences, 8 heads of 128, 52 nodes, 2100 keys 481, 56.4 and 56.
 #include <type_traits>
 
 #include "jk_ancestors.h"
@@ -34,70 +39,134 @@ struct FParams {
   unsigned* err;  // the workspace's sticky device error word
   int B, T, Hkv, G, M, m_pad, D, max_prefix, splits;
   long long q_sb, q_st, q_sh, kc_sb, kc_sl, kc_sh, kt_sb, kt_st, kt_sh, o_sb, o_st, o_sh;
+  unsigned long long mg_g, mg_hkv;  // floor(2^32 / d) + 1: n / d == (n * mg) >> 32 while n * d < 2^32
   float scale;
 };
+static_assert(sizeof(FParams) > 192 && sizeof(FParams) <= 256, "four lines of kernel arguments");
+__device__ __forceinline__ int div_mg(int n, unsigned long long mg) { return (int)(((unsigned long long)(unsigned)n * mg) >> 32); }
 
-// KJ: 16-column chunks of a head (rounded up); WAVES: by how many registers that leaves
+// KJ: 16-column chunks of a head (rounded up); WAVES: by how many registers that leaves.  WHOLE: an undivided key range of a
+// small head, whose first loads do not wait for the prefix length
 template <int KJ>
 constexpr int waves_for() { return KJ <= 8 ? 8 : 4; }
 
-template <int KJ>
-__global__ __launch_bounds__(64 * waves_for<KJ>(), KJ <= 8 ? 2 : 1) void tva_f32_kernel(FParams p) {
-  constexpr int WAVES = waves_for<KJ>(), DB = (KJ + 3) / 4, LDO = 64 * DB + 4;
+template <int KJ, int WAVES, bool WHOLE>
+__global__ __launch_bounds__(64 * WAVES, KJ <= 8 ? (WAVES + 3) / 4 : 1) void tva_f32_kernel(FParams p) {
+  constexpr int DB = (KJ + 3) / 4, LDO = 64 * DB + 4;
   __shared__ float tops[WAVES][16];     // a wave's maximum of a row,
   __shared__ float2 shares[WAVES][16];  // and its share of the row's sum, beside the maximum of all
   extern __shared__ __attribute__((aligned(16))) float osum[];  // [WAVES][16][LDO]
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  {  // every 64-byte line of the kernel arguments at once: the compiler fetches them in several dependent batches
+    typedef __attribute__((address_space(4))) const unsigned kernarg_word;
+    kernarg_word* ka = (kernarg_word*)__builtin_amdgcn_kernarg_segment_ptr();
+    const unsigned a0 = ka[0], a1 = ka[16], a2 = ka[32], a3 = ka[48];
+    asm volatile("" ::"s"(a0), "s"(a1), "s"(a2), "s"(a3));
+  }
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int c = lane & 15, g = lane >> 4;
   const int split = blockIdx.x, row0 = blockIdx.y * 16;
-  const int kv = blockIdx.z % p.Hkv, b = blockIdx.z / p.Hkv;
+  const int b = div_mg(blockIdx.z, p.mg_hkv), kv = blockIdx.z - b * p.Hkv;
   const int D = p.D;
   const float* kc = p.kc + b * p.kc_sb + (long long)kv * p.kc_sh;
   const float* vc = p.vc + b * p.kc_sb + (long long)kv * p.kc_sh;
   const float* kt = p.kt + b * p.kt_sb + (long long)kv * p.kt_sh;
   const float* vt = p.vt + b * p.kt_sb + (long long)kv * p.kt_sh;
 
-  int L = p.prefix_len[b];
-  const int pa0 = lane < p.T ? p.parent[(long long)b * p.T + lane] : -1, pa1 = lane + 64 < p.T ? p.parent[(long long)b * p.T + lane + 64] : -1;
-  const int m = min(row0 + c, p.M - 1), node = m / p.G;  // this lane's query row (rows past the end repeat the last one)
+  int lane_zero = 0;
+  asm volatile("" : "+v"(lane_zero));  // (a vector load: a scalar one would be waited for with the arguments)
+  const int L_raw = __hip_atomic_load(p.prefix_len + b + lane_zero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int pa0 = p.parent[(long long)b * p.T + min(lane, p.T - 1)], pa1 = p.parent[(long long)b * p.T + min(lane + 64, p.T - 1)];
+  const int m = min(row0 + c, p.M - 1), node = div_mg(m, p.mg_g);  // this lane's query row (rows past the end repeat the last one)
   floatx4 q[KJ], k[KJ], v[DB][4];  // the row, and a block's K and V
   // column 16 j + 4 g of a row; columns past the end: the row's first ones, against zeros of q
   auto col = [&](int j) { return 16 * j + 4 * g < D ? 16 * j + 4 * g : 0; };
-  auto load_k = [&](const float* row) {
-#pragma unroll
-    for (int j = 0; j < KJ; ++j) k[j] = *reinterpret_cast<const floatx4*>(row + col(j));
+
+  // ---- this wave's blocks of 16 keys: of the tree's first, first + WAVES, ..., then of the prefix's wave, wave + WAVES, ...  The
+  // tree's begin with the waves that have fewer of the prefix, if its length is the host's bound: so which wave has them, and
+  // what it asks for first, does not depend on the length.  (At most 512 ranges of at most 65 664 keys.)
+  const bool whole = WHOLE || p.splits == 1;
+  int p_end, tree_begin, tree_end, n_mine_t, n_mine, first, k_begin;
+  auto set_range = [&](int L, bool bound) {
+    const int ktot = L + p.T;
+    k_begin = whole ? 0 : (int)((unsigned)split * (unsigned)ktot / (unsigned)p.splits);
+    const int k_end = whole ? ktot : (int)((unsigned)(split + 1) * (unsigned)ktot / (unsigned)p.splits);
+    p_end = min(k_end, L);
+    tree_begin = max(k_begin, L) - L;
+    tree_end = k_end - L;
+    const int n_prefix = max(p_end - k_begin + 15, 0) >> 4, n_tree = max(tree_end - tree_begin + 15, 0) >> 4;
+    if (bound) first = (wave - n_prefix) & (WAVES - 1);
+    n_mine_t = max(n_tree - first + WAVES - 1, 0) / (unsigned)WAVES;
+    n_mine = n_mine_t + max(n_prefix - wave + WAVES - 1, 0) / (unsigned)WAVES;
   };
-  auto load_v = [&](auto v_at) {  // v_at(i): where key i of the block has its values
+  struct Block {
+    const float *k, *v;   // the rows
+    long long stride;
+    int key0, last;       // the first of them, and the last that counts
+    bool tree;
+  };
+  auto block_at = [&](int i) {
+    Block x;
+    x.tree = i < n_mine_t;
+    x.k = x.tree ? kt : kc;
+    x.v = x.tree ? vt : vc;
+    x.stride = x.tree ? p.kt_st : p.kc_sl;
+    x.key0 = x.tree ? tree_begin + 16 * (first + WAVES * i) : k_begin + 16 * (wave + WAVES * (i - n_mine_t));
+    x.last = (x.tree ? tree_end : p_end) - 1;
+    return x;
+  };
+  auto load_k = [&](const Block& x, int c, int g) {
+    const float* row = x.k + (long long)min(x.key0 + c, x.last) * x.stride;
+#pragma unroll
+    for (int j = 0; j < KJ; ++j) k[j] = *reinterpret_cast<const floatx4*>(row + (16 * j + 4 * g < D ? 16 * j + 4 * g : 0));
+  };
+  auto load_v = [&](const Block& x, int c, int g) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float* row = v_at(4 * g + i);
+      const float* row = x.v + (long long)min(x.key0 + 4 * g + i, x.last) * x.stride;
 #pragma unroll
       for (int d = 0; d < DB; ++d) v[d][i] = *reinterpret_cast<const floatx4*>(row + (64 * d + 4 * c < D ? 64 * d + 4 * c : 0));
     }
   };
-  if (split == 0 && p.max_prefix > 0) load_k(kc + (long long)min(16 * wave + c, p.max_prefix - 1) * p.kc_sl);
-  {
+  auto load_row = [&]() {
     const float* src = p.q + b * p.q_sb + node * p.q_st + (long long)(kv * p.G + m - node * p.G) * p.q_sh;
 #pragma unroll
     for (int j = 0; j < KJ; ++j) q[j] = *reinterpret_cast<const floatx4*>(src + col(j));
-    if (16 * KJ != D) {
-#pragma unroll
-      for (int j = 0; j < KJ; ++j)
-        if (16 * j + 4 * g >= D) q[j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    }
+  };
+  auto length = [&]() {
+    const int len = __builtin_amdgcn_readfirstlane(L_raw);
+    return len < 0 ? 0 : (len > p.max_prefix ? p.max_prefix : len);
+  };
+  Block cur;
+  load_row();
+  if constexpr (WHOLE) {
+    // The first block on the assumption that the length is the host's bound: one trip to memory for all of it.  (In a branch,
+    // the compiler would wait for all of it where it waits for the length: a wave without a block asks for one key of the tree
+    // in every lane.)
+    set_range(p.max_prefix, true);
+    const bool some = n_mine > 0;
+    cur = block_at(0);
+    if (!some) cur = Block{kt, vt, 0, 0, 0, true};
+    load_k(cur, some ? c : 0, some ? g : 0);
+    load_v(cur, some ? c : 0, some ? g : 0);
+    set_range(length(), false);
+    if (!cur.tree) cur.last = p_end - 1;
+  } else {
+    set_range(length(), true);
+    cur = block_at(0);
   }
-  L = L < 0 ? 0 : (L > p.max_prefix ? p.max_prefix : L);
-  const int ktot = L + p.T;  // (at most 512 ranges of at most 65 664 keys)
-  const int k_begin = p.splits == 1 ? 0 : (int)((unsigned)split * (unsigned)ktot / (unsigned)p.splits);
-  const int k_end = p.splits == 1 ? ktot : (int)((unsigned)(split + 1) * (unsigned)ktot / (unsigned)p.splits);
-  const int p_end = min(k_end, L), t_begin = max(k_begin, L);
-  const int n_prefix = p_end > k_begin ? (p_end - k_begin + 15) / 16 : 0, n_tree = k_end > t_begin ? (k_end - t_begin + 15) / 16 : 0;
-
-  // The waves with fewer blocks of the prefix take the tree's first; who has one makes its rows' ancestors while the keys come
-  const int first = (wave + WAVES - n_prefix % WAVES) % WAVES;
   dev::Ancestors seen{0ull, 0ull};
-  if (first < n_tree || (split == 0 && wave == 0)) seen = dev::ancestors_of(p.T, p.err, pa0, pa1, node, split == 0 && row0 == 0 && kv == 0 && wave == 0);
+  if (n_mine_t > 0 || (split == 0 && wave == 0))
+    seen = dev::ancestors_of(p.T, p.err, lane < p.T ? pa0 : -1, lane + 64 < p.T ? pa1 : -1, node, split == 0 && row0 == 0 && kv == 0 && wave == 0);
+  if (!WHOLE && n_mine > 0) {
+    load_k(cur, c, g);
+    load_v(cur, c, g);
+  }
+  if (16 * KJ != D) {
+#pragma unroll
+    for (int j = 0; j < KJ; ++j)
+      if (16 * j + 4 * g >= D) q[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  }
 
   // A weight of zero - an unseen key's above all - leaves its value out, whatever that is.  The matrix product has one
   // value for sixteen rows' weights, so an infinity or a NaN reaches them all; it stays in the accumulators to the end, and
@@ -105,66 +174,6 @@ __global__ __launch_bounds__(64 * waves_for<KJ>(), KJ <= 8 ? 2 : 1) void tva_f32
   // each product: 57.0 us for 4 sequences, 8 heads of 128, 52 nodes, 2100 keys became 59.8.)
   floatx4 o[DB][4];
   float mx, sum;
-  // 16 keys, whose K and V have been asked for: visible(i) whether this lane's row sees key 4 g + i; `next` asks for the K of
-  // the block behind this one as soon as this one's is used.  (careful: V at v_at(i))
-  auto block = [&](auto careful, auto v_at, auto visible, auto next) {
-    if (16 * KJ != D) {  // (uniform; what stands in for columns past the end of a key with an infinity must not meet q's zeros)
-#pragma unroll
-      for (int j = 0; j < KJ; ++j)
-        if (16 * j + 4 * g >= D) k[j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    }
-    floatx4 s = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int j = 0; j < KJ; ++j)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_mfma_f32_16x16x4f32(k[j][i], q[j][i], s, 0, 0, 0);
-    next();
-#pragma unroll
-    for (int i = 0; i < 4; ++i) s[i] = visible(i) ? s[i] * p.scale : -INFINITY;
-    float top = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
-    top = fmaxf(top, __uint_as_float(dev::other16(__float_as_uint(top), lane & 16)));
-    top = fmaxf(top, __uint_as_float(dev::other32(__float_as_uint(top), lane & 32)));
-    const float mn = fmaxf(mx, top), base = mn == -INFINITY ? 0.f : mn;
-    if (__any(mn > mx && mx > -INFINITY)) {  // (nothing to rescale before the row's first key)
-      const float f = expf(mx - base);
-      sum *= f;
-#pragma unroll
-      for (int d = 0; d < DB; ++d)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) o[d][i] *= f;
-    }
-    mx = mn;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      s[i] = expf(s[i] - base);
-      sum += s[i];
-    }
-    if (careful) {
-#pragma unroll 1
-      for (int key = 0; key < 16; ++key) {
-        const float mine = (key & 2) ? ((key & 1) ? s[3] : s[2]) : ((key & 1) ? s[1] : s[0]);
-        const float w = __shfl(mine, 16 * (key >> 2) + c);
-        const float* row = v_at(key);
-#pragma unroll
-        for (int d = 0; d < DB; ++d)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {  // (as everywhere: columns past the end take the row's first ones, and are not stored)
-            const int at = 64 * d + 16 * g + 4 * r;
-            const floatx4 x = *reinterpret_cast<const floatx4*>(row + (at < D ? at : 0));
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[d][e][r] = w != 0.f ? fmaf(x[e], w, o[d][e][r]) : o[d][e][r];
-          }
-      }
-      return;
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int d = 0; d < DB; ++d)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[d][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[d][i][e], s[i], o[d][e], 0, 0, 0);
-  };
-  auto prefix_k = [&](int blk) { load_k(kc + (long long)min(k_begin + 16 * blk + c, p_end - 1) * p.kc_sl); };
   auto pass = [&](auto careful) {
 #pragma unroll
     for (int d = 0; d < DB; ++d)
@@ -172,32 +181,85 @@ __global__ __launch_bounds__(64 * waves_for<KJ>(), KJ <= 8 ? 2 : 1) void tva_f32
       for (int i = 0; i < 4; ++i) o[d][i] = floatx4{0.f, 0.f, 0.f, 0.f};
     mx = -INFINITY;
     sum = 0.f;
-    if ((split != 0 || careful) && wave < n_prefix) prefix_k(wave);
-    const int tree_begin = t_begin - L, last = k_end - L - 1;
-    auto tree_k = [&](int blk) { load_k(kt + (long long)min(tree_begin + 16 * blk + c, last) * p.kt_st); };
-    if (wave >= n_prefix && first < n_tree) tree_k(first);
-    for (int blk = wave; blk < n_prefix; blk += WAVES) {
-      const int key0 = k_begin + 16 * blk, left = p_end - key0 - 4 * g;
-      auto v_at = [&](int i) { return vc + (long long)min(key0 + i, p_end - 1) * p.kc_sl; };
-      if (!careful) load_v(v_at);
-      block(careful, v_at, [&](int i) { return i < left; },
-            [&]() {
-              if (blk + WAVES < n_prefix) prefix_k(blk + WAVES);
-              else if (first < n_tree) tree_k(first);
-            });
+    if (careful && n_mine > 0) {
+      cur = block_at(0);
+      load_k(cur, c, g);
     }
-    const unsigned long long lo = seen.lo, hi = seen.hi;
-    for (int blk = first; blk < n_tree; blk += WAVES) {
-      const int key0 = tree_begin + 16 * blk, left = last + 1 - key0 - 4 * g;
-      auto v_at = [&](int i) { return vt + (long long)min(key0 + i, last) * p.kt_st; };
-      if (!careful) load_v(v_at);
-      // the bits of keys key0 .. key0 + 63, then this lane's four
-      const unsigned long long set = key0 >= 64 ? hi >> (key0 - 64) : key0 > 0 ? lo >> key0 | hi << (64 - key0) : lo;
-      const unsigned mine = (unsigned)(set >> (4 * g));
-      block(careful, v_at, [&](int i) { return i < left && ((mine >> i) & 1u); },
-            [&]() {
-              if (blk + WAVES < n_tree) tree_k(blk + WAVES);
-            });
+    for (int blk = 0; blk < n_mine; ++blk) {  // (its K and V have been asked for)
+      const Block now = cur;
+      if (16 * KJ != D) {  // (uniform; what stands in for columns past the end of a key with an infinity must not meet q's zeros)
+#pragma unroll
+        for (int j = 0; j < KJ; ++j)
+          if (16 * j + 4 * g >= D) k[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+      }
+      floatx4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < KJ; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_mfma_f32_16x16x4f32(k[j][i], q[j][i], s, 0, 0, 0);
+      if (blk + 1 < n_mine) {
+        cur = block_at(blk + 1);
+        load_k(cur, c, g);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s[i] *= p.scale;
+      if (now.tree || now.key0 + 15 > now.last) {  // (uniform) the keys that this lane's row sees, a bit each; then its four
+        unsigned mine = ~0u;
+        if (now.tree) mine = (unsigned)(now.key0 >= 64 ? seen.hi >> (now.key0 - 64) : now.key0 > 0 ? seen.lo >> now.key0 | seen.hi << (64 - now.key0) : seen.lo);
+        mine &= (2u << min(now.last - now.key0, 15)) - 1u;
+        mine >>= 4 * g;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[i] = (mine >> i) & 1u ? s[i] : -INFINITY;
+      }
+      float top = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+      top = fmaxf(top, __uint_as_float(dev::other16(__float_as_uint(top), lane & 16)));
+      top = fmaxf(top, __uint_as_float(dev::other32(__float_as_uint(top), lane & 32)));
+      const float mn = fmaxf(mx, top), base = mn == -INFINITY ? 0.f : mn;
+      if (__any(mn > mx && mx > -INFINITY)) {  // (nothing to rescale before the row's first key)
+        const float f = expf(mx - base);
+        sum *= f;
+#pragma unroll
+        for (int d = 0; d < DB; ++d)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) o[d][i] *= f;
+      }
+      mx = mn;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        s[i] = expf(s[i] - base);
+        sum += s[i];
+      }
+      if (careful) {
+#pragma unroll 1
+        for (int key = 0; key < 16; ++key) {
+          const float mine = (key & 2) ? ((key & 1) ? s[3] : s[2]) : ((key & 1) ? s[1] : s[0]);
+          const float w = __shfl(mine, 16 * (key >> 2) + c);
+          const float* row = now.v + (long long)min(now.key0 + key, now.last) * now.stride;
+#pragma unroll
+          for (int d = 0; d < DB; ++d)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {  // (as everywhere: columns past the end take the row's first ones, and are not stored)
+              const int at = 64 * d + 16 * g + 4 * r;
+              const floatx4 x = *reinterpret_cast<const floatx4*>(row + (at < D ? at : 0));
+#pragma unroll
+              for (int e = 0; e < 4; ++e) o[d][e][r] = w != 0.f ? fmaf(x[e], w, o[d][e][r]) : o[d][e][r];
+            }
+        }
+        continue;
+      }
+      if (now.key0 + 15 > now.last) {  // (a first block asked for beyond the prefix's end: what is there is nobody's value)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int d = 0; d < DB; ++d) v[d][i] = now.key0 + 4 * g + i > now.last ? floatx4{0.f, 0.f, 0.f, 0.f} : v[d][i];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int d = 0; d < DB; ++d)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[d][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[d][i][e], s[i], o[d][e], 0, 0, 0);
+      if (blk + 1 < n_mine) load_v(cur, c, g);
     }
   };
   pass(std::false_type());
@@ -261,13 +323,20 @@ __global__ __launch_bounds__(64 * waves_for<KJ>(), KJ <= 8 ? 2 : 1) void tva_f32
   }
 }
 
+template <int KJ, int WAVES, bool WHOLE>
+hipError_t launch_waves(const FParams& fp, hipStream_t stream) {
+  constexpr int SMEM = WAVES * 16 * (64 * ((KJ + 3) / 4) + 4) * 4;
+  static LdsLimitRaised raised;
+  if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(tva_f32_kernel<KJ, WAVES, WHOLE>), SMEM, raised); e != hipSuccess) return e;
+  hipLaunchKernelGGL((tva_f32_kernel<KJ, WAVES, WHOLE>), dim3(fp.splits, (fp.M + 15) / 16, fp.B * fp.Hkv), dim3(64 * WAVES), SMEM, stream, fp);
+  return hipGetLastError();
+}
 template <int KJ>
 hipError_t launch_kj(const FParams& fp, hipStream_t stream) {
-  constexpr int WAVES = waves_for<KJ>(), SMEM = WAVES * 16 * (64 * ((KJ + 3) / 4) + 4) * 4;
-  static LdsLimitRaised raised;
-  if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(tva_f32_kernel<KJ>), SMEM, raised); e != hipSuccess) return e;
-  hipLaunchKernelGGL(tva_f32_kernel<KJ>, dim3(fp.splits, (fp.M + 15) / 16, fp.B * fp.Hkv), dim3(64 * WAVES), SMEM, stream, fp);
-  return hipGetLastError();
+  if constexpr (KJ == 4) {
+    if (fp.splits == 1) return launch_waves<4, 8, true>(fp, stream);
+  }
+  return launch_waves<KJ, waves_for<KJ>(), false>(fp, stream);
 }
 
 }  // namespace
@@ -293,6 +362,8 @@ hipError_t launch_tva_f32(const AttnArgs& a, const AttnPlan& pl, hipStream_t str
   fp.kt_sb = d.kt_stride_b; fp.kt_st = d.kt_stride_t; fp.kt_sh = d.kt_stride_h;
   fp.out = static_cast<float*>(a.out);
   fp.o_sb = d.o_stride_b; fp.o_st = d.o_stride_t; fp.o_sh = d.o_stride_h;
+  auto magic = [](int v) { return (1ull << 32) / (unsigned)v + 1; };
+  fp.mg_g = magic(fp.G); fp.mg_hkv = magic(fp.Hkv);
   fp.scale = a.scale_log2;  // for this path the host passes the plain softmax scale here
   switch ((d.head_dim + 15) / 16) {
     case 1: case 2: case 3:
