@@ -133,7 +133,8 @@ struct PlanModel {
 };
 
 namespace {
-bool f32_in_parts(long long keys, int head_dim) { return keys >= (head_dim <= 64 ? 300 : head_dim <= 128 ? 200 : 112); }  // the line: see compute_attn_plan
+// Whether a workspace has room for fp32 ranges in parts; the line from which they are taken so: see compute_attn_plan
+bool f32_in_parts(long long keys, int head_dim) { return keys >= (head_dim <= 64 ? 300 : head_dim <= 128 ? 200 : 112); }
 
 // A workspace serves every call that is no larger in batch, nodes, heads, head_dim and prefix bound than the one it was
 // sized for.  Partial results alone do not have that order - a smaller call may be cut into more splits, and take more
@@ -363,20 +364,25 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
     long long s = (keys + 1023) / 1024;  // ranges of 1024 keys, for 16 query rows a workgroup
     if (s > kMaxSplits) return false;  // fp32 path: at most 64 * 1024 keys
     pl->splits = (int)s;
-    // Few workgroups: each range in up to eight parts, where the merging launch (3 us) is needed anyway or costs less than
-    // what the parts save.  A wave's time for a block of keys hardly depends on head_dim up to 64 (maximum, exponentials, trips), so
-    // neither does the line; beyond 128 a workgroup has four waves instead of eight.  Whole / in parts, us, 20 nodes and 8 heads, of 4, 16,
-    // 32 and 64: 256 keys 8.6 / 9.1, 8.6 / 9.1, 8.6 / 9.1, 8.1 / 8.6; 320 10.1 / 9.0, 10.0 / 9.0, 10.1 / 9.1, 9.4 / 8.6; 640 13.8 /
-    // 9.9 and (64) 13.1 / 9.2.  Of 80, 96 and 128: 176 keys 8.3 / 9.5, 8.9 / 9.9, 10.2 / 10.8; 208 9.9 / 9.5, 10.6 / 9.9, 11.9 / 10.9.  Of 192
-    // and 256: 80 14.8 / 14.9, 14.7 / 15.0; 112 15.4 / 15.0, 15.2 / 15.1; 144 18.7 / 15.0, 18.3 / 15.1.
+    // Few workgroups: each range in up to eight parts, where merging them (in the kernel, by the last workgroup of a row tile; beyond 16
+    // parts in a launch of its own) costs less than what the parts save.  A wave's time for a block of keys hardly depends on head_dim
+    // up to 64 (maximum, exponentials, trips), so neither does the line; beyond 128 a workgroup has four waves instead of eight, and
+    // 128 keys are two turns of theirs.  More than four parts of few keys only add to the merge.  Whole / in 4 / 6 / 8 parts, us,
+    // 20 nodes and 8 heads, of 64: 320 keys 8.9 / 7.8 / 7.7 / 7.8, 620 12.2 / 9.0 / 8.2 / 8.5; of 128: 200 11.5 / 9.3 / 9.6 / 9.8, 320
+    // 15.1 / 10.8 / 10.6 / 10.1; of 192: 115 14.0 / 14.5 / 14.7 / 15.3, 145 17.1 / 14.8 / 14.9 / 15.5.  Where three parts fill the CUs
+    // (80 row tiles), whole / in 3: of 64, 170 keys 6.6 / 7.6, 340 9.5 / 8.2; of 80, 170 8.6 / 8.9, 340 12.8 / 10.1.  Four parts
+    // would pay a little earlier (of 64, 250 keys 7.9 / 7.4; of 128, 150 9.9 / 9.2), but the bytes that a call asks for stay as
+    // they are, so that a workspace allocated by them still serves it.
     const long long wgs = units * ((pl->m_rows + 15) / 16) * s;
     pl->parts = pl->splits;
-    if (f32_in_parts(keys, d.head_dim))
-      for (int sub = 8; sub > 1; --sub)
+    if (f32_in_parts(keys, d.head_dim) && keys >= 130) {
+      const int most = keys < 220 ? 4 : keys < 300 ? 6 : 8;
+      for (int sub = most; sub > 1; --sub)
         if (wgs * sub <= device_cu_count() && s * sub <= kMaxSplits) {
           pl->parts = pl->splits * sub;
           break;
         }
+    }
   }
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
   const size_t rows = pl->parts > 1 ? (size_t)units * pl->parts * pl->m_pad : 0, o_row = (size_t)d.head_dim * (d.dtype == JK_BF16 ? 2 : sizeof(float));
@@ -564,8 +570,9 @@ static jk_status attention_common(const jk_attn_desc* desc, const jk_paged_kv* p
     if (e == hipSuccess && pl.splits > 1 && !pl.fused) e = launch_tva_combine(a, pl, stream);
   } else {
     a.scale_log2 = scale;  // the fp32 path works in natural units
+    if (!f32_merges(d, pl)) a.sync = nullptr;
     e = launch_tva_f32(a, pl, stream);
-    if (e == hipSuccess && pl.parts > 1) e = launch_tva_combine(a, pl, stream);
+    if (e == hipSuccess && pl.parts > 1 && !a.sync) e = launch_tva_combine(a, pl, stream);
   }
   return e == hipSuccess ? JK_OK : JK_ERR_HIP;
 }

@@ -107,6 +107,7 @@ struct AttnArgs {
 
 hipError_t launch_tva_bf16(const AttnArgs& a, const AttnPlan& p, hipStream_t stream);
 hipError_t launch_tva_f32(const AttnArgs& a, const AttnPlan& p, hipStream_t stream);
+bool f32_merges(const jk_attn_desc& d, const AttnPlan& pl);  // whether that launch merges the parts of a divided range itself
 hipError_t launch_tva_combine(const AttnArgs& a, const AttnPlan& p, hipStream_t stream);
 
 struct AcceptArgs {

@@ -23,12 +23,17 @@
 #include <type_traits>
 
 #include "jk_ancestors.h"
+#include "jk_device.h"
 #include "jk_wave.h"
 
 namespace jk {
 namespace {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+// The word of row tile `i` among all: neighbours 64 bytes apart (an atomic takes 11 ns of the memory channel that has its word)
+__device__ __forceinline__ int word_of(int i) { return i % kMaxFusedGroups * 16 + i / kMaxFusedGroups; }
 
 struct FParams {
   const float *q, *kc, *vc, *kt, *vt;
@@ -37,6 +42,7 @@ struct FParams {
   float2* part_ml;
   float* out;     // undivided key range: the result
   unsigned* err;  // the workspace's sticky device error word
+  unsigned* words;  // divided range, merged by the last of a row tile's workgroups: a word each (see word_of); or null
   int B, T, Hkv, G, M, m_pad, D, max_prefix, splits;
   long long q_sb, q_st, q_sh, kc_sb, kc_sl, kc_sh, kt_sb, kt_st, kt_sh, o_sb, o_st, o_sh;
   unsigned long long mg_g, mg_hkv;  // floor(2^32 / d) + 1: n / d == (n * mg) >> 32 while n * d < 2^32
@@ -311,15 +317,90 @@ __global__ __launch_bounds__(64 * WAVES, KJ <= 8 ? (WAVES + 3) / 4 : 1) void tva
       tot += shares[w][r].x;
     }
     if (p.splits == 1) {
-      const int n = row / p.G;
+      const int n = div_mg(row, p.mg_g);
       float* dst = p.out + b * p.o_sb + n * p.o_st + (long long)(kv * p.G + row - n * p.G) * p.o_sh;
       const float inv = 1.f / tot;  // (tot > 0: every row sees at least its own tree key)
       *reinterpret_cast<floatx4*>(dst + 4 * x) = floatx4{t[0] * inv, t[1] * inv, t[2] * inv, t[3] * inv};
     } else {
       const long long prow = ((long long)(b * p.Hkv + kv) * p.splits + split) * p.m_pad + row;
-      *reinterpret_cast<floatx4*>(p.part_o + prow * D + 4 * x) = t;
-      if (x == 0) p.part_ml[prow] = make_float2(shares[0][r].y, tot);
+      const float2 ml = make_float2(shares[0][r].y, tot);
+      if (p.words) {
+        dev::store_through(p.part_o + prow * D + 4 * x, __builtin_bit_cast(dev::store_u32x4, t));
+        if (x == 0) dev::store_through(p.part_ml + prow, __builtin_bit_cast(dev::store_u32x2, ml));
+      } else {
+        *reinterpret_cast<floatx4*>(p.part_o + prow * D + 4 * x) = t;
+        if (x == 0) p.part_ml[prow] = ml;
+      }
     }
+  }
+  if constexpr (!WHOLE) {
+    if (p.splits == 1 || !p.words) return;
+    // ---- Merge of the parts by the last of the row tile's workgroups to come: nobody waits, and the sum is the same whoever it is.
+    // Results go through to memory in front of the count and are read past the caches (the workgroups run on different XCDs).
+    // With a second launch for it before, a call: two sequences, 16 heads of 64, 3 nodes, 1811 keys in front 9.7 / 9.0 us; 4 of 80, 2 nodes,
+    // 581 keys 9.7 / 8.5; 2 of 64, 3 nodes, 705 keys 8.6 / 7.3.
+    __shared__ int last_s;
+    dev::wait_vm<0>();
+    __syncthreads();
+    if (tid == 0) {
+      unsigned* word = p.words + word_of((int)(blockIdx.z * gridDim.y + blockIdx.y));
+      const bool last = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)p.splits - 1u;
+      if (last) __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      last_s = last;
+    }
+    __syncthreads();
+    if (!__builtin_amdgcn_readfirstlane(last_s)) return;
+    const long long first = (long long)(b * p.Hkv + kv) * p.splits * p.m_pad + row0;  // the first part's first row
+    const uint64_t* pairs = reinterpret_cast<const uint64_t*>(p.part_ml) + first;
+    // (at most 16 parts of a unit's rows: below 2^31 bytes by the host's choice)
+    const auto sums = __builtin_amdgcn_make_buffer_rsrc(p.part_o + first * D, 0, ((p.splits - 1) * p.m_pad + min(16, p.M - row0)) * D * 4, 0x00020000);
+    auto merge = [&](auto at_once) {  // (as many parts under way as there are, and no more: 8 for three of them took as long again)
+      constexpr int AT_ONCE = decltype(at_once)::value;
+      for (int i = tid; i < 16 * d4; i += 64 * WAVES) {
+        const int r = i / d4, x = i - r * d4, row = row0 + r;
+        if (row >= p.M) break;
+        floatx4 t = {0.f, 0.f, 0.f, 0.f};
+        float tot = 0.f, top = -INFINITY;
+        for (int s0 = 0; s0 < p.splits; s0 += AT_ONCE) {
+          uint64_t ml[AT_ONCE];
+          u32x4 o4[AT_ONCE];
+#pragma unroll
+          for (int u = 0; u < AT_ONCE; ++u) ml[u] = __hip_atomic_load(pairs + (long long)min(s0 + u, p.splits - 1) * p.m_pad + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+          for (int u = 0; u < AT_ONCE; ++u) o4[u] = __builtin_amdgcn_raw_buffer_load_b128(sums, ((min(s0 + u, p.splits - 1) * p.m_pad + r) * D + 4 * x) * 4, 0, dev::kDeviceScope);
+          float here = top;
+          float part_top[AT_ONCE], part_sum[AT_ONCE];
+#pragma unroll
+          for (int u = 0; u < AT_ONCE; ++u) {  // (a part without a key that the row sees, and what stands in for one past the last: no weight)
+            part_sum[u] = s0 + u < p.splits ? __uint_as_float((unsigned)(ml[u] >> 32)) : 0.f;
+            part_top[u] = part_sum[u] > 0.f ? __uint_as_float((unsigned)ml[u]) : -INFINITY;
+            here = fmaxf(here, part_top[u]);
+          }
+          if (here == -INFINITY) continue;
+          const float f = expf(top - here);  // (0 in front of the first)
+          tot *= f;
+          t *= f;
+          top = here;
+#pragma unroll
+          for (int u = 0; u < AT_ONCE; ++u) {
+            const float w = expf(part_top[u] - here);
+            if (w != 0.f) {
+              tot = fmaf(part_sum[u], w, tot);
+              const floatx4 own = __builtin_bit_cast(floatx4, o4[u]);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) t[e] = fmaf(own[e], w, t[e]);
+            }
+          }
+        }
+        const int n = div_mg(row, p.mg_g);
+        float* dst = p.out + b * p.o_sb + n * p.o_st + (long long)(kv * p.G + row - n * p.G) * p.o_sh;
+        const float inv = 1.f / tot;
+        *reinterpret_cast<floatx4*>(dst + 4 * x) = floatx4{t[0] * inv, t[1] * inv, t[2] * inv, t[3] * inv};
+      }
+    };
+    if (p.splits <= 4) merge(std::integral_constant<int, 4>());
+    else if (p.splits <= 8 || KJ > 5) merge(std::integral_constant<int, 8>());
+    else merge(std::integral_constant<int, 16>());
   }
 }
 
@@ -341,6 +422,15 @@ hipError_t launch_kj(const FParams& fp, hipStream_t stream) {
 
 }  // namespace
 
+// Up to 16 parts (the last workgroup of a row tile reads them all: beyond that the merging launch, which spreads them over the
+// CUs), with a word for each row tile
+bool f32_merges(const jk_attn_desc& d, const AttnPlan& pl) {
+  constexpr int kMergedParts = 16;
+  const long long tiles = (long long)d.batch * d.n_kv_heads * ((pl.m_rows + 15) / 16);
+  return pl.parts > 1 && pl.parts <= kMergedParts && tiles <= kMaxFusedGroups * 16 && tuning().attn_fused != 0 &&
+         (long long)pl.parts * pl.m_pad * d.head_dim * 4 < (1LL << 31);
+}
+
 hipError_t launch_tva_f32(const AttnArgs& a, const AttnPlan& pl, hipStream_t stream) {
   FParams fp;
   fp.q = static_cast<const float*>(a.q);
@@ -353,6 +443,7 @@ hipError_t launch_tva_f32(const AttnArgs& a, const AttnPlan& pl, hipStream_t str
   fp.part_o = a.part_o;
   fp.part_ml = a.part_ml;
   fp.err = a.err;
+  fp.words = a.sync;
   const jk_attn_desc& d = a.d;
   fp.B = d.batch; fp.T = d.n_tree; fp.Hkv = d.n_kv_heads; fp.G = d.n_q_heads / d.n_kv_heads;
   fp.M = pl.m_rows; fp.m_pad = pl.m_pad; fp.D = d.head_dim; fp.max_prefix = a.max_prefix_len;

@@ -3,10 +3,12 @@ the bound, with values behind them that are no numbers, blocks that become short
 and trees of one to eight blocks beside them."""
 import numpy as np
 import pytest
+import torch
 
+import paper_2502_06282_amd as jk
 from workloads import CONFIGS, attention_inputs
 
-from gpu_util import gpu_attention, oracle_attention
+from gpu_util import gpu_attention, oracle_attention, to_dev, tune
 
 pytestmark = pytest.mark.gpu
 
@@ -27,3 +29,44 @@ def test_lengths_below_the_bound(D, bound, T):
     assert np.isfinite(got).all()
     # (sums of at most 830 fp32 terms of order one, a few units of rounding each: far below 1e-5 of the largest result)
     assert np.abs(got - ref).max() <= 1e-5 * max(1.0, np.abs(ref).max())
+
+
+# keys of a bound whose ranges are 2, 3, 4, 6, 8, 10 and 16 parts, a range beyond what the kernel merges (24: a launch of its own), at
+# lengths that leave parts empty
+@pytest.mark.parametrize("B,H,D,T,bound", [(8, 8, 64, 20, 500), (5, 8, 128, 20, 300), (1, 8, 80, 17, 190), (1, 4, 256, 40, 100), (2, 3, 96, 33, 250),
+                                           (2, 2, 16, 64, 450), (1, 6, 40, 50, 1900), (3, 2, 128, 1, 1500), (1, 3, 192, 20, 2600)])
+def test_parts_merged_by_the_last_workgroup(B, H, D, T, bound):
+    """The same as merging them in a second launch, captured and replayed in a workspace whose partial results are
+    noise each time; its words are zero again behind every call."""
+    cfg = CONFIGS["c1_tiny"].with_(batch=B, n_tree=T, n_q_heads=H, n_kv_heads=H, head_dim=D, prefix_len=bound)
+    x = attention_inputs(cfg, seed=bound)
+    par = np.tile(np.array([-1] + [i // 2 for i in range(T - 1)], dtype=np.int32), (B, 1))
+    lens = [(bound, 1, bound // 2, 0, bound - 1)[b % 5] for b in range(B)]
+    ref = oracle_attention(**x, parent=par, prefix_len=lens)
+    d = to_dev(x, "f32")
+    parent, pl = torch.from_numpy(par).cuda(), torch.tensor(lens, dtype=torch.int32).cuda()
+    ws = torch.zeros(jk.tree_verify_attention_workspace(d["q"], d["k_cache"], d["k_tree"], bound), dtype=torch.uint8, device="cuda")
+    outs = {}
+    for fused in (0, -1):
+        tune("attn_fused", fused)
+        out = torch.empty_like(d["q"])
+        call = jk.prepare_tree_verify_attention(d["q"], d["k_cache"], d["v_cache"], d["k_tree"], d["v_tree"], parent, pl, out, ws,
+                                                max_prefix_len=bound)
+        call.launch()
+        torch.cuda.synchronize()
+        outs[fused] = out.clone()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+            call.launch()
+        for rep in range(3):
+            out.fill_(float("nan"))
+            ws[jk.JK_WORKSPACE_HEADER_BYTES:].random_(0, 255)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, outs[fused]), (fused, rep)
+            assert not ws[:jk.JK_WORKSPACE_HEADER_BYTES].any()
+    # (sums of at most 2600 fp32 terms of order one, as above; the two merges weigh the same parts and add them in another order)
+    tol = 1e-5 * max(1.0, np.abs(ref).max())
+    for out in outs.values():
+        assert np.abs(out.double().cpu().numpy() - ref).max() <= tol
+    assert (outs[0] - outs[-1]).abs().max().item() <= 1e-6 * max(1.0, np.abs(ref).max())
