@@ -364,21 +364,25 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
     long long s = (keys + 1023) / 1024;  // ranges of 1024 keys, for 16 query rows a workgroup
     if (s > kMaxSplits) return false;  // fp32 path: at most 64 * 1024 keys
     pl->splits = (int)s;
-    // Few workgroups: each range in up to eight parts, where merging them (in the kernel, by the last workgroup of a row tile; beyond 16
+    // Few workgroups: each range in up to eight parts, where merging them (in the kernel, by the last workgroup of a row tile; of many
     // parts in a launch of its own) costs less than what the parts save.  A wave's time for a block of keys hardly depends on head_dim
-    // up to 64 (maximum, exponentials, trips), so neither does the line; beyond 128 a workgroup has four waves instead of eight, and
-    // 128 keys are two turns of theirs.  More than four parts of few keys only add to the merge.  Whole / in 4 / 6 / 8 parts, us,
-    // 20 nodes and 8 heads, of 64: 320 keys 8.9 / 7.8 / 7.7 / 7.8, 620 12.2 / 9.0 / 8.2 / 8.5; of 128: 200 11.5 / 9.3 / 9.6 / 9.8, 320
-    // 15.1 / 10.8 / 10.6 / 10.1; of 192: 115 14.0 / 14.5 / 14.7 / 15.3, 145 17.1 / 14.8 / 14.9 / 15.5.  Where three parts fill the CUs
-    // (80 row tiles), whole / in 3: of 64, 170 keys 6.6 / 7.6, 340 9.5 / 8.2; of 80, 170 8.6 / 8.9, 340 12.8 / 10.1.  Four parts
-    // would pay a little earlier (of 64, 250 keys 7.9 / 7.4; of 128, 150 9.9 / 9.2), but the bytes that a call asks for stay as
-    // they are, so that a workspace allocated by them still serves it.
+    // up to 64 (maximum, exponentials, trips), so neither does the line; beyond 128 a workgroup has four waves instead of eight.
+    // Whole / in 4 / 6 / 8 parts, us, 20 nodes and 8 heads, of 64: 320 keys 8.9 / 7.8 / 7.7 / 7.8, 620 12.2 / 9.0 / 8.2 / 8.5; of 128:
+    // 200 11.5 / 9.3 / 9.6 / 9.8, 320 15.1 / 10.8 / 10.6 / 10.1; of 192: 121 14.0 / 12.6 / 13.3 / 13.2, 200 20.2 / 13.6 / 14.3 / 14.0, 300
+    // 23.6 / 16.9 / 14.8 / 14.5.  Where three parts fill the CUs (80 row tiles), whole / in 3: of 64, 170 keys 6.6 / 7.6, 340 9.5 / 8.2; of 80,
+    // 170 8.6 / 8.9, 340 12.8 / 10.1.  Four parts would pay a little earlier (of 64, 250 keys 7.9 / 7.4; of 128, 150 9.9 / 9.2), but the bytes
+    // that a call asks for stay as they are, so that a workspace allocated by them still serves it.
+    // A fifth part, where no more fit, is one more to merge.  In 4 / 5 parts a range, one range of 503 keys, heads of 128, 12.5 / 11.6, of 440
+    // and 192 17.4 / 18.2, of 840 24.3 / 22.6; two of 770 and 64 10.2 / 11.3, and 128 15.3 / 15.8, and 192 24.2 / 22.4; three of 843 and 64
+    // 12.0 / 11.5, and 192 25.6 / 23.1; of 977 12.1 / 12.6 and 25.9 / 26.3.
     const long long wgs = units * ((pl->m_rows + 15) / 16) * s;
     pl->parts = pl->splits;
-    if (f32_in_parts(keys, d.head_dim) && keys >= 130) {
+    if (f32_in_parts(keys, d.head_dim)) {
+      auto turns = [&](int sub) { return ((keys / s + sub - 1) / sub - 1) / 64; };  // (of four blocks of 16 keys)
+      const bool small_heads = d.head_dim <= 128, fifth = small_heads && s <= 2 ? s == 1 : turns(5) < turns(4);
       const int most = keys < 220 ? 4 : keys < 300 ? 6 : 8;
       for (int sub = most; sub > 1; --sub)
-        if (wgs * sub <= device_cu_count() && s * sub <= kMaxSplits) {
+        if (wgs * sub <= device_cu_count() && s * sub <= kMaxSplits && (sub != 5 || fifth)) {
           pl->parts = pl->splits * sub;
           break;
         }

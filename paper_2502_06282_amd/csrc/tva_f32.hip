@@ -352,51 +352,63 @@ __global__ __launch_bounds__(64 * WAVES, KJ <= 8 ? (WAVES + 3) / 4 : 1) void tva
     if (!__builtin_amdgcn_readfirstlane(last_s)) return;
     const long long first = (long long)(b * p.Hkv + kv) * p.splits * p.m_pad + row0;  // the first part's first row
     const uint64_t* pairs = reinterpret_cast<const uint64_t*>(p.part_ml) + first;
-    // (at most 16 parts of a unit's rows: below 2^31 bytes by the host's choice)
+    // (a unit's parts are below 2^31 bytes by the host's choice)
     const auto sums = __builtin_amdgcn_make_buffer_rsrc(p.part_o + first * D, 0, ((p.splits - 1) * p.m_pad + min(16, p.M - row0)) * D * 4, 0x00020000);
+    // 4 * WAVES threads a row, each all of its columns at once: with one after the other, of 256, a trip to memory each
+    // (8 sequences, 4 heads, 10 nodes, 138 keys 16.6 us / 14.1 so)
+    constexpr int LANES = 4 * WAVES, COLS = (4 * KJ + LANES - 1) / LANES;
+    const int r = tid / LANES, x = tid % LANES, row = row0 + r;
+    if (row >= p.M) return;
     auto merge = [&](auto at_once) {  // (as many parts under way as there are, and no more: 8 for three of them took as long again)
       constexpr int AT_ONCE = decltype(at_once)::value;
-      for (int i = tid; i < 16 * d4; i += 64 * WAVES) {
-        const int r = i / d4, x = i - r * d4, row = row0 + r;
-        if (row >= p.M) break;
-        floatx4 t = {0.f, 0.f, 0.f, 0.f};
-        float tot = 0.f, top = -INFINITY;
-        for (int s0 = 0; s0 < p.splits; s0 += AT_ONCE) {
-          uint64_t ml[AT_ONCE];
-          u32x4 o4[AT_ONCE];
+      floatx4 t[COLS];
 #pragma unroll
-          for (int u = 0; u < AT_ONCE; ++u) ml[u] = __hip_atomic_load(pairs + (long long)min(s0 + u, p.splits - 1) * p.m_pad + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      for (int c = 0; c < COLS; ++c) t[c] = floatx4{0.f, 0.f, 0.f, 0.f};
+      float tot = 0.f, top = -INFINITY;
+      for (int s0 = 0; s0 < p.splits; s0 += AT_ONCE) {
+        uint64_t ml[AT_ONCE];
+        u32x4 o4[AT_ONCE][COLS];
 #pragma unroll
-          for (int u = 0; u < AT_ONCE; ++u) o4[u] = __builtin_amdgcn_raw_buffer_load_b128(sums, ((min(s0 + u, p.splits - 1) * p.m_pad + r) * D + 4 * x) * 4, 0, dev::kDeviceScope);
-          float here = top;
-          float part_top[AT_ONCE], part_sum[AT_ONCE];
+        for (int u = 0; u < AT_ONCE; ++u) ml[u] = __hip_atomic_load(pairs + (long long)min(s0 + u, p.splits - 1) * p.m_pad + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-          for (int u = 0; u < AT_ONCE; ++u) {  // (a part without a key that the row sees, and what stands in for one past the last: no weight)
-            part_sum[u] = s0 + u < p.splits ? __uint_as_float((unsigned)(ml[u] >> 32)) : 0.f;
-            part_top[u] = part_sum[u] > 0.f ? __uint_as_float((unsigned)ml[u]) : -INFINITY;
-            here = fmaxf(here, part_top[u]);
-          }
-          if (here == -INFINITY) continue;
-          const float f = expf(top - here);  // (0 in front of the first)
-          tot *= f;
-          t *= f;
-          top = here;
+        for (int u = 0; u < AT_ONCE; ++u)
 #pragma unroll
-          for (int u = 0; u < AT_ONCE; ++u) {
-            const float w = expf(part_top[u] - here);
-            if (w != 0.f) {
-              tot = fmaf(part_sum[u], w, tot);
-              const floatx4 own = __builtin_bit_cast(floatx4, o4[u]);
+          for (int c = 0; c < COLS; ++c)
+            o4[u][c] = __builtin_amdgcn_raw_buffer_load_b128(sums, ((min(s0 + u, p.splits - 1) * p.m_pad + r) * D + 4 * min(x + LANES * c, d4 - 1)) * 4, 0, dev::kDeviceScope);
+        float here = top;
+        float part_top[AT_ONCE], part_sum[AT_ONCE];
 #pragma unroll
-              for (int e = 0; e < 4; ++e) t[e] = fmaf(own[e], w, t[e]);
+        for (int u = 0; u < AT_ONCE; ++u) {  // (a part without a key that the row sees, and what stands in for one past the last: no weight)
+          part_sum[u] = s0 + u < p.splits ? __uint_as_float((unsigned)(ml[u] >> 32)) : 0.f;
+          part_top[u] = part_sum[u] > 0.f ? __uint_as_float((unsigned)ml[u]) : -INFINITY;
+          here = fmaxf(here, part_top[u]);
+        }
+        if (here == -INFINITY) continue;
+        const float f = expf(top - here);  // (0 in front of the first)
+        tot *= f;
+#pragma unroll
+        for (int c = 0; c < COLS; ++c) t[c] *= f;
+        top = here;
+#pragma unroll
+        for (int u = 0; u < AT_ONCE; ++u) {
+          const float w = expf(part_top[u] - here);
+          if (w != 0.f) {
+            tot = fmaf(part_sum[u], w, tot);
+#pragma unroll
+            for (int c = 0; c < COLS; ++c) {
+              const floatx4 own = __builtin_bit_cast(floatx4, o4[u][c]);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) t[c][e] = fmaf(own[e], w, t[c][e]);
             }
           }
         }
-        const int n = div_mg(row, p.mg_g);
-        float* dst = p.out + b * p.o_sb + n * p.o_st + (long long)(kv * p.G + row - n * p.G) * p.o_sh;
-        const float inv = 1.f / tot;
-        *reinterpret_cast<floatx4*>(dst + 4 * x) = floatx4{t[0] * inv, t[1] * inv, t[2] * inv, t[3] * inv};
       }
+      const int n = div_mg(row, p.mg_g);
+      float* dst = p.out + b * p.o_sb + n * p.o_st + (long long)(kv * p.G + row - n * p.G) * p.o_sh;
+      const float inv = 1.f / tot;
+#pragma unroll
+      for (int c = 0; c < COLS; ++c)
+        if (x + LANES * c < d4) *reinterpret_cast<floatx4*>(dst + 4 * (x + LANES * c)) = floatx4{t[c][0] * inv, t[c][1] * inv, t[c][2] * inv, t[c][3] * inv};
     };
     if (p.splits <= 4) merge(std::integral_constant<int, 4>());
     else if (p.splits <= 8 || KJ > 5) merge(std::integral_constant<int, 8>());
@@ -422,12 +434,12 @@ hipError_t launch_kj(const FParams& fp, hipStream_t stream) {
 
 }  // namespace
 
-// Up to 16 parts (the last workgroup of a row tile reads them all: beyond that the merging launch, which spreads them over the
-// CUs), with a word for each row tile
+// Up to 16 parts, 8 for four waves (the last workgroup of a row tile reads them all: beyond that the merging launch, which spreads
+// them over the CUs; head_dim 256, 16 parts 25.4 us in the kernel, 24.2 with the launch, 64 6.5 % to the kernel), with a word for each row tile
 bool f32_merges(const jk_attn_desc& d, const AttnPlan& pl) {
-  constexpr int kMergedParts = 16;
+  const int most_parts = d.head_dim > 128 ? 8 : 16;
   const long long tiles = (long long)d.batch * d.n_kv_heads * ((pl.m_rows + 15) / 16);
-  return pl.parts > 1 && pl.parts <= kMergedParts && tiles <= kMaxFusedGroups * 16 && tuning().attn_fused != 0 &&
+  return pl.parts > 1 && pl.parts <= most_parts && tiles <= kMaxFusedGroups * 16 && tuning().attn_fused != 0 &&
          (long long)pl.parts * pl.m_pad * d.head_dim * 4 < (1LL << 31);
 }
 
