@@ -10,8 +10,8 @@
 //             above its parent, so ancestors come along), renumbered in increasing old index.
 //   gather    the kept nodes' draft distributions as the dense [batch][n_tree][vocab] array that
 //             jk_accept_path takes.
-// All choices are made by counting how many entries beat a given one (no sorting network, no
-// reduction rounds): at most a few hundred entries per sequence.
+// Choices are made by counting how many entries beat a given one (no sorting network, no reduction rounds), among a few hundred
+// entries per sequence: where more are cut, among those in the bin of scores that the last kept one lies in.
 #include <climits>
 
 #include "jk_internal.h"
