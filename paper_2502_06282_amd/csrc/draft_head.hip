@@ -79,6 +79,7 @@ __global__ __launch_bounds__(64) void head_inputs_kernel(MixParams p) {
 // A row (a vocabulary of 10^5 entries) is cut into parts of 256 threads x PT entries so that the work spreads over all
 // CUs; everything a thread needs is in its registers after one trip to memory:
 //   row_parts_kernel   per (row, part): maximum, sum of exp((x - max) / T), the part's k best
+//   row_whole_kernel   all of it, for short rows: one workgroup of 1024 threads per row
 //   row_finish_kernel  a workgroup per row first: the k best of the parts' candidates, their probabilities; then one per
 //                      (row, part): q = exp((x - max) / T) / Z (if asked for).  Each takes the row's maximum and
 //                      normaliser from the parts' pairs for itself.
@@ -133,9 +134,9 @@ __device__ __forceinline__ unsigned long long wave_max_key(unsigned long long k)
 constexpr int kCandCap = 512;
 
 // Place of each of the n listed keys (all different) by counting the larger ones: `put(rank, key)` for ranks below k.
-template <class F>
+template <int THREADS = kPartThreads, class F>
 __device__ __forceinline__ void rank_list(const unsigned long long* list, int n, int k, F put) {
-  for (int j = threadIdx.x; j < n; j += kPartThreads) {
+  for (int j = threadIdx.x; j < n; j += THREADS) {
     const unsigned long long mine = list[j];
     int rank = 0;
 #pragma unroll 8
@@ -155,20 +156,20 @@ __device__ __forceinline__ float wave_kth_largest(float v, int k) {
 
 // A part as its workgroup holds it: PT entries a thread, ids increasing with the index.  Four consecutive entries per
 // load where rows start at multiples of 16 bytes, single ones otherwise; past the end: -inf.
-template <int PT>
+template <int PT, int THREADS = kPartThreads>
 struct PartView {
   int lo, hi, tid;
   bool vec;
   __device__ __forceinline__ PartView(const SoftParams& p, int part, bool aligned)
       : lo(part * p.part_len), hi(min(p.vocab, part * p.part_len + p.part_len)), tid(threadIdx.x), vec(aligned && (p.vocab & 3) == 0) {}
   __device__ __forceinline__ int id(int i) const {
-    return lo + (vec ? 4 * (tid + kPartThreads * (i >> 2)) + (i & 3) : tid + kPartThreads * i);
+    return lo + (vec ? 4 * (tid + THREADS * (i >> 2)) + (i & 3) : tid + THREADS * i);
   }
   __device__ __forceinline__ void load(const float* x, float (&val)[PT]) const {
     if (vec) {
 #pragma unroll
       for (int u = 0; u < PT / 4; ++u) {
-        const int e = lo + 4 * (tid + kPartThreads * u);
+        const int e = lo + 4 * (tid + THREADS * u);
         floatx4 q = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
         if (e < hi) q = *reinterpret_cast<const floatx4*>(x + e);
 #pragma unroll
@@ -177,7 +178,7 @@ struct PartView {
     } else {
 #pragma unroll
       for (int i = 0; i < PT; ++i) {
-        const int e = lo + tid + kPartThreads * i;
+        const int e = lo + tid + THREADS * i;
         val[i] = e < hi ? x[e] : -INFINITY;
       }
     }
@@ -186,19 +187,40 @@ struct PartView {
     if (vec) {
 #pragma unroll
       for (int u = 0; u < PT / 4; ++u) {
-        const int e = lo + 4 * (tid + kPartThreads * u);
+        const int e = lo + 4 * (tid + THREADS * u);
         if (e < hi) *reinterpret_cast<floatx4*>(x + e) = floatx4{val[4 * u], val[4 * u + 1], val[4 * u + 2], val[4 * u + 3]};
       }
     } else {
 #pragma unroll
       for (int i = 0; i < PT; ++i) {
-        const int e = lo + tid + kPartThreads * i;
+        const int e = lo + tid + THREADS * i;
         if (e < hi) x[e] = val[i];
       }
     }
   }
 };
 __device__ __forceinline__ bool on16(const void* p) { return (reinterpret_cast<size_t>(p) & 15) == 0; }
+
+// A part's logits; the k parts' partial products come together here, in a fixed order
+template <int PT, class View>
+__device__ __forceinline__ void load_logits(const SoftParams& p, const View& view, int row, float (&val)[PT]) {
+  const long long at = (long long)row * p.vocab;
+  if (p.sums) {
+    const long long step = (long long)p.n_rows * p.vocab;
+    view.load(p.sums + at, val);
+    constexpr int kAhead = PT <= 4 ? 4 : (PT <= 8 ? 2 : 1);
+#pragma unroll kAhead
+    for (int z = 1; z < p.ksplit; ++z) {
+      float more[PT];
+      view.load(p.sums + at + z * step, more);
+#pragma unroll
+      for (int i = 0; i < PT; ++i) val[i] += more[i];
+    }
+    view.store(p.logits + at, val);
+  } else {
+    view.load(p.logits + at, val);
+  }
+}
 
 // Top-k of a part: the k-th largest of 64 disjoint groups' maxima is a lower bound of the part's
 // k-th largest value, so only entries at or above it can be among the k best; they are put on a
@@ -217,22 +239,7 @@ __global__ __launch_bounds__(kPartThreads) void row_parts_kernel(SoftParams p) {
   const int row = blockIdx.x / p.parts, part = blockIdx.x % p.parts;
   const PartView<PT> view(p, part, on16(p.logits) && on16(p.sums));
   float val[PT];
-  if (p.sums) {  // the k parts' partial products come together here, in a fixed order
-    const float* x = p.sums + (long long)row * V;
-    const long long step = (long long)p.n_rows * V;
-    view.load(x, val);
-    constexpr int kAhead = PT <= 4 ? 4 : (PT <= 8 ? 2 : 1);
-#pragma unroll kAhead
-    for (int z = 1; z < p.ksplit; ++z) {
-      float more[PT];
-      view.load(x + z * step, more);
-#pragma unroll
-      for (int i = 0; i < PT; ++i) val[i] += more[i];
-    }
-    view.store(p.logits + (long long)row * V, val);
-  } else {
-    view.load(p.logits + (long long)row * V, val);
-  }
+  load_logits<PT>(p, view, row, val);
   float tv = -INFINITY;
 #pragma unroll
   for (int i = 0; i < PT; ++i) tv = fmaxf(tv, val[i]);
@@ -384,6 +391,90 @@ __global__ __launch_bounds__(kPartThreads) void row_finish_kernel(SoftParams p) 
   view.store(p.probs + (long long)row * V, val);
 }
 
+// A short row whole: a workgroup of 16 waves has it in its registers, so that nothing is left for a second launch and no logit
+// is read twice.  The second launch was 2 - 4 us of 12 - 30 (calls of 1024 columns, us, before / now: 4 tokens and 4000 entries 14.9 /
+// 11.7, 8000 13.9 / 11.7; 64 tokens and 16 384 entries 30.5 / 26.5).
+constexpr int kRowThreads = 1024, kRowWaves = kRowThreads / 64, kRowPerThreadMax = 32;
+
+template <int PT>
+__global__ __launch_bounds__(kRowThreads) void row_whole_kernel(SoftParams p) {
+  __shared__ unsigned long long cand[kCandCap];
+  __shared__ unsigned long long sk[2][kRowWaves];
+  __shared__ float lane_max[kRowThreads];
+  __shared__ float sf[kRowWaves], ss[kRowWaves];
+  __shared__ float s_tau;
+  __shared__ int n_cand;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, V = p.vocab, K = p.k, row = blockIdx.x;
+  const PartView<PT, kRowThreads> view(p, 0, on16(p.logits) && on16(p.sums) && on16(p.probs));
+  float val[PT], e[PT];
+  load_logits<PT>(p, view, row, val);
+  float tv = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < PT; ++i) tv = fmaxf(tv, val[i]);
+  lane_max[tid] = tv;
+  {
+    const float m = dev::wave_max(tv);
+    if (lane == 0) sf[wave] = m;
+  }
+  if (tid == 0) n_cand = 0;
+  __syncthreads();
+  const float m = dev::wave_max(sf[lane & (kRowWaves - 1)]);
+  const float m_use = m > -INFINITY ? m : 0.f;
+  if (wave == 0) {  // the threshold: group g is threads g, g + 64, ...
+    float t = tv;
+#pragma unroll
+    for (int w = 1; w < kRowWaves; ++w) t = fmaxf(t, lane_max[lane + 64 * w]);
+    t = wave_kth_largest(t, K);
+    if (lane == 0) s_tau = t;
+  }
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < PT; ++i) s += e[i] = expf((val[i] - m_use) * p.inv_temp);
+  s = dev::wave_sum(s);
+  if (lane == 0) ss[wave] = s;
+  __syncthreads();
+  const float inv_z = (float)(1.0 / dev::wave_sum(lane < kRowWaves ? (double)ss[lane] : 0.0));
+  const float tau = s_tau;
+#pragma unroll
+  for (int i = 0; i < PT; ++i)
+    if (val[i] >= tau && val[i] > -INFINITY) {  // (-inf: past the end, or impossible)
+      const int at = atomicAdd(&n_cand, 1);
+      if (at < kCandCap) cand[at] = key_of(val[i], view.id(i));
+    }
+  if (p.probs) {
+#pragma unroll
+    for (int i = 0; i < PT; ++i) e[i] *= inv_z;
+    view.store(p.probs + (long long)row * V, e);
+  }
+  __syncthreads();
+  const int nc = n_cand;
+  auto put = [&](int rank, unsigned long long key) {  // (0: fewer than k candidates)
+    p.tk_ids[(long long)row * K + rank] = key ? key_id(key) : 0;
+    p.tk_probs[(long long)row * K + rank] = key ? expf((key_value(key) - m_use) * p.inv_temp) * inv_z : 0.f;
+  };
+  if (nc <= kCandCap) {
+    if (tid < K && tid >= nc) put(tid, 0ull);
+    rank_list<kRowThreads>(cand, nc, K, put);
+    return;
+  }
+  unsigned long long prev = ~0ull;  // very many ties: the largest key below the previous winner's per pass
+  for (int round = 0; round < K; ++round) {
+    unsigned long long best = 0ull;
+#pragma unroll
+    for (int i = 0; i < PT; ++i) {
+      const unsigned long long key = key_of(val[i], view.id(i));
+      if (val[i] >= tau && val[i] > -INFINITY && key < prev && key > best) best = key;
+    }
+    best = wave_max_key(best);
+    if (lane == 0) sk[round & 1][wave] = best;
+    __syncthreads();  // (one is enough: the buffers alternate)
+#pragma unroll
+    for (int w = 0; w < kRowWaves; ++w) best = sk[round & 1][w] > best ? sk[round & 1][w] : best;
+    if (tid == 0) put(round, best);
+    prev = best;
+  }
+}
+
 template <int PT>
 hipError_t launch_rows(const SoftParams& p, hipStream_t stream) {
   const unsigned parts = (unsigned)(p.n_rows * p.parts);
@@ -392,6 +483,11 @@ hipError_t launch_rows(const SoftParams& p, hipStream_t stream) {
   hipLaunchKernelGGL(row_finish_kernel<PT>, dim3(p.n_rows + (p.probs ? parts : 0u)), dim3(kPartThreads), 0, stream, p);
   return hipGetLastError();
 }
+
+// Rows of up to 16 entries a thread whole; longer ones only where there are so many that parts would not spread them over more CUs (what a
+// CU draws bounds the kernel then).  Calls of 1024 columns, us, in parts / whole: 1 token and 16 384 entries 16.3 / 16.0, 24 000 17.6 / 19.9, 32 000
+// 20.5 / 22.5; 10 tokens 17.8 / 17.1, 19.9 / 21.9, 22.3 / 23.5; 32 tokens 21.7 / 19.6, 23.9 / 23.1, 27.1 / 25.5.
+bool rows_whole(int n_rows, int vocab) { return vocab <= kRowThreads * (n_rows >= 64 ? kRowPerThreadMax : kRowPerThreadMax / 2); }
 
 // ------------------------------------------------------------------ router and experts (Eq. 2, 3, 5)
 constexpr int kMaxExperts = 64;
@@ -715,6 +811,19 @@ hipError_t launch_draft_heads(const DraftHeadsArgs& a, hipStream_t stream) {
   sp.keys = reinterpret_cast<unsigned long long*>(ws + rp.key_off);
   sp.n_rows = m; sp.vocab = a.vocab; sp.k = a.top_k; sp.parts = rp.parts; sp.part_len = rp.part_len;
   sp.inv_temp = 1.0f / a.temperature;
+  if (rows_whole(m, a.vocab)) {
+    sp.parts = 1;
+    sp.part_len = (a.vocab + 3) / 4 * 4;
+    auto whole = [&](auto per_thread) {
+      hipLaunchKernelGGL(row_whole_kernel<decltype(per_thread)::value>, dim3((unsigned)m), dim3(kRowThreads), 0, stream, sp);
+      return hipGetLastError();
+    };
+    const int need = (a.vocab + kRowThreads - 1) / kRowThreads;
+    if (need <= 4) return whole(std::integral_constant<int, 4>());
+    if (need <= 8) return whole(std::integral_constant<int, 8>());
+    if (need <= 16) return whole(std::integral_constant<int, 16>());
+    return whole(std::integral_constant<int, 32>());
+  }
   switch (rp.per_thread) {
     case 4: return launch_rows<4>(sp, stream);
     case 8: return launch_rows<8>(sp, stream);

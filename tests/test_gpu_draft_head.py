@@ -262,3 +262,18 @@ def test_equal_shares_of_the_vocabulary_are_bit_exact(rows, d, vocab):
 def test_either_kernel_takes_the_heads(forced, rows, d, vocab):
     tune("ring_gemm", forced)
     test_equal_shares_of_the_vocabulary_are_bit_exact(rows, d, vocab)
+
+
+@pytest.mark.parametrize("rows,d,vocab", [(1, 128, 5), (3, 128, 4096), (2, 128, 4097), (9, 4096, 300), (5, 128, 8192), (3, 128, 8193), (4, 1024, 12290),
+                                          (2, 128, 16383), (33, 128, 16384), (31, 128, 16385), (32, 128, 16385), (34, 128, 32768), (32, 128, 32769)])
+def test_short_rows_are_taken_whole(rows, d, vocab):
+    """The edges of what a thread holds, one entry more than a workgroup takes, and where longer rows change ways; then rows of
+    equal logits, all of them candidates (exact sums: 1 / vocab within the tolerance of every probability here)."""
+    top_k = min(vocab, 11)
+    x = _exact_inputs(rows, d, vocab, vocab)
+    _check(x, top_k=top_k, temperature=0.8, exact=True)
+    _check(draft_head_inputs(rows, d, vocab, seed=rows), top_k=top_k)
+    x["w_head"][:] = x["w_head"][0]
+    lg, q, tk, tp = _check(x, top_k=top_k, exact=True)
+    np.testing.assert_array_equal(tk, np.broadcast_to(np.arange(top_k), tk.shape))
+    np.testing.assert_allclose(q, 1.0 / vocab, rtol=3e-5)
