@@ -265,7 +265,8 @@ def test_either_kernel_takes_the_heads(forced, rows, d, vocab):
 
 
 @pytest.mark.parametrize("rows,d,vocab", [(1, 128, 5), (3, 128, 4096), (2, 128, 4097), (9, 4096, 300), (5, 128, 8192), (3, 128, 8193), (4, 1024, 12290),
-                                          (2, 128, 16383), (33, 128, 16384), (31, 128, 16385), (32, 128, 16385), (34, 128, 32768), (32, 128, 32769)])
+                                          (1, 128, 12288), (2, 128, 16383), (33, 128, 16384), (31, 128, 16385), (32, 128, 16385), (32, 128, 20481),
+                                          (33, 128, 24576), (32, 128, 28700), (34, 128, 32768), (32, 128, 32769)])
 def test_short_rows_are_taken_whole(rows, d, vocab):
     """The edges of what a thread holds, one entry more than a workgroup takes, and where longer rows change ways; then rows of
     equal logits, all of them candidates (exact sums: 1 / vocab within the tolerance of every probability here)."""
