@@ -180,19 +180,10 @@ struct GreedyParams {
   const int *tokens, *parent;
   const float* logits;
   uint64_t* part;   // [rows][chunks] (bits of the maximum, its lowest index)
-  unsigned* words;  // 508 lines of 16; see greedy_word
+  unsigned* words;  // the header's lines; see greedy_word (jk_words.h)
   int *out_path, *out_len, *out_bonus;
   unsigned* err;
 };
-
-// Words in which the workgroups of a call count themselves, zero between calls: number i's line and word in it, neighbours
-// 256 bytes apart.  (An atomic takes about 11 ns of the memory channel that has the word: with the words of four trees in
-// one channel, four trees of 61 rows in two parts each spent 5 us on them.)
-constexpr int kGreedyWords = kMaxFusedGroups * 12;  // (the first four words of a line: attention's, and one spare)
-__device__ __forceinline__ unsigned* greedy_word(unsigned* words, int i) {
-  const int line = i % kMaxFusedGroups, blocks = kMaxFusedGroups / 4;
-  return words + ((line % blocks) * 4 + line / blocks) * 16 + 4 + i / kMaxFusedGroups;
-}
 
 // The rows' maxima and the walk in one kernel: a workgroup per (chunk, row) leaves its (max, argmax) in memory and counts
 // itself; the one that finds itself the last of its tree walks it.  Nobody waits, so it does not matter how many run at
@@ -260,7 +251,7 @@ __global__ __launch_bounds__(THREADS) void greedy_kernel(GreedyParams p) {
     dev::store_through(p.part + (size_t)row * nch + blockIdx.x, dev::store_u32x2{__float_as_uint(bmax), (unsigned)bmin});
     dev::wait_vm<0>();
     auto arrive = [&](int i, int of) {
-      unsigned* word = greedy_word(p.words, i);
+      unsigned* word = p.words + greedy_word(i);
       if (of > 1 && __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != (unsigned)of - 1) return false;
       if (of > 1) __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       return true;

@@ -233,7 +233,7 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
         // tell the rest)
         if (direct && !forced_ok && n_tiles > 28) break;
         if (s > 1 && forced_s < 1 && (size_t)(wgs * s * q_rows) > most_rows) continue;  // (one split always fits)
-        if (wm == 8 && s > 1 && (wgs * s > kMaxWideMerged || (size_t)wgs * s * q_rows * d.head_dim * sizeof(float) > kFineBytes)) continue;
+        if (wm == 8 && s > 1 && (wgs * s > kMaxCounted || (size_t)wgs * s * q_rows * d.head_dim * sizeof(float) > kFineBytes)) continue;
         // rounds of the longest split: the 4x1 arrangement deals tiles (an odd last tile costs about
         // half a round), the 2x2 arrangement whole rounds
         double rounds;

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "jakiro_verify.h"
+#include "jk_words.h"
 
 namespace jk {
 // The dynamic-LDS limit of a kernel is an attribute it has per device: raised on a device's first launch of
@@ -52,15 +53,11 @@ struct AttnPlan {
 };
 
 // Every attention and acceptance workspace starts with a header: 256 bytes whose first word is the
-// sticky device error word (jk_last_device_error), then 64-byte lines of synchronisation words: in an
-// attention workspace one line per (unit, row tile) group for the merges inside the kernels, in an
-// acceptance workspace the counting words of the greedy launch (accept.hip).  The header
+// sticky device error word (jk_last_device_error), then 64-byte lines of synchronisation words for the merges inside the
+// attention kernels and the greedy launch (jk_words.h: whose is which).  The header
 // must be zero before the first use of a workspace and is kept consistent by the calls themselves.
 constexpr size_t kWsErrBytes = 256;
-constexpr int kMaxFusedGroups = 508;
 constexpr size_t kAttnHeaderBytes = kWsErrBytes + (size_t)kMaxFusedGroups * 64;  // 32 KiB
-constexpr int kWideWords = 13;       // of each line: words of the merge in tva_wide.hip, one per workgroup
-constexpr int kMaxWideMerged = kMaxFusedGroups * kWideWords;
 static_assert(kAttnHeaderBytes == JK_WORKSPACE_HEADER_BYTES, "public constant");
 
 // Device error bits (public names in jakiro_verify.h)

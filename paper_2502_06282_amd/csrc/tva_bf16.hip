@@ -423,11 +423,6 @@ __device__ __forceinline__ void l2_atomic_add_noret(unsigned* p, unsigned x) {
   asm volatile("global_atomic_add %0, %1, off" ::"v"(p), "v"(x) : "memory");
 }
 
-// Group word: bits 0-7 arrivals of this call, bits 8-15 workgroups that gave up waiting, bits
-// 16-31 call number (epoch).  The last arriver adds 2^16 - S - (give-ups << 8): count and
-// give-ups return to zero and the epoch moves on, which is what the waiting workgroups look for.
-constexpr unsigned kSyncCountMask = 0xffu, kSyncGaveUpOne = 0x100u, kSyncEpochOne = 0x10000u;
-
 // Merge of rows [slice * R, (slice + 1) * R) of the group's row tile over all S splits, written to
 // the output.  16 bytes (8 columns) of a row per thread; the arithmetic per element is that of the
 // stand-alone merge kernel (splits in chunks of 8, running maximum), so both give the same bits.
@@ -1234,7 +1229,7 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
       __syncthreads();
       JK_TS(8);
       if (tid_e == 0) {
-        unsigned* word = late->sync + (size_t)(unit_id * late->n_qtiles + qtile) * 16;
+        unsigned* word = late->sync + group_word(unit_id * late->n_qtiles + qtile);
         const unsigned S = (unsigned)splits;
         const unsigned old = l2_atomic_add(word, 1u);
         const unsigned epoch = old >> 16;

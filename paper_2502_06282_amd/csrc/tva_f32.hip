@@ -32,9 +32,6 @@ namespace {
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
-// The word of row tile `i` among all: neighbours 64 bytes apart (an atomic takes 11 ns of the memory channel that has its word)
-__device__ __forceinline__ int word_of(int i) { return i % kMaxFusedGroups * 16 + i / kMaxFusedGroups; }
-
 struct FParams {
   const float *q, *kc, *vc, *kt, *vt;
   const int32_t *parent, *prefix_len;
@@ -42,7 +39,7 @@ struct FParams {
   float2* part_ml;
   float* out;     // undivided key range: the result
   unsigned* err;  // the workspace's sticky device error word
-  unsigned* words;  // divided range, merged by the last of a row tile's workgroups: a word each (see word_of); or null
+  unsigned* words;  // divided range, merged by the last of a row tile's workgroups: a word each (f32_word); or null
   int B, T, Hkv, G, M, m_pad, D, max_prefix, splits;
   long long q_sb, q_st, q_sh, kc_sb, kc_sl, kc_sh, kt_sb, kt_st, kt_sh, o_sb, o_st, o_sh;
   unsigned long long mg_g, mg_hkv;  // floor(2^32 / d) + 1: n / d == (n * mg) >> 32 while n * d < 2^32
@@ -343,7 +340,7 @@ __global__ __launch_bounds__(64 * WAVES, KJ <= 8 ? (WAVES + 3) / 4 : 1) void tva
     dev::wait_vm<0>();
     __syncthreads();
     if (tid == 0) {
-      unsigned* word = p.words + word_of((int)(blockIdx.z * gridDim.y + blockIdx.y));
+      unsigned* word = p.words + f32_word(blockIdx.z * gridDim.y + blockIdx.y);
       const bool last = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)p.splits - 1u;
       if (last) __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       last_s = last;
@@ -439,7 +436,7 @@ hipError_t launch_kj(const FParams& fp, hipStream_t stream) {
 bool f32_merges(const jk_attn_desc& d, const AttnPlan& pl) {
   const int most_parts = d.head_dim > 128 ? 8 : 16;
   const long long tiles = (long long)d.batch * d.n_kv_heads * ((pl.m_rows + 15) / 16);
-  return pl.parts > 1 && pl.parts <= most_parts && tiles <= kMaxFusedGroups * 16 && tuning().attn_fused != 0 &&
+  return pl.parts > 1 && pl.parts <= most_parts && tiles <= kMaxCounted && tuning().attn_fused != 0 &&
          (long long)pl.parts * pl.m_pad * d.head_dim * 4 < (1LL << 31);
 }
 

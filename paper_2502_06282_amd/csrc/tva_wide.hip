@@ -594,10 +594,7 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
   constexpr int QUADS = kBlocks * DB * 4;  // float4 per lane
   constexpr int kDeviceScope = 16;         // (the sc1 bit of a buffer load)
   auto place_of = [&](int piece) { return (place0 + piece * place_step) * p.n_qtiles + qtile; };
-  auto word_of = [&](int m) {  // (the first three of a line belong to tva_bf16.hip)
-    const int place = place_of(m);
-    return p.sync + place / kWideWords * 16 + 3 + place % kWideWords;
-  };
+  auto word_of = [&](int m) { return p.sync + wide_word(place_of(m)); };
   int* answer_s = repeat_s + 1;  // thread 0's answer; two in turn, so that one barrier does
   bool is_first = false;         // (thread 0's)
   auto answered = [&]() {

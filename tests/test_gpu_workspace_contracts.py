@@ -74,6 +74,67 @@ def test_attention_calls_of_any_shape_take_turns_on_one_workspace():
             assert jk.last_device_error(shared) == 0, case[0]
 
 
+def test_calls_that_merge_in_the_kernel_take_turns_on_one_workspace():
+    """Every kind of call whose workgroups meet in the header's words - bf16 groups, bf16 pieces two and two, fp32 parts (4, 2,
+    12 and 16 of them, one call with more than two words' worth of row tiles to a line), greedy acceptance -, in both orders, with waits that
+    expire at once in the third pass: each result equals the one on a fresh workspace bit for bit, the words that are counted
+    in from zero are zero behind each call, and the error word says nothing but that waits expired."""
+    from workloads import accept_inputs
+    dev = torch.device("cuda")
+    # (name, batch, Hq, Hkv, D, T, L, dtype, forced waves, forced splits, forced merge)
+    cases = [("sixteen_splits", 1, 32, 8, 128, 60, 4096, "bf16", 0, 0, -1), ("f32_4", 1, 4, 4, 128, 20, 190, "f32", 0, 0, -1),
+             ("five_splits", 2, 8, 2, 64, 33, 700, "bf16", 0, 5, 1), ("f32_16", 2, 2, 2, 64, 20, 1480, "f32", 0, 0, -1),
+             ("pieces", 2, 32, 4, 128, 100, 1500, "bf16", 8, 6, -1), ("f32_many_tiles", 12, 32, 32, 16, 40, 1100, "f32", 0, 0, -1),
+             ("many_groups", 16, 32, 16, 64, 40, 200, "bf16", 0, 2, 1), ("f32_12", 2, 2, 2, 64, 20, 1180, "f32", 0, 0, -1)]
+    prepared = []
+    need = jk.accept_path_workspace(4, 60, 3000, jk.JK_GREEDY)
+    for i, (name, B, Hq, Hkv, D, T, L, dtype, waves, splits, fused) in enumerate(cases):
+        cfg = CONFIGS["c3_llama3_8b"].with_(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, n_tree=T, prefix_len=L)
+        x = attention_inputs(cfg, seed=80 + i, scale_mult=np.sqrt(float(D)))
+        d = {k: _dev(v, torch.float32 if dtype == "f32" else BF) for k, v in x.items()}
+        lens = torch.tensor([max(0, L - 37 * b) for b in range(B)], dtype=torch.int32, device=dev)
+        knobs = {"attn_wm": waves, "attn_wn": 1 if waves else 0, "attn_splits": splits, "attn_fused": fused}
+        for k, v in knobs.items():
+            tune(k, v)
+        need = max(need, jk.tree_verify_attention_workspace(d["q"], d["k_cache"], d["k_tree"], L))
+        prepared.append((name, d, torch.from_numpy(tree_for_config(cfg, seed=80 + i)).to(dev), lens, L, knobs))
+    acfg = CONFIGS["c3_llama3_8b"].with_(vocab=3000, batch=4, n_tree=60)
+    apar = tree_for_config(acfg)
+    a = accept_inputs(acfg, apar, seed=3)
+    greedy = [torch.from_numpy(np.ascontiguousarray(v)).to(dev) for v in (a["tokens"], apar, a["logits"])]
+    prepared.insert(3, ("greedy", greedy, None, None, None, {}))
+    prepared.append(prepared[3])
+
+    def run(case, ws, spin_limit):
+        name, d, parent, lens, L, knobs = case
+        tune("spin_limit", spin_limit)
+        if not knobs:
+            outs = list(jk.accept_path(*d, jk.JK_GREEDY, workspace=ws))
+        else:
+            for k, v in knobs.items():
+                tune(k, v)
+            out = torch.full_like(d["q"], float("nan"))
+            jk.tree_verify_attention(d["q"], d["k_cache"], d["v_cache"], d["k_tree"], d["v_tree"], parent, lens,
+                                     max_prefix_len=L, out=out, workspace=ws)
+            outs = [out]
+        torch.cuda.synchronize()
+        return outs
+
+    want = {case[0]: run(case, torch.zeros(need, dtype=torch.uint8, device=dev), -1) for case in prepared}
+    shared = torch.zeros(need, dtype=torch.uint8, device=dev)
+    words = shared[256:jk.JK_WORKSPACE_HEADER_BYTES].view(torch.int32).view(-1, 16)
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    for rnd, (order, spin_limit) in enumerate([(prepared, -1), (prepared[::-1], -1), (prepared, 0), (prepared[::-1], -1)]):
+        for case in order:
+            shared[jk.JK_WORKSPACE_HEADER_BYTES:] = torch.randint(0, 256, (need - jk.JK_WORKSPACE_HEADER_BYTES,), dtype=torch.uint8,
+                                                                  device=dev, generator=gen)
+            for got, ref in zip(run(case, shared, spin_limit), want[case[0]]):
+                assert torch.isfinite(ref.float()).all(), case[0]
+                assert torch.equal(got.view(torch.uint8), ref.view(torch.uint8)), (rnd, case[0])
+            assert not words[:, 3:].any(), (rnd, case[0])
+            assert jk.last_device_error(shared) & ~(jk.JK_DEVERR_MERGE_WAIT if rnd >= 2 else 0) == 0, (rnd, case[0])
+
+
 def test_draft_side_workspaces_may_hold_anything():
     """jk_draft_heads and jk_moe_experts with workspaces full of 0xFF bytes (NaN patterns) against workspaces of
     zeros: the same outputs bit for bit, for two shapes in turn on the same buffers."""
