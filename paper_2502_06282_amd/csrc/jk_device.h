@@ -64,6 +64,11 @@ __device__ __forceinline__ void store_through(void* dst, unsigned int v) {
   asm volatile("global_store_dword %0, %1, off sc0 sc1" ::"v"(dst), "v"(v) : "memory");
 }
 
+// Where a merge of partial results takes a part's weights from: its maximum of the row, and -inf, no weight, of a part without a
+// key that the row sees (sum 0).  A sum that is no number (a score was none, or +inf) makes the merged row none, as undivided:
+// from +inf the other parts weigh nothing and this one NaN, whatever maximum it found beside it.
+__device__ __forceinline__ float part_top(float top, float sum) { return sum > 0.f ? top : (sum == 0.f ? -INFINITY : INFINITY); }
+
 constexpr int kDeviceScope = 16;  // the sc1 bit of a buffer load: past the L2 of the XCD
 
 // Of two workgroups the second to come, in every thread: its own results and, with loads of the device's scope, those that

@@ -538,7 +538,7 @@ __device__ __forceinline__ void merge_rows(const MergeArgs& p, const MergeThread
   // ---- (A): pair (row, split) of this thread
   const int wsh = sh < 2 ? 2 : sh;  // (a row's weights start at a multiple of four floats, for the 16-byte reads below)
   {
-    if (!(ml.y > 0.f)) ml = make_float2(-INFINITY, 0.f);  // an empty split carries no weight
+    ml.x = dev::part_top(ml.x, ml.y);
     const float mx = group_max(ml.x, sh);
     const float w = fast_exp2(ml.x - ((mx == -INFINITY) ? 0.f : mx));  // exp2(-inf) = 0
     const float l = group_sum(ml.y * w, sh);

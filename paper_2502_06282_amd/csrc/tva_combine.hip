@@ -79,7 +79,8 @@ __global__ __launch_bounds__(256) void tva_combine_kernel(CParams p) {
     if (r2 < n_rows && sp < p.splits) {
       const long long unit2 = r2 / p.M;
       const float2 ml = p.part_ml[(unit2 * p.splits + sp) * p.m_pad + (r2 % p.M)];
-      if (ml.y > 0.f) { mv = ml.x; l = ml.y; }  // an empty split carries no weight
+      mv = dev::part_top(ml.x, ml.y);
+      l = ml.y;
     }
     float mx = mv;
     // the (at most 64) real splits of a row sit in one wave: slots are 64-aligned
@@ -184,7 +185,7 @@ __global__ __launch_bounds__(256) void tva_combine_bf16_kernel(CParams p) {
     for (int u = 0; u < 8; ++u) {
       const bool ok = s0 + u < S;
       ml[u] = ok ? pml[(long long)(s0 + u) * p.m_pad] : make_float2(-INFINITY, 0.f);
-      if (!(ml[u].y > 0.f)) ml[u] = make_float2(-INFINITY, 0.f);  // an empty split carries no weight
+      ml[u].x = dev::part_top(ml[u].x, ml[u].y);
       raw[u] = Raw{};
       if (ok) {
         const Part* src = po + (long long)(s0 + u) * po_step;

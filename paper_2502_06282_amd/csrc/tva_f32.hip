@@ -377,7 +377,7 @@ __global__ __launch_bounds__(64 * WAVES, KJ <= 8 ? (WAVES + 3) / 4 : 1) void tva
 #pragma unroll
         for (int u = 0; u < AT_ONCE; ++u) {  // (a part without a key that the row sees, and what stands in for one past the last: no weight)
           part_sum[u] = s0 + u < p.splits ? __uint_as_float((unsigned)(ml[u] >> 32)) : 0.f;
-          part_top[u] = part_sum[u] > 0.f ? __uint_as_float((unsigned)ml[u]) : -INFINITY;
+          part_top[u] = dev::part_top(__uint_as_float((unsigned)ml[u]), part_sum[u]);
           here = fmaxf(here, part_top[u]);
         }
         if (here == -INFINITY) continue;
