@@ -549,8 +549,8 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
   if (!(st.l[0][0] < 1.8446744e19f) || !(st.l[1][0] < 1.8446744e19f)) *repeat_s = 1;
   __syncthreads();  // everybody is done with the ring
   if (__builtin_amdgcn_readfirstlane(*repeat_s) != 0) {
-    // ---- A weight beyond 2^64 (a score 44 nats above the row's first): the split once more, with a reference that
-    // moves and accumulators that follow it.  Rare, and in no hurry: one tile after the other.
+    // ---- A weight beyond 2^64 (a score 44 nats above the row's first), or a sum that is no number: the split once
+    // more, with a reference that moves and accumulators that follow it.  Rare, and in no hurry: one tile after the other.
     clear();
     for (int i = 0; i < n; ++i) {
       transfer(i);
@@ -572,10 +572,13 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
         st.mu[r] = mu;
 #pragma unroll
         for (int e = 0; e < 16; ++e) st.p[r][e / 8][e % 8] = (__bf16)fast_exp2(fmaf(st.s[r][e], scale_log2, -mu));
+        // (added up without the matrix, whose zeros would carry a weight that is no number into the row 16 further)
+        float sum = 0.f;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) st.l[r][k] *= alpha;
+        for (int e = 0; e < 16; ++e) sum += (float)st.p[r][e / 8][e % 8];
+        sum += __uint_as_float(dev::other32(__float_as_uint(sum), lane & 32));
 #pragma unroll
-        for (int j = 0; j < 2; ++j) st.l[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(st.adds, st.p[r][j], st.l[r], 0, 0, 0);
+        for (int k = 0; k < 4; ++k) st.l[r][k] = fmaf(st.l[r][k], alpha, sum);
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll

@@ -12,7 +12,7 @@ from gpu_util import gpu_attention, oracle_attention, tune
 pytestmark = pytest.mark.gpu
 
 # (dtype, heads, KV heads, head_dim, nodes, prefix, knobs): fp32 whole, 8 parts, 16, 24 (a second launch); bf16 whole, two key
-# columns, groups of 2 - 24 splits, a second launch, 16 rows a workgroup
+# columns, groups of 2 - 24 splits, pieces, 16 rows a workgroup
 PATHS = {
     "f32_whole": ("f32", 4, 2, 64, 20, 200, {}), "f32_8": ("f32", 4, 2, 64, 20, 480, {}), "f32_8_launch": ("f32", 4, 2, 64, 20, 480, {"attn_fused": 0}),
     "f32_16": ("f32", 4, 4, 128, 20, 1400, {}), "f32_8_of_192": ("f32", 2, 2, 192, 20, 300, {}), "f32_24_of_192": ("f32", 2, 2, 192, 20, 2600, {}),
@@ -24,6 +24,7 @@ PATHS = {
     "groups_of_24": ("bf16", 8, 2, 128, 60, 3300, {"attn_wm": 4, "attn_wn": 1, "attn_splits": 24, "attn_fused": 1}),
     "launch": ("bf16", 8, 2, 128, 60, 1500, {"attn_wm": 4, "attn_wn": 1, "attn_splits": 6, "attn_fused": 0}),
     "launch_fine": ("bf16", 8, 2, 64, 60, 500, {"attn_wm": 2, "attn_wn": 2, "attn_splits": 2, "attn_fused": 0}),
+    "pieces": ("bf16", 8, 2, 128, 60, 1500, {"attn_wm": 8, "attn_wn": 1, "attn_splits": 3}),
     "direct": ("bf16", 8, 2, 128, 60, 500, {"attn_wm": 1, "attn_wn": 4}),
 }
 
