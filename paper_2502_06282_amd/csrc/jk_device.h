@@ -65,9 +65,9 @@ __device__ __forceinline__ void store_through(void* dst, unsigned int v) {
 }
 
 // Where a merge of partial results takes a part's weights from: its maximum of the row, and -inf, no weight, of a part without a
-// key that the row sees (sum 0).  A sum that is no number (a score was none, or +inf) makes the merged row none, as undivided:
-// from +inf the other parts weigh nothing and this one NaN, whatever maximum it found beside it.
-__device__ __forceinline__ float part_top(float top, float sum) { return sum > 0.f ? top : (sum == 0.f ? -INFINITY : INFINITY); }
+// key that the row sees (sum 0).  A sum that is no number (a score was none, or +inf) makes the merged row none, as undivided, if
+// it enters the merged sum whatever its weight: zero times NaN.
+__device__ __forceinline__ float part_top(float top, float sum) { return sum == 0.f ? -INFINITY : top; }
 
 constexpr int kDeviceScope = 16;  // the sc1 bit of a buffer load: past the L2 of the XCD
 

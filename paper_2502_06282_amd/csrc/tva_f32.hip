@@ -380,17 +380,16 @@ __global__ __launch_bounds__(64 * WAVES, KJ <= 8 ? (WAVES + 3) / 4 : 1) void tva
           part_top[u] = dev::part_top(__uint_as_float((unsigned)ml[u]), part_sum[u]);
           here = fmaxf(here, part_top[u]);
         }
-        if (here == -INFINITY) continue;
-        const float f = expf(top - here);  // (0 in front of the first)
+        const float base = here == -INFINITY ? 0.f : here, f = expf(top - base);  // (0 in front of the first)
         tot *= f;
 #pragma unroll
         for (int c = 0; c < COLS; ++c) t[c] *= f;
         top = here;
 #pragma unroll
         for (int u = 0; u < AT_ONCE; ++u) {
-          const float w = expf(part_top[u] - here);
+          const float w = expf(part_top[u] - base);
+          tot = fmaf(part_sum[u], w, tot);
           if (w != 0.f) {
-            tot = fmaf(part_sum[u], w, tot);
 #pragma unroll
             for (int c = 0; c < COLS; ++c) {
               const floatx4 own = __builtin_bit_cast(floatx4, o4[u][c]);
