@@ -24,6 +24,7 @@
 
 #include "jk_ancestors.h"
 #include "jk_device.h"
+#include "jk_divide.h"
 #include "jk_wave.h"
 
 namespace jk {
@@ -40,13 +41,13 @@ struct FParams {
   float* out;     // undivided key range: the result
   unsigned* err;  // the workspace's sticky device error word
   unsigned* words;  // divided range, merged by the last of a row tile's workgroups: a word each (f32_word); or null
-  int B, T, Hkv, G, M, m_pad, D, max_prefix, splits;
+  int B, T, Hkv, G, M, m_pad, D, max_prefix, splits, over_hkv;
   long long q_sb, q_st, q_sh, kc_sb, kc_sl, kc_sh, kt_sb, kt_st, kt_sh, o_sb, o_st, o_sh;
-  unsigned long long mg_g, mg_hkv;  // floor(2^32 / d) + 1: n / d == (n * mg) >> 32 while n * d < 2^32
+  unsigned long long mg_g, mg_hkv;  // for n / G and n / Hkv, with over_g and over_hkv (jk_divide.h)
+  int over_g;
   float scale;
 };
 static_assert(sizeof(FParams) > 192 && sizeof(FParams) <= 256, "four lines of kernel arguments");
-__device__ __forceinline__ int div_mg(int n, unsigned long long mg) { return (int)(((unsigned long long)(unsigned)n * mg) >> 32); }
 
 // KJ: 16-column chunks of a head (rounded up); WAVES: by how many registers that leaves.  WHOLE: an undivided key range of a
 // small head, whose first loads do not wait for the prefix length
@@ -69,7 +70,7 @@ __global__ __launch_bounds__(64 * WAVES, KJ <= 8 ? (WAVES + 3) / 4 : 1) void tva
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int c = lane & 15, g = lane >> 4;
   const int split = blockIdx.x, row0 = blockIdx.y * 16;
-  const int b = div_mg(blockIdx.z, p.mg_hkv), kv = blockIdx.z - b * p.Hkv;
+  const int b = quotient((int)blockIdx.z, p.mg_hkv, p.over_hkv), kv = blockIdx.z - b * p.Hkv;
   const int D = p.D;
   const float* kc = p.kc + b * p.kc_sb + (long long)kv * p.kc_sh;
   const float* vc = p.vc + b * p.kc_sb + (long long)kv * p.kc_sh;
@@ -80,7 +81,7 @@ __global__ __launch_bounds__(64 * WAVES, KJ <= 8 ? (WAVES + 3) / 4 : 1) void tva
   asm volatile("" : "+v"(lane_zero));  // (a vector load: a scalar one would be waited for with the arguments)
   const int L_raw = __hip_atomic_load(p.prefix_len + b + lane_zero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const int pa0 = p.parent[(long long)b * p.T + min(lane, p.T - 1)], pa1 = p.parent[(long long)b * p.T + min(lane + 64, p.T - 1)];
-  const int m = min(row0 + c, p.M - 1), node = div_mg(m, p.mg_g);  // this lane's query row (rows past the end repeat the last one)
+  const int m = min(row0 + c, p.M - 1), node = quotient(m, p.mg_g, p.over_g);  // this lane's query row (rows past the end repeat the last one)
   floatx4 q[KJ], k[KJ], v[DB][4];  // the row, and a block's K and V
   // column 16 j + 4 g of a row; columns past the end: the row's first ones, against zeros of q
   auto col = [&](int j) { return 16 * j + 4 * g < D ? 16 * j + 4 * g : 0; };
@@ -314,7 +315,7 @@ __global__ __launch_bounds__(64 * WAVES, KJ <= 8 ? (WAVES + 3) / 4 : 1) void tva
       tot += shares[w][r].x;
     }
     if (p.splits == 1) {
-      const int n = div_mg(row, p.mg_g);
+      const int n = quotient(row, p.mg_g, p.over_g);
       float* dst = p.out + b * p.o_sb + n * p.o_st + (long long)(kv * p.G + row - n * p.G) * p.o_sh;
       const float inv = 1.f / tot;  // (tot > 0: every row sees at least its own tree key)
       *reinterpret_cast<floatx4*>(dst + 4 * x) = floatx4{t[0] * inv, t[1] * inv, t[2] * inv, t[3] * inv};
@@ -399,7 +400,7 @@ __global__ __launch_bounds__(64 * WAVES, KJ <= 8 ? (WAVES + 3) / 4 : 1) void tva
           }
         }
       }
-      const int n = div_mg(row, p.mg_g);
+      const int n = quotient(row, p.mg_g, p.over_g);
       float* dst = p.out + b * p.o_sb + n * p.o_st + (long long)(kv * p.G + row - n * p.G) * p.o_sh;
       const float inv = 1.f / tot;
 #pragma unroll
@@ -461,8 +462,9 @@ hipError_t launch_tva_f32(const AttnArgs& a, const AttnPlan& pl, hipStream_t str
   fp.kt_sb = d.kt_stride_b; fp.kt_st = d.kt_stride_t; fp.kt_sh = d.kt_stride_h;
   fp.out = static_cast<float*>(a.out);
   fp.o_sb = d.o_stride_b; fp.o_st = d.o_stride_t; fp.o_sh = d.o_stride_h;
-  auto magic = [](int v) { return (1ull << 32) / (unsigned)v + 1; };
-  fp.mg_g = magic(fp.G); fp.mg_hkv = magic(fp.Hkv);
+  const Divisor by_g = divisor(fp.M, fp.G), by_hkv = divisor((long long)fp.B * fp.Hkv, fp.Hkv);
+  fp.mg_g = by_g.mg; fp.over_g = by_g.over;
+  fp.mg_hkv = by_hkv.mg; fp.over_hkv = by_hkv.over;
   fp.scale = a.scale_log2;  // for this path the host passes the plain softmax scale here
   switch ((d.head_dim + 15) / 16) {
     case 1: case 2: case 3:
