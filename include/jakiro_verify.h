@@ -127,7 +127,8 @@ size_t jk_tree_verify_attention_workspace(const jk_attn_desc* desc, int32_t max_
  * head_dim <= 256 and a multiple of 4 and max_prefix_len + n_tree <= 65536
  * (fp32 MFMA path); 1 <= n_tree <= JK_MAX_TREE;
  * n_q_heads a multiple of n_kv_heads; JK_BF16: kc_stride_l and kt_stride_t at
- * most 2^24 elements (JK_ERR_UNSUPPORTED beyond).  JK_BF16: value rows of tree nodes that a
+ * most 2^24 elements, and n_tree * (n_q_heads / n_kv_heads)^2 and batch * n_kv_heads^2 below 2^32
+ * (JK_ERR_UNSUPPORTED beyond, but where the divisor happens to divide 2^32 nearly enough).  JK_BF16: value rows of tree nodes that a
  * query cannot see must be finite (they are multiplied by an exact zero; JK_F32 leaves a value
  * with a weight of zero out, whatever it is); their key rows, and anything in the cache beyond
  * prefix_len, are never used.

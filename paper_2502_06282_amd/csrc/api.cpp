@@ -8,6 +8,7 @@
 #include <initializer_list>
 #include <random>
 
+#include "jk_divide.h"
 #include "jk_internal.h"
 
 namespace jk {
@@ -532,6 +533,10 @@ static jk_status attention_common(const jk_attn_desc* desc, const jk_paged_kv* p
   if (d.q_stride_t < d.head_dim && d.n_tree > 1) return JK_ERR_INVALID_ARG;
   // the bf16 kernel addresses a tile's rows with 32-bit byte offsets from the tile's first row
   if (d.dtype == JK_BF16 && (d.kc_stride_l > (1 << 24) || d.kt_stride_t > (1 << 24))) return JK_ERR_UNSUPPORTED;
+  // and finds a row's node and a workgroup's sequence by multiplications of 32 bits (beyond: the wrong ones)
+  const int group = d.n_q_heads / d.n_kv_heads;
+  if (d.dtype == JK_BF16 && !(exact_in_32((long long)d.n_tree * group, group) && exact_in_32((long long)d.batch * d.n_kv_heads, d.n_kv_heads)))
+    return JK_ERR_UNSUPPORTED;
   const void* ptrs[] = {q, k_cache, v_cache, k_tree, v_tree, out};
   for (const void* p : ptrs)
     if (reinterpret_cast<uintptr_t>(p) % (align * es)) return JK_ERR_INVALID_ARG;

@@ -70,6 +70,22 @@ def test_null_arguments_are_rejected_before_any_launch(lib):
     assert st == 1
 
 
+@pytest.mark.parametrize("B,T,Hq,Hkv,ok", [(1, 128, 5792, 1, True), (1, 128, 8191, 1, False), (1, 1, 8191, 1, True), (1, 64, 2 * 8191, 2, True),
+                                           (1, 128, 2 * 8191, 2, False), (1, 1, 131071, 131071, False), (2, 1, 40001, 40001, True)])
+def test_bf16_calls_whose_rows_32_bits_cannot_tell_apart_are_refused(lib, B, T, Hq, Hkv, ok):
+    """Before the workspace is looked at (there is none); of those that are taken, the last row's node and the last
+    workgroup's sequence are what division says.  fp32 calls divide with as many bits as they need."""
+    d = _desc(B, T, Hq, Hkv, 64, 16)
+    p = ctypes.c_void_p(4096)
+    call = lambda: lib.jk_tree_verify_attention(ctypes.byref(d), p, p, p, p, p, p, p, 16, p, None, 0, None)  # noqa: E731
+    assert call() == (4 if ok else 3)
+    for n, by in ((T * (Hq // Hkv), Hq // Hkv), (B * Hkv, Hkv)):
+        if ok:
+            assert ((n - 1) * (2 ** 32 // by + 1)) >> 32 == (n - 1) // by
+    d.dtype = 1
+    assert call() == 4
+
+
 def test_draft_layer_workspace_queries_and_argument_checks_are_host_only(lib):
     n = lib.jk_draft_heads_workspace(80, 4096, 128256)
     assert n > 0 and n % 256 == 0
