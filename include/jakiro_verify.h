@@ -546,7 +546,7 @@ jk_status jk_init(void* hip_stream);
  * plans are functions of the descriptors and the device; these knobs force parts of them.
  * Process-wide, not thread-safe against concurrent calls.  Names: "attn_wm", "attn_wn" (wave
  * arrangement of the bf16 attention kernel: 4x1 or 2x2, 8x1 for four waves of 64 rows each, or 1x4
- * for 16 rows that four waves share the keys of, undivided; 0 = automatic), "attn_splits" (key splits, 0 = automatic), "attn_fused" (-1 automatic, 0 never merge
+ * for 16 rows that four waves share the keys of, undivided whatever the splits; 0 = automatic), "attn_splits" (key splits, 0 = automatic), "attn_fused" (-1 automatic, 0 never merge
  * inside the kernel - which keeps the 8x1 arrangement out of automatic plans, its splits merge in
  * no other way -, 1 whenever the grid allows it), "attn_deep" (-1 automatic, 0 never use the deeper
  * K/V ring of the 2x2 arrangement, 1 whenever one workgroup per CU is planned), "accept_single" (1: one-workgroup sampling walk), "spin_limit" (polls of

@@ -229,7 +229,8 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
         const long long s_min = (n_tiles + kMaxTilesPerSplit - 1) / kMaxTilesPerSplit;
         if (s < s_min) s = s_min;
         if (s > kMaxSplits) continue;
-        if (direct && s > 1) break;
+        if (direct && sc > 1) break;
+        if (direct) s = 1;  // (it has no splits, and its page ids are in registers: whatever is forced)
         // (beyond that the splits of the others are the better one in most calls, 1.15 - 1.7 times, and the estimate too coarse to
         // tell the rest)
         if (direct && !forced_ok && n_tiles > 28) break;

@@ -87,7 +87,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void tva_direct_kernel(const KParam
   // by.  A wave without keys asks for one address in all lanes.
   const int tc = some ? c : 0, tg = some ? g : 0;
   const int pa_lo = p.parent[(long long)b * T + min(lane, T - 1)], pa_hi = p.parent[(long long)b * T + min(lane + 64, T - 1)];
-  // page ids of 64 blocks of this wave, a lane each; ids outside the pool are clamped (and reported where they count)
+  // page ids of 64 blocks of this wave, a lane each; ids outside the pool are clamped (and reported where they count).  (A planned
+  // call has at most 28 blocks for all waves; only where this kernel is forced are there more than one lane each.)
   int ids = 0;
   auto ask_pages = [&](int first) {
     const int at = div_mg(max(first + kWaves * lane - n_tblk, 0), p.mg_tpp);

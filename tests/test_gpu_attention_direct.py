@@ -160,3 +160,27 @@ def test_which_calls_the_plan_gives_it():
             assert plan(B, T, G, Hkv, D, L) == [1, 4, 1, -(-T * G // 16), 1, 0]
         for B, T, G, Hkv, L in ((1, 60, 4, 8, 4096), (16, 60, 4, 8, 512), (1, 2, 1, 8, 1000)):
             assert plan(B, T, G, Hkv, D, L)[0] != 1
+
+
+@pytest.mark.parametrize("splits", [0, 2, 64])
+@pytest.mark.parametrize("L", [0, 300, 40000, 2000000])
+def test_the_forced_kernel_takes_every_range(splits, L):
+    """Host only: it has no splits, whatever number is forced and however long the range that a plan can have."""
+    lib = binding.lib()
+    d = binding.AttnDesc(2, 20, 8, 2, 128, 20 * 1024, 1024, 128, 256, 256, 128, 20 * 256, 256, 128, 20 * 1024, 1024, 128, 0.0, 0)
+    out = (ctypes.c_int32 * 6)()
+    try:
+        for name, v in ((b"attn_wm", 1), (b"attn_wn", 4), (b"attn_splits", splits)):
+            lib.jk_set_tuning(name, v)
+        assert lib.jk_tree_verify_attention_plan(ctypes.byref(d), L, out) == 0 and list(out) == [1, 4, 1, 5, 1, 0]
+        assert lib.jk_tree_verify_attention_workspace(ctypes.byref(d), L) >= jk.JK_WORKSPACE_HEADER_BYTES
+    finally:
+        for name in (b"attn_wm", b"attn_wn", b"attn_splits"):
+            lib.jk_set_tuning(name, 0)
+
+
+@gpu
+def test_the_forced_kernel_beyond_what_others_take_undivided():
+    """More keys than a workgroup of the others has page ids for (1024 tiles), two splits asked for."""
+    tune("attn_splits", 2)
+    _check(_cfg(5, 2, 1, 64, 33000), [33000], seed=7)
