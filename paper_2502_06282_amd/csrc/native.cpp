@@ -133,20 +133,6 @@ void dims(const at::Tensor& t, int n, const char* what) {
 at::Tensor empty(at::IntArrayRef size, at::ScalarType type, const at::Tensor& like) {
   return at::Tensor(at::detail::empty_cuda(size, type, like.device(), std::nullopt));
 }
-// `n` int32 tensors of one size in one allocation, 256 bytes or more between their beginnings: each allocation and its return cost
-// the host 0.4 us.  (Four of them, and the workspace that most linear layers do not use: 8 drawn tree and small layer calls, which
-// their enqueueing binds, 1.12 times as fast.)
-void empty_together(at::IntArrayRef size, int n, const at::Tensor& like, at::Tensor* out) {
-  int64_t count = 1;
-  for (int64_t s : size) count *= s;
-  const int64_t step = (count + 63) / 64 * 64;
-  const at::Tensor all = empty({n * step}, at::kInt, like);
-  for (int i = 0; i < n; ++i) {
-    out[i] = at::detail::make_tensor<c10::TensorImpl>(c10::Storage(all.storage()), all.key_set(), all.dtype());
-    out[i].unsafeGetTensorImpl()->set_sizes_contiguous(size);
-    out[i].unsafeGetTensorImpl()->set_storage_offset(i * step);
-  }
-}
 PyObject* wrap(at::Tensor t) {
   PyObject* o = THPVariable_Wrap(std::move(t));
   if (!o) throw PyFailure{};
@@ -774,7 +760,7 @@ PyObject* tree_finalize(Args& a) {  // state, n_keep, stream -> (tokens, parent,
   at::Tensor o[4], n;
   check(unlocked([&] {
           n = empty({t.batch}, at::kInt, like);
-          empty_together({t.batch, keep > 0 ? keep : 0}, 4, like, o);
+          for (at::Tensor& x : o) x = empty({t.batch, keep > 0 ? keep : 0}, at::kInt, like);
           auto out = [&](int i) { return static_cast<int32_t*>(ptr(o[i])); };
           return jk_tree_finalize(&t.s, t.batch, keep, out(0), out(1), out(2), out(3), static_cast<int32_t*>(ptr(n)), stream);
         }),

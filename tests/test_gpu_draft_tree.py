@@ -114,7 +114,7 @@ def test_cut_by_bins_of_scores(n, n_keep, scores):
 
 @pytest.mark.parametrize("n_keep", [1, 3, 64, 65])
 def test_cut_results_are_tensors_of_their_own(n_keep):
-    """They share an allocation: contiguous, apart from each other, beginning at multiples of 256 bytes."""
+    """Contiguous, apart from each other, beginning at multiples of 256 bytes."""
     state = jk.TreeState(2, 256)
     state.n_nodes.fill_(70)
     out = jk.tree_finalize(state, n_keep)[:4]
@@ -122,6 +122,22 @@ def test_cut_results_are_tensors_of_their_own(n_keep):
         assert x.shape == (2, n_keep) and x.dtype == torch.int32 and x.is_contiguous() and x.data_ptr() % 256 == 0
         x.fill_(i)
     assert all((x == i).all() for i, x in enumerate(out))
+
+
+def test_cut_results_may_be_resized():
+    """Each result has a storage of its own size: a larger one is a new allocation, and the others keep what they hold."""
+    state = jk.TreeState(3, 128)
+    rng = np.random.default_rng(2)
+    tok, p = _cands(rng, 3, 5)
+    jk.tree_grow(state, None, torch.from_numpy(tok).cuda(), torch.from_numpy(p).cuda(), 5, 0)
+    outs = jk.tree_finalize(state, 8)
+    before = [o.clone() for o in outs]
+    for i, o in enumerate(outs):
+        assert o.untyped_storage().nbytes() == o.nbytes and o.storage_offset() == 0
+        o.resize_(4096).fill_(-7)
+        torch.cuda.synchronize()
+        for j in range(i + 1, len(outs)):
+            assert torch.equal(outs[j], before[j])
 
 
 def test_gather_draft_probs():
