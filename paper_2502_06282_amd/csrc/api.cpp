@@ -377,14 +377,12 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
     // A fifth part, where no more fit, is one more to merge.  In 4 / 5 parts a range, one range of 503 keys, heads of 128, 12.5 / 11.6, of 440
     // and 192 17.4 / 18.2, of 840 24.3 / 22.6; two of 770 and 64 10.2 / 11.3, and 128 15.3 / 15.8, and 192 24.2 / 22.4; three of 843 and 64
     // 12.0 / 11.5, and 192 25.6 / 23.1; of 977 12.1 / 12.6 and 25.9 / 26.3.
-    // Two short ranges in six parts each, 12 to merge, not 16: 2 sequences, 8 row tiles, 16 / 12 parts together, of 64, 1220 keys 10.1 /
-    // 9.8, 1420 10.2 / 10.3, 1670 10.2 / 10.7; of 80, 1040 11.1 / 10.6; of 128, 1220 13.2 / 13.1, 1420 13.4 / 13.9.
     const long long wgs = units * ((pl->m_rows + 15) / 16) * s;
     pl->parts = pl->splits;
     if (f32_in_parts(keys, d.head_dim)) {
       auto turns = [&](int sub) { return ((keys / s + sub - 1) / sub - 1) / 64; };  // (of four blocks of 16 keys)
       const bool small_heads = d.head_dim <= 128, fifth = small_heads && s <= 2 ? s == 1 : turns(5) < turns(4);
-      const int most = keys < 220 ? 4 : keys < 300 || (small_heads && s == 2 && keys < 1300) ? 6 : 8;
+      const int most = keys < 220 ? 4 : keys < 300 ? 6 : 8;
       for (int sub = most; sub > 1; --sub)
         if (wgs * sub <= device_cu_count() && s * sub <= kMaxSplits && (sub != 5 || fifth)) {
           pl->parts = pl->splits * sub;

@@ -85,7 +85,7 @@ def test_calls_that_merge_in_the_kernel_take_turns_on_one_workspace():
     cases = [("sixteen_splits", 1, 32, 8, 128, 60, 4096, "bf16", 0, 0, -1), ("f32_4", 1, 4, 4, 128, 20, 190, "f32", 0, 0, -1),
              ("five_splits", 2, 8, 2, 64, 33, 700, "bf16", 0, 5, 1), ("f32_16", 2, 2, 2, 64, 20, 1480, "f32", 0, 0, -1),
              ("pieces", 2, 32, 4, 128, 100, 1500, "bf16", 8, 6, -1), ("f32_many_tiles", 12, 32, 32, 16, 40, 1100, "f32", 0, 0, -1),
-             ("many_groups", 16, 32, 16, 64, 40, 200, "bf16", 0, 2, 1), ("f32_12", 2, 2, 2, 64, 20, 1180, "f32", 0, 0, -1)]
+             ("many_groups", 16, 32, 16, 64, 40, 200, "bf16", 0, 2, 1), ("f32_12", 1, 5, 5, 64, 64, 1180, "f32", 0, 0, -1)]
     prepared = []
     need = jk.accept_path_workspace(4, 60, 3000, jk.JK_GREEDY)
     for i, (name, B, Hq, Hkv, D, T, L, dtype, waves, splits, fused) in enumerate(cases):
