@@ -374,14 +374,16 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
     // 23.6 / 16.9 / 14.8 / 14.5.  Where three parts fill the CUs (80 row tiles), whole / in 3: of 64, 170 keys 6.6 / 7.6, 340 9.5 / 8.2; of 80,
     // 170 8.6 / 8.9, 340 12.8 / 10.1.  Four parts would pay a little earlier (of 64, 250 keys 7.9 / 7.4; of 128, 150 9.9 / 9.2), but the bytes
     // that a call asks for stay as they are, so that a workspace allocated by them still serves it.
-    // A fifth part, where no more fit, is one more to merge.  In 4 / 5 parts a range, one range of 503 keys, heads of 128, 12.5 / 11.6, of 440
-    // and 192 17.4 / 18.2, of 840 24.3 / 22.6; two of 770 and 64 10.2 / 11.3, and 128 15.3 / 15.8, and 192 24.2 / 22.4; three of 843 and 64
-    // 12.0 / 11.5, and 192 25.6 / 23.1; of 977 12.1 / 12.6 and 25.9 / 26.3.
+    // A fifth part, where no more fit, is one more to merge, and pays where it saves a turn of the waves, but for two ranges of heads up
+    // to 128.  In 4 / 5 parts a range, one range of 423 keys, heads of 80, 8.6 / 9.8, of 990 and 128 15.2 / 16.3, of 547 and 32 9.0 / 8.6, of 749 and 128 14.4 / 13.9 (not taken); two
+    // of 1316 and 80 10.8 / 12.5, of 1153 and 256 20.6 / 19.8; three of 2726 and 32 11.7 / 10.8, of 2117 and 256 22.0 / 23.4.
+    // Over the 260 drawn calls of profiles/f32_parts_times.csv (90 - 4000 keys, head_dim 16 - 256, every number of parts that fits) the
+    // one taken is 1.7 % slower than the best (6.6 % at the 90th percentile; 21 % at the 99th, calls in front of the lines above).
     const long long wgs = units * ((pl->m_rows + 15) / 16) * s;
     pl->parts = pl->splits;
     if (f32_in_parts(keys, d.head_dim)) {
       auto turns = [&](int sub) { return ((keys / s + sub - 1) / sub - 1) / 64; };  // (of four blocks of 16 keys)
-      const bool small_heads = d.head_dim <= 128, fifth = small_heads && s <= 2 ? s == 1 : turns(5) < turns(4);
+      const bool fifth = !(d.head_dim <= 128 && s == 2) && turns(5) < turns(4);
       const int most = keys < 220 ? 4 : keys < 300 ? 6 : 8;
       for (int sub = most; sub > 1; --sub)
         if (wgs * sub <= device_cu_count() && s * sub <= kMaxSplits && (sub != 5 || fifth)) {
