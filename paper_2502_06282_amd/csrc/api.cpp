@@ -93,10 +93,10 @@ bool shape_supported(const jk_attn_desc& d) {
 }  // namespace
 
 // Constants of the attention plan's time estimate, fitted together to timed plans of drawn shapes (those timings were not
-// kept).  What they are worth is measured by profiles/attention_plan_times.py: over the 1000 shapes and 11146 plans of
+// kept).  What they are worth is measured by profiles/attention_plan_times.py: over the 1000 shapes and 11711 plans of
 // profiles/attention_plan_times.csv (batch 1 - 32, 1 - 128 tree nodes, 2 - 40 KV heads, head_dim 64/128, prefixes up to
-// 32k) the plan the estimate takes is 1.2 % slower than the best one timed (geometric mean; 5 % at the 90th percentile,
-// 16 % at the 99th); runs of one plan differ by about 1 %.  The fit is of the whole estimate: single constants are near,
+// 32k) the plan the estimate takes is 1.3 % slower than the best one timed (geometric mean; 5 % at the 90th percentile,
+// 17 % at the 99th); runs of one plan differ by about 1 %.  The fit is of the whole estimate: single constants are near,
 // not at, what a part takes when it is timed alone.
 struct PlanModel {
   double round_4x1 = 1.13, round_4x1_d64 = 0.84;  // us per round (a pair of 32-key tiles) of a 4x1 workgroup alone on its CU
@@ -116,8 +116,8 @@ struct PlanModel {
   // 256 rows per workgroup (tva_wide.hip), one of them per CU: us per tile without a mask, per other tile (the first, tree
   // and ragged ones, those that four does not divide), per turn of workgroups, per call, per level of the pairwise merge
   // and per MB that changes hands there.  (Searched together like the others; a tile takes 0.55 us timed alone.  The plan takes
-  // this kernel for 72 of the 1000 shapes above, as many as it is the fastest for; over those the best plan of the other
-  // kernels is 1.13 times as slow in the geometric mean, 0.86 to 1.38.)
+  // this kernel for 72 of the 1000 shapes above, and it is the fastest for 67; over the 72 the best plan of the other
+  // kernels is 1.11 times as slow in the geometric mean, 0.88 to 1.31.)
   double wide_tile = 0.44, wide_tile_d64 = 0.385, wide_slow = 1.06, wide_slow_d64 = 0.70;
   double wide_hot = 0.31, wide_hot_tiles = 500.0;  // the clock falls under the matrix units' load: the tiles of a long call
                                 // take up to this much longer
@@ -126,9 +126,12 @@ struct PlanModel {
   // 16 rows per workgroup and K, V in registers (tva_direct.hip): us of a call outside its blocks, per turn of four blocks of 32
   // keys, per workgroup of a CU beyond the first, for trees of more than 64 nodes (their ancestors); bytes per us that a CU
   // draws of K and V, and all CUs together.  Fitted to the times of 320 drawn calls of up to 1300 keys of prefix and 2000
-  // workgroups (5.0 % rms).  The others' estimates of such short calls are 1.2 times what they take (2x2 waves, geometric mean):
-  // direct_level puts this one beside them.  (At 1.3 the 320 calls take 0.840 of what they take without this kernel, the best choice
-  // would take 0.834, and three are slower than without it by more than 3 %, 7 % at most; at 1.2 ten are, at 1.4 they take 0.849.)
+  // workgroups (5.0 % rms; those timings were not kept).  The others' estimates of such short calls are 1.2 times what they take (2x2
+  // waves, geometric mean): direct_level puts this one beside them.  (At 1.3 the 320 calls take 0.840 of what they take without
+  // this kernel, the best choice would take 0.834, and three are slower than without it by more than 3 %, 7 % at most; at 1.2 ten
+  // are, at 1.4 they take 0.849.)  The plan takes it for 273 of the 1000 shapes above, and it is the fastest for 291; over the 273 the
+  // best plan of the other kernels is 1.31 times as slow, 0.92 to 1.62 (two are slower with it by more than 3 %: 38 and 145 MB
+  // of K and V, 8 and 6 %).
   double direct_call = 3.31, direct_call_d64 = 2.97, direct_round = 0.66, direct_round_d64 = 0.63, direct_next = 0.81,
          direct_deep_tree = 0.65, direct_draw = 6.05e4, direct_stream = 3.40e7, direct_level = 1.3;
 };
@@ -231,8 +234,9 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
         if (s > kMaxSplits) continue;
         if (direct && sc > 1) break;
         if (direct) s = 1;  // (it has no splits, and its page ids are in registers: whatever is forced)
-        // (beyond that the splits of the others are the better one in most calls, 1.15 - 1.7 times, and the estimate too coarse to
-        // tell the rest)
+        // (beyond that the splits of the others are the better one in most calls, and the estimate too coarse to tell the rest: of the
+        // 139 shapes of profiles/attention_plan_times.csv with 29 to 56 tiles six are more than 3 % faster with this kernel, 14 % at most,
+        // and all together take 1.6 times as long)
         if (direct && !forced_ok && n_tiles > 28) break;
         if (s > 1 && forced_s < 1 && (size_t)(wgs * s * q_rows) > most_rows) continue;  // (one split always fits)
         if (wm == 8 && s > 1 && (wgs * s > kMaxCounted || (size_t)wgs * s * q_rows * d.head_dim * sizeof(float) > kFineBytes)) continue;
@@ -375,8 +379,8 @@ bool compute_attn_plan(const jk_attn_desc& d, int max_prefix_len, bool fused_all
     // 170 8.6 / 8.9, 340 12.8 / 10.1.  Four parts would pay a little earlier (of 64, 250 keys 7.9 / 7.4; of 128, 150 9.9 / 9.2), but the bytes
     // that a call asks for stay as they are, so that a workspace allocated by them still serves it.
     // A fifth part, where no more fit, is one more to merge, and pays where it saves a turn of the waves, but for two ranges of heads up
-    // to 128.  In 4 / 5 parts a range, one range of 423 keys, heads of 80, 8.6 / 9.8, of 990 and 128 15.2 / 16.3, of 547 and 32 9.0 / 8.6, of 749 and 128 14.4 / 13.9 (not taken); two
-    // of 1316 and 80 10.8 / 12.5, of 1153 and 256 20.6 / 19.8; three of 2726 and 32 11.7 / 10.8, of 2117 and 256 22.0 / 23.4.
+    // to 128.  In 4 / 5 parts a range, one range of 423 keys, heads of 80, 8.6 / 9.8, of 990 and 128 15.2 / 16.3, of 547 and 32 9.0 / 8.6, of 749
+    // and 128 14.4 / 13.9 (not taken); two of 1316 and 80 10.8 / 12.5, of 1153 and 256 20.6 / 19.8; three of 2726 and 32 11.7 / 10.8, of 2117 and 256 22.0 / 23.4.
     // Over the 260 drawn calls of profiles/f32_parts_times.csv (90 - 4000 keys, head_dim 16 - 256, every number of parts that fits) the
     // one taken is 1.7 % slower than the best (6.6 % at the 90th percentile; 21 % at the 99th, calls in front of the lines above).
     const long long wgs = units * ((pl->m_rows + 15) / 16) * s;

@@ -40,12 +40,15 @@ def candidates(shape, chosen, rng):
     b, t, hq, hkv, _, length = shape
     rows, top = t * hq // hkv, max(1, min(64, (-(-length // 32) - (-t // 32)) // 4))
     out = []
+    tiles = -(-length // 32) - (-t // 32)
     for wm, wn in ((2, 2), (4, 1), (8, 1)):
         if wm == 8 and rows <= 96 or wm == 4 and rows <= 64:
             continue
         wgs = b * hkv * -(-rows // (32 * wm))
         fit = {max(1, round(x * 256 / wgs)) for x in (0.5, 1, 1.5, 2, 3, 4)}  # a workgroup for that many times the CUs
         out += [(wm, wn, s) for s in sorted(fit.union(SPLITS)) if s <= top and wgs * s <= 3072 and (s == 1 or wgs * s >= 64 or s >= top // 2)]
+    if tiles <= 56:  # (undivided; the plan takes it up to 28)
+        out.append((1, 4, 1))
     keep = sorted({chosen, *(c for c in out if c[2] <= 2)})
     rest = [c for c in out if c not in keep]
     rng.shuffle(rest)
