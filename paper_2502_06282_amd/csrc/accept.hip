@@ -251,7 +251,7 @@ __global__ __launch_bounds__(THREADS) void greedy_kernel(GreedyParams p) {
     dev::store_through(p.part + (size_t)row * nch + blockIdx.x, dev::store_u32x2{__float_as_uint(bmax), (unsigned)bmin});
     dev::wait_vm<0>();
     auto arrive = [&](int i, int of) {
-      unsigned* word = p.words + greedy_word(i);
+      unsigned* word = greedy_word(p.words, i);
       if (of > 1 && __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != (unsigned)of - 1) return false;
       if (of > 1) __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       return true;

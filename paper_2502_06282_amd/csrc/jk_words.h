@@ -34,9 +34,9 @@ constexpr unsigned f32_word(unsigned tile) {
 
 // Counters of the greedy launch: number i's line and word in it, neighbours 256 bytes apart.  (With the words of four trees in
 // one channel, four trees of 61 rows in two parts each spent 5 us on them.)
-constexpr int greedy_word(int i) {
+constexpr unsigned* greedy_word(unsigned* words, int i) {
   const int line = i % kMaxFusedGroups, blocks = kMaxFusedGroups / 4;
-  return ((line % blocks) * 4 + line / blocks) * kLineWords + 4 + i / kMaxFusedGroups;
+  return words + ((line % blocks) * 4 + line / blocks) * kLineWords + 4 + i / kMaxFusedGroups;
 }
 
 }  // namespace jk

@@ -204,8 +204,8 @@ void greedy(std::mt19937& rng, int trees, int rows, int parts) {
   std::vector<int> walked(trees, 0);
   Work work(trees * rows * parts, [&](Turns& t, int me) {
     const int row = me / parts, b = row / rows;
-    if (parts > 1 && !last_of(t, me, header[greedy_word(trees + row)], parts)) return;
-    if (rows > 1 && !last_of(t, me, header[greedy_word(b)], rows)) return;
+    if (parts > 1 && !last_of(t, me, *greedy_word(header.data(), trees + row), parts)) return;
+    if (rows > 1 && !last_of(t, me, *greedy_word(header.data(), b), rows)) return;
     ++walked[b];
   });
   Turns(rng, work);
@@ -244,7 +244,7 @@ void owns(const char* who, int n, int lo, F word) {
 int main() {
   owns("wide_word", kMaxCounted, kFirstCounting, [](int i) { return wide_word(i); });
   owns("f32_word", kMaxCounted, kFirstCounting, [](int i) { return f32_word((unsigned)i); });
-  owns("greedy_word", kGreedyWords, kFirstCounting, [](int i) { return greedy_word(i); });
+  owns("greedy_word", kGreedyWords, kFirstCounting, [](int i) { return greedy_word(header.data(), i) - header.data(); });
   for (int g = 0; g < kMaxFusedGroups; ++g) expect(group_word(g) == (unsigned long)g * kLineWords, "group_word");
   for (unsigned seed = 0; seed < 40 && bad == 0; ++seed) {
     std::mt19937 rng(seed);

@@ -31,10 +31,11 @@ def test_lengths_below_the_bound(D, bound, T):
     assert np.abs(got - ref).max() <= 1e-5 * max(1.0, np.abs(ref).max())
 
 
-# keys of a bound whose ranges are 2, 3, 4, 6, 8, 10 and 16 parts, and more than the kernel merges (24, and 16 of 192: a launch of its
-# own), at lengths that leave parts empty
+# keys of a bound whose ranges are 2, 3, 4, 5, 6, 8, 14 and 16 parts, and more than the kernel merges (24, and 10 and 16 of 192: a launch of
+# its own), at lengths that leave parts empty
 @pytest.mark.parametrize("B,H,D,T,bound", [(8, 8, 64, 20, 500), (5, 8, 128, 20, 300), (1, 8, 80, 17, 190), (1, 4, 256, 40, 100), (2, 4, 192, 20, 280), (1, 5, 132, 33, 400), (1, 3, 192, 20, 1800), (2, 3, 96, 33, 250),
-                                           (2, 2, 16, 64, 450), (1, 6, 40, 50, 1900), (3, 2, 128, 1, 1500), (1, 3, 192, 20, 2600)])
+                                           (2, 2, 16, 64, 450), (1, 6, 40, 50, 1900), (3, 2, 128, 1, 1500), (1, 3, 192, 20, 2600), (4, 3, 64, 64, 480),
+                                           (1, 17, 64, 10, 1500), (1, 24, 192, 10, 1090)])
 def test_parts_merged_by_the_last_workgroup(B, H, D, T, bound):
     """The same as merging them in a second launch, captured and replayed in a workspace whose partial results are
     noise each time; its words are zero again behind every call."""
