@@ -79,7 +79,7 @@ struct Weights {
     k0 = 0;
     k1 = p.k;
     if (p.ksplit > 1) {
-      const unsigned units = (unsigned)p.k / 128u, parts = (unsigned)p.ksplit;  // (at most 8192 and 128: the products fit)
+      const unsigned units = (unsigned)p.k / 128u, parts = (unsigned)p.ksplit;  // (at most 8192 and 64: the products fit)
       k0 = (int)(blockIdx.z * units / parts) * 128;
       k1 = (int)((blockIdx.z + 1u) * units / parts) * 128;
     }
