@@ -474,8 +474,9 @@ struct MergeThread {
   unsigned raw_off;   // byte offset of this thread's 4 columns in split 0's partial (rows of the first pass)
   unsigned ml_off;    // byte offset of this thread's (row, split) pair
   unsigned dst_off;   // element offset of this thread's 4 output columns in `out` (first pass)
+  unsigned unit_end;  // rows of partials up to the end of the unit's
   int r_b, row_lo, row_hi;
-  bool live_a, live_b;
+  bool live_a;
 };
 
 template <int D, int THREADS, int QROWS, bool FINE>
@@ -488,13 +489,15 @@ __device__ __forceinline__ MergeThread merge_prepare(const MergeArgs& p, int uni
   t.row_hi = min(QROWS, t.row_lo + R);
   const int chunk = tid % CPR;
   t.r_b = t.row_lo + tid / CPR;
-  const unsigned unit_row0 = (unsigned)(unit_id * S) * (unsigned)p.m_pad + (unsigned)tile_row0;  // (the host keeps the
-  t.live_b = t.r_b < t.row_hi && tile_row0 + t.r_b < p.M;                                        // partials below 2^31 bytes)
+  const unsigned unit_row0 = (unsigned)(unit_id * S) * (unsigned)p.m_pad + (unsigned)tile_row0;  // (the host keeps
+  t.unit_end = (unsigned)((unit_id + 1) * S) * (unsigned)p.m_pad;                                // the partials below 2^31 bytes)
   t.raw_off = ((unit_row0 + (unsigned)t.r_b) * (unsigned)D + (unsigned)chunk * 4u) * (FINE ? 4u : 2u);
   const int ra = t.row_lo + (tid >> sh), sa = tid & ((1 << sh) - 1);
   t.live_a = ra < t.row_hi && tile_row0 + ra < p.M && sa < S;
-  t.ml_off = (unit_row0 + (unsigned)ra + (unsigned)sa * (unsigned)p.m_pad) * 8u;
-  const int m = tile_row0 + (t.live_b ? t.r_b : 0);
+  // (a lane without a pair asks for one of its own group's: a line of another group's, read before that one is complete, would
+  // stay in this CU's vector cache for the workgroup that merges it)
+  t.ml_off = (t.live_a ? unit_row0 + (unsigned)ra + (unsigned)sa * (unsigned)p.m_pad : unit_row0) * 8u;
+  const int m = min(tile_row0 + t.r_b, p.M - 1);
   const int node = div_mg(m, p.mg_g);
   t.dst_off = (unsigned)(b * p.o_sb + node * p.o_st + (long long)(kv * p.G + (m - node * p.G)) * p.o_sh) + chunk * 4;
   return t;
@@ -508,39 +511,53 @@ __device__ __forceinline__ void merge_rows(const MergeArgs& p, const MergeThread
                                            int tid, float* wbuf) {
   constexpr int CPR = D / 4, RPP = THREADS / CPR, SP = SH < 4 ? 1 << SH : 16, ROWS = 16 / SP;
   const int S = p.splits;
-  const unsigned char* part = reinterpret_cast<const unsigned char*>(p.part_o);
   typedef std::conditional_t<FINE, u32x4, u32x2> Raw;
   constexpr unsigned ROW_BYTES = D * (FINE ? 4 : 2);
   const unsigned po_step = (unsigned)p.m_pad * ROW_BYTES;  // from one split's partial to the next
   const int rows_end = min(t.row_hi, p.M - tile_row0);
+  // (The unit's partials end where the buffer does: what a padded split or a row past the slice would read is zeros, without a
+  // condition.  With a branch for each of the sixteen loads, and the code in front of them that the compiler made of those,
+  // a layer of an 8B model, 4096 keys in sixteen splits, had its rows' weights 1.7 us after the group was complete, and has
+  // them after 0.9 like this; the step of 32 such layers takes 456 us instead of 469.)
+  const auto part = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.part_o), 0, t.unit_end * ROW_BYTES, 0x00020000);
+  constexpr unsigned kNowhere = 0x80000000u;  // (merged here are at most two workgroups a CU: tens of megabytes)
   Raw raw[16];
-  // (Only branches that a wave takes as one: a row past the slice next to one inside it takes that one's data, and is not
-  // stored.  A lane mask for each of the sixteen loads would not fit the scalar registers.)
   auto fetch = [&](int r0, int s0) {
-    const int wave_r0 = __builtin_amdgcn_readfirstlane(r0);
 #pragma unroll
     for (int k = 0; k < ROWS; ++k) {
-      const bool any = wave_r0 + k * RPP < rows_end;
-      unsigned off = t.raw_off + (unsigned)s0 * po_step + (unsigned)(min(r0 + k * RPP, rows_end - 1) - t.r_b) * ROW_BYTES;  // (32-bit offsets from one base)
+      const int r = r0 + k * RPP;
+      unsigned off = r < rows_end ? t.raw_off + (unsigned)s0 * po_step + (unsigned)(r - t.r_b) * ROW_BYTES : kNowhere;
+      asm volatile("" : "+v"(off));  // (one addition a load: left alone, the compiler makes sixteen induction variables of the loop
+                                     // over left slices, ninety instructions in front of it)
 #pragma unroll
       for (int u = 0; u < SP; ++u) {
-        raw[k * SP + u] = Raw(0u);
-        if (any && s0 + u < S) raw[k * SP + u] = *reinterpret_cast<const Raw*>(part + off);
+        if constexpr (FINE) raw[k * SP + u] = __builtin_amdgcn_raw_buffer_load_b128(part, (int)off, 0, 0);
+        else raw[k * SP + u] = __builtin_amdgcn_raw_buffer_load_b64(part, (int)off, 0, 0);
         off += po_step;
       }
     }
   };
   // ---- the (max, sum) pair of this thread's (row, split) first, then (B), first half
-  float2 ml = make_float2(-INFINITY, 0.f);
-  if (t.live_a) ml = *reinterpret_cast<const float2*>(reinterpret_cast<const unsigned char*>(p.part_ml) + t.ml_off);
-  fetch(t.r_b, 0);
+  // (The pair is loaded by hand and waited for by number, with the sixteen loads behind it on their way: left alone, the
+  // compiler waits in front of them, or for all of them.)
+  u32x2 pair;
+  asm volatile("global_load_dwordx2 %0, %1, %2" : "=v"(pair) : "v"(t.ml_off), "s"(p.part_ml) : "memory");
+  const bool rows_here = __builtin_amdgcn_readfirstlane(t.r_b) < rows_end;  // (of this wave: its first row is its least)
+  if (rows_here) {
+    fetch(t.r_b, 0);
+    dev::wait_vm<16>();
+  } else {
+    dev::wait_vm<0>();
+  }
+  asm volatile("" : "+v"(pair));
+  const float2 ml = t.live_a ? make_float2(__uint_as_float(pair[0]), __uint_as_float(pair[1])) : make_float2(-INFINITY, 0.f);
   JK_TS(11);
   // ---- (A): pair (row, split) of this thread
   const int wsh = sh < 2 ? 2 : sh;  // (a row's weights start at a multiple of four floats, for the 16-byte reads below)
   {
-    ml.x = dev::part_top(ml.x, ml.y);
-    const float mx = group_max(ml.x, sh);
-    const float w = fast_exp2(ml.x - ((mx == -INFINITY) ? 0.f : mx));  // exp2(-inf) = 0
+    const float top = dev::part_top(ml.x, ml.y);
+    const float mx = group_max(top, sh);
+    const float w = fast_exp2(top - ((mx == -INFINITY) ? 0.f : mx));  // exp2(-inf) = 0
     const float l = group_sum(ml.y * w, sh);
     // (l > 0 for a live row: it sees at least its own tree key; dead rows are not stored)
     wbuf[((tid >> sh) << wsh) | (tid & ((1 << sh) - 1))] = w / l;
@@ -552,6 +569,7 @@ __device__ __forceinline__ void merge_rows(const MergeArgs& p, const MergeThread
   JK_TS(13);
 #endif
   // ---- (B), second half
+  if (!rows_here) return;
   for (int r0 = t.r_b; r0 < t.row_hi; r0 += ROWS * RPP) {
     float acc[ROWS][4];
 #pragma unroll
@@ -569,13 +587,12 @@ __device__ __forceinline__ void merge_rows(const MergeArgs& p, const MergeThread
 #pragma unroll
           for (int v = 0; v < 4 && u + v < SP; ++v) {
             const Raw x = raw[k * SP + u + v];
-            const float wu = s0 + u + v < S ? w[v] : 0.f;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               unsigned bits;
               if constexpr (FINE) bits = x[e];
               else bits = (e & 1) ? x[e / 2] & 0xffff0000u : x[e / 2] << 16;
-              acc[k][e] = fmaf(__uint_as_float(bits), wu, acc[k][e]);
+              acc[k][e] = fmaf(__uint_as_float(bits), w[v], acc[k][e]);
             }
           }
         }
@@ -1114,12 +1131,15 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
           *(lds_u32x4*)(size_t)(prow ^ (q4 << 5)) = u32x4{__float_as_uint(o[4 * q4]), __float_as_uint(o[4 * q4 + 1]),
                                                           __float_as_uint(o[4 * q4 + 2]), __float_as_uint(o[4 * q4 + 3])};
         }
+        u32x4 v[kWaveRows / 8];
+#pragma unroll
+        for (int k = 0; k < kWaveRows / 8; ++k) v[k] = *reinterpret_cast<const u32x4*>(from + k * 1024);
 #pragma unroll
         for (int k = 0; k < kWaveRows / 8; ++k) {
-          const u32x4 v = *reinterpret_cast<const u32x4*>(from + k * 1024);
-          if (k * 8 + r8 < rows_valid) {
-            if (thr) dev::store_through(dst0 + k * 8 * D + 32 * db, v);
-            else *reinterpret_cast<u32x4*>(dst0 + k * 8 * D + 32 * db) = v;
+          asm volatile("" : "+v"(v[k]));  // (read outside the condition)
+          if (k * 8 < rows_valid) {
+            if (thr) dev::store_through(dst0 + k * 8 * D + 32 * db, v[k]);
+            else *reinterpret_cast<u32x4*>(dst0 + k * 8 * D + 32 * db) = v[k];
           }
         }
       }
@@ -1136,13 +1156,16 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
             const floatx16& o = st.o[h * (DB / 2) + db];
             *reinterpret_cast<float4*>(prow + (32 * db + 8 * q4) * 4) = make_float4(o[4 * q4], o[4 * q4 + 1], o[4 * q4 + 2], o[4 * q4 + 3]);
           }
+        u32x4 v[kWaveRows / RPI];
+#pragma unroll
+        for (int k = 0; k < kWaveRows / RPI; ++k) v[k] = *reinterpret_cast<const u32x4*>(src0 + k * RPI * LD);
 #pragma unroll
         for (int k = 0; k < kWaveRows / RPI; ++k) {
-          const u32x4 v = *reinterpret_cast<const u32x4*>(src0 + k * RPI * LD);
           unsigned char* dst = dst0 + k * RPI * D * 4 + h * D * 2;
-          if (k * RPI + rsub < rows_valid) {
-            if (thr) dev::store_through(dst, v);
-            else *reinterpret_cast<u32x4*>(dst) = v;
+          asm volatile("" : "+v"(v[k]));
+          if (k * RPI < rows_valid) {
+            if (thr) dev::store_through(dst, v[k]);
+            else *reinterpret_cast<u32x4*>(dst) = v[k];
           }
         }
       }
@@ -1166,39 +1189,39 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
         pk.y = __builtin_bit_cast(unsigned int, hi);
         *reinterpret_cast<uint2*>(prow + (32 * db + 8 * q4) * 2) = pk;
       }
+    u32x4 v[kWaveRows / RPI];
+#pragma unroll
+    for (int k = 0; k < kWaveRows / RPI; ++k) v[k] = *reinterpret_cast<const u32x4*>(src0 + k * RPI * LD);
+    // (all read in front of the first store and its condition: read and stored one after the other, a trip to LDS each, the
+    // waves whose rows end among their 32 kept their row tile's merge waiting)
     if (whole) {
 #pragma unroll
       for (int k = 0; k < kWaveRows / RPI; ++k) {
         const int rr = k * RPI + rsub;                               // row of the wave
         const int m = qtile * QROWS + wm * kWaveRows + rr;           // query row
-        const u32x4 v = *reinterpret_cast<const u32x4*>(src0 + k * RPI * LD);
+        asm volatile("" : "+v"(v[k]));
         if (rr < rows_valid) {
           const int node = div_mg(m, p.mg_g);
           uint16_t* dst = p.out + b * p.o_sb + node * p.o_st + (long long)(kv * G + (m - node * G)) * p.o_sh + wn * OCOLS + chunk * 8;
-          if (thr) dev::store_through(dst, v);
-          else *reinterpret_cast<u32x4*>(dst) = v;
+          if (thr) dev::store_through(dst, v[k]);
+          else *reinterpret_cast<u32x4*>(dst) = v[k];
         }
       }
     } else {
-      // partial rows are D elements apart: one address, constant steps
+      // partial rows are D elements apart: one address, constant steps; what a store holds besides rows that exist goes to
+      // the padding of their row tile, which nobody reads
       unsigned char* dst0 = reinterpret_cast<unsigned char*>(p.part_o) + ((prow0 + rsub) * D + wn * OCOLS + chunk * 8) * 2;
-      auto store_rows = [&](auto through, auto guarded) {
+      auto store_rows = [&](auto through) {
 #pragma unroll
         for (int k = 0; k < kWaveRows / RPI; ++k) {
-          const u32x4 v = *reinterpret_cast<const u32x4*>(src0 + k * RPI * LD);
-          if (!decltype(guarded)::value || k * RPI + rsub < rows_valid) {
-            if (decltype(through)::value) dev::store_through(dst0 + k * RPI * D * 2, v);
-            else *reinterpret_cast<u32x4*>(dst0 + k * RPI * D * 2) = v;
-          }
+          asm volatile("" : "+v"(v[k]));
+          if (k * RPI >= rows_valid) break;  // (uniform)
+          if (decltype(through)::value) dev::store_through(dst0 + k * RPI * D * 2, v[k]);
+          else *reinterpret_cast<u32x4*>(dst0 + k * RPI * D * 2) = v[k];
         }
       };
-      if (rows_valid >= kWaveRows) {
-        if (thr) store_rows(std::true_type{}, std::false_type{});
-        else store_rows(std::false_type{}, std::false_type{});
-      } else {
-        if (thr) store_rows(std::true_type{}, std::true_type{});
-        else store_rows(std::false_type{}, std::true_type{});
-      }
+      if (thr) store_rows(std::true_type{});
+      else store_rows(std::false_type{});
     }
   }
   if constexpr (MERGE > 0) {
@@ -1224,12 +1247,18 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
       const int slice_rows = late->merge_rows, merge_shift = MERGE < 6 ? tva::merge_shift_of(MERGE) : late->merge_shift;
       const int tile_row0 = qtile * QROWS;
       MergeThread mt = merge_prepare<D, THREADS, QROWS, FINE>(ma, unit_id, b, kv, split, slice_rows, merge_shift, tile_row0, tid_e);
+      unsigned* word = late->sync + group_word(unit_id * late->n_qtiles + qtile);
+      unsigned limit = late->spin_limit;
+      // (here, and not where it is used: left alone, the compiler puts it behind the wait for the group)
+      int live = mt.live_a;
+      asm volatile("" : "+v"(mt.raw_off), "+v"(mt.ml_off), "+v"(mt.dst_off), "+v"(mt.r_b), "+v"(live), "+s"(mt.unit_end), "+s"(mt.row_lo), "+s"(mt.row_hi));
+      asm volatile("" : "+s"(word), "+s"(limit));
+      mt.live_a = live != 0;
       JK_TS(7);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's partial stores have reached L2
       __syncthreads();
       JK_TS(8);
       if (tid_e == 0) {
-        unsigned* word = late->sync + group_word(unit_id * late->n_qtiles + qtile);
         const unsigned S = (unsigned)splits;
         const unsigned old = l2_atomic_add(word, 1u);
         const unsigned epoch = old >> 16;
@@ -1243,8 +1272,9 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
             m_lo = l2_atomic_swap(word + 1, 0u);
             m_hi = l2_atomic_swap(word + 2, 0u);
           }
+        } else if (mt.row_lo >= min(mt.row_hi, late->M - tile_row0)) {
+          mode = 0;  // (no row of the slice exists: nothing to wait for, and the CU is free for the next workgroup)
         } else {
-          const unsigned limit = late->spin_limit;
           unsigned polls = 0;
           for (;;) {
             const unsigned v = l2_atomic_add(word, 0u);

@@ -439,6 +439,24 @@ def test_bf16_every_merge_instance(splits, D, arr, T):
     assert jk.last_device_error(ws) in (0, jk.JK_DEVERR_MERGE_WAIT)   # (0: every partner was there at the first look)
 
 
+@pytest.mark.parametrize("T,splits", [(1, 7), (5, 7), (5, 4), (16, 3)])
+def test_bf16_merges_of_two_workgroups_a_cu_read_nothing_of_the_call_before(T, splits):
+    """Two workgroups share a CU and its vector cache, and most slices of a row tile of few rows have none: what such a
+    workgroup asks for must not leave a line of another group's partials in that cache before they are written.  Other inputs
+    on the same workspace each time, so that a stale line shows; the merge kernel's results beside."""
+    cfg = _cfg("c3_llama3_8b", batch=8, prefix_len=700, n_tree=T)
+    par = np.tile(np.arange(-1, T - 1, dtype=np.int32), (8, 1))
+    lens = [700, 88, 301, 512, 640, 95, 222, 450]
+    tune("attn_wm", 2); tune("attn_wn", 2); tune("attn_splits", splits)
+    ws = None
+    for seed in range(4):
+        x = attention_inputs(cfg, seed=seed, scale_mult=np.sqrt(128.0))
+        a, ws, plan = _attn_with_ws(x, par, lens, 1, ws=ws)
+        b, _, _ = _attn_with_ws(x, par, lens, 0)
+        assert plan["fused"] == 1 and plan["splits"] == splits
+        assert (np.abs(a - b) <= 1.01 * 2.0 ** -7 * np.maximum(np.abs(a), np.abs(b)) + 1e-6 * np.abs(a).max()).all()
+
+
 @pytest.mark.parametrize("kw,arr,splits,fused", [
     (dict(n_q_heads=8, n_kv_heads=8, prefix_len=1500, n_tree=40), (2, 2), (1, 2, 3), 1),
     (dict(n_q_heads=32, n_kv_heads=8, prefix_len=900, n_tree=30), (4, 1), (1, 2, 3), 1),
