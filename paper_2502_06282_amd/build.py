@@ -19,6 +19,8 @@ SOURCES = ["api.cpp", "tva_f32.hip", "tva_combine.hip", "accept.hip", "accept_co
 # matrix results in ordinary registers: by default a kernel of more than 256 registers keeps all of them in accumulation
 # registers, which the vector unit cannot read (32 moves per tile for the scores of tva_wide.hip)
 UNIT_FLAGS = {"tva_wide.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+# kernel arguments in scalar registers when a wave starts: the leading ones, fourteen words at most
+PRELOAD = ["-mllvm", "-amdgpu-kernarg-preload-count=14"]
 MERGES = 7  # tva_bf16.hip is compiled once for each of its merges (JK_MERGE)
 # packed-fp32 code generation is switched off for all device code
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -53,7 +55,7 @@ def _native_command(output: str):
 def build(verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(OBJ, exist_ok=True)
-    units = [("tva_bf16.hip", f"tva_bf16_{m}.o", [f"-DJK_MERGE={m}"]) for m in range(MERGES)]
+    units = [("tva_bf16.hip", f"tva_bf16_{m}.o", [f"-DJK_MERGE={m}"] + PRELOAD) for m in range(MERGES)]
     units += [(s, os.path.splitext(s)[0] + ".o", UNIT_FLAGS.get(s, [])) for s in SOURCES]
     objects = [os.path.join(OBJ, o) for _, o, _ in units]
     native_obj = os.path.join(OBJ, "native.o")

@@ -623,6 +623,16 @@ __device__ __forceinline__ void merge_rows(const MergeArgs& p, const MergeThread
   }
 }
 
+// The kernel's arguments in front of its KParams: what a wave needs first, fourteen words, as many as the hardware puts into scalar registers
+struct LeadingArgs {
+  const int32_t* prefix_len;
+  int batch, total_wgs, n_qtiles, splits, units_per_xcd, second_turn, n_kv_heads;
+  unsigned mg_qtiles, mg_splits, mg_hkv, mg_upx;  // the lower halves of KParams'
+};
+constexpr int kParamsAt = (sizeof(LeadingArgs) + 7) / 8 * 8;
+// n / d, mg the lower half of what div_mg takes
+__device__ __forceinline__ int divide(int n, unsigned mg, int d) { return d == 1 ? n : (int)__umulhi((unsigned)n, mg); }
+
 // LDS plan of one workgroup, shared by the kernel and its launcher.
 template <int D, int WM, int WN, int KT, bool PAGED = false, bool DEEP = false>
 struct Plan {
@@ -662,7 +672,8 @@ struct Plan {
 // splits, took 15.2 us, and 14.7 like this.
 template <int D, int WM, int WN, int KT, bool PAGED, bool DEEP, int MERGE>
 __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<D, WM, WN, KT, PAGED, DEEP>::REG_WGS)) void tva_bf16_kernel(
-    const KParams p) {
+    const int32_t* prefix_len, int batch, int total_wgs, int n_qtiles, int splits, int units_per_xcd, int second_turn, int n_kv_heads,
+    unsigned mg_qtiles, unsigned mg_splits, unsigned mg_hkv, unsigned mg_upx, const KParams p) {
   using G_ = Geo<D>;
   using P_ = Plan<D, WM, WN, KT, PAGED, DEEP>;
   constexpr int TPR = P_::TPR;
@@ -684,15 +695,14 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
   int* pg_s = repeat_s + 4;             // [1024], paged caches only
 
   JK_TS(0);
-  // ---- touch every 64-byte line of the kernel arguments at once: the compiler fetches them
-  // in several dependent batches, and this way only the first batch pays a trip to memory
-  {
-    typedef __attribute__((address_space(4))) const unsigned kernarg_word;
-    kernarg_word* ka = (kernarg_word*)__builtin_amdgcn_kernarg_segment_ptr();
-    static_assert(sizeof(KParams) > 320 && sizeof(KParams) <= 384, "six lines of kernel arguments");
-    const unsigned a0 = ka[0], a1 = ka[16], a2 = ka[32], a3 = ka[48], a4 = ka[64], a5 = ka[80];
-    asm volatile("" ::"s"(a0), "s"(a1), "s"(a2), "s"(a3), "s"(a4), "s"(a5));
-  }
+  // ---- The leading arguments are in scalar registers when a wave starts (a compiler option for this file): which piece of work
+  // this is, and the lengths' address.  The others take 0.25 us to come from memory, for which their 64-byte lines are
+  // touched at once: the compiler fetches them in several dependent batches, and this way only the first pays the trip.
+  typedef __attribute__((address_space(4))) const unsigned kernarg_word;
+  kernarg_word* ka = (kernarg_word*)__builtin_amdgcn_kernarg_segment_ptr();
+  static_assert(kParamsAt == 56 && sizeof(LeadingArgs) <= 56 && sizeof(KParams) > 328 && sizeof(KParams) <= 392, "seven lines of kernel arguments");
+  const unsigned a0 = ka[14], a1 = ka[16], a2 = ka[32], a3 = ka[48], a4 = ka[64], a5 = ka[80], a6 = ka[96];
+  __builtin_amdgcn_sched_barrier(0);
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -700,9 +710,12 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
   const int wn = wave / WM;
   const int c32 = lane & 31;
   const int g = lane >> 5;
-  const int T = p.T, G = p.G, M = p.M, splits = p.splits;
-  const float scale_log2 = p.scale_log2;
-
+  // (what needs no argument is worked out while they are on their way)
+  unsigned column = lane_column<D, NW>(wave, lane);
+  // (A wave of key column 1 takes the blocks of the head dimension second half first: its first accumulators then are the
+  // half that it finishes, and no register is chosen by the wave.)
+  unsigned k_lane = G_::k_lane(lane), v_lane = G_::v_lane(lane) ^ ((unsigned)(wn * P_::OB) << 6);
+  asm volatile("" : "+v"(column), "+v"(k_lane), "+v"(v_lane));
   // ---- which piece of work: consecutive hardware workgroup ids alternate between the 8
   // XCDs, so give each XCD a contiguous range of logical ids; q-tiles of one (b, kv, split)
   // are adjacent logical ids and therefore share that XCD's L2 for their common K/V.
@@ -711,62 +724,66 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
   // the long ones, and where the grid is two workgroups a CU the second 32 of an XCD come the other way round, so that
   // the longest shares its CU with the shortest.  16 sequences of 512 to 4096 tokens (8B shapes) took 88 us in the
   // order of the batch (an XCD had two sequences of its own), 67 like this.
-  const bool ranked = p.units_per_xcd > 0;
+  const bool ranked = units_per_xcd > 0;
+  // The prefix length first.  Ordinary loads are issued by hand like the transfers behind them, and waited for by number: the
+  // compiler, which does not know of the transfers, would wait for the oldest of its loads by waiting for all but a few of
+  // everything issued since.
+  int lengths;  // (lane i: of sequence i, of the first 64)
+  load_by_hand(lengths, prefix_len + min(lane, batch - 1));
   int wid;
   {
     const int n = blockIdx.x;
-    const int per = p.total_wgs >> 3;  // total_wgs is padded to a multiple of 8
+    const int per = total_wgs >> 3;  // total_wgs is padded to a multiple of 8
     int local = n >> 3;
-    if (ranked && local >= p.second_turn) local = p.second_turn + per - 1 - local;
+    if (ranked && local >= second_turn) local = second_turn + per - 1 - local;
     wid = (n & 7) * per + local;
   }
-  int rest = div_mg(wid, p.mg_qtiles);
-  const int qtile = wid - rest * p.n_qtiles;
-  const int unit = div_mg(rest, p.mg_splits);  // b * Hkv + kv in the order of the batch
-  if (unit >= p.B * p.Hkv) return;             // padding workgroup
+  const int rest = divide(wid, mg_qtiles, n_qtiles);
+  const int qtile = wid - rest * n_qtiles;
+  const int unit = divide(rest, mg_splits, splits);  // b * Hkv + kv in the order of the batch
+  if (unit >= batch * n_kv_heads) return;    // padding workgroup
   const int split = rest - unit * splits;
   int place = unit;  // rank * Hkv + kv
   if (ranked) {
-    const int x = div_mg(unit, p.mg_upx), i = unit - x * p.units_per_xcd;
+    const int x = divide(unit, mg_upx, units_per_xcd), i = unit - x * units_per_xcd;
     place = i * 8 + ((i & 1) ? 7 - x : x);
   }
-  const int rank = div_mg(place, p.mg_hkv);
-  const int kv = place - rank * p.Hkv;
-  int b = rank;  // (if all lengths are equal, the order of the batch: assumed until they have arrived)
-
-  // ---- the prefix length first, as a per-lane vector load (an atomic load is never turned
-  // into a scalar one, and the compiler must not see that the address is uniform, or it
-  // moves the value to a scalar register at once and waits for it): scalar loads share one
-  // counter with the kernel-argument loads, so waiting for an argument would wait for this
-  // trip to memory as well.  Then the query rows and the
-  // parent array, none of which depends on it.  All ordinary loads are older than the K/V
-  // transfers: the compiler's waits for them then never include a transfer.
-  int lane_zero = 0;
-  asm volatile("" : "+v"(lane_zero));  // hides from the compiler that the address is uniform
-  const int L_raw = __hip_atomic_load(p.prefix_len + (ranked ? min(lane, p.B - 1) : b) + lane_zero, __ATOMIC_RELAXED,
-                                      __HIP_MEMORY_SCOPE_AGENT);  // (of a batch: lane i has sequence i's)
-  WaveState<D> st;
+  const int rank = divide(place, mg_hkv, n_kv_heads);
+  const int kv = place - rank * n_kv_heads;
+  int b = rank;  // (a ranked batch: until the lengths are there)
+  // ---- from here on with the arguments that had to come
+  {
+    int r = rank, q = qtile, s = split;
+    asm volatile("" : "+s"(r), "+s"(q), "+s"(s));
+    asm volatile("" ::"s"(a0), "s"(a1), "s"(a2), "s"(a3), "s"(a4), "s"(a5), "s"(a6));
+  }
+  const int T = p.T, G = p.G, M = p.M;
+  const float scale_log2 = p.scale_log2;
   const int m_row = qtile * QROWS + wm * kWaveRows + c32;  // this lane's query row
   const bool row_ok = m_row < M;
-  const int mm = row_ok ? m_row : M - 1;
+  const int mm = row_ok ? m_row : M - 1;  // (clamped: in bounds)
   const int my_node = div_mg(mm, p.mg_g);
-  u32x4 q_raw[DK];
-  // (the first wave builds the ancestor sets, nodes lane and lane + 64)
-  int parent_lo = -1, parent_hi = -1;
-  auto load_rows = [&]() {
-    const uint16_t* src =
-        p.q + b * p.q_sb + my_node * p.q_st + (long long)(kv * G + (mm - my_node * G)) * p.q_sh + 8 * g;
-#pragma unroll
-    for (int ks = 0; ks < DK; ++ks) q_raw[ks] = *reinterpret_cast<const u32x4*>(src + ks * 16);  // clamped row: in bounds
-    if (wave == 0) {
-      if (lane < T) parent_lo = p.parent[(long long)b * T + lane];
-      if (lane + 64 < T) parent_hi = p.parent[(long long)b * T + lane + 64];
+  unsigned long long row_at = (unsigned)my_node * (unsigned long long)p.q_st + (unsigned)(kv * G + (mm - my_node * G)) * (unsigned long long)p.q_sh + 8 * g;
+  int L = p.max_prefix, L_one;
+  // (a load's result is in nobody's hands before it has been waited for: the values below are copies, so that no two branches'
+  // meet in one variable, for which the compiler would move what has not arrived)
+  if (ranked) {
+    asm volatile("" : "+v"(row_at));
+    dev::wait_vm<0>();
+    int len;
+    asm volatile("v_mov_b32 %0, %1" : "=v"(len) : "v"(lengths));
+    len = len < 0 ? 0 : (len > p.max_prefix ? p.max_prefix : len);
+    if (!__all(len == p.max_prefix)) {
+      b = sequence_of_rank(len, batch, rank, lane);
+      L = __builtin_amdgcn_readlane(len, b);
     }
-  };
-  load_rows();
+  } else if (batch > 64) {
+    load_by_hand(L_one, prefix_len + b);
+  }
+  JK_TS(14);
 
-  // ---- tile range of this split.  The prefix length is still on its way: start the K/V
-  // stream on the assumption that it equals the host's upper bound (the usual case); if it
+  // ---- tile range of this split.  One sequence (or more than 64): the prefix length is still on its way, and the K/V
+  // stream starts on the assumption that it equals the host's upper bound (the usual case); if it
   // turns out shorter, the speculative transfers are waited for and everything is redone.
   TileSrc ts;
   ts.T = T;
@@ -789,10 +806,10 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
     const int nt = ts.n_ptiles + n_ttiles;
     const int R = (nt + TPR - 1) / TPR;
     const int slow = R - (len / kTileKeys) / TPR;  // rounds that are not all full prefix tiles
-    const int share = div_mg(R, p.mg_splits);
+    const int share = divide(R, mg_splits, splits);
     const int extra = slow < share / 2 ? slow : share / 2;
     const int Rv = R + extra;
-    const int base = div_mg(Rv, p.mg_splits);
+    const int base = divide(Rv, mg_splits, splits);
     const int rem = Rv - base * splits;
     int rb = split * base + (split < rem ? split : rem);
     int re = rb + base + (split < rem ? 1 : 0);
@@ -813,7 +830,7 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
       const int tail = nt - F;
       int tb = 0, te = nt;
       if (splits > 1) {
-        const int per = div_mg(F + 2 * tail + splits - 1, p.mg_splits);  // ceil((F + 2 tail) / splits)
+        const int per = divide(F + 2 * tail + splits - 1, mg_splits, splits);  // ceil((F + 2 tail) / splits)
         int f_last = per - 2 * tail;
         f_last = f_last < 0 ? 0 : (f_last > F ? F : f_last);
         f_last &= ~1;  // (whole pairs: the general path takes the tail two tiles at a time, and a full tile must not split one of its rounds)
@@ -831,25 +848,20 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
     }
   };
   const unsigned ring_addr = (unsigned)(size_t)LDS_PTR(unsigned char, ring);  // a multiple of 1024
-  // (A wave of key column 1 takes the blocks of the head dimension second half first: its first accumulators then are the
-  // half that it finishes, and no register is chosen by the wave.)
-  const unsigned k_lane = G_::k_lane(lane), v_lane = G_::v_lane(lane) ^ ((unsigned)(wn * P_::OB) << 6);
   LaneChunks<D, NW> lc;
-  auto set_streams = [&]() {
-    lane_chunks<D, NW>(lc, wave, lane, ts, p.kc + (PAGED ? 0 : b * p.kc_sb) + (long long)kv * p.kc_sh,
-                       p.vc + (PAGED ? 0 : b * p.kc_sb) + (long long)kv * p.kc_sh, p.kt + b * p.kt_sb + (long long)kv * p.kt_sh,
-                       p.vt + b * p.kt_sb + (long long)kv * p.kt_sh);
-  };
-  set_streams();
+  lane_chunks<D, NW>(lc, wave, lane, column, ts);
+  const bool is_v = wave * LaneChunks<D, NW>::N >= G_::NB;
+  lc.cache = uniform_ptr((is_v ? p.vc : p.kc) + (PAGED ? 0 : (unsigned)b * (unsigned long long)p.kc_sb) + (unsigned)kv * (unsigned long long)p.kc_sh);
 
-  set_range(p.max_prefix);
+  set_range(L);
   int n_rounds = (ts.t_end - ts.t_begin + TPR - 1) / TPR;
   // Paged cache: page ids of the prefix tiles this split will fetch (whole rounds), clamped into the pool, so
   // that a transfer stays inside the pool whatever the table holds: the first rounds can then be asked for on
   // the same assumption as with a contiguous cache (entries past a sequence's pages may hold anything; if the
   // length turns out shorter, the list is made again).  An id outside the pool is reported once the list is final.
   bool bad_page = false;
-  int n_pg = 0, first_id = 0;  // pages of the list; this thread's first entry
+  int n_pg = 0, first_id;  // pages of the list; this thread's first entry
+  const int* table = p.block_table + (long long)b * p.max_blocks;
   auto ask_pages = [&]() {
     const int te = min(ts.n_ptiles, ts.t_begin + n_rounds * TPR);
     n_pg = 0;
@@ -857,71 +869,82 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
       ts.pg_first = div_mg(ts.t_begin, p.mg_tpp);
       n_pg = div_mg(te - 1, p.mg_tpp) - ts.pg_first + 1;  // <= kMaxPagesPerSplit by the host's plan
     }
-    first_id = tid < n_pg && ts.pg_first + tid < p.max_blocks ? p.block_table[(long long)b * p.max_blocks + ts.pg_first + tid] : 0;
+    // (in every lane: the compiler may not move the result before it has been waited for)
+    load_by_hand(first_id, tid < n_pg && ts.pg_first + tid < p.max_blocks ? table + ts.pg_first + tid : p.prefix_len);
   };
-  auto fill_pages = [&]() {
+  auto fill_pages = [&]() {  // (the ids have been waited for)
+    asm volatile("" : "+v"(first_id));
     bad_page = false;
     for (int i = tid; i < n_pg && i < kMaxPagesPerSplit; i += THREADS) {
       const int pi = ts.pg_first + i;
-      const int id = i == tid ? first_id : (pi < p.max_blocks ? p.block_table[(long long)b * p.max_blocks + pi] : 0);
+      const int id = pi >= p.max_blocks ? 0 : (i == tid ? first_id : table[pi]);
       bad_page = bad_page || id < 0 || id >= p.n_pages;
       pg_s[i] = id < 0 ? 0 : (id >= p.n_pages ? p.n_pages - 1 : id);
     }
     __syncthreads();
   };
-  if (PAGED) ask_pages();
-  // (A paged batch asks for nothing on that assumption but the page ids, which take as long as the lengths: lengths are
-  // seldom all equal, and the rounds in vain had to land before the right ones took their places.  us, before / after:
-  // 6 sequences of up to 437 keys, 14 nodes, 32 heads 11.7 / 10.9; 24 of up to 36 keys, 12 nodes, 40 heads 18.0 / 15.9; 8 of up
-  // to 4933 keys 30.8 / 29.4; equal lengths the same within 1 %.  Contiguous caches lose 1 - 4 % by the wait where lengths are equal.)
-  const bool at_once = !PAGED || !ranked;
-  if (PAGED && at_once) fill_pages();
-  const bool spec_any = at_once && n_rounds > 0 && (ts.t_begin + TPR) * kTileKeys <= p.max_prefix;  // same for every wave
+  if (PAGED) ask_pages();  // (the query rows come while the page ids do)
+
+  // ---- the query rows, and in the first wave, which builds the ancestor sets, the parents of nodes lane and lane + 64
+  WaveState<D> st;
+  u32x4 q_raw[DK];
+  int parent_lo, parent_hi;
+  {
+    load_rows_by_hand(q_raw, p.q + (unsigned)b * (unsigned long long)p.q_sb + row_at);
+    if (wave == 0) {
+      const int32_t* parents = p.parent + (unsigned)(b * T);
+      load_by_hand(parent_lo, parents + min(lane, T - 1));
+      load_by_hand(parent_hi, parents + min(lane + 64, T - 1));
+    }
+  }
+  if (PAGED) {
+    dev::wait_vm<DK>();
+    fill_pages();
+  }
+  // ---- the first rounds.  (A ranked batch has its lengths by now.  Asked for as if all of them equalled the bound, which is seldom
+  // so, the first rounds had to land before the right ones took their places.  us, so / like this: 8 sequences of up to 2048
+  // keys, five nodes (8B shapes) 17.2 / 16.1, 12 of up to 900, 24 nodes 19.7 / 17.4, 4 of up to 2000, 60 nodes 22.2 / 20.8; equal lengths
+  // within 1 % either way: 4 of 2048, 40 heads 43.8 / 44.2, 4 of 1024, 28 nodes, 32 heads 20.4 / 20.0.)
   int n_spec = 0;  // rounds already issued, all of them full prefix tiles under the assumption
 #pragma unroll
   for (int r = 0; r < NR - 1; ++r)
-    if (at_once && n_spec == r && r < n_rounds && (ts.t_begin + (r + 1) * TPR) * kTileKeys <= p.max_prefix) {
+    if (n_spec == r && r < n_rounds && (ts.t_begin + (r + 1) * TPR) * kTileKeys <= L) {
       dma_round<D, NW, TPR, PAGED>(r, ts, lc, ring_addr + r * STAGE_BYTES);
       n_spec = r + 1;
     }
   JK_TS(1);
-
-  int L;
-  bool moved = false;  // another sequence than the assumed one
-  if (ranked) {
-    const int len = L_raw < 0 ? 0 : (L_raw > p.max_prefix ? p.max_prefix : L_raw);
-    L = p.max_prefix;
-    if (!__all(len == p.max_prefix)) {
-      const int mine = sequence_of_rank(len, p.B, rank, lane);
-      moved = mine != b;
-      b = mine;
-      L = __builtin_amdgcn_readlane(len, mine);
+  // (not in front of the transfers, which are full prefix tiles)
+  int b_late = b;
+  asm volatile("" : "+s"(b_late));
+  lc.tree = uniform_ptr((is_v ? p.vt : p.kt) + (unsigned)b_late * (unsigned long long)p.kt_sb + (unsigned)kv * (unsigned long long)p.kt_sh);
+  if (!ranked) {
+    if (n_spec == NR - 1) dev::wait_vm<DK + (NR - 1) * DMA_PER_ROUND>();
+    else dev::wait_vm<DK>();  // (no less than needed)
+    if (batch <= 64) {
+      int len;
+      asm volatile("v_mov_b32 %0, %1" : "=v"(len) : "v"(lengths));
+      L = __builtin_amdgcn_readlane(len, b);
+    } else {
+      int len;
+      asm volatile("v_mov_b32 %0, %1" : "=v"(len) : "v"(L_one));
+      L = __builtin_amdgcn_readfirstlane(len);
     }
-  } else {
-    L = __builtin_amdgcn_readfirstlane(L_raw);
     L = L < 0 ? 0 : (L > p.max_prefix ? p.max_prefix : L);
-  }
-  JK_TS(2);
-  if (L != p.max_prefix || moved) {  // uniform over the workgroup
-    if (spec_any) {
-      wait_dma<DMA_PER_ROUND>(0);  // the ring must be quiet before the same slots are filled again
+    JK_TS(2);
+    if (L != p.max_prefix) {  // uniform over the workgroup
+      dev::wait_vm<0>();  // the ring must be quiet before the same slots are filled again
       __syncthreads();
-    }
-    if (moved) {
-      set_streams();
-      load_rows();
-    }
-    n_spec = 0;
-    set_range(L);
-    n_rounds = (ts.t_end - ts.t_begin + TPR - 1) / TPR;
-    if (PAGED) ask_pages();
-    if (PAGED && at_once) {
-      __syncthreads();  // (nobody reads the first list any more)
-      fill_pages();
+      n_spec = 0;
+      set_range(L);
+      n_rounds = (ts.t_end - ts.t_begin + TPR - 1) / TPR;
+      if (PAGED) {
+        ask_pages();
+        dev::wait_vm<0>();
+        fill_pages();
+      }
     }
   }
-  if (PAGED && !at_once) fill_pages();
-  const int unit_id = b * p.Hkv + kv;
+  const int unit_id = b * n_kv_heads + kv;
   const bool has_tree = ts.t_end > ts.n_ptiles;
   if (PAGED && bad_page) __hip_atomic_fetch_or(p.err, kDevErrBadPage, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
@@ -929,9 +952,15 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
     if (r >= n_spec && r < n_rounds) dma_round<D, NW, TPR, PAGED>(r, ts, lc, ring_addr + r * STAGE_BYTES);
 
   JK_TS(3);
+  wait_dma<DMA_PER_ROUND>(n_rounds < NR - 1 ? n_rounds : NR - 1);  // (what is older than the first rounds)
+#pragma unroll
+  for (int ks = 0; ks < DK; ++ks) asm volatile("" : "+v"(q_raw[ks]));
   // ---- ancestor sets (only workgroups that reach tree tiles need them); the barrier of the first round publishes them:
   // tree tiles are masked inside the loop only
-  if (has_tree && wave == 0) build_ancestor_sets(lane, T, parent_lo, parent_hi, par_s, anc);
+  if (has_tree && wave == 0) {
+    asm volatile("" : "+v"(parent_lo), "+v"(parent_hi));
+    build_ancestor_sets<kParamsAt>(lane, T, lane < T ? parent_lo : -1, lane + 64 < T ? parent_hi : -1, par_s, anc);
+  }
 
 #pragma unroll
   for (int ks = 0; ks < DK; ++ks) {
@@ -1233,7 +1262,7 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
     // (The arguments this part needs are fetched from the kernel-argument segment here rather than
     // held in scalar registers across the tile loop, which has none to spare.)
     typedef __attribute__((address_space(4))) const KParams KArgs;
-    KArgs* late = (KArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    KArgs* late = (KArgs*)((__attribute__((address_space(4))) const char*)__builtin_amdgcn_kernarg_segment_ptr() + kParamsAt);
     asm volatile("" : "+s"(late));
     const int tid_e = wave * 64 + lane_e;  // (the thread id, rebuilt: see the note on lane_e above)
     {
@@ -1334,7 +1363,8 @@ hipError_t launch_one(const KParams& kp, hipStream_t stream) {
   auto kern = tva_bf16_kernel<D, WM, WN, KT, PAGED, DEEP, JK_MERGE>;
   static LdsLimitRaised raised;
   if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), P_::SMEM, raised); e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(kp.total_wgs), dim3(P_::THREADS), P_::SMEM, stream, kp);
+  hipLaunchKernelGGL(kern, dim3(kp.total_wgs), dim3(P_::THREADS), P_::SMEM, stream, kp.prefix_len, kp.B, kp.total_wgs, kp.n_qtiles, kp.splits, kp.units_per_xcd,
+                     kp.second_turn, kp.Hkv, (unsigned)kp.mg_qtiles, (unsigned)kp.mg_splits, (unsigned)kp.mg_hkv, (unsigned)kp.mg_upx, kp);
   return hipGetLastError();
 }
 template <int D, bool PAGED>

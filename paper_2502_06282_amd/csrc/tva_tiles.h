@@ -115,6 +115,22 @@ struct Geo {
   }
 };
 
+// Ordinary loads by hand (what waits for them says how many transfers may have been issued since)
+__device__ __forceinline__ void load_by_hand(u32x4& v, const void* src) {
+  asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(v) : "v"(src) : "memory");
+}
+__device__ __forceinline__ void load_by_hand(int& v, const void* src) {
+  asm volatile("global_load_dword %0, %1, off" : "=v"(v) : "v"(src) : "memory");
+}
+// N times 16 bytes, every 32 bytes
+template <int N, int I = 0>
+__device__ __forceinline__ void load_rows_by_hand(u32x4 (&v)[N], const void* src) {
+  if constexpr (I < N) {
+    asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(v[I]) : "v"(src), "n"(32 * I) : "memory");
+    load_rows_by_hand<N, I + 1>(v, src);
+  }
+}
+
 using dev::dma16;
 using dev::uniform_ptr;
 
@@ -177,25 +193,32 @@ struct LaneChunks {
   }
 };
 
+// The part of a chunk's byte offset in its row that does not depend on which of the wave's chunks it is.  A wave's rows are a
+// multiple of 64 / CPR apart, so `where`'s swizzles come apart: V's is the same for all of them, K's differs by a
+// constant in the bits above.
 template <int D, int NW>
-__device__ __forceinline__ void lane_chunks(LaneChunks<D, NW>& lc, int wave, int lane, const TileSrc& ts,
-                                            const uint16_t* kc, const uint16_t* vc, const uint16_t* kt,
-                                            const uint16_t* vt) {
+__device__ __forceinline__ unsigned lane_column(int wave, int lane) {
   using G_ = Geo<D>;
-  constexpr int N = LaneChunks<D, NW>::N;
-  const int is_v = (wave * N) / G_::NB;
-  lc.cache = uniform_ptr(is_v ? vc : kc);
-  lc.tree = uniform_ptr(is_v ? vt : kt);
+  const int lr = lane / G_::CPR, pc = lane % G_::CPR;
+  const int k_swz = lr / (16 / G_::CPR), v_swz = lr / (4 / G_::DB) % G_::DB << 2;
+  return (unsigned)(pc ^ (wave * LaneChunks<D, NW>::N >= G_::NB ? v_swz : k_swz)) * 16u;
+}
+// `column`: lane_column's, worked out while the kernel's arguments are on their way
+template <int D, int NW>
+__device__ __forceinline__ void lane_chunks(LaneChunks<D, NW>& lc, int wave, int lane, unsigned column, const TileSrc& ts) {
+  using G_ = Geo<D>;
+  constexpr int N = LaneChunks<D, NW>::N, RPB = 64 / G_::CPR;
+  const bool is_v = wave * N >= G_::NB;
   lc.wave = wave;
   lc.lane = lane;
+  const unsigned row_bytes = (unsigned)ts.kc_sl * 2u;  // < 2^25: strides are bounded by the host
+  unsigned lane_rows = (unsigned)(lane / G_::CPR) * row_bytes;
+  asm("" : "+v"(lane_rows));  // (one product, not one a chunk)
 #pragma unroll
   for (int i = 0; i < N; ++i) {
-    const int blk = (wave * N + i) % G_::NB;
-    int row;
-    unsigned col_b;
-    lc.where(i, row, col_b);
-    lc.off[i] = (unsigned)row * (unsigned)ts.kc_sl * 2u + col_b;  // < 2^31: strides are bounded by the host
-    lc.lds[i] = is_v * G_::TILE_BYTES + blk * 1024;
+    const unsigned blk = (unsigned)(wave * N % G_::NB + i), k_swz = is_v ? 0u : blk % (unsigned)(G_::CPR / 4) * 64u;
+    lc.off[i] = (column ^ k_swz) + (lane_rows + blk * (unsigned)RPB * row_bytes);
+    lc.lds[i] = (is_v ? G_::TILE_BYTES : 0) + blk * 1024;
   }
 }
 
@@ -309,7 +332,8 @@ __device__ __forceinline__ void mask_tile(floatx16& sacc, int mask_mode, int nva
 // nodes per lane (parents of nodes lane and lane + 64): the LDS operations of a wave complete in program order, so the steps
 // need no barrier (as rounds of the whole workgroup, with two or three barriers each, the
 // same steps took three times as long, and the split that owns the tree tiles is the one
-// the others wait for).  The kernel's first argument is its KParams.
+// the others wait for).  PARAMS_AT: where the kernel's KParams lie among its arguments.
+template <int PARAMS_AT = 0>
 __device__ __forceinline__ void build_ancestor_sets(int lane, int T, int parent_lo, int parent_hi, int* par_s,
                                                     unsigned long long* anc) {
   const int n_lo = lane, n_hi = lane + 64;
@@ -318,7 +342,7 @@ __device__ __forceinline__ void build_ancestor_sets(int lane, int T, int parent_
   // an entry that breaks -1 <= parent[i] < i was just replaced by -1: say so in the workspace's error word
   if (up_lo != parent_lo || up_hi != parent_hi) {
     typedef __attribute__((address_space(4))) const KParams KArgs;
-    KArgs* late = (KArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    KArgs* late = (KArgs*)((__attribute__((address_space(4))) const char*)__builtin_amdgcn_kernarg_segment_ptr() + PARAMS_AT);
     asm volatile("" : "+s"(late));  // (fetched here: not worth a scalar register pair across the kernel)
     __hip_atomic_fetch_or(late->err, kDevErrBadTree, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }

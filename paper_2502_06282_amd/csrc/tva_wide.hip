@@ -34,13 +34,6 @@ using tva::KParams;
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ void load_by_hand(u32x4& v, const void* src) {
-  asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(v) : "v"(src) : "memory");
-}
-__device__ __forceinline__ void load_by_hand(int& v, const void* src) {
-  asm volatile("global_load_dword %0, %1, off" : "=v"(v) : "v"(src) : "memory");
-}
-
 constexpr int kWideThreads = 256, kWideWaves = 4, kBlocks = 2, kWideRows = kBlocks * kWaveRows;
 
 template <int D, bool PAGED>
@@ -267,9 +260,10 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
   };
   const unsigned ring_addr = (unsigned)(size_t)LDS_PTR(unsigned char, smem);
   LaneChunks<D, kWideWaves> lc;
-  lane_chunks<D, kWideWaves>(lc, wave, lane, ts, p.kc + (PAGED ? 0 : b * p.kc_sb) + (long long)kv * p.kc_sh,
-                             p.vc + (PAGED ? 0 : b * p.kc_sb) + (long long)kv * p.kc_sh, p.kt + b * p.kt_sb + (long long)kv * p.kt_sh,
-                             p.vt + b * p.kt_sb + (long long)kv * p.kt_sh);
+  lane_chunks<D, kWideWaves>(lc, wave, lane, lane_column<D, kWideWaves>(wave, lane), ts);
+  const bool is_v = wave * N >= G_::NB;
+  lc.cache = uniform_ptr((is_v ? p.vc : p.kc) + (PAGED ? 0 : b * p.kc_sb) + (long long)kv * p.kc_sh);
+  lc.tree = uniform_ptr((is_v ? p.vt : p.kt) + b * p.kt_sb + (long long)kv * p.kt_sh);
 #pragma unroll
   for (int i = 0; i < N; ++i) lc.lds[i] = (wave * N) / G_::NB * P_::HALF_BYTES + (wave * N + i) % G_::NB * 1024;
   set_range(L);
@@ -307,8 +301,7 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
   for (int r = 0; r < kBlocks; ++r) {
     const int mm = min(row0 + r * kWaveRows + c32, M - 1), node = div_mg(mm, p.mg_g);
     const uint16_t* src = p.q + b * p.q_sb + node * p.q_st + (long long)(kv * G + (mm - node * G)) * p.q_sh + 8 * g;
-#pragma unroll
-    for (int ks = 0; ks < DK; ++ks) load_by_hand(q_raw[r][ks], src + ks * 16);
+    load_rows_by_hand(q_raw[r], src);
   }
   load_by_hand(parent_lo, p.parent + (long long)b * T + min(lane, T - 1));
   load_by_hand(parent_hi, p.parent + (long long)b * T + min(lane + 64, T - 1));

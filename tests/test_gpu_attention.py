@@ -258,6 +258,27 @@ def test_bf16_prefix_shorter_than_bound(monkeypatch, wm, wn):
     assert np.abs(got - ref).max() <= BF16_TOL
 
 
+@pytest.mark.parametrize("lengths", ["bound", "ragged", "one_shorter"])
+@pytest.mark.parametrize("arr,splits", [((2, 2), 1), ((2, 2), 2), ((4, 1), 2)])
+@pytest.mark.parametrize("batch", [1, 2, 63, 64, 65])
+def test_bf16_lengths_of_batches(batch, arr, splits, lengths):
+    """A batch of up to 64 has its lengths in front of its first transfers, a lane each; one sequence, or more than 64, assume
+    the bound and find out: lengths of zero, of a key, and at the bound, at the edges of both."""
+    tune("attn_wm", arr[0]); tune("attn_wn", arr[1]); tune("attn_splits", splits)
+    cfg = _cfg("c3_llama3_8b", batch=batch, n_q_heads=8, n_kv_heads=8, prefix_len=150, n_tree=6)
+    rng = np.random.default_rng(batch)
+    lens = [150] * batch
+    if lengths == "ragged":
+        lens = [int(v) for v in rng.integers(0, 151, size=batch)]
+    elif lengths == "one_shorter":
+        lens[batch // 2] = 1
+    par = np.tile(np.array([-1, 0, 0, 1, -1, 4], dtype=np.int32), (batch, 1))
+    x = attention_inputs(cfg, scale_mult=np.sqrt(128.0))
+    ref = oracle_attention(**x, parent=par, prefix_len=lens)
+    got = gpu_attention(x, par, lens, "bf16", max_prefix_len=150)
+    assert np.abs(got - ref).max() <= BF16_TOL
+
+
 def _every_element(cfg, x, par, got):
     """The whole result against the oracle, element by element (the oracle needs well under a second per layer
     at these sizes): absolute bound of the graded metric, and relative to the layer's largest output."""
