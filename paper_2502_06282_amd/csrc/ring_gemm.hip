@@ -54,8 +54,18 @@ struct RingCfg {
   static_assert(DEPTH >= 2, "LDS plan");
 };
 
+// (The leading arguments are in scalar registers when a wave starts, see stream_gemm.hip)
 template <RingKind KIND, int RG, int NF>
-__global__ __launch_bounds__(kRingThreads, 1) void ring_gemm_kernel(StreamGemmArgs p) {
+__global__ __launch_bounds__(kRingThreads, 1) void ring_gemm_kernel(const int* sel_lead, int rows_all, int experts, int n, int k, int all,
+                                                                    const uint16_t* x, const uint16_t* w, long long w_batch, StreamGemmArgs p) {
+  p.sel = sel_lead;
+  p.m = rows_all;
+  p.batch = experts;
+  p.n = n;
+  p.k = k;
+  p.x = x;
+  p.w = w;
+  p.w_batch = w_batch;
   using C = RingCfg<KIND, RG, NF>;
   constexpr int MT = C::MT, CAP = 8 * RG, GROUP = KIND == PAIR ? 8 : 16;  // rows of X at a time; output columns of a group
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -117,7 +127,7 @@ __global__ __launch_bounds__(kRingThreads, 1) void ring_gemm_kernel(StreamGemmAr
   }
 
   // ---- this workgroup's share of the groups (neighbours on one XCD have the same X)
-  const int all = gridDim.x, blk = blockIdx.x;
+  const int blk = blockIdx.x;
   const int id = xcd_place(blk, all);
   const int per_item = (p.n + GROUP - 1) / GROUP;
   const ring::Shares shares{per_item, NF};
@@ -341,7 +351,9 @@ hipError_t launch(const StreamGemmArgs& p, hipStream_t stream) {
   if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(ring_gemm_kernel<KIND, RG, NF>), smem, raised); e != hipSuccess) return e;
   const long long groups = (long long)((p.n + (KIND == PAIR ? 7 : 15)) / (KIND == PAIR ? 8 : 16)) * p.batch;
   const int cus = device_cu_count();
-  hipLaunchKernelGGL((ring_gemm_kernel<KIND, RG, NF>), dim3((unsigned)(groups < cus ? groups : cus)), dim3(kRingThreads), smem, stream, p);
+  const int all = (int)(groups < cus ? groups : cus);
+  hipLaunchKernelGGL((ring_gemm_kernel<KIND, RG, NF>), dim3((unsigned)all), dim3(kRingThreads), smem, stream, p.sel, p.m, p.batch, p.n, p.k, all, p.x,
+                     p.w, p.w_batch, p);
   return hipGetLastError();
 }
 // `items`: how many experts are likely to be chosen

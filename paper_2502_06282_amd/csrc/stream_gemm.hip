@@ -74,7 +74,7 @@ struct Weights {
   int k0, k1;        // this part's k range, in units of 128
   unsigned wg;
 
-  __device__ __forceinline__ void start(const StreamGemmArgs& p, int n_base, int e, int wave, int r, int g) {
+  __device__ __forceinline__ void start(const StreamGemmArgs& p, int strips, int n_base, int e, int wave, int r, int g) {
     // (64-bit divisions here were half of the 412 instructions in front of the first load: 2 - 4 % of a small call)
     k0 = 0;
     k1 = p.k;
@@ -83,7 +83,7 @@ struct Weights {
       k0 = (int)(blockIdx.z * units / parts) * 128;
       k1 = (int)((blockIdx.z + 1u) * units / parts) * 128;
     }
-    wg = blockIdx.x + gridDim.x * blockIdx.y;
+    wg = blockIdx.x + strips * blockIdx.y;
     const uint16_t* base = (KIND == PAIR && wave >= 4 ? p.w2 : p.w) + (long long)e * p.w_batch;
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
@@ -99,12 +99,15 @@ struct Weights {
   }
   // Workgroups start at different chunks and wrap around: rows often lie a power of two apart, so that workgroups in
   // step would all ask the same few memory channels (16 x 4096 x 4096: 115 us in step, 98 us like this; 32000 x 4096:
-  // 58 and 46).  Workgroups run on the eight XCDs in turn, so the start has to vary within every eighth of them too.
-  // (A half chunk at the end stays last.)
+  // 58 and 46).  Workgroups run on the eight XCDs in turn, so the start has to vary within every eighth of them too: by seven
+  // chunks from one to the next, and where a row has 16 chunks or more by eight from XCD to XCD, else by five.  Of 28 pairs of steps,
+  // five and nine / eight and seven, kernels of a call, us: 20 rows, 128256 x 4096 195 / 190, 80, 32000 x 4096 69.3 / 68.6, 40, 64000 x
+  // 8192 196 / 193, eight experts of 4096 x 4096 148.8 / 144.7; in eight chunks the other way round, 64000 x 2048 1 : 0.985, experts of 2048 x
+  // 8192 1 : 0.976.  (A half chunk at the end stays last.)
   template <int KC>
   __device__ __forceinline__ int chunk(int c) const {
     const int whole = (k1 - k0) / KC;
-    const int rot = whole > 0 ? (int)((5u * wg + (wg >> 3)) % (unsigned)whole) : 0;
+    const int rot = whole > 0 ? (int)((whole >= 16 ? 8u * (wg & 7u) + 7u * (wg >> 3) : 5u * wg + (wg >> 3)) % (unsigned)whole) : 0;
     const int t = c + rot;
     return k0 + (c < whole ? (t < whole ? t : t - whole) : c) * KC;
   }
@@ -339,15 +342,27 @@ __device__ __forceinline__ void strip_products(const StreamGemmArgs& p, Weights<
   }
 }
 
+// The leading arguments are in scalar registers when a wave starts (a compiler option for this file, fourteen words at most): the
+// others take 0.3 us to come from memory, and the first requests for weights wait for none of them.  (With those of ring_gemm.hip, us,
+// in memory / so: experts, 8 rows, eight of 512 x 512 15.0 / 14.2, 64 rows, four of 1024 x 2048 29.6 / 28.4.)
 template <int MT, int NF, Kind KIND>
-__global__ __launch_bounds__(kThreads, 2) void stream_gemm_kernel(StreamGemmArgs p) {
+__global__ __launch_bounds__(kThreads, 2) void stream_gemm_kernel(const uint16_t* lead_w, const uint16_t* lead_w2, long long w_batch, int n, int k,
+                                                                  int ksplit, int strips, const uint16_t* x, int rows, StreamGemmArgs p) {
+  p.w = lead_w;
+  p.w2 = lead_w2;
+  p.w_batch = w_batch;
+  p.n = n;
+  p.k = k;
+  p.ksplit = ksplit;
+  p.x = x;
+  p.m = rows;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, e = blockIdx.y;
   // (PAIR: four waves have gate rows, four the same rows of the up projection; with both in one wave, two fragments of
   // half as many k steps each, the short pieces of a row cost 5 - 9 % of the bandwidth unless rows are a power of two long)
   const int n_base = KIND == PAIR ? ((int)blockIdx.x * 4 + (wave & 3)) * 16 * NF : ((int)blockIdx.x * 8 + wave) * 16 * NF;
   Weights<NF, KIND> w;
-  w.start(p, n_base, e, wave, lane & 15, lane >> 4);
+  w.start(p, strips, n_base, e, wave, lane & 15, lane >> 4);
   // (chunks have the same order whatever their number of rows: KC is 256 in all of a kernel's variants)
   constexpr int KC = Cfg<MT, NF>::KC;
   const int first = w.template chunk<KC>(0);
@@ -400,8 +415,9 @@ hipError_t launch(const StreamGemmArgs& p, hipStream_t stream) {
   if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(stream_gemm_kernel<MT, NF, KIND>), smem, raised); e != hipSuccess)
     return e;
   constexpr int COLS = strip_rows(NF) / (KIND == PAIR ? 2 : 1);
-  hipLaunchKernelGGL((stream_gemm_kernel<MT, NF, KIND>), dim3((unsigned)((p.n + COLS - 1) / COLS), (unsigned)p.batch, (unsigned)p.ksplit),
-                     dim3(kThreads), smem, stream, p);
+  const int strips = (p.n + COLS - 1) / COLS;
+  hipLaunchKernelGGL((stream_gemm_kernel<MT, NF, KIND>), dim3((unsigned)strips, (unsigned)p.batch, (unsigned)p.ksplit), dim3(kThreads), smem, stream,
+                     p.w, p.w2, p.w_batch, p.n, p.k, p.ksplit, strips, p.x, p.m, p);
   return hipGetLastError();
 }
 
@@ -520,16 +536,21 @@ hipError_t launch_stream_gemm_down(const StreamGemmArgs& p, hipStream_t stream) 
 
 // ------------------------------------------------------------------ few output columns, few rows
 namespace {
+// What the products' first requests are made of stands in front as arguments of its own, in scalar registers when a wave starts (see
+// stream_gemm_kernel): the operands, their sizes, a workgroup's rows of W (strip, one of `strips`) and of X, parts of the k range
+// and places in a row of the grid.  The rest is for the end.
 struct NarrowArgs {
-  const uint16_t *x, *w, *residual;
+  const uint16_t* residual;
   float* y;
   uint16_t* out_bf16;
-  int m, n, k, strip, strips;
-  int rows;                // of X for a workgroup
-  int parts;               // of the k range
   float* part;             // parts > 1: their sums, one workgroup's behind the other's
   unsigned long long* words;  // and a word per strip and block, kWordStep apart
   unsigned long long tag;
+};
+struct NarrowCall {
+  const uint16_t *x, *w;
+  int m, n, k, strip, strips, rows, parts;
+  NarrowArgs end;
 };
 // Y = X . W^T (+ residual) for up to 128 rows and at most 64 columns per CU: a workgroup per CU has its strip of weight rows and
 // all of k, its waves every eighth (fourth) 64 of k each (128-byte lines of W's and X's rows), and adds the waves' sums up
@@ -570,33 +591,37 @@ struct NarrowCfg {
 };
 
 template <int RG, int NF, int WAVES>
-__global__ __launch_bounds__(64 * WAVES, WAVES / 4) void narrow_gemm_kernel(NarrowArgs p) {
+__global__ __launch_bounds__(64 * WAVES, WAVES / 4) void narrow_gemm_kernel(const uint16_t* w, const uint16_t* x, int m_all, int n, int k,
+                                                                            int strip_len, int strips, int rows, int parts, int places,
+                                                                            NarrowArgs p) {
   using C = NarrowCfg<RG, NF, WAVES>;
   constexpr int MT = C::MT, TILES = C::TILES, UK = C::UK, STEPS = UK / 32;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   floatx4* sums = reinterpret_cast<floatx4*>(smem);  // [wave][tile][lane], behind the loop
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, g = lane >> 4;
-  const int blk = blockIdx.x, id = xcd_place(blk, gridDim.x);  // (neighbours on one XCD share lines of Y)
+  const int blk = blockIdx.x, id = xcd_place(blk, places);  // (neighbours on one XCD share lines of Y)
   // (the blocks of X's rows are the grid's second dimension: what shares a strip's weights runs on one XCD, and in step)
-  const int halves = p.parts - 1, strip = id >> halves;  // (one or two parts)
-  if (strip >= p.strips) return;  // (the whole workgroup, see xcd_grid)
-  const int z = id - (strip << halves), row0 = (int)blockIdx.y * p.rows, m = min(p.m - row0, p.rows);
-  const int meet = strip + (int)blockIdx.y * p.strips;
-  const int n_base = strip * p.strip, n_end = min(n_base + p.strip, p.n);
-  const int units = (int)((unsigned)p.k / (unsigned)UK), u0 = (z * units) >> halves, u1 = ((z + 1) * units) >> halves;
+  const int halves = parts - 1, strip = id >> halves;  // (one or two parts)
+  if (strip >= strips) return;  // (the whole workgroup, see xcd_grid)
+  const int z = id - (strip << halves), row0 = (int)blockIdx.y * rows, m = min(m_all - row0, rows);
+  const int meet = strip + (int)blockIdx.y * strips;
+  const int n_base = strip * strip_len, n_end = min(n_base + strip_len, n);
+  const int units = (int)((unsigned)k / (unsigned)UK), u0 = (z * units) >> halves, u1 = ((z + 1) * units) >> halves;
   // (byte offsets from one scalar address each; rows past the end repeat the last one, and are not stored)
-  const uint16_t *w0 = dev::uniform_ptr(p.w + (long long)n_base * p.k), *x0 = dev::uniform_ptr(p.x + (long long)row0 * p.k);
+  const uint16_t *w0 = dev::uniform_ptr(w + (long long)n_base * k), *x0 = dev::uniform_ptr(x + (long long)row0 * k);
   const int lrow = lane / C::CHUNKS, lcol = 16 * (lane % C::CHUNKS ^ C::swizzle(lrow));
   unsigned wr[C::WI], xr[C::XI];
 #pragma unroll
-  for (int i = 0; i < C::WI; ++i) wr[i] = (unsigned)min(C::RPI * i + lrow, n_end - 1 - n_base) * (unsigned)p.k * 2u + lcol;
+  for (int i = 0; i < C::WI; ++i) wr[i] = (unsigned)min(C::RPI * i + lrow, n_end - 1 - n_base) * (unsigned)k * 2u + lcol;
 #pragma unroll
-  for (int i = 0; i < C::XI; ++i) xr[i] = (unsigned)min(C::RPI * i + lrow, m - 1) * (unsigned)p.k * 2u + lcol;
+  for (int i = 0; i < C::XI; ++i) xr[i] = (unsigned)min(C::RPI * i + lrow, m - 1) * (unsigned)k * 2u + lcol;
   unsigned char* ring = smem + wave * C::RING;
   const unsigned ring_at = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)ring;
   const int count = (u1 - u0 - wave + WAVES - 1) / WAVES;  // this wave's units
-  // (workgroups start at different units: see Weights::chunk)
-  const int rot = count > 0 ? (int)((5u * blk + (blk >> 3)) % (unsigned)count) : 0;
+  // (workgroups start at different units, see Weights::chunk: in 32nds of the wave's, five from XCD to XCD and one from each workgroup to the
+  // next there.  A remainder by the number of units, 5 blk + blk / 8, was 20 instructions in front of the first request, us, so / like
+  // this: 45 x 12288 x 4096 21.6 / 20.7, 80 x 8192 x 8192 35.1 / 33.9, 40 x 4096 x 8192 17.3 / 16.4, with the leading arguments in registers)
+  const int rot = count > 0 ? (int)__umulhi((unsigned)(5 * (blk & 7) + (blk >> 3)) << 27, (unsigned)count) : 0;
   auto ask = [&](int j, int slot) {
     const int u = j + rot, at = (u0 + wave + WAVES * (u < count ? u : u - count)) * UK;
     const unsigned to = ring_at + slot * (C::PER * 1024);
@@ -677,13 +702,13 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void narrow_gemm_kernel(Narr
       sums[(wave * TILES + f * MT + t) * 64 + lane] = v;
     }
   __syncthreads();
-  const bool vec = (p.n & 3) == 0 && (reinterpret_cast<size_t>(p.y) & 15) == 0 && (reinterpret_cast<size_t>(p.residual) & 7) == 0 &&
+  const bool vec = (n & 3) == 0 && (reinterpret_cast<size_t>(p.y) & 15) == 0 && (reinterpret_cast<size_t>(p.residual) & 7) == 0 &&
                    (reinterpret_cast<size_t>(p.out_bf16) & 7) == 0;
   auto finish = [&](int i, floatx4 v) {
     // (a lane of a tile has row lane % 16 of X and four consecutive columns)
     const int tile = i >> 6, row = (tile % MT) * 16 + (i & 15), col = n_base + (tile / MT) * 16 + ((i & 63) >> 4) * 4;
     if (row >= m || col >= n_end) return;
-    const long long at = (long long)(row0 + row) * p.n + col;
+    const long long at = (long long)(row0 + row) * n + col;
     if (vec && col + 4 <= n_end) {
       if (p.residual) {
         const uint2 q = *reinterpret_cast<const uint2*>(p.residual + at);
@@ -708,7 +733,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void narrow_gemm_kernel(Narr
     }
   };
   constexpr int QUADS = TILES * 64;  // of a workgroup's results
-  float* own_part = p.part + (size_t)(meet * p.parts + z) * (QUADS * 4);
+  float* own_part = p.part + (size_t)(meet * parts + z) * (QUADS * 4);
   for (int i = tid; i < QUADS; i += 64 * WAVES) {
     floatx4 part[WAVES];
 #pragma unroll
@@ -717,10 +742,10 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void narrow_gemm_kernel(Narr
     for (int d = 1; d < WAVES; d *= 2)  // (two and two: fewer roundings on the way of each)
 #pragma unroll
       for (int w = 0; w < WAVES; w += 2 * d) part[w] += part[w + d];
-    if (p.parts == 1) finish(i, part[0]);
+    if (parts == 1) finish(i, part[0]);
     else dev::store_through(own_part + 4 * i, __builtin_bit_cast(dev::store_u32x4, part[0]));
   }
-  if (p.parts == 1) return;
+  if (parts == 1) return;
   if (!dev::second_to_meet(p.words + (size_t)meet * kWordStep, p.tag, reinterpret_cast<int*>(smem))) return;
   const auto both = __builtin_amdgcn_make_buffer_rsrc(p.part + (size_t)meet * (2 * QUADS * 4), 0, 2 * QUADS * 16, 0x00020000);
   for (int i = tid; i < QUADS; i += 64 * WAVES) {  // (the same sum whoever comes second)
@@ -731,18 +756,19 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void narrow_gemm_kernel(Narr
 }
 
 template <int RG, int NF>
-hipError_t launch_narrow(const NarrowArgs& p, int blocks, hipStream_t stream) {
+hipError_t launch_narrow(const NarrowCall& p, int blocks, hipStream_t stream) {
   static LdsLimitRaised raised;
   constexpr int WAVES = narrow_waves(RG, NF);
   constexpr int smem = NarrowCfg<RG, NF, WAVES>::SMEM;
   if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(narrow_gemm_kernel<RG, NF, WAVES>), smem, raised); e != hipSuccess) return e;
   // (Where the row blocks of a strip ran on different XCDs, with 121 strips of 56, 80 x 6760 x 7296 took 40.7 us, and takes 36.9.)
   const dim3 grid((unsigned)xcd_grid(p.strips * p.parts, blocks), (unsigned)blocks);
-  hipLaunchKernelGGL((narrow_gemm_kernel<RG, NF, WAVES>), grid, dim3(64 * WAVES), smem, stream, p);
+  hipLaunchKernelGGL((narrow_gemm_kernel<RG, NF, WAVES>), grid, dim3(64 * WAVES), smem, stream, p.w, p.x, p.m, p.n, p.k, p.strip, p.strips, p.rows,
+                     p.parts, (int)grid.x, p.end);
   return hipGetLastError();
 }
 template <int RG>
-hipError_t launch_narrow_rows(const NarrowArgs& p, int blocks, hipStream_t stream) {
+hipError_t launch_narrow_rows(const NarrowCall& p, int blocks, hipStream_t stream) {
   switch ((p.strip + 15) / 16) {
     case 1: return launch_narrow<RG, 1>(p, blocks, stream);
     case 2: return launch_narrow<RG, 2>(p, blocks, stream);
@@ -780,13 +806,14 @@ size_t narrow_gemm_bytes(const NarrowPlan& plan) {
   return (size_t)plan.strips * plan.blocks * (kWordStep * 8 + plan.parts * tiles * 1024);
 }
 hipError_t launch_narrow_gemm(const StreamGemmArgs& g, const NarrowPlan& plan, void* workspace, hipStream_t stream) {
-  NarrowArgs p;
-  p.x = g.x; p.w = g.w; p.residual = g.residual; p.y = g.y; p.out_bf16 = g.out_bf16;
+  NarrowCall p;
+  p.x = g.x; p.w = g.w;
   p.m = g.m; p.n = g.n; p.k = g.k;
   p.strip = plan.strip; p.strips = plan.strips; p.rows = plan.rows; p.parts = plan.parts;
-  p.words = static_cast<unsigned long long*>(workspace);
-  p.part = reinterpret_cast<float*>(static_cast<char*>(workspace) + (size_t)plan.strips * plan.blocks * (kWordStep * 8));
-  p.tag = meeting_tag();
+  p.end.residual = g.residual; p.end.y = g.y; p.end.out_bf16 = g.out_bf16;
+  p.end.words = static_cast<unsigned long long*>(workspace);
+  p.end.part = reinterpret_cast<float*>(static_cast<char*>(workspace) + (size_t)plan.strips * plan.blocks * (kWordStep * 8));
+  p.end.tag = meeting_tag();
   switch (plan.rows / 8) {
     case 1: return launch_narrow_rows<1>(p, plan.blocks, stream);
     case 2: return launch_narrow_rows<2>(p, plan.blocks, stream);
