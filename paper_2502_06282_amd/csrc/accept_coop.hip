@@ -189,14 +189,15 @@ struct Walk {
   unsigned n_exch = 0, tag = 0;
   Table* tab = nullptr;
 
-  __device__ __forceinline__ Walk(const CoopParams& params, NodeTable& nodes)
-      : p(params), table(nodes), tid(threadIdx.x), lane(tid & 63), wave(__builtin_amdgcn_readfirstlane(tid >> 6)), W(p.W),
-        b(blockIdx.x / p.W), w(blockIdx.x % p.W), N(p.n_tree), V(p.vocab), tw(&p.trees[b].words) {}
+  __device__ __forceinline__ Walk(const CoopParams& params, NodeTable& nodes, int W, int b, int n_tree, int vocab)
+      : p(params), table(nodes), tid(threadIdx.x), lane(tid & 63), wave(__builtin_amdgcn_readfirstlane(tid >> 6)), W(W), b(b),
+        w((int)blockIdx.x - b * W), N(n_tree), V(vocab) {}
   __device__ __forceinline__ const float* row_of(int r) const { return p.logits + ((long long)b * (N + 1) + r) * V; }
   // What a walk starts from is asked for in one trip to memory: a value that the compiler knows to be the same in all lanes it
   // moves to a scalar register at once, and waits for everything asked for before it.  So these are different ones, to it,
   // until settle().
   __device__ __forceinline__ void load_words() {
+    tw = &p.trees[b].words;
     asm volatile("" : "=v"(lane_zero) : "0"(0));
     epoch = __hip_atomic_load(&tw->epoch + lane_zero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     uni_last = p.uniforms[(long long)b * (N + 1) + N + lane_zero];
@@ -206,23 +207,36 @@ struct Walk {
     epoch = (unsigned long long)hi << 32 | lo;
     uni_last = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(uni_last)));
   }
-  // by one wave, in front of a barrier
-  __device__ __forceinline__ void make_table() {
-    int par[2], tok[2], uni[2];
-    long long draft[2];
-    const int* rows = p.draft_row ? p.draft_row : p.parent;  // (asked for without a branch, see load_words)
+  // What the table is made of, nodes lane and lane + 64; and, by the same wave, the table, in front of a barrier
+  struct Nodes {
+    int par[2], tok[2], uni[2], draft[2];
+  };
+  __device__ __forceinline__ void ask_nodes(Nodes& x, const int* parent, const int* tokens, const float* uniforms, const int* draft_row) const {
+    const int* rows = draft_row ? draft_row : parent;  // (asked for without a branch, see load_words)
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int k = min(lane + 64 * h, N - 1);
       const long long at = (long long)b * N + k;
-      par[h] = p.parent[at];
-      tok[h] = p.tokens[at];
-      uni[h] = __float_as_int(p.uniforms[at + b]);
-      draft[h] = rows[at];
+      x.par[h] = parent[at];
+      x.tok[h] = tokens[at];
+      x.uni[h] = __float_as_int(uniforms[at + b]);
+      x.draft[h] = rows[at];
     }
+  }
+  __device__ __forceinline__ void make_table(Nodes x) {
     for (int i = lane; i <= N; i += 64) *reinterpret_cast<uint4*>(table.kids[i]) = make_uint4(0u, 0u, 0u, 0u);
     auto in_order = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };  // (LDS operations of a wave complete in order)
     in_order();
+    int par[2], tok[2], uni[2];
+    long long draft[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      asm volatile("" : "+v"(x.par[h]), "+v"(x.tok[h]), "+v"(x.uni[h]), "+v"(x.draft[h]));  // (else widened, and waited for, where it was asked for)
+      par[h] = x.par[h];
+      tok[h] = x.tok[h];
+      uni[h] = x.uni[h];
+      draft[h] = x.draft[h];
+    }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int k = lane + 64 * h, pa = par[h], tk = tok[h];
@@ -478,7 +492,9 @@ struct Walk {
 };
 
 template <int PER, int THREADS>
-__global__ __launch_bounds__(THREADS, 2) void walk_sample_coop_kernel(CoopParams params) {
+__global__ __launch_bounds__(THREADS, 2) void walk_sample_coop_kernel(const float* logits, const int* parent, const int* tokens,
+                                                                      const float* uniforms, const int* draft_row, int n_tree, int vocab, int W_lead,
+                                                                      unsigned mg_w, CoopParams params) {
   constexpr int SLICE = THREADS * PER, WAVES = THREADS / 64;
   __shared__ NodeTable nodes;
   __shared__ double red_d[2][WAVES];
@@ -490,7 +506,7 @@ __global__ __launch_bounds__(THREADS, 2) void walk_sample_coop_kernel(CoopParams
   __shared__ int got_ok[3];
   __shared__ double pv_s;
 
-  Walk wk(params, nodes);
+  Walk wk(params, nodes, W_lead, mg_w ? (int)__umulhi(blockIdx.x, mg_w) : (int)blockIdx.x, n_tree, vocab);
   const CoopParams& p = wk.p;
   const int tid = wk.tid, lane = wk.lane, wave = wk.wave, W = wk.W;
   const Walk::Part<PER> mine(wk.w * SLICE + tid * PER, wk.V);
@@ -506,10 +522,20 @@ __global__ __launch_bounds__(THREADS, 2) void walk_sample_coop_kernel(CoopParams
   // (The root's first child is node 0, since a parent comes before its children: its own row is row 1.)
   Candidate then;
   float lg[PER];
-  mine.load(lg, wk.row_of(0));  // (the first rows are on their way before anything else is known)
-  mine.load(then.lg, wk.row_of(1));
+  // The first rows are on their way before anything else is known, and the nodes: their addresses are made of the leading arguments,
+  // which are in scalar registers when a wave starts (a compiler option for this file, fourteen words at most).  The others take
+  // 0.3 us to come from memory, and which tree this is was a division.  (us, before / so: one tree of 60 nodes, 128256 entries 13.59 /
+  // 13.39, eight of 100, 32000 entries 21.44 / 21.21.)
+  Walk::Nodes first_nodes;
+  {
+    const float* row = logits + (long long)wk.b * (n_tree + 1) * vocab;
+    mine.load(lg, row);
+    mine.load(then.lg, row + vocab);
+    if (wave == 0) wk.ask_nodes(first_nodes, parent, tokens, uniforms, draft_row);
+    __builtin_amdgcn_sched_barrier(0);
+  }
   wk.load_words();
-  if (wave == 0) wk.make_table();
+  if (wave == 0) wk.make_table(first_nodes);
   wk.settle();
   __syncthreads();
   then.k = 0;
@@ -739,7 +765,7 @@ __global__ __launch_bounds__(kWideThreads) void walk_sample_wide_kernel(CoopPara
   __shared__ int got_ok;
   __shared__ double pv_s;
 
-  Walk wk(params, nodes);
+  Walk wk(params, nodes, params.W, (int)(blockIdx.x / (unsigned)params.W), params.n_tree, params.vocab);
   const CoopParams& p = wk.p;
   const int tid = wk.tid, lane = wk.lane, wave = wk.wave;
   const Walk::Part<PER> mine(wk.w * SLICE + tid * PER, wk.V);
@@ -749,7 +775,9 @@ __global__ __launch_bounds__(kWideThreads) void walk_sample_wide_kernel(CoopPara
   wk.load_words();
   const unsigned before = wk.finished();
   if (wave == 0) {
-    wk.make_table();
+    Walk::Nodes first_nodes;
+    wk.ask_nodes(first_nodes, p.parent, p.tokens, p.uniforms, p.draft_row);
+    wk.make_table(first_nodes);
     if (lane == 0) got_ok = before >> 16 == 0u;  // (where somebody of the tree has given up there is nothing to wait for)
   }
   wk.settle();
@@ -933,9 +961,12 @@ __global__ __launch_bounds__(kWideThreads) void walk_sample_wide_kernel(CoopPara
 constexpr int kCoopMaxTrees = 512;
 size_t accept_coop_bytes() { return (size_t)kCoopMaxTrees * sizeof(TreeBlock); }
 
+unsigned W_reciprocal(int W) { return W > 1 ? (unsigned)((1ull << 32) / (unsigned)W + 1) : 0u; }
+
 template <int PER, int THREADS>
 hipError_t launch_walk(const CoopParams& cp, int wgs, hipStream_t stream) {
-  hipLaunchKernelGGL((walk_sample_coop_kernel<PER, THREADS>), dim3((unsigned)wgs), dim3(THREADS), 0, stream, cp);
+  hipLaunchKernelGGL((walk_sample_coop_kernel<PER, THREADS>), dim3((unsigned)wgs), dim3(THREADS), 0, stream, cp.logits, cp.parent, cp.tokens,
+                     cp.uniforms, cp.draft_row, cp.n_tree, cp.vocab, cp.W, W_reciprocal(cp.W), cp);
   return hipGetLastError();
 }
 
