@@ -19,7 +19,7 @@
 // and of its partner in the other half-wave (16 cycles for 512 weights), of the weights as they are rounded.
 //
 // What bounds it: the vector instructions beside the matrix instructions, and the clock, which the card lowers under this
-// load (1.6 to 1.9 GHz).  A tile takes 1330 cycles, of which 1120 are matrix instructions.  Measured against the kernel of
+// load (1.5 to 1.9 GHz: with all of K and V in the caches a tile takes 0.88 us, with them in memory 0.9 - 1.0).  A tile takes 1330 cycles, of which 1120 are matrix instructions.  Measured against the kernel of
 // four waves with 32 rows: 8 sequences of 16384 keys, 8 KV heads, 800 rows 476 -> 399 us; 16 sequences of at most 4096 keys
 // in pages, 8 KV heads, 240 rows 70 -> 59 us; 29 sequences of 10023 keys, 46 nodes, D = 64 255 -> 178 us.
 #include <type_traits>
@@ -155,17 +155,26 @@ __device__ __forceinline__ Deal deal_pieces(int tiles, int batch, int splits, in
   const int hi = divided(longest + splits - 1, splits);
   const int lo = min(max((int)(total * __builtin_amdgcn_rcpf((float)places)), 1), hi);
   const int len = lane == 63 ? hi : lo + (int)((float)(hi - lo) * (float)lane * (1.f / 63.f));
+  // (tiles / len rounded up as in `divided`, the half unit and len - 1 brought along by the addition; without tiles 0, as len - 1/2 is less
+  // than len.  The quotient's error is below a quarter of a millionth of it, tiles and len together below 2^20: not half a unit.)
+  struct Cut {
+    float inv, up;
+    __device__ __forceinline__ explicit Cut(int len) : inv(__builtin_amdgcn_rcpf((float)len)), up(((float)len - 0.5f) * inv) {}
+    __device__ __forceinline__ int pieces(float tiles) const { return (int)fmaf(tiles, inv, up); }
+  };
+  const Cut cut(len);
+  const float tiles_f = (float)tiles;
   int count = 0;
   for (int i = 0; i < batch; i += 4)
 #pragma unroll
-    for (int k = 0; k < 4; ++k) count += divided(__builtin_amdgcn_readlane(tiles, i + k) + len - 1, len);
+    for (int k = 0; k < 4; ++k)
+      count += cut.pieces(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(tiles_f), i + k)));
   const int best = __builtin_amdgcn_readlane(len, __ffsll((long long)__ballot(count <= places)) - 1);
   Deal d;
-  d.pieces = tiles > 0 ? divided(tiles + best - 1, best) : 0;
-  d.first = 0;
-  for (int i = 0; i < batch; i += 4)
-#pragma unroll
-    for (int k = 0; k < 4; ++k) d.first += i + k < lane ? __builtin_amdgcn_readlane(d.pieces, i + k) : 0;
+  d.pieces = Cut(best).pieces(tiles_f);  // (the same operations: all together as many as were counted)
+  // (sums over the lanes in front: by lane moves.  Sequence by sequence the loop had a branch for each of them, and dealing sixteen took
+  // 1.75 us at the clock of a loaded card, 0.9 like this.)
+  d.first = dev::wave_scan(d.pieces) - d.pieces;
   return d;
 }
 
@@ -214,8 +223,15 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
     load_by_hand(L_raw, p.prefix_len + min(lane, p.B - 1));  // (lane i: sequence i's)
     const int order = div_mg(rest, p.mg_hkv);  // of the piece, or of the sequence
     kv = rest - order * p.Hkv;
-    if (order >= p.B * splits) return;  // padding workgroup
-    dev::wait_vm<0>();
+    if (order >= p.B * splits) {  // padding workgroup
+      dev::wait_vm<0>();
+      return;
+    }
+    // (the page table's first 32 KB, a line a thread, on their way into the L2 while the pieces are dealt)
+    int touched;
+    const long long last = (long long)p.B * p.max_blocks - 1;
+    load_by_hand(touched, PAGED ? p.block_table + (32 * tid < last ? 32 * tid : (int)last) : p.prefix_len);
+    dev::wait_vm<1>();
     asm volatile("" : "+v"(L_raw));
     const int len = bounded(L_raw);
     if (dealt) {
@@ -223,10 +239,12 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
       b = __popcll(__ballot(lane < p.B && d.first <= order)) - 1;
       split = order - __builtin_amdgcn_readlane(d.first, b);
       pieces = __builtin_amdgcn_readlane(d.pieces, b);
-      if (split >= pieces) return;  // (fewer pieces than places)
     } else {
       b = sequence_of_rank(len, p.B, order, lane);
     }
+    dev::wait_vm<0>();
+    asm volatile("" ::"v"(touched));
+    if (split >= pieces) return;  // (fewer pieces than places)
     L = __builtin_amdgcn_readlane(len, b);
     place0 = (order - split) * p.Hkv + kv;
     place_step = p.Hkv;
@@ -258,14 +276,6 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
     ts.t_begin = split * base + min(split, rem);
     ts.t_end = ts.t_begin + base + (split < rem ? 1 : 0);
   };
-  const unsigned ring_addr = (unsigned)(size_t)LDS_PTR(unsigned char, smem);
-  LaneChunks<D, kWideWaves> lc;
-  lane_chunks<D, kWideWaves>(lc, wave, lane, lane_column<D, kWideWaves>(wave, lane), ts);
-  const bool is_v = wave * N >= G_::NB;
-  lc.cache = uniform_ptr((is_v ? p.vc : p.kc) + (PAGED ? 0 : b * p.kc_sb) + (long long)kv * p.kc_sh);
-  lc.tree = uniform_ptr((is_v ? p.vt : p.kt) + b * p.kt_sb + (long long)kv * p.kt_sh);
-#pragma unroll
-  for (int i = 0; i < N; ++i) lc.lds[i] = (wave * N) / G_::NB * P_::HALF_BYTES + (wave * N + i) % G_::NB * 1024;
   set_range(L);
   int n = ts.t_end - ts.t_begin;
   bool bad_page = false;
@@ -292,19 +302,31 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
     }
     __syncthreads();
   };
-  // (the query rows come while the page ids do: behind them, and the transfers, they took 4.9 us of a call's first 10.8)
+  // (the query rows come while the page ids do: behind them, and the transfers, they took 4.9 us of a call's first 10.8; what the
+  // transfers need is worked out behind these requests)
   if (PAGED) ask_pages();
+  __builtin_amdgcn_sched_barrier(0);
   const int row0 = qtile * QROWS + wave * kWideRows;  // the wave's first query row
   u32x4 q_raw[kBlocks][DK];
   int parent_lo, parent_hi;  // of nodes lane and lane + 64
 #pragma unroll
   for (int r = 0; r < kBlocks; ++r) {
     const int mm = min(row0 + r * kWaveRows + c32, M - 1), node = div_mg(mm, p.mg_g);
-    const uint16_t* src = p.q + b * p.q_sb + node * p.q_st + (long long)(kv * G + (mm - node * G)) * p.q_sh + 8 * g;
+    const uint16_t* src = p.q + (unsigned)b * (unsigned long long)p.q_sb + (unsigned)node * (unsigned long long)p.q_st +
+                          (unsigned)(kv * G + (mm - node * G)) * (unsigned long long)p.q_sh + 8 * g;
     load_rows_by_hand(q_raw[r], src);
   }
   load_by_hand(parent_lo, p.parent + (long long)b * T + min(lane, T - 1));
   load_by_hand(parent_hi, p.parent + (long long)b * T + min(lane + 64, T - 1));
+  __builtin_amdgcn_sched_barrier(0);
+  const unsigned ring_addr = (unsigned)(size_t)LDS_PTR(unsigned char, smem);
+  LaneChunks<D, kWideWaves> lc;
+  lane_chunks<D, kWideWaves>(lc, wave, lane, lane_column<D, kWideWaves>(wave, lane), ts);
+  const bool is_v = wave * N >= G_::NB;
+  lc.cache = uniform_ptr((is_v ? p.vc : p.kc) + (PAGED ? 0 : (unsigned)b * (unsigned long long)p.kc_sb) + (unsigned)kv * (unsigned long long)p.kc_sh);
+  lc.tree = uniform_ptr((is_v ? p.vt : p.kt) + (unsigned)b * (unsigned long long)p.kt_sb + (unsigned)kv * (unsigned long long)p.kt_sh);
+#pragma unroll
+  for (int i = 0; i < N; ++i) lc.lds[i] = (wave * N) / G_::NB * P_::HALF_BYTES + (wave * N + i) % G_::NB * 1024;
   if (PAGED) {
     dev::wait_vm<ROW_LOADS>();
     fill_pages();
@@ -422,6 +444,10 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
     const float tmax = half_swap_max(max16(st.s[r])) * scale_log2;
     st.m[r] = st.m[r] == -INFINITY ? tmax : st.m[r];
     st.mu[r] = st.m[r] == -INFINITY ? 0.f : st.m[r];
+    // (no weights for rows past the end, which nobody stores: products with zeros take less power, and a long loop runs at the clock that
+    // power allows.  16 sequences of 60 nodes, four heads to one: 16 of 256 rows; us, without / with: up to 4096 keys in pages 59.2 /
+    // 58.3, with the pieces dealt faster, in one block 59.4 / 58.3; 8 of 4096 keys 50.9 / 50.5)
+    if (row0 + r * kWaveRows + c32 >= M) st.mu[r] = 1e30f;
   };
   const int n_full = min(max(L / kTileKeys - ts.t_begin, 0), n);  // tiles without a mask, the split's first ones
 
