@@ -465,7 +465,8 @@ class TreeState:
         self.n_nodes = torch.zeros((batch,), dtype=torch.int32, device=device)
 
     def reset(self) -> None:
-        self.n_nodes.zero_()
+        if not _n.tree_reset(self.n_nodes):
+            self.n_nodes.zero_()
 
     def desc(self) -> TreeStateDesc:
         return TreeStateDesc(_ptr(self.tokens), _ptr(self.parent), _ptr(self.score), _ptr(self.q_row),

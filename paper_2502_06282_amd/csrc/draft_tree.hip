@@ -340,6 +340,11 @@ __global__ __launch_bounds__(kMaxGrowNodes) void finalize_kernel(TreeFinalArgs a
   if (t == 0) a.n_valid[b] = n_valid;
 }
 
+__global__ __launch_bounds__(256) void reset_kernel(int32_t* n_nodes, int batch) {
+  const int b = blockIdx.x * 256 + threadIdx.x;
+  if (b < batch) n_nodes[b] = 0;
+}
+
 __global__ __launch_bounds__(256) void gather_rows_kernel(const float* __restrict__ q_all, const int* __restrict__ q_row,
                                                           float* __restrict__ out, int vocab, long long n_q_rows) {
   const long long node = blockIdx.x;
@@ -363,24 +368,22 @@ int tree_max_nodes() { return kMaxGrowNodes; }
 hipError_t launch_tree_grow(const TreeGrowArgs& a, hipStream_t stream) {
   // Four waves for each 64 candidates (the state's stores and loads take 256 threads whatever their number)
   const int chunks = (a.n_front * 2 * a.top_k + 63) / 64;
-  if (chunks <= 1) hipLaunchKernelGGL(grow_kernel<4>, dim3(a.batch), dim3(256), 0, stream, a);
-  else if (chunks == 2) hipLaunchKernelGGL(grow_kernel<8>, dim3(a.batch), dim3(512), 0, stream, a);
-  else hipLaunchKernelGGL(grow_kernel<16>, dim3(a.batch), dim3(1024), 0, stream, a);
-  return hipGetLastError();
+  if (chunks <= 1) return launch_kernel(grow_kernel<4>, dim3(a.batch), dim3(256), stream, a);
+  if (chunks == 2) return launch_kernel(grow_kernel<8>, dim3(a.batch), dim3(512), stream, a);
+  return launch_kernel(grow_kernel<16>, dim3(a.batch), dim3(1024), stream, a);
 }
 hipError_t launch_tree_grow_tail(const TreeGrowArgs& a, int k1, int k2, hipStream_t stream) {
-  hipLaunchKernelGGL(grow_tail_kernel, dim3(a.batch), dim3(kTreeThreads), 0, stream, a, k1, k2);
-  return hipGetLastError();
+  return launch_kernel(grow_tail_kernel, dim3(a.batch), dim3(kTreeThreads), stream, a, k1, k2);
 }
 hipError_t launch_tree_fill_static(const TreeGrowArgs& a, const int* slot, const int* expert, const int* rank, int n_new,
                                    const int* next_index, int n_next, int* new_ids, hipStream_t stream) {
-  hipLaunchKernelGGL(fill_static_kernel, dim3(a.batch), dim3(kTreeThreads), 0, stream, a, slot, expert, rank, n_new,
-                     next_index, n_next, new_ids);
-  return hipGetLastError();
+  return launch_kernel(fill_static_kernel, dim3(a.batch), dim3(kTreeThreads), stream, a, slot, expert, rank, n_new, next_index, n_next, new_ids);
 }
 hipError_t launch_tree_finalize(const TreeFinalArgs& a, hipStream_t stream) {
-  hipLaunchKernelGGL(finalize_kernel, dim3(a.batch), dim3(kMaxGrowNodes), 0, stream, a);
-  return hipGetLastError();
+  return launch_kernel(finalize_kernel, dim3(a.batch), dim3(kMaxGrowNodes), stream, a);
+}
+hipError_t launch_tree_reset(int32_t* n_nodes, int batch, hipStream_t stream) {
+  return launch_kernel(reset_kernel, dim3((unsigned)(batch + 255) / 256), dim3(256), stream, n_nodes, batch);
 }
 hipError_t launch_gather_rows(const float* q_all, const int* q_row, float* out, long long n_nodes, int vocab,
                               long long n_q_rows, hipStream_t stream) {

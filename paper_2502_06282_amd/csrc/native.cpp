@@ -18,7 +18,10 @@
 #include <string>
 
 #include <ATen/ATen.h>
+#include <ATen/functorch/BatchedTensorImpl.h>
 #include <ATen/hip/EmptyTensor.h>
+#include <c10/core/impl/TorchDispatchModeTLS.h>
+#include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
 #include <hip/hip_runtime.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -751,6 +754,24 @@ PyObject* tree_fill_static(Args& a) {  // state, candidates, slot, expert, rank,
         "jk_tree_fill_static");
   return pack(n_next ? wrap(std::move(out)) : none(), wrap(std::move(ids)));
 }
+// n_nodes -> whether it was cleared here: an ordinary tensor of the current device, which nobody traces or intercepts.  (zero_ takes 4.0 us
+// of a thread, this 3.05.)
+PyObject* tree_reset(Args& a) {
+  PyObject* o = a.next();
+  bool plain = THPVariable_CheckExact(o) && !c10::impl::TorchDispatchModeTLS::any_modes_set();
+  if (plain) {
+    const at::Tensor& n = THPVariable_Unpack(o);
+    plain = n.is_cuda() && n.has_storage() && !n.is_inference() && is_i32(n) && !n.unsafeGetTensorImpl()->is_python_dispatch() && !at::functorch::isBatchedTensor(n) &&
+            n.numel() > 0 && n.numel() <= INT32_MAX && n.get_device() == c10::hip::current_device();
+    if (plain) {
+      int32_t* counts = static_cast<int32_t*>(ptr(n));
+      const int batch = (int)n.numel();
+      void* stream = stream_handle(nullptr);
+      check(unlocked([&] { return jk::launch_tree_reset(counts, batch, static_cast<hipStream_t>(stream)) == hipSuccess ? JK_OK : JK_ERR_HIP; }), "tree_reset");
+    }
+  }
+  return PyBool_FromLong(plain);
+}
 PyObject* tree_finalize(Args& a) {  // state, n_keep, stream -> (tokens, parent, q_row, old_index, n_valid)
   const Py_ssize_t first = a.at;
   const TreeState t = read_tree_state(a);
@@ -814,7 +835,7 @@ PyMethodDef methods[] = {
     method<heads>("draft_heads"), method<prepare_heads>("prepare_draft_heads"),
     method<moe>("moe_experts"), method<prepare_moe>("prepare_moe_experts"),
     method<linear>("linear"), method<tree_grow>("tree_grow"), method<tree_grow_tail>("tree_grow_tail"),
-    method<tree_fill_static>("tree_fill_static"), method<tree_finalize>("tree_finalize"),
+    method<tree_fill_static>("tree_fill_static"), method<tree_finalize>("tree_finalize"), method<tree_reset>("tree_reset"),
     method<gather_draft_probs>("gather_draft_probs"), method<stream_of>("stream_handle"),
     {"set_error_class", set_error_class, METH_O, nullptr},
     {nullptr, nullptr, 0, nullptr}};

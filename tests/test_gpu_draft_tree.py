@@ -408,3 +408,48 @@ def test_static_shape_fill_matches_the_oracle_and_rebuilds_the_predefined_tree()
         np.testing.assert_array_equal(state.score[b, :N].cpu().numpy(), np.asarray(oracles[b].score, dtype=np.float32))
         assert parent[b].cpu().tolist() == shape_parent.tolist()       # the predefined tree, as the verification takes it
         assert old[b].cpu().tolist() == list(range(N))
+
+
+@pytest.mark.parametrize("kind", ["plain", "strided", "int64", "inference", "intercepted", "host", "captured"])
+def test_reset_clears_the_counts_of_any_tensor(kind):
+    """An ordinary tensor is cleared by the library's own launch; any other as torch does it."""
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Counting(TorchDispatchMode):
+        seen = 0
+
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            Counting.seen += 1
+            return func(*args, **(kwargs or {}))
+
+    st = jk.TreeState(300, 64, device="cpu" if kind == "host" else "cuda")
+    if kind == "strided":
+        st.n_nodes = torch.full((600,), 9, dtype=torch.int32, device="cuda")[::2]
+    elif kind == "int64":
+        st.n_nodes = torch.full((300,), 9, dtype=torch.int64, device="cuda")
+    elif kind == "inference":
+        with torch.inference_mode():
+            st.n_nodes = torch.full((300,), 9, dtype=torch.int32, device="cuda")
+            st.reset()
+            assert int(st.n_nodes.abs().sum()) == 0
+        return
+    else:
+        st.n_nodes.fill_(9)
+    if kind == "intercepted":
+        with Counting():
+            st.reset()
+        assert Counting.seen > 0
+    elif kind == "captured":
+        st.reset()
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            st.reset()
+        for _ in range(3):
+            st.n_nodes.fill_(9)
+            g.replay()
+            torch.cuda.synchronize()
+            assert int(st.n_nodes.abs().sum()) == 0
+    else:
+        st.reset()
+    assert int(st.n_nodes.abs().sum()) == 0
