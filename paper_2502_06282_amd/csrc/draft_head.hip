@@ -80,6 +80,7 @@ __global__ __launch_bounds__(64) void head_inputs_kernel(MixParams p) {
 // CUs; everything a thread needs is in its registers after one trip to memory:
 //   row_parts_kernel   per (row, part): maximum, sum of exp((x - max) / T), the part's k best
 //   row_whole_kernel   all of it, for short rows: one workgroup of 1024 threads per row
+//   row_stats_kernel   what row_finish_kernel does, where the product has left the statistics of each row's 128 entries
 //   row_finish_kernel  a workgroup per row first: the k best of the parts' candidates, their probabilities; then one per
 //                      (row, part): q = exp((x - max) / T) / Z (if asked for).  Each takes the row's maximum and
 //                      normaliser from the parts' pairs for itself.
@@ -98,6 +99,9 @@ struct SoftParams {
   unsigned long long* keys;  // [n_rows][parts][k]   candidates, best first (0: none)
   int n_rows, vocab, k, parts, part_len;  // part_len: entries per part, a multiple of 4
   float inv_temp;
+  const float2* stats;  // row_stats_kernel: [n_rows][blocks] (maximum, sum) of kStatColumns entries each, from the product
+  int blocks;
+  float scale_hi, scale_lo;  // (see StreamGemmArgs)
 };
 
 // Order of candidates - larger value first, equal values by increasing id - as one unsigned comparison: the value's bits
@@ -391,6 +395,182 @@ __global__ __launch_bounds__(kPartThreads) void row_finish_kernel(SoftParams p) 
   view.store(p.probs + (long long)row * V, val);
 }
 
+// ---- The product's workgroups leave the (maximum, sum) of each row's blocks of 128 entries, which are in their LDS for the result's sake: no
+// launch that reads all logits for them.  A workgroup of four waves takes a row's maximum and normaliser from the pairs, the
+// same operations in the same order everywhere.
+struct RowStats {
+  float m, inv_z;
+  float2 own[4];  // this thread's first blocks: tid, tid + 256, ...
+};
+struct RowStatsShared {
+  float top[4];
+  double sum[4];
+  float lane_max[kPartThreads];
+  float tau;
+};
+// LIST: also the k-th largest of 64 groups of blocks' maxima, in sh.tau (behind the caller's next barrier too)
+template <bool LIST>
+__device__ __forceinline__ RowStats row_stats(const SoftParams& p, const float2* ms, RowStatsShared& sh) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  RowStats s;
+  float top = -INFINITY;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int j = tid + kPartThreads * u;
+    s.own[u] = make_float2(-INFINITY, 0.f);
+    if (j < p.blocks) s.own[u] = ms[j];
+    top = fmaxf(top, s.own[u].x);
+  }
+  for (int j = tid + 4 * kPartThreads; j < p.blocks; j += kPartThreads) top = fmaxf(top, ms[j].x);
+  if (LIST) sh.lane_max[tid] = top;
+  top = dev::wave_max(top);
+  if (lane == 0) sh.top[wave] = top;
+  __syncthreads();
+  const float m = fmaxf(fmaxf(sh.top[0], sh.top[1]), fmaxf(sh.top[2], sh.top[3]));
+  s.m = m > -INFINITY ? m : 0.f;
+  double z = 0.0;  // (a block of -inf only: 0 times 0; of NaNs: NaN)
+  auto add = [&](float2 q) { z += (double)q.y * (double)dev::exp_scaled(q.x - s.m, p.scale_hi, p.scale_lo); };
+#pragma unroll
+  for (int u = 0; u < 4; ++u) add(s.own[u]);
+  for (int j = tid + 4 * kPartThreads; j < p.blocks; j += kPartThreads) add(ms[j]);
+  z = dev::wave_sum(z);
+  if (lane == 0) sh.sum[wave] = z;
+  if (LIST && wave == 0) {
+    const float t = wave_kth_largest(fmaxf(fmaxf(sh.lane_max[lane], sh.lane_max[lane + 64]), fmaxf(sh.lane_max[lane + 128], sh.lane_max[lane + 192])), p.k);
+    if (lane == 0) sh.tau = t;
+  }
+  __syncthreads();
+  s.inv_z = (float)(1.0 / ((sh.sum[0] + sh.sum[1]) + (sh.sum[2] + sh.sum[3])));
+  return s;
+}
+
+// The k best of a row: entries at or above the threshold, all in blocks whose maximum is; few blocks, and few entries, unless
+// there are many ties.  Then k rounds, each the largest key below the last winner's: of a block with no winner yet, its
+// maximum at its first place stands for its best key; the others, at most as many as there were winners, are looked through.
+__device__ __forceinline__ void row_stats_top_k(const SoftParams& p, int row) {
+  constexpr int kListed = 256;
+  __shared__ RowStatsShared sh;
+  __shared__ unsigned long long cand[kCandCap], sk[2][4];
+  __shared__ int list[kListed];
+  __shared__ int n_list, n_cand;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, K = p.k;
+  const float2* ms = p.stats + (long long)row * p.blocks;
+  const float* x = p.logits + (long long)row * p.vocab;
+  if (tid == 0) n_list = n_cand = 0;
+  const RowStats s = row_stats<true>(p, ms, sh);
+  auto put = [&](int rank, unsigned long long key) {  // (0: fewer than k candidates in the whole row)
+    p.tk_ids[(long long)row * K + rank] = key ? key_id(key) : 0;
+    p.tk_probs[(long long)row * K + rank] = key ? expf((key_value(key) - s.m) * p.inv_temp) * s.inv_z : 0.f;
+  };
+  auto entry = [&](int block, int e) {  // (past the end: -inf, as an impossible one)
+    const int i = block * kStatColumns + e;
+    return i < p.vocab ? x[i] : -INFINITY;
+  };
+  const float tau = sh.tau;
+  auto look = [&](int j, float top) {
+    if (!(top >= tau && top > -INFINITY)) return;
+    const int at = atomicAdd(&n_list, 1);
+    if (at < kListed) list[at] = j;
+  };
+#pragma unroll
+  for (int u = 0; u < 4; ++u) look(tid + kPartThreads * u, s.own[u].x);
+  for (int j = tid + 4 * kPartThreads; j < p.blocks; j += kPartThreads) look(j, ms[j].x);
+  __syncthreads();
+  const int listed = n_list;
+  if (listed <= kListed) {
+    constexpr int AT_ONCE = 4;
+    for (int i0 = wave; i0 < listed; i0 += 4 * AT_ONCE) {
+      int block[AT_ONCE];
+      float v[AT_ONCE][2];
+#pragma unroll
+      for (int u = 0; u < AT_ONCE; ++u) {  // (one past the list's end: its last once more, and not used)
+        block[u] = list[min(i0 + 4 * u, listed - 1)];
+        v[u][0] = entry(block[u], lane);
+        v[u][1] = entry(block[u], lane + 64);
+      }
+#pragma unroll
+      for (int u = 0; u < AT_ONCE; ++u)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          if (i0 + 4 * u < listed && v[u][h] >= tau && v[u][h] > -INFINITY) {
+            const int at = atomicAdd(&n_cand, 1);
+            if (at < kCandCap) cand[at] = key_of(v[u][h], block[u] * kStatColumns + lane + 64 * h);
+          }
+    }
+    __syncthreads();
+    const int nc = n_cand;
+    if (nc <= kCandCap) {
+      if (tid < K && tid >= nc) put(tid, 0ull);
+      rank_list(cand, nc, K, put);
+      return;
+    }
+  }
+  unsigned long long prev = ~0ull;
+  for (int round = 0; round < K; ++round) {
+    __syncthreads();  // (the list of the round before has been read)
+    if (tid == 0) n_list = 0;
+    __syncthreads();
+    unsigned long long best = 0ull;
+    for (int j = tid; j < p.blocks; j += kPartThreads) {
+      const float top = ms[j].x;
+      if (!(top > -INFINITY)) continue;
+      const unsigned long long first = key_of(top, j * kStatColumns);  // (none of the block's keys is larger)
+      if (first < prev) {
+        best = first > best ? first : best;
+      } else {
+        const int at = atomicAdd(&n_list, 1);
+        if (at < kListed) list[at] = j;
+      }
+    }
+    __syncthreads();
+    for (int i = wave; i < min(n_list, kListed); i += 4)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const float v = entry(list[i], lane + 64 * h);
+        const unsigned long long key = key_of(v, list[i] * kStatColumns + lane + 64 * h);
+        if (v > -INFINITY && key < prev && key > best) best = key;
+      }
+    best = wave_max_key(best);
+    if (lane == 0) sk[round & 1][wave] = best;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < 4; ++w) best = sk[round & 1][w] > best ? sk[round & 1][w] : best;
+    if (best != 0ull) {
+      const int j = key_id(best) / kStatColumns;
+      if (key_of(ms[j].x, j * kStatColumns) == best) {  // (a block without a winner: where its maximum is)
+        const unsigned want = (unsigned)(best >> 32);
+        const unsigned long long lo = __ballot(ordered_bits(entry(j, lane)) == want), hi = __ballot(ordered_bits(entry(j, lane + 64)) == want);
+        best = (best & ~0xFFFFFFFFull) | (unsigned)~(j * kStatColumns + (lo ? __ffsll((long long)lo) - 1 : 63 + __ffsll((long long)hi)));
+      }
+    }
+    if (tid == 0) put(round, best);
+    if (best == 0ull) {  // (nothing comes after it)
+      if (tid > round && tid < K) put(tid, 0ull);
+      return;
+    }
+    prev = best;
+  }
+}
+
+// Bound by the trips to memory of its longer chain (the k best: pairs, blocks that matter, their entries), which starts first.
+// 20 rows of 128256: 9.4 us under the tracer, 7.2 without the distributions, where the two launches took 7.05 and 6.95.
+template <int PT>
+__global__ __launch_bounds__(kPartThreads) void row_stats_kernel(SoftParams p) {
+  if ((int)blockIdx.x < p.n_rows) {
+    row_stats_top_k(p, blockIdx.x);
+    return;
+  }
+  __shared__ RowStatsShared sh;
+  const int at = (int)blockIdx.x - p.n_rows, row = at / p.parts, part = at % p.parts;
+  const PartView<PT> view(p, part, on16(p.logits) && on16(p.probs));
+  float val[PT];
+  view.load(p.logits + (long long)row * p.vocab, val);  // on its way while the row's pairs are reduced
+  const RowStats s = row_stats<false>(p, p.stats + (long long)row * p.blocks, sh);
+#pragma unroll
+  for (int i = 0; i < PT; ++i) val[i] = expf((val[i] - s.m) * p.inv_temp) * s.inv_z;
+  view.store(p.probs + (long long)row * p.vocab, val);
+}
+
 // A short row whole: a workgroup of 16 waves has it in its registers, so that nothing is left for a second launch and no logit
 // is read twice.  The second launch was 2 - 4 us of 12 - 30 (calls of 1024 columns, us, before / now: 4 tokens and 4000 entries 14.9 /
 // 11.7, 8000 13.9 / 11.7; 64 tokens and 16 384 entries 30.5 / 26.5).
@@ -478,6 +658,10 @@ __global__ __launch_bounds__(kRowThreads) void row_whole_kernel(SoftParams p) {
 template <int PT>
 hipError_t launch_rows(const SoftParams& p, hipStream_t stream) {
   const unsigned parts = (unsigned)(p.n_rows * p.parts);
+  if (p.stats) {
+    hipLaunchKernelGGL(row_stats_kernel<PT>, dim3(p.n_rows + (p.probs ? parts : 0u)), dim3(kPartThreads), 0, stream, p);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(row_parts_kernel<PT>, dim3(parts), dim3(kPartThreads), 0, stream, p);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   hipLaunchKernelGGL(row_finish_kernel<PT>, dim3(p.n_rows + (p.probs ? parts : 0u)), dim3(kPartThreads), 0, stream, p);
@@ -748,7 +932,7 @@ int capped_ksplit(int m, int n, int k, int split_ns, double* ns = nullptr) {
 }
 
 struct RowPlan {
-  bool ring;
+  bool ring, stats;  // stats: the product leaves the rows' statistics (row_stats_kernel)
   int per_thread, parts, part_len, ksplit;
   size_t x_bytes, ms_off, key_off, part_off, total;
 };
@@ -772,6 +956,13 @@ RowPlan row_plan(int rows, int d_model, int vocab) {
   r.ring = ring_gemm_takes_heads((int)m, vocab);
   r.ksplit = r.ring ? 1 : capped_ksplit((int)m, vocab, d_model, 0);
   r.total = r.part_off + (r.ksplit > 1 ? up((size_t)r.ksplit * m * vocab * 4) : 0);
+  // The statistics come with the product wherever a workgroup has all of k and mixes its rows itself (launch_stream_gemm_heads).
+  // Calls, us, in two launches over the rows (long rows) or one (short ones) / like this: 2 rows of 32000 x 4096 53.9 / 51.6, 20
+  // of 128256 x 4096 189.5 / 186.9, 40 of 32000 x 4096 57.8 / 54.6, of 60000 x 1024 40.8 / 38.7, 64 of 128256 x 4096 221 / 218, 2 of 30000 x 512 16.7 /
+  // 14.5; short rows, 64 of 32000 x 4096 61.7 / 61.3, of 20000 x 1024 22.6 / 22.3, 40 of 16384 x 4096 35.7 / 35.7.  The distributions' distance from
+  // those in 64 bits of the same logits, mean of 480 - 768 rows: 0.94 - 0.995 times what it was in seven shapes at temperatures of 0.3 - 2.5.
+  r.stats = !r.ring && r.ksplit == 1 && m <= 64;
+  if (r.stats) r.total = r.ms_off + up(m * ((vocab + kStatColumns - 1) / kStatColumns) * 8);
   return r;
 }
 
@@ -802,6 +993,9 @@ hipError_t launch_draft_heads(const DraftHeadsArgs& a, hipStream_t stream) {
   g.m = m; g.n = a.vocab; g.k = a.d_model;
   g.ksplit = rp.ksplit; g.y_split = (long long)m * a.vocab; g.batch = 1;
   g.s_top = a.s_top; g.heads_mode = a.mode; g.alpha = a.alpha; g.beta = a.beta;
+  g.stats = rp.stats ? reinterpret_cast<float2*>(ws + rp.ms_off) : nullptr;
+  const double scale = (double)(1.0f / a.temperature) * 1.4426950408889634;
+  g.scale_hi = (float)scale; g.scale_lo = (float)(scale - (double)g.scale_hi);
   e = rp.ring ? launch_ring_gemm_heads(g, stream) : mixes ? launch_stream_gemm_heads(g, stream) : launch_stream_gemm(g, stream);
   if (e != hipSuccess) return e;
 
@@ -811,7 +1005,9 @@ hipError_t launch_draft_heads(const DraftHeadsArgs& a, hipStream_t stream) {
   sp.keys = reinterpret_cast<unsigned long long*>(ws + rp.key_off);
   sp.n_rows = m; sp.vocab = a.vocab; sp.k = a.top_k; sp.parts = rp.parts; sp.part_len = rp.part_len;
   sp.inv_temp = 1.0f / a.temperature;
-  if (rows_whole(m, a.vocab)) {
+  sp.stats = g.stats; sp.blocks = (a.vocab + kStatColumns - 1) / kStatColumns;
+  sp.scale_hi = g.scale_hi; sp.scale_lo = g.scale_lo;
+  if (!rp.stats && rows_whole(m, a.vocab)) {
     sp.parts = 1;
     sp.part_len = (a.vocab + 3) / 4 * 4;
     auto whole = [&](auto per_thread) {

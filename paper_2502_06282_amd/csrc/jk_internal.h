@@ -187,7 +187,11 @@ struct StreamGemmArgs {
   const float* s_top;
   int heads_mode;
   float alpha, beta;
+  // output heads, undivided k range: or null, [m][blocks of kStatColumns columns]: a block's maximum and sum of exp((x - maximum) inv_temp)
+  float2* stats;
+  float scale_hi, scale_lo;  // inv_temp log2(e), in two parts
 };
+constexpr int kStatColumns = 128;
 int stream_gemm_ksplit(int m, int n, int k, int batch, bool pair, int split_ns, double* ns = nullptr);
 hipError_t launch_stream_gemm(const StreamGemmArgs& p, hipStream_t stream);       // m <= 256
 // plain products with `finish` of few rows and columns, in one launch

@@ -49,6 +49,28 @@ __device__ __forceinline__ double wave_sum(double v) {
   v += swap64(v, true);
   return v;
 }
+// 2^(d (hi + lo)) for d <= 0: the whole part of the exponent apart, the rest of it exact to the last place but one product's rounding, so
+// that what the instruction itself rounds is all there is
+__device__ __forceinline__ float exp_scaled(float d, float hi, float lo) {
+  const float n = __builtin_rintf(fmaxf(d * hi, -300.f));
+  const float e = __builtin_ldexpf(__builtin_amdgcn_exp2f(fmaf(d, lo, fmaf(d, hi, -n))), (int)n);
+  return d == -INFINITY ? 0.f : e;
+}
+// Over the 32 lanes of each half of a wave, in all of them
+__device__ __forceinline__ float half_max(float v) {
+  v = fmaxf(v, __int_as_float(dpp<0xB1>(__float_as_int(v))));
+  v = fmaxf(v, __int_as_float(dpp<0x4E>(__float_as_int(v))));
+  v = fmaxf(v, __int_as_float(dpp<0x141>(__float_as_int(v))));
+  v = fmaxf(v, __int_as_float(dpp<0x140>(__float_as_int(v))));
+  return fmaxf(v, __uint_as_float(other16(__float_as_uint(v), __lane_id() & 16)));
+}
+__device__ __forceinline__ float half_sum(float v) {
+  v += __int_as_float(dpp<0xB1>(__float_as_int(v)));
+  v += __int_as_float(dpp<0x4E>(__float_as_int(v)));
+  v += __int_as_float(dpp<0x141>(__float_as_int(v)));
+  v += __int_as_float(dpp<0x140>(__float_as_int(v)));
+  return v + __uint_as_float(other16(__float_as_uint(v), __lane_id() & 16));
+}
 // Inclusive sums over the lanes: rows of 16 by shifts, then the rows' totals broadcast into the rows behind them
 __device__ __forceinline__ int wave_scan(int v) {
   v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1

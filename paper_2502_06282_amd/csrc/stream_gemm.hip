@@ -16,6 +16,7 @@
 
 #include "jk_device.h"
 #include "jk_internal.h"
+#include "jk_wave.h"
 #include "xcd_grid.h"
 
 namespace jk {
@@ -252,6 +253,23 @@ __device__ __forceinline__ void strip_products(const StreamGemmArgs& p, Weights<
   float* tile = reinterpret_cast<float*>(xbuf);
   const int n0 = (int)blockIdx.x * OUT;
   auto y_row = [&](int row) { return (long long)(KIND == PAIR || KIND == DOWN ? list[row] : row); };
+  // The statistics of a row's 128 columns, by half a wave with four columns a lane: the launch that read all logits again for them was 7 us of
+  // 190 (20 rows, 128256 x 4096).  (With expf this was 0.7 us of every workgroup's end, and those of a CU come one after the other.)
+  auto stats_of = [&](floatx4 v, int row, int col) {
+    float top = -INFINITY, sum = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[e] = n0 + col + e < p.n ? v[e] : -INFINITY;
+      top = fmaxf(top, v[e]);
+    }
+    top = dev::half_max(top);
+    const float from = top > -INFINITY ? top : 0.f;  // (nothing sensible to subtract)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sum += dev::exp_scaled(v[e] - from, p.scale_hi, p.scale_lo);
+    sum = dev::half_sum(sum);
+    const int blocks = (p.n + kStatColumns - 1) / kStatColumns, at = (n0 + col) / kStatColumns;
+    if ((lane & 31) == 0 && at < blocks) p.stats[(long long)row * blocks + at] = make_float2(top, sum);
+  };
   // emit4 (emit1): element offset in the output, and where its four values (its value) are in LDS
   auto put = [&](auto emit4, auto emit1) {
 #pragma unroll
@@ -277,6 +295,12 @@ __device__ __forceinline__ void strip_products(const StreamGemmArgs& p, Weights<
           if (n0 + col < p.n) emit1(y_row(16 * t0 + row) * p.n + n0 + col, tile + row * LDO + col);
         }
       }
+      if constexpr (KIND == HEADS)  // (half waves at a time: all lanes that a move between lanes asks take part)
+        if (p.stats)
+          for (int i = tid; i < rows * (OUT / 4); i += kThreads) {
+            const int row = i / (OUT / 4), col = i % (OUT / 4) * 4;
+            stats_of(*reinterpret_cast<const floatx4*>(tile + row * LDO + col), 16 * t0 + row, col);
+          }
     }
   };
   const long long part = (long long)blockIdx.z * p.y_split;

@@ -278,3 +278,40 @@ def test_short_rows_are_taken_whole(rows, d, vocab):
     lg, q, tk, tp = _check(x, top_k=top_k, exact=True)
     np.testing.assert_array_equal(tk, np.broadcast_to(np.arange(top_k), tk.shape))
     np.testing.assert_allclose(q, 1.0 / vocab, rtol=3e-5)
+
+
+@pytest.mark.parametrize("vocab", [5, 127, 128, 129, 1001, 16385, 33000, 131072, 140003])
+@pytest.mark.parametrize("rows", [1, 9, 32])
+def test_rows_by_the_statistics_of_their_blocks(rows, vocab):
+    """Strips of weights leave each row's (maximum, sum) of 128 entries: whole and ragged blocks, more of them than threads hold, one entry
+    more than a block.  Then choices that the short list of entries cannot hold: the same maximum once in every block, at
+    another place in each (its lowest ids win, behind a few larger ones), all entries equal, and rows with fewer finite entries than candidates."""
+    tune("ring_gemm", 0)
+    if rows == 32 and vocab > 33000:
+        vocab = 65537
+    top_k = min(vocab, 16)
+    x = _exact_inputs(rows, 128, vocab, vocab)
+    _check(x, top_k=top_k, temperature=0.7, exact=True)
+    _check(draft_head_inputs(rows, 128, vocab, seed=rows), top_k=top_k, temperature=1.3)
+    x["f_top"][:] = 1.0
+    one = np.zeros_like(x["w_head"][0])
+    one[0] = 2.0
+    x["w_head"][:] = 0.0
+    for b in range(0, vocab, 128):
+        x["w_head"][min(b + (37 * b // 128) % 128, vocab - 1)] = one
+    _check(x, top_k=top_k, exact=True)
+    for i, v in enumerate((vocab // 2, vocab - 1, vocab // 3)):
+        x["w_head"][v] = one * (4.0 + i)
+    _check(x, top_k=top_k, exact=True)
+    x["w_head"][:] = 0.0
+    lg, q, tk, tp = _check(x, top_k=top_k, exact=True)
+    np.testing.assert_array_equal(tk, np.broadcast_to(np.arange(top_k), tk.shape))
+    x["w_head"][:, 0] = -np.inf
+    alive = sorted({vocab - 1, vocab // 2, 0})
+    x["w_head"][alive] = one
+    lg, q, tk, tp = _call(x, top_k=top_k)
+    n = len(alive)
+    assert (tk[:, :, :n] == np.array(alive)).all() and (tk[:, :, n:] == 0).all() and (tp[:, :, n:] == 0).all()
+    np.testing.assert_allclose(tp[:, :, :n], 1.0 / n, rtol=1e-6)
+    np.testing.assert_allclose(q[:, :, alive], 1.0 / n, rtol=1e-6)
+    assert np.count_nonzero(q) == 2 * rows * n
