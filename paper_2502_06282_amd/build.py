@@ -21,7 +21,7 @@ SOURCES = ["api.cpp", "tva_f32.hip", "tva_combine.hip", "accept.hip", "accept_co
 UNIT_FLAGS = {"tva_wide.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 # kernel arguments in scalar registers when a wave starts: the leading ones, fourteen words at most
 PRELOAD = ["-mllvm", "-amdgpu-kernarg-preload-count=14"]
-for _unit in ("accept.hip", "accept_coop.hip", "stream_gemm.hip", "ring_gemm.hip"):
+for _unit in ("accept.hip", "accept_coop.hip", "draft_head.hip", "stream_gemm.hip", "ring_gemm.hip"):
     UNIT_FLAGS[_unit] = PRELOAD
 MERGES = 7  # tva_bf16.hip is compiled once for each of its merges (JK_MERGE)
 # packed-fp32 code generation is switched off for all device code

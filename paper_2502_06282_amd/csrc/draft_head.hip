@@ -555,7 +555,10 @@ __device__ __forceinline__ void row_stats_top_k(const SoftParams& p, int row) {
 // Bound by the trips to memory of its longer chain (the k best: pairs, blocks that matter, their entries), which starts first.
 // 20 rows of 128256: 9.4 us under the tracer, 7.2 without the distributions, where the two launches took 7.05 and 6.95.
 template <int PT>
-__global__ __launch_bounds__(kPartThreads) void row_stats_kernel(SoftParams p) {
+__global__ __launch_bounds__(kPartThreads) void row_stats_kernel(const float2* stats, float* logits, int n_rows, int parts, int blocks, int vocab, int part_len,
+                                                                 int k, float* probs, SoftParams p) {
+  p.stats = stats; p.logits = logits; p.probs = probs;
+  p.n_rows = n_rows; p.parts = parts; p.blocks = blocks; p.vocab = vocab; p.part_len = part_len; p.k = k;
   if ((int)blockIdx.x < p.n_rows) {
     row_stats_top_k(p, blockIdx.x);
     return;
@@ -659,7 +662,8 @@ template <int PT>
 hipError_t launch_rows(const SoftParams& p, hipStream_t stream) {
   const unsigned parts = (unsigned)(p.n_rows * p.parts);
   if (p.stats) {
-    hipLaunchKernelGGL(row_stats_kernel<PT>, dim3(p.n_rows + (p.probs ? parts : 0u)), dim3(kPartThreads), 0, stream, p);
+    hipLaunchKernelGGL(row_stats_kernel<PT>, dim3(p.n_rows + (p.probs ? parts : 0u)), dim3(kPartThreads), 0, stream, p.stats, p.logits, p.n_rows, p.parts, p.blocks,
+                       p.vocab, p.part_len, p.k, p.probs, p);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(row_parts_kernel<PT>, dim3(parts), dim3(kPartThreads), 0, stream, p);
@@ -676,14 +680,6 @@ bool rows_whole(int n_rows, int vocab) { return vocab <= kRowThreads * (n_rows >
 // ------------------------------------------------------------------ router and experts (Eq. 2, 3, 5)
 constexpr int kMaxExperts = 64;
 
-struct RouterParams {
-  const uint16_t* u;          // [rows][d] bf16
-  const uint16_t* centroids;  // [n_experts][d] bf16
-  float* s_top;               // [rows][2]
-  int* idx;                   // [rows][2]
-  int rows, d, n_experts;
-};
-
 // One workgroup per row: the router scores s_j = softmax_j(u . e_j) (Eq. 2; fp32), of which it picks the two largest
 // (Eq. 5, K = 2, ties to the lower expert; a NaN score ranks below every other, so that the row always names two
 // different experts that exist - the experts' outputs are addressed with them).  Bound by a trip to memory: a wave asks for up to
@@ -692,23 +688,27 @@ struct RouterParams {
 // four experts of 2048 - 29.0 and 29.4), and the softmax and both maxima are taken across the
 // lanes of a wave, by lane moves.  (By shuffles, and with eight pieces whatever the row's length; and select_kernel with its
 // scores asked for, and waited for, in front of the results: 18 drawn calls of experts 1.036 times as long, small ones 1.04 - 1.09.)
-__global__ __launch_bounds__(256) void router_kernel(RouterParams p) {
+// u [rows][d] and centroids [n_experts][d] bf16, s_top and idx [rows][2].  (These kernels' arguments are in scalar registers when a wave
+// starts, a compiler option for this file, fourteen words at most: from memory they took 0.3 us of each.  Calls, us, so / like this: 8 rows,
+// eight experts of 512 x 512 14.2 / 13.9, 64 rows, four of 1024 x 2048 28.8 / 28.0, 40 rows, eight of 4096 x 4096 144.2 / 143.7; heads of one token,
+// 30000 x 512 14.4 / 13.8.)
+__global__ __launch_bounds__(256) void router_kernel(const uint16_t* u_rows, const uint16_t* centroids, int d, int n_experts, float* s_top, int* idx) {
   __shared__ float score[kMaxExperts];
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const u32x4* src = reinterpret_cast<const u32x4*>(p.u + (long long)row * p.d);
+  const u32x4* src = reinterpret_cast<const u32x4*>(u_rows + (long long)row * d);
   // (as many pieces of 1 KB a time as a row has: 2, 4 or 8)
   auto scores = [&](auto n_pieces) {
-    for (int j0 = wave; j0 < p.n_experts; j0 += 8) {  // two experts per pass: their loads share the trip to memory
-      const bool two = j0 + 4 < p.n_experts;
-      const u32x4* e0 = reinterpret_cast<const u32x4*>(p.centroids + (long long)j0 * p.d);
-      const u32x4* e1 = reinterpret_cast<const u32x4*>(p.centroids + (long long)(two ? j0 + 4 : j0) * p.d);
+    for (int j0 = wave; j0 < n_experts; j0 += 8) {  // two experts per pass: their loads share the trip to memory
+      const bool two = j0 + 4 < n_experts;
+      const u32x4* e0 = reinterpret_cast<const u32x4*>(centroids + (long long)j0 * d);
+      const u32x4* e1 = reinterpret_cast<const u32x4*>(centroids + (long long)(two ? j0 + 4 : j0) * d);
       float acc0 = 0.f, acc1 = 0.f;
       constexpr int PIECES = decltype(n_pieces)::value;
-      for (int c0 = 0; c0 < p.d / 8; c0 += 64 * PIECES) {
+      for (int c0 = 0; c0 < d / 8; c0 += 64 * PIECES) {
         u32x4 a[PIECES], b0[PIECES], b1[PIECES];
 #pragma unroll
         for (int u = 0; u < PIECES; ++u) {
-          const int c = min(c0 + 64 * u + lane, p.d / 8 - 1);
+          const int c = min(c0 + 64 * u + lane, d / 8 - 1);
           a[u] = src[c];
           b0[u] = e0[c];
           b1[u] = e1[c];
@@ -716,7 +716,7 @@ __global__ __launch_bounds__(256) void router_kernel(RouterParams p) {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < PIECES; ++u) {
-          if (c0 + 64 * u + lane >= p.d / 8) break;
+          if (c0 + 64 * u + lane >= d / 8) break;
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             acc0 += bf16_lo(a[u][i]) * bf16_lo(b0[u][i]) + bf16_hi(a[u][i]) * bf16_hi(b0[u][i]);
@@ -732,23 +732,23 @@ __global__ __launch_bounds__(256) void router_kernel(RouterParams p) {
       }
     }
   };
-  if (p.d <= 1024) scores(std::integral_constant<int, 2>());
-  else if (p.d <= 2048) scores(std::integral_constant<int, 4>());
+  if (d <= 1024) scores(std::integral_constant<int, 2>());
+  else if (d <= 2048) scores(std::integral_constant<int, 4>());
   else scores(std::integral_constant<int, 8>());
   __syncthreads();
   if (wave != 0) return;
   // (at most 64 experts; a lane without one has key 0, which loses to every expert's key, a NaN's 0 above ~id included)
-  const float mine = lane < p.n_experts ? score[lane] : -INFINITY;
-  const unsigned long long key = lane >= p.n_experts ? 0ull : mine == mine ? key_of(mine, lane) : (unsigned long long)(unsigned)~lane;
+  const float mine = lane < n_experts ? score[lane] : -INFINITY;
+  const unsigned long long key = lane >= n_experts ? 0ull : mine == mine ? key_of(mine, lane) : (unsigned long long)(unsigned)~lane;
   const int i1 = key_id(wave_max_key(key)), i2 = key_id(wave_max_key(lane == i1 ? 0ull : key));
   auto score_of = [&](int i) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mine), __builtin_amdgcn_readfirstlane(i))); };
   const float v1 = score_of(i1), v2 = score_of(i2);
-  const float z = dev::wave_sum(lane < p.n_experts ? expf(mine - v1) : 0.f);
+  const float z = dev::wave_sum(lane < n_experts ? expf(mine - v1) : 0.f);
   if (lane == 0) {
-    p.s_top[2 * row] = 1.f / z;
-    p.s_top[2 * row + 1] = expf(v2 - v1) / z;
-    p.idx[2 * row] = i1;
-    p.idx[2 * row + 1] = i2;
+    s_top[2 * row] = 1.f / z;
+    s_top[2 * row + 1] = expf(v2 - v1) / z;
+    idx[2 * row] = i1;
+    idx[2 * row + 1] = i2;
   }
 }
 
@@ -791,57 +791,41 @@ __device__ __forceinline__ void sum_two(const float* pa, const float* pb, int ks
   }
 }
 
-struct ActParams {
-  const float *g, *up;  // [ksplit][2 rows][f] fp32: partial gate and up projections, by choice
-  uint16_t* h;          // [2 rows][f] bf16
-  int f, ksplit;
-  long long split_stride;
-};
-
 // h = silu(gate) * up, rounded to bf16 once, where the k range of the two projections was divided (an undivided one
-// has this in its epilogue)
-__global__ __launch_bounds__(256) void gated_act_kernel(ActParams p) {
+// has this in its epilogue).  gate and up [ksplit][2 rows][f] fp32, partial, by choice; h [2 rows][f] bf16
+__global__ __launch_bounds__(256) void gated_act_kernel(const float* gate, const float* up, int f, int ksplit, long long split_stride, uint16_t* h) {
   const int c = blockIdx.y * 256 + threadIdx.x;
-  if (c >= p.f / 4) return;
-  const long long at = (long long)blockIdx.x * p.f;
+  if (c >= f / 4) return;
+  const long long at = (long long)blockIdx.x * f;
   floatx4 a, b;
-  sum_two(p.g + at + 4 * c, p.up + at + 4 * c, p.ksplit, p.split_stride, a, b);
+  sum_two(gate + at + 4 * c, up + at + 4 * c, ksplit, split_stride, a, b);
   float o[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) o[i] = a[i] / (1.f + expf(-a[i])) * b[i];
   uint2 w;
   w.x = bf16_bits_rne(o[0]) | (bf16_bits_rne(o[1]) << 16);
   w.y = bf16_bits_rne(o[2]) | (bf16_bits_rne(o[3]) << 16);
-  reinterpret_cast<uint2*>(p.h + at)[c] = w;
+  reinterpret_cast<uint2*>(h + at)[c] = w;
 }
 
-struct SelectParams {
-  int ksplit;
-  long long split_stride;
-  const float* y;     // [ksplit][rows][2][d] fp32: the chosen experts' (partial) outputs
-  const uint16_t* u;  // [rows][d] bf16
-  const float* s_top;
-  uint16_t* f_top;    // [rows][2][d] bf16
-  uint16_t* f_mix;    // [rows][d] bf16 or null
-  int d;
-};
-
-// f_top[r][k] = Expert_{idx[r][k]}(u_r) + u_r; f_mix[r] = sum_k s_k Expert_k(u_r) + u_r (Eq. 3)
-__global__ __launch_bounds__(256) void select_kernel(SelectParams p) {
+// f_top[r][k] = Expert_{idx[r][k]}(u_r) + u_r; f_mix[r] = sum_k s_k Expert_k(u_r) + u_r (Eq. 3).  y_parts [ksplit][rows][2][d] fp32: the chosen
+// experts' (partial) outputs; u_rows [rows][d], f_top [rows][2][d], f_mix [rows][d] (or null) bf16
+__global__ __launch_bounds__(256) void select_kernel(const float* y_parts, const uint16_t* u_rows, const float* s_top, int d, int ksplit, long long split_stride,
+                                                     uint16_t* f_top, uint16_t* f_mix) {
   const int row = blockIdx.x;
   const int c = blockIdx.y * 256 + threadIdx.x;
-  if (c >= p.d / 4) return;
-  const uint2 uu = reinterpret_cast<const uint2*>(p.u + (long long)row * p.d)[c];
+  if (c >= d / 4) return;
+  const uint2 uu = reinterpret_cast<const uint2*>(u_rows + (long long)row * d)[c];
   int lane_zero = 0;
   asm volatile("" : "+v"(lane_zero));  // (a vector load: the scalar one's trip was waited for in front of the results')
-  const float s1 = p.s_top[2 * row + lane_zero], s2 = p.s_top[2 * row + 1 + lane_zero];
-  const float* y = p.y + (long long)(2 * row) * p.d + 4 * c;
+  const float s1 = s_top[2 * row + lane_zero], s2 = s_top[2 * row + 1 + lane_zero];
+  const float* y = y_parts + (long long)(2 * row) * d + 4 * c;
   floatx4 a, b;
-  if (p.ksplit == 1) {
+  if (ksplit == 1) {
     a = *reinterpret_cast<const floatx4*>(y);
-    b = *reinterpret_cast<const floatx4*>(y + p.d);
+    b = *reinterpret_cast<const floatx4*>(y + d);
   } else {
-    sum_two(y, y + p.d, p.ksplit, p.split_stride, a, b);
+    sum_two(y, y + d, ksplit, split_stride, a, b);
   }
   const floatx4 u = {bf16_lo(uu.x), bf16_hi(uu.x), bf16_lo(uu.y), bf16_hi(uu.y)};
   auto store = [&](uint16_t* dst, const floatx4& v) {
@@ -850,9 +834,9 @@ __global__ __launch_bounds__(256) void select_kernel(SelectParams p) {
     w.y = bf16_bits_rne(v[2]) | (bf16_bits_rne(v[3]) << 16);
     reinterpret_cast<uint2*>(dst)[c] = w;
   };
-  store(p.f_top + ((long long)row * 2 + 0) * p.d, a + u);
-  store(p.f_top + ((long long)row * 2 + 1) * p.d, b + u);
-  if (p.f_mix) store(p.f_mix + (long long)row * p.d, s1 * a + s2 * b + u);
+  store(f_top + ((long long)row * 2 + 0) * d, a + u);
+  store(f_top + ((long long)row * 2 + 1) * d, b + u);
+  if (f_mix) store(f_mix + (long long)row * d, s1 * a + s2 * b + u);
 }
 
 struct MoePlan {
@@ -888,39 +872,33 @@ MoePlan moe_plan(int rows, int d, int f, int n) {
 
 
 // ------------------------------------------------------------------ plain linear layer
-struct LinFinishParams {
-  const float* part;        // [ksplit][m*n]
-  const uint16_t* residual; // [m*n] bf16 or null
-  float* out_f32;           // or null
-  uint16_t* out_bf16;       // or null
-  long long n_out;
-  int ksplit;
-};
-__global__ __launch_bounds__(256) void linear_finish_kernel(LinFinishParams p) {
+// part [ksplit][m*n] fp32; residual (or null) and out_bf16 (or null) [m*n] bf16, out_f32 (or null) fp32
+__global__ __launch_bounds__(256) void linear_finish_kernel(const float* part, const uint16_t* residual, long long n_out, int ksplit, float* out_f32,
+                                                            uint16_t* out_bf16) {
   const long long i = ((long long)blockIdx.x * 256 + threadIdx.x) * 4;
-  if (i >= p.n_out) return;
-  const bool vec = (p.n_out & 3) == 0 && (reinterpret_cast<size_t>(p.residual) & 7) == 0 && (reinterpret_cast<size_t>(p.out_bf16) & 7) == 0 &&
-                   (reinterpret_cast<size_t>(p.out_f32) & 15) == 0;
+  if (i >= n_out) return;
+  const bool vec = (n_out & 3) == 0 && (reinterpret_cast<size_t>(residual) & 7) == 0 && (reinterpret_cast<size_t>(out_bf16) & 7) == 0 &&
+                   (reinterpret_cast<size_t>(out_f32) & 15) == 0;
   if (vec) {
     uint2 q = {0u, 0u};
-    if (p.residual) q = *reinterpret_cast<const uint2*>(p.residual + i);
-    floatx4 v = sum_parts(p.part + i, p.ksplit, p.n_out);
-    if (p.residual) v += floatx4{bf16_lo(q.x), bf16_hi(q.x), bf16_lo(q.y), bf16_hi(q.y)};
-    if (p.out_f32) *reinterpret_cast<floatx4*>(p.out_f32 + i) = v;
-    if (p.out_bf16) {
+    if (residual) q = *reinterpret_cast<const uint2*>(residual + i);
+    floatx4 v = sum_parts(part + i, ksplit, n_out);
+    if (residual) v += floatx4{bf16_lo(q.x), bf16_hi(q.x), bf16_lo(q.y), bf16_hi(q.y)};
+    if (out_f32) *reinterpret_cast<floatx4*>(out_f32 + i) = v;
+    if (out_bf16) {
       uint2 w;
       w.x = bf16_bits_rne(v[0]) | (bf16_bits_rne(v[1]) << 16);
       w.y = bf16_bits_rne(v[2]) | (bf16_bits_rne(v[3]) << 16);
-      *reinterpret_cast<uint2*>(p.out_bf16 + i) = w;
+      *reinterpret_cast<uint2*>(out_bf16 + i) = w;
     }
     return;
   }
-  for (long long j = i; j < i + 4 && j < p.n_out; ++j) {
-    float v = p.part[j];
-    for (int z = 1; z < p.ksplit; ++z) v += p.part[j + z * p.n_out];
-    if (p.residual) v += bf16_lo(p.residual[j]);
-    if (p.out_f32) p.out_f32[j] = v;
-    if (p.out_bf16) p.out_bf16[j] = (uint16_t)bf16_bits_rne(v);
+  for (long long j = i; j < i + 4 && j < n_out; ++j) {
+    float v = part[j];
+    for (int z = 1; z < ksplit; ++z) v += part[j + z * n_out];
+    if (residual) v += bf16_lo(residual[j]);
+    if (out_f32) out_f32[j] = v;
+    if (out_bf16) out_bf16[j] = (uint16_t)bf16_bits_rne(v);
   }
 }
 
@@ -1040,17 +1018,15 @@ hipError_t launch_moe_experts(const MoeArgs& a, hipStream_t stream) {
   const MoePlan mp = moe_plan(a.rows, a.d_model, a.d_ff, a.n_experts);
   char* ws = static_cast<char*>(a.workspace);
   hipError_t e;
-  RouterParams rp;
-  rp.u = static_cast<const uint16_t*>(a.u); rp.centroids = static_cast<const uint16_t*>(a.centroids);
-  rp.s_top = a.s_top; rp.idx = a.expert_idx;
-  rp.rows = a.rows; rp.d = a.d_model; rp.n_experts = a.n_experts;
-  hipLaunchKernelGGL(router_kernel, dim3(a.rows), dim3(256), 0, stream, rp);
+  const uint16_t* u = static_cast<const uint16_t*>(a.u);
+  hipLaunchKernelGGL(router_kernel, dim3(a.rows), dim3(256), 0, stream, u, static_cast<const uint16_t*>(a.centroids), a.d_model, a.n_experts, a.s_top,
+                     a.expert_idx);
   if ((e = hipGetLastError()) != hipSuccess) return e;
 
   // Each expert runs for the rows that chose it only
   uint16_t* h = reinterpret_cast<uint16_t*>(ws + mp.h_off);
   StreamGemmArgs g{};
-  g.x = rp.u; g.m = a.rows; g.n = a.d_ff; g.k = a.d_model;
+  g.x = u; g.m = a.rows; g.n = a.d_ff; g.k = a.d_model;
   g.batch = a.n_experts; g.w_batch = (long long)a.d_ff * a.d_model;
   g.sel = a.expert_idx;
   g.ksplit = mp.split1; g.y_split = (long long)a.rows * 2 * a.d_ff;
@@ -1062,10 +1038,8 @@ hipError_t launch_moe_experts(const MoeArgs& a, hipStream_t stream) {
   }
   if ((e = mp.ring1 ? launch_ring_gemm_pair(g, mp.rows, mp.used, stream) : launch_stream_gemm_pair(g, stream)) != hipSuccess) return e;  // gate and up projections of all experts
   if (mp.split1 > 1) {
-    ActParams ap;
-    ap.g = g.y; ap.up = g.y2; ap.h = h;
-    ap.f = a.d_ff; ap.ksplit = mp.split1; ap.split_stride = g.y_split;
-    hipLaunchKernelGGL(gated_act_kernel, dim3(2 * a.rows, (unsigned)((a.d_ff / 4 + 255) / 256)), dim3(256), 0, stream, ap);
+    hipLaunchKernelGGL(gated_act_kernel, dim3(2 * a.rows, (unsigned)((a.d_ff / 4 + 255) / 256)), dim3(256), 0, stream, g.y, g.y2, a.d_ff, mp.split1,
+                       g.y_split, h);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   StreamGemmArgs o{};
@@ -1076,12 +1050,8 @@ hipError_t launch_moe_experts(const MoeArgs& a, hipStream_t stream) {
   o.w = static_cast<const uint16_t*>(a.w_down); o.y = reinterpret_cast<float*>(ws + mp.y_off);
   if ((e = mp.ring2 ? launch_ring_gemm_down(o, mp.rows, mp.used, stream) : launch_stream_gemm_down(o, stream)) != hipSuccess) return e;
 
-  SelectParams sp;
-  sp.y = o.y; sp.u = rp.u; sp.s_top = a.s_top;
-  sp.f_top = static_cast<uint16_t*>(a.f_top); sp.f_mix = static_cast<uint16_t*>(a.f_mix);
-  sp.d = a.d_model;
-  sp.ksplit = mp.split2; sp.split_stride = o.y_split;
-  hipLaunchKernelGGL(select_kernel, dim3(a.rows, (unsigned)((a.d_model / 4 + 255) / 256)), dim3(256), 0, stream, sp);
+  hipLaunchKernelGGL(select_kernel, dim3(a.rows, (unsigned)((a.d_model / 4 + 255) / 256)), dim3(256), 0, stream, o.y, u, a.s_top, a.d_model, mp.split2,
+                     o.y_split, static_cast<uint16_t*>(a.f_top), static_cast<uint16_t*>(a.f_mix));
   return hipGetLastError();
 }
 
@@ -1145,10 +1115,9 @@ hipError_t launch_linear(const LinearArgs& a, hipStream_t stream) {
   g.y = static_cast<float*>(a.workspace);
   hipError_t e = launch_stream_gemm(g, stream);
   if (e != hipSuccess) return e;
-  LinFinishParams fp;
-  fp.part = g.y; fp.residual = static_cast<const uint16_t*>(a.residual); fp.out_f32 = a.out_f32;
-  fp.out_bf16 = static_cast<uint16_t*>(a.out_bf16); fp.n_out = (long long)a.m * a.n; fp.ksplit = lp.ksplit;
-  hipLaunchKernelGGL(linear_finish_kernel, dim3((unsigned)((fp.n_out + 1023) / 1024)), dim3(256), 0, stream, fp);
+  const long long n_out = (long long)a.m * a.n;
+  hipLaunchKernelGGL(linear_finish_kernel, dim3((unsigned)((n_out + 1023) / 1024)), dim3(256), 0, stream, g.y, static_cast<const uint16_t*>(a.residual),
+                     n_out, lp.ksplit, a.out_f32, static_cast<uint16_t*>(a.out_bf16));
   return hipGetLastError();
 }
 
