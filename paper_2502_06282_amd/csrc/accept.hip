@@ -306,17 +306,16 @@ __global__ __launch_bounds__(THREADS) void greedy_kernel(const float* logits, in
 }
 
 template <int THREADS>
-void launch_greedy(const AcceptArgs& a, const GreedyParams& p, int chunk, int parts, hipStream_t stream) {
+hipError_t launch_greedy(const AcceptArgs& a, const GreedyParams& p, int chunk, int parts, hipStream_t stream) {
   const int rows = a.batch * (a.n_tree + 1), loads = (chunk + THREADS * 4 - 1) / (THREADS * 4);
   const unsigned mg_rows = (unsigned)((1ull << 32) / (unsigned)(a.n_tree + 1) + 1);  // (rows of a tree: at least two)
   auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(parts, rows), dim3(THREADS), 0, stream, a.logits, a.vocab, chunk, mg_rows, a.n_tree, a.parent, a.tokens, parts,
-                       rows, p);
+    return launch_kernel(kernel, dim3(parts, rows), dim3(THREADS), 0, stream, a.logits, a.vocab, chunk, mg_rows, a.n_tree, a.parent, a.tokens, parts,
+                         rows, p);
   };
-  if (loads <= 1) launch(greedy_kernel<THREADS, 1>);
-  else if (loads <= 2) launch(greedy_kernel<THREADS, 2>);
-  else if (loads <= 4) launch(greedy_kernel<THREADS, 4>);
-  else launch(greedy_kernel<THREADS, kGreedyLoads>);
+  if (loads <= 1) return launch(greedy_kernel<THREADS, 1>);
+  if (loads <= 2) return launch(greedy_kernel<THREADS, 2>);
+  return loads <= 4 ? launch(greedy_kernel<THREADS, 4>) : launch(greedy_kernel<THREADS, kGreedyLoads>);
 }
 
 // ------------------------------------------------------------------ sampling walk
@@ -488,9 +487,7 @@ hipError_t launch_accept(const AcceptArgs& a, hipStream_t stream) {
     gp.words = reinterpret_cast<unsigned*>(ws + w.words);
     gp.out_path = a.out_path; gp.out_len = a.out_len; gp.out_bonus = a.out_bonus;
     gp.err = reinterpret_cast<unsigned*>(ws);
-    if (threads == 1024) launch_greedy<1024>(a, gp, chunk, parts, stream);
-    else launch_greedy<512>(a, gp, chunk, parts, stream);
-    return hipGetLastError();
+    return threads == 1024 ? launch_greedy<1024>(a, gp, chunk, parts, stream) : launch_greedy<512>(a, gp, chunk, parts, stream);
   }
   if (a.mode == JK_GREEDY) {
     hipLaunchKernelGGL(row_reduce_kernel<false>, grid, dim3(256), 0, stream, a.logits, a.vocab, 1.0, pmax, pidx,

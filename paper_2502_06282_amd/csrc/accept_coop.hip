@@ -965,16 +965,14 @@ unsigned W_reciprocal(int W) { return W > 1 ? (unsigned)((1ull << 32) / (unsigne
 
 template <int PER, int THREADS>
 hipError_t launch_walk(const CoopParams& cp, int wgs, hipStream_t stream) {
-  hipLaunchKernelGGL((walk_sample_coop_kernel<PER, THREADS>), dim3((unsigned)wgs), dim3(THREADS), 0, stream, cp.logits, cp.parent, cp.tokens,
+  return launch_kernel(walk_sample_coop_kernel<PER, THREADS>, dim3((unsigned)wgs), dim3(THREADS), 0, stream, cp.logits, cp.parent, cp.tokens,
                      cp.uniforms, cp.draft_row, cp.n_tree, cp.vocab, cp.W, W_reciprocal(cp.W), cp);
-  return hipGetLastError();
 }
 
 template <int PER>
 hipError_t launch_wide(CoopParams cp, const dev::AloneParams& alone, int wgs, hipStream_t stream) {
   if (tuning().spin_limit < 0) cp.spin_limit = kWideSpinLimit;
-  hipLaunchKernelGGL(walk_sample_wide_kernel<PER>, dim3((unsigned)wgs), dim3(kWideThreads), 0, stream, cp, alone);
-  return hipGetLastError();
+  return launch_kernel(walk_sample_wide_kernel<PER>, dim3((unsigned)wgs), dim3(kWideThreads), 0, stream, cp, alone);
 }
 
 bool accept_coop_plan(int batch, int vocab, int cus, int* W, int* slice) {
@@ -1042,9 +1040,8 @@ hipError_t launch_stream_read(const void* src, size_t bytes, void* sink, hipStre
   const size_t n = bytes / 16;
   if (n == 0) return hipSuccess;
   const unsigned grid = (unsigned)((n + 1023) / 1024 < 16384 ? (n + 1023) / 1024 : 16384);  // ~4 chunks per thread
-  hipLaunchKernelGGL(stream_read_kernel, dim3(grid), dim3(256), 0, stream, static_cast<const probe_u32x4*>(src), n,
+  return launch_kernel(stream_read_kernel, dim3(grid), dim3(256), 0, stream, static_cast<const probe_u32x4*>(src), n,
                      static_cast<unsigned*>(sink));
-  return hipGetLastError();
 }
 
 // zero fill as a kernel (safe inside HIP-graph capture, unlike a memset node)
@@ -1055,8 +1052,7 @@ hipError_t launch_zero_fill(void* p, size_t bytes, hipStream_t stream) {
   const size_t n = bytes / 8;
   if (n == 0) return hipSuccess;
   const unsigned grid = (unsigned)((n + 255) / 256 < 1024 ? (n + 255) / 256 : 1024);
-  hipLaunchKernelGGL(zero_fill_kernel, dim3(grid), dim3(256), 0, stream, static_cast<unsigned long long*>(p), n);
-  return hipGetLastError();
+  return launch_kernel(zero_fill_kernel, dim3(grid), dim3(256), 0, stream, static_cast<unsigned long long*>(p), n);
 }
 
 }  // namespace jk

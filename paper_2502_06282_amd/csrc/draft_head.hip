@@ -662,14 +662,12 @@ template <int PT>
 hipError_t launch_rows(const SoftParams& p, hipStream_t stream) {
   const unsigned parts = (unsigned)(p.n_rows * p.parts);
   if (p.stats) {
-    hipLaunchKernelGGL(row_stats_kernel<PT>, dim3(p.n_rows + (p.probs ? parts : 0u)), dim3(kPartThreads), 0, stream, p.stats, p.logits, p.n_rows, p.parts, p.blocks,
+    return launch_kernel(row_stats_kernel<PT>, dim3(p.n_rows + (p.probs ? parts : 0u)), dim3(kPartThreads), 0, stream, p.stats, p.logits, p.n_rows, p.parts, p.blocks,
                        p.vocab, p.part_len, p.k, p.probs, p);
-    return hipGetLastError();
   }
   hipLaunchKernelGGL(row_parts_kernel<PT>, dim3(parts), dim3(kPartThreads), 0, stream, p);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  hipLaunchKernelGGL(row_finish_kernel<PT>, dim3(p.n_rows + (p.probs ? parts : 0u)), dim3(kPartThreads), 0, stream, p);
-  return hipGetLastError();
+  return launch_kernel(row_finish_kernel<PT>, dim3(p.n_rows + (p.probs ? parts : 0u)), dim3(kPartThreads), 0, stream, p);
 }
 
 // Rows of up to 16 entries a thread whole; longer ones only where there are so many that parts would not spread them over more CUs (what a
@@ -960,8 +958,7 @@ hipError_t launch_draft_heads(const DraftHeadsArgs& a, hipStream_t stream) {
   const bool mixes = rp.ring || m <= 64;  // the product makes its rows itself (see launch_stream_gemm_heads)
   hipError_t e = hipSuccess;
   if (!mixes) {
-    hipLaunchKernelGGL(head_inputs_kernel, dim3((unsigned)(((long long)a.rows * (a.d_model / 8) + 63) / 64)), dim3(64), 0, stream, mp);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = launch_kernel(head_inputs_kernel, dim3((unsigned)(((long long)a.rows * (a.d_model / 8) + 63) / 64)), dim3(64), 0, stream, mp)) != hipSuccess) return e;
   }
 
   const uint16_t *x = mixes ? mp.f_top : reinterpret_cast<const uint16_t*>(ws), *w = static_cast<const uint16_t*>(a.w_head);
@@ -989,8 +986,7 @@ hipError_t launch_draft_heads(const DraftHeadsArgs& a, hipStream_t stream) {
     sp.parts = 1;
     sp.part_len = (a.vocab + 3) / 4 * 4;
     auto whole = [&](auto per_thread) {
-      hipLaunchKernelGGL(row_whole_kernel<decltype(per_thread)::value>, dim3((unsigned)m), dim3(kRowThreads), 0, stream, sp);
-      return hipGetLastError();
+      return launch_kernel(row_whole_kernel<decltype(per_thread)::value>, dim3((unsigned)m), dim3(kRowThreads), 0, stream, sp);
     };
     switch ((a.vocab + 4 * kRowThreads - 1) / (4 * kRowThreads)) {  // (four entries a thread more take 0.5 us: 4 tokens and 9000 entries in 12 instead of 16 13.8 / 13.3)
       case 1: return whole(std::integral_constant<int, 4>());
@@ -1019,9 +1015,8 @@ hipError_t launch_moe_experts(const MoeArgs& a, hipStream_t stream) {
   char* ws = static_cast<char*>(a.workspace);
   hipError_t e;
   const uint16_t* u = static_cast<const uint16_t*>(a.u);
-  hipLaunchKernelGGL(router_kernel, dim3(a.rows), dim3(256), 0, stream, u, static_cast<const uint16_t*>(a.centroids), a.d_model, a.n_experts, a.s_top,
-                     a.expert_idx);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if ((e = launch_kernel(router_kernel, dim3(a.rows), dim3(256), 0, stream, u, static_cast<const uint16_t*>(a.centroids), a.d_model, a.n_experts, a.s_top,
+                     a.expert_idx)) != hipSuccess) return e;
 
   // Each expert runs for the rows that chose it only
   uint16_t* h = reinterpret_cast<uint16_t*>(ws + mp.h_off);
@@ -1038,9 +1033,8 @@ hipError_t launch_moe_experts(const MoeArgs& a, hipStream_t stream) {
   }
   if ((e = mp.ring1 ? launch_ring_gemm_pair(g, mp.rows, mp.used, stream) : launch_stream_gemm_pair(g, stream)) != hipSuccess) return e;  // gate and up projections of all experts
   if (mp.split1 > 1) {
-    hipLaunchKernelGGL(gated_act_kernel, dim3(2 * a.rows, (unsigned)((a.d_ff / 4 + 255) / 256)), dim3(256), 0, stream, g.y, g.y2, a.d_ff, mp.split1,
-                       g.y_split, h);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = launch_kernel(gated_act_kernel, dim3(2 * a.rows, (unsigned)((a.d_ff / 4 + 255) / 256)), dim3(256), 0, stream, g.y, g.y2, a.d_ff, mp.split1,
+                       g.y_split, h)) != hipSuccess) return e;
   }
   StreamGemmArgs o{};
   o.x = h; o.m = a.rows; o.n = a.d_model; o.k = a.d_ff;
@@ -1050,9 +1044,8 @@ hipError_t launch_moe_experts(const MoeArgs& a, hipStream_t stream) {
   o.w = static_cast<const uint16_t*>(a.w_down); o.y = reinterpret_cast<float*>(ws + mp.y_off);
   if ((e = mp.ring2 ? launch_ring_gemm_down(o, mp.rows, mp.used, stream) : launch_stream_gemm_down(o, stream)) != hipSuccess) return e;
 
-  hipLaunchKernelGGL(select_kernel, dim3(a.rows, (unsigned)((a.d_model / 4 + 255) / 256)), dim3(256), 0, stream, o.y, u, a.s_top, a.d_model, mp.split2,
+  return launch_kernel(select_kernel, dim3(a.rows, (unsigned)((a.d_model / 4 + 255) / 256)), dim3(256), 0, stream, o.y, u, a.s_top, a.d_model, mp.split2,
                      o.y_split, static_cast<uint16_t*>(a.f_top), static_cast<uint16_t*>(a.f_mix));
-  return hipGetLastError();
 }
 
 namespace {
@@ -1116,9 +1109,8 @@ hipError_t launch_linear(const LinearArgs& a, hipStream_t stream) {
   hipError_t e = launch_stream_gemm(g, stream);
   if (e != hipSuccess) return e;
   const long long n_out = (long long)a.m * a.n;
-  hipLaunchKernelGGL(linear_finish_kernel, dim3((unsigned)((n_out + 1023) / 1024)), dim3(256), 0, stream, g.y, static_cast<const uint16_t*>(a.residual),
+  return launch_kernel(linear_finish_kernel, dim3((unsigned)((n_out + 1023) / 1024)), dim3(256), 0, stream, g.y, static_cast<const uint16_t*>(a.residual),
                      n_out, lp.ksplit, a.out_f32, static_cast<uint16_t*>(a.out_bf16));
-  return hipGetLastError();
 }
 
 }  // namespace jk

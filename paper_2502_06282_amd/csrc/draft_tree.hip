@@ -368,22 +368,22 @@ int tree_max_nodes() { return kMaxGrowNodes; }
 hipError_t launch_tree_grow(const TreeGrowArgs& a, hipStream_t stream) {
   // Four waves for each 64 candidates (the state's stores and loads take 256 threads whatever their number)
   const int chunks = (a.n_front * 2 * a.top_k + 63) / 64;
-  if (chunks <= 1) return launch_kernel(grow_kernel<4>, dim3(a.batch), dim3(256), stream, a);
-  if (chunks == 2) return launch_kernel(grow_kernel<8>, dim3(a.batch), dim3(512), stream, a);
-  return launch_kernel(grow_kernel<16>, dim3(a.batch), dim3(1024), stream, a);
+  if (chunks <= 1) return launch_kernel(grow_kernel<4>, dim3(a.batch), dim3(256), 0, stream, a);
+  if (chunks == 2) return launch_kernel(grow_kernel<8>, dim3(a.batch), dim3(512), 0, stream, a);
+  return launch_kernel(grow_kernel<16>, dim3(a.batch), dim3(1024), 0, stream, a);
 }
 hipError_t launch_tree_grow_tail(const TreeGrowArgs& a, int k1, int k2, hipStream_t stream) {
-  return launch_kernel(grow_tail_kernel, dim3(a.batch), dim3(kTreeThreads), stream, a, k1, k2);
+  return launch_kernel(grow_tail_kernel, dim3(a.batch), dim3(kTreeThreads), 0, stream, a, k1, k2);
 }
 hipError_t launch_tree_fill_static(const TreeGrowArgs& a, const int* slot, const int* expert, const int* rank, int n_new,
                                    const int* next_index, int n_next, int* new_ids, hipStream_t stream) {
-  return launch_kernel(fill_static_kernel, dim3(a.batch), dim3(kTreeThreads), stream, a, slot, expert, rank, n_new, next_index, n_next, new_ids);
+  return launch_kernel(fill_static_kernel, dim3(a.batch), dim3(kTreeThreads), 0, stream, a, slot, expert, rank, n_new, next_index, n_next, new_ids);
 }
 hipError_t launch_tree_finalize(const TreeFinalArgs& a, hipStream_t stream) {
-  return launch_kernel(finalize_kernel, dim3(a.batch), dim3(kMaxGrowNodes), stream, a);
+  return launch_kernel(finalize_kernel, dim3(a.batch), dim3(kMaxGrowNodes), 0, stream, a);
 }
 hipError_t launch_tree_reset(int32_t* n_nodes, int batch, hipStream_t stream) {
-  return launch_kernel(reset_kernel, dim3((unsigned)(batch + 255) / 256), dim3(256), stream, n_nodes, batch);
+  return launch_kernel(reset_kernel, dim3((unsigned)(batch + 255) / 256), dim3(256), 0, stream, n_nodes, batch);
 }
 hipError_t launch_gather_rows(const float* q_all, const int* q_row, float* out, long long n_nodes, int vocab,
                               long long n_q_rows, hipStream_t stream) {

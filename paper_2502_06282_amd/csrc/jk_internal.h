@@ -30,9 +30,9 @@ struct SameType {
   typedef T type;
 };
 template <class... P>
-hipError_t launch_kernel(void (*kernel)(P...), dim3 grid, dim3 threads, hipStream_t stream, typename SameType<P>::type... args) {
+hipError_t launch_kernel(void (*kernel)(P...), dim3 grid, dim3 threads, unsigned lds, hipStream_t stream, typename SameType<P>::type... args) {
   void* pointers[] = {const_cast<void*>(static_cast<const void*>(&args))...};
-  const hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, threads, pointers, 0, stream);
+  const hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, threads, pointers, lds, stream);
   if (e != hipSuccess) (void)hipGetLastError();
   return e;
 }

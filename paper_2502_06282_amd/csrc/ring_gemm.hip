@@ -352,9 +352,8 @@ hipError_t launch(const StreamGemmArgs& p, hipStream_t stream) {
   const long long groups = (long long)((p.n + (KIND == PAIR ? 7 : 15)) / (KIND == PAIR ? 8 : 16)) * p.batch;
   const int cus = device_cu_count();
   const int all = (int)(groups < cus ? groups : cus);
-  hipLaunchKernelGGL((ring_gemm_kernel<KIND, RG, NF>), dim3((unsigned)all), dim3(kRingThreads), smem, stream, p.sel, p.m, p.batch, p.n, p.k, all, p.x,
+  return launch_kernel(ring_gemm_kernel<KIND, RG, NF>, dim3((unsigned)all), dim3(kRingThreads), smem, stream, p.sel, p.m, p.batch, p.n, p.k, all, p.x,
                      p.w, p.w_batch, p);
-  return hipGetLastError();
 }
 // `items`: how many experts are likely to be chosen
 template <RingKind KIND, int RG>

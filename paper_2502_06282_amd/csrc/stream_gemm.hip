@@ -440,9 +440,8 @@ hipError_t launch(const StreamGemmArgs& p, hipStream_t stream) {
     return e;
   constexpr int COLS = strip_rows(NF) / (KIND == PAIR ? 2 : 1);
   const int strips = (p.n + COLS - 1) / COLS;
-  hipLaunchKernelGGL((stream_gemm_kernel<MT, NF, KIND>), dim3((unsigned)strips, (unsigned)p.batch, (unsigned)p.ksplit), dim3(kThreads), smem, stream,
+  return launch_kernel(stream_gemm_kernel<MT, NF, KIND>, dim3((unsigned)strips, (unsigned)p.batch, (unsigned)p.ksplit), dim3(kThreads), smem, stream,
                      p.w, p.w2, p.w_batch, p.n, p.k, p.ksplit, strips, p.x, p.m, p);
-  return hipGetLastError();
 }
 
 }  // namespace
@@ -787,9 +786,8 @@ hipError_t launch_narrow(const NarrowCall& p, int blocks, hipStream_t stream) {
   if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(narrow_gemm_kernel<RG, NF, WAVES>), smem, raised); e != hipSuccess) return e;
   // (Where the row blocks of a strip ran on different XCDs, with 121 strips of 56, 80 x 6760 x 7296 took 40.7 us, and takes 36.9.)
   const dim3 grid((unsigned)xcd_grid(p.strips * p.parts, blocks), (unsigned)blocks);
-  hipLaunchKernelGGL((narrow_gemm_kernel<RG, NF, WAVES>), grid, dim3(64 * WAVES), smem, stream, p.w, p.x, p.m, p.n, p.k, p.strip, p.strips, p.rows,
+  return launch_kernel(narrow_gemm_kernel<RG, NF, WAVES>, grid, dim3(64 * WAVES), smem, stream, p.w, p.x, p.m, p.n, p.k, p.strip, p.strips, p.rows,
                      p.parts, (int)grid.x, p.end);
-  return hipGetLastError();
 }
 template <int RG>
 hipError_t launch_narrow_rows(const NarrowCall& p, int blocks, hipStream_t stream) {

@@ -1363,9 +1363,8 @@ hipError_t launch_one(const KParams& kp, hipStream_t stream) {
   auto kern = tva_bf16_kernel<D, WM, WN, KT, PAGED, DEEP, JK_MERGE>;
   static LdsLimitRaised raised;
   if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), P_::SMEM, raised); e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(kp.total_wgs), dim3(P_::THREADS), P_::SMEM, stream, kp.prefix_len, kp.B, kp.total_wgs, kp.n_qtiles, kp.splits, kp.units_per_xcd,
+  return launch_kernel(kern, dim3(kp.total_wgs), dim3(P_::THREADS), P_::SMEM, stream, kp.prefix_len, kp.B, kp.total_wgs, kp.n_qtiles, kp.splits, kp.units_per_xcd,
                      kp.second_turn, kp.Hkv, (unsigned)kp.mg_qtiles, (unsigned)kp.mg_splits, (unsigned)kp.mg_hkv, (unsigned)kp.mg_upx, kp);
-  return hipGetLastError();
 }
 template <int D, bool PAGED>
 hipError_t launch_arranged(const KParams& kp, const AttnPlan& pl, hipStream_t stream) {

@@ -302,12 +302,13 @@ namespace tva {
 hipError_t launch_direct(const KParams& kp, int head_dim, hipStream_t stream) {
   const dim3 grid(kp.total_wgs), block(64 * kWaves);
   const bool paged = kp.block_table != nullptr;
-  if (head_dim == 128 && paged) hipLaunchKernelGGL((tva_direct_kernel<128, true>), grid, block, 0, stream, kp);
-  else if (head_dim == 128) hipLaunchKernelGGL((tva_direct_kernel<128, false>), grid, block, 0, stream, kp);
-  else if (head_dim == 64 && paged) hipLaunchKernelGGL((tva_direct_kernel<64, true>), grid, block, 0, stream, kp);
-  else if (head_dim == 64) hipLaunchKernelGGL((tva_direct_kernel<64, false>), grid, block, 0, stream, kp);
-  else return hipErrorInvalidValue;
-  return hipGetLastError();
+  if (head_dim == 128)
+    return paged ? launch_kernel(tva_direct_kernel<128, true>, grid, block, 0, stream, kp)
+                 : launch_kernel(tva_direct_kernel<128, false>, grid, block, 0, stream, kp);
+  if (head_dim == 64)
+    return paged ? launch_kernel(tva_direct_kernel<64, true>, grid, block, 0, stream, kp)
+                 : launch_kernel(tva_direct_kernel<64, false>, grid, block, 0, stream, kp);
+  return hipErrorInvalidValue;
 }
 }  // namespace tva
 

@@ -418,8 +418,7 @@ hipError_t launch_waves(const FParams& fp, hipStream_t stream) {
   constexpr int SMEM = WAVES * 16 * (64 * ((KJ + 3) / 4) + 4) * 4;
   static LdsLimitRaised raised;
   if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(tva_f32_kernel<KJ, WAVES, WHOLE>), SMEM, raised); e != hipSuccess) return e;
-  hipLaunchKernelGGL((tva_f32_kernel<KJ, WAVES, WHOLE>), dim3(fp.splits, (fp.M + 15) / 16, fp.B * fp.Hkv), dim3(64 * WAVES), SMEM, stream, fp);
-  return hipGetLastError();
+  return launch_kernel(tva_f32_kernel<KJ, WAVES, WHOLE>, dim3(fp.splits, (fp.M + 15) / 16, fp.B * fp.Hkv), dim3(64 * WAVES), SMEM, stream, fp);
 }
 template <int KJ>
 hipError_t launch_kj(const FParams& fp, hipStream_t stream) {

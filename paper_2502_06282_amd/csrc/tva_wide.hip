@@ -756,8 +756,7 @@ hipError_t launch_one(const KParams& kp, hipStream_t stream) {
   auto kern = tva_wide_kernel<D, PAGED>;
   static LdsLimitRaised raised;
   if (hipError_t e = raise_lds_limit(reinterpret_cast<const void*>(kern), P_::SMEM, raised); e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(kp.total_wgs), dim3(kWideThreads), P_::SMEM, stream, kp);
-  return hipGetLastError();
+  return launch_kernel(kern, dim3(kp.total_wgs), dim3(kWideThreads), P_::SMEM, stream, kp);
 }
 
 }  // namespace
