@@ -101,14 +101,14 @@ struct Weights {
   // Workgroups start at different chunks and wrap around: rows often lie a power of two apart, so that workgroups in
   // step would all ask the same few memory channels (16 x 4096 x 4096: 115 us in step, 98 us like this; 32000 x 4096:
   // 58 and 46).  Workgroups run on the eight XCDs in turn, so the start has to vary within every eighth of them too: by seven
-  // chunks from one to the next, and where a row has 16 chunks or more by eight from XCD to XCD, else by five.  Of 28 pairs of steps,
+  // chunks from one to the next and by eight from XCD to XCD where a row has 16 chunks of 256 or more, else by one and five.  Of 28 pairs of steps,
   // five and nine / eight and seven, kernels of a call, us: 20 rows, 128256 x 4096 195 / 190, 80, 32000 x 4096 69.3 / 68.6, 40, 64000 x
   // 8192 196 / 193, eight experts of 4096 x 4096 148.8 / 144.7; in eight chunks the other way round, 64000 x 2048 1 : 0.985, experts of 2048 x
-  // 8192 1 : 0.976.  (A half chunk at the end stays last.)
+  // 8192 1 : 0.976; chunks of 128 (more than 128 rows) either, 160 rows of 83155 x 3968 221.4 / 226, of 32000 x 4096 88.7 / 86.5.  (A half chunk at the end stays last.)
   template <int KC>
   __device__ __forceinline__ int chunk(int c) const {
     const int whole = (k1 - k0) / KC;
-    const int rot = whole > 0 ? (int)((whole >= 16 ? 8u * (wg & 7u) + 7u * (wg >> 3) : 5u * wg + (wg >> 3)) % (unsigned)whole) : 0;
+    const int rot = whole > 0 ? (int)((KC == 256 && whole >= 16 ? 8u * (wg & 7u) + 7u * (wg >> 3) : 5u * wg + (wg >> 3)) % (unsigned)whole) : 0;
     const int t = c + rot;
     return k0 + (c < whole ? (t < whole ? t : t - whole) : c) * KC;
   }
