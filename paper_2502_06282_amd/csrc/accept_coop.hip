@@ -189,9 +189,9 @@ struct Walk {
   unsigned n_exch = 0, tag = 0;
   Table* tab = nullptr;
 
-  __device__ __forceinline__ Walk(const CoopParams& params, NodeTable& nodes, int W, int b, int n_tree, int vocab)
+  __device__ __forceinline__ Walk(const CoopParams& params, NodeTable& nodes, int W, int b, int w, int n_tree, int vocab)
       : p(params), table(nodes), tid(threadIdx.x), lane(tid & 63), wave(__builtin_amdgcn_readfirstlane(tid >> 6)), W(W), b(b),
-        w((int)blockIdx.x - b * W), N(n_tree), V(vocab) {}
+        w(w), N(n_tree), V(vocab) {}
   __device__ __forceinline__ const float* row_of(int r) const { return p.logits + ((long long)b * (N + 1) + r) * V; }
   // What a walk starts from is asked for in one trip to memory: a value that the compiler knows to be the same in all lanes it
   // moves to a scalar register at once, and waits for everything asked for before it.  So these are different ones, to it,
@@ -223,6 +223,7 @@ struct Walk {
       x.draft[h] = rows[at];
     }
   }
+  template <bool EARLY = false>  // asked for in a branch of its own
   __device__ __forceinline__ void make_table(Nodes x) {
     for (int i = lane; i <= N; i += 64) *reinterpret_cast<uint4*>(table.kids[i]) = make_uint4(0u, 0u, 0u, 0u);
     auto in_order = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };  // (LDS operations of a wave complete in order)
@@ -231,7 +232,7 @@ struct Walk {
     long long draft[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      asm volatile("" : "+v"(x.par[h]), "+v"(x.tok[h]), "+v"(x.uni[h]), "+v"(x.draft[h]));  // (else widened, and waited for, where it was asked for)
+      if (EARLY) asm volatile("" : "+v"(x.par[h]), "+v"(x.tok[h]), "+v"(x.uni[h]), "+v"(x.draft[h]));  // (else widened, and waited for, where it was asked for)
       par[h] = x.par[h];
       tok[h] = x.tok[h];
       uni[h] = x.uni[h];
@@ -491,12 +492,10 @@ struct Walk {
   __device__ __forceinline__ unsigned finished() const { return __hip_atomic_load(&tw->finish + lane_zero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 };
 
-template <int PER, int THREADS>
-__global__ __launch_bounds__(THREADS, 2) void walk_sample_coop_kernel(const float* logits, const int* parent, const int* tokens,
-                                                                      const float* uniforms, const int* draft_row, int n_tree, int vocab, int W_lead,
-                                                                      unsigned mg_w, CoopParams params) {
+// `start`: asks for the slices of rows 0 and 1, and for what a walk starts from, and makes the table
+template <int PER, int THREADS, class Start>
+__device__ __forceinline__ void walk_together(Walk& wk, const Start& start) {
   constexpr int SLICE = THREADS * PER, WAVES = THREADS / 64;
-  __shared__ NodeTable nodes;
   __shared__ double red_d[2][WAVES];
   __shared__ float red_f[2][WAVES];
   __shared__ double xs[64];  // the slices' sums under the current distribution, still to be multiplied by xs_mul
@@ -506,7 +505,6 @@ __global__ __launch_bounds__(THREADS, 2) void walk_sample_coop_kernel(const floa
   __shared__ int got_ok[3];
   __shared__ double pv_s;
 
-  Walk wk(params, nodes, W_lead, mg_w ? (int)__umulhi(blockIdx.x, mg_w) : (int)blockIdx.x, n_tree, vocab);
   const CoopParams& p = wk.p;
   const int tid = wk.tid, lane = wk.lane, wave = wk.wave, W = wk.W;
   const Walk::Part<PER> mine(wk.w * SLICE + tid * PER, wk.V);
@@ -522,20 +520,7 @@ __global__ __launch_bounds__(THREADS, 2) void walk_sample_coop_kernel(const floa
   // (The root's first child is node 0, since a parent comes before its children: its own row is row 1.)
   Candidate then;
   float lg[PER];
-  // The first rows are on their way before anything else is known, and the nodes: their addresses are made of the leading arguments,
-  // which are in scalar registers when a wave starts (a compiler option for this file, fourteen words at most).  The others take
-  // 0.3 us to come from memory, and which tree this is was a division.  (us, before / so: one tree of 60 nodes, 128256 entries 13.59 /
-  // 13.39, eight of 100, 32000 entries 21.44 / 21.21.)
-  Walk::Nodes first_nodes;
-  {
-    const float* row = logits + (long long)wk.b * (n_tree + 1) * vocab;
-    mine.load(lg, row);
-    mine.load(then.lg, row + vocab);
-    if (wave == 0) wk.ask_nodes(first_nodes, parent, tokens, uniforms, draft_row);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  wk.load_words();
-  if (wave == 0) wk.make_table(first_nodes);
+  start(mine, lg, then.lg);
   wk.settle();
   __syncthreads();
   then.k = 0;
@@ -741,6 +726,48 @@ __global__ __launch_bounds__(THREADS, 2) void walk_sample_coop_kernel(const floa
   }
 }
 
+// The first rows are on their way before anything else is known, and the nodes: their addresses are made of the leading arguments,
+// which are in scalar registers when a wave starts (a compiler option for this file, fourteen words at most).  The others take
+// 0.3 us to come from memory, and which tree this is was a division.  (us, before / so: one tree of 60 nodes, 128256 entries 13.59 /
+// 13.39, eight of 100, 32000 entries 21.44 / 21.21.)
+template <int PER, int THREADS>
+__global__ __launch_bounds__(THREADS, 2) void walk_sample_coop_kernel(const float* logits, const int* parent, const int* tokens,
+                                                                      const float* uniforms, const int* draft_row, int n_tree, int vocab, int W,
+                                                                      unsigned mg_w, CoopParams params) {
+  __shared__ NodeTable nodes;
+  const int b = mg_w ? (int)__umulhi(blockIdx.x, mg_w) : (int)blockIdx.x;
+  Walk wk(params, nodes, W, b, (int)blockIdx.x - b * W, n_tree, vocab);
+  walk_together<PER, THREADS>(wk, [&](const Walk::Part<PER>& mine, float (&row0)[PER], float (&row1)[PER]) __attribute__((always_inline)) {
+    Walk::Nodes first_nodes;
+    const float* row = logits + (long long)wk.b * (n_tree + 1) * vocab;
+    mine.load(row0, row);
+    mine.load(row1, row + vocab);
+    if (wk.wave == 0) wk.ask_nodes(first_nodes, parent, tokens, uniforms, draft_row);
+    __builtin_amdgcn_sched_barrier(0);
+    wk.load_words();
+    if (wk.wave == 0) wk.make_table<true>(first_nodes);
+  });
+}
+// Eight and sixteen entries a thread, where scalar registers are short: a place in the tree made by the compiler's remainder, and
+// arguments read where they are needed.  Made of b * W, b and W stay alive through the walk, and 61 and 72 scalar registers are
+// spilled instead of 45 and 63.  (us, so / by leading arguments and b * W, of one card: 10 trees of 25 nodes, 128512 entries 27.08 /
+// 27.41, 16 trees, 100000 entries 32.5 / 33.1.)
+template <int PER, int THREADS>
+__global__ __launch_bounds__(THREADS, 2) void walk_sample_long_kernel(CoopParams params) {
+  __shared__ NodeTable nodes;
+  Walk wk(params, nodes, params.W, (int)(blockIdx.x / (unsigned)params.W), (int)(blockIdx.x % (unsigned)params.W), params.n_tree, params.vocab);
+  walk_together<PER, THREADS>(wk, [&](const Walk::Part<PER>& mine, float (&row0)[PER], float (&row1)[PER]) __attribute__((always_inline)) {
+    mine.load(row0, wk.row_of(0));
+    mine.load(row1, wk.row_of(1));
+    wk.load_words();
+    if (wk.wave == 0) {
+      Walk::Nodes first_nodes;
+      wk.ask_nodes(first_nodes, params.parent, params.tokens, params.uniforms, params.draft_row);
+      wk.make_table(first_nodes);
+    }
+  });
+}
+
 // The walk of many trees over large vocabularies, where slices of 4096 entries would be more workgroups than are resident
 // together: 512 threads, a workgroup for each CU at most, a slice of 8192 to 20480 entries each.  (The workgroups of a tree
 // follow each other in the grid: of a call that gets only some of the CUs at most one tree waits for others to end.)  A thread
@@ -765,7 +792,7 @@ __global__ __launch_bounds__(kWideThreads) void walk_sample_wide_kernel(CoopPara
   __shared__ int got_ok;
   __shared__ double pv_s;
 
-  Walk wk(params, nodes, params.W, (int)(blockIdx.x / (unsigned)params.W), params.n_tree, params.vocab);
+  Walk wk(params, nodes, params.W, (int)(blockIdx.x / (unsigned)params.W), (int)(blockIdx.x % (unsigned)params.W), params.n_tree, params.vocab);
   const CoopParams& p = wk.p;
   const int tid = wk.tid, lane = wk.lane, wave = wk.wave;
   const Walk::Part<PER> mine(wk.w * SLICE + tid * PER, wk.V);
@@ -965,7 +992,8 @@ unsigned W_reciprocal(int W) { return W > 1 ? (unsigned)((1ull << 32) / (unsigne
 
 template <int PER, int THREADS>
 hipError_t launch_walk(const CoopParams& cp, int wgs, hipStream_t stream) {
-  return launch_kernel(walk_sample_coop_kernel<PER, THREADS>, dim3((unsigned)wgs), dim3(THREADS), 0, stream, cp.logits, cp.parent, cp.tokens,
+  if constexpr (PER > 4) return launch_kernel(walk_sample_long_kernel<PER, THREADS>, dim3((unsigned)wgs), dim3(THREADS), 0, stream, cp);
+  else return launch_kernel(walk_sample_coop_kernel<PER, THREADS>, dim3((unsigned)wgs), dim3(THREADS), 0, stream, cp.logits, cp.parent, cp.tokens,
                      cp.uniforms, cp.draft_row, cp.n_tree, cp.vocab, cp.W, W_reciprocal(cp.W), cp);
 }
 
