@@ -13,6 +13,7 @@
 //                          surrounds the experts' three projections (Eq. 3).
 // The products with weight matrices run in stream_gemm.hip and ring_gemm.hip.
 
+#include <cfloat>
 #include <cmath>
 #include <type_traits>
 
@@ -969,8 +970,10 @@ hipError_t launch_draft_heads(const DraftHeadsArgs& a, hipStream_t stream) {
   g.ksplit = rp.ksplit; g.y_split = (long long)m * a.vocab; g.batch = 1;
   g.s_top = a.s_top; g.heads_mode = a.mode; g.alpha = a.alpha; g.beta = a.beta;
   g.stats = rp.stats ? reinterpret_cast<float2*>(ws + rp.ms_off) : nullptr;
+  // (1 / T below the largest float has its log2(e)-fold beyond it from T = 4.24e-39 downwards: then the first part is the largest float, and
+  // the second what is left, a number too.  An infinite one made rows none by zero times it.)
   const double scale = (double)(1.0f / a.temperature) * 1.4426950408889634;
-  g.scale_hi = (float)scale; g.scale_lo = (float)(scale - (double)g.scale_hi);
+  g.scale_hi = scale > (double)FLT_MAX ? FLT_MAX : (float)scale; g.scale_lo = (float)(scale - (double)g.scale_hi);
   e = rp.ring ? launch_ring_gemm_heads(g, stream) : mixes ? launch_stream_gemm_heads(g, stream) : launch_stream_gemm(g, stream);
   if (e != hipSuccess) return e;
 

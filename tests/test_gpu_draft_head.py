@@ -315,3 +315,27 @@ def test_rows_by_the_statistics_of_their_blocks(rows, vocab):
     np.testing.assert_allclose(tp[:, :, :n], 1.0 / n, rtol=1e-6)
     np.testing.assert_allclose(q[:, :, alive], 1.0 / n, rtol=1e-6)
     assert np.count_nonzero(q) == 2 * rows * n
+
+
+@pytest.mark.parametrize("temperature", [4.3e-39, 4.2e-39, 3.5e-39, 2.95e-39])   # log2(e) / T beyond the largest float from 4.24e-39 downwards
+def test_smallest_temperatures(temperature):
+    """1 / T is a number down to 2.94e-39: rows of ordinary logits have the one distribution on their maximum, and rows whose logits are
+    a few times 2^-126 apart (exact) an ordinary one."""
+    tune("ring_gemm", 0)
+    x = _exact_inputs(3, 128, 1001, 1)
+    lg, q, tk, tp = _call(x, temperature=temperature)
+    top = lg == lg.max(-1, keepdims=True)
+    np.testing.assert_allclose(q, top / top.sum(-1, keepdims=True), rtol=1e-6)
+    np.testing.assert_array_equal(tk, dh.top_candidates(lg, 5))
+    np.testing.assert_allclose(tp, np.take_along_axis(q, tk.astype(np.int64), axis=-1), rtol=1e-6)
+    x["f_top"][:] = 0.0
+    x["f_top"][:, :, 0] = 1.0
+    x["s_top"][:] = 1.0
+    x["w_head"][:] = 0.0
+    x["w_head"][:, 0] = np.arange(1001) % 9 * 2.0 ** -126
+    lg, q, tk, tp = _call(x, temperature=temperature)
+    np.testing.assert_array_equal(lg.astype(np.float64), np.broadcast_to(np.arange(1001) % 9 * 2.0 ** -126, lg.shape))
+    # (against the reciprocal in 32 bits, which the division by a subnormal number does not have more of: a few roundings of exponents below 32)
+    e = np.exp((lg.astype(np.float64) - 8 * 2.0 ** -126) * np.float64(np.float32(1.0) / np.float32(temperature)))
+    np.testing.assert_allclose(q, e / e.sum(-1, keepdims=True), rtol=3e-5)
+    np.testing.assert_allclose(tp, np.take_along_axis(q, tk.astype(np.int64), axis=-1), rtol=1e-6)
