@@ -465,7 +465,9 @@ class TreeState:
         self.n_nodes = torch.zeros((batch,), dtype=torch.int32, device=device)
 
     def reset(self) -> None:
-        if not _n.tree_reset(self.n_nodes):
+        import torch
+        # (a graph of torch.compile takes zero_, and no call of the extension)
+        if torch.compiler.is_dynamo_compiling() or not _n.tree_reset(self.n_nodes):
             self.n_nodes.zero_()
 
     def desc(self) -> TreeStateDesc:

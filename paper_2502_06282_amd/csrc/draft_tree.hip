@@ -383,7 +383,7 @@ hipError_t launch_tree_finalize(const TreeFinalArgs& a, hipStream_t stream) {
   return launch_kernel(finalize_kernel, dim3(a.batch), dim3(kMaxGrowNodes), 0, stream, a);
 }
 hipError_t launch_tree_reset(int32_t* n_nodes, int batch, hipStream_t stream) {
-  return launch_kernel(reset_kernel, dim3((unsigned)(batch + 255) / 256), dim3(256), 0, stream, n_nodes, batch);
+  return launch_kernel(reset_kernel, dim3(((unsigned)batch + 255u) / 256u), dim3(256), 0, stream, n_nodes, batch);
 }
 hipError_t launch_gather_rows(const float* q_all, const int* q_row, float* out, long long n_nodes, int vocab,
                               long long n_q_rows, hipStream_t stream) {

@@ -453,3 +453,65 @@ def test_reset_clears_the_counts_of_any_tensor(kind):
     else:
         st.reset()
     assert int(st.n_nodes.abs().sum()) == 0
+
+
+@pytest.mark.parametrize("kind", ["function_mode", "traced", "recorded", "functionalized", "batched"])
+def test_reset_is_seen_by_whoever_intercepts_it(kind):
+    """Function modes, tracing, the profiler and transforms see torch's own operation."""
+    from torch.overrides import TorchFunctionMode
+
+    st = jk.TreeState(300, 64)
+    st.n_nodes.fill_(9)
+    if kind == "function_mode":
+        seen = []
+
+        class Counting(TorchFunctionMode):
+            def __torch_function__(self, func, types, args=(), kwargs=None):
+                seen.append(func.__name__)
+                return func(*args, **(kwargs or {}))
+
+        with Counting():
+            st.reset()
+        assert seen == ["zero_"]
+    elif kind == "traced":
+        def fn(x):
+            st.n_nodes = x.clone()
+            st.reset()
+            return st.n_nodes + 1
+        traced = torch.jit.trace(fn, (st.n_nodes,), check_trace=False)
+        assert "aten::zero_" in str(traced.graph)
+        assert bool((traced(torch.full_like(st.n_nodes, 4)) == 1).all())
+    elif kind == "recorded":
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CPU]) as prof:
+            st.reset()
+        assert any(e.key == "aten::zero_" for e in prof.key_averages())
+    elif kind == "functionalized":
+        def fn(x):
+            st.n_nodes = x
+            st.reset()
+            return x + 1
+        counts = st.n_nodes
+        assert bool((torch.func.functionalize(fn)(counts) == 1).all())
+        st.n_nodes = counts
+    else:
+        def fn(x):
+            st.n_nodes = x
+            st.reset()
+            return x + 1
+        counts = st.n_nodes.view(30, 10)
+        assert bool((torch.vmap(fn)(counts) == 1).all())
+        st.n_nodes = counts.view(300)
+    assert int(st.n_nodes.abs().sum()) == 0
+
+
+def test_reset_is_a_change_in_place_to_autograd():
+    """Counts that a backward pass needs: clearing them meanwhile is an error there, and not a wrong gradient."""
+    st = jk.TreeState(300, 64)
+    before = st.n_nodes._version
+    st.reset()
+    assert st.n_nodes._version == before + 1
+    x = torch.ones(10, device="cuda", requires_grad=True)
+    y = (x[st.n_nodes] * 2).sum()
+    st.reset()
+    with pytest.raises(RuntimeError, match="modified by an inplace operation"):
+        y.backward()

@@ -286,3 +286,18 @@ def test_a_draft_workspace_covers_fewer_rows(lib):
     for n, k in ((4096, 8192), (6144, 4096), (4096, 4096), (512, 1024), (128, 16384), (100000, 128), (777, 2944)):
         sizes = [lib.jk_linear_workspace(m, n, k) for m in range(1, 257)]
         assert sizes[0] > 0 and sizes == sorted(sizes), (n, k)
+
+
+def test_clearing_a_tree_goes_into_a_compiled_graph():
+    """TreeState.reset is one operation of torch's there, and not a call that a graph cannot hold."""
+    import torch
+    from paper_2502_06282_amd import TreeState
+    st = TreeState(3, 8, device="cpu")
+    st.n_nodes.fill_(5)
+
+    @torch.compile(fullgraph=True, backend="eager")
+    def fn(state, x):
+        state.reset()
+        return state.n_nodes + x
+
+    assert fn(st, torch.ones(3, dtype=torch.int32)).tolist() == [1, 1, 1] and st.n_nodes.tolist() == [0, 0, 0]
