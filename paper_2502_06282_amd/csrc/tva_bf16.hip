@@ -541,7 +541,7 @@ __device__ __forceinline__ void merge_rows(const MergeArgs& p, const MergeThread
   // (The pair is loaded by hand and waited for by number, with the sixteen loads behind it on their way: left alone, the
   // compiler waits in front of them, or for all of them.)
   u32x2 pair;
-  asm volatile("global_load_dwordx2 %0, %1, %2" : "=v"(pair) : "v"(t.ml_off), "s"(p.part_ml) : "memory");
+  asm volatile("global_load_dwordx2 %0, %1, %2 ; asked %0 as %3" : "=v"(pair) : "v"(t.ml_off), "s"(p.part_ml), "n"(kAskedPair) : "memory");
   const bool rows_here = __builtin_amdgcn_readfirstlane(t.r_b) < rows_end;  // (of this wave: its first row is its least)
   if (rows_here) {
     fetch(t.r_b, 0);
@@ -549,7 +549,7 @@ __device__ __forceinline__ void merge_rows(const MergeArgs& p, const MergeThread
   } else {
     dev::wait_vm<0>();
   }
-  asm volatile("" : "+v"(pair));
+  arrived<kAskedPair>(pair);
   const float2 ml = t.live_a ? make_float2(__uint_as_float(pair[0]), __uint_as_float(pair[1])) : make_float2(-INFINITY, 0.f);
   JK_TS(11);
   // ---- (A): pair (row, split) of this thread
@@ -729,7 +729,7 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
   // compiler, which does not know of the transfers, would wait for the oldest of its loads by waiting for all but a few of
   // everything issued since.
   int lengths;  // (lane i: of sequence i, of the first 64)
-  load_by_hand(lengths, prefix_len + min(lane, batch - 1));
+  load_by_hand<kAskedLengths>(lengths, prefix_len + min(lane, batch - 1));
   int wid;
   {
     const int n = blockIdx.x;
@@ -741,7 +741,11 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
   const int rest = divide(wid, mg_qtiles, n_qtiles);
   const int qtile = wid - rest * n_qtiles;
   const int unit = divide(rest, mg_splits, splits);  // b * Hkv + kv in the order of the batch
-  if (unit >= batch * n_kv_heads) return;    // padding workgroup
+  if (unit >= batch * n_kv_heads) {  // padding workgroup
+    dev::wait_vm<0>();
+    dropped<kAskedLengths>(lengths);
+    return;
+  }
   const int split = rest - unit * splits;
   int place = unit;  // rank * Hkv + kv
   if (ranked) {
@@ -765,20 +769,17 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
   const int my_node = div_mg(mm, p.mg_g);
   unsigned long long row_at = (unsigned)my_node * (unsigned long long)p.q_st + (unsigned)(kv * G + (mm - my_node * G)) * (unsigned long long)p.q_sh + 8 * g;
   int L = p.max_prefix, L_one;
-  // (a load's result is in nobody's hands before it has been waited for: the values below are copies, so that no two branches'
-  // meet in one variable, for which the compiler would move what has not arrived)
   if (ranked) {
     asm volatile("" : "+v"(row_at));
     dev::wait_vm<0>();
-    int len;
-    asm volatile("v_mov_b32 %0, %1" : "=v"(len) : "v"(lengths));
+    int len = taken<kAskedLengths>(lengths);
     len = len < 0 ? 0 : (len > p.max_prefix ? p.max_prefix : len);
     if (!__all(len == p.max_prefix)) {
       b = sequence_of_rank(len, batch, rank, lane);
       L = __builtin_amdgcn_readlane(len, b);
     }
   } else if (batch > 64) {
-    load_by_hand(L_one, prefix_len + b);
+    load_by_hand<kAskedLength>(L_one, prefix_len + b);
   }
   JK_TS(14);
 
@@ -870,10 +871,10 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
       n_pg = div_mg(te - 1, p.mg_tpp) - ts.pg_first + 1;  // <= kMaxPagesPerSplit by the host's plan
     }
     // (in every lane: the compiler may not move the result before it has been waited for)
-    load_by_hand(first_id, tid < n_pg && ts.pg_first + tid < p.max_blocks ? table + ts.pg_first + tid : p.prefix_len);
+    load_by_hand<kAskedPages>(first_id, tid < n_pg && ts.pg_first + tid < p.max_blocks ? table + ts.pg_first + tid : p.prefix_len);
   };
   auto fill_pages = [&]() {  // (the ids have been waited for)
-    asm volatile("" : "+v"(first_id));
+    arrived<kAskedPages>(first_id);
     bad_page = false;
     for (int i = tid; i < n_pg && i < kMaxPagesPerSplit; i += THREADS) {
       const int pi = ts.pg_first + i;
@@ -890,11 +891,11 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
   u32x4 q_raw[DK];
   int parent_lo, parent_hi;
   {
-    load_rows_by_hand(q_raw, p.q + (unsigned)b * (unsigned long long)p.q_sb + row_at);
+    load_rows_by_hand<kAskedRow>(q_raw, p.q + (unsigned)b * (unsigned long long)p.q_sb + row_at);
     if (wave == 0) {
       const int32_t* parents = p.parent + (unsigned)(b * T);
-      load_by_hand(parent_lo, parents + min(lane, T - 1));
-      load_by_hand(parent_hi, parents + min(lane + 64, T - 1));
+      load_by_hand<kAskedParent>(parent_lo, parents + min(lane, T - 1));
+      load_by_hand<kAskedParent + 1>(parent_hi, parents + min(lane + 64, T - 1));
     }
   }
   if (PAGED) {
@@ -920,15 +921,8 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
   if (!ranked) {
     if (n_spec == NR - 1) dev::wait_vm<DK + (NR - 1) * DMA_PER_ROUND>();
     else dev::wait_vm<DK>();  // (no less than needed)
-    if (batch <= 64) {
-      int len;
-      asm volatile("v_mov_b32 %0, %1" : "=v"(len) : "v"(lengths));
-      L = __builtin_amdgcn_readlane(len, b);
-    } else {
-      int len;
-      asm volatile("v_mov_b32 %0, %1" : "=v"(len) : "v"(L_one));
-      L = __builtin_amdgcn_readfirstlane(len);
-    }
+    if (batch <= 64) L = __builtin_amdgcn_readlane(taken<kAskedLengths>(lengths), b);
+    else L = __builtin_amdgcn_readfirstlane(taken<kAskedLength>(L_one));
     L = L < 0 ? 0 : (L > p.max_prefix ? p.max_prefix : L);
     JK_TS(2);
     if (L != p.max_prefix) {  // uniform over the workgroup
@@ -953,14 +947,15 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
 
   JK_TS(3);
   wait_dma<DMA_PER_ROUND>(n_rounds < NR - 1 ? n_rounds : NR - 1);  // (what is older than the first rounds)
-#pragma unroll
-  for (int ks = 0; ks < DK; ++ks) asm volatile("" : "+v"(q_raw[ks]));
+  arrived_rows<kAskedRow>(q_raw);
+  arrived<kAskedParent>(parent_lo);
+  arrived<kAskedParent + 1>(parent_hi);
+  dropped<kAskedLengths>(lengths);  // (more than 64 sequences have no use for it)
+  dropped<kAskedLength>(L_one);
   // ---- ancestor sets (only workgroups that reach tree tiles need them); the barrier of the first round publishes them:
   // tree tiles are masked inside the loop only
-  if (has_tree && wave == 0) {
-    asm volatile("" : "+v"(parent_lo), "+v"(parent_hi));
+  if (has_tree && wave == 0)
     build_ancestor_sets<kParamsAt>(lane, T, lane < T ? parent_lo : -1, lane + 64 < T ? parent_hi : -1, par_s, anc);
-  }
 
 #pragma unroll
   for (int ks = 0; ks < DK; ++ks) {

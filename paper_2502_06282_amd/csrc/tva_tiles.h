@@ -115,20 +115,45 @@ struct Geo {
   }
 };
 
-// Ordinary loads by hand (what waits for them says how many transfers may have been issued since)
-__device__ __forceinline__ void load_by_hand(u32x4& v, const void* src) {
-  asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(v) : "v"(src) : "memory");
-}
+// Ordinary loads by hand (what waits for them says how many transfers may have been issued since).  The compiler takes their results to be
+// there at once.  So until the wait a result's register must be neither moved nor given to another value: every path that asks for one
+// gets to an arrived(), taken() or dropped() of it behind the wait, whether the value is of use there or not.  TAG names the value in the listing, where a
+// test compares the registers of both.
+enum Asked { kAskedLengths, kAskedLength, kAskedPages, kAskedTable, kAskedPair, kAskedParent, kAskedRow = 8 };  // (parents: two; rows: up to sixteen)
+template <int TAG>
 __device__ __forceinline__ void load_by_hand(int& v, const void* src) {
-  asm volatile("global_load_dword %0, %1, off" : "=v"(v) : "v"(src) : "memory");
+  asm volatile("global_load_dword %0, %1, off ; asked %0 as %2" : "=v"(v) : "v"(src), "n"(TAG) : "memory");
 }
 // N times 16 bytes, every 32 bytes
-template <int N, int I = 0>
+template <int TAG, int N, int I = 0>
 __device__ __forceinline__ void load_rows_by_hand(u32x4 (&v)[N], const void* src) {
   if constexpr (I < N) {
-    asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(v[I]) : "v"(src), "n"(32 * I) : "memory");
-    load_rows_by_hand<N, I + 1>(v, src);
+    asm volatile("global_load_dwordx4 %0, %1, off offset:%2 ; asked %0 as %3" : "=v"(v[I]) : "v"(src), "n"(32 * I), "n"(TAG + I) : "memory");
+    load_rows_by_hand<TAG, N, I + 1>(v, src);
   }
+}
+// Behind the wait, and in front of every use
+template <int TAG, class T>
+__device__ __forceinline__ void arrived(T& v) {
+  asm volatile("; arrived %0 as %1" : "+v"(v) : "n"(TAG));
+}
+template <int TAG, int N, int I = 0>
+__device__ __forceinline__ void arrived_rows(u32x4 (&v)[N]) {
+  if constexpr (I < N) {
+    arrived<TAG + I>(v[I]);
+    arrived_rows<TAG, N, I + 1>(v);
+  }
+}
+template <int TAG>
+__device__ __forceinline__ void dropped(const int& v) {  // (as arrived(), where no use comes any more)
+  asm volatile("; arrived %0 as %1" ::"v"(v), "n"(TAG));
+}
+// A copy, where several paths have a use of their own: with arrived() in each, the compiler would move the value in front of them
+template <int TAG>
+__device__ __forceinline__ int taken(const int& v) {
+  int copy;
+  asm volatile("v_mov_b32 %0, %1 ; arrived %1 as %2" : "=v"(copy) : "v"(v), "n"(TAG));
+  return copy;
 }
 
 using dev::dma16;

@@ -216,24 +216,21 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
   // not know of the transfers, would wait for the oldest of its loads by waiting for all but a few of everything issued
   // since.
   constexpr int ROW_LOADS = kBlocks * DK + 2;
-  int L_raw, L = p.max_prefix;
+  int L_lane, L_one, L = p.max_prefix;
   auto bounded = [&](int len) { return len < 0 ? 0 : (len > p.max_prefix ? p.max_prefix : len); };
   const int n_ttiles = (T + kTileKeys - 1) / kTileKeys;
   if (batch) {
-    load_by_hand(L_raw, p.prefix_len + min(lane, p.B - 1));  // (lane i: sequence i's)
     const int order = div_mg(rest, p.mg_hkv);  // of the piece, or of the sequence
     kv = rest - order * p.Hkv;
-    if (order >= p.B * splits) {  // padding workgroup
-      dev::wait_vm<0>();
-      return;
-    }
+    if (order >= p.B * splits) return;  // padding workgroup
+    load_by_hand<kAskedLengths>(L_lane, p.prefix_len + min(lane, p.B - 1));  // (lane i: sequence i's)
     // (the page table's first 32 KB, a line a thread, on their way into the L2 while the pieces are dealt)
     int touched;
     const long long last = (long long)p.B * p.max_blocks - 1;
-    load_by_hand(touched, PAGED ? p.block_table + (32 * tid < last ? 32 * tid : (int)last) : p.prefix_len);
+    load_by_hand<kAskedTable>(touched, PAGED ? p.block_table + (32 * tid < last ? 32 * tid : (int)last) : p.prefix_len);
     dev::wait_vm<1>();
-    asm volatile("" : "+v"(L_raw));
-    const int len = bounded(L_raw);
+    arrived<kAskedLengths>(L_lane);
+    const int len = bounded(L_lane);
     if (dealt) {
       const Deal d = deal_pieces(lane < p.B ? (len + kTileKeys - 1) / kTileKeys + n_ttiles : 0, p.B, splits, lane);
       b = __popcll(__ballot(lane < p.B && d.first <= order)) - 1;
@@ -243,7 +240,7 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
       b = sequence_of_rank(len, p.B, order, lane);
     }
     dev::wait_vm<0>();
-    asm volatile("" ::"v"(touched));
+    dropped<kAskedTable>(touched);
     if (split >= pieces) return;  // (fewer pieces than places)
     L = __builtin_amdgcn_readlane(len, b);
     place0 = (order - split) * p.Hkv + kv;
@@ -257,7 +254,7 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
     place0 = unit * splits;
     place_step = 1;
     // (starts its K/V stream as if its prefix had the length of the bound, and again if it turns out shorter)
-    load_by_hand(L_raw, p.prefix_len + b);
+    load_by_hand<kAskedLength>(L_one, p.prefix_len + b);
   }
   // ---- the split's tiles
   TileSrc ts;
@@ -289,10 +286,10 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
       n_pg = div_mg(te - 1, p.mg_tpp) - ts.pg_first + 1;  // <= kMaxPagesPerSplit by the host's plan
     }
     // (a load by hand in every lane: the compiler may not move its result before it has been waited for)
-    load_by_hand(first_id, tid < n_pg && ts.pg_first + tid < p.max_blocks ? table + ts.pg_first + tid : p.prefix_len);
+    load_by_hand<kAskedPages>(first_id, tid < n_pg && ts.pg_first + tid < p.max_blocks ? table + ts.pg_first + tid : p.prefix_len);
   };
   auto fill_pages = [&]() {  // (the ids have been waited for)
-    asm volatile("" : "+v"(first_id));
+    arrived<kAskedPages>(first_id);
     bad_page = false;
     for (int i = tid; i < n_pg && i < kMaxPagesPerSplit; i += kWideThreads) {
       const int pi = ts.pg_first + i;
@@ -314,10 +311,11 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
     const int mm = min(row0 + r * kWaveRows + c32, M - 1), node = div_mg(mm, p.mg_g);
     const uint16_t* src = p.q + (unsigned)b * (unsigned long long)p.q_sb + (unsigned)node * (unsigned long long)p.q_st +
                           (unsigned)(kv * G + (mm - node * G)) * (unsigned long long)p.q_sh + 8 * g;
-    load_rows_by_hand(q_raw[r], src);
+    if (r == 0) load_rows_by_hand<kAskedRow>(q_raw[r], src);
+    else load_rows_by_hand<kAskedRow + DK>(q_raw[r], src);
   }
-  load_by_hand(parent_lo, p.parent + (long long)b * T + min(lane, T - 1));
-  load_by_hand(parent_hi, p.parent + (long long)b * T + min(lane + 64, T - 1));
+  load_by_hand<kAskedParent>(parent_lo, p.parent + (long long)b * T + min(lane, T - 1));
+  load_by_hand<kAskedParent + 1>(parent_hi, p.parent + (long long)b * T + min(lane + 64, T - 1));
   __builtin_amdgcn_sched_barrier(0);
   const unsigned ring_addr = (unsigned)(size_t)LDS_PTR(unsigned char, smem);
   LaneChunks<D, kWideWaves> lc;
@@ -353,8 +351,7 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
   if (!batch) {
     if (n >= P_::AHEAD) dev::wait_vm<ROW_LOADS + P_::AHEAD * N>();
     else dev::wait_vm<ROW_LOADS>();  // (no less than needed)
-    asm volatile("" : "+v"(L_raw));
-    L = bounded(__builtin_amdgcn_readfirstlane(L_raw));
+    L = bounded(__builtin_amdgcn_readfirstlane(taken<kAskedLength>(L_one)));
     if (L != p.max_prefix) {  // (uniform over the workgroup)
       dev::wait_vm<0>();  // the ring must be quiet before the same places are filled again
       __syncthreads();
@@ -371,11 +368,11 @@ __global__ __launch_bounds__(kWideThreads, 1) void tva_wide_kernel(const KParams
   if (PAGED && bad_page) __hip_atomic_fetch_or(p.err, kDevErrBadPage, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (n >= P_::AHEAD) dev::wait_vm<P_::AHEAD * N>();
   else wait_dma<N>(n);
-#pragma unroll
-  for (int r = 0; r < kBlocks; ++r)
-#pragma unroll
-    for (int ks = 0; ks < DK; ++ks) asm volatile("" : "+v"(q_raw[r][ks]));
-  asm volatile("" : "+v"(parent_lo), "+v"(parent_hi));
+  arrived_rows<kAskedRow>(q_raw[0]);
+  arrived_rows<kAskedRow + DK>(q_raw[1]);
+  arrived<kAskedParent>(parent_lo);
+  arrived<kAskedParent + 1>(parent_hi);
+  dropped<kAskedLength>(L_one);
   if (lane >= T) parent_lo = -1;
   if (lane + 64 >= T) parent_hi = -1;
   // the sets are published by the barrier in front of the first tile
