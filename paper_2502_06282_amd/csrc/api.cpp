@@ -784,7 +784,7 @@ jk_status jk_draft_heads(const jk_draft_heads_desc* desc, const void* f_top, con
   if (d.rows > 128 || d.d_model < 128 || d.d_model > 16384 || d.d_model % 128 || d.top_k > 16) return JK_ERR_UNSUPPORTED;
   if ((long long)2 * d.rows * d.vocab > 0x7fffffffLL * 4) return JK_ERR_UNSUPPORTED;
   if (d.vocab > (1 << 24)) return JK_ERR_UNSUPPORTED;
-  const size_t need = draft_heads_workspace_bytes(d.rows, d.d_model, d.vocab);
+  const size_t need = draft_heads_least_bytes(d.rows, d.d_model, d.vocab);
   if (!workspace || reinterpret_cast<uintptr_t>(workspace) % 256 || workspace_bytes < need) return JK_ERR_WORKSPACE;
   DraftHeadsArgs a;
   a.rows = d.rows; a.d_model = d.d_model; a.vocab = d.vocab; a.top_k = d.top_k; a.mode = d.mode;
@@ -792,6 +792,7 @@ jk_status jk_draft_heads(const jk_draft_heads_desc* desc, const void* f_top, con
   a.f_top = f_top; a.w_head = w_head; a.s_top = s_top;
   a.logits = logits; a.draft_probs = draft_probs; a.topk_probs = topk_probs; a.topk_tokens = topk_tokens;
   a.workspace = workspace;
+  a.workspace_bytes = workspace_bytes;
   return launch_draft_heads(a, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? JK_OK : JK_ERR_HIP;
 }
 

@@ -911,10 +911,12 @@ int capped_ksplit(int m, int n, int k, int split_ns, double* ns = nullptr) {
 struct RowPlan {
   bool ring, stats;  // stats: the product leaves the rows' statistics (row_stats_kernel)
   int per_thread, parts, part_len, ksplit;
-  size_t x_bytes, ms_off, key_off, part_off, total;
+  size_t ms_off, key_off, part_off;
+  size_t total, most;  // bytes that the call needs, and all that it has a use for
 };
 
-RowPlan row_plan(int rows, int d_model, int vocab) {
+// `bytes`: of the workspace
+RowPlan row_plan(int rows, int d_model, int vocab, size_t bytes) {
   RowPlan r;
   const size_t m = 2 * (size_t)rows;
   // Short parts spread a few rows over the CUs; with many rows long ones keep the grid at one turn of eight workgroups
@@ -926,8 +928,7 @@ RowPlan row_plan(int rows, int d_model, int vocab) {
   r.parts = (vocab + kPartThreads * r.per_thread - 1) / (kPartThreads * r.per_thread);
   r.part_len = ((vocab + r.parts - 1) / r.parts + 3) / 4 * 4;
   auto up = [](size_t v) { return (v + 255) / 256 * 256; };
-  r.x_bytes = up(m * (size_t)d_model * 2);
-  r.ms_off = r.x_bytes;
+  r.ms_off = up(m * (size_t)d_model * 2);
   r.key_off = r.ms_off + up(m * r.parts * 2 * 4);
   r.part_off = r.key_off + up(m * r.parts * kMaxTopK * 8);
   r.ring = ring_gemm_takes_heads((int)m, vocab);
@@ -938,18 +939,23 @@ RowPlan row_plan(int rows, int d_model, int vocab) {
   // of 128256 x 4096 189.5 / 186.9, 40 of 32000 x 4096 57.8 / 54.6, of 60000 x 1024 40.8 / 38.7, 64 of 128256 x 4096 221 / 218, 2 of 30000 x 512 16.7 /
   // 14.5; short rows, 64 of 32000 x 4096 61.7 / 61.3, of 20000 x 1024 22.6 / 22.3, 40 of 16384 x 4096 35.7 / 35.7.  The distributions' distance from
   // those in 64 bits of the same logits, mean of 480 - 768 rows: 0.94 - 0.995 times what it was in seven shapes at temperatures of 0.3 - 2.5.
-  r.stats = !r.ring && r.ksplit == 1 && m <= 64;
-  if (r.stats) r.total = r.ms_off + up(m * ((vocab + kStatColumns - 1) / kStatColumns) * 8);
+  // They are more bytes than the parts of 4096 entries and their candidates where d_model is small; a workspace that holds those only still
+  // serves the call, in the two launches.
+  const size_t stat_bytes = up(m * ((vocab + kStatColumns - 1) / kStatColumns) * 8);
+  const bool can = !r.ring && r.ksplit == 1 && m <= 64;
+  r.stats = can && stat_bytes <= bytes;
+  r.most = can && stat_bytes > r.total ? stat_bytes : r.total;
   return r;
 }
 
 }  // namespace
 
-size_t draft_heads_workspace_bytes(int rows, int d_model, int vocab) { return row_plan(rows, d_model, vocab).total; }
+size_t draft_heads_workspace_bytes(int rows, int d_model, int vocab) { return row_plan(rows, d_model, vocab, 0).most; }
+size_t draft_heads_least_bytes(int rows, int d_model, int vocab) { return row_plan(rows, d_model, vocab, 0).total; }
 
 hipError_t launch_draft_heads(const DraftHeadsArgs& a, hipStream_t stream) {
   const int m = 2 * a.rows;
-  const RowPlan rp = row_plan(a.rows, a.d_model, a.vocab);
+  const RowPlan rp = row_plan(a.rows, a.d_model, a.vocab, a.workspace_bytes);
   char* ws = static_cast<char*>(a.workspace);
   MixParams mp;
   mp.f_top = static_cast<const unsigned short*>(a.f_top);
@@ -969,7 +975,7 @@ hipError_t launch_draft_heads(const DraftHeadsArgs& a, hipStream_t stream) {
   g.m = m; g.n = a.vocab; g.k = a.d_model;
   g.ksplit = rp.ksplit; g.y_split = (long long)m * a.vocab; g.batch = 1;
   g.s_top = a.s_top; g.heads_mode = a.mode; g.alpha = a.alpha; g.beta = a.beta;
-  g.stats = rp.stats ? reinterpret_cast<float2*>(ws + rp.ms_off) : nullptr;
+  g.stats = rp.stats ? reinterpret_cast<float2*>(ws) : nullptr;  // (nothing else is in the workspace then)
   // (1 / T below the largest float has its log2(e)-fold beyond it from T = 4.24e-39 downwards: then the first part is the largest float, and
   // the second what is left, a number too.  An infinite one made rows none by zero times it.)
   const double scale = (double)(1.0f / a.temperature) * 1.4426950408889634;

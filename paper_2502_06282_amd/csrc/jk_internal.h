@@ -230,8 +230,10 @@ struct DraftHeadsArgs {
   float *logits, *draft_probs, *topk_probs;
   int32_t* topk_tokens;
   void* workspace;
+  size_t workspace_bytes;
 };
 size_t draft_heads_workspace_bytes(int rows, int d_model, int vocab);
+size_t draft_heads_least_bytes(int rows, int d_model, int vocab);  // without which a call is refused
 hipError_t launch_draft_heads(const DraftHeadsArgs& a, hipStream_t stream);
 
 // router + expert MLPs of the draft layer

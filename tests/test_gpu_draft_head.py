@@ -339,3 +339,31 @@ def test_smallest_temperatures(temperature):
     e = np.exp((lg.astype(np.float64) - 8 * 2.0 ** -126) * np.float64(np.float32(1.0) / np.float32(temperature)))
     np.testing.assert_allclose(q, e / e.sum(-1, keepdims=True), rtol=3e-5)
     np.testing.assert_allclose(tp, np.take_along_axis(q, tk.astype(np.int64), axis=-1), rtol=1e-6)
+
+
+@pytest.mark.parametrize("rows,d,vocab,least", [(32, 128, 97144, 225280), (21, 512, 105552, 191744), (10, 4096, 128256, 335360), (3, 128, 1000, 2560)])
+def test_the_least_workspace_serves_the_call(rows, d, vocab, least):
+    """What the parts and their candidates take is enough, also where the statistics of the rows' blocks are more bytes; less is refused."""
+    tune("ring_gemm", 0)
+    g = torch.Generator(device="cuda").manual_seed(vocab)
+    f = torch.randn((rows, 2, d), device="cuda", dtype=torch.bfloat16, generator=g)
+    s = torch.rand((rows, 2), device="cuda", generator=g)
+    w = torch.randn((vocab, d), device="cuda", dtype=torch.bfloat16, generator=g) * 5 * d ** -0.5
+
+    def call(nbytes, guard=1024):
+        room = torch.full((nbytes + guard,), 0xA5, dtype=torch.uint8, device="cuda")
+        out = (torch.empty((rows, 2, vocab), device="cuda"), torch.empty((rows, 2, vocab), device="cuda"),
+               torch.empty((rows, 2, 7), dtype=torch.int32, device="cuda"), torch.empty((rows, 2, 7), device="cuda"))
+        jk.prepare_draft_heads(f, s, w, jk.JK_HEADS_DECOUPLED, 0.9, 7, 0.0, 0.0, *out, room[:nbytes]).launch()
+        torch.cuda.synchronize()
+        assert bool((room[nbytes:] == 0xA5).all())
+        return out
+
+    full = call(jk.draft_heads_workspace(rows, d, vocab))
+    lg, q, tk, tp = call(least)
+    assert torch.equal(lg, full[0]) and torch.equal(tk, full[2])
+    torch.testing.assert_close(q, full[1], rtol=3e-5, atol=1e-30)
+    torch.testing.assert_close(tp, full[3], rtol=3e-5, atol=1e-30)
+    np.testing.assert_allclose(q.cpu().numpy(), dh.draft_distribution(lg.cpu().numpy(), 0.9), rtol=3e-5, atol=1e-30)
+    with pytest.raises(jk.JakiroError):
+        call(least - 256)
