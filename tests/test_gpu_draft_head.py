@@ -76,11 +76,27 @@ def test_random_inputs_every_row_block_count(rows):
 
 @pytest.mark.parametrize("rows,vocab,top_k", [(1, 1024, 16), (1, 1025, 2), (2, 5, 4), (1, 70003, 12), (66, 16388, 10),
                                               (66, 16385, 10), (70, 33001, 5), (70, 40000, 16)])
-def test_rows_cut_into_parts_of_every_length(rows, vocab, top_k):
-    """4, 8 and 16 entries a thread (by the number of rows and the vocabulary), whole and ragged last parts, rows that
-    start at multiples of 16 bytes and not, equal logits in several parts."""
+def test_rows_of_every_length(rows, vocab, top_k):
+    """Rows from blocks' statistics, whole and cut into parts (by the number of rows and the vocabulary), rows that start at multiples of
+    16 bytes and not, equal logits far from each other."""
     _check(draft_head_inputs(rows, 128, vocab, seed=vocab), top_k=top_k)
     _check(_exact_inputs(rows, 128, vocab, vocab), top_k=top_k, exact=True)
+
+
+@pytest.mark.parametrize("forced,rows,vocab,top_k", [(1, 16, 33000, 16), (1, 2, 32772, 3), (1, 16, 49151, 11),              # 4 entries a thread
+                                                     (-1, 33, 32769, 16), (-1, 40, 40000, 10), (-1, 60, 32772, 5),          # 8
+                                                     (-1, 70, 33001, 5), (-1, 70, 40000, 16), (-1, 128, 32769, 12)])        # 16
+def test_rows_cut_into_parts_of_every_length(forced, rows, vocab, top_k):
+    """Calls whose product leaves no statistics (equal shares of the vocabulary, or more than 32 tokens), of rows too long to be taken whole:
+    4, 8 and 16 entries a thread, whole and ragged last parts; then equal logits, more candidates than any list holds."""
+    tune("ring_gemm", forced)
+    _check(draft_head_inputs(rows, 128, vocab, seed=vocab), top_k=top_k)
+    x = _exact_inputs(rows, 128, vocab, vocab)
+    _check(x, top_k=top_k, temperature=0.8, exact=True)
+    x["w_head"][:] = x["w_head"][0]
+    lg, q, tk, tp = _check(x, top_k=top_k, exact=True)
+    np.testing.assert_array_equal(tk, np.broadcast_to(np.arange(top_k), tk.shape))
+    np.testing.assert_allclose(q, 1.0 / vocab, rtol=3e-5)
 
 
 def test_widest_model_and_longest_candidate_lists():
@@ -266,10 +282,12 @@ def test_either_kernel_takes_the_heads(forced, rows, d, vocab):
 
 @pytest.mark.parametrize("rows,d,vocab", [(1, 128, 5), (3, 128, 4096), (2, 128, 4097), (9, 4096, 300), (5, 128, 8192), (3, 128, 8193), (4, 1024, 12290),
                                           (1, 128, 12288), (2, 128, 16383), (33, 128, 16384), (31, 128, 16385), (32, 128, 16385), (32, 128, 20481),
-                                          (33, 128, 24576), (32, 128, 28700), (34, 128, 32768), (32, 128, 32769)])
-def test_short_rows_are_taken_whole(rows, d, vocab):
-    """The edges of what a thread holds, one entry more than a workgroup takes, and where longer rows change ways; then rows of
-    equal logits, all of them candidates (exact sums: 1 / vocab within the tolerance of every probability here)."""
+                                          (33, 128, 24576), (32, 128, 28700), (34, 128, 32768), (32, 128, 32769), (33, 128, 5), (33, 128, 4096), (40, 128, 4097),
+                                          (33, 128, 8193), (40, 128, 12290), (33, 128, 16385), (64, 128, 20481), (33, 128, 28672), (33, 128, 28673), (40, 128, 32767)])
+def test_short_rows(rows, d, vocab):
+    """Of more than 32 tokens, short rows are taken whole: the edges of what a thread holds, and the most that a workgroup takes.  Of fewer
+    the same lengths from blocks' statistics.  Then rows of equal logits, all of them candidates (exact sums: 1 / vocab within
+    the tolerance of every probability here)."""
     top_k = min(vocab, 11)
     x = _exact_inputs(rows, d, vocab, vocab)
     _check(x, top_k=top_k, temperature=0.8, exact=True)
@@ -367,3 +385,35 @@ def test_the_least_workspace_serves_the_call(rows, d, vocab, least):
     np.testing.assert_allclose(q.cpu().numpy(), dh.draft_distribution(lg.cpu().numpy(), 0.9), rtol=3e-5, atol=1e-30)
     with pytest.raises(jk.JakiroError):
         call(least - 256)
+
+
+@pytest.mark.parametrize("vocab", [5, 300, 16385, 33000])
+@pytest.mark.parametrize("rows", [1, 9, 32])
+def test_statistics_of_rows_that_are_no_numbers(rows, vocab):
+    """A NaN anywhere in a row, a block of nothing else and +inf make the whole distribution none, as the softmax of the same logits does; other
+    rows stay what they are, and candidates are entries of the vocabulary."""
+    tune("ring_gemm", 0)
+    top_k = min(vocab, 8)
+
+    def in_range(tk):
+        assert ((tk >= 0) & (tk < vocab)).all()
+
+    for first, n in ((vocab // 2, 1), (vocab // 128 // 2 * 128, 128)):   # an entry; a block
+        x = _exact_inputs(rows, 128, vocab, vocab)
+        x["w_head"][first:first + n] = np.nan
+        lg, q, tk, tp = _call(x, top_k=top_k)
+        assert np.isnan(lg[:, :, first:first + n]).all() and np.isnan(q).all()
+        in_range(tk)
+    x = _exact_inputs(rows, 128, vocab, vocab)
+    x["f_top"][:, :, 7] = 0.0
+    good = _call(x, top_k=top_k)
+    for column, low in ((1.0, -1.0), (0.0, -1.0), (0.0, 0.5)):   # +inf and -inf; NaN and -inf; NaN and +inf
+        x["w_head"][:, 7] = low
+        x["w_head"][vocab // 3, 7] = column
+        x["f_top"][0, 0, 7] = np.inf
+        lg, q, tk, tp = _call(x, top_k=top_k)
+        assert not np.isfinite(lg[0, 0]).any() and np.isnan(q[0, 0]).all()
+        in_range(tk)
+        for got, ref in zip((lg, q, tk, tp), good):
+            np.testing.assert_array_equal(got[0, 1], ref[0, 1])
+            np.testing.assert_array_equal(got[1:], ref[1:])

@@ -51,14 +51,16 @@ def test_paged_attention_matches_oracle_and_contiguous(monkeypatch, wm, wn, page
 
 @pytest.mark.parametrize("wm,wn", [(2, 2), (4, 1), (8, 1)], ids=["2x2", "4x1", "8x1"])
 @pytest.mark.parametrize("plen", [(9001, 8300), (9001, 9001), (33, 9001)], ids=["ragged", "equal", "swapped"])
-def test_paged_batch_with_more_pages_than_threads(wm, wn, plen):
-    """A batch's page ids are asked for before its lengths are there, a thread's first one at once and what lies past 256 of
-    them in turn; lengths that differ have the list made again.  Bitwise equal to the contiguous call."""
+@pytest.mark.parametrize("Hkv", [8, 2])
+def test_paged_batch_with_more_pages_than_threads(Hkv, wm, wn, plen):
+    """Page ids come a thread's first one at once, and what lies past 256 of them in turn.  A batch whose KV heads are a multiple of
+    eight together asks for them when its lengths are there; another one (arrangements of up to 128 rows), as if all had the bound's
+    length, and those below it make their list again, here of more than 256 too.  Bitwise equal to the contiguous call."""
     tune("attn_wm", str(wm))
     tune("attn_wn", str(wn))
     tune("attn_splits", "1")
     g = torch.Generator(device="cuda").manual_seed(sum(plen))
-    B, T, H, Hkv, D, L, page = 2, 40, 32, 8, 128, max(plen), 32
+    B, T, H, D, L, page = 2, 40, 4 * Hkv, 128, max(plen), 32
     par = torch.from_numpy(np.stack([tree_for_config(CONFIGS["c3_llama3_8b"].with_(n_tree=T), seed=b)[0] for b in range(B)])).cuda()
     blocks = -(-L // page)
     rand = lambda *s: torch.randn(s, device="cuda", generator=g).to(BF)
