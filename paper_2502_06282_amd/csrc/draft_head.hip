@@ -7,8 +7,9 @@
 // Kernels:
 //   head_inputs_kernel     X[2R, d] bf16 from f_top, s_top (elementwise; more than 32 tokens:
 //                          of fewer the product makes its rows itself)
-//   row_parts_kernel, row_finish_kernel   per logits row: maximum, normaliser,
-//                          top-k by value (ties to the lower token id), probabilities.
+//   row_stats_kernel; row_whole_kernel; row_parts_kernel, row_finish_kernel   per logits row: maximum, normaliser,
+//                          top-k by value (ties to the lower token id), probabilities: with the
+//                          product's statistics, of short rows, of longer ones.
 //   router_kernel, gated_act_kernel, select_kernel   the draft layer's router (Eq. 2, 5) and what
 //                          surrounds the experts' three projections (Eq. 3).
 // The products with weight matrices run in stream_gemm.hip and ring_gemm.hip.

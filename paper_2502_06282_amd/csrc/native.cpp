@@ -766,7 +766,7 @@ bool ordinary(const at::Tensor& t) {
   return t.key_set() == plain && c10::impl::tls_local_dispatch_key_set().included_.add(c10::DispatchKey::ADInplaceOrView) == c10::default_included_set &&
          !at::impl::torch_function_mode_enabled() && !c10::impl::TorchDispatchModeTLS::any_modes_set() && !at::hasCallbacks();
 }
-// n_nodes -> whether it was cleared here, as zero_ would have.  (zero_ takes 4.0 us of a thread, this 3.05.)
+// n_nodes -> whether it was cleared here, as zero_ would have.  (zero_ takes 3.6 us of a thread, TreeState.reset with this 2.8.)
 PyObject* tree_reset(Args& a) {
   PyObject* o = a.next();
   bool plain = THPVariable_CheckExact(o);

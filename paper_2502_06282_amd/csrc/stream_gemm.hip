@@ -101,10 +101,14 @@ struct Weights {
   // Workgroups start at different chunks and wrap around: rows often lie a power of two apart, so that workgroups in
   // step would all ask the same few memory channels (16 x 4096 x 4096: 115 us in step, 98 us like this; 32000 x 4096:
   // 58 and 46).  Workgroups run on the eight XCDs in turn, so the start has to vary within every eighth of them too: by seven
-  // chunks from one to the next and by eight from XCD to XCD where a row has 16 chunks of 256 or more, else by one and five.  Of 28 pairs of steps,
-  // five and nine / eight and seven, kernels of a call, us: 20 rows, 128256 x 4096 195 / 190, 80, 32000 x 4096 69.3 / 68.6, 40, 64000 x
+  // chunks from one to the next and by eight from XCD to XCD where a row has 16 chunks of 256 or more, else by 41 and five (5 wg + wg / 8).  Of 28 pairs of
+  // steps, 41 and five / seven and eight, kernels of a call, us: 20 rows, 128256 x 4096 195 / 190, 80, 32000 x 4096 69.3 / 68.6, 40, 64000 x
   // 8192 196 / 193, eight experts of 4096 x 4096 148.8 / 144.7; in eight chunks the other way round, 64000 x 2048 1 : 0.985, experts of 2048 x
-  // 8192 1 : 0.976; chunks of 128 (more than 128 rows) either, 160 rows of 83155 x 3968 221.4 / 226, of 32000 x 4096 88.7 / 86.5.  (A half chunk at the end stays last.)
+  // 8192 1 : 0.976.  Seven divides the chunks of k = 7168 and 14336, whose workgroups of an XCD then share four and eight places to start
+  // with seven, and have 28 and 32 with 41: the calls are the same to 0.8 %, or faster with seven (40 rows, four experts of 7168 x 4096 134.7 /
+  // 133.7, of 4096 x 14336 252.0 / 252.1, eight of 7168 x 2048 138.1 / 137.0; heads of 64 rows, 20000 x 7168 87.4 / 86.9, of 40, 64000 x 7168 182.5 /
+  // 182.5, of 60, 100000 x 7168 349.5 / 350.6).  Chunks of 128 (more than 128 rows, wide strips) went both ways, 160 rows of 83155 x 3968 221.4 / 226, of 32000 x
+  // 4096 88.7 / 86.5, and keep 41 and five, with which none of them lost.  (A half chunk at the end stays last.)
   template <int KC>
   __device__ __forceinline__ int chunk(int c) const {
     const int whole = (k1 - k0) / KC;
@@ -387,7 +391,7 @@ __global__ __launch_bounds__(kThreads, 2) void stream_gemm_kernel(const uint16_t
   const int n_base = KIND == PAIR ? ((int)blockIdx.x * 4 + (wave & 3)) * 16 * NF : ((int)blockIdx.x * 8 + wave) * 16 * NF;
   Weights<NF, KIND> w;
   w.start(p, strips, n_base, e, wave, lane & 15, lane >> 4);
-  // (chunks have the same order whatever their number of rows: KC is 256 in all of a kernel's variants)
+  // (an expert's chunks have the same order whatever its number of rows, at most 128: KC is 256 in all of those variants)
   constexpr int KC = Cfg<MT, NF>::KC;
   const int first = w.template chunk<KC>(0);
 #pragma unroll
