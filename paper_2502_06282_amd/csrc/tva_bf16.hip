@@ -741,11 +741,7 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
   const int rest = divide(wid, mg_qtiles, n_qtiles);
   const int qtile = wid - rest * n_qtiles;
   const int unit = divide(rest, mg_splits, splits);  // b * Hkv + kv in the order of the batch
-  if (unit >= batch * n_kv_heads) {  // padding workgroup
-    dev::wait_vm<0>();
-    dropped<kAskedLengths>(lengths);
-    return;
-  }
+  if (unit >= batch * n_kv_heads) return;    // padding workgroup (a wave's end waits for what it has asked for)
   const int split = rest - unit * splits;
   int place = unit;  // rank * Hkv + kv
   if (ranked) {
