@@ -33,9 +33,9 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 # rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs (KiB per dispatch), each scaled by the same counter's reading
 # for a 256 MiB device copy (factors 2.00 and 1.00); source: profiles/<workload>_attention_and_acceptance.md.
 # {workload: bytes}; None for workloads that were not measured.
-MEASURED_TRAFFIC = {"c2_vicuna7b": 24775626, "c3_llama3_8b": 34335950, "c4_llama2_13b": 207925267,
-                    "c5_llama2_70b": 635375944, "c6_chain_sps": 273279528,
-                    "c7_static_tree": 78230030}
+MEASURED_TRAFFIC = {"c2_vicuna7b": 24777432, "c3_llama3_8b": 34335691, "c4_llama2_13b": 207921983,
+                    "c5_llama2_70b": 635362049, "c6_chain_sps": 273273308,
+                    "c7_static_tree": 78228316}
 
 
 def attn_bytes(cfg) -> int:
