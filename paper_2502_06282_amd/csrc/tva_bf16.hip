@@ -901,10 +901,12 @@ __global__ __launch_bounds__((Plan<D, WM, WN, KT, PAGED, DEEP>::THREADS), (Plan<
   // ---- the first rounds.  (A ranked batch has its lengths by now.  Asked for as if all of them equalled the bound, which is seldom
   // so, the first rounds had to land before the right ones took their places.  us, so / like this: 8 sequences of up to 2048
   // keys, five nodes (8B shapes) 17.2 / 16.1, 12 of up to 900, 24 nodes 19.7 / 17.4, 4 of up to 2000, 60 nodes 22.2 / 20.8.  Lengths that do all
-  // equal the bound pay for it where nothing else in the call got shorter.  Whole calls with the shorter start and merge that came with it, lengths equal, and
-  // in brackets ragged: 13 of 2519 keys, 12 nodes, 40 KV heads 137.5 / 139.5 (97.5 / 93.5), 16 of 123, 115 nodes, 40 KV heads 33.7 / 34.3
-  // (33.8 / 31.6), 4 of 2048, 60 nodes, 40 KV heads 42.5 / 42.9 (43.0 / 41.7), 5 of 1296, 43 nodes, heads of 64 10.9 / 11.0 (11.0 / 10.4);
-  // forty equal batches together 1.016 times as fast, 0.981 to 1.08.)
+  // equal the bound can lose: in a grid of several turns the lengths come through a busy CU's memory queue, and the later workgroups have their
+  // first tiles 4.7 us after their start, 4.1 before; in one turn the first tiles come earlier, 4.6 instead of 4.9, but all at once, and c4's loop, bound
+  // by HBM, takes 26.3 instead of 25.7.  Whole calls with the shorter start and merge that came with it, lengths equal, and in brackets
+  // ragged: 13 of 2519 keys, 12 nodes, 40 KV heads 137.5 / 139.5 (97.5 / 93.5), 16 of 123, 115 nodes, 40 KV heads 33.7 / 34.3 (33.8 / 31.6), 4 of
+  // 2048, 60 nodes, 40 KV heads 42.5 / 42.9 (43.0 / 41.7), 5 of 1296, 43 nodes, heads of 64 10.9 / 11.0 (11.0 / 10.4); forty equal batches
+  // together 1.016 times as fast, 0.981 to 1.08.)
   int n_spec = 0;  // rounds already issued, all of them full prefix tiles under the assumption
 #pragma unroll
   for (int r = 0; r < NR - 1; ++r)
